@@ -68,6 +68,9 @@ wersa_status forward_checked(const wersa_desc *desc, const void *q, const void *
     return fast_forward(*desc, q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, out, (float *)saved,
                         (float *)workspace, (hipStream_t)hip_stream, pooled);
   }
+  if (use_split(*desc))
+    return split_forward(*desc, q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, out, (float *)saved, (float *)workspace,
+                         (hipStream_t)hip_stream);
   return generic_forward(*desc, q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, out, (float *)saved,
                          (float *)workspace, (hipStream_t)hip_stream);
 }
@@ -80,8 +83,9 @@ extern "C" {
 
 size_t wersa_workspace_bytes(const wersa_desc *desc, int for_backward) {
   if (validate_desc(desc) != WERSA_OK) return 0;
-  return use_fast(*desc) ? fast_workspace_bytes(*desc, for_backward)
-                         : generic_workspace_bytes(*desc, for_backward);
+  return use_fast(*desc)    ? fast_workspace_bytes(*desc, for_backward)
+         : use_split(*desc) ? split_workspace_bytes(*desc, for_backward)
+                            : generic_workspace_bytes(*desc, for_backward);
 }
 
 size_t wersa_saved_bytes(const wersa_desc *desc) {
@@ -155,6 +159,9 @@ wersa_status wersa_backward(const wersa_desc *desc, const void *q, const void *k
                          (const float *)saved, dq, dk, dv, dgate_w, dgate_b, dscale_w, dsigma,
                          (float *)workspace, (hipStream_t)hip_stream);
   }
+  if (use_split(*desc))
+    return split_backward(*desc, q, k, v, gate_w, scale_w, out, dout, (const float *)saved, dq, dk, dv, dgate_w, dgate_b,
+                          dscale_w, dsigma, (float *)workspace, (hipStream_t)hip_stream);
   return generic_backward(*desc, q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, out, dout,
                           (const float *)saved, dq, dk, dv, dgate_w, dgate_b, dscale_w, dsigma,
                           (float *)workspace, (hipStream_t)hip_stream);

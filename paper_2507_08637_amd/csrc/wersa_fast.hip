@@ -20,6 +20,7 @@ namespace wersa {
 namespace {
 
 #include "wersa_small_kernels.inc"
+#include "wersa_filter.inc"
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -356,43 +357,6 @@ __global__ __launch_bounds__(256) void qbar_partial_kernel(const bf16_t *q, View
   }
   if (amax_part && threadIdx.x == 0)
     amax_part[(int64_t)slice * chunks + chunk] = fmaxf(fmaxf(amax_w[0], amax_w[1]), fmaxf(amax_w[2], amax_w[3]));
-}
-
-// ------------------------------------------------------------------------------------
-// Gated Haar filter in block-mean form on one column, RS consecutive rows held by a thread.
-//   bs_l = sum over the aligned 2^l block;  out = sum_l coef_l * bs_l
-// `upper` is sum_{l > log2 RS} coef_l * bs_l for the blocks that contain this segment.
-// ------------------------------------------------------------------------------------
-template <int RS>
-__device__ __forceinline__ void filter_segment(float (&v)[RS], const float *coef, float upper) {
-  constexpr int LV = RS == 32 ? 5 : 4;
-  static_assert(RS == 16 || RS == 32, "segment of 16 or 32 rows");
-  float bs[LV + 1][RS];
-#pragma unroll
-  for (int i = 0; i < RS; ++i) bs[0][i] = v[i];
-#pragma unroll
-  for (int l = 1; l <= LV; ++l)
-#pragma unroll
-    for (int k = 0; k < (RS >> l); ++k) bs[l][k] = bs[l - 1][2 * k] + bs[l - 1][2 * k + 1];
-  float T[LV + 1][RS];
-  T[LV][0] = fmaf(coef[LV], bs[LV][0], upper);
-#pragma unroll
-  for (int l = LV - 1; l >= 0; --l)
-#pragma unroll
-    for (int k = 0; k < (RS >> l); ++k) T[l][k] = fmaf(coef[l], bs[l][k], T[l + 1][k >> 1]);
-#pragma unroll
-  for (int i = 0; i < RS; ++i) v[i] = T[0][i];
-}
-template <int RS>
-__device__ __forceinline__ float segment_sum(const float (&v)[RS]) {
-  float s[RS];
-#pragma unroll
-  for (int i = 0; i < RS; ++i) s[i] = v[i];
-#pragma unroll
-  for (int w = RS / 2; w >= 1; w >>= 1)
-#pragma unroll
-    for (int k = 0; k < w; ++k) s[k] = s[2 * k] + s[2 * k + 1];
-  return s[0];
 }
 
 // X (bf16, strided) -> X_F (fp16, contiguous [slices][n][DH]); one 64-row tile per workgroup.
@@ -1834,51 +1798,6 @@ __global__ __launch_bounds__(256) void add_pooled_kernel(bf16_t *dq, View v, con
     }
   }
 }
-
-// ------------------------------------------------------------------------------------
-// Transforms deeper than one 64-row block (L > 6).  In block-mean form the
-// levels above 6 add, to every row of a tile, coef_l times the sum of X over the 2^l-row block
-// that holds the tile: a per-(tile, column) addend built from the tile sums.
-// Pyramid of one signal: level j (1 .. J) holds the sums over 2^j consecutive tiles,
-// [ceil(ntiles / 2^j)][d], levels packed one after the other in P (< ntiles + J rows).
-// d / 16 workgroups of 1024 threads per signal, one per 16 columns; thread (column c = tid % 16 of
-// its 16, group g = tid / 16 of kCoarseGroups); the loops over tiles carry no dependency and
-// are unrolled so that several loads are in flight.
-// ------------------------------------------------------------------------------------
-constexpr int kCoarseGroups = 64, kCoarseCols = 16;   // (the gradient rows kernel leaves d / 16 extra rows in its band partials)
-__device__ __forceinline__ void build_tile_pyramid(const float *T, int ntiles, int d, int J, float *P, int c, int g) {
-  const float *prev = T;
-  int nprev = ntiles;
-  float *cur = P;
-  for (int j = 1; j <= J; ++j) {
-    const int nb = (nprev + 1) / 2;
-#pragma unroll 4
-    for (int b = g; b < nb; b += kCoarseGroups)
-      cur[b * d + c] = prev[2 * b * d + c] + (2 * b + 1 < nprev ? prev[(2 * b + 1) * d + c] : 0.f);
-    __threadfence_block();
-    __syncthreads();
-    prev = cur;
-    nprev = nb;
-    cur += nb * d;
-  }
-}
-// addend[tile][c] = sum over j of coef[6 + j] * P_j[tile >> j][c]
-__device__ __forceinline__ void tile_addend(const float *P, const float *coef, int ntiles, int d, int J, float *A, int c, int g) {
-#pragma unroll 4
-  for (int tile = g; tile < ntiles; tile += kCoarseGroups) {
-    float acc = 0.f;
-    const float *lvl = P;
-    int nprev = ntiles;
-    for (int j = 1; j <= J; ++j) {
-      const int nb = (nprev + 1) / 2;
-      acc = fmaf(coef[6 + j], lvl[(tile >> j) * d + c], acc);
-      lvl += nb * d;
-      nprev = nb;
-    }
-    A[tile * d + c] = acc;
-  }
-}
-constexpr int64_t pyramid_floats(int ntiles, int d) { return ((int64_t)ntiles + 32) * d; }
 
 // Forward: blockIdx.y = 0 for Q, 1 for K; blockIdx.z = group of 16 columns.  T*: tile sums
 // [S][ntiles][d]; A*: addends, same shape; pyr: 2 * S pyramids of pyramid_floats(ntiles, d).

@@ -1,6 +1,7 @@
 // Generic WERSA path: float32 arithmetic for every storage dtype, one kernel per step of
-// Section 3.1 (steps 3-8), staged through caller workspace.  It covers the whole supported
-// range and is the float32 product path.  Reductions are fixed-order two-pass sums.
+// Section 3.1 (steps 3-8), staged through caller workspace.  It runs head dimensions above 128 (below, the
+// same arithmetic without the n x m arrays in memory is wersa_split.hip) and the filter as a stage of its
+// own where the streaming kernel does not take it.  Reductions are fixed-order two-pass sums.
 #include "wersa_internal.h"
 
 namespace wersa {

@@ -51,6 +51,14 @@ inline bool use_fast(const wersa_desc &c) {
   return !(c.flags & WERSA_FLAG_GENERIC_PATH) && fast_supported(c);
 }
 
+// Split path (float32 arithmetic on the bf16 matrix cores): what the MFMA path does not take, head
+// dimensions up to 128.
+inline bool use_split(const wersa_desc &c) { return !use_fast(c) && c.d <= 128; }
+struct SplitSizes {
+  int64_t X, OA, OB, SA;   // floats: packed Q_F or K_F, Omega both ways, S with its features as vectors
+};
+SplitSizes split_sizes(const wersa_desc &c);
+
 struct SavedLayout {
   int64_t S, z, qbar, s, F, D, QF, KF, total;
   // MFMA path only: per-call constants and bf16 operand copies written by the forward and
@@ -59,6 +67,9 @@ struct SavedLayout {
   // MFMA path with L > 6: sums of Q and K over 64-row tiles [S][n/64][d] and the per-tile
   // addends of the levels above 6 (same shape), kept for the backward.
   int64_t tileQ, tileK, addQ, addK;
+  // Split path only: the operands of the contractions that the backward uses again (with scalars, coef and, for
+  // L > 6, the tile sums and addends above).
+  int64_t XQ, XK, OA, OB, SA;
 };
 inline SavedLayout saved_layout(const wersa_desc &c) {
   SavedLayout o;
@@ -93,6 +104,24 @@ inline SavedLayout saved_layout(const wersa_desc &c) {
       o.addK = off;  off += up(tiles);
     }
   }
+  o.XQ = o.XK = o.OA = o.OB = o.SA = -1;
+  if (use_split(c)) {
+    const SplitSizes z = split_sizes(c);
+    o.scalars = off; off += 64;
+    o.coef = off;    off += up(sl * kCoefStride);
+    o.XQ = off;      off += up(z.X);
+    o.XK = off;      off += up(z.X);
+    o.OA = off;      off += up(z.OA);
+    o.OB = off;      off += up(z.OB);
+    o.SA = off;      off += up(z.SA);
+    if (c.L > kTileL) {
+      const int64_t tiles = sl * ((c.n + 63) / 64) * c.d;
+      o.tileQ = off; off += up(tiles);
+      o.tileK = off; off += up(tiles);
+      o.addQ = off;  off += up(tiles);
+      o.addK = off;  off += up(tiles);
+    }
+  }
   o.total = off;
   return o;
 }
@@ -111,9 +140,7 @@ void prof_end(hipStream_t st);
     ::wersa::prof_end(st);           \
   } while (0)
 
-// Generic path: float32 arithmetic for every dtype, staged through workspace. Correct for
-// the whole supported range; it is the float32 product path and the fallback for bf16 shapes
-// the MFMA path does not cover.
+// Generic path: float32 arithmetic for every dtype, staged through workspace: head dimensions above 128.
 size_t generic_workspace_bytes(const wersa_desc &c, int for_backward);
 wersa_status generic_forward(const wersa_desc &c, const void *q, const void *k, const void *v,
                              const void *omega_rf, const float *sigma, const float *gate_w,
@@ -125,6 +152,14 @@ wersa_status generic_backward(const wersa_desc &c, const void *q, const void *k,
                               const void *dout, const float *saved, void *dq, void *dk, void *dv,
                               float *dgate_w, float *dgate_b, float *dscale_w, float *dsigma,
                               float *ws, hipStream_t st);
+size_t split_workspace_bytes(const wersa_desc &c, int for_backward);
+wersa_status split_forward(const wersa_desc &c, const void *q, const void *k, const void *v, const void *omega_rf,
+                           const float *sigma, const float *gate_w, const float *gate_b, const float *scale_w, void *out,
+                           float *saved, float *ws, hipStream_t st);
+wersa_status split_backward(const wersa_desc &c, const void *q, const void *k, const void *v, const float *gate_w,
+                            const float *scale_w, const void *out, const void *dout, const float *saved, void *dq, void *dk,
+                            void *dv, float *dgate_w, float *dgate_b, float *dscale_w, float *dsigma, float *ws,
+                            hipStream_t st);
 size_t fast_workspace_bytes(const wersa_desc &c, int for_backward);
 // Column sums of Q over 128-row blocks computed by the caller (the attention block's W^Q GEMM
 // leaves them in its epilogue): sums[row block of (B*n)/128][H*d], float32.  When given to the

@@ -1,0 +1,1523 @@
+// Split path: float32 arithmetic on the bf16 matrix cores, the n x m feature matrices in registers
+// (Section 3.1 steps 3-8 and their derivatives; every dtype, head dimensions up to 128, any m).
+//
+// Every float32 operand of a contraction is written as a sum of three bf16 values,
+//   x = x0 + x1 + x2,  x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1)   (24 significant bits),
+// and a product of two such operands is the six bf16 products x0 y0, x0 y1, x1 y0, x0 y2, x1 y1, x2 y0
+// accumulated in float32; what is left out is of the order of 2^-25 of |x y|, a rounding error of the
+// float32 product itself.  A bf16 tensor is one exact term, so products with it take three.  The bf16
+// matrix rate is 16 times the float32 one, so even six products leave a factor of 2.7.
+//
+// What bounds it: per 32 x 32 tile of a feature matrix the matrix cores spend 32 cycles per product and
+// 16 of the contraction's length, the vector units about 5 x 64 cycles on ReLU or mask and the split
+// (7 instructions per pair of elements), so head dimensions 16 and 32 are bound by the vector units and
+// 64 and above by the matrix cores.  Two waves per SIMD let one run under the other.
+//
+// Layout: every operand is kept in the order in which a wave loads it ("operand tile": 32 vectors x 16
+// k-values of bf16; lane (l32, h) holds vector l32, k = 8 h .. 8 h + 7, 16 bytes; 1 KiB).  Where k runs
+// over the rows of an accumulator tile (features, or tokens), the k-slots stand for the rows in the
+// order in which the accumulator registers hold them: slot (h, q) of half a is row 16 a + 8 (q / 4)
+// + 4 h + q % 4.  The tensors of n x d (a small share of the time: m / 16 feature tiles are formed per
+// row) are filtered, split and packed by streaming kernels; rows past n and columns past d are zeros.
+#include "wersa_internal.h"
+
+#include <initializer_list>
+#include <type_traits>
+
+namespace wersa {
+namespace {
+
+#include "wersa_small_kernels.inc"
+#include "wersa_filter.inc"
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
+
+constexpr int kTile = 512;   // bf16 values of one operand tile
+
+__device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x16 zero16() {
+  f32x16 z;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) z[i] = 0.f;
+  return z;
+}
+// x[lane] + x[lane ^ 32] in every lane
+__device__ __forceinline__ float xor32_sum(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Split of eight floats.  The residual x - x0 is one pair dot product with (-1, 0) or (0, -1): exact,
+// since both products and the difference are representable.  (The constants pass through registers the compiler
+// does not look into: it would encode the first one as the inline constant -1.0, whose set bits the
+// instruction finds in the upper half.)
+__device__ __forceinline__ void split8(const float *v, bf16x8 *t) {
+  unsigned int ulo = 0x0000bf80u, uhi = 0xbf800000u;
+  asm("" : "+s"(ulo), "+s"(uhi));
+  const bf16x2 lo = __builtin_bit_cast(bf16x2, ulo), hi = __builtin_bit_cast(bf16x2, uhi);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    f32x2 x;
+    x[0] = v[2 * j];
+    x[1] = v[2 * j + 1];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const bf16x2 p = __builtin_convertvector(x, bf16x2);
+      t[i][2 * j] = p[0];
+      t[i][2 * j + 1] = p[1];
+      if (i < 2) {
+        x[0] = __builtin_amdgcn_fdot2_f32_bf16(p, lo, x[0], false);
+        x[1] = __builtin_amdgcn_fdot2_f32_bf16(p, hi, x[1], false);
+      }
+    }
+  }
+}
+__device__ __forceinline__ void split_half(const f32x16 &acc, int a, bf16x8 *t) {
+  float v[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) v[q] = acc[8 * a + q];
+  split8(v, t);
+}
+__device__ __forceinline__ void split1(float x, __bf16 *t) {
+  t[0] = (__bf16)x;
+  const float r = x - (float)t[0];
+  t[1] = (__bf16)r;
+  t[2] = (__bf16)(r - (float)t[1]);
+}
+
+// acc + the product of a three-term operand with one of NB terms, smallest products first.
+// SWAP: the NB-term operand is the first one of the instruction (its vectors are the result's rows).
+template <int NB, bool SWAP>
+__device__ __forceinline__ f32x16 mfma_terms(f32x16 acc, const bf16x8 *x, const bf16x8 *y) {
+  auto go = [&](int i, int j) { acc = SWAP ? mfma(y[j], x[i], acc) : mfma(x[i], y[j], acc); };
+  if (NB == 3) {
+    go(0, 2);
+    go(1, 1);
+    go(2, 0);
+    go(0, 1);
+    go(1, 0);
+    go(0, 0);
+  } else {
+    go(2, 0);
+    go(1, 0);
+    go(0, 0);
+  }
+  return acc;
+}
+__device__ __forceinline__ bf16x8 lds_operand(const bf16_t *tile, int lane) {
+  return *reinterpret_cast<const bf16x8 *>(tile + lane * 8);
+}
+__device__ __forceinline__ void store_operand(bf16_t *tile, int lane, bf16x8 v) {
+  *reinterpret_cast<bf16x8 *>(tile + lane * 8) = v;
+}
+
+// Eight consecutive elements as float; vec: the tensor's rows are 16-byte aligned.
+__device__ __forceinline__ void load8(const float *p, bool vec, float *v) {
+  if (vec) {
+    const f32x4 a = reinterpret_cast<const f32x4 *>(p)[0], b = reinterpret_cast<const f32x4 *>(p)[1];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      v[q] = a[q];
+      v[4 + q] = b[q];
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = p[q];
+  }
+}
+__device__ __forceinline__ void load8(const bf16_t *p, bool vec, float *v) {
+  if (vec) {
+    const u16x8 a = *reinterpret_cast<const u16x8 *>(p);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = bf16_to_f32(a[q]);
+  } else {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = bf16_to_f32(p[q]);
+  }
+}
+
+// Sizes of one problem.
+struct Dims {
+  int n, d, m;
+  int nt;    // 32-row tiles of tokens per slice (even: whole 64-row blocks)
+  int mt;    // 32-feature tiles
+};
+
+// ------------------------------------------------------------------------------------
+// Column sums of Q (and, for L > 6, of K) per chunk of rows; workgroups past `chunks` of slice 0 carry the
+// per-call constants and pack Omega.  Grid (chunks + extra, slices, tensors).
+// ------------------------------------------------------------------------------------
+template <typename T>
+struct OmegaPack {
+  const T *omega;      // [matrices][d][m]
+  const float *sigma;
+  float bw_floor;
+  float *scalars;
+  bf16_t *OA, *OB;     // features as vectors (k = columns), columns as vectors (k = features)
+  int matrices, KS, CT, PT, blocks;
+};
+template <typename T>
+__device__ void omega_pack_body(const OmegaPack<T> &o, const Dims &s, int block) {
+  if (block == 0 && threadIdx.x == 0) {
+    const float sg = *o.sigma, se = fmaxf(sg, o.bw_floor);
+    o.scalars[0] = 1.0f / (se * sqrtf((float)s.m));
+    o.scalars[1] = se;
+    o.scalars[2] = sg > o.bw_floor ? 1.0f : 0.0f;
+    o.scalars[3] = 1.0f;
+  }
+  const int per_ft = 64 * (o.KS + 2 * o.CT), per_mat = s.mt * per_ft;
+  const int e = block * 256 + threadIdx.x;
+  if (e >= o.matrices * per_mat) return;
+  const int mat = e / per_mat, ft = e % per_mat / per_ft, piece = e % per_ft, lane = piece & 63, which = piece >> 6;
+  const int l32 = lane & 31, h = lane >> 5;
+  const T *om = o.omega + (int64_t)mat * s.d * s.m;
+  float v[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    int f, c;
+    if (which < o.KS) {
+      f = 32 * ft + l32;
+      c = 16 * which + 8 * h + q;
+    } else {
+      const int a = (which - o.KS) / o.CT, ct = (which - o.KS) % o.CT;
+      f = 32 * ft + 16 * a + 8 * (q >> 2) + 4 * h + (q & 3);
+      c = 32 * ct + l32;
+    }
+    v[q] = (f < s.m && c < s.d) ? ld(om + (int64_t)c * s.m + f) : 0.f;
+  }
+  bf16x8 t[3];
+  split8(v, t);
+  const int64_t tile = which < o.KS ? ((int64_t)(mat * s.mt + ft) * o.KS + which) * o.PT
+                                    : ((int64_t)(mat * s.mt + ft) * 2 * o.CT + which - o.KS) * o.PT;
+  bf16_t *dst = (which < o.KS ? o.OA : o.OB) + tile * kTile;
+  for (int i = 0; i < o.PT; ++i) store_operand(dst + i * kTile, lane, t[i]);
+}
+template <typename T>
+__global__ __launch_bounds__(256) void pool_kernel(const T *q, const T *k, View v, Dims s, int vec, int rows_per_chunk,
+                                                  int chunks, float *partq, float *partk, OmegaPack<T> om) {
+  if ((int)blockIdx.x >= chunks) {
+    if (blockIdx.y == 0 && blockIdx.z == 0) omega_pack_body(om, s, blockIdx.x - chunks);
+    return;
+  }
+  const int slice = blockIdx.y, chunk = blockIdx.x;
+  const int cpr = s.d / 8, rpi = 256 / cpr;   // 8 columns per thread, rpi rows at a time
+  const int t0 = chunk * rows_per_chunk, t1 = min(s.n, t0 + rows_per_chunk);
+  const int cc = threadIdx.x % cpr, rr = threadIdx.x / cpr;
+  const T *xs = (blockIdx.z ? k : q) + v.slice_base(slice) + cc * 8;
+  float acc[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+  if (rr < rpi) {
+    int t = t0 + rr;
+    for (; t + 3 * rpi < t1; t += 4 * rpi) {   // four rows in flight
+      float x[4][8];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) load8(xs + (int64_t)(t + u * rpi) * v.sn, vec, x[u]);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] += x[u][e];
+    }
+    for (; t < t1; t += rpi) {
+      float x[8];
+      load8(xs + (int64_t)t * v.sn, vec, x);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] += x[e];
+    }
+  }
+  __shared__ float red[2048 + 128];   // [rpi][d + 1]: at most 128 x 17
+  if (rr < rpi)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) red[rr * (s.d + 1) + cc * 8 + e] = acc[e];
+  __syncthreads();
+  // halves of the rows are folded until a few are left (fixed order), then summed per column
+  int rows = rpi;
+  while (rows > 8) {
+    const int half = rows / 2, keep = rows - half;
+    for (int e = threadIdx.x; e < half * s.d; e += 256)
+      red[(e / s.d) * (s.d + 1) + e % s.d] += red[(e / s.d + keep) * (s.d + 1) + e % s.d];
+    __syncthreads();
+    rows = keep;
+  }
+  if ((int)threadIdx.x < s.d) {
+    float sum = 0.f;
+    for (int r = 0; r < rows; ++r) sum += red[r * (s.d + 1) + threadIdx.x];
+    (blockIdx.z ? partk : partq)[((int64_t)slice * chunks + chunk) * s.d + threadIdx.x] = sum;
+  }
+}
+
+// ------------------------------------------------------------------------------------
+// Forward operands: gated Haar filter of Q and K (steps 3, 5, 6), split and packed with k = columns;
+// V packed with k = tokens.  4096 elements per workgroup: TR rows x CW columns, one thread per
+// (column, 16 rows) in the filter, the 32- and 64-row sums through LDS.
+// Grid (row groups * column pieces, slices, 3: Q, K, V).
+// ------------------------------------------------------------------------------------
+template <int DH>
+struct Geo {
+  static constexpr int KS = DH / 16, CT = DH < 32 ? 1 : DH / 32, CW = DH < 64 ? DH : 64, TR = 4096 / CW,
+                       PIECES = DH / CW, LS = CW + 4, SEGS = 256 / CW;
+};
+// sum over the levels above four of coef_l * (block sum): levels 5 and 6 from the 16-row sums of a tile
+template <int CW>
+__device__ __forceinline__ float upper_levels(const float (*segsum)[CW], const float *cf, int seg, int c) {
+  const int b = seg & ~3;
+  const float s5 = segsum[seg & ~1][c] + segsum[seg | 1][c];
+  const float s6 = (segsum[b][c] + segsum[b + 1][c]) + (segsum[b + 2][c] + segsum[b + 3][c]);
+  return fmaf(cf[5], s5, cf[6] * s6);
+}
+template <typename T, int DH, int PT>
+__global__ __launch_bounds__(256) void prep_fwd_kernel(const T *q, const T *k, const T *vv, View v, Dims s, int vec,
+                                                      const float *coef, const float *addQ, const float *addK,
+                                                      bf16_t *XQ, bf16_t *XK, bf16_t *VC) {
+  using G = Geo<DH>;
+  constexpr int CW = G::CW, TR = G::TR, LS = G::LS;
+  __shared__ __attribute__((aligned(16))) float tile[TR * LS];
+  __shared__ float segsum[G::SEGS][CW];
+  __shared__ float cf[8];
+  const int tid = threadIdx.x, slice = blockIdx.y, side = blockIdx.z;
+  const int rg = blockIdx.x / G::PIECES, piece = blockIdx.x % G::PIECES;
+  const int t0 = rg * TR, c0 = piece * CW;
+  if (tid < 8) cf[tid] = coef[slice * kCoefStride + tid];
+  const T *xs = (side == 0 ? q : side == 1 ? k : vv) + v.slice_base(slice);
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int e = tid + 256 * u, r = e / (CW / 8), cc = e % (CW / 8) * 8;
+    float x[8];
+    if (t0 + r < s.n && c0 + cc < s.d) load8(xs + (int64_t)(t0 + r) * v.sn + c0 + cc, vec, x);
+    else
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[i] = 0.f;
+    f32x4 a, b;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      a[i] = x[i];
+      b[i] = x[4 + i];
+    }
+    *reinterpret_cast<f32x4 *>(&tile[r * LS + cc]) = a;
+    *reinterpret_cast<f32x4 *>(&tile[r * LS + cc + 4]) = b;
+  }
+  __syncthreads();
+  if (side < 2) {
+    const int c = tid % CW, seg = tid / CW;
+    float vals[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) vals[i] = tile[(seg * 16 + i) * LS + c];
+    segsum[seg][c] = segment_sum<16>(vals);
+    __syncthreads();
+    float upper = upper_levels<CW>(segsum, cf, seg, c);
+    const float *add = side ? addK : addQ;
+    const int gt = t0 / 64 + seg / 4, ntl = (s.n + 63) / 64;
+    if (add && gt < ntl && c0 + c < s.d) upper += add[((int64_t)slice * ntl + gt) * s.d + c0 + c];
+    filter_segment<16>(vals, cf, upper);
+    // (rows past n must stay zero: they are padding, not output)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) tile[(seg * 16 + i) * LS + c] = t0 + seg * 16 + i < s.n ? vals[i] : 0.f;
+    __syncthreads();
+    bf16_t *dst = side ? XK : XQ;
+    constexpr int KSL = CW / 16;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int p = tid + 256 * u, lane = p & 63, ksl = (p >> 6) % KSL, tb = t0 / 32 + (p >> 6) / KSL;
+      if (tb >= s.nt) continue;
+      float x[8];
+      load8(&tile[(((p >> 6) / KSL) * 32 + (lane & 31)) * LS + 16 * ksl + 8 * (lane >> 5)], true, x);
+      bf16x8 t[3];
+      split8(x, t);
+      bf16_t *o = dst + (((int64_t)slice * s.nt + tb) * G::KS + piece * KSL + ksl) * 3 * kTile;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) store_operand(o + i * kTile, lane, t[i]);
+    }
+  } else {
+    constexpr int CTL = CW < 32 ? 1 : CW / 32, NP = TR / 32 * 2 * CTL * 64;
+#pragma unroll
+    for (int u = 0; u < NP / 256; ++u) {
+      const int p = tid + 256 * u, lane = p & 63, ctl = (p >> 6) % CTL, a = (p >> 6) / CTL % 2, tbl = (p >> 6) / (2 * CTL);
+      const int tb = t0 / 32 + tbl, c = 32 * ctl + (lane & 31), h = lane >> 5;
+      if (tb >= s.nt) continue;
+      float x[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int r = tbl * 32 + 16 * a + 8 * (i >> 2) + 4 * h + (i & 3);
+        // (head dimension 16: column 16 of the 32 is the column of ones that gives z)
+        x[i] = c < CW ? tile[r * LS + c] : (c == 16 ? 1.f : 0.f);
+      }
+      bf16x8 t[3];
+      split8(x, t);
+      bf16_t *o = VC + ((((int64_t)slice * s.nt + tb) * 2 + a) * G::CT + piece * CTL + ctl) * PT * kTile;
+#pragma unroll
+      for (int i = 0; i < PT; ++i) store_operand(o + i * kTile, lane, t[i]);
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------
+// Backward operands.  Per row: <dO_t, O_t>, then dN_t and dD_t; dN packed both ways (k = columns for
+// dPhi_Q, k = tokens for dS), V packed with k = columns.
+//   PT == 1 (bf16 storage): dN stays dO, one exact term; 1 / D_t goes into the rows of Q_F of the dS
+//   product (XS; ReLU is positively homogeneous) and into the scale of the rows of dQ_F (rowscale), so
+//   ddw is then -<dO_t, O_t>.   PT == 3: dN = dO / D in float32, ddw = dD_t = -<dO_t, O_t> / D_t.
+//   With the LayerNorm output stage: dN = rstd (dO - mean dO - O mean(dO O)), ddw = 0.
+// part[slice][workgroup]: sum of the per-row term of d sigma (dD_t, or -<dO_t, O_t> rstd_t^2).
+// 4096 elements (whole rows) per workgroup.  Grid (row groups, slices).
+// ------------------------------------------------------------------------------------
+template <typename T, int DH, int PT>
+__global__ __launch_bounds__(256) void prep_bwd_kernel(const T *dout, const T *out, const T *vv, View v, Dims s, int vec,
+                                                      int ln, const float *D, const bf16_t *XQ, bf16_t *NR, bf16_t *NC,
+                                                      bf16_t *VR, bf16_t *XS, float *ddw, float *rowscale, float *part) {
+  using G = Geo<DH>;
+  constexpr int RB = 4096 / DH, PARTS = DH / 16, LS = DH + 4;
+  __shared__ __attribute__((aligned(16))) float tile[RB * LS];
+  __shared__ float wrow[RB], irow[RB], red[4];
+  const int tid = threadIdx.x, slice = blockIdx.y, t0 = blockIdx.x * RB;
+  const int r = tid / PARTS, pc = tid % PARTS * 16, t = t0 + r;
+  const bool ok = t < s.n && pc < s.d;
+  const int64_t base = v.slice_base(slice) + (int64_t)(t < s.n ? t : 0) * v.sn + (pc < s.d ? pc : 0);
+  float g[16], o[16];
+  load8(dout + base, vec, g);
+  load8(dout + base + 8, vec, g + 8);
+  load8(out + base, vec, o);
+  load8(out + base + 8, vec, o + 8);
+  if (!ok)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) g[i] = o[i] = 0.f;
+  float dot = 0.f, sum = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    dot = fmaf(g[i], o[i], dot);
+    sum += g[i];
+  }
+#pragma unroll
+  for (int w = 1; w < PARTS; w <<= 1) {
+    dot += __shfl_xor(dot, w, 64);
+    sum += __shfl_xor(sum, w, 64);
+  }
+  const float Dt = t < s.n ? D[(int64_t)slice * s.n + t] : 1.f;
+  float w = 0.f, sig, inv = 1.f;
+  if (ln) {
+    const float m1 = sum / (float)s.d, m2 = dot / (float)s.d;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) g[i] = ok ? Dt * (g[i] - m1 - o[i] * m2) : 0.f;
+    sig = -dot * Dt * Dt;
+  } else if (PT == 1) {
+    w = -dot;
+    inv = 1.0f / Dt;
+    sig = w * inv;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) g[i] = g[i] / Dt;
+    w = sig = -dot / Dt;
+  }
+  if (t >= s.n) w = sig = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    f32x4 x;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x[j] = g[4 * i + j];
+    *reinterpret_cast<f32x4 *>(&tile[r * LS + pc + 4 * i]) = x;
+  }
+  if (pc == 0) {
+    wrow[r] = w;
+    irow[r] = inv;
+    if (t < 32 * s.nt) {
+      ddw[(int64_t)slice * 32 * s.nt + t] = w;
+      rowscale[(int64_t)slice * 32 * s.nt + t] = inv;
+    }
+  } else {
+    sig = 0.f;
+  }
+  sig = wave_sum(sig);
+  if ((tid & 63) == 0) red[tid >> 6] = sig;
+  __syncthreads();
+  if (tid == 0) part[(int64_t)slice * gridDim.x + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+  auto pack_rows = [&](bf16_t *dst) {   // k = columns
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int p = tid + 256 * u, lane = p & 63, ks = (p >> 6) % G::KS, tbl = (p >> 6) / G::KS, tb = t0 / 32 + tbl;
+      if (tb >= s.nt) continue;
+      float x[8];
+      load8(&tile[(tbl * 32 + (lane & 31)) * LS + 16 * ks + 8 * (lane >> 5)], true, x);
+      bf16x8 tt[3];
+      split8(x, tt);
+      bf16_t *dd = dst + (((int64_t)slice * s.nt + tb) * G::KS + ks) * PT * kTile;
+#pragma unroll
+      for (int i = 0; i < PT; ++i) store_operand(dd + i * kTile, lane, tt[i]);
+    }
+  };
+  pack_rows(NR);
+  constexpr int NP = RB / 32 * 2 * G::CT * 64;
+#pragma unroll
+  for (int u = 0; u < NP / 256; ++u) {   // k = tokens
+    const int p = tid + 256 * u, lane = p & 63, ct = (p >> 6) % G::CT, a = (p >> 6) / G::CT % 2, tbl = (p >> 6) / (2 * G::CT);
+    const int tb = t0 / 32 + tbl, c = 32 * ct + (lane & 31), h = lane >> 5;
+    if (tb >= s.nt) continue;
+    float x[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int rr = tbl * 32 + 16 * a + 8 * (i >> 2) + 4 * h + (i & 3);
+      // (head dimension 16: the weights w_t of dz = Phi^T w sit in column 16, with one term per operand in
+      // columns 16, 17, 18)
+      x[i] = c < DH ? tile[rr * LS + (c < DH ? c : 0)] : (c < (PT == 1 ? 19 : 17) ? wrow[rr] : 0.f);
+    }
+    bf16x8 tt[3];
+    split8(x, tt);
+    if (DH == 16 && PT == 1) {
+      if (c == 17) tt[0] = tt[1];
+      if (c == 18) tt[0] = tt[2];
+    }
+    bf16_t *dd = NC + ((((int64_t)slice * s.nt + tb) * 2 + a) * G::CT + ct) * PT * kTile;
+#pragma unroll
+    for (int i = 0; i < PT; ++i) store_operand(dd + i * kTile, lane, tt[i]);
+  }
+  if (PT == 1) {   // Q_F / D
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int p = tid + 256 * u, lane = p & 63, ks = (p >> 6) % G::KS, tbl = (p >> 6) / G::KS, tb = t0 / 32 + tbl;
+      if (tb >= s.nt) continue;
+      const int64_t off = (((int64_t)slice * s.nt + tb) * G::KS + ks) * 3 * kTile;
+      const bf16x8 x0 = lds_operand(XQ + off, lane), x1 = lds_operand(XQ + off + kTile, lane),
+                   x2 = lds_operand(XQ + off + 2 * kTile, lane);
+      const float iv = irow[tbl * 32 + (lane & 31)];
+      float x[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) x[q] = (((float)x2[q] + (float)x1[q]) + (float)x0[q]) * iv;
+      bf16x8 tt[3];
+      split8(x, tt);
+#pragma unroll
+      for (int i = 0; i < 3; ++i) store_operand(XS + off + i * kTile, lane, tt[i]);
+    }
+  }
+  __syncthreads();
+  {
+    float x[16];
+    const int64_t vb = v.slice_base(slice) + (int64_t)(t < s.n ? t : 0) * v.sn + (pc < s.d ? pc : 0);
+    load8(vv + vb, vec, x);
+    load8(vv + vb + 8, vec, x + 8);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) tile[r * LS + pc + i] = ok ? x[i] : 0.f;
+  }
+  __syncthreads();
+  pack_rows(VR);
+}
+
+// ------------------------------------------------------------------------------------
+// part[slice][p][f][c] = sum over the p-th share of the tokens of ReLU(X Omega)[t, f] Y[t, c], and the
+// same against the weights w_t (1 where w is nullptr) into zpart[slice][p][f]; head dimension 16 has that
+// column among the 32 of Y.  Eight waves: FW of them own one feature tile each, and TW such groups take the token
+// tiles of a stage in turn (each group a share of its own).  X and Y go through LDS, one stage of SG token
+// tiles ahead in registers; Omega stays in registers.  Grid (splits, feature tiles / FW, slices).
+// ------------------------------------------------------------------------------------
+constexpr int stage_tokens(int DH) { return DH <= 32 ? 4 : (DH == 64 ? 2 : 1); }   // (in 32-row tiles)
+template <int DH, int PT>
+__global__ __launch_bounds__(512, 2) void contract_kernel(const bf16_t *X, const bf16_t *Y, const float *w, const bf16_t *OA,
+                                                         Dims s, int FW, int TW, int tiles_per_split, float *part, float *zpart) {
+  using G = Geo<DH>;
+  constexpr int SG = stage_tokens(DH), NX = G::KS * 3, NY = 2 * G::CT * PT, NS = SG * (NX + NY),
+                U = (NS + 7) / 8;
+  __shared__ __attribute__((aligned(16))) bf16_t lds[2][NS * kTile];
+  __shared__ float lw[2][SG * 32];
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int slice = blockIdx.z, fw = wave % FW, tw = wave / FW;
+  const int ft = blockIdx.y * FW + fw;
+  const int tb0 = blockIdx.x * tiles_per_split, tb1 = min(s.nt, tb0 + tiles_per_split);
+  const bf16_t *xs = X + (int64_t)slice * s.nt * NX * kTile, *ys = Y + (int64_t)slice * s.nt * NY * kTile;
+  bf16x8 om[G::KS][PT];
+#pragma unroll
+  for (int ks = 0; ks < G::KS; ++ks)
+#pragma unroll
+    for (int i = 0; i < PT; ++i) om[ks][i] = lds_operand(OA + (((int64_t)ft * G::KS + ks) * PT + i) * kTile, lane);
+  u32x4 st[U];
+  float stw = 0.f;
+  auto fetch = [&](int tb) {   // tiles past the end of the slice are clamped (never used)
+    const int last = s.nt - 1;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = wave + 8 * u;
+      if (i < NS) {
+        const bool isx = i < SG * NX;
+        const int j = isx ? i : i - SG * NX, per = isx ? NX : NY;
+        const int tt = min(tb + j / per, last);
+        const bf16_t *src = (isx ? xs : ys) + ((int64_t)tt * per + j % per) * kTile;
+        st[u] = *reinterpret_cast<const u32x4 *>(src + lane * 8);
+      }
+    }
+    if (DH > 16 && w && tid < SG * 32) stw = w[(int64_t)slice * s.nt * 32 + min(tb * 32 + tid, s.nt * 32 - 1)];
+  };
+  auto put = [&](int b) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = wave + 8 * u;
+      if (i < NS) *reinterpret_cast<u32x4 *>(&lds[b][i * kTile + lane * 8]) = st[u];
+    }
+    if (DH > 16 && tid < SG * 32) lw[b][tid] = w ? stw : 1.f;
+  };
+  f32x16 acc[G::CT];
+#pragma unroll
+  for (int ct = 0; ct < G::CT; ++ct) acc[ct] = zero16();
+  float zacc = 0.f;
+  if (tb0 < tb1) {
+    fetch(tb0);
+    put(0);
+    __syncthreads();
+    int b = 0;
+    for (int tb = tb0; tb < tb1; tb += SG, b ^= 1) {
+      const bool more = tb + SG < tb1;
+      if (more) fetch(tb + SG);
+      for (int g = tw < TW ? tw : SG; g < SG && tb + g < tb1; g += TW) {
+        const bf16_t *lx = &lds[b][g * NX * kTile], *ly = &lds[b][(SG * NX + g * NY) * kTile];
+        f32x16 R = zero16();
+#pragma unroll
+        for (int ks = 0; ks < G::KS; ++ks) {
+          bf16x8 x[3];
+#pragma unroll
+          for (int i = 0; i < 3; ++i) x[i] = lds_operand(lx + (ks * 3 + i) * kTile, lane);
+          R = mfma_terms<PT, false>(R, x, om[ks]);   // rows: tokens, columns (lanes): features
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) R[i] = fmaxf(R[i], 0.f);
+        if (DH > 16) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const f32x4 w4 = *reinterpret_cast<const f32x4 *>(&lw[b][g * 32 + 8 * j + 4 * h]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) zacc = fmaf(R[4 * j + i], w4[i], zacc);
+          }
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          bf16x8 p[3];
+          split_half(R, a, p);
+#pragma unroll
+          for (int ct = 0; ct < G::CT; ++ct) {
+            bf16x8 y[PT];
+#pragma unroll
+            for (int i = 0; i < PT; ++i) y[i] = lds_operand(ly + ((a * G::CT + ct) * PT + i) * kTile, lane);
+            acc[ct] = mfma_terms<PT, false>(acc[ct], p, y);   // rows: features, columns: columns of Y
+          }
+        }
+      }
+      if (more) put(b ^ 1);
+      __syncthreads();
+    }
+  }
+  if (tw >= TW) return;
+  const int64_t pidx = (int64_t)slice * gridDim.x * TW + blockIdx.x * TW + tw;
+  constexpr int PW = 32 * G::CT;
+  float *po = part + (pidx * s.mt + ft) * 32 * PW;
+#pragma unroll
+  for (int ct = 0; ct < G::CT; ++ct)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) po[(8 * (i >> 2) + 4 * h + (i & 3)) * PW + 32 * ct + l32] = acc[ct][i];
+  if (DH > 16) {
+    zacc = xor32_sum(zacc);
+    if (h == 0) zpart[(pidx * s.mt + ft) * 32 + l32] = zacc;
+  }
+}
+
+// ------------------------------------------------------------------------------------
+// S (or dS) and z (or dz) of one feature tile: fixed-order sum of the shares, times c; float32 results
+// [m][d] and [m], and the operand tiles of the kernels that follow: features as vectors with the
+// extension tile that carries the rank-one term dD z^T (three-term products in six k-slots), and columns
+// as vectors with k = features.  Grid (feature tiles, slices).
+// ------------------------------------------------------------------------------------
+template <int DH>
+__global__ __launch_bounds__(256) void reduce_kernel(const float *part, const float *zpart, int shares, int zcols,
+                                                    const float *scalars, Dims s, float *S, float *z, float *zpad,
+                                                    bf16_t *SA, bf16_t *SB) {
+  using G = Geo<DH>;
+  constexpr int PW = 32 * G::CT, LS = PW + 1;
+  __shared__ float tile[32 * LS];
+  __shared__ float zt[32];
+  const int tid = threadIdx.x, ft = blockIdx.x, slice = blockIdx.y;
+  const float c = scalars[0];
+  const int64_t step = (int64_t)s.mt * 32 * PW;
+  const float *p0 = part + ((int64_t)slice * shares * s.mt + ft) * 32 * PW;
+  // four lanes groups of the shares would change the order with the count; each element is one chain
+#pragma unroll
+  for (int u = 0; u < 32 * PW / 1024; ++u) {
+    const int e = (tid + 256 * u) * 4;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    int sh = 0;
+    for (; sh + 8 <= shares; sh += 8) {   // eight loads in flight
+      f32x4 x[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[i] = *reinterpret_cast<const f32x4 *>(p0 + (sh + i) * step + e);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc += x[i];
+    }
+    for (; sh < shares; ++sh) acc += *reinterpret_cast<const f32x4 *>(p0 + sh * step + e);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) tile[(e / PW) * LS + e % PW + i] = acc[i] * c;
+  }
+  if (DH > 16 && tid < 32) {
+    const float *zp = zpart + ((int64_t)slice * shares * s.mt + ft) * 32 + tid;
+    float acc = 0.f;
+    for (int sh = 0; sh < shares; ++sh) acc += zp[(int64_t)sh * s.mt * 32];
+    zt[tid] = acc * c;
+  }
+  __syncthreads();
+  if (DH == 16 && tid < 32) {
+    float acc = 0.f;
+    for (int j = zcols - 1; j >= 0; --j) acc += tile[tid * LS + 16 + j];
+    zt[tid] = acc;
+    tile[tid * LS + 16] = acc;   // (column 16 of the operand: the normaliser's column)
+  }
+  __syncthreads();
+  for (int e = tid; e < 32 * s.d; e += 256) {
+    const int f = e / s.d, cc = e % s.d;
+    if (32 * ft + f < s.m) S[((int64_t)slice * s.m + 32 * ft + f) * s.d + cc] = tile[f * LS + cc];
+  }
+  if (tid < 32) {
+    if (32 * ft + tid < s.m) z[(int64_t)slice * s.m + 32 * ft + tid] = zt[tid];
+    zpad[((int64_t)slice * s.mt + ft) * 32 + tid] = zt[tid];
+  }
+  bf16_t *sa = SA + ((int64_t)slice * s.mt + ft) * (3 * G::KS + 1) * kTile;
+  bf16_t *sb = SB + ((int64_t)slice * s.mt + ft) * 6 * G::CT * kTile;
+  for (int p = tid; p < 64 * (G::KS + 1 + 2 * G::CT); p += 256) {
+    const int lane = p & 63, which = p >> 6, l32 = lane & 31, h = lane >> 5;
+    bf16x8 t[3];
+    if (which < G::KS) {
+      float x[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) x[q] = tile[l32 * LS + 16 * which + 8 * h + q];
+      split8(x, t);
+#pragma unroll
+      for (int i = 0; i < 3; ++i) store_operand(sa + (3 * which + i) * kTile, lane, t[i]);
+    } else if (which == G::KS) {
+      __bf16 zz[3];
+      split1(h == 0 ? zt[l32] : 0.f, zz);
+      const __bf16 o = (__bf16)0.f;
+      const bf16x8 e = {zz[0], zz[1], zz[0], zz[2], zz[0], zz[1], o, o};
+      store_operand(sa + 3 * G::KS * kTile, lane, e);
+    } else {
+      const int a = (which - G::KS - 1) / G::CT, ct = (which - G::KS - 1) % G::CT, cc = 32 * ct + l32;
+      float x[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const float val = tile[(16 * a + 8 * (q >> 2) + 4 * h + (q & 3)) * LS + cc];
+        x[q] = (DH == 16 && cc > 16) ? 0.f : val;
+      }
+      split8(x, t);
+#pragma unroll
+      for (int i = 0; i < 3; ++i) store_operand(sb + ((a * G::CT + ct) * 3 + i) * kTile, lane, t[i]);
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------
+// Kernels that own token rows and walk over the features: RT token tiles per wave, NW waves, the operands
+// of FC feature tiles per stage through LDS (shared by the waves), the next stage ahead in registers.
+// Sections of a stage: up to four packed arrays, each contiguous per feature tile.
+// ------------------------------------------------------------------------------------
+template <int N0, int N1, int N2, int N3, int FC, int NW>
+struct Stager {
+  static constexpr int NS = FC * (N0 + N1 + N2 + N3), U = (NS + NW - 1) / NW;
+  static constexpr int O1 = FC * N0, O2 = O1 + FC * N1, O3 = O2 + FC * N2;   // first tile of each section in LDS
+  const bf16_t *p0, *p1, *p2, *p3;
+  u32x4 st[U];
+  __device__ __forceinline__ void fetch(int ft, int wave, int lane) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = wave + NW * u;
+      if (i < NS) {
+        const bf16_t *src = i < O1   ? p0 + ((int64_t)ft * N0 + i) * kTile
+                            : i < O2 ? p1 + ((int64_t)ft * N1 + (i - O1)) * kTile
+                            : i < O3 ? p2 + ((int64_t)ft * N2 + (i - O2)) * kTile
+                                     : p3 + ((int64_t)ft * N3 + (i - O3)) * kTile;
+        st[u] = *reinterpret_cast<const u32x4 *>(src + lane * 8);
+      }
+    }
+  }
+  __device__ __forceinline__ void put(bf16_t *lds, int wave, int lane) const {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = wave + NW * u;
+      if (i < NS) *reinterpret_cast<u32x4 *>(&lds[i * kTile + lane * 8]) = st[u];
+    }
+  }
+};
+
+// MODE 0: O = (Phi S) / (Phi z + eps) and D.   1: N = Phi S in float32 (LayerNorm follows).
+// MODE 2: dV = Phi_K dS.     X: operand tiles of Q_F or K_F.  Grid (row groups, slices).
+template <typename T, int DH, int PT, int MODE, int RT, int NW>
+__global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void apply_kernel(const bf16_t *X, const bf16_t *OA, const bf16_t *SB,
+                                                                       const float *zpad, const float *scalars, float eps,
+                                                                       Dims s, T *out, View v, float *N, float *D) {
+  using G = Geo<DH>;
+  constexpr int FC = DH <= 32 ? 2 : 1, NA = G::KS * PT, NB = 6 * G::CT;
+  constexpr bool ZV = MODE == 0 && DH > 16;   // normaliser on the vector units (head dimension 16: column 16 of S)
+  typedef Stager<NA, NB, 0, 0, FC, NW> Stg;
+  __shared__ __attribute__((aligned(16))) bf16_t lds[2][Stg::NS * kTile];
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int slice = blockIdx.y, tb0 = (blockIdx.x * NW + wave) * RT;
+  bf16x8 x[RT][G::KS][3];
+#pragma unroll
+  for (int r = 0; r < RT; ++r) {
+    const bf16_t *xp = X + ((int64_t)slice * s.nt + min(tb0 + r, s.nt - 1)) * G::KS * 3 * kTile;
+#pragma unroll
+    for (int ks = 0; ks < G::KS; ++ks)
+#pragma unroll
+      for (int i = 0; i < 3; ++i) x[r][ks][i] = lds_operand(xp + (ks * 3 + i) * kTile, lane);
+  }
+  Stg sg;
+  sg.p0 = OA;
+  sg.p1 = SB + (int64_t)slice * s.mt * NB * kTile;
+  sg.p2 = sg.p3 = nullptr;
+  f32x16 acc[RT][G::CT];
+  float dsum[RT];
+#pragma unroll
+  for (int r = 0; r < RT; ++r) {
+    dsum[r] = 0.f;
+#pragma unroll
+    for (int ct = 0; ct < G::CT; ++ct) acc[r][ct] = zero16();
+  }
+  const float *zs = zpad + (int64_t)slice * s.mt * 32 + 4 * h;
+  sg.fetch(0, wave, lane);
+  sg.put(lds[0], wave, lane);
+  __syncthreads();
+  int b = 0;
+  for (int f0 = 0; f0 < s.mt; f0 += FC, b ^= 1) {
+    const bool more = f0 + FC < s.mt;
+    if (more) sg.fetch(f0 + FC, wave, lane);
+#pragma unroll
+    for (int fi = 0; fi < FC; ++fi) {
+      if (f0 + fi >= s.mt) break;
+      const bf16_t *la = &lds[b][fi * NA * kTile], *lb = &lds[b][(Stg::O1 + fi * NB) * kTile];
+      f32x4 z4[4];
+      if (ZV)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) z4[j] = *reinterpret_cast<const f32x4 *>(zs + (f0 + fi) * 32 + 8 * j);
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        f32x16 R = zero16();
+#pragma unroll
+        for (int ks = 0; ks < G::KS; ++ks) {
+          bf16x8 o[PT];
+#pragma unroll
+          for (int i = 0; i < PT; ++i) o[i] = lds_operand(la + (ks * PT + i) * kTile, lane);
+          R = mfma_terms<PT, true>(R, x[r][ks], o);   // rows: features, lanes: tokens
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) R[i] = fmaxf(R[i], 0.f);
+        if (ZV)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) dsum[r] = fmaf(R[i], z4[i >> 2][i & 3], dsum[r]);
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          bf16x8 p[3];
+          split_half(R, a, p);
+#pragma unroll
+          for (int ct = 0; ct < G::CT; ++ct) {
+            bf16x8 y[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) y[i] = lds_operand(lb + ((a * G::CT + ct) * 3 + i) * kTile, lane);
+            acc[r][ct] = mfma_terms<3, false>(acc[r][ct], p, y);   // rows: tokens, lanes: columns
+          }
+        }
+      }
+    }
+    if (more) sg.put(lds[b ^ 1], wave, lane);
+    __syncthreads();
+  }
+  const float c = scalars[0];
+#pragma unroll
+  for (int r = 0; r < RT; ++r) {
+    const int tb = tb0 + r;
+    if (tb >= s.nt) continue;
+    float Dl = 0.f;
+    if (ZV) Dl = fmaf(c, xor32_sum(dsum[r]), eps);   // token l32
+    if (ZV && h == 0 && 32 * tb + l32 < s.n) D[(int64_t)slice * s.n + 32 * tb + l32] = Dl;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int row = 8 * (i >> 2) + 4 * h + (i & 3), t = 32 * tb + row;
+      float Dt = 1.f;
+      if (MODE == 0) {
+        Dt = ZV ? __shfl(Dl, row, 64) : fmaf(c, __shfl(acc[r][0][i], (lane & 32) | 16, 64), eps);
+        if (!ZV && l32 == 16 && t < s.n) D[(int64_t)slice * s.n + t] = Dt;
+      }
+#pragma unroll
+      for (int ct = 0; ct < G::CT; ++ct) {
+        const int col = 32 * ct + l32;
+        if (t < s.n && col < s.d) {
+          const float val = c * acc[r][ct][i];
+          if (MODE == 1) N[((int64_t)slice * s.n + t) * s.d + col] = val;
+          else st(out + v.slice_base(slice) + (int64_t)t * v.sn + col, MODE == 0 ? val / Dt : val);
+        }
+      }
+    }
+  }
+}
+
+// dX_F of one side: R = X Omega, G = Y S^T + w z^T (Y = dN, S, w = dD on the query side; Y = V, dS, w = 1
+// on the key side), dX_F = c rowscale ((G masked where R > 0) Omega^T) in float32 [slice][32 nt][DH].
+// DV: dV = c ReLU(R) dS rides along.  ddw, rowscale nullptr: 1.
+template <typename T, int DH, int PT, bool DV, int RT, int NW>
+__global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void grad_kernel(const bf16_t *X, const bf16_t *Y, const float *ddw,
+                                                                      const float *rowscale, const bf16_t *OA,
+                                                                      const bf16_t *SA, const bf16_t *OB, const bf16_t *SB,
+                                                                      const float *scalars, Dims s, float *dXF, T *dv, View v) {
+  using G = Geo<DH>;
+  constexpr int FC = DH == 16 ? 2 : 1, NA = G::KS * PT, NSA = 3 * G::KS + 1, NOB = 2 * G::CT * PT, NSB = DV ? 6 * G::CT : 0;
+  typedef Stager<NA, NSA, NOB, NSB, FC, NW> Stg;
+  __shared__ __attribute__((aligned(16))) bf16_t lds[2][Stg::NS * kTile];
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int slice = blockIdx.y, tb0 = (blockIdx.x * NW + wave) * RT;
+  bf16x8 x[RT][G::KS][3], y[RT][G::KS][PT], ext[RT];
+#pragma unroll
+  for (int r = 0; r < RT; ++r) {
+    const int64_t tb = (int64_t)slice * s.nt + min(tb0 + r, s.nt - 1);
+    const bf16_t *xp = X + tb * G::KS * 3 * kTile, *yp = Y + tb * G::KS * PT * kTile;
+#pragma unroll
+    for (int ks = 0; ks < G::KS; ++ks) {
+#pragma unroll
+      for (int i = 0; i < 3; ++i) x[r][ks][i] = lds_operand(xp + (ks * 3 + i) * kTile, lane);
+#pragma unroll
+      for (int i = 0; i < PT; ++i) y[r][ks][i] = lds_operand(yp + (ks * PT + i) * kTile, lane);
+    }
+    __bf16 w[3];
+    split1(h ? 0.f : (ddw ? ddw[tb * 32 + l32] : 1.f), w);
+    const __bf16 o = (__bf16)0.f;
+    ext[r] = bf16x8{w[0], w[0], w[1], w[0], w[2], w[1], o, o};   // against z0, z1, z0, z2, z0, z1
+  }
+  Stg sg;
+  sg.p0 = OA;
+  sg.p1 = SA + (int64_t)slice * s.mt * NSA * kTile;
+  sg.p2 = OB;
+  sg.p3 = DV ? SB + (int64_t)slice * s.mt * NSB * kTile : nullptr;
+  f32x16 acc[RT][G::CT], accv[DV ? RT : 1][G::CT];
+#pragma unroll
+  for (int r = 0; r < RT; ++r)
+#pragma unroll
+    for (int ct = 0; ct < G::CT; ++ct) {
+      acc[r][ct] = zero16();
+      if (DV) accv[r][ct] = zero16();
+    }
+  sg.fetch(0, wave, lane);
+  sg.put(lds[0], wave, lane);
+  __syncthreads();
+  int b = 0;
+  for (int f0 = 0; f0 < s.mt; f0 += FC, b ^= 1) {
+    const bool more = f0 + FC < s.mt;
+    if (more) sg.fetch(f0 + FC, wave, lane);
+#pragma unroll
+    for (int fi = 0; fi < FC; ++fi) {
+      if (f0 + fi >= s.mt) break;
+      const bf16_t *la = &lds[b][fi * NA * kTile], *ls = &lds[b][(Stg::O1 + fi * NSA) * kTile],
+                   *lo = &lds[b][(Stg::O2 + fi * NOB) * kTile], *lv = &lds[b][(Stg::O3 + fi * NSB) * kTile];
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        f32x16 R = zero16(), Gr = zero16();
+#pragma unroll
+        for (int ks = 0; ks < G::KS; ++ks) {
+          bf16x8 o[PT], sa[3];
+#pragma unroll
+          for (int i = 0; i < PT; ++i) o[i] = lds_operand(la + (ks * PT + i) * kTile, lane);
+          R = mfma_terms<PT, true>(R, x[r][ks], o);   // rows: features, lanes: tokens
+#pragma unroll
+          for (int i = 0; i < 3; ++i) sa[i] = lds_operand(ls + (ks * 3 + i) * kTile, lane);
+          Gr = mfma_terms<PT, false>(Gr, sa, y[r][ks]);
+        }
+        Gr = mfma(lds_operand(ls + 3 * G::KS * kTile, lane), ext[r], Gr);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) Gr[i] = R[i] > 0.f ? Gr[i] : 0.f;
+        if (DV)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) R[i] = fmaxf(R[i], 0.f);
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          bf16x8 p[3];
+          split_half(Gr, a, p);
+#pragma unroll
+          for (int ct = 0; ct < G::CT; ++ct) {
+            bf16x8 o[PT];
+#pragma unroll
+            for (int i = 0; i < PT; ++i) o[i] = lds_operand(lo + ((a * G::CT + ct) * PT + i) * kTile, lane);
+            acc[r][ct] = mfma_terms<PT, false>(acc[r][ct], p, o);   // rows: tokens, lanes: columns
+          }
+          if (DV) {
+            split_half(R, a, p);
+#pragma unroll
+            for (int ct = 0; ct < G::CT; ++ct) {
+              bf16x8 o[3];
+#pragma unroll
+              for (int i = 0; i < 3; ++i) o[i] = lds_operand(lv + ((a * G::CT + ct) * 3 + i) * kTile, lane);
+              accv[r][ct] = mfma_terms<3, false>(accv[r][ct], p, o);
+            }
+          }
+        }
+      }
+    }
+    if (more) sg.put(lds[b ^ 1], wave, lane);
+    __syncthreads();
+  }
+  const float c = scalars[0];
+#pragma unroll
+  for (int r = 0; r < RT; ++r) {
+    const int tb = tb0 + r;
+    if (tb >= s.nt) continue;
+    const float rs = rowscale ? c * rowscale[((int64_t)slice * s.nt + tb) * 32 + l32] : c;   // token l32
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int row = 8 * (i >> 2) + 4 * h + (i & 3), t = 32 * tb + row;
+      const float sc = rowscale ? __shfl(rs, row, 64) : c;
+#pragma unroll
+      for (int ct = 0; ct < G::CT; ++ct) {
+        const int col = 32 * ct + l32;
+        if (col < DH) dXF[((int64_t)slice * s.nt * 32 + t) * DH + col] = sc * acc[r][ct][i];
+        if (DV && t < s.n && col < s.d) st(dv + v.slice_base(slice) + (int64_t)t * v.sn + col, c * accv[r][ct][i]);
+      }
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------
+// Band inner products of X and dX_F on 64-row tiles (band l - 1: details of level l; band L: the
+// approximation) -> part[slice][workgroup][L + 1].  One thread per (column, 16 rows); with block sums A, B of the halves of a
+// 2^l-row block the detail coefficients are (A - B) / sqrt(2^l).  tgq, tgk (L > 6): the tile
+// sums of dX_F.  Grid (row groups * column pieces, slices, 2: Q, K).
+// ------------------------------------------------------------------------------------
+template <typename T, int DH>
+__global__ __launch_bounds__(256) void dots_kernel(const T *q, const T *k, View v, const float *gq, const float *gk, Dims s,
+                                                  int L, int rows_out, float *partq, float *partk, float *tgq, float *tgk) {
+  using G = Geo<DH>;
+  constexpr int CW = G::CW, TR = G::TR;
+  __shared__ float sg[G::SEGS][CW], sx[G::SEGS][CW];
+  __shared__ float red[4][8];
+  const int tid = threadIdx.x, slice = blockIdx.y, side = blockIdx.z;
+  const int rg = blockIdx.x / G::PIECES, piece = blockIdx.x % G::PIECES;
+  const int c = tid % CW, seg = tid / CW, col = piece * CW + c, t0 = rg * TR + seg * 16;
+  const bool cok = col < s.d;
+  const T *xp = (side ? k : q) + v.slice_base(slice) + (cok ? col : 0);
+  const float *gp = (side ? gk : gq) + (int64_t)slice * s.nt * 32 * DH + col;
+  float a[16], b[16], e[8];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int t = t0 + i;
+    a[i] = ld(xp + (int64_t)min(t, s.n - 1) * v.sn);
+    b[i] = gp[(int64_t)min(t, s.n - 1) * DH];
+  }
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    if (!cok || t0 + i >= s.n) a[i] = b[i] = 0.f;
+#pragma unroll
+  for (int l = 0; l < 8; ++l) e[l] = 0.f;
+  auto top = [&](int l, int cnt) {   // e[7]: the approximation band, once level L is reached
+    if (l == L)
+#pragma unroll
+      for (int i = 0; i < cnt; ++i) e[7] = fmaf(a[i], b[i], e[7]);
+  };
+  top(0, 16);
+#pragma unroll
+  for (int l = 1; l <= 4; ++l) {
+#pragma unroll
+    for (int i = 0; i < (16 >> l); ++i) {
+      e[l] = fmaf(a[2 * i] - a[2 * i + 1], b[2 * i] - b[2 * i + 1], e[l]);
+      a[i] = a[2 * i] + a[2 * i + 1];
+      b[i] = b[2 * i] + b[2 * i + 1];
+    }
+    top(l, 16 >> l);
+  }
+  sx[seg][c] = a[0];
+  sg[seg][c] = b[0];
+  __syncthreads();
+  if ((seg & 1) == 0) {
+    const float x1 = sx[seg + 1][c], g1 = sg[seg + 1][c];
+    e[5] = (a[0] - x1) * (b[0] - g1);
+    a[0] += x1;
+    b[0] += g1;
+    top(5, 1);
+    if ((seg & 2) == 0) {
+      const float x2 = sx[seg + 2][c] + sx[seg + 3][c], g2 = sg[seg + 2][c] + sg[seg + 3][c];
+      e[6] = (a[0] - x2) * (b[0] - g2);
+      a[0] += x2;
+      b[0] += g2;
+      top(6, 1);
+      float *tg = side ? tgk : tgq;
+      const int ntl = (s.n + 63) / 64, gt = (rg * TR) / 64 + seg / 4;
+      if (tg && cok && gt < ntl) tg[((int64_t)slice * ntl + gt) * s.d + col] = b[0];
+    }
+  }
+#pragma unroll
+  for (int l = 1; l < 8; ++l) {
+    const float t = wave_sum(e[l]);
+    if ((tid & 63) == 0) red[tid >> 6][l] = t;
+  }
+  __syncthreads();
+  if (tid <= L) {
+    float val = 0.f;
+    const int l = tid < L ? tid + 1 : 7;   // (bands of levels above 6 are left at zero here)
+    if (tid < L ? tid < 6 : L <= 6)
+      val = ((red[0][l] + red[1][l]) + (red[2][l] + red[3][l])) / (float)(1 << (tid < L ? tid + 1 : L));
+    (side ? partk : partq)[((int64_t)slice * rows_out + blockIdx.x) * (L + 1) + tid] = val;
+  }
+}
+
+// y = G_F x (+ addscale * addvec[slice][column]) from float32 [slice][rows][DH] or a strided tensor: the filter's backward
+// (symmetric matrix) with the pooled query's share, and the filter as a stage of its own.  add: the per-tile
+// addends of the levels above 6.  filt: coefficient rows as the gate kernel leaves them (stride
+// kCoefStride), or band weights [slice][L + 1] (raw).  Grid (row groups * column pieces, slices, tensors).
+struct FilterJob {
+  const void *x;
+  void *y;
+  const float *add, *addvec;
+};
+template <typename TI, typename TO, int DH>
+__global__ __launch_bounds__(256) void filter_kernel(FilterJob j0, FilterJob j1, View vx, View vy, Dims s, const float *filt, int raw, int L,
+                                                    float addscale) {
+  using G = Geo<DH>;
+  constexpr int CW = G::CW, TR = G::TR;
+  __shared__ float segsum[G::SEGS][CW];
+  __shared__ float cf[8];
+  const int tid = threadIdx.x, slice = blockIdx.y;
+  const FilterJob &j = blockIdx.z ? j1 : j0;
+  if (tid < 8) {
+    if (raw) {
+      const float *F = filt + (int64_t)slice * (L + 1);
+      cf[tid] = tid == 0 ? F[0] : (tid <= L ? (F[tid] - F[tid - 1]) / (float)(1 << tid) : 0.f);
+    } else {
+      cf[tid] = filt[slice * kCoefStride + tid];
+    }
+  }
+  const int rg = blockIdx.x / G::PIECES, piece = blockIdx.x % G::PIECES;
+  const int c = tid % CW, seg = tid / CW, col = piece * CW + c, t0 = rg * TR + seg * 16;
+  const bool cok = col < s.d;
+  const TI *xp = (const TI *)j.x + vx.slice_base(slice) + (cok ? col : 0);
+  float v[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = ld(xp + (int64_t)min(t0 + i, s.n - 1) * vx.sn);
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    if (t0 + i >= s.n) v[i] = 0.f;
+  segsum[seg][c] = segment_sum<16>(v);
+  __syncthreads();
+  float upper = upper_levels<CW>(segsum, cf, seg, c);
+  const int ntl = (s.n + 63) / 64, gt = (rg * TR) / 64 + seg / 4;
+  if (j.add && cok && gt < ntl) upper += j.add[((int64_t)slice * ntl + gt) * s.d + col];
+  filter_segment<16>(v, cf, upper);
+  const float extra = (j.addvec && cok) ? addscale * j.addvec[(int64_t)slice * s.d + col] : 0.f;
+  TO *yp = (TO *)j.y + vy.slice_base(slice) + (cok ? col : 0);
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    if (cok && t0 + i < s.n) st(yp + (int64_t)(t0 + i) * vy.sn, v[i] + extra);
+}
+
+// ------------------------------------------------------------------------------------
+// Levels above 6 (see build_tile_pyramid): addends of Q_F, K_F from the tile sums of Q and K; in the backward
+// the addends of dQ, dK from the tile sums of dQ_F, dK_F, and the band inner products of the levels
+// above 6 into d / 16 extra rows of the partials.  Grid (slices, 2, d / 16) of 1024 threads.
+// ------------------------------------------------------------------------------------
+__global__ __launch_bounds__(1024) void deep_addend_kernel(const float *Tq, const float *Tk, const float *coef, int ntiles, int d, int L,
+                                                          float *pyr, float *Aq, float *Ak) {
+  const int slice = blockIdx.x, side = blockIdx.y;
+  const int c = kCoarseCols * blockIdx.z + (threadIdx.x & (kCoarseCols - 1)), g = threadIdx.x / kCoarseCols;
+  const int64_t base = (int64_t)slice * ntiles * d;
+  float *P = pyr + ((int64_t)slice * 2 + side) * pyramid_floats(ntiles, d);
+  build_tile_pyramid((side ? Tk : Tq) + base, ntiles, d, L - 6, P, c, g);
+  tile_addend(P, coef + slice * kCoefStride, ntiles, d, L - 6, (side ? Ak : Aq) + base, c, g);
+}
+__global__ __launch_bounds__(1024) void deep_bwd_kernel(const float *TgQ, const float *TgK, const float *TxQ, const float *TxK,
+                                                       const float *coef, int ntiles, int d, int L, float *pyr, float *AQ,
+                                                       float *AK, float *partQ, float *partK, int row) {
+  const int slice = blockIdx.x, side = blockIdx.y, J = L - 6;
+  const int c = kCoarseCols * blockIdx.z + (threadIdx.x & (kCoarseCols - 1)), g = threadIdx.x / kCoarseCols;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t base = (int64_t)slice * ntiles * d;
+  float *Pg = pyr + (((int64_t)slice * 2 + side) * 2) * pyramid_floats(ntiles, d);
+  float *Px = Pg + pyramid_floats(ntiles, d);
+  const float *Tg = (side ? TgK : TgQ) + base, *Tx = (side ? TxK : TxQ) + base;
+  build_tile_pyramid(Tg, ntiles, d, J, Pg, c, g);
+  build_tile_pyramid(Tx, ntiles, d, J, Px, c, g);
+  tile_addend(Pg, coef + slice * kCoefStride, ntiles, d, J, (side ? AK : AQ) + base, c, g);
+  __shared__ float red[2][16];
+  float *part = (side ? partK : partQ) + ((int64_t)slice * (row + gridDim.z) + row + blockIdx.z) * (L + 1);
+  if ((int)threadIdx.x < 6) part[threadIdx.x] = 0.f;
+  const float *pg = Tg, *px = Tx, *lg = Pg, *lx = Px;
+  int nprev = ntiles;
+  for (int j = 1; j <= J; ++j) {
+    const int nb = (nprev + 1) / 2;
+    float acc = 0.f, top = 0.f;
+#pragma unroll 4
+    for (int b = g; b < nb; b += kCoarseGroups) {
+      const bool two = 2 * b + 1 < nprev;
+      const float dg = pg[2 * b * d + c] - (two ? pg[(2 * b + 1) * d + c] : 0.f);
+      const float dx = px[2 * b * d + c] - (two ? px[(2 * b + 1) * d + c] : 0.f);
+      acc = fmaf(dg, dx, acc);
+      top = fmaf(lg[b * d + c], lx[b * d + c], top);
+    }
+    acc = wave_sum(acc);
+    top = wave_sum(top);
+    if (lane == 0) {
+      red[0][wave] = acc;
+      red[1][wave] = top;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 && (threadIdx.x == 0 || j == J)) {
+      float tot = 0.f;
+      for (int i = 0; i < 16; ++i) tot += red[threadIdx.x][i];
+      part[threadIdx.x == 0 ? 5 + j : L] = tot / (float)(1 << (6 + j));
+    }
+    __syncthreads();
+    pg = lg;
+    px = lx;
+    lg += nb * d;
+    lx += nb * d;
+    nprev = nb;
+  }
+}
+
+// Output stage of Algorithm 1 (LayerNorm over the d columns of a row, rstd kept in D); one wave per row.
+template <typename T>
+__global__ __launch_bounds__(256) void ln_out_kernel(const float *N, T *out, View v, int n, int d, float eps, float *D) {
+  const int slice = blockIdx.y;
+  const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (t >= n) return;
+  const float *p = N + ((int64_t)slice * n + t) * d;
+  float x[2], acc = 0.f;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    x[u] = lane + 64 * u < d ? p[lane + 64 * u] : 0.f;
+    acc += x[u];
+  }
+  const float mu = wave_sum(acc) / (float)d;
+  acc = 0.f;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const float e = lane + 64 * u < d ? x[u] - mu : 0.f;
+    acc += e * e;
+  }
+  const float rstd = 1.0f / sqrtf(wave_sum(acc) / (float)d + eps);
+  T *o = out + v.slice_base(slice) + (int64_t)t * v.sn;
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+    if (lane + 64 * u < d) st(o + lane + 64 * u, (x[u] - mu) * rstd);
+  if (lane == 0) D[(int64_t)slice * n + t] = rstd;
+}
+
+// ------------------------------------------------------------------------------------
+// Host side
+// ------------------------------------------------------------------------------------
+constexpr int kFillBlocks = 512;   // two 8-wave workgroups per compute unit
+
+int dh_of(int d) { return d <= 16 ? 16 : d <= 32 ? 32 : d <= 64 ? 64 : 128; }
+// One term for what comes in as bf16 (head dimensions up to 32, where that pays for instances of its own; the LayerNorm
+// output stage has a float32 dN); otherwise three terms for every operand.
+int terms_of(const wersa_desc &c) {
+  return c.dtype == WERSA_BF16 && c.d <= 32 && !(c.flags & WERSA_FLAG_LAYERNORM) ? 1 : 3;
+}
+struct Plan {
+  Dims s;
+  int DH, KS, CT, PT, matrices;
+  int chunks, rows_per_chunk;         // pooling
+  int FW, TW, splits, tiles_per_split, shares;
+  int groups;                         // 4096-element workgroups per slice
+  int bgroups;                        // the same for whole rows (prep_bwd)
+  int ntl;                            // 64-row tiles per slice
+};
+Plan plan_of(const wersa_desc &c) {
+  Plan p{};
+  const int slices = c.B * c.H;
+  p.DH = dh_of(c.d);
+  p.KS = p.DH / 16;
+  p.CT = p.DH < 32 ? 1 : p.DH / 32;
+  p.PT = terms_of(c);
+  p.matrices = (c.flags & WERSA_FLAG_SEPARATE_OMEGA) ? 2 : 1;
+  p.s = Dims{c.n, c.d, c.m, (c.n + 63) / 64 * 2, (c.m + 31) / 32};
+  p.ntl = (c.n + 63) / 64;
+  if (c.L > kTileL) {
+    p.rows_per_chunk = 64;   // the partial sums are the tile sums of the levels above 6
+  } else {
+    // about 2048 workgroups, at most 256 partials per slice (the gate kernel sums them), at least 64 rows
+    int want = (2048 + slices - 1) / slices;
+    want = want > 256 ? 256 : (want < 1 ? 1 : want);
+    const int rows = (c.n + want - 1) / want;
+    p.rows_per_chunk = rows < 64 ? 64 : rows;
+  }
+  p.chunks = (c.n + p.rows_per_chunk - 1) / p.rows_per_chunk;
+  p.FW = 8;
+  while (p.s.mt % p.FW) p.FW /= 2;
+  p.TW = 8 / p.FW;
+  const int sg = stage_tokens(p.DH);
+  p.TW = p.TW < sg ? p.TW : sg;
+  const int base = slices * (p.s.mt / p.FW);
+  int splits = (kFillBlocks + base - 1) / base;
+  const int most = (p.s.nt + 7) / 8;               // at least eight token tiles each
+  splits = splits > most ? most : splits;
+  p.tiles_per_split = (p.s.nt + splits - 1) / splits;
+  p.splits = (p.s.nt + p.tiles_per_split - 1) / p.tiles_per_split;
+  p.shares = p.splits * p.TW;
+  const int cw = p.DH < 64 ? p.DH : 64, tr = 4096 / cw;
+  p.groups = (c.n + tr - 1) / tr * (p.DH / cw);
+  p.bgroups = (p.s.nt * 32 + 4096 / p.DH - 1) / (4096 / p.DH);
+  return p;
+}
+
+struct Ws {
+  float *qpart, *part, *zpart, *zpad, *Nbuf, *pyr;
+  bf16_t *VC, *SB;
+  // backward
+  bf16_t *NR, *NC, *VR, *XS, *dSA, *dSB;
+  float *ddw, *rowscale, *dpart, *dS, *dz, *gq, *gk, *partQ, *partK, *dF, *dlogit, *dqbar, *tgq, *tgk, *aq, *ak;
+  int64_t total;
+};
+int64_t tile_floats(int64_t tiles) { return tiles * (kTile / 2); }
+Ws ws_of(const wersa_desc &c, const Plan &p, int bwd, float *base) {
+  Ws w{};
+  Bump b(base);
+  const int64_t sl = (int64_t)c.B * c.H;
+  auto op = [&](int64_t tiles) { return (bf16_t *)b.take(tile_floats(tiles)); };
+  const int64_t rows = sl * p.s.nt;
+  const bool deep = c.L > kTileL;
+  w.part = b.take(sl * p.shares * p.s.mt * 32 * 32 * p.CT);
+  w.zpart = b.take(sl * p.shares * p.s.mt * 32);
+  w.zpad = b.take(sl * p.s.mt * 32);
+  if (!bwd) {
+    w.qpart = b.take(sl * p.chunks * c.d);
+    w.VC = op(rows * 2 * p.CT * p.PT);
+    w.SB = op(sl * p.s.mt * 6 * p.CT + 6 * p.CT);       // (one feature tile more: a stage reads whole groups)
+    if (c.flags & WERSA_FLAG_LAYERNORM) w.Nbuf = b.take(sl * c.n * c.d);
+    if (deep) w.pyr = b.take(2 * sl * pyramid_floats(p.ntl, c.d));
+  } else {
+    w.NR = op(rows * p.KS * p.PT);
+    w.NC = op(rows * 2 * p.CT * p.PT);
+    w.VR = op(rows * p.KS * p.PT);
+    if (p.PT == 1) w.XS = op(rows * p.KS * 3);
+    w.dSA = op(sl * p.s.mt * (3 * p.KS + 1) + 3 * p.KS + 1);
+    w.dSB = op(sl * p.s.mt * 6 * p.CT + 6 * p.CT);
+    w.ddw = b.take(rows * 32);
+    w.rowscale = b.take(rows * 32);
+    w.dpart = b.take(sl * p.bgroups);
+    w.dS = b.take(sl * c.m * c.d);
+    w.dz = b.take(sl * c.m);
+    w.gq = b.take(rows * 32 * p.DH);
+    w.gk = b.take(rows * 32 * p.DH);
+    const int64_t prow = p.groups + (deep ? c.d / kCoarseCols : 0);
+    w.partQ = b.take(sl * prow * (c.L + 1));
+    w.partK = b.take(sl * prow * (c.L + 1));
+    w.dF = b.take(sl * (c.L + 1));
+    w.dlogit = b.take(sl * (c.L + 1));
+    w.dqbar = b.take(sl * c.d);
+    if (deep) {
+      w.tgq = b.take(sl * p.ntl * c.d);
+      w.tgk = b.take(sl * p.ntl * c.d);
+      w.aq = b.take(sl * p.ntl * c.d);
+      w.ak = b.take(sl * p.ntl * c.d);
+      w.pyr = b.take(4 * sl * pyramid_floats(p.ntl, c.d));
+    }
+  }
+  w.total = b.off;
+  return w;
+}
+
+// Rows of the strided tensors can be read in 16-byte pieces.
+bool rows_aligned(const wersa_desc &c, std::initializer_list<const void *> ptrs) {
+  const int64_t es = c.dtype == WERSA_BF16 ? 2 : 4;
+  if (c.stride_n * es % 16 || c.stride_h * es % 16 || c.stride_b * es % 16) return false;
+  for (const void *q : ptrs)
+    if ((uintptr_t)q % 16) return false;
+  return true;
+}
+
+// Workgroup sizes of the row kernels: 8 waves (two per SIMD) that share the staged operands; 2 waves where the rows
+// are too few to give every compute unit a workgroup of 8 (each wave walks all features whatever the size, so
+// more and smaller workgroups cost only the staging).  Head dimension 128 holds 64 rows' operands in too many registers for two
+// waves per SIMD and runs 4 waves.
+template <int DH, int RT>
+int row_waves(const Plan &p, int slices) {
+  if (DH == 128) return 4;
+  return (int64_t)slices * ((p.s.nt + 8 * RT - 1) / (8 * RT)) >= 256 ? 8 : 2;
+}
+template <int DH> constexpr int row_tiles() { return DH <= 32 ? 2 : 1; }
+
+template <typename T, int DH, int PT, int MODE>
+void launch_apply(const wersa_desc &c, const Plan &p, const bf16_t *X, const bf16_t *OA, const bf16_t *SB, const float *zpad,
+                  const float *scalars, T *out, View v, float *N, float *D, hipStream_t st) {
+  constexpr int RT = row_tiles<DH>();
+  const int slices = c.B * c.H, nw = row_waves<DH, RT>(p, slices);
+  const dim3 grid((p.s.nt + nw * RT - 1) / (nw * RT), slices);
+  auto go = [&](auto NW) {
+    WERSA_STAGE(MODE == 2 ? "split_apply_dv" : "split_apply", st, apply_kernel<T, DH, PT, MODE, RT, NW.value><<<grid, 64 * NW.value, 0, st>>>(
+        X, OA, SB, zpad, scalars, c.eps, p.s, out, v, N, D));
+  };
+  if constexpr (DH == 128) {
+    go(std::integral_constant<int, 4>());
+  } else {
+    if (nw == 8) go(std::integral_constant<int, 8>());
+    else go(std::integral_constant<int, 2>());
+  }
+}
+template <typename T, int DH, int PT, bool DV>
+void launch_grad(const wersa_desc &c, const Plan &p, const bf16_t *X, const bf16_t *Y, const float *ddw, const float *rowscale,
+                 const bf16_t *OA, const bf16_t *SA, const bf16_t *OB, const bf16_t *SB, const float *scalars, float *dXF,
+                 T *dv, View v, hipStream_t st) {
+  constexpr int RT = DH == 16 && (PT == 1 || !DV) ? 2 : 1;   // (as many token tiles as the registers of two waves per SIMD hold)
+  const int slices = c.B * c.H, nw = row_waves<DH, RT>(p, slices);
+  const dim3 grid((p.s.nt + nw * RT - 1) / (nw * RT), slices);
+  auto go = [&](auto NW) {
+    WERSA_STAGE(DV ? "split_grad_k" : "split_grad", st, grad_kernel<T, DH, PT, DV, RT, NW.value><<<grid, 64 * NW.value, 0, st>>>(
+        X, Y, ddw, rowscale, OA, SA, OB, SB, scalars, p.s, dXF, dv, v));
+  };
+  if constexpr (DH == 128) {
+    go(std::integral_constant<int, 4>());
+  } else {
+    if (nw == 8) go(std::integral_constant<int, 8>());
+    else go(std::integral_constant<int, 2>());
+  }
+}
+
+template <typename T, int DH, int PT>
+wersa_status forward_t(const wersa_desc &c, const T *q, const T *k, const T *v, const T *omega, const float *sigma,
+                       const float *gate_w, const float *gate_b, const float *scale_w, T *out, float *saved, float *ws,
+                       hipStream_t st) {
+  const Plan p = plan_of(c);
+  const Ws w = ws_of(c, p, 0, ws);
+  const SavedLayout sv = saved_layout(c);
+  const int slices = c.B * c.H;
+  const View tv{c.stride_b, c.stride_h, c.stride_n, c.H};
+  const bool deep = c.L > kTileL, ln = (c.flags & WERSA_FLAG_LAYERNORM) != 0;
+  float *scalars = saved + sv.scalars, *coef = saved + sv.coef;
+  bf16_t *XQ = (bf16_t *)(saved + sv.XQ), *XK = (bf16_t *)(saved + sv.XK), *OA = (bf16_t *)(saved + sv.OA),
+         *OB = (bf16_t *)(saved + sv.OB), *SA = (bf16_t *)(saved + sv.SA);
+  const bf16_t *OAk = OA + (p.matrices == 2 ? (int64_t)p.s.mt * p.KS * PT * kTile : 0);
+  float *addQ = deep ? saved + sv.addQ : nullptr, *addK = deep ? saved + sv.addK : nullptr;
+  float *qpart = deep ? saved + sv.tileQ : w.qpart, *kpart = deep ? saved + sv.tileK : nullptr;
+  const int vec = rows_aligned(c, {q, k, v});
+  const int pieces = p.matrices * p.s.mt * 64 * (p.KS + 2 * p.CT);
+  const OmegaPack<T> om{omega, sigma, c.bw_floor, scalars, OA, OB, p.matrices, p.KS, p.CT, PT, (pieces + 255) / 256};
+  WERSA_STAGE("split_pool", st, pool_kernel<T><<<dim3(p.chunks + om.blocks, slices, deep ? 2 : 1), 256, 0, st>>>(
+      q, k, tv, p.s, vec, p.rows_per_chunk, p.chunks, qpart, kpart, om));
+  WERSA_STAGE("gate_fwd_kernel", st, gate_fwd_kernel<<<slices, 256, 0, st>>>(
+      qpart, p.chunks, c.n, c.d, c.L, c.H, gate_w, gate_b, scale_w, saved + sv.qbar, saved + sv.s, saved + sv.F, coef,
+      (c.flags & WERSA_FLAG_POOLED_GATE) ? 1 : 0,
+      PooledLayout{(int64_t)c.H * p.chunks * c.d, (int64_t)p.chunks * c.d, c.d}, nullptr, 0, scalars));
+  if (deep)
+    WERSA_STAGE("split_deep", st, deep_addend_kernel<<<dim3(slices, 2, c.d / kCoarseCols), 1024, 0, st>>>(
+        qpart, kpart, coef, p.ntl, c.d, c.L, w.pyr, addQ, addK));
+  WERSA_STAGE("split_prep_fwd", st, prep_fwd_kernel<T, DH, PT><<<dim3(p.groups, slices, 3), 256, 0, st>>>(
+      q, k, v, tv, p.s, vec, coef, addQ, addK, XQ, XK, w.VC));
+  WERSA_STAGE("split_contract", st, contract_kernel<DH, PT><<<dim3(p.splits, p.s.mt / p.FW, slices), 512, 0, st>>>(
+      XK, w.VC, nullptr, OAk, p.s, p.FW, p.TW, p.tiles_per_split, w.part, w.zpart));
+  WERSA_STAGE("split_reduce", st, reduce_kernel<DH><<<dim3(p.s.mt, slices), 256, 0, st>>>(
+      w.part, w.zpart, p.shares, 1, scalars, p.s, saved + sv.S, saved + sv.z, w.zpad, SA, w.SB));
+  if (ln) {
+    launch_apply<T, DH, PT, 1>(c, p, XQ, OA, w.SB, w.zpad, scalars, out, tv, w.Nbuf, nullptr, st);
+    WERSA_STAGE("split_ln", st, ln_out_kernel<T><<<dim3((c.n + 3) / 4, slices), 256, 0, st>>>(w.Nbuf, out, tv, c.n, c.d, c.eps, saved + sv.D));
+  } else {
+    launch_apply<T, DH, PT, 0>(c, p, XQ, OA, w.SB, w.zpad, scalars, out, tv, nullptr, saved + sv.D, st);
+  }
+  return hipGetLastError() == hipSuccess ? WERSA_OK : WERSA_ERR_LAUNCH;
+}
+
+template <typename T, int DH, int PT>
+wersa_status backward_t(const wersa_desc &c, const T *q, const T *k, const T *v, const float *gate_w, const float *scale_w,
+                        const T *out, const T *dout, const float *saved, T *dq, T *dk, T *dv, float *dgate_w, float *dgate_b,
+                        float *dscale_w, float *dsigma, float *ws, hipStream_t st) {
+  const Plan p = plan_of(c);
+  const Ws w = ws_of(c, p, 1, ws);
+  const SavedLayout sv = saved_layout(c);
+  const int slices = c.B * c.H;
+  const View tv{c.stride_b, c.stride_h, c.stride_n, c.H};
+  const bool deep = c.L > kTileL, ln = (c.flags & WERSA_FLAG_LAYERNORM) != 0;
+  const float *scalars = saved + sv.scalars, *coef = saved + sv.coef;
+  const bf16_t *XQ = (const bf16_t *)(saved + sv.XQ), *XK = (const bf16_t *)(saved + sv.XK), *OA = (const bf16_t *)(saved + sv.OA),
+               *OB = (const bf16_t *)(saved + sv.OB), *SA = (const bf16_t *)(saved + sv.SA);
+  const int64_t two = p.matrices == 2 ? p.s.mt : 0;
+  const bf16_t *OAk = OA + two * p.KS * PT * kTile, *OBk = OB + two * 2 * p.CT * PT * kTile;
+  const int vec = rows_aligned(c, {v, out, dout});
+  WERSA_STAGE("split_prep_bwd", st, prep_bwd_kernel<T, DH, PT><<<dim3(p.bgroups, slices), 256, 0, st>>>(
+      dout, out, v, tv, p.s, vec, ln, saved + sv.D, XQ, w.NR, w.NC, w.VR, w.XS, w.ddw, w.rowscale, w.dpart));
+  WERSA_STAGE("split_contract", st, contract_kernel<DH, PT><<<dim3(p.splits, p.s.mt / p.FW, slices), 512, 0, st>>>(
+      PT == 1 ? w.XS : XQ, w.NC, w.ddw, OA, p.s, p.FW, p.TW, p.tiles_per_split, w.part, w.zpart));
+  WERSA_STAGE("split_reduce", st, reduce_kernel<DH><<<dim3(p.s.mt, slices), 256, 0, st>>>(
+      w.part, w.zpart, p.shares, PT == 1 ? 3 : 1, scalars, p.s, w.dS, w.dz, w.zpad, w.dSA, w.dSB));
+  if constexpr (DH == 128) {   // (dV on its own: no registers left for its accumulators)
+    launch_grad<T, DH, PT, false>(c, p, XK, w.VR, nullptr, nullptr, OAk, w.dSA, OBk, nullptr, scalars, w.gk, nullptr, tv, st);
+    launch_apply<T, DH, PT, 2>(c, p, XK, OAk, w.dSB, w.zpad, scalars, dv, tv, nullptr, nullptr, st);
+  } else {
+    launch_grad<T, DH, PT, true>(c, p, XK, w.VR, nullptr, nullptr, OAk, w.dSA, OBk, w.dSB, scalars, w.gk, dv, tv, st);
+  }
+  launch_grad<T, DH, PT, false>(c, p, XQ, w.NR, w.ddw, PT == 1 ? w.rowscale : nullptr, OA, SA, OB, nullptr, scalars, w.gq,
+                                nullptr, tv, st);
+  const int prow = p.groups + (deep ? c.d / kCoarseCols : 0);
+  WERSA_STAGE("split_dots", st, dots_kernel<T, DH><<<dim3(p.groups, slices, 2), 256, 0, st>>>(
+      q, k, tv, w.gq, w.gk, p.s, c.L, prow, w.partQ, w.partK, w.tgq, w.tgk));
+  if (deep)
+    WERSA_STAGE("split_deep", st, deep_bwd_kernel<<<dim3(slices, 2, c.d / kCoarseCols), 1024, 0, st>>>(
+        w.tgq, w.tgk, saved + sv.tileQ, saved + sv.tileK, coef, p.ntl, c.d, c.L, w.pyr, w.aq, w.ak, w.partQ, w.partK, p.groups));
+  WERSA_STAGE("gate_bwd_slice_kernel", st, gate_bwd_slice_kernel<<<slices, kGateBwdThreads, 0, st>>>(
+      w.partQ, w.partK, prow, c.L, c.d, c.H, saved + sv.s, gate_w, scale_w, w.dF, w.dlogit, w.dqbar,
+      (c.flags & WERSA_FLAG_POOLED_GATE) ? 1 : 0));
+  WERSA_STAGE("gate_bwd_params_kernel", st, gate_bwd_params_kernel<<<gate_bwd_params_blocks(c.H, c.L, c.d), 256, 0, st>>>(
+      w.dF, w.dlogit, saved + sv.s, saved + sv.qbar, w.dpart, slices * p.bgroups, c.B, c.H, c.L, c.d, c.eps, scalars, dgate_w,
+      dgate_b, dscale_w, dsigma));
+  const View gv{(int64_t)p.s.nt * 32 * DH, 0, DH, 1};
+  WERSA_STAGE("split_filter_bwd", st, filter_kernel<float, T, DH><<<dim3(p.groups, slices, 2), 256, 0, st>>>(
+      FilterJob{w.gq, dq, w.aq, w.dqbar}, FilterJob{w.gk, dk, w.ak, nullptr}, gv, tv, p.s, coef, 0, c.L, 1.0f / (float)c.n));
+  return hipGetLastError() == hipSuccess ? WERSA_OK : WERSA_ERR_LAUNCH;
+}
+
+// Calls f(element type tag, head dimension, terms) of the instance that serves the descriptor.
+template <typename F>
+wersa_status dispatch(const wersa_desc &c, F f) {
+  using std::integral_constant;
+  const int DH = dh_of(c.d), PT = terms_of(c);
+  auto by_dh = [&](auto tag) -> wersa_status {
+    using T = decltype(tag);
+    if constexpr (sizeof(T) == 2) {
+      if (PT == 1) return DH == 16 ? f(tag, integral_constant<int, 16>(), integral_constant<int, 1>())
+                                   : f(tag, integral_constant<int, 32>(), integral_constant<int, 1>());
+    }
+    switch (DH) {
+      case 16: return f(tag, integral_constant<int, 16>(), integral_constant<int, 3>());
+      case 32: return f(tag, integral_constant<int, 32>(), integral_constant<int, 3>());
+      case 64: return f(tag, integral_constant<int, 64>(), integral_constant<int, 3>());
+      default: return f(tag, integral_constant<int, 128>(), integral_constant<int, 3>());
+    }
+  };
+  return c.dtype == WERSA_F32 ? by_dh(float()) : by_dh(bf16_t());
+}
+
+}  // namespace
+
+SplitSizes split_sizes(const wersa_desc &c) {
+  const Plan p = plan_of(c);
+  const int64_t sl = (int64_t)c.B * c.H;
+  // (one feature tile more than there are: a stage of the row kernels reads whole groups of them)
+  return SplitSizes{tile_floats(sl * p.s.nt * p.KS * 3), tile_floats((int64_t)(p.matrices * p.s.mt + 1) * p.KS * p.PT),
+                    tile_floats((int64_t)(p.matrices * p.s.mt + 1) * 2 * p.CT * p.PT),
+                    tile_floats((sl * p.s.mt + 1) * (3 * p.KS + 1))};
+}
+size_t split_workspace_bytes(const wersa_desc &c, int for_backward) {
+  return (size_t)ws_of(c, plan_of(c), for_backward, nullptr).total * sizeof(float);
+}
+wersa_status split_forward(const wersa_desc &c, const void *q, const void *k, const void *v, const void *omega_rf,
+                           const float *sigma, const float *gate_w, const float *gate_b, const float *scale_w, void *out,
+                           float *saved, float *ws, hipStream_t st) {
+  return dispatch(c, [&](auto tag, auto DH, auto PT) {
+    using T = decltype(tag);
+    return forward_t<T, DH.value, PT.value>(c, (const T *)q, (const T *)k, (const T *)v, (const T *)omega_rf, sigma, gate_w,
+                                            gate_b, scale_w, (T *)out, saved, ws, st);
+  });
+}
+wersa_status split_backward(const wersa_desc &c, const void *q, const void *k, const void *v, const float *gate_w,
+                            const float *scale_w, const void *out, const void *dout, const float *saved, void *dq, void *dk,
+                            void *dv, float *dgate_w, float *dgate_b, float *dscale_w, float *dsigma, float *ws,
+                            hipStream_t st) {
+  return dispatch(c, [&](auto tag, auto DH, auto PT) {
+    using T = decltype(tag);
+    return backward_t<T, DH.value, PT.value>(c, (const T *)q, (const T *)k, (const T *)v, gate_w, scale_w, (const T *)out,
+                                             (const T *)dout, saved, (T *)dq, (T *)dk, (T *)dv, dgate_w, dgate_b, dscale_w,
+                                             dsigma, ws, st);
+  });
+}
+
+}  // namespace wersa

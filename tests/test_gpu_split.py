@@ -1,0 +1,79 @@
+"""Split path (float32 arithmetic on the bf16 matrix cores: three bf16 terms per float32 operand) at the sizes
+where its kernels change shape: head dimensions padded to 16, 32, 64, 128; feature counts that are not whole
+32-feature tiles, or an odd number of them; token counts around the 32- and 64-row tiles and the
+4096-element workgroups; few rows (2-wave workgroups) and many (8 waves); rows that are not 16-byte aligned."""
+import numpy as np
+import pytest
+
+from tests import helpers as hp
+from paper_2507_08637_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+# O, S, z and D against float64: operands exact to 2^-24 and accumulators rounded at most some thousand times, which
+# adds up like a random walk: 2^-24 * sqrt(1000) = 1.9e-6.
+SUMS = 2e-6
+
+
+def _grad_tol(cfg):
+    """The float32 bar of the library, 1e-4, unless pre-activations within a few rounding errors of zero (a share of
+    about 2e-7 of them) are to be expected in a problem of this size: each that takes the other side of the ReLU's
+    step changes its row by one of about m / 2 terms, a share 2 / m of the row's squared norm."""
+    if cfg["dtype"] == "bf16":
+        return 2e-2
+    rows = cfg["B"] * cfg["H"] * cfg["n"]
+    flips = 2e-7 * rows * cfg["m"]
+    return 1e-4 if flips < 0.1 else max(1e-4, ((4 + 4 * flips) * (2 / cfg["m"]) / rows) ** 0.5)
+
+
+SHAPES = [
+    dict(B=1, H=1, n=65, d=16, L=2, m=16),       # half a feature tile; one row past a 64-row block
+    dict(B=2, H=3, n=257, d=16, L=5, m=544),     # 17 feature tiles: every wave of the contraction takes the same one; one row past 256
+    dict(B=1, H=2, n=31, d=32, L=1, m=96),       # less than one token tile; three feature tiles
+    dict(B=1, H=2, n=129, d=48, L=6, m=64),      # columns padded to 64, two feature tiles
+    dict(B=2, H=1, n=2300, d=64, L=9, m=256),    # levels above one tile, ragged
+    dict(B=1, H=2, n=97, d=112, L=3, m=160),     # columns padded to 128, five feature tiles
+    dict(B=1, H=1, n=700, d=128, L=7, m=48),
+    dict(B=16, H=16, n=520, d=16, L=3, m=64),    # 8-wave workgroups, the last one partly idle
+    dict(B=16, H=16, n=260, d=32, L=4, m=128),
+    dict(B=16, H=16, n=200, d=64, L=0, m=32),
+]
+
+
+def _check(res, ref, fwd, cfg):
+    grads = _grad_tol(cfg)
+    for k in ("S", "z", "D"):
+        assert hp.rel_err(res["saved"][k], fwd[k].reshape(res["saved"][k].shape)) < SUMS, k
+    assert hp.rel_err(res["O"], ref["O"]) < (SUMS if cfg["dtype"] == "f32" else 4e-3), "O"   # bf16: rounded once, by 2^-9 at most
+    for k in ("dQ", "dK", "dV") + (("dWg", "dbg") if cfg["L"] and cfg["dtype"] == "f32" else ()):
+        assert hp.rel_err(res[k], ref[k]) < grads, k
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "B{B}H{H}n{n}d{d}L{L}m{m}".format(**s))
+def test_split_path_shapes(shape, dtype):
+    cfg = dict(shape, dtype=dtype, flavour="plain", seed_base=5100, q_mean=0.5)
+    p = workloads.make_inputs(**cfg)
+    res = hp.gpu_forward_backward(p, cfg, flags=1)
+    _check(res, hp.oracle_backward(p, cfg), hp.oracle_forward(p, cfg), cfg)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_split_path_rows_off_16_byte_alignment(dtype):
+    """A row stride of d + 1 elements: every load of the packing kernels falls back to single elements, same bits."""
+    import torch
+    from paper_2507_08637_amd import binding
+    cfg = dict(B=1, H=2, n=200, d=32, L=3, m=64, dtype=dtype, flavour="plain", seed_base=5200, q_mean=0.5)
+    t = hp.to_device(workloads.make_inputs(**cfg), dtype)
+    outs = []
+    for pad in (0, 1):
+        def lay(x):
+            y = torch.zeros(*x.shape[:3], x.shape[3] + pad, dtype=x.dtype, device=x.device)[..., :x.shape[3]]
+            return y.copy_(x)
+        q, k, v, do = (lay(t[name]) for name in ("Q", "K", "V", "dO"))
+        par = (t["Omega"], t["sigma"], t["Wg"], t["bg"], t["omega"])
+        out, saved = binding.wersa_forward(q, k, v, *par, cfg["L"], flags=1)
+        g = binding.wersa_backward(q, k, v, *par, out, do, saved, cfg["L"], flags=1)
+        outs.append([out, g["dq"], g["dk"], g["dv"], g["dgate_w"]])
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
