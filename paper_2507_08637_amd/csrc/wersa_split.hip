@@ -55,14 +55,8 @@ __device__ __forceinline__ float xor32_sum(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Split of eight floats.  The residual x - x0 is one pair dot product with (-1, 0) or (0, -1): exact,
-// since both products and the difference are representable.  (The constants pass through registers the compiler
-// does not look into: it would encode the first one as the inline constant -1.0, whose set bits the
-// instruction finds in the upper half.)
+// Split of eight floats.
 __device__ __forceinline__ void split8(const float *v, bf16x8 *t) {
-  unsigned int ulo = 0x0000bf80u, uhi = 0xbf800000u;
-  asm("" : "+s"(ulo), "+s"(uhi));
-  const bf16x2 lo = __builtin_bit_cast(bf16x2, ulo), hi = __builtin_bit_cast(bf16x2, uhi);
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     f32x2 x;
@@ -73,19 +67,73 @@ __device__ __forceinline__ void split8(const float *v, bf16x8 *t) {
       const bf16x2 p = __builtin_convertvector(x, bf16x2);
       t[i][2 * j] = p[0];
       t[i][2 * j + 1] = p[1];
-      if (i < 2) {
-        x[0] = __builtin_amdgcn_fdot2_f32_bf16(p, lo, x[0], false);
-        x[1] = __builtin_amdgcn_fdot2_f32_bf16(p, hi, x[1], false);
-      }
+      x[0] -= (float)p[0];
+      x[1] -= (float)p[1];
     }
   }
 }
-__device__ __forceinline__ void split_half(const f32x16 &acc, int a, bf16x8 *t) {
-  float v[8];
+// Split of an accumulator tile into operands (t[a][i]: half a, term i).  The vector units take 5.5 instructions per
+// element for it, most of them for the two residuals x - x0 and x - x0 - x1.  LV of these come from the matrix
+// cores instead: x - bf16(x) is the accumulator plus the product of the packed term with a negated identity
+// matrix whose columns are in the order of the k-slots, two instructions for the 16 values per lane, and exact (one
+// non-zero product per element).  Measured (one SIMD, four waves): a matrix instruction takes 32 cycles of its
+// own pipe and keeps the vector units from issuing for about 15, a vector instruction takes 4; a pair dot
+// product (v_dot2c_f32_bf16, which would do a residual in one instruction) does not run beside matrix
+// instructions at all.
+struct NegIdentity {
+  bf16x8 half[2];
+  __device__ __forceinline__ explicit NegIdentity(int lane) {
 #pragma unroll
-  for (int q = 0; q < 8; ++q) v[q] = acc[8 * a + q];
-  split8(v, t);
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        half[a][q] = (__bf16)((lane & 31) == 16 * a + 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3) ? -1.f : 0.f);
+  }
+};
+// Calls use(a, terms) for both halves.
+template <int LV, typename F>
+__device__ __forceinline__ void with_split(f32x16 x, const NegIdentity &ni, F use) {
+  if (LV == 0) {   // one half at a time: fewer registers
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      float v[8];
+      bf16x8 t[3];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = x[8 * a + q];
+      split8(v, t);
+      use(a, t);
+    }
+    return;
+  }
+  bf16x8 t[2][3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        f32x2 f;
+        f[0] = x[8 * a + 2 * j];
+        f[1] = x[8 * a + 2 * j + 1];
+        const bf16x2 p = __builtin_convertvector(f, bf16x2);
+        t[a][i][2 * j] = p[0];
+        t[a][i][2 * j + 1] = p[1];
+        if (i < 2 && i >= LV) {
+          x[8 * a + 2 * j] -= (float)p[0];
+          x[8 * a + 2 * j + 1] -= (float)p[1];
+        }
+      }
+    if (i < LV) {
+      x = mfma(ni.half[0], t[0][i], x);
+      x = mfma(ni.half[1], t[1][i], x);
+    }
+  }
+  use(0, t[0]);
+  use(1, t[1]);
 }
+// Residuals left to the matrix cores, by what is idle: with head dimensions 16 and 32 the contractions are too short to
+// fill them.
+constexpr int mfma_residuals(int DH, int PT) { return DH == 16 || (DH == 32 && PT == 1) ? 2 : 0; }
 __device__ __forceinline__ void split1(float x, __bf16 *t) {
   t[0] = (__bf16)x;
   const float r = x - (float)t[0];
@@ -115,9 +163,18 @@ __device__ __forceinline__ f32x16 mfma_terms(f32x16 acc, const bf16x8 *x, const 
 __device__ __forceinline__ bf16x8 lds_operand(const bf16_t *tile, int lane) {
   return *reinterpret_cast<const bf16x8 *>(tile + lane * 8);
 }
+// All loads from memory have arrived.  Before a loop that requests its next stage first and works on operands loaded
+// before it: the compiler would otherwise wait, in the loop, for those and with them for the stage just requested.
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 __device__ __forceinline__ void store_operand(bf16_t *tile, int lane, bf16x8 v) {
   *reinterpret_cast<bf16x8 *>(tile + lane * 8) = v;
 }
+
+// 1 where x > 0, else 0 (also for NaN), exact for every float: one multiplication with output clamp.  With
+// additions and plain moves it runs at twice the rate of the other vector instructions (measured: 2 cycles against 4).
+__device__ __forceinline__ float positive(float x) { return __builtin_amdgcn_fmed3f(x * __builtin_inff(), 0.f, 1.f); }
+// As integers, negative floats are negative: one instruction (fmaxf is two: it quiets a NaN first).
+__device__ __forceinline__ float relu(float x) { return __int_as_float(max(__float_as_int(x), 0)); }
 
 // Eight consecutive elements as float; vec: the tensor's rows are 16-byte aligned.
 __device__ __forceinline__ void load8(const float *p, bool vec, float *v) {
@@ -264,7 +321,26 @@ template <int DH>
 struct Geo {
   static constexpr int KS = DH / 16, CT = DH < 32 ? 1 : DH / 32, CW = DH < 64 ? DH : 64, TR = 4096 / CW,
                        PIECES = DH / CW, LS = CW + 4, SEGS = 256 / CW;
+  // Operand tiles per feature tile of S with its columns as vectors.  Head dimension 16 leaves half of the 32 columns
+  // free: [S0 | S1] and [S2 | 0] take four products instead of six (see apply_terms).
+  static constexpr int NSB = DH == 16 ? 4 : 6 * CT;
 };
+// acc + Phi S for one half of a feature tile and one column tile; sb: the operand tiles of S from lds_operand.
+template <int DH>
+__device__ __forceinline__ f32x16 apply_terms(f32x16 acc, const bf16x8 *p, const bf16_t *sb, int a, int ct, int lane) {
+  if (DH == 16) {   // columns 0-15: p0 S2 + (p2 + p1 + p0) S0; columns 16-31: (p2 + p1 + p0) S1; added at the end
+    const bf16x8 s01 = lds_operand(sb + 2 * a * kTile, lane), s2 = lds_operand(sb + (2 * a + 1) * kTile, lane);
+    acc = mfma(p[0], s2, acc);
+    acc = mfma(p[2], s01, acc);
+    acc = mfma(p[1], s01, acc);
+    return mfma(p[0], s01, acc);
+  }
+  constexpr int CT = DH < 32 ? 1 : DH / 32;
+  bf16x8 y[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) y[i] = lds_operand(sb + ((a * CT + ct) * 3 + i) * kTile, lane);
+  return mfma_terms<3, false>(acc, p, y);
+}
 // sum over the levels above four of coef_l * (block sum): levels 5 and 6 from the 16-row sums of a tile
 template <int CW>
 __device__ __forceinline__ float upper_levels(const float (*segsum)[CW], const float *cf, int seg, int c) {
@@ -514,15 +590,17 @@ __global__ __launch_bounds__(256) void prep_bwd_kernel(const T *dout, const T *o
 // tiles of a stage in turn (each group a share of its own).  X and Y go through LDS, one stage of SG token
 // tiles ahead in registers; Omega stays in registers.  Grid (splits, feature tiles / FW, slices).
 // ------------------------------------------------------------------------------------
-constexpr int stage_tokens(int DH) { return DH <= 32 ? 4 : (DH == 64 ? 2 : 1); }   // (in 32-row tiles)
+// Token tiles (32 rows) per stage: the double-buffered stage stays below 100 KiB of LDS, and below 50 KiB where that lets
+// the registers of a second workgroup in (head dimension 32 with three terms: 359 -> 334 us with half the stage).
+constexpr int stage_tokens(int DH, int PT) { return DH == 128 ? 1 : (DH == 64 || (DH == 32 && PT == 3) ? 2 : 4); }
 template <int DH, int PT>
 __global__ __launch_bounds__(512, 2) void contract_kernel(const bf16_t *X, const bf16_t *Y, const float *w, const bf16_t *OA,
                                                          Dims s, int FW, int TW, int tiles_per_split, float *part, float *zpart) {
   using G = Geo<DH>;
-  constexpr int SG = stage_tokens(DH), NX = G::KS * 3, NY = 2 * G::CT * PT, NS = SG * (NX + NY),
-                U = (NS + 7) / 8;
+  constexpr int SG = stage_tokens(DH, PT), NX = G::KS * 3, NY = 2 * G::CT * PT, NS = SG * (NX + NY),
+                NW = 8, U = (NS + NW - 1) / NW;
   __shared__ __attribute__((aligned(16))) bf16_t lds[2][NS * kTile];
-  __shared__ float lw[2][SG * 32];
+  __shared__ __attribute__((aligned(16))) float lw[2][SG * 32];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slice = blockIdx.z, fw = wave % FW, tw = wave / FW;
@@ -536,36 +614,32 @@ __global__ __launch_bounds__(512, 2) void contract_kernel(const bf16_t *X, const
     for (int i = 0; i < PT; ++i) om[ks][i] = lds_operand(OA + (((int64_t)ft * G::KS + ks) * PT + i) * kTile, lane);
   u32x4 st[U];
   float stw = 0.f;
-  auto fetch = [&](int tb) {   // tiles past the end of the slice are clamped (never used)
-    const int last = s.nt - 1;
+  auto fetch = [&](int tb) {   // (consecutive token tiles are contiguous; what lies past the slice is clamped and not used)
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int i = wave + 8 * u;
-      if (i < NS) {
-        const bool isx = i < SG * NX;
-        const int j = isx ? i : i - SG * NX, per = isx ? NX : NY;
-        const int tt = min(tb + j / per, last);
-        const bf16_t *src = (isx ? xs : ys) + ((int64_t)tt * per + j % per) * kTile;
-        st[u] = *reinterpret_cast<const u32x4 *>(src + lane * 8);
-      }
+      const int i = min(wave + NW * u, NS - 1);   // (no branch: a last tile may be moved twice)
+      const int64_t tile = i < SG * NX ? min(tb * NX + i, s.nt * NX - 1) : min(tb * NY + i - SG * NX, s.nt * NY - 1);
+      st[u] = *reinterpret_cast<const u32x4 *>((i < SG * NX ? xs : ys) + tile * kTile + lane * 8);
     }
-    if (DH > 16 && w && tid < SG * 32) stw = w[(int64_t)slice * s.nt * 32 + min(tb * 32 + tid, s.nt * 32 - 1)];
+    if (DH > 16 && w) stw = w[(int64_t)slice * s.nt * 32 + min(tb * 32 + (tid & (SG * 32 - 1)), s.nt * 32 - 1)];
   };
   auto put = [&](int b) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int i = wave + 8 * u;
-      if (i < NS) *reinterpret_cast<u32x4 *>(&lds[b][i * kTile + lane * 8]) = st[u];
+      const int i = min(wave + NW * u, NS - 1);
+      *reinterpret_cast<u32x4 *>(&lds[b][i * kTile + lane * 8]) = st[u];
     }
-    if (DH > 16 && tid < SG * 32) lw[b][tid] = w ? stw : 1.f;
+    if (DH > 16) lw[b][tid & (SG * 32 - 1)] = w ? stw : 1.f;
   };
   f32x16 acc[G::CT];
 #pragma unroll
   for (int ct = 0; ct < G::CT; ++ct) acc[ct] = zero16();
   float zacc = 0.f;
+  const NegIdentity ni(lane);
   if (tb0 < tb1) {
     fetch(tb0);
     put(0);
+    wait_loads();
     __syncthreads();
     int b = 0;
     for (int tb = tb0; tb < tb1; tb += SG, b ^= 1) {
@@ -582,7 +656,7 @@ __global__ __launch_bounds__(512, 2) void contract_kernel(const bf16_t *X, const
           R = mfma_terms<PT, false>(R, x, om[ks]);   // rows: tokens, columns (lanes): features
         }
 #pragma unroll
-        for (int i = 0; i < 16; ++i) R[i] = fmaxf(R[i], 0.f);
+        for (int i = 0; i < 16; ++i) R[i] = relu(R[i]);
         if (DH > 16) {
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
@@ -591,10 +665,7 @@ __global__ __launch_bounds__(512, 2) void contract_kernel(const bf16_t *X, const
             for (int i = 0; i < 4; ++i) zacc = fmaf(R[4 * j + i], w4[i], zacc);
           }
         }
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-          bf16x8 p[3];
-          split_half(R, a, p);
+        with_split<mfma_residuals(DH, PT)>(R, ni, [&](int a, const bf16x8 *p) {
 #pragma unroll
           for (int ct = 0; ct < G::CT; ++ct) {
             bf16x8 y[PT];
@@ -602,7 +673,7 @@ __global__ __launch_bounds__(512, 2) void contract_kernel(const bf16_t *X, const
             for (int i = 0; i < PT; ++i) y[i] = lds_operand(ly + ((a * G::CT + ct) * PT + i) * kTile, lane);
             acc[ct] = mfma_terms<PT, false>(acc[ct], p, y);   // rows: features, columns: columns of Y
           }
-        }
+        });
       }
       if (more) put(b ^ 1);
       __syncthreads();
@@ -668,7 +739,6 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float *part, const fl
     float acc = 0.f;
     for (int j = zcols - 1; j >= 0; --j) acc += tile[tid * LS + 16 + j];
     zt[tid] = acc;
-    tile[tid * LS + 16] = acc;   // (column 16 of the operand: the normaliser's column)
   }
   __syncthreads();
   for (int e = tid; e < 32 * s.d; e += 256) {
@@ -680,7 +750,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float *part, const fl
     zpad[((int64_t)slice * s.mt + ft) * 32 + tid] = zt[tid];
   }
   bf16_t *sa = SA + ((int64_t)slice * s.mt + ft) * (3 * G::KS + 1) * kTile;
-  bf16_t *sb = SB + ((int64_t)slice * s.mt + ft) * 6 * G::CT * kTile;
+  bf16_t *sb = SB + ((int64_t)slice * s.mt + ft) * G::NSB * kTile;
   for (int p = tid; p < 64 * (G::KS + 1 + 2 * G::CT); p += 256) {
     const int lane = p & 63, which = p >> 6, l32 = lane & 31, h = lane >> 5;
     bf16x8 t[3];
@@ -702,12 +772,17 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float *part, const fl
       float x[8];
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
-        const float val = tile[(16 * a + 8 * (q >> 2) + 4 * h + (q & 3)) * LS + cc];
-        x[q] = (DH == 16 && cc > 16) ? 0.f : val;
+        x[q] = tile[(16 * a + 8 * (q >> 2) + 4 * h + (q & 3)) * LS + (DH == 16 ? cc & 15 : cc)];
       }
       split8(x, t);
+      if (DH == 16) {
+        const bf16x8 none = {};
+        store_operand(sb + 2 * a * kTile, lane, cc < 16 ? t[0] : t[1]);
+        store_operand(sb + (2 * a + 1) * kTile, lane, cc < 16 ? t[2] : none);
+      } else {
 #pragma unroll
-      for (int i = 0; i < 3; ++i) store_operand(sb + ((a * G::CT + ct) * 3 + i) * kTile, lane, t[i]);
+        for (int i = 0; i < 3; ++i) store_operand(sb + ((a * G::CT + ct) * 3 + i) * kTile, lane, t[i]);
+      }
     }
   }
 }
@@ -726,36 +801,38 @@ struct Stager {
   __device__ __forceinline__ void fetch(int ft, int wave, int lane) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int i = wave + NW * u;
-      if (i < NS) {
-        const bf16_t *src = i < O1   ? p0 + ((int64_t)ft * N0 + i) * kTile
-                            : i < O2 ? p1 + ((int64_t)ft * N1 + (i - O1)) * kTile
-                            : i < O3 ? p2 + ((int64_t)ft * N2 + (i - O2)) * kTile
-                                     : p3 + ((int64_t)ft * N3 + (i - O3)) * kTile;
-        st[u] = *reinterpret_cast<const u32x4 *>(src + lane * 8);
-      }
+      const int i = min(wave + NW * u, NS - 1);   // (no branch: a last tile may be moved twice)
+      const bf16_t *src = i < O1   ? p0 + ((int64_t)ft * N0 + i) * kTile
+                          : i < O2 ? p1 + ((int64_t)ft * N1 + (i - O1)) * kTile
+                          : i < O3 ? p2 + ((int64_t)ft * N2 + (i - O2)) * kTile
+                                   : p3 + ((int64_t)ft * N3 + (i - O3)) * kTile;
+      st[u] = *reinterpret_cast<const u32x4 *>(src + lane * 8);
     }
   }
   __device__ __forceinline__ void put(bf16_t *lds, int wave, int lane) const {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int i = wave + NW * u;
-      if (i < NS) *reinterpret_cast<u32x4 *>(&lds[i * kTile + lane * 8]) = st[u];
+      const int i = min(wave + NW * u, NS - 1);
+      *reinterpret_cast<u32x4 *>(&lds[i * kTile + lane * 8]) = st[u];
     }
   }
 };
 
+// Waves per SIMD that the register budget is set for.
+constexpr int row_occupancy(int DH, int NW) { return NW >= 4 && DH < 128 ? 2 : 1; }
+
 // MODE 0: O = (Phi S) / (Phi z + eps) and D.   1: N = Phi S in float32 (LayerNorm follows).
 // MODE 2: dV = Phi_K dS.     X: operand tiles of Q_F or K_F.  Grid (row groups, slices).
 template <typename T, int DH, int PT, int MODE, int RT, int NW>
-__global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void apply_kernel(const bf16_t *X, const bf16_t *OA, const bf16_t *SB,
+__global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(const bf16_t *X, const bf16_t *OA, const bf16_t *SB,
                                                                        const float *zpad, const float *scalars, float eps,
                                                                        Dims s, T *out, View v, float *N, float *D) {
   using G = Geo<DH>;
-  constexpr int FC = DH <= 32 ? 2 : 1, NA = G::KS * PT, NB = 6 * G::CT;
-  constexpr bool ZV = MODE == 0 && DH > 16;   // normaliser on the vector units (head dimension 16: column 16 of S)
+  constexpr int FC = DH <= 32 ? 2 : 1, NA = G::KS * PT, NB = G::NSB;
+  constexpr bool ZV = MODE == 0;   // the normaliser, on the vector units
   typedef Stager<NA, NB, 0, 0, FC, NW> Stg;
   __shared__ __attribute__((aligned(16))) bf16_t lds[2][Stg::NS * kTile];
+  __shared__ __attribute__((aligned(16))) float lz[2][ZV ? FC * 32 : 1];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slice = blockIdx.y, tb0 = (blockIdx.x * NW + wave) * RT;
@@ -780,14 +857,23 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void apply_kernel(const b
 #pragma unroll
     for (int ct = 0; ct < G::CT; ++ct) acc[r][ct] = zero16();
   }
-  const float *zs = zpad + (int64_t)slice * s.mt * 32 + 4 * h;
+  const NegIdentity ni(lane);
+  const float *zs = zpad + (int64_t)slice * s.mt * 32;
+  const int zi = tid & (FC * 32 - 1);
+  float zr = 0.f;
   sg.fetch(0, wave, lane);
+  if (ZV) zr = zs[min(zi, s.mt * 32 - 1)];
   sg.put(lds[0], wave, lane);
+  if (ZV) lz[0][zi] = zr;
+  wait_loads();
   __syncthreads();
   int b = 0;
   for (int f0 = 0; f0 < s.mt; f0 += FC, b ^= 1) {
     const bool more = f0 + FC < s.mt;
-    if (more) sg.fetch(f0 + FC, wave, lane);
+    if (more) {
+      sg.fetch(f0 + FC, wave, lane);
+      if (ZV) zr = zs[min((f0 + FC) * 32 + zi, s.mt * 32 - 1)];
+    }
 #pragma unroll
     for (int fi = 0; fi < FC; ++fi) {
       if (f0 + fi >= s.mt) break;
@@ -795,7 +881,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void apply_kernel(const b
       f32x4 z4[4];
       if (ZV)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) z4[j] = *reinterpret_cast<const f32x4 *>(zs + (f0 + fi) * 32 + 8 * j);
+        for (int j = 0; j < 4; ++j) z4[j] = *reinterpret_cast<const f32x4 *>(&lz[b][fi * 32 + 8 * j + 4 * h]);
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
         f32x16 R = zero16();
@@ -807,28 +893,24 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void apply_kernel(const b
           R = mfma_terms<PT, true>(R, x[r][ks], o);   // rows: features, lanes: tokens
         }
 #pragma unroll
-        for (int i = 0; i < 16; ++i) R[i] = fmaxf(R[i], 0.f);
+        for (int i = 0; i < 16; ++i) R[i] = relu(R[i]);
         if (ZV)
 #pragma unroll
           for (int i = 0; i < 16; ++i) dsum[r] = fmaf(R[i], z4[i >> 2][i & 3], dsum[r]);
+        with_split<mfma_residuals(DH, PT)>(R, ni, [&](int a, const bf16x8 *p) {
 #pragma unroll
-        for (int a = 0; a < 2; ++a) {
-          bf16x8 p[3];
-          split_half(R, a, p);
-#pragma unroll
-          for (int ct = 0; ct < G::CT; ++ct) {
-            bf16x8 y[3];
-#pragma unroll
-            for (int i = 0; i < 3; ++i) y[i] = lds_operand(lb + ((a * G::CT + ct) * 3 + i) * kTile, lane);
-            acc[r][ct] = mfma_terms<3, false>(acc[r][ct], p, y);   // rows: tokens, lanes: columns
-          }
-        }
+          for (int ct = 0; ct < G::CT; ++ct) acc[r][ct] = apply_terms<DH>(acc[r][ct], p, lb, a, ct, lane);   // rows: tokens, lanes: columns
+        });
       }
     }
-    if (more) sg.put(lds[b ^ 1], wave, lane);
+    if (more) {
+      sg.put(lds[b ^ 1], wave, lane);
+      if (ZV) lz[b ^ 1][zi] = zr;
+    }
     __syncthreads();
   }
   const float c = scalars[0];
+  T *const ob = MODE == 1 ? nullptr : out + v.slice_base(slice);
 #pragma unroll
   for (int r = 0; r < RT; ++r) {
     const int tb = tb0 + r;
@@ -840,17 +922,15 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void apply_kernel(const b
     for (int i = 0; i < 16; ++i) {
       const int row = 8 * (i >> 2) + 4 * h + (i & 3), t = 32 * tb + row;
       float Dt = 1.f;
-      if (MODE == 0) {
-        Dt = ZV ? __shfl(Dl, row, 64) : fmaf(c, __shfl(acc[r][0][i], (lane & 32) | 16, 64), eps);
-        if (!ZV && l32 == 16 && t < s.n) D[(int64_t)slice * s.n + t] = Dt;
-      }
+      if (ZV) Dt = __shfl(Dl, row, 64);
+      if (DH == 16) acc[r][0][i] += __shfl_xor(acc[r][0][i], 16, 64);
 #pragma unroll
       for (int ct = 0; ct < G::CT; ++ct) {
         const int col = 32 * ct + l32;
         if (t < s.n && col < s.d) {
           const float val = c * acc[r][ct][i];
           if (MODE == 1) N[((int64_t)slice * s.n + t) * s.d + col] = val;
-          else st(out + v.slice_base(slice) + (int64_t)t * v.sn + col, MODE == 0 ? val / Dt : val);
+          else st(ob + (int64_t)t * v.sn + col, MODE == 0 ? val / Dt : val);
         }
       }
     }
@@ -861,12 +941,12 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void apply_kernel(const b
 // on the key side), dX_F = c rowscale ((G masked where R > 0) Omega^T) in float32 [slice][32 nt][DH].
 // DV: dV = c ReLU(R) dS rides along.  ddw, rowscale nullptr: 1.
 template <typename T, int DH, int PT, bool DV, int RT, int NW>
-__global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void grad_kernel(const bf16_t *X, const bf16_t *Y, const float *ddw,
+__global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void grad_kernel(const bf16_t *X, const bf16_t *Y, const float *ddw,
                                                                       const float *rowscale, const bf16_t *OA,
                                                                       const bf16_t *SA, const bf16_t *OB, const bf16_t *SB,
                                                                       const float *scalars, Dims s, float *dXF, T *dv, View v) {
   using G = Geo<DH>;
-  constexpr int FC = DH == 16 ? 2 : 1, NA = G::KS * PT, NSA = 3 * G::KS + 1, NOB = 2 * G::CT * PT, NSB = DV ? 6 * G::CT : 0;
+  constexpr int FC = DH == 16 ? 2 : 1, NA = G::KS * PT, NSA = 3 * G::KS + 1, NOB = 2 * G::CT * PT, NSB = DV ? G::NSB : 0;
   typedef Stager<NA, NSA, NOB, NSB, FC, NW> Stg;
   __shared__ __attribute__((aligned(16))) bf16_t lds[2][Stg::NS * kTile];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
@@ -902,8 +982,10 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void grad_kernel(const bf
       acc[r][ct] = zero16();
       if (DV) accv[r][ct] = zero16();
     }
+  const NegIdentity ni(lane);
   sg.fetch(0, wave, lane);
   sg.put(lds[0], wave, lane);
+  wait_loads();
   __syncthreads();
   int b = 0;
   for (int f0 = 0; f0 < s.mt; f0 += FC, b ^= 1) {
@@ -929,14 +1011,12 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void grad_kernel(const bf
         }
         Gr = mfma(lds_operand(ls + 3 * G::KS * kTile, lane), ext[r], Gr);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) Gr[i] = R[i] > 0.f ? Gr[i] : 0.f;
-        if (DV)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) R[i] = fmaxf(R[i], 0.f);
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-          bf16x8 p[3];
-          split_half(Gr, a, p);
+        for (int i = 0; i < 16; ++i) {
+          const float mask = positive(R[i]);
+          Gr[i] *= mask;
+          if (DV) R[i] *= mask;
+        }
+        with_split<mfma_residuals(DH, PT)>(Gr, ni, [&](int a, const bf16x8 *p) {
 #pragma unroll
           for (int ct = 0; ct < G::CT; ++ct) {
             bf16x8 o[PT];
@@ -944,23 +1024,19 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void grad_kernel(const bf
             for (int i = 0; i < PT; ++i) o[i] = lds_operand(lo + ((a * G::CT + ct) * PT + i) * kTile, lane);
             acc[r][ct] = mfma_terms<PT, false>(acc[r][ct], p, o);   // rows: tokens, lanes: columns
           }
-          if (DV) {
-            split_half(R, a, p);
+        });
+        if (DV)
+          with_split<mfma_residuals(DH, PT)>(R, ni, [&](int a, const bf16x8 *p) {
 #pragma unroll
-            for (int ct = 0; ct < G::CT; ++ct) {
-              bf16x8 o[3];
-#pragma unroll
-              for (int i = 0; i < 3; ++i) o[i] = lds_operand(lv + ((a * G::CT + ct) * 3 + i) * kTile, lane);
-              accv[r][ct] = mfma_terms<3, false>(accv[r][ct], p, o);
-            }
-          }
-        }
+            for (int ct = 0; ct < G::CT; ++ct) accv[r][ct] = apply_terms<DH>(accv[r][ct], p, lv, a, ct, lane);
+          });
       }
     }
     if (more) sg.put(lds[b ^ 1], wave, lane);
     __syncthreads();
   }
   const float c = scalars[0];
+  T *const vb = DV ? dv + v.slice_base(slice) : nullptr;
 #pragma unroll
   for (int r = 0; r < RT; ++r) {
     const int tb = tb0 + r;
@@ -970,11 +1046,12 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void grad_kernel(const bf
     for (int i = 0; i < 16; ++i) {
       const int row = 8 * (i >> 2) + 4 * h + (i & 3), t = 32 * tb + row;
       const float sc = rowscale ? __shfl(rs, row, 64) : c;
+      if (DV && DH == 16) accv[r][0][i] += __shfl_xor(accv[r][0][i], 16, 64);
 #pragma unroll
       for (int ct = 0; ct < G::CT; ++ct) {
         const int col = 32 * ct + l32;
         if (col < DH) dXF[((int64_t)slice * s.nt * 32 + t) * DH + col] = sc * acc[r][ct][i];
-        if (DV && t < s.n && col < s.d) st(dv + v.slice_base(slice) + (int64_t)t * v.sn + col, c * accv[r][ct][i]);
+        if (DV && t < s.n && col < s.d) st(vb + (int64_t)t * v.sn + col, c * accv[r][ct][i]);
       }
     }
   }
@@ -1206,7 +1283,7 @@ __global__ __launch_bounds__(256) void ln_out_kernel(const float *N, T *out, Vie
 // ------------------------------------------------------------------------------------
 // Host side
 // ------------------------------------------------------------------------------------
-constexpr int kFillBlocks = 512;   // two 8-wave workgroups per compute unit
+constexpr int kFillBlocks = 1024;   // workgroups of the contraction: four per compute unit, so that the last ones to end leave little idle
 
 int dh_of(int d) { return d <= 16 ? 16 : d <= 32 ? 32 : d <= 64 ? 64 : 128; }
 // One term for what comes in as bf16 (head dimensions up to 32, where that pays for instances of its own; the LayerNorm
@@ -1216,7 +1293,7 @@ int terms_of(const wersa_desc &c) {
 }
 struct Plan {
   Dims s;
-  int DH, KS, CT, PT, matrices;
+  int DH, KS, CT, PT, NSB, matrices;
   int chunks, rows_per_chunk;         // pooling
   int FW, TW, splits, tiles_per_split, shares;
   int groups;                         // 4096-element workgroups per slice
@@ -1230,6 +1307,7 @@ Plan plan_of(const wersa_desc &c) {
   p.KS = p.DH / 16;
   p.CT = p.DH < 32 ? 1 : p.DH / 32;
   p.PT = terms_of(c);
+  p.NSB = p.DH == 16 ? 4 : 6 * p.CT;
   p.matrices = (c.flags & WERSA_FLAG_SEPARATE_OMEGA) ? 2 : 1;
   p.s = Dims{c.n, c.d, c.m, (c.n + 63) / 64 * 2, (c.m + 31) / 32};
   p.ntl = (c.n + 63) / 64;
@@ -1246,7 +1324,7 @@ Plan plan_of(const wersa_desc &c) {
   p.FW = 8;
   while (p.s.mt % p.FW) p.FW /= 2;
   p.TW = 8 / p.FW;
-  const int sg = stage_tokens(p.DH);
+  const int sg = stage_tokens(p.DH, p.PT);
   p.TW = p.TW < sg ? p.TW : sg;
   const int base = slices * (p.s.mt / p.FW);
   int splits = (kFillBlocks + base - 1) / base;
@@ -1283,7 +1361,7 @@ Ws ws_of(const wersa_desc &c, const Plan &p, int bwd, float *base) {
   if (!bwd) {
     w.qpart = b.take(sl * p.chunks * c.d);
     w.VC = op(rows * 2 * p.CT * p.PT);
-    w.SB = op(sl * p.s.mt * 6 * p.CT + 6 * p.CT);       // (one feature tile more: a stage reads whole groups)
+    w.SB = op((sl * p.s.mt + 1) * p.NSB);       // (one feature tile more: a stage reads whole groups)
     if (c.flags & WERSA_FLAG_LAYERNORM) w.Nbuf = b.take(sl * c.n * c.d);
     if (deep) w.pyr = b.take(2 * sl * pyramid_floats(p.ntl, c.d));
   } else {
@@ -1292,7 +1370,7 @@ Ws ws_of(const wersa_desc &c, const Plan &p, int bwd, float *base) {
     w.VR = op(rows * p.KS * p.PT);
     if (p.PT == 1) w.XS = op(rows * p.KS * 3);
     w.dSA = op(sl * p.s.mt * (3 * p.KS + 1) + 3 * p.KS + 1);
-    w.dSB = op(sl * p.s.mt * 6 * p.CT + 6 * p.CT);
+    w.dSB = op((sl * p.s.mt + 1) * p.NSB);
     w.ddw = b.take(rows * 32);
     w.rowscale = b.take(rows * 32);
     w.dpart = b.take(sl * p.bgroups);
@@ -1327,14 +1405,17 @@ bool rows_aligned(const wersa_desc &c, std::initializer_list<const void *> ptrs)
   return true;
 }
 
-// Workgroup sizes of the row kernels: 8 waves (two per SIMD) that share the staged operands; 2 waves where the rows
-// are too few to give every compute unit a workgroup of 8 (each wave walks all features whatever the size, so
-// more and smaller workgroups cost only the staging).  Head dimension 128 holds 64 rows' operands in too many registers for two
-// waves per SIMD and runs 4 waves.
+// Workgroup sizes of the row kernels.  Head dimensions up to 32: 4 waves, several workgroups per compute unit, so that one
+// runs while another waits for its stage (d 16, m 1024, 8 x 131072 tokens: the forward's kernel 420 -> 392 us against 8 waves).
+// 64: 8 waves, the stage fills the LDS.  128: 4 waves with the whole register file.  2 waves where the rows are too few
+// to give every compute unit a full workgroup (each wave walks all features whatever the size, so more and
+// smaller workgroups cost only the staging).
+constexpr int full_waves(int DH) { return DH <= 32 ? 4 : 8; }
 template <int DH, int RT>
 int row_waves(const Plan &p, int slices) {
   if (DH == 128) return 4;
-  return (int64_t)slices * ((p.s.nt + 8 * RT - 1) / (8 * RT)) >= 256 ? 8 : 2;
+  const int full = full_waves(DH);
+  return (int64_t)slices * ((p.s.nt + full * RT - 1) / (full * RT)) >= 256 ? full : 2;
 }
 template <int DH> constexpr int row_tiles() { return DH <= 32 ? 2 : 1; }
 
@@ -1351,7 +1432,7 @@ void launch_apply(const wersa_desc &c, const Plan &p, const bf16_t *X, const bf1
   if constexpr (DH == 128) {
     go(std::integral_constant<int, 4>());
   } else {
-    if (nw == 8) go(std::integral_constant<int, 8>());
+    if (nw != 2) go(std::integral_constant<int, full_waves(DH)>());
     else go(std::integral_constant<int, 2>());
   }
 }
@@ -1369,7 +1450,7 @@ void launch_grad(const wersa_desc &c, const Plan &p, const bf16_t *X, const bf16
   if constexpr (DH == 128) {
     go(std::integral_constant<int, 4>());
   } else {
-    if (nw == 8) go(std::integral_constant<int, 8>());
+    if (nw != 2) go(std::integral_constant<int, full_waves(DH)>());
     else go(std::integral_constant<int, 2>());
   }
 }
