@@ -1,7 +1,9 @@
 // Attention block around the WERSA core (Section 3.1 steps 1-2: Q' = X W^Q, K' = X W^K,
 // V' = X W^V, split into heads; Algorithm 1's closing line: merged heads times W_out) and its
 // backward.  The projections are plain dense contractions over hidden = H*d: one bf16 MFMA
-// GEMM kernel (float32 accumulation) in two operand forms,
+// GEMM kernel (float32 accumulation) in three operand forms,
+//   NN  C[M][N] = A[M][K] B[K][N]              (forward: activations times weights as they are stored; the three
+//       projections in one launch)
 //   NT  C[M][N] = sum_s A_s[M][K] B_s[N][K]^T   (both operands contiguous along K; up to three
 //       (A, B) pairs summed, which gives dX = dQ' W^Q^T + dK' W^K^T + dV' W^V^T in one pass)
 //   TN  C[M][N] = A[K][M]^T B[K][N]            (both operands contiguous across K: the weight
@@ -18,206 +20,289 @@ typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int BM = 256, BN = 256, BK = 64;   // workgroup tile
-constexpr int LS = BK + 8;                   // NT form: LDS tiles [row][k], row stride (elements)
-constexpr int LT = BM + 32;                  // TN form: LDS tiles [k][row]; 576-byte rows put four
-                                             // consecutive k rows into different bank quarters
+constexpr int BK = 32;                       // k per stage
+constexpr int kStages = 4;                   // LDS stages: one computed on, one landed or landing, two requested
+constexpr int kGemmWaves = 4;                // 2 x 2 waves of WT x WT, WT = 128 or 64
+constexpr int kBigTile = 256, kSmallTile = 128;   // workgroup tiles (2 WT)
 constexpr int kMaxSrc = 3;
 constexpr int kMaxSplit = 32;
 
-// MFMA operand (row or column l32 = lane % 32, k = 8 h + q) out of a tile stored [k][row] in LDS,
-// through the transposing LDS read of gfx950 (ds_read_b64_tr_b16): within each group of 16
-// lanes, lane i passes the address of four consecutive 16-bit values, taken as row i / 4,
-// columns 4 (i % 4) .. + 3 of a 4 x 16 block, and receives column i of that block.  (Lane
-// mapping checked on the GPU with an index-valued LDS array.)  `tile` points at (k row 0, first
-// row of the 32-row operand tile); krow is this lane's first k.
-__device__ __forceinline__ bf16x8 lds_operand_tr(const bf16_t *tile, int krow, int lane) {
-  const int i16 = lane & 15, grp = (lane >> 4) & 1;
-  const bf16_t *p0 = tile + (krow + (i16 >> 2)) * LT + 16 * grp + 4 * (i16 & 3);
-  typedef s16x4 __attribute__((address_space(3))) * lds_s16x4_ptr;
-  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)p0);
-  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p0 + 4 * LT));
-  s16x8 r;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    r[q] = lo[q];
-    r[4 + q] = hi[q];
-  }
-  return __builtin_bit_cast(bf16x8, r);
-}
-
-struct GemmSrc {
+// One product, or several in one launch.  batch products C[i] = A[i] B[i] of equal shape (the three
+// projections, their three weight gradients), or batch = 1 and C[0] = sum of `count` products.
+struct GemmJob {
   const bf16_t *a[kMaxSrc];
   const bf16_t *b[kMaxSrc];
-  int count;
+  void *c[kMaxSrc];
+  int count, batch;
 };
 
 __device__ __forceinline__ bf16_t to_bf16(float f) { return __builtin_bit_cast(bf16_t, (__bf16)f); }
 
-// TRANS = false: NT form, A [M][K] (lda), B [N][K] (ldb).  TRANS = true: TN form, A [K][M] (lda),
-// B [K][N] (ldb).  OUT_F32: float32 output at C + split * M * ldc (split = this workgroup's K
-// range), else bf16 output.  M % 256 == 0, N % 256 == 0, every K range a multiple of 64.
-// NW waves: 4 (2 x 2 waves of 128 x 128) or 8 (2 x 4 waves of 128 x 64, two waves per SIMD).
-// Logical tile ids are dealt to the eight XCDs in contiguous runs (workgroup w runs on XCD
-// w % 8), n fastest within a run, so that the workgroups sharing an A panel share an L2.
-template <bool TRANS, bool OUT_F32, int NW>
-// colsum (bf16 output form, may be nullptr): float32 [M / 128][N], the column sums of each wave's
-// 128 output rows from the float32 accumulators; the block uses them as the pooled-query partial
-// sums of Q' = X W^Q (Section 3.1 step 4) instead of a separate pass over Q'.
-// colmax (with colsum): float32 [M / 128][N / 64], the largest |accumulator| of each wave's 128 rows x
-// 64 columns; the core derives the fp16 operand scale of a (batch, head) slice from them.
-__global__ __launch_bounds__(64 * NW, 1) void gemm_bf16_kernel(GemmSrc src, int lda, int ldb, void *Cout,
-                                                              int ldc, int M, int N, int K, int k_chunk,
-                                                              int splits, float *colsum, float *colmax) {
-  constexpr int NT = 64 * NW;
-  constexpr int WN = NW / 2;            // waves along n
-  constexpr int TN = 8 / WN;            // 32-column tiles per wave: 4 or 2
-  constexpr int PPT = 2048 / NT;        // 16-byte pieces per thread and operand per k-step
+// 16 bytes per lane from base + voff (bytes) to LDS at lds (bytes, wave-uniform) + 16 * lane, without passing
+// through registers.  Written as a statement because the compiler waits for every such load before the next
+// LDS read, whatever it reads; the caller counts them (vmcnt) instead.  It has no register outputs.
+__device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t voff, const bf16_t *base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base)
+               : "memory", "m0");
+}
+
+// Operand forms: TA = false: A [M][K] (lda), its LDS stage [row][32 k] in 64-byte rows; TA = true: A [K][M],
+// stage [32 k][row]; TB alike for B [N][K] / [K][N].  Stages are unpadded (a direct load to LDS writes 64
+// consecutive 16-byte pieces), so bank conflicts are avoided by permuting the pieces of a row:
+//   [row][k]: piece c of row r at slot c ^ ((r / 4) % 4): any 16 rows read one piece each without conflict;
+//   [k][row]: piece c of row k at slot c ^ (4 (k % 4)): the 4 k-rows x 64 bytes of a half-wave's transposing
+//   read cover all 64 banks.
+// OUT_F32: float32 output, one partial per (product, split), else bf16 output.  M, N multiples of 2 WT, every
+// K range a multiple of 32.  DMA = false stages through registers: operands whose base is not 16-byte aligned.
+//
+// What bounds it: per matrix instruction (32 cycles) a wave of WT = 128 reads 0.5 KB of LDS, so a compute unit
+// reads 64 B/clk and writes 32 of about 128; with two waves of 128 x 64 per SIMD (the form before) it was 96 + 32,
+// the whole LDS bandwidth.  One wave per SIMD hides nothing by itself, so nothing may stall: operands of the next
+// 16 k are read between the matrix instructions of the current ones, across the stage boundary too (a stage is
+// known to have landed one step before it is needed), and global loads have two steps (2048 cycles) to land.
+//
+// Logical tiles are dealt to the eight XCDs in contiguous runs (workgroup w runs on XCD w % 8); a run goes down
+// kGroupM row panels before it takes the next column panel, so that the 32 workgroups of an XCD at a time share
+// 4 panels of A and 8 of B in its L2.
+//
+// colsum (bf16 output form of product 0, may be nullptr): float32 [M / 128][N], the column sums of 128 output rows
+// from the float32 accumulators; the block uses them as the pooled-query partial sums of Q' = X W^Q (Section 3.1
+// step 4) instead of a separate pass over Q'.  colmax (with colsum): float32 [M / 128][N / 64], the largest
+// |accumulator| of 128 rows x 64 columns; the core derives the fp16 operand scale of a (batch, head) slice from them.
+constexpr int kGroupM = 4;
+
+template <int WT, bool TA, bool TB, bool OUT_F32, bool DMA>
+__global__ __launch_bounds__(64 * kGemmWaves, WT == 128 ? 1 : 2) void gemm_bf16_kernel(
+    GemmJob job, int lda, int ldb, int ldc, int M, int N, int K, int k_chunk, int splits, float *colsum, float *colmax) {
+  constexpr int T = 2 * WT;              // workgroup tile, rows and columns
+  constexpr int TI = WT / 32;            // 32 x 32 tiles per wave in each direction
+  constexpr int OPB = T * BK * 2;        // bytes of one operand's stage
+  constexpr int SB = 2 * OPB;            // bytes of a stage
+  constexpr int G = OPB / 1024 / kGemmWaves;   // 1 KB loads per wave, operand and stage
+  constexpr int RB = T * 2;              // bytes of a row of a [k][row] stage
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  bf16_t *At = reinterpret_cast<bf16_t *>(smem_raw);          // [2][BM][LS]
-  bf16_t *Bt = At + 2 * BM * LS;                              // [2][BN][LS]
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
-  const int tiles_n = N / BN, tiles = (M / BM) * tiles_n, total = tiles * splits;
+  typedef __attribute__((address_space(3))) unsigned char lds_byte;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte *)smem_raw;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31,
+            h = lane >> 5;
+  const int tm = M / T, tn = N / T * job.batch, tiles = tm * tn, total = tiles * splits;
   const int per = (total + 7) / 8;
   const int lt = (blockIdx.x % 8) * per + blockIdx.x / 8;
-  if (lt >= total) return;
+  if ((int)(blockIdx.x / 8) >= per || lt >= total) return;
   const int split = lt / tiles, tile = lt % tiles;
-  const int m0 = (tile / tiles_n) * BM, n0 = (tile % tiles_n) * BN;
+  const int grp = tile / (kGroupM * tn), rest = tile - grp * kGroupM * tn, rows = min(kGroupM, tm - grp * kGroupM);
+  const int nb = rest / rows, mt = grp * kGroupM + rest % rows;
+  const int which = nb / (N / T);        // product of the batch
+  const int m0 = mt * T, n0 = (nb - which * (N / T)) * T;
   const int k_begin = split * k_chunk, k_end = min(K, k_begin + k_chunk);
-  const int steps_per_src = (k_end - k_begin) / BK, steps = steps_per_src * src.count;
-  const int wm = (wave / WN) * 128, wn = (wave % WN) * (32 * TN);
+  const int steps = (k_end - k_begin) / BK * job.count;
+  const int wm = (wave >> 1) * WT, wn = (wave & 1) * WT;
 
-  f32x16 acc[4][TN];
+  // Source offsets of this lane's piece in the wave's G loads of each operand (bytes from the stage's corner).
+  uint32_t va[G], vb[G];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int u = 0; u < G; ++u) {
+    const int ins = wave * G + u;
+    auto off = [&](bool kmajor, int ld) -> uint32_t {
+      if (!kmajor) {
+        const int r = 16 * ins + (lane >> 2), c = (lane & 3) ^ ((lane >> 4) & 3);
+        return (uint32_t)(r * ld * 2 + c * 16);
+      }
+      constexpr int PR = RB / 16, KR = 64 / PR;   // pieces per k row, k rows per load
+      const int k = KR * ins + lane / PR, c = (lane % PR) ^ ((k & 3) << 2);
+      return (uint32_t)(k * ld * 2 + c * 16);
+    };
+    va[u] = off(TA, lda);
+    vb[u] = off(TB, ldb);
+  }
+  int src = which, k_next = k_begin;     // the next stage to request
+  auto corner = [&](const bf16_t *p, bool kmajor, int ld, int o0) {
+    return p + (kmajor ? (int64_t)k_next * ld + o0 : (int64_t)o0 * ld + k_next);
+  };
+  const bf16_t *pa = corner(job.a[src], TA, lda, m0), *pb = corner(job.b[src], TB, ldb, n0);
+  const int64_t da = TA ? (int64_t)BK * lda : BK, db = TB ? (int64_t)BK * ldb : BK;
+  auto next_source = [&]() {   // after the last stage the same one is requested again, and never read
+    if (k_next + BK < k_end) {
+      k_next += BK;
+      pa += da;
+      pb += db;
+    } else if (src - which + 1 < job.count) {
+      ++src;
+      k_next = k_begin;
+      pa = corner(job.a[src], TA, lda, m0);
+      pb = corner(job.b[src], TB, ldb, n0);
+    }
+  };
+  typedef u16x8 u16x8_any __attribute__((aligned(2)));
+  auto request = [&](int stage, int u, bool is_b) {
+    const uint32_t at = (uint32_t)(stage * SB + (is_b ? OPB : 0) + (wave * G + u) * 1024);
+    if (DMA) {
+      lds_dma16(lds0 + at, is_b ? vb[u] : va[u], is_b ? pb : pa);
+    } else {
+      const u16x8 piece = *reinterpret_cast<const u16x8_any *>(reinterpret_cast<const unsigned char *>(is_b ? pb : pa) +
+                                                               (is_b ? vb[u] : va[u]));
+      *reinterpret_cast<u16x8 *>(smem_raw + at + 16 * lane) = piece;
+    }
+  };
+
+  // Operand i of 16 k: A rows wm + 32 i .., or B columns wn + 32 i ...  [row][k]: one 16-byte read at row l32, k = 8 h.
+  // [k][row]: the transposing read of gfx950 (ds_read_b64_tr_b16): within each group of 16 lanes, lane i passes the
+  // address of four consecutive 16-bit values, taken as row i / 4, columns 4 (i % 4) .. + 3 of a 4 x 16 block, and
+  // receives column i of that block.  (Lane mapping checked on the GPU with an index-valued LDS array.)
+  typedef __attribute__((address_space(3))) s16x4 *lds_s16x4_ptr;
+  typedef __attribute__((address_space(3))) bf16x8 *lds_bf16x8_ptr;
+  const int i16 = lane & 15, g16 = (lane >> 4) & 1;
+  auto lane_off = [&](bool kmajor, int w0, int i) -> uint32_t {   // of operand i at ks = 0
+    if (!kmajor) return (uint32_t)((w0 + 32 * i + l32) * 64 + (h ^ ((l32 >> 2) & 3)) * 16);
+    const int piece = (w0 / 8 + 4 * i + 2 * g16 + ((i16 & 3) >> 1)) ^ ((i16 >> 2) << 2);
+    return (uint32_t)((8 * h + (i16 >> 2)) * RB + piece * 16 + (i16 & 1) * 8);
+  };
+  uint32_t oa[TI], ob[TI];
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+  for (int i = 0; i < TI; ++i) {
+    oa[i] = lds0 + lane_off(TA, wm, i);
+    ob[i] = lds0 + OPB + lane_off(TB, wn, i);
+  }
+  auto operand = [&](bool kmajor, uint32_t base, int ks) -> bf16x8 {
+    if (!kmajor) return *(lds_bf16x8_ptr)(ks ? base ^ 32u : base);   // piece 2 ks + h, permuted
+    const uint32_t p = base + (uint32_t)(16 * ks * RB);
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)p);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * RB));
+    s16x8 r;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      r[q] = lo[q];
+      r[4 + q] = hi[q];
+    }
+    return __builtin_bit_cast(bf16x8, r);
+  };
+
+  f32x16 acc[TI][TI];
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = 0; j < TI; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  u16x8 ra[PPT], rb[PPT];
-  auto fetch = [&](int s) {
-    const int which = s / steps_per_src, k0 = k_begin + (s % steps_per_src) * BK;
-    const bf16_t *A = src.a[which], *B = src.b[which];
-    if (!TRANS) {   // 256 rows x 8 pieces of 16 bytes along K, row-major
-#pragma unroll
-      for (int i = 0; i < PPT; ++i) {
-        const int e = tid + NT * i, r = e >> 3, cc = e & 7;
-        ra[i] = *reinterpret_cast<const u16x8 *>(A + (int64_t)(m0 + r) * lda + k0 + cc * 8);
-        rb[i] = *reinterpret_cast<const u16x8 *>(B + (int64_t)(n0 + r) * ldb + k0 + cc * 8);
-      }
-    } else {        // 64 k rows x 32 pieces of 16 bytes along the output rows, as stored
-#pragma unroll
-      for (int i = 0; i < PPT; ++i) {
-        const int e = tid + NT * i, r = e >> 5, cc = e & 31;
-        ra[i] = *reinterpret_cast<const u16x8 *>(A + (int64_t)(k0 + r) * lda + m0 + cc * 8);
-        rb[i] = *reinterpret_cast<const u16x8 *>(B + (int64_t)(k0 + r) * ldb + n0 + cc * 8);
-      }
-    }
+  // A wave's own loads up to the last `2 G` have landed and all its LDS reads have returned; then every wave's.
+  auto arrive = [&]() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * G) : "memory");
   };
-  auto stash = [&](int buf) {
-    bf16_t *as = At + buf * BM * LS, *bs = Bt + buf * BN * LS;   // BM * LS == BK * LT
-    if (!TRANS) {
 #pragma unroll
-      for (int i = 0; i < PPT; ++i) {
-        const int e = tid + NT * i, r = e >> 3, cc = e & 7;
-        *reinterpret_cast<u16x8 *>(&as[r * LS + cc * 8]) = ra[i];
-        *reinterpret_cast<u16x8 *>(&bs[r * LS + cc * 8]) = rb[i];
-      }
-    } else {        // [k][row] tiles: the transposition happens at the operand reads
+  for (int s = 0; s < kStages - 1; ++s) {
 #pragma unroll
-      for (int i = 0; i < PPT; ++i) {
-        const int e = tid + NT * i, r = e >> 5, cc = e & 31;
-        *reinterpret_cast<u16x8 *>(&as[r * LT + cc * 8]) = ra[i];
-        *reinterpret_cast<u16x8 *>(&bs[r * LT + cc * 8]) = rb[i];
-      }
+    for (int u = 0; u < G; ++u) {
+      request(s, u, false);
+      request(s, u, true);
     }
-  };
-
-  if (steps > 0) {
-    fetch(0);
-    stash(0);
+    next_source();
   }
-  __syncthreads();
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(4 * G) : "memory");
+  bf16x8 a0[TI], b0[TI], a1[TI], b1[TI];
+#pragma unroll
+  for (int i = 0; i < TI; ++i) {
+    a0[i] = operand(TA, oa[i], 0);
+    b0[i] = operand(TB, ob[i], 0);
+  }
+  // Sixteen (four) matrix instructions on one set of operands with the reads of the next set between the first
+  // half of them and the requests of a later stage between the others.
+  auto half = [&](const bf16x8 *a, const bf16x8 *b, bf16x8 *an, bf16x8 *bn, uint32_t stage, int ks, int into, bool req_b) {
+    constexpr int MM = TI * TI;
+#pragma unroll
+    for (int x = 0; x < MM; ++x) {
+      const int i = x / TI, j = x % TI;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+      if (x < TI) an[x] = operand(TA, oa[x] + stage, ks);
+      else if (x < 2 * TI) bn[x - TI] = operand(TB, ob[x - TI] + stage, ks);
+      if (MM == 16 ? (x >= 8 && (x & 1)) : x >= 2) {
+        const int u = MM == 16 ? (x - 8) / 2 : x - 2;
+        if (u < G) request(into, u, req_b);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
   for (int s = 0; s < steps; ++s) {
-    const int buf = s & 1;
-    const bool more = s + 1 < steps;
-    if (more) fetch(s + 1);
-    const bf16_t *as = At + buf * BM * LS + (TRANS ? wm : wm * LS);
-    const bf16_t *bs = Bt + buf * BN * LS + (TRANS ? wn : wn * LS);
-    // Two waves per SIMD: the one in its matrix phase goes ahead of the other's tile traffic (the
-    // requests above, the LDS writes below): NT -2 %, TN -3 %.
-    __builtin_amdgcn_s_setprio(3);
-#pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-      bf16x8 a[4], b[TN];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        a[i] = TRANS ? lds_operand_tr(as + 32 * i, 16 * ks + 8 * h, lane)
-                     : *reinterpret_cast<const bf16x8 *>(&as[(32 * i + l32) * LS + 16 * ks + 8 * h]);
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        b[j] = TRANS ? lds_operand_tr(bs + 32 * j, 16 * ks + 8 * h, lane)
-                     : *reinterpret_cast<const bf16x8 *>(&bs[(32 * j + l32) * LS + 16 * ks + 8 * h]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    __builtin_amdgcn_s_setprio(0);
-    if (more) stash(buf ^ 1);
-    __syncthreads();
+    const int cur = s % kStages, nxt = (s + 1) % kStages, into = (s + kStages - 1) % kStages;
+    arrive();   // stage s + 1 has landed; every wave is done with stage s - 1, which `into` overwrites
+    half(a0, b0, a1, b1, (uint32_t)(cur * SB), 1, into, false);
+    half(a1, b1, a0, b0, (uint32_t)(nxt * SB), 0, into, true);
+    next_source();
   }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the stages are free
 
   // acc[i][j][r]: row wm + 32 i + 8 (r / 4) + 4 h + (r % 4), column wn + 32 j + l32.
   if (OUT_F32) {
-    float *C = reinterpret_cast<float *>(Cout) + (int64_t)split * M * ldc;
+    float *C = splits == 1 ? reinterpret_cast<float *>(job.c[which])
+                           : reinterpret_cast<float *>(job.c[0]) + ((int64_t)which * splits + split) * M * ldc;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int j = 0; j < TI; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int row = m0 + wm + 32 * i + 8 * (r >> 2) + 4 * h + (r & 3);
           C[(int64_t)row * ldc + n0 + wn + 32 * j + l32] = acc[i][j][r];
         }
   } else {
-    // bf16 through a wave-private LDS tile of 32 rows x (32 TN) columns: 16-byte row-major
-    // stores.  (All waves are past the last barrier of the loop: the operand tiles are free.)
-    constexpr int ES = 32 * TN + 8, PPR = 4 * TN;   // tile row stride; 16-byte pieces per row
-    bf16_t *C = reinterpret_cast<bf16_t *>(Cout);
-    if (colsum) {
+    // bf16 through a wave-private LDS tile of 32 rows x WT columns: 16-byte row-major stores.
+    constexpr int ES = WT + 8, PPR = WT / 8;   // tile row stride; 16-byte pieces per row
+    bf16_t *C = reinterpret_cast<bf16_t *>(job.c[which]);
+    if (colsum && which == 0) {
+      float sum[TI], mx[TI];
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        float v = 0.f;
+      for (int j = 0; j < TI; ++j) {
+        sum[j] = mx[j] = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < TI; ++i)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) v += acc[i][j][r];
-        v += __shfl_xor(v, 32, 64);   // the two half-waves hold the two halves of every 8-row group
-        if (h == 0) colsum[(int64_t)((m0 + wm) >> 7) * N + n0 + wn + 32 * j + l32] = v;
+          for (int r = 0; r < 16; ++r) {
+            sum[j] += acc[i][j][r];
+            mx[j] = fmaxf(mx[j], fabsf(acc[i][j][r]));
+          }
+        sum[j] += __shfl_xor(sum[j], 32, 64);   // the two half-waves hold the two halves of every 8-row group
       }
-      if (colmax) {
-        static_assert(NW != 8 || 32 * TN == kPooledMaxCols, "one maximum per wave tile of 64 columns");
-        float mx = 0.f;
+      float *other = reinterpret_cast<float *>(smem_raw);   // WT = 64: rows 64 .. 127 are another wave's
+      if (WT == 64) {
+        float *mine = other + (wave & 1) * 192;
+        if (wave >= 2) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+          for (int j = 0; j < TI; ++j) {
+            if (h == 0) mine[32 * j + l32] = sum[j];
+            mine[64 + 64 * j + lane] = mx[j];
+          }
+        }
+        __syncthreads();
+        if (wave < 2) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
+          for (int j = 0; j < TI; ++j) {
+            sum[j] += mine[32 * j + l32];
+            mx[j] = fmaxf(mx[j], mine[64 + 64 * j + lane]);
+          }
+        }
+        __syncthreads();
+      }
+      if (WT == 128 || wave < 2) {
+        const int64_t blk = (m0 + wm) >> 7;
+        static_assert(kPooledMaxCols == 64, "two column tiles per maximum");
 #pragma unroll
-            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, fabsf(acc[i][j][r]));
+        for (int j = 0; j < TI; ++j) {
+          if (h == 0) colsum[blk * N + n0 + wn + 32 * j + l32] = sum[j];
+          if (colmax && (j & 1)) {
+            float v = fmaxf(mx[j - 1], mx[j]);
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-        if (lane == 0) colmax[(int64_t)((m0 + wm) >> 7) * (N / (32 * TN)) + (n0 + wn) / (32 * TN)] = mx;
+            for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+            if (lane == 0) colmax[blk * (N / 64) + (n0 + wn) / 64 + j / 2] = v;
+          }
+        }
       }
     }
     bf16_t *tl = reinterpret_cast<bf16_t *>(smem_raw) + wave * (32 * ES);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < TI; ++i) {
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int j = 0; j < TI; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
           tl[(8 * (r >> 2) + 4 * h + (r & 3)) * ES + 32 * j + l32] = to_bf16(acc[i][j][r]);
@@ -232,10 +317,12 @@ __global__ __launch_bounds__(64 * NW, 1) void gemm_bf16_kernel(GemmSrc src, int 
   }
 }
 
-// out[e] = sum over splits of part[split][e], fixed order.
-__global__ void splitk_reduce_kernel(const float *part, int splits, int64_t count, float *out) {
+// out[e] = sum over splits of part[split][e], fixed order; blockIdx.y: product of the batch.
+__global__ void splitk_reduce_kernel(const float *part, int splits, int64_t count, float *out0, float *out1, float *out2) {
   const int64_t e = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
   if (e >= count) return;
+  part += (int64_t)blockIdx.y * splits * count;
+  float *out = blockIdx.y == 0 ? out0 : (blockIdx.y == 1 ? out1 : out2);
   float4 acc = *reinterpret_cast<const float4 *>(part + e);
   for (int s = 1; s < splits; ++s) {
     const float4 v = *reinterpret_cast<const float4 *>(part + (int64_t)s * count + e);
@@ -244,39 +331,38 @@ __global__ void splitk_reduce_kernel(const float *part, int splits, int64_t coun
   *reinterpret_cast<float4 *>(out + e) = acc;
 }
 
-// dst [C][R] = src [R][C]^T (bf16), 64 x 64 tiles through LDS.
-__global__ void transpose_bf16_kernel(const bf16_t *src, int R, int C, bf16_t *dst) {
-  __shared__ bf16_t t[64][66];
-  const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-  for (int e = threadIdx.x; e < 64 * 64; e += blockDim.x) {
-    const int r = e >> 6, c = e & 63;
-    if (r0 + r < R && c0 + c < C) t[r][c] = src[(int64_t)(r0 + r) * C + c0 + c];
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < 64 * 64; e += blockDim.x) {
-    const int c = e >> 6, r = e & 63;
-    if (r0 + r < R && c0 + c < C) dst[(int64_t)(c0 + c) * R + r0 + r] = t[r][c];
-  }
-}
+constexpr int kBigTileMin = 256;
 
-constexpr size_t kGemmSmem = (size_t)2 * (BM + BN) * LS * sizeof(bf16_t);
-static_assert(BM * LS == BK * LT && BN == BM, "both tile forms share one LDS budget");
-
-template <bool TRANS, bool OUT_F32>
-hipError_t launch_gemm(const char *name, const GemmSrc &src, int lda, int ldb, void *C, int ldc, int M, int N,
-                       int K, int k_chunk, int splits, hipStream_t st, float *colsum = nullptr,
-                       float *colmax = nullptr) {
-  constexpr int kGemmWaves = 8;   // two waves per SIMD
-  auto kern = &gemm_bf16_kernel<TRANS, OUT_F32, kGemmWaves>;
+template <int WT, bool TA, bool TB, bool OUT_F32, bool DMA>
+hipError_t launch_gemm_tile(const char *name, const GemmJob &job, int ld, int M, int N, int K, int k_chunk, int splits,
+                            hipStream_t st, float *colsum, float *colmax) {
+  constexpr size_t smem = (size_t)kStages * 2 * (2 * WT) * BK * sizeof(bf16_t);
+  static_assert(smem >= (size_t)kGemmWaves * 32 * (WT + 8) * sizeof(bf16_t), "the epilogue's tiles fit into the stages");
+  auto kern = &gemm_bf16_kernel<WT, TA, TB, OUT_F32, DMA>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGemmSmem);
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
-  const int total = (M / BM) * (N / BN) * splits;
+  const int total = (M / (2 * WT)) * (N / (2 * WT)) * job.batch * splits;
   const int grid = ((total + 7) / 8) * 8;
-  WERSA_STAGE(name, st,
-              kern<<<grid, 64 * kGemmWaves, kGemmSmem, st>>>(src, lda, ldb, C, ldc, M, N, K, k_chunk, splits, colsum, colmax));
+  WERSA_STAGE(name, st, kern<<<grid, 64 * kGemmWaves, smem, st>>>(job, ld, ld, ld, M, N, K, k_chunk, splits, colsum, colmax));
   return hipSuccess;
 }
+
+template <bool TA, bool TB, bool OUT_F32>
+hipError_t launch_gemm(const char *name, const GemmJob &job, int ld, int M, int N, int K, int k_chunk, int splits,
+                       hipStream_t st, float *colsum = nullptr, float *colmax = nullptr) {
+  bool aligned = true;   // direct loads to LDS take 16-byte aligned sources
+  for (int i = 0; i < job.count * job.batch; ++i)
+    aligned = aligned && ((uintptr_t)job.a[i] | (uintptr_t)job.b[i]) % 16 == 0;
+  const int64_t big = (int64_t)(M / kBigTile) * (N / kBigTile) * job.batch * splits;
+  if (!aligned)
+    return launch_gemm_tile<64, TA, TB, OUT_F32, false>(name, job, ld, M, N, K, k_chunk, splits, st, colsum, colmax);
+  if (big >= kBigTileMin)
+    return launch_gemm_tile<128, TA, TB, OUT_F32, true>(name, job, ld, M, N, K, k_chunk, splits, st, colsum, colmax);
+  return launch_gemm_tile<64, TA, TB, OUT_F32, true>(name, job, ld, M, N, K, k_chunk, splits, st, colsum, colmax);
+}
+
+constexpr int kMinChunk = 256;   // tokens
 
 struct BlockPlan {
   int64_t tokens, hidden, act;   // act = tokens * hidden elements
@@ -289,10 +375,12 @@ BlockPlan block_plan(const wersa_desc &c) {
   p.tokens = (int64_t)c.B * c.n;
   p.hidden = (int64_t)c.H * c.d;
   p.act = p.tokens * p.hidden;
-  const int tiles = (int)((p.hidden / BM) * (p.hidden / BN));
-  int64_t z = 1024 / tiles;
+  // Weight gradients: 512 workgroups of the large tile per product (the three of Q, K, V share a launch), at least
+  // 256 tokens each.
+  const int64_t tiles = (p.hidden / kBigTile) * (p.hidden / kBigTile);
+  int64_t z = 512 / tiles;
   if (z > kMaxSplit) z = kMaxSplit;
-  if (z > p.tokens / BK) z = p.tokens / BK;
+  if (z > p.tokens / kMinChunk) z = p.tokens / kMinChunk;
   if (z < 1) z = 1;
   const int64_t steps = (p.tokens / BK + z - 1) / z;
   p.k_chunk = (int)(steps * BK);
@@ -306,7 +394,7 @@ BlockPlan block_plan(const wersa_desc &c) {
 
 // Byte layouts. saved: Q' | K' | V' | A (bf16, (B, n, hidden)) | the core's saved buffer.
 struct BlockSaved { size_t qp, kp, vp, a, core, total; };
-struct BlockWs { size_t wT[4], qsums, qmax, dA, dQp, dKp, dVp, part, core, total; };
+struct BlockWs { size_t qsums, qmax, dA, dQp, dKp, dVp, part, core, total; };
 size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 
 BlockSaved block_saved(const BlockPlan &p) {
@@ -326,7 +414,6 @@ BlockWs block_ws(const BlockPlan &p, int bwd) {
   BlockWs w{};
   size_t off = 0;
   if (!bwd) {
-    for (int i = 0; i < 4; ++i) { w.wT[i] = off; off += up256((size_t)p.hidden * p.hidden * 2); }
     w.qsums = off; off += up256((size_t)(p.tokens / 128) * p.hidden * 4);   // column sums of Q' per 128 rows
     w.qmax = off;  off += up256((size_t)(p.tokens / 128) * (p.hidden / kPooledMaxCols) * 4);   // and the largest |Q'| per 64 columns
   } else {
@@ -335,7 +422,7 @@ BlockWs block_ws(const BlockPlan &p, int bwd) {
     w.dQp = off; off += act;
     w.dKp = off; off += act;
     w.dVp = off; off += act;
-    w.part = off; off += up256((size_t)p.splits * p.hidden * p.hidden * 4);
+    w.part = off; off += up256((size_t)kMaxSrc * p.splits * p.hidden * p.hidden * 4);
   }
   w.core = off; off += up256(wersa_workspace_bytes(&p.core, bwd));
   w.total = off;
@@ -351,7 +438,7 @@ wersa_status validate_block(const wersa_desc *c) {
   if (c->dtype != WERSA_F32 && c->dtype != WERSA_BF16) return WERSA_ERR_INVALID_ARG;
   if (c->dtype != WERSA_BF16) return WERSA_ERR_UNSUPPORTED;
   const int64_t hidden = (int64_t)c->H * c->d, tokens = (int64_t)c->B * c->n;
-  if (hidden % BM != 0 || tokens % BM != 0 || hidden > 16384) return WERSA_ERR_UNSUPPORTED;
+  if (hidden % kBigTile != 0 || tokens % kBigTile != 0 || hidden > 16384) return WERSA_ERR_UNSUPPORTED;
   const BlockPlan p = block_plan(*c);
   return validate_desc(&p.core);
 }
@@ -417,22 +504,19 @@ wersa_status wersa_block_forward(const wersa_desc *desc, const void *x, const vo
   hipStream_t st = (hipStream_t)hip_stream;
   unsigned char *ws = (unsigned char *)workspace, *sb = (unsigned char *)saved;
   const int hid = (int)p.hidden, M = (int)p.tokens;
-  const void *wsrc[4] = {wq, wk, wv, wo};
-  bf16_t *wT[4];
-  for (int i = 0; i < 4; ++i) {
-    wT[i] = (bf16_t *)(ws + w.wT[i]);
-    WERSA_STAGE("wersa_transpose", st,
-                transpose_bf16_kernel<<<dim3(hid / 64, hid / 64), 256, 0, st>>>((const bf16_t *)wsrc[i], hid, hid, wT[i]));
-  }
   bf16_t *proj[3] = {(bf16_t *)(sb + sv.qp), (bf16_t *)(sb + sv.kp), (bf16_t *)(sb + sv.vp)};
-  for (int i = 0; i < 3; ++i) {
-    GemmSrc src{};
-    src.a[0] = (const bf16_t *)x;
-    src.b[0] = wT[i];
-    src.count = 1;
-    if (launch_gemm<false, false>("wersa_gemm_nt", src, hid, hid, proj[i], hid, M, hid, hid, hid, 1, st,
-                                  i == 0 ? (float *)(ws + w.qsums) : nullptr,
-                                  i == 0 ? (float *)(ws + w.qmax) : nullptr) != hipSuccess)
+  {
+    GemmJob job{};
+    const void *w3[3] = {wq, wk, wv};
+    for (int i = 0; i < 3; ++i) {
+      job.a[i] = (const bf16_t *)x;
+      job.b[i] = (const bf16_t *)w3[i];
+      job.c[i] = proj[i];
+    }
+    job.count = 1;
+    job.batch = 3;
+    if (launch_gemm<false, true, false>("wersa_gemm_nn", job, hid, M, hid, hid, hid, 1, st, (float *)(ws + w.qsums),
+                                        (float *)(ws + w.qmax)) != hipSuccess)
       return WERSA_ERR_LAUNCH;
   }
   bf16_t *A = (bf16_t *)(sb + sv.a);
@@ -442,11 +526,12 @@ wersa_status wersa_block_forward(const wersa_desc *desc, const void *x, const vo
                                           scale_w, A, sb + sv.core, ws + w.core,
                                           wersa_workspace_bytes(&p.core, 0), hip_stream, &pooled);
   if (cs != WERSA_OK) return cs;
-  GemmSrc src{};
-  src.a[0] = A;
-  src.b[0] = wT[3];
-  src.count = 1;
-  if (launch_gemm<false, false>("wersa_gemm_nt", src, hid, hid, y, hid, M, hid, hid, hid, 1, st) != hipSuccess)
+  GemmJob job{};
+  job.a[0] = A;
+  job.b[0] = (const bf16_t *)wo;
+  job.c[0] = y;
+  job.count = job.batch = 1;
+  if (launch_gemm<false, true, false>("wersa_gemm_nn", job, hid, M, hid, hid, hid, 1, st) != hipSuccess)
     return WERSA_ERR_LAUNCH;
   return hipGetLastError() == hipSuccess ? WERSA_OK : WERSA_ERR_LAUNCH;
 }
@@ -479,47 +564,57 @@ wersa_status wersa_block_backward(const wersa_desc *desc, const void *x, const v
   float *part = (float *)(ws + w.part);
   const int64_t wcount = (int64_t)hid * hid;
 
-  auto weight_grad = [&](const bf16_t *left, const bf16_t *right, float *out) -> bool {
-    GemmSrc src{};
-    src.a[0] = left;
-    src.b[0] = right;
-    src.count = 1;
-    float *target = p.splits == 1 ? out : part;
-    if (launch_gemm<true, true>("wersa_gemm_tn", src, hid, hid, target, hid, hid, hid, M, p.k_chunk, p.splits,
-                                st) != hipSuccess)
+  auto weight_grads = [&](const bf16_t *left, int batch, const bf16_t *const *right, float *const *out) -> bool {
+    GemmJob job{};
+    for (int i = 0; i < batch; ++i) {
+      job.a[i] = left;
+      job.b[i] = right[i];
+      job.c[i] = p.splits == 1 ? out[i] : part;
+    }
+    job.count = 1;
+    job.batch = batch;
+    if (launch_gemm<true, true, true>("wersa_gemm_tn", job, hid, hid, hid, M, p.k_chunk, p.splits, st) != hipSuccess)
       return false;
     if (p.splits > 1)
       WERSA_STAGE("wersa_splitk_reduce", st,
-                  splitk_reduce_kernel<<<(unsigned)((wcount / 4 + 255) / 256), 256, 0, st>>>(part, p.splits, wcount, out));
+                  splitk_reduce_kernel<<<dim3((unsigned)((wcount / 4 + 255) / 256), batch), 256, 0, st>>>(
+                      part, p.splits, wcount, out[0], batch > 1 ? out[1] : nullptr, batch > 2 ? out[2] : nullptr));
     return true;
   };
 
   {  // dA = dY W_out^T: B operand [N = in][K = out] is W_out as stored
-    GemmSrc src{};
-    src.a[0] = (const bf16_t *)dy;
-    src.b[0] = (const bf16_t *)wo;
-    src.count = 1;
-    if (launch_gemm<false, false>("wersa_gemm_nt", src, hid, hid, dA, hid, M, hid, hid, hid, 1, st) != hipSuccess)
+    GemmJob job{};
+    job.a[0] = (const bf16_t *)dy;
+    job.b[0] = (const bf16_t *)wo;
+    job.c[0] = dA;
+    job.count = job.batch = 1;
+    if (launch_gemm<false, false, false>("wersa_gemm_nt", job, hid, M, hid, hid, hid, 1, st) != hipSuccess)
       return WERSA_ERR_LAUNCH;
   }
-  if (!weight_grad(A, (const bf16_t *)dy, dwo)) return WERSA_ERR_LAUNCH;
+  {
+    const bf16_t *const right[1] = {(const bf16_t *)dy};
+    float *const outs[1] = {dwo};
+    if (!weight_grads(A, 1, right, outs)) return WERSA_ERR_LAUNCH;
+  }
   const wersa_status cs =
       wersa_backward(&p.core, Qp, Kp, Vp, omega_rf, sigma, gate_w, gate_b, scale_w, A, dA, sb + sv.core, dQp, dKp,
                      dVp, dgate_w, dgate_b, dscale_w, dsigma, ws + w.core, wersa_workspace_bytes(&p.core, 1),
                      hip_stream);
   if (cs != WERSA_OK) return cs;
   {  // dX = dQ' W^Q^T + dK' W^K^T + dV' W^V^T
-    GemmSrc src{};
-    src.a[0] = dQp; src.b[0] = (const bf16_t *)wq;
-    src.a[1] = dKp; src.b[1] = (const bf16_t *)wk;
-    src.a[2] = dVp; src.b[2] = (const bf16_t *)wv;
-    src.count = 3;
-    if (launch_gemm<false, false>("wersa_gemm_nt", src, hid, hid, dx, hid, M, hid, hid, hid, 1, st) != hipSuccess)
+    GemmJob job{};
+    job.a[0] = dQp; job.b[0] = (const bf16_t *)wq;
+    job.a[1] = dKp; job.b[1] = (const bf16_t *)wk;
+    job.a[2] = dVp; job.b[2] = (const bf16_t *)wv;
+    job.c[0] = dx;
+    job.count = 3;
+    job.batch = 1;
+    if (launch_gemm<false, false, false>("wersa_gemm_nt", job, hid, M, hid, hid, hid, 1, st) != hipSuccess)
       return WERSA_ERR_LAUNCH;
   }
-  if (!weight_grad((const bf16_t *)x, dQp, dwq)) return WERSA_ERR_LAUNCH;
-  if (!weight_grad((const bf16_t *)x, dKp, dwk)) return WERSA_ERR_LAUNCH;
-  if (!weight_grad((const bf16_t *)x, dVp, dwv)) return WERSA_ERR_LAUNCH;
+  const bf16_t *const right[3] = {dQp, dKp, dVp};
+  float *const outs[3] = {dwq, dwk, dwv};
+  if (!weight_grads((const bf16_t *)x, 3, right, outs)) return WERSA_ERR_LAUNCH;
   return hipGetLastError() == hipSuccess ? WERSA_OK : WERSA_ERR_LAUNCH;
 }
 
