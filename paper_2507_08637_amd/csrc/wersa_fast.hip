@@ -944,9 +944,47 @@ __global__ __launch_bounds__(256) void reduce_contract_kernel(const float *Spart
 // layout, rows on registers), per-band inner products with X for dF, bf16 stores.
 // ------------------------------------------------------------------------------------
 
+// The rows of one 64-row block as a buffer of `valid` rows of `sn` elements (values v of 2 or 4 bytes): loads past
+// the last row return zeros and stores past it do nothing, by the bounds check of the buffer instructions, so a
+// partial last block runs the code of a whole one.  All arguments are the same for the whole wave; 64 rows must
+// stay below 2^32 bytes (see kMaxBufferStride).
+typedef __amdgpu_buffer_rsrc_t RowBuf;
+constexpr int64_t kMaxBufferStride = 1 << 24;   // row stride (elements) up to which a partial last block is a buffer
+template <typename T>
+__device__ __forceinline__ RowBuf row_buffer(const T *rows, int64_t sn, int valid) {
+  const uint64_t a = reinterpret_cast<uint64_t>(rows);   // (the compiler does not see that a wave's index is uniform)
+  const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+  const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
+  const int v = __builtin_amdgcn_readfirstlane(valid < 0 ? 0 : (valid < 64 ? valid : 64));
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(hi << 32 | lo), 0,
+                                           (int)(uint32_t)((uint64_t)v * (uint64_t)sn * sizeof(T)), 0x00020000);
+}
+template <typename V> __device__ __forceinline__ V buf_load16(RowBuf r, uint32_t off) {
+  return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+}
+template <typename V> __device__ __forceinline__ V buf_load8(RowBuf r, uint32_t off) {
+  return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+}
+__device__ __forceinline__ float buf_load4(RowBuf r, uint32_t off) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+}
+// A value that the compiler re-derives from in every block: offsets that depend on the lane alone would otherwise be
+// kept in registers across the feature loop and spill (60 bytes per lane in the kernel with dV).
+__device__ __forceinline__ uint32_t opaque(uint32_t v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+typedef unsigned int u32x2v __attribute__((ext_vector_type(2)));
+template <typename V> __device__ __forceinline__ void buf_store8(RowBuf r, uint32_t off, V v) {
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2v, v), r, off, 0, 0);
+}
+__device__ __forceinline__ void buf_store4(RowBuf r, uint32_t off, float v) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, off, 0, 0);
+}
+
 // LN (MODE 0): LayerNorm over the columns of a row instead of the normaliser.  RAGGED: n is not a
-// multiple of 64; rows past n of the last block read as zeros (clamped address, value replaced)
-// and that block's output goes through a side buffer.  The plain instance has none of that code.
+// multiple of 64; rows are read and written through buffers that end at row n (see row_buffer).
+// The plain instance has none of that code.
 // DEEP: L > 6: X_F starts from the per-tile addend of the levels above 6 (tile_add
 // [slices][ceil(n / 64)][DH]; head dimension 128 finds them in xf already); the gradient modes also
 // write the 64-row sums of dX_F per column (tile_gsum, same shape) and leave band 6 of their
@@ -971,7 +1009,6 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
     bf16_t *out0, View vo,     // O (MODE 0) / dQ or dK (MODE 1, 2) / dV (MODE 3)
     float *Dout,               // D (MODE 0)
     float *partF, int L,       // [slices][gridDim.x][L+1] band partials (MODE 1, 2)
-    bf16_t *tail_out, float *tail_D,   // partial last block: its 64 output rows [slices][64][DH] and D [slices][64]
     const float *tile_add, float *tile_gsum,   // DEEP (see above)
     bf16_t *out1)                              // DV: dV, laid out like out0
 {
@@ -1101,15 +1138,8 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
   bf16x8 yb[2][KSX];    // dO or V rows (+ the a_t extension): B operand of the dPhi MFMA
   float dval[2] = {1.f, 1.f};   // D of rows 32 ti + l32 (MODE 1)
   float aval[2] = {1.f, 1.f};   // dD of the same rows (MODE 1)
-  auto zero_if = [](bool bad, auto v) {
-    if (bad) {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) v[q] = 0;
-    }
-    return v;
-  };
   auto load_rows = [&](int t0) {
-    const int last = RAGGED ? n - t0 - 1 : 63;   // last row of this block that exists
+    const int valid = RAGGED ? n - t0 : 64;   // rows of this block that exist
     if (FUSE) {
       if (!RAGGED) {
         // one running pointer (eight separately scaled row offsets would each be kept in registers)
@@ -1120,23 +1150,27 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
           xsrc += 8 * vx.sn;
         }
       } else {
-        const bf16_t *xsrc = x + vx.slice_base(slice) + (int64_t)t0 * vx.sn + (lane & 7) * 8;
+        const RowBuf xr = row_buffer(x + vx.slice_base(slice) + (int64_t)t0 * vx.sn, vx.sn, valid);
+        const uint32_t sn2 = (uint32_t)vx.sn * 2;
+        const uint32_t ln = opaque(lane);
+        uint32_t off = (ln >> 3) * sn2 + (ln & 7) * 16;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-          const int row = (lane >> 3) + 8 * j;
-          xp[j] = zero_if(row > last, *reinterpret_cast<const u16x8 *>(xsrc + (int64_t)min(row, last) * vx.sn));
+          xp[j] = buf_load16<u16x8>(xr, off);
+          off += 8 * sn2;
         }
       }
     } else {
       const _Float16 *xs = xf + ((int64_t)slice * n + t0) * DH;
+      RowBuf xr;
+      if (RAGGED) xr = row_buffer(xs, DH, valid);
 #pragma unroll
       for (int ti = 0; ti < 2; ++ti) {
-        const int row = 32 * ti + l32, rc = RAGGED ? min(row, last) : row;
+        const int row = 32 * ti + l32;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          const f16x8 v = *reinterpret_cast<const f16x8 *>(xs + (int64_t)rc * DH + 16 * ks + 8 * h);
-          xb[ti][ks] = RAGGED ? zero_if(row > last, v) : v;
-        }
+        for (int ks = 0; ks < KS; ++ks)
+          xb[ti][ks] = RAGGED ? buf_load16<f16x8>(xr, (uint32_t)(row * DH + 16 * ks + 8 * h) * 2)
+                              : *reinterpret_cast<const f16x8 *>(xs + (int64_t)row * DH + 16 * ks + 8 * h);
       }
     }
     if (IS_GRAD) {
@@ -1144,23 +1178,31 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
       // row t of dX_F is scaled by c / D_t at the end; MODE 2 scales by c (extension 1, or 0 for
       // a row past n, which must not pick up the vector part).
       const bf16_t *ys = y + vy.slice_base(slice);
+      RowBuf yr, dr, ar;
+      uint32_t yoff = 0;
+      if (RAGGED) {
+        const uint32_t ln = opaque(lane);
+        yoff = (ln & 31) * ((uint32_t)vy.sn * 2) + (ln >> 5) * 16;
+        yr = row_buffer(ys + (int64_t)t0 * vy.sn, vy.sn, valid);
+        if (MODE == 1) {
+          dr = row_buffer(Dsaved + (int64_t)slice * n + t0, 1, valid);
+          ar = row_buffer(arow + (int64_t)slice * n + t0, 1, valid);
+        }
+      }
 #pragma unroll
       for (int ti = 0; ti < 2; ++ti) {
-        const int row = 32 * ti + l32;
-        const bool bad = RAGGED && row > last;
-        const int t = t0 + (RAGGED ? min(row, last) : row);
+        const int row = 32 * ti + l32, t = t0 + row;
+        const bool bad = RAGGED && row >= valid;
         if (MODE == 1) {   // only requested here: used at the top of the next round (finish_rows)
-          dval[ti] = Dsaved[(int64_t)slice * n + t];
-          aval[ti] = arow[(int64_t)slice * n + t];
-          if (bad) { dval[ti] = 1.f; aval[ti] = 0.f; }
+          dval[ti] = RAGGED ? buf_load4(dr, 4 * row) : Dsaved[(int64_t)slice * n + t];
+          aval[ti] = RAGGED ? buf_load4(ar, 4 * row) : arow[(int64_t)slice * n + t];
         } else if (RAGGED) {
           aval[ti] = bad ? 0.f : 1.f;
         }
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          const bf16x8 v = *reinterpret_cast<const bf16x8 *>(ys + (int64_t)t * vy.sn + 16 * ks + 8 * h);
-          yb[ti][ks] = RAGGED ? zero_if(bad, v) : v;
-        }
+        for (int ks = 0; ks < KS; ++ks)
+          yb[ti][ks] = RAGGED ? buf_load16<bf16x8>(yr, yoff + (uint32_t)ti * ((uint32_t)vy.sn * 64) + 32u * ks)
+                              : *reinterpret_cast<const bf16x8 *>(ys + (int64_t)t * vy.sn + 16 * ks + 8 * h);
       }
     }
   };
@@ -1213,11 +1255,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
   for (int rg = blockIdx.x; rg < row_groups; rg += gridDim.x) {
     const int t0 = (rg * NWR + wave) * 64;
     const bool active = t0 < n;
-    // A partial last block (n not a multiple of 64) writes all its 64 rows to a side buffer, from
-    // which a small kernel copies the rows that exist: the stores themselves stay unguarded
-    // (guards or pointer selects around them cost the gradient kernels 230 bytes of spills per lane).
     const int valid = RAGGED ? n - t0 : 64;
-    const bool tail = RAGGED && valid < 64;
 
     bf16x4 xpiece[8];   // X tile of the band inner products (MODE 1, 2, head dimension 128), 8-byte row-major pieces
     auto load_xpiece = [&](int ct, bf16x4 *dst) {
@@ -1229,13 +1267,14 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
           xsrc += 8 * vx.sn;
         }
       } else {
-        const bf16_t *xsrc = x + vx.slice_base(slice) + (int64_t)t0 * vx.sn + 32 * ct + (lane & 7) * 4;
+        const RowBuf xr = row_buffer(x + vx.slice_base(slice) + (int64_t)t0 * vx.sn, vx.sn, valid);
+        const uint32_t sn2 = (uint32_t)vx.sn * 2;
+        const uint32_t ln = opaque(lane);
+        uint32_t off = (ln >> 3) * sn2 + (32 * ct + (ln & 7) * 4) * 2;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {   // rows past n: clamped address, value replaced by zeros
-          const int row = (lane >> 3) + 8 * j;
-          bf16x4 v4 = *reinterpret_cast<const bf16x4 *>(xsrc + (int64_t)min(row, valid - 1) * vx.sn);
-          if (row >= valid) v4 = bf16x4{0, 0, 0, 0};
-          dst[j] = v4;
+        for (int j = 0; j < 8; ++j) {
+          dst[j] = buf_load8<bf16x4>(xr, off);
+          off += 8 * sn2;
         }
       }
     };
@@ -1293,7 +1332,10 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
     if (MODE == 1 && active) {   // row scales c / D_t for the epilogue, before the next rows' D replace them
 #pragma unroll
       for (int ti = 0; ti < 2; ++ti)
-        if (h == 0) s_wave[wave * 64 + 32 * ti + l32] = cscale * __builtin_amdgcn_rcpf(dval[ti]);
+        // (rows past n: D reads as 0 there, and their scale must be finite for the sums over the block)
+        if (h == 0)
+          s_wave[wave * 64 + 32 * ti + l32] =
+              (RAGGED && 32 * ti + l32 >= valid) ? 0.f : cscale * __builtin_amdgcn_rcpf(dval[ti]);
     }
     f32x16 acc0[2][CT];   // N, dV (MODE 0, 3) or dX_F (MODE 1, 2): rows on registers, columns on lanes
     f32x16 acc1[DV ? 2 : 1][DV ? CT : 1];   // DV: dV
@@ -1372,7 +1414,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
         // The pipelined form keeps two more chain results alive than the plain one: it is used where
         // the registers allow it without spills (not next to the dV accumulators, not with the
         // partial-block code).
-        constexpr bool PIPE = !DV && !RAGGED;
+        constexpr bool PIPE = !DV;
         if (PIPE) {
           // Software pipeline over the feature tiles: while the matrix pipe works through the
           // chain of one row tile, the VALU masks the other row tile's finished chain (inside the
@@ -1510,11 +1552,22 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
         *reinterpret_cast<bf16x4 *>(&tl[l32 * TT + 32 * ti + 8 * g + 4 * h]) = pk;
       }
     };
-    auto tile_store = [&](bf16_t *dst, int64_t sn, int col0) {
+    auto tile_store = [&](bf16_t *dst, RowBuf buf, int64_t sn, int col0) {
       bf16x4 piece[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u)
         piece[u] = lds_read_tr4(&tl[(16 * (u >> 2) + 4 * g16 + (i16 >> 2)) * TT + 16 * (u & 3) + 4 * (i16 & 3)]);
+      if (RAGGED) {
+        const uint32_t ln = opaque(lane);
+        uint32_t off = (ln & 15) * ((uint32_t)sn * 2) + ((uint32_t)col0 + 4 * (ln >> 4)) * 2;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          buf_store8(buf, off, piece[u]);
+          buf_store8(buf, off + 32, piece[u + 4]);
+          off += 32 * (uint32_t)sn;
+        }
+        return;
+      }
       bf16_t *drow = dst + (int64_t)i16 * sn + col0 + 4 * g16;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {   // one running pointer instead of four scaled row offsets
@@ -1524,13 +1577,16 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
       }
     };
     const int prow = lane >> 3, pcol = (lane & 7) * 4;   // this lane's 8-byte piece: rows prow + 8 j
-    bf16_t *os = tail ? tail_out + (int64_t)slice * 64 * DH : out0 + vo.slice_base(slice) + (int64_t)t0 * vo.sn;
-    const int64_t osn = tail ? DH : vo.sn;   // row stride of the output rows
-    float *Dp = tail ? tail_D + slice * 64 : Dout + (int64_t)slice * n + t0;
-    // DV: the second output's rows (side buffer: behind the first output's, [2][slices][64][DH])
-    bf16_t *os1 = !DV ? nullptr
-                      : (tail ? tail_out + ((int64_t)gridDim.y + slice) * 64 * DH
-                              : out1 + vo.slice_base(slice) + (int64_t)t0 * vo.sn);
+    bf16_t *os = out0 + vo.slice_base(slice) + (int64_t)t0 * vo.sn;
+    const int64_t osn = vo.sn;   // row stride of the output rows
+    float *Dp = MODE == 0 ? Dout + (int64_t)slice * n + t0 : nullptr;
+    bf16_t *os1 = !DV ? nullptr : out1 + vo.slice_base(slice) + (int64_t)t0 * vo.sn;   // DV: the second output's rows
+    RowBuf osb, osb1, Dpb;
+    if (RAGGED) {
+      osb = row_buffer(os, osn, valid);
+      if (DV) osb1 = row_buffer(os1, osn, valid);
+      if (MODE == 0) Dpb = row_buffer(Dp, 1, valid);
+    }
 
     if (MODE == 0 && LN) {
       // Output stage of Algorithm 1: O_t = (N_t - mean N_t) / sqrt(var N_t + eps), N = c * acc.
@@ -1558,7 +1614,8 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
           if (l32 == 0) dl[32 * ti + acc_row(i, h)] = rstd;
         }
       __builtin_amdgcn_wave_barrier();
-      Dp[lane] = dl[lane];
+      if (RAGGED) buf_store4(Dpb, 4 * lane, dl[lane]);
+      else Dp[lane] = dl[lane];
     } else if (MODE == 0) {   // normaliser D_t = c * sum_r relu(R) z + eps, row scale c / D_t
       float *dl = s_wave + wave * 64;
 #pragma unroll
@@ -1567,7 +1624,8 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
         const float Dt = fmaf(cscale, dsum, eps);
         // both half-waves hold the same sum and write the same values: no branch around the store
         dl[32 * ti + l32] = cscale * __builtin_amdgcn_rcpf(Dt);
-        Dp[32 * ti + l32] = Dt;
+        if (RAGGED) buf_store4(Dpb, 4 * (32 * ti + l32), Dt);
+        else Dp[32 * ti + l32] = Dt;
       }
     }
     // Row scale of the accumulators (rows on registers): c / D_t (MODE 0 from the per-wave LDS
@@ -1608,6 +1666,16 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
 #pragma unroll
         for (int j = 0; j < 8; ++j)
           piece[j] = *reinterpret_cast<const bf16x4 *>(&tl[(prow + 8 * j) * TS + pcol]);
+        if (RAGGED) {
+          const uint32_t ln = opaque(lane);
+          uint32_t off = (ln >> 3) * ((uint32_t)osn * 2) + (32 * ct + (ln & 7) * 4) * 2;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            buf_store8(osb, off, piece[j]);
+            off += 16 * (uint32_t)osn;
+          }
+          continue;
+        }
         bf16_t *orow = os + (int64_t)prow * osn + 32 * ct + pcol;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -1714,7 +1782,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
       }
       __builtin_amdgcn_wave_barrier();
       // ---- LDS -> dX
-      tile_store(os, osn, 32 * ct);
+      tile_store(os, osb, osn, 32 * ct);
       if (DV) {   // dV tile through the same panel (its X values are used up)
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -1725,7 +1793,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
           tile_put(ti, o16);
         }
         __builtin_amdgcn_wave_barrier();
-        tile_store(os1, osn, 32 * ct);
+        tile_store(os1, osb1, osn, 32 * ct);
       }
     }
     put_rows();
@@ -1915,21 +1983,6 @@ __global__ __launch_bounds__(256) void ln_prep_kernel(const bf16_t *dout, const 
   if (tid == 0) part[(int64_t)slice * gridDim.x + chunk] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// Partial last block of a sequence: rows [t0, n) of the side buffer [slices][64][DH] (and of
-// D [slices][64] when given) go to their place in the output.
-template <int DH>
-__global__ __launch_bounds__(256) void tail_copy_kernel(const bf16_t *tail_out, const float *tail_D, int n,
-                                                       int t0, bf16_t *out, View v, float *D) {
-  constexpr int CPR = DH / 8;
-  const int slice = blockIdx.x, valid = n - t0;
-  for (int e = threadIdx.x; e < valid * CPR; e += 256) {
-    const int r = e / CPR, cc = e % CPR;
-    *reinterpret_cast<u16x8 *>(out + v.slice_base(slice) + (int64_t)(t0 + r) * v.sn + cc * 8) =
-        *reinterpret_cast<const u16x8 *>(tail_out + ((int64_t)slice * 64 + r) * DH + cc * 8);
-  }
-  if (D && (int)threadIdx.x < valid) D[(int64_t)slice * n + t0 + threadIdx.x] = tail_D[slice * 64 + threadIdx.x];
-}
-
 // ---------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------
@@ -1981,8 +2034,6 @@ struct FastWs {
   float *qamax;   // largest |Q| per (slice, chunk) of the pooling pass
   float *scalars, *coef, *qpart, *Spart, *zpart, *dD, *dDpart, *dS, *dz, *partQ, *partK, *dF,
       *dlogit, *dqbar;
-  bf16_t *tail_out;   // partial last block of the sequence: its 64 output rows [slices][64][d]
-  float *tail_D;      // and its D values [slices][64]
   _Float16 *omT;
   bf16_t *Sx, *ST, *zb, *dSx, *dST, *dzb;
   bf16_t *dN;    // LayerNorm output stage: gradient with respect to the un-normalised rows
@@ -2016,8 +2067,6 @@ FastWs fast_ws(const wersa_desc &c, const FastPlan &p, int bwd, float *base, flo
   }
   const bool deep = c.L > kTileL;
   const int ntiles = (c.n + 63) / 64;
-  w.tail_out = reinterpret_cast<bf16_t *>(b.take(2 * sl * 64 * c.d / 2));   // (two outputs when dV rides along with dK)
-  w.tail_D = b.take(sl * 64);
   w.qpart = b.take(sl * p.chunksQ * c.d);
   w.qamax = b.take(sl * p.chunksQ);
   w.Spart = b.take(sl * p.chunksC * md);
@@ -2068,10 +2117,9 @@ size_t rows_smem_bytes(int mc) {
 }
 
 // dV formed by the K-side gradient kernel instead of a launch of its own: head dimension 64 with
-// 256 features staged per pass, whole 64-row blocks (with a partial last block the merged kernel
-// would spill ~100 bytes per lane; those shapes keep the two launches).
+// 256 features staged per pass.
 inline bool dv_rides_along(const wersa_desc &c, const FastPlan &p) {
-  return c.d == 64 && p.mc == 256 && c.n % 64 == 0;
+  return c.d == 64 && p.mc == 256;
 }
 
 template <int DH, int MODE>
@@ -2101,22 +2149,17 @@ hipError_t launch_rows(const wersa_desc &c, const FastPlan &p, const _Float16 *x
     WERSA_STAGE(name, st,
                 kern<<<dim3(wgs, c.B * c.H), NW * 64, smem, st>>>(
                     xf, x, tv, y, yview ? *yview : tv, Dsaved, arow, omT, omega, Mx, MT, bb, w.coef, w.scalars,
-                    c.eps, c.n, c.m, groups, out0, tv, Dout, partF, c.L, w.tail_out, w.tail_D,
+                    c.eps, c.n, c.m, groups, out0, tv, Dout, partF, c.L,
                     MODE >= 2 ? w.addK : w.addQ, MODE == 1 ? w.gsumQ : w.gsumK, out1));
-    if (c.n % 64 != 0) {
-      WERSA_STAGE("wersa_tail_copy", st,
-                  tail_copy_kernel<DH><<<c.B * c.H, 256, 0, st>>>(w.tail_out, MODE == 0 ? w.tail_D : nullptr, c.n,
-                                                                   c.n / 64 * 64, out0, tv, Dout));
-      if (out1)
-        WERSA_STAGE("wersa_tail_copy", st,
-                    tail_copy_kernel<DH><<<c.B * c.H, 256, 0, st>>>(w.tail_out + (int64_t)c.B * c.H * 64 * DH, nullptr, c.n,
-                                                                     c.n / 64 * 64, out1, tv, nullptr));
-    }
     return hipSuccess;
   };
   if (out1) {   // dV rides along with the K-side gradient (see dv_rides_along)
     constexpr bool OK = MODE == 2 && DH == 64;
     constexpr int MCV = OK ? 256 : 128;
+    if (c.n % 64 != 0) {
+      if (c.L > kTileL) return go(&rows_kernel<DH, MODE, NW, MCV, false, OK, OK, OK>);
+      return go(&rows_kernel<DH, MODE, NW, MCV, false, OK, false, OK>);
+    }
     if (c.L > kTileL) return go(&rows_kernel<DH, MODE, NW, MCV, false, false, OK, OK>);
     return go(&rows_kernel<DH, MODE, NW, MCV, false, false, false, OK>);
   }
@@ -2347,7 +2390,8 @@ wersa_status fast_haar_filter(const wersa_desc &c, const void *x, const float *f
 
 bool fast_supported(const wersa_desc &c) {
   return c.dtype == WERSA_BF16 && (c.d == 64 || c.d == 128) && c.m % 128 == 0 &&
-         c.stride_n % 8 == 0 && c.stride_h % 8 == 0 && c.stride_b % 8 == 0;
+         c.stride_n % 8 == 0 && c.stride_h % 8 == 0 && c.stride_b % 8 == 0 &&
+         (c.n % 64 == 0 || c.stride_n <= kMaxBufferStride);
 }
 
 size_t fast_workspace_bytes(const wersa_desc &c, int for_backward) {
