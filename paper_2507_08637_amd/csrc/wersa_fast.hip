@@ -2258,7 +2258,7 @@ wersa_status fast_forward_t(const wersa_desc &c, const bf16_t *q, const bf16_t *
     // the caller's column sums per 128 token rows: batch b owns row blocks [b n/128, (b+1) n/128)
     const int chunks = c.n / 128;
     WERSA_STAGE("gate_fwd_kernel", st,
-                gate_fwd_kernel<<<slices, 256, 0, st>>>(pooled->sums, chunks, c.n, c.d, c.L, c.H, gate_w, gate_b, scale_w,
+                gate_fwd_kernel<<<slices, kGateFwdThreads, 0, st>>>(pooled->sums, chunks, c.n, c.d, c.L, c.H, gate_w, gate_b, scale_w,
                                                        qbar, s, F, w.coef, (c.flags & WERSA_FLAG_POOLED_GATE) ? 1 : 0,
                                                        PooledLayout{chunks * pooled->hidden, c.d, pooled->hidden},
                                                        pooled->amax, chunks * (c.d / kPooledMaxCols), w.scalars,
@@ -2271,7 +2271,7 @@ wersa_status fast_forward_t(const wersa_desc &c, const bf16_t *q, const bf16_t *
                 qbar_partial_kernel<DH><<<dim3(p.chunksQ + su.blocks, slices), 256, 0, st>>>(q, tv, c.n, p.rowsQ, qpart,
                                                                                              p.chunksQ, su, w.qamax));
     WERSA_STAGE("gate_fwd_kernel", st,
-                gate_fwd_kernel<<<slices, 256, 0, st>>>(qpart, p.chunksQ, c.n, c.d, c.L, c.H, gate_w, gate_b, scale_w,
+                gate_fwd_kernel<<<slices, kGateFwdThreads, 0, st>>>(qpart, p.chunksQ, c.n, c.d, c.L, c.H, gate_w, gate_b, scale_w,
                                                        qbar, s, F, w.coef, (c.flags & WERSA_FLAG_POOLED_GATE) ? 1 : 0,
                                                        PooledLayout{(int64_t)c.H * p.chunksQ * c.d, (int64_t)p.chunksQ * c.d, c.d},
                                                        w.qamax, p.chunksQ, w.scalars,

@@ -1476,7 +1476,7 @@ wersa_status forward_t(const wersa_desc &c, const T *q, const T *k, const T *v, 
   const OmegaPack<T> om{omega, sigma, c.bw_floor, scalars, OA, OB, p.matrices, p.KS, p.CT, PT, (pieces + 255) / 256};
   WERSA_STAGE("split_pool", st, pool_kernel<T><<<dim3(p.chunks + om.blocks, slices, deep ? 2 : 1), 256, 0, st>>>(
       q, k, tv, p.s, vec, p.rows_per_chunk, p.chunks, qpart, kpart, om));
-  WERSA_STAGE("gate_fwd_kernel", st, gate_fwd_kernel<<<slices, 256, 0, st>>>(
+  WERSA_STAGE("gate_fwd_kernel", st, gate_fwd_kernel<<<slices, kGateFwdThreads, 0, st>>>(
       qpart, p.chunks, c.n, c.d, c.L, c.H, gate_w, gate_b, scale_w, saved + sv.qbar, saved + sv.s, saved + sv.F, coef,
       (c.flags & WERSA_FLAG_POOLED_GATE) ? 1 : 0,
       PooledLayout{(int64_t)c.H * p.chunks * c.d, (int64_t)p.chunks * c.d, c.d}, nullptr, 0, scalars));
