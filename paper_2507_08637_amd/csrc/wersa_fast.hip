@@ -1935,7 +1935,9 @@ __global__ __launch_bounds__(1024) void coarse_bwd_kernel(const float *TgQ, cons
 // The gradient kernels then run as without a normaliser: D = 1 and dD = 0 (written here).
 // part[slice][chunk] = sum over the chunk's rows of -<dO_t, O_t> rstd_t^2, the per-row term of
 // d sigma (N scales with 1 / sigma^2 and <dN_t, N_t> = <dO_t, O_t> eps rstd_t^2).
-// DH / 8 lanes share a row, 16 bytes each.
+// DH / 8 lanes share a row, 16 bytes each.  Bound by memory; its workgroups have a split of their own, enough of
+// them (kLnWgs) to fill every compute unit: with the contraction's split (16 slices of 4096 rows: 128 workgroups of
+// 32 dependent rounds of loads) it took 34 us, now 11 us for 50 MB.
 template <int DH>
 __global__ __launch_bounds__(256) void ln_prep_kernel(const bf16_t *dout, const bf16_t *out, View v,
                                                      const float *rstd, int n, int rows_per_chunk,
@@ -1946,6 +1948,7 @@ __global__ __launch_bounds__(256) void ln_prep_kernel(const bf16_t *dout, const 
   const int r = tid / CPR, cc = tid % CPR;
   const int64_t base = v.slice_base(slice);
   float acc = 0.f;
+#pragma unroll 2
   for (int t = t_begin + r; t < t_end; t += RPB) {
     const int64_t off = base + (int64_t)t * v.sn + cc * 8;
     const u16x8 g8 = *reinterpret_cast<const u16x8 *>(dout + off);
@@ -1987,6 +1990,7 @@ __global__ __launch_bounds__(256) void ln_prep_kernel(const bf16_t *dout, const 
 // host side
 // ---------------------------------------------------------------------------------------
 constexpr int kWavesGrad = 4;
+constexpr int kLnWgs = 2048;   // workgroups of ln_prep: eight of 256 threads per compute unit
 constexpr int waves_apply(int d) { return d == 64 ? 8 : 4; }   // head dimension 128: 512 registers per lane
 
 struct FastPlan {
@@ -1995,6 +1999,7 @@ struct FastPlan {
   int chunksC, rowsC;   // split of n in phiT_contract
   int rowGroupsA, rowsWgsA;   // apply-type rows kernel (4 waves): row groups / workgroups per slice
   int rowGroupsG, rowsWgsG;   // gradient-type rows kernel (8 waves)
+  int chunksL, rowsL;   // split of n in ln_prep
 };
 
 FastPlan fast_plan(const wersa_desc &c) {
@@ -2020,6 +2025,9 @@ FastPlan fast_plan(const wersa_desc &c) {
   const int bpc = (blocks + want - 1) / want;
   p.rowsC = bpc * 64;
   p.chunksC = (blocks + bpc - 1) / bpc;
+  const int wantL = kLnWgs / slices < 1 ? 1 : kLnWgs / slices, bpl = (blocks + wantL - 1) / wantL;
+  p.rowsL = bpl * 64;
+  p.chunksL = (blocks + bpl - 1) / bpl;
   p.rowGroupsA = (blocks + waves_apply(c.d) - 1) / waves_apply(c.d);
   // One resident workgroup per compute unit (the operand arrays fill most of the LDS): at most
   // 256 workgroups in total, so that no second, mostly empty round follows the first.
@@ -2074,7 +2082,7 @@ FastWs fast_ws(const wersa_desc &c, const FastPlan &p, int bwd, float *base, flo
   const int64_t mx = (int64_t)c.m * (c.d + 16);
   if (bwd) {
     w.dD = b.take(sl * c.n);
-    w.dDpart = b.take(sl * p.chunksC);
+    w.dDpart = b.take(sl * (c.flags & WERSA_FLAG_LAYERNORM ? p.chunksL : p.chunksC));
     w.dS = b.take(sl * md);
     w.dz = b.take(sl * c.m);
     w.dSx = reinterpret_cast<bf16_t *>(b.take(sl * mx / 2));
@@ -2321,7 +2329,7 @@ wersa_status fast_backward_t(const wersa_desc &c, const bf16_t *q, const bf16_t 
   const View nv{(int64_t)c.H * c.n * DH, (int64_t)c.n * DH, DH, c.H};
   if (ln) {
     WERSA_STAGE("wersa_ln_prep", st,
-                ln_prep_kernel<DH><<<dim3(p.chunksC, slices), 256, 0, st>>>(dout, out, tv, D, c.n, p.rowsC, w.dN,
+                ln_prep_kernel<DH><<<dim3(p.chunksL, slices), 256, 0, st>>>(dout, out, tv, D, c.n, p.rowsL, w.dN,
                                                                            w.ones, w.dD, w.dDpart));
     launch_contract<DH>(c, p, QF, q, w.dN, nv, nullptr, w.dD, nullptr, false, w, w.dS, w.dz, w.dSx, w.dST, w.dzb, st);
   } else {
@@ -2356,7 +2364,7 @@ wersa_status fast_backward_t(const wersa_desc &c, const bf16_t *q, const bf16_t 
                                                            c.d, c.H, s, gate_w, scale_w, w.dF, w.dlogit, w.dqbar,
                                                            (c.flags & WERSA_FLAG_POOLED_GATE) ? 1 : 0, w.coef));
   WERSA_STAGE("gate_bwd_params_kernel", st,
-              gate_bwd_params_kernel<<<gate_bwd_params_blocks(c.H, c.L, c.d), 256, 0, st>>>(w.dF, w.dlogit, s, qbar, w.dDpart, slices * p.chunksC,
+              gate_bwd_params_kernel<<<gate_bwd_params_blocks(c.H, c.L, c.d), 256, 0, st>>>(w.dF, w.dlogit, s, qbar, w.dDpart, slices * (ln ? p.chunksL : p.chunksC),
                                                         c.B, c.H, c.L, c.d, c.eps, w.scalars, dgate_w,
                                                         dgate_b, dscale_w, dsigma));
   const int64_t chunks = (int64_t)c.n * (DH / 8);
