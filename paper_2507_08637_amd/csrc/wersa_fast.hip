@@ -1826,11 +1826,19 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
 // dX[t][:] += dqbar / n (the pooled-query path; dqbar may be nullptr) + tile_add[t / 64][:] (the
 // part of the gated filter above level 6; may be nullptr), bf16 read-modify-write with 16-byte
 // accesses, four independent pieces per thread.
-template <int DH, bool TILE>   // TILE: tile_add is given (the plain instance has none of its code)
+// TILE: tile_add is given (the plain instance has none of its code), and blockIdx.z = 1 is dK with its own addends and
+// without the pooled term (a launch of its own before: 8 slices of 30000 rows, 17 + 14 us for the two, 26 us now).
+template <int DH, bool TILE>
 __global__ __launch_bounds__(256) void add_pooled_kernel(bf16_t *dq, View v, const float *dqbar, int n,
-                                                        float inv_n, const float *tile_add) {
+                                                        float inv_n, const float *tile_add, bf16_t *dk,
+                                                        const float *tile_add_k) {
   constexpr int CPR = DH / 8;
   const int slice = blockIdx.y;
+  if (TILE && blockIdx.z) {
+    dq = dk;
+    tile_add = tile_add_k;
+    dqbar = nullptr;
+  }
   const int64_t total = (int64_t)n * CPR;
   const int64_t e0 = (int64_t)blockIdx.x * 1024 + threadIdx.x;
   const int cc = threadIdx.x % CPR;   // 256 and 1024 are multiples of CPR: same columns for all four
@@ -1884,7 +1892,9 @@ __global__ __launch_bounds__(1024) void coarse_addend_kernel(const float *Tq, co
 // rows row .. row + d / 16 - 1 (one per workgroup) of the band partials part*[S][row + d / 16][L + 1], the
 // contribution of the levels above 6: with u_l = 2^-l * sum over 2^l-row blocks and columns of
 // blocksum(dX_F) * blocksum(X), band 6 gets -u_7, band l (7 .. L-1) gets u_l - u_{l+1}, band L
-// gets u_L (the gradient kernels leave u_6 alone in band 6 and zeros above).
+// gets u_L (the gradient kernels leave u_6 alone in band 6 and zeros above).  Bound by latency: a chain of barriers,
+// one per level and signal and two per inner product before, one per level now (8 slices of 469 tiles, 4 levels:
+// 30.7 -> 14.1 us).
 __global__ __launch_bounds__(1024) void coarse_bwd_kernel(const float *TgQ, const float *TgK, const float *TxQ,
                                                          const float *TxK, const float *coef, int ntiles, int d, int L,
                                                          float *pyr, float *AQ, float *AK, float *partQ,
@@ -1895,31 +1905,49 @@ __global__ __launch_bounds__(1024) void coarse_bwd_kernel(const float *TgQ, cons
   const int64_t base = (int64_t)slice * ntiles * d;
   float *Pg = pyr + (((int64_t)slice * 2 + side) * 2) * pyramid_floats(ntiles, d);
   float *Px = Pg + pyramid_floats(ntiles, d);
-  build_tile_pyramid((side ? TgK : TgQ) + base, ntiles, d, J, Pg, c, g);
-  build_tile_pyramid((side ? TxK : TxQ) + base, ntiles, d, J, Px, c, g);
-  tile_addend(Pg, coef + slice * kCoefStride, ntiles, d, J, (side ? AK : AQ) + base, c, g);
-  __shared__ float red[16];
+  // both pyramids level by level, the inner product of a level from the registers that hold its sums
+  __shared__ float red[kMaxBands][16];
   __shared__ float u[kMaxBands + 1];
-  const float *lg = Pg, *lx = Px;
+  const float *pg = (side ? TgK : TgQ) + base, *px = (side ? TxK : TxQ) + base;
+  float *lg = Pg, *lx = Px;
   int nprev = ntiles;
   for (int j = 1; j <= J; ++j) {
     const int nb = (nprev + 1) / 2;
     float acc = 0.f;
-#pragma unroll 4
-    for (int b = g; b < nb; b += kCoarseGroups) acc = fmaf(lg[b * d + c], lx[b * d + c], acc);
-    acc = wave_sum64(acc);
-    if (lane == 0) red[wave] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      float tot = 0.f;
-      for (int i = 0; i < 16; ++i) tot += red[i];
-      u[6 + j] = tot / (float)(1 << (6 + j));
+    for (int b0 = g; b0 < nb; b0 += kCoarseBatch * kCoarseGroups) {
+      float sg[kCoarseBatch], sx[kCoarseBatch];
+#pragma unroll
+      for (int i = 0; i < kCoarseBatch; ++i) {
+        sg[i] = tile_pair(pg, b0 + i * kCoarseGroups, nb, nprev, d, c);
+        sx[i] = tile_pair(px, b0 + i * kCoarseGroups, nb, nprev, d, c);
+      }
+#pragma unroll
+      for (int i = 0; i < kCoarseBatch; ++i) {
+        acc = fmaf(sg[i], sx[i], acc);
+        const int b = b0 + i * kCoarseGroups;
+        if (b < nb) {
+          lg[b * d + c] = sg[i];
+          lx[b * d + c] = sx[i];
+        }
+      }
     }
+    acc = wave_sum64(acc);
+    if (lane == 0) red[j][wave] = acc;
+    __threadfence_block();
     __syncthreads();
+    pg = lg;
+    px = lx;
     lg += nb * d;
     lx += nb * d;
     nprev = nb;
   }
+  if (wave == 0 && lane >= 1 && lane <= J) {
+    float tot = 0.f;
+    for (int i = 0; i < 16; ++i) tot += red[lane][i];
+    u[6 + lane] = tot / (float)(1 << (6 + lane));
+  }
+  tile_addend(Pg, coef + slice * kCoefStride, ntiles, d, J, (side ? AK : AQ) + base, c, g);
+  __syncthreads();
   if ((int)threadIdx.x <= L) {
     const int i = threadIdx.x;
     float val = 0.f;
@@ -2368,15 +2396,13 @@ wersa_status fast_backward_t(const wersa_desc &c, const bf16_t *q, const bf16_t 
                                                         c.B, c.H, c.L, c.d, c.eps, w.scalars, dgate_w,
                                                         dgate_b, dscale_w, dsigma));
   const int64_t chunks = (int64_t)c.n * (DH / 8);
-  const dim3 agrid((unsigned)((chunks + 1023) / 1024), slices);
+  const dim3 agrid((unsigned)((chunks + 1023) / 1024), slices, deep ? 2 : 1);
   if (deep) {
     WERSA_STAGE("wersa_add_pooled", st,
-                (add_pooled_kernel<DH, true><<<agrid, 256, 0, st>>>(dq, tv, w.dqbar, c.n, 1.0f / (float)c.n, w.gaddQ)));
-    WERSA_STAGE("wersa_add_pooled", st,
-                (add_pooled_kernel<DH, true><<<agrid, 256, 0, st>>>(dk, tv, nullptr, c.n, 0.f, w.gaddK)));
+                (add_pooled_kernel<DH, true><<<agrid, 256, 0, st>>>(dq, tv, w.dqbar, c.n, 1.0f / (float)c.n, w.gaddQ, dk, w.gaddK)));
   } else {
     WERSA_STAGE("wersa_add_pooled", st,
-                (add_pooled_kernel<DH, false><<<agrid, 256, 0, st>>>(dq, tv, w.dqbar, c.n, 1.0f / (float)c.n, nullptr)));
+                (add_pooled_kernel<DH, false><<<agrid, 256, 0, st>>>(dq, tv, w.dqbar, c.n, 1.0f / (float)c.n, nullptr, nullptr, nullptr)));
   }
   return hipGetLastError() == hipSuccess ? WERSA_OK : WERSA_ERR_LAUNCH;
 }
