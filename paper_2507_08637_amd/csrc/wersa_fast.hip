@@ -16,6 +16,8 @@
 // 2^-12, which the ReLU derivative needs); everything downstream of the ReLU uses bf16 MFMA.
 #include "wersa_internal.h"
 
+#include <type_traits>
+
 namespace wersa {
 namespace {
 
@@ -881,50 +883,82 @@ __global__ __launch_bounds__(256, 2) void phiT_contract_kernel(
 //   Mx  [m][DH+16]: row r = (M[r][0..DH), b[r], 0 x 15)   (A operand of dPhi = Y M^T + a b^T)
 //   MT  [DH][m]   : M transposed                           (B operand of Phi M)
 //   bb  [m]       : b in bf16
-// One workgroup = 64 consecutive outputs x 4 waves; wave g sums the chunks g, g+4, ... with up
+// One workgroup = 64 VEC consecutive outputs x 4 waves; wave g sums the chunks g, g+4, ... with up
 // to 16 loads in flight, the four partial sums meet in LDS in a fixed order.  Workgroups
-// [0, m*DH/64) handle M, the next m/64 handle b.
-template <int DH>
+// [0, m*DH/(64 VEC)) handle M, the ones after those b.
+// Two widths: VEC = 4 columns per lane (16-byte loads, S^T leaves as one piece per column through LDS instead of
+// 2-byte stores m apart) where that still gives every compute unit a workgroup; 1 where it does not (one slice of 131072 rows:
+// 64 workgroups would read 32 MB).  8 slices, m 256, d 64, 59 partials: 11.2 -> 7.8 us; 16 slices,
+// m 512, d 128, 8 partials: 13.8 -> 13.6 us.  Both add in the same order: the results are the same bits.
+template <int DH, int VEC>
 __global__ __launch_bounds__(256) void reduce_contract_kernel(const float *Spart, const float *zpart,
                                                              int chunks, int m, const float *scale_ptr,
                                                              float *S, float *z, bf16_t *Mx, bf16_t *MT,
                                                              bf16_t *bb) {
-  constexpr int DX = DH + 16;
-  const int slice = blockIdx.y, lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
+  constexpr int DX = DH + 16, COLS = 64 * VEC;   // elements of a workgroup
+  typedef float fv __attribute__((ext_vector_type(VEC)));
+  const int slice = blockIdx.y, tid = threadIdx.x, lane = tid & 63, grp = tid >> 6;
   const int64_t W = (int64_t)m * DH;
-  const int wblocks = (int)(W / 64);
+  const int wblocks = (int)(W / COLS);
   const bool is_z = (int)blockIdx.x >= wblocks;
   const int64_t count = is_z ? m : W;
-  const int64_t e = (is_z ? (int64_t)(blockIdx.x - wblocks) : (int64_t)blockIdx.x) * 64 + lane;
-  const float *p = (is_z ? zpart : Spart) + (int64_t)slice * chunks * count + e;
-  float acc = 0.f;
-  int c = grp;
-  for (; c + 60 < chunks; c += 64) {
-    float v16[16];
+  const int64_t e0 = (int64_t)(is_z ? blockIdx.x - wblocks : blockIdx.x) * COLS, el = e0 + lane * VEC;
+  __shared__ __align__(16) float part[4][COLS];
+  fv acc = (fv)(0.f);
+  if (el < count) {   // (m may end inside the last workgroup of z)
+    const float *p = (is_z ? zpart : Spart) + (int64_t)slice * chunks * count + el;
+    int c = grp;
+    for (; c + 60 < chunks; c += 64) {
+      fv v16[16];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) v16[u] = p[(int64_t)(c + 4 * u) * count];
+      for (int u = 0; u < 16; ++u) v16[u] = *reinterpret_cast<const fv *>(p + (int64_t)(c + 4 * u) * count);
 #pragma unroll
-    for (int u = 0; u < 16; ++u) acc += v16[u];
+      for (int u = 0; u < 16; ++u) acc += v16[u];
+    }
+    for (; c + 12 < chunks; c += 16) {
+      fv v4[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v4[u] = *reinterpret_cast<const fv *>(p + (int64_t)(c + 4 * u) * count);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc += v4[u];
+    }
+    for (; c < chunks; c += 4) acc += *reinterpret_cast<const fv *>(p + (int64_t)c * count);
   }
-  for (; c < chunks; c += 4) acc += p[(int64_t)c * count];
-  __shared__ float part[4][64];
-  part[grp][lane] = acc;
+  *reinterpret_cast<fv *>(&part[grp][lane * VEC]) = acc;
   __syncthreads();
-  if (grp != 0) return;
-  acc = ((part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane])) * scale_ptr[slice * kCoefStride];
-  const bf16_t b = f32_to_bf16(acc);
-  if (!is_z) {
-    S[(int64_t)slice * W + e] = acc;
-    const int r = (int)(e / DH), cidx = (int)(e % DH);
-    Mx[((int64_t)slice * m + r) * DX + cidx] = b;
-    MT[(int64_t)slice * W + (int64_t)cidx * m + r] = b;
-  } else {
-    z[(int64_t)slice * m + e] = acc;
-    bb[(int64_t)slice * m + e] = b;
-    bf16_t *ext = Mx + ((int64_t)slice * m + e) * DX + DH;
-    ext[0] = b;
+  const int64_t e = e0 + tid;
+  const bool mine = tid < COLS && e < count;
+  bf16_t b = 0;
+  if (mine) {
+    const float sum = ((part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid])) * scale_ptr[slice * kCoefStride];
+    b = f32_to_bf16(sum);
+    if (!is_z) {
+      S[(int64_t)slice * W + e] = sum;
+      const int r = (int)(e / DH), cidx = (int)(e % DH);
+      Mx[((int64_t)slice * m + r) * DX + cidx] = b;
+      if (VEC == 1) MT[(int64_t)slice * W + (int64_t)cidx * m + r] = b;
+    } else {
+      z[(int64_t)slice * m + e] = sum;
+      bb[(int64_t)slice * m + e] = b;
+      bf16_t *ext = Mx + ((int64_t)slice * m + e) * DX + DH;
+      ext[0] = b;
 #pragma unroll
-    for (int q = 1; q < 16; ++q) ext[q] = 0;
+      for (int q = 1; q < 16; ++q) ext[q] = 0;
+    }
+  }
+  if constexpr (VEC == 4) {
+    if (is_z) return;
+    constexpr int RW = COLS / DH;   // features of this workgroup: 4 or 2, so pieces of 8 or 4 bytes
+    typedef bf16_t bv __attribute__((ext_vector_type(RW)));
+    __shared__ bf16_t tile[COLS];
+    tile[tid] = b;
+    __syncthreads();
+    if (tid < DH) {
+      bv o;
+#pragma unroll
+      for (int q = 0; q < RW; ++q) o[q] = tile[q * DH + tid];
+      *reinterpret_cast<bv *>(MT + (int64_t)slice * W + (int64_t)tid * m + e0 / DH) = o;
+    }
   }
 }
 
@@ -2265,9 +2299,14 @@ void launch_contract(const wersa_desc &c, const FastPlan &p, const _Float16 *xf,
     else ragged ? go(&phiT_contract_kernel<DH, 32, false, true, false>) : go(&phiT_contract_kernel<DH, 32, false, false, false>);
   }
   const int64_t W = (int64_t)c.m * DH;
-  WERSA_STAGE("wersa_reduce_contract", st,
-              reduce_contract_kernel<DH><<<dim3((unsigned)(W / 64 + c.m / 64), slices), 256, 0, st>>>(
-                  w.Spart, w.zpart, p.chunksC, c.m, w.coef + kCoefCscale, S, z, Mx, MT, bb));
+  auto reduce = [&](auto VEC) {
+    constexpr int cols = 64 * VEC.value;
+    WERSA_STAGE("wersa_reduce_contract", st,
+                (reduce_contract_kernel<DH, VEC.value><<<dim3((unsigned)(W / cols + (c.m + cols - 1) / cols), slices), 256, 0, st>>>(
+                    w.Spart, w.zpart, p.chunksC, c.m, w.coef + kCoefCscale, S, z, Mx, MT, bb)));
+  };
+  if (slices * (W / 256) >= 256) reduce(std::integral_constant<int, 4>());
+  else reduce(std::integral_constant<int, 1>());
 }
 
 template <int DH>
