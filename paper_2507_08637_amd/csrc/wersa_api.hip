@@ -29,7 +29,6 @@ static bool misaligned(const void *p, size_t a) { return ((uintptr_t)p % a) != 0
 // One copy of the array lives on every device the library's code object is loaded on, at that
 // device's own address; the name below is only a host-side handle for hipGetSymbolAddress and is
 // never passed to a kernel.
-constexpr size_t kStaticScratchBytes = (size_t)40 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
 static void *g_scratch_ptr[kMaxDevices] = {};

@@ -51,9 +51,19 @@ inline bool use_fast(const wersa_desc &c) {
   return !(c.flags & WERSA_FLAG_GENERIC_PATH) && fast_supported(c);
 }
 
+// Scratch array of wersa_forward_static.
+constexpr size_t kStaticScratchBytes = (size_t)40 << 20;
+size_t generic_workspace_bytes(const wersa_desc &c, int for_backward);
+size_t split_workspace_bytes(const wersa_desc &c, int for_backward);
+
 // Split path (float32 arithmetic on the bf16 matrix cores): what the MFMA path does not take, head
-// dimensions up to 128.
-inline bool use_split(const wersa_desc &c) { return !use_fast(c) && c.d <= 128; }
+// dimensions up to 128.  With far fewer rows than features its copies of S (m d) outweigh the feature matrix
+// (n m) that it saves: 32 slices, n 64, d 128, m 1024 take 41 MiB instead of 29, more than wersa_forward_static has.
+// Shapes that fit there on the generic path alone stay on it.
+inline bool use_split(const wersa_desc &c) {
+  if (use_fast(c) || c.d > 128) return false;
+  return split_workspace_bytes(c, 0) <= kStaticScratchBytes || generic_workspace_bytes(c, 0) > kStaticScratchBytes;
+}
 struct SplitSizes {
   int64_t X, OA, OB, SA;   // floats: packed Q_F or K_F, Omega both ways, S with its features as vectors
 };
@@ -140,8 +150,7 @@ void prof_end(hipStream_t st);
     ::wersa::prof_end(st);           \
   } while (0)
 
-// Generic path: float32 arithmetic for every dtype, staged through workspace: head dimensions above 128.
-size_t generic_workspace_bytes(const wersa_desc &c, int for_backward);
+// Generic path: float32 arithmetic for every dtype, staged through workspace: what the split path does not take.
 wersa_status generic_forward(const wersa_desc &c, const void *q, const void *k, const void *v,
                              const void *omega_rf, const float *sigma, const float *gate_w,
                              const float *gate_b, const float *scale_w, void *out, float *saved,
@@ -152,7 +161,6 @@ wersa_status generic_backward(const wersa_desc &c, const void *q, const void *k,
                               const void *dout, const float *saved, void *dq, void *dk, void *dv,
                               float *dgate_w, float *dgate_b, float *dscale_w, float *dsigma,
                               float *ws, hipStream_t st);
-size_t split_workspace_bytes(const wersa_desc &c, int for_backward);
 wersa_status split_forward(const wersa_desc &c, const void *q, const void *k, const void *v, const void *omega_rf,
                            const float *sigma, const float *gate_w, const float *gate_b, const float *scale_w, void *out,
                            float *saved, float *ws, hipStream_t st);

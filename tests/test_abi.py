@@ -48,6 +48,14 @@ def test_sizes_and_status_strings(lib):
     assert lib.wersa_version() >= 100
 
 
+@pytest.mark.parametrize("dtype,flags", [(0, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("L", [3, 8])
+def test_few_rows_many_features_fit_the_static_scratch(lib, L, dtype, flags):
+    """29 MiB on the generic path; packed copies of S would take 41 and have wersa_forward_static refuse the call."""
+    d = _desc(H=32, n=64, d=128, L=L, m=1024, dtype=dtype, flags=flags, stride_b=32 * 64 * 128, stride_h=64 * 128, stride_n=128)
+    assert 0 < lib.wersa_workspace_bytes(ctypes.byref(d), 0) <= lib.wersa_static_scratch_bytes()
+
+
 @pytest.mark.parametrize("kw,status", [
     (dict(B=0), 1), (dict(n=0), 1), (dict(L=-1), 1), (dict(dtype=7), 1), (dict(bw_floor=0.0), 1),
     (dict(stride_n=32), 1), (dict(stride_h=0), 1), (dict(flags=1 << 20), 1),

@@ -58,6 +58,24 @@ def test_split_path_shapes(shape, dtype):
     _check(res, hp.oracle_backward(p, cfg), hp.oracle_forward(p, cfg), cfg)
 
 
+@pytest.mark.parametrize("L", [3, 8])
+def test_few_rows_many_features_keep_the_generic_kernels(L):
+    """The shape class that fits wersa_forward_static's scratch on the generic kernels alone: forward and backward
+    meet the same bars, and the call without workspace gives the same bits as the one with."""
+    import torch
+    from paper_2507_08637_amd import binding
+    cfg = dict(B=1, H=32, n=64, d=128, L=L, m=1024, dtype="f32", flavour="plain", seed_base=5300, q_mean=0.5)
+    p = workloads.make_inputs(**cfg)
+    res = hp.gpu_forward_backward(p, cfg, flags=1)
+    _check(res, hp.oracle_backward(p, cfg), hp.oracle_forward(p, cfg), cfg)
+    t = hp.to_device(p, "f32")
+    args = (t["Q"], t["K"], t["V"], t["Omega"], t["sigma"], t["Wg"], t["bg"], t["omega"], L)
+    ref, saved = binding.wersa_forward(*args)
+    out = torch.empty_like(ref)
+    binding.wersa_forward_static(*args, out, torch.empty_like(saved))
+    assert torch.equal(out, ref)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_split_path_rows_off_16_byte_alignment(dtype):
     """A row stride of d + 1 elements: every load of the packing kernels falls back to single elements, same bits."""
