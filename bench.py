@@ -75,12 +75,20 @@ def kernel_models(cfg):
         "wersa_ln_prep": ("hbm", "hbm", 3 * nd * e),
         "wersa_add_pooled": ("hbm", "hbm", 2 * nd * e),
     }
-    # attention block (configuration 5): hidden x hidden projections over all tokens.  Average
-    # launch: forward and backward hold 6 NT launches worth 8 products (dX sums three), 4 TN launches.
+    # float32 arithmetic on the bf16 matrix cores (d <= 128): the method's contractions, each of which takes
+    # three bf16 products (one operand a bf16 tensor) or six
+    models["split_contract"] = ("mfma", "mfma_bf16", 2 * unit)   # projection + Phi^T Y
+    models["split_apply"] = ("mfma", "mfma_bf16", 2 * unit)      # projection + Phi S
+    models["split_apply_dv"] = ("mfma", "mfma_bf16", 2 * unit)   # projection + Phi dS
+    models["split_grad"] = ("mfma", "mfma_bf16", 3 * unit)       # projection, dPhi, dX_F
+    models["split_grad_k"] = ("mfma", "mfma_bf16", 4 * unit)     # the same and dV
+    # attention block (configuration 5): hidden x hidden projections over all tokens.  Average launch: each form
+    # has two launches worth four products (NN: Q', K', V' in one, Y; NT: dA, dX as a sum of three; TN: the weight
+    # gradients of Q, K, V in one, dW^out).
     hidden, tokens = cfg["H"] * d, cfg["B"] * n
     gemm = 2.0 * tokens * hidden * hidden
-    models["wersa_gemm_nt"] = ("mfma", "mfma_bf16", gemm * 8.0 / 6.0)
-    models["wersa_gemm_tn"] = ("mfma", "mfma_bf16", gemm)
+    for form in ("nn", "nt", "tn"):
+        models["wersa_gemm_" + form] = ("mfma", "mfma_bf16", 2 * gemm)
     return models
 
 
