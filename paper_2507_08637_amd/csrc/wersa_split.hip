@@ -13,6 +13,10 @@
 // (7 instructions per pair of elements), so head dimensions 16 and 32 are bound by the vector units and
 // 64 and above by the matrix cores.  Two waves per SIMD let one run under the other.
 //
+// Measured against the generic kernels, which write every n x m feature matrix to memory: float32 training step, 128
+// slices of 4000 tokens, d 32, m 1024: 13990 -> 2464 us; bf16 training step, 8 slices of 131072 tokens, d 16, m 1024:
+// 26290 -> 2264 us; float32 inference, one slice of 1024 tokens, d 64, m 64: 118 -> 38 us.
+//
 // Layout: every operand is kept in the order in which a wave loads it ("operand tile": 32 vectors x 16
 // k-values of bf16; lane (l32, h) holds vector l32, k = 8 h .. 8 h + 7, 16 bytes; 1 KiB).  Where k runs
 // over the rows of an accumulator tile (features, or tokens), the k-slots stand for the rows in the
