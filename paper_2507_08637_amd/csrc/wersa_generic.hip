@@ -4,6 +4,8 @@
 // own where the streaming kernel does not take it.  Reductions are fixed-order two-pass sums.
 #include "wersa_internal.h"
 
+#include <type_traits>
+
 namespace wersa {
 namespace {
 
