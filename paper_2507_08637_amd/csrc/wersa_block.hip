@@ -251,40 +251,47 @@ __global__ __launch_bounds__(64 * kGemmWaves, WT == 128 ? 1 : 2) void gemm_bf16_
     constexpr int ES = WT + 8, PPR = WT / 8;   // tile row stride; 16-byte pieces per row
     bf16_t *C = reinterpret_cast<bf16_t *>(job.c[which]);
     if (colsum && which == 0) {
+      // Per column one chain over a lane's 64 of the 128 rows; with WT = 64 rows 64 .. 127 are another wave's, which goes
+      // on from where the first one stopped, so that the sums have the same bits with either tile.
       float sum[TI], mx[TI];
+      auto add_rows = [&]() {
 #pragma unroll
-      for (int j = 0; j < TI; ++j) {
-        sum[j] = mx[j] = 0.f;
+        for (int j = 0; j < TI; ++j)
 #pragma unroll
-        for (int i = 0; i < TI; ++i)
+          for (int i = 0; i < TI; ++i)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            sum[j] += acc[i][j][r];
-            mx[j] = fmaxf(mx[j], fabsf(acc[i][j][r]));
-          }
-        sum[j] += __shfl_xor(sum[j], 32, 64);   // the two half-waves hold the two halves of every 8-row group
-      }
-      float *other = reinterpret_cast<float *>(smem_raw);   // WT = 64: rows 64 .. 127 are another wave's
+            for (int r = 0; r < 16; ++r) {
+              sum[j] += acc[i][j][r];
+              mx[j] = fmaxf(mx[j], fabsf(acc[i][j][r]));
+            }
+      };
+#pragma unroll
+      for (int j = 0; j < TI; ++j) sum[j] = mx[j] = 0.f;
+      if (WT == 128 || wave < 2) add_rows();
       if (WT == 64) {
-        float *mine = other + (wave & 1) * 192;
-        if (wave >= 2) {
-#pragma unroll
-          for (int j = 0; j < TI; ++j) {
-            if (h == 0) mine[32 * j + l32] = sum[j];
-            mine[64 + 64 * j + lane] = mx[j];
-          }
-        }
-        __syncthreads();
+        float *carry = reinterpret_cast<float *>(smem_raw) + (wave & 1) * (2 * TI * 64) + lane;
         if (wave < 2) {
 #pragma unroll
           for (int j = 0; j < TI; ++j) {
-            sum[j] += mine[32 * j + l32];
-            mx[j] = fmaxf(mx[j], mine[64 + 64 * j + lane]);
+            carry[64 * j] = sum[j];
+            carry[64 * (TI + j)] = mx[j];
           }
         }
         __syncthreads();
+        if (wave >= 2) {
+#pragma unroll
+          for (int j = 0; j < TI; ++j) {
+            sum[j] = carry[64 * j];
+            mx[j] = carry[64 * (TI + j)];
+          }
+          add_rows();
+        }
+        __syncthreads();
       }
-      if (WT == 128 || wave < 2) {
+#pragma unroll
+      for (int j = 0; j < TI; ++j)
+        sum[j] += __shfl_xor(sum[j], 32, 64);   // the two half-waves hold the two halves of every 8-row group
+      if (WT == 128 || wave >= 2) {
         const int64_t blk = (m0 + wm) >> 7;
         static_assert(kPooledMaxCols == 64, "two column tiles per maximum");
 #pragma unroll
@@ -380,10 +387,10 @@ BlockPlan block_plan(const wersa_desc &c) {
   p.tokens = (int64_t)c.B * c.n;
   p.hidden = (int64_t)c.H * c.d;
   p.act = p.tokens * p.hidden;
-  // Weight gradients: 512 workgroups of the large tile per product (the three of Q, K, V share a launch), at least
-  // 256 tokens each.
+  // Weight gradients: 1024 workgroups of the large tile per product (the three of Q, K, V share a launch), at least
+  // 256 tokens each.  (512 are as fast but make the float32 chain over the tokens of a split twice as long.)
   const int64_t tiles = (p.hidden / kBigTile) * (p.hidden / kBigTile);
-  int64_t z = 512 / tiles;
+  int64_t z = 1024 / tiles;
   if (z > kMaxSplit) z = kMaxSplit;
   if (z > p.tokens / kMinChunk) z = p.tokens / kMinChunk;
   if (z < 1) z = 1;
