@@ -4,7 +4,7 @@
 // Every float32 operand of a contraction is written as a sum of three bf16 values,
 //   x = x0 + x1 + x2,  x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1)   (24 significant bits),
 // and a product of two such operands is the six bf16 products x0 y0, x0 y1, x1 y0, x0 y2, x1 y1, x2 y0
-// accumulated in float32; what is left out is of the order of 2^-25 of |x y|, a rounding error of the
+// accumulated in float32; what is left out (x1 y2, x2 y1, x2 y2) is at most 2^-24 of |x y|, a rounding error of the
 // float32 product itself.  A bf16 tensor is one exact term, so products with it take three.  The bf16
 // matrix rate is 16 times the float32 one, so even six products leave a factor of 2.7.
 //
@@ -164,6 +164,18 @@ __device__ __forceinline__ f32x16 mfma_terms(f32x16 acc, const bf16x8 *x, const 
   }
   return acc;
 }
+// The same products with the leading one in acc and the others in lo (see apply_terms); lo may be acc.
+template <int NB>
+__device__ __forceinline__ void add_terms(f32x16 &acc, f32x16 &lo, const bf16x8 *x, const bf16x8 *y) {
+  if (NB == 3) {
+    lo = mfma(x[0], y[2], lo);
+    lo = mfma(x[1], y[1], lo);
+  }
+  lo = mfma(x[2], y[0], lo);
+  if (NB == 3) lo = mfma(x[0], y[1], lo);
+  lo = mfma(x[1], y[0], lo);
+  acc = mfma(x[0], y[0], acc);
+}
 __device__ __forceinline__ bf16x8 lds_operand(const bf16_t *tile, int lane) {
   return *reinterpret_cast<const bf16x8 *>(tile + lane * 8);
 }
@@ -179,6 +191,15 @@ __device__ __forceinline__ void store_operand(bf16_t *tile, int lane, bf16x8 v) 
 __device__ __forceinline__ float positive(float x) { return __builtin_amdgcn_fmed3f(x * __builtin_inff(), 0.f, 1.f); }
 // As integers, negative floats are negative: one instruction (fmaxf is two: it quiets a NaN first).
 __device__ __forceinline__ float relu(float x) { return __int_as_float(max(__float_as_int(x), 0)); }
+
+// Product of the 16 values of an accumulator tile that a lane holds with 16 weights.  D and z are sums of these, D of eight
+// at a time: one chain over all features or tokens is four times as far from the exact sum at 4096 features.
+__device__ __forceinline__ float dot16(const f32x16 &x, const f32x4 (&w)[4]) {
+  float acc = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc = fmaf(x[i], w[i >> 2][i & 3], acc);
+  return acc;
+}
 
 // Eight consecutive elements as float; vec: the tensor's rows are 16-byte aligned.
 __device__ __forceinline__ void load8(const float *p, bool vec, float *v) {
@@ -329,21 +350,27 @@ struct Geo {
   // free: [S0 | S1] and [S2 | 0] take four products instead of six (see apply_terms).
   static constexpr int NSB = DH == 16 ? 4 : 6 * CT;
 };
-// acc + Phi S for one half of a feature tile and one column tile; sb: the operand tiles of S from lds_operand.
+// Phi S for one half of a feature tile and one column tile; sb: the operand tiles of S from lds_operand.  acc takes the
+// product of the leading terms, lo all others (together Phi S): acc is rounded once per 16 features instead of six
+// times, and the slight bias of the matrix cores' rounding towards zero stays in proportion.  In one accumulator O came
+// out 9e-8 too small at 4096 features, the same in all columns of a row, which <dO, O> does not average out.
+// One float32 sequence of 2048 tokens, d 32, 4096 features, error against float64: O 6.9e-7 -> 3.4e-7, dQ 8.9e-7 -> 2.7e-7,
+// dW_g 4.3e-7 -> 1.3e-7; 4000 tokens, 1024 features: 3.8e-7 -> 1.7e-7, 5.0e-7 -> 2.2e-7, 1.7e-7 -> 1.2e-7.  Same time: the products are as many.
 template <int DH>
-__device__ __forceinline__ f32x16 apply_terms(f32x16 acc, const bf16x8 *p, const bf16_t *sb, int a, int ct, int lane) {
+__device__ __forceinline__ void apply_terms(f32x16 &acc, f32x16 &lo, const bf16x8 *p, const bf16_t *sb, int a, int ct, int lane) {
   if (DH == 16) {   // columns 0-15: p0 S2 + (p2 + p1 + p0) S0; columns 16-31: (p2 + p1 + p0) S1; added at the end
     const bf16x8 s01 = lds_operand(sb + 2 * a * kTile, lane), s2 = lds_operand(sb + (2 * a + 1) * kTile, lane);
-    acc = mfma(p[0], s2, acc);
-    acc = mfma(p[2], s01, acc);
-    acc = mfma(p[1], s01, acc);
-    return mfma(p[0], s01, acc);
+    lo = mfma(p[0], s2, lo);
+    lo = mfma(p[2], s01, lo);
+    lo = mfma(p[1], s01, lo);
+    acc = mfma(p[0], s01, acc);
+    return;
   }
   constexpr int CT = DH < 32 ? 1 : DH / 32;
   bf16x8 y[3];
 #pragma unroll
   for (int i = 0; i < 3; ++i) y[i] = lds_operand(sb + ((a * CT + ct) * 3 + i) * kTile, lane);
-  return mfma_terms<3, false>(acc, p, y);
+  add_terms<3>(acc, lo, p, y);
 }
 // sum over the levels above four of coef_l * (block sum): levels 5 and 6 from the 16-row sums of a tile
 template <int CW>
@@ -662,12 +689,10 @@ __global__ __launch_bounds__(512, 2) void contract_kernel(const bf16_t *X, const
 #pragma unroll
         for (int i = 0; i < 16; ++i) R[i] = relu(R[i]);
         if (DH > 16) {
+          f32x4 w4[4];
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const f32x4 w4 = *reinterpret_cast<const f32x4 *>(&lw[b][g * 32 + 8 * j + 4 * h]);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) zacc = fmaf(R[4 * j + i], w4[i], zacc);
-          }
+          for (int j = 0; j < 4; ++j) w4[j] = *reinterpret_cast<const f32x4 *>(&lw[b][g * 32 + 8 * j + 4 * h]);
+          zacc += dot16(R, w4);
         }
         with_split<mfma_residuals(DH, PT)>(R, ni, [&](int a, const bf16x8 *p) {
 #pragma unroll
@@ -703,6 +728,25 @@ __global__ __launch_bounds__(512, 2) void contract_kernel(const bf16_t *X, const
 // extension tile that carries the rank-one term dD z^T (three-term products in six k-slots), and columns
 // as vectors with k = features.  Grid (feature tiles, slices).
 // ------------------------------------------------------------------------------------
+// Sum of the values at p, p + step, ...: eight at a time (in flight together) as a tree, eight of these in a chain, and a
+// chain of those.  In one chain, the hundreds of shares of a long sequence would lose more than the products do.
+template <typename V>
+__device__ __forceinline__ V sum_shares(const float *p, int64_t step, int shares) {
+  V acc = (V)(0.f), part = (V)(0.f);
+  int sh = 0;
+  for (; sh + 8 <= shares; sh += 8) {
+    V x[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = *reinterpret_cast<const V *>(p + (sh + i) * step);
+    part += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+    if (sh % 64 == 56) {
+      acc += part;
+      part = (V)(0.f);
+    }
+  }
+  for (; sh < shares; ++sh) part += *reinterpret_cast<const V *>(p + sh * step);
+  return acc + part;
+}
 template <int DH>
 __global__ __launch_bounds__(256) void reduce_kernel(const float *part, const float *zpart, int shares, int zcols,
                                                     const float *scalars, Dims s, float *S, float *z, float *zpad,
@@ -715,27 +759,16 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float *part, const fl
   const float c = scalars[0];
   const int64_t step = (int64_t)s.mt * 32 * PW;
   const float *p0 = part + ((int64_t)slice * shares * s.mt + ft) * 32 * PW;
-  // four lanes groups of the shares would change the order with the count; each element is one chain
 #pragma unroll
   for (int u = 0; u < 32 * PW / 1024; ++u) {
     const int e = (tid + 256 * u) * 4;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    int sh = 0;
-    for (; sh + 8 <= shares; sh += 8) {   // eight loads in flight
-      f32x4 x[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) x[i] = *reinterpret_cast<const f32x4 *>(p0 + (sh + i) * step + e);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) acc += x[i];
-    }
-    for (; sh < shares; ++sh) acc += *reinterpret_cast<const f32x4 *>(p0 + sh * step + e);
+    const f32x4 acc = sum_shares<f32x4>(p0 + e, step, shares);
 #pragma unroll
     for (int i = 0; i < 4; ++i) tile[(e / PW) * LS + e % PW + i] = acc[i] * c;
   }
   if (DH > 16 && tid < 32) {
     const float *zp = zpart + ((int64_t)slice * shares * s.mt + ft) * 32 + tid;
-    float acc = 0.f;
-    for (int sh = 0; sh < shares; ++sh) acc += zp[(int64_t)sh * s.mt * 32];
+    const float acc = sum_shares<float>(zp, (int64_t)s.mt * 32, shares);
     zt[tid] = acc * c;
   }
   __syncthreads();
@@ -853,13 +886,13 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(c
   sg.p0 = OA;
   sg.p1 = SB + (int64_t)slice * s.mt * NB * kTile;
   sg.p2 = sg.p3 = nullptr;
-  f32x16 acc[RT][G::CT];
-  float dsum[RT];
+  f32x16 acc[RT][G::CT], lo[RT][G::CT];
+  float dsum[RT], dpart[RT];   // Phi z: of all groups of eight feature tiles before, of this one
 #pragma unroll
   for (int r = 0; r < RT; ++r) {
-    dsum[r] = 0.f;
+    dsum[r] = dpart[r] = 0.f;
 #pragma unroll
-    for (int ct = 0; ct < G::CT; ++ct) acc[r][ct] = zero16();
+    for (int ct = 0; ct < G::CT; ++ct) acc[r][ct] = lo[r][ct] = zero16();
   }
   const NegIdentity ni(lane);
   const float *zs = zpad + (int64_t)slice * s.mt * 32;
@@ -898,13 +931,18 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(c
         }
 #pragma unroll
         for (int i = 0; i < 16; ++i) R[i] = relu(R[i]);
-        if (ZV)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) dsum[r] = fmaf(R[i], z4[i >> 2][i & 3], dsum[r]);
+        if (ZV) dpart[r] += dot16(R, z4);
         with_split<mfma_residuals(DH, PT)>(R, ni, [&](int a, const bf16x8 *p) {
 #pragma unroll
-          for (int ct = 0; ct < G::CT; ++ct) acc[r][ct] = apply_terms<DH>(acc[r][ct], p, lb, a, ct, lane);   // rows: tokens, lanes: columns
+          for (int ct = 0; ct < G::CT; ++ct) apply_terms<DH>(acc[r][ct], lo[r][ct], p, lb, a, ct, lane);   // rows: tokens, lanes: columns
         });
+      }
+    }
+    if (ZV && (!more || (f0 + FC) % 8 == 0)) {
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        dsum[r] += dpart[r];
+        dpart[r] = 0.f;
       }
     }
     if (more) {
@@ -927,6 +965,8 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(c
       const int row = 8 * (i >> 2) + 4 * h + (i & 3), t = 32 * tb + row;
       float Dt = 1.f;
       if (ZV) Dt = __shfl(Dl, row, 64);
+#pragma unroll
+      for (int ct = 0; ct < G::CT; ++ct) acc[r][ct][i] += lo[r][ct][i];
       if (DH == 16) acc[r][0][i] += __shfl_xor(acc[r][0][i], 16, 64);
 #pragma unroll
       for (int ct = 0; ct < G::CT; ++ct) {
@@ -941,6 +981,10 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(c
   }
 }
 
+// Whether the gradient kernel keeps an accumulator for the small terms too: where the registers hold it.
+constexpr bool grad_low_terms(int DH, int PT, bool DV, int RT) {
+  return DH == 32 || (DH == 16 && (RT == 1 || (PT == 1 && !DV))) || (DH == 64 && !DV);
+}
 // dX_F of one side: R = X Omega, G = Y S^T + w z^T (Y = dN, S, w = dD on the query side; Y = V, dS, w = 1
 // on the key side), dX_F = c rowscale ((G masked where R > 0) Omega^T) in float32 [slice][32 nt][DH].
 // DV: dV = c ReLU(R) dS rides along.  ddw, rowscale nullptr: 1.
@@ -978,12 +1022,14 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void grad_kernel(co
   sg.p1 = SA + (int64_t)slice * s.mt * NSA * kTile;
   sg.p2 = OB;
   sg.p3 = DV ? SB + (int64_t)slice * s.mt * NSB * kTile : nullptr;
-  f32x16 acc[RT][G::CT], accv[DV ? RT : 1][G::CT];
+  constexpr bool LO = grad_low_terms(DH, PT, DV, RT);
+  f32x16 acc[RT][G::CT], low[LO ? RT : 1][G::CT], accv[DV ? RT : 1][G::CT];
 #pragma unroll
   for (int r = 0; r < RT; ++r)
 #pragma unroll
     for (int ct = 0; ct < G::CT; ++ct) {
       acc[r][ct] = zero16();
+      if (LO) low[LO ? r : 0][ct] = zero16();
       if (DV) accv[r][ct] = zero16();
     }
   const NegIdentity ni(lane);
@@ -1026,13 +1072,13 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void grad_kernel(co
             bf16x8 o[PT];
 #pragma unroll
             for (int i = 0; i < PT; ++i) o[i] = lds_operand(lo + ((a * G::CT + ct) * PT + i) * kTile, lane);
-            acc[r][ct] = mfma_terms<PT, false>(acc[r][ct], p, o);   // rows: tokens, lanes: columns
+            add_terms<PT>(acc[r][ct], LO ? low[LO ? r : 0][ct] : acc[r][ct], p, o);   // rows: tokens, lanes: columns
           }
         });
         if (DV)
           with_split<mfma_residuals(DH, PT)>(R, ni, [&](int a, const bf16x8 *p) {
 #pragma unroll
-            for (int ct = 0; ct < G::CT; ++ct) accv[r][ct] = apply_terms<DH>(accv[r][ct], p, lv, a, ct, lane);
+            for (int ct = 0; ct < G::CT; ++ct) apply_terms<DH>(accv[r][ct], accv[r][ct], p, lv, a, ct, lane);
           });
       }
     }
@@ -1050,6 +1096,9 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void grad_kernel(co
     for (int i = 0; i < 16; ++i) {
       const int row = 8 * (i >> 2) + 4 * h + (i & 3), t = 32 * tb + row;
       const float sc = rowscale ? __shfl(rs, row, 64) : c;
+      if (LO)
+#pragma unroll
+        for (int ct = 0; ct < G::CT; ++ct) acc[r][ct][i] += low[LO ? r : 0][ct][i];
       if (DV && DH == 16) accv[r][0][i] += __shfl_xor(accv[r][0][i], 16, 64);
 #pragma unroll
       for (int ct = 0; ct < G::CT; ++ct) {
@@ -1483,7 +1532,8 @@ wersa_status forward_t(const wersa_desc &c, const T *q, const T *k, const T *v, 
   WERSA_STAGE("gate_fwd_kernel", st, gate_fwd_kernel<<<slices, kGateFwdThreads, 0, st>>>(
       qpart, p.chunks, c.n, c.d, c.L, c.H, gate_w, gate_b, scale_w, saved + sv.qbar, saved + sv.s, saved + sv.F, coef,
       (c.flags & WERSA_FLAG_POOLED_GATE) ? 1 : 0,
-      PooledLayout{(int64_t)c.H * p.chunks * c.d, (int64_t)p.chunks * c.d, c.d}, nullptr, 0, scalars));
+      PooledLayout{(int64_t)c.H * p.chunks * c.d, (int64_t)p.chunks * c.d, c.d}, nullptr, 0, scalars,
+      AmaxLayout{0, 0, 0, 1}, 1));
   if (deep)
     WERSA_STAGE("split_deep", st, deep_addend_kernel<<<dim3(slices, 2, c.d / kCoarseCols), 1024, 0, st>>>(
         qpart, kpart, coef, p.ntl, c.d, c.L, w.pyr, addQ, addK));

@@ -1,4 +1,4 @@
-"""The pooled query (Section 3.1 step 4) bit for bit: four interleaved float32 sums over the partial sums of Q,
+"""The pooled query (Section 3.1 step 4) of the MFMA path bit for bit: four interleaved float32 sums over the partial sums of Q,
 ((s0 + s1) + (s2 + s3)) / n, whatever kernel adds them and with how many waves.  A last bit of it moves the filter and,
 at rounding edges of the operands and of the ReLU's step, everything after.  One row per 64-row tile is not
 zero, so that the partial sums of a transform deeper than one tile are exactly those rows."""
@@ -18,12 +18,12 @@ def _interleaved(parts, n):
 
 @pytest.mark.parametrize("flags", [0, 4], ids=["plain", "pooled_gate"])
 @pytest.mark.parametrize("tiles", [1, 4, 31, 33, 100, 161, 400])
-@pytest.mark.parametrize("dtype,d,m", [("bf16", 64, 128), ("bf16", 128, 128), ("f32", 16, 32), ("f32", 112, 32)])
-def test_order_of_the_partial_sums(dtype, d, m, tiles, flags):
+@pytest.mark.parametrize("d", [64, 128])
+def test_order_of_the_partial_sums(d, tiles, flags):
     import torch
     from paper_2507_08637_amd import binding
-    B, H, L, n = 1, 3, 7, 64 * tiles - 5
-    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    B, H, L, n, m = 1, 3, 7, 64 * tiles - 5, 128
+    tdt = torch.bfloat16
     g = torch.Generator(device="cuda").manual_seed(tiles * d)
 
     def normal(*s):

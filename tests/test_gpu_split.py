@@ -95,3 +95,57 @@ def test_split_path_rows_off_16_byte_alignment(dtype):
         outs.append([out, g["dq"], g["dk"], g["dv"], g["dgate_w"]])
     for a, b in zip(*outs):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n,d,m,bound", [
+    # long chains over the features (D, O): sixteen features, eight of these, sixteen of those for D; for O one rounding of
+    # its accumulator per 16 features
+    (2048, 32, 4096, dict(S=1.5e-7, z=1.2e-7, D=1.5e-7, O=4.5e-7)),
+    (2048, 16, 4096, dict(S=1.5e-7, z=1.2e-7, D=1.5e-7, O=4.5e-7)),
+    # and over the tokens (S, z): hundreds of shares
+    (100000, 64, 128, dict(S=1.4e-7, z=1.4e-7, D=1.4e-7, O=1.3e-7)),
+])
+def test_sums_stay_close_to_float64(n, d, m, bound):
+    """n additions of like terms one after the other are off by about 2.5e-8 sqrt(n / 3), so the bounds hold chains of a few
+    ten at the most; the kernels that wrote every feature matrix to memory met D 1.5e-7, O 6.7e-7, z 2.5e-7 here, one chain
+    for each sum D 3.4e-7, O 6.9e-7, S and z 4e-7.  Medians over seven inputs."""
+    import torch
+    from paper_2507_08637_amd import binding
+    L, errs = 2, {}
+    for seed in range(7):
+        g = torch.Generator(device="cuda").manual_seed(seed)
+
+        def normal(*s):
+            return torch.randn(s, generator=g, device="cuda")
+
+        wave = torch.sin(torch.arange(n, device="cuda") / 40.0)[:, None]
+        q, k, v = (normal(n, d) * s + a * wave + c for s, a, c in ((1, 0.7, 0.2), (1, 0.7, 0.2), (0.3, 1, 1)))
+        omega, sigma, gw, gb = normal(d, m), torch.ones(1, device="cuda"), normal(1, L + 1, d) / d ** 0.5, 0.5 * normal(1, L + 1)
+        sw = 1 + 0.1 * normal(L + 1)
+        qkv = [x[None, None] for x in (q, k, v)]
+        out, saved = binding.wersa_forward(*qkv, omega, sigma, gw, gb, sw, L)
+        got = binding.saved_views(binding.make_desc(qkv[0], L, m), saved)
+        # (only what the sums are made of: the filter as the library computed it)
+        F = got["F"][0].double()
+
+        def filtered(x):
+            y = F[0] * x
+            for lvl in range(1, L + 1):
+                pad = -n % (1 << lvl)
+                z = torch.cat([x, x.new_zeros(pad, d)]).view(-1, 1 << lvl, d).mean(1, keepdim=True)
+                y = y + (F[lvl] - F[lvl - 1]) * z.expand(-1, 1 << lvl, -1).reshape(-1, d)[:n]
+            return y
+
+        Q, K = filtered(q.double()), filtered(k.double())
+        c = 1 / m ** 0.5
+        pk, pq = torch.relu(K @ omega.double()) * c, torch.relu(Q @ omega.double()) * c
+        S, z = pk.t() @ v.double(), pk.sum(0)
+        D = pq @ z + 1e-6
+        O = pq @ S / D[:, None]
+        ref = dict(S=S, z=z, D=D, O=O)
+        res = dict(S=got["S"][0], z=got["z"][0], D=got["D"][0], O=out[0, 0])
+        for name, r in ref.items():
+            errs.setdefault(name, []).append(float((res[name].double() - r).norm() / r.norm()))
+    med = {name: sorted(e)[3] for name, e in errs.items()}
+    print((n, d, m), {name: f"{e:.2e}" for name, e in med.items()}, flush=True)
+    assert all(med[name] < b for name, b in bound.items()), med
