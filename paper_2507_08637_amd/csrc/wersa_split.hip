@@ -189,8 +189,16 @@ __device__ __forceinline__ void store_operand(bf16_t *tile, int lane, bf16x8 v) 
 // 1 where x > 0, else 0 (also for NaN), exact for every float: one multiplication with output clamp.  With
 // additions and plain moves it runs at twice the rate of the other vector instructions (measured: 2 cycles against 4).
 __device__ __forceinline__ float positive(float x) { return __builtin_amdgcn_fmed3f(x * __builtin_inff(), 0.f, 1.f); }
-// As integers, negative floats are negative: one instruction (fmaxf is two: it quiets a NaN first).
-__device__ __forceinline__ float relu(float x) { return __int_as_float(max(__float_as_int(x), 0)); }
+// max(x, 0), 0 for NaN of either sign as fmaxf gives.  One instruction: fmaxf is two (it quiets a NaN first), and so is
+// the median where the compiler sees that its bound is infinity.
+__device__ __forceinline__ float relu(float x) {
+  float bound = __builtin_inff();
+  asm("" : "+s"(bound));
+  return __builtin_amdgcn_fmed3f(x, 0.f, bound);
+}
+// x where mask is 1, 0 where it is 0, also for NaN and infinities (0 times anything is 0 in this instruction).
+__device__ float mul_legacy(float, float) __asm("llvm.amdgcn.fmul.legacy");
+__device__ __forceinline__ float masked(float x, float mask) { return mul_legacy(x, mask); }
 
 // Product of the 16 values of an accumulator tile that a lane holds with 16 weights.  D and z are sums of these, D of eight
 // at a time: one chain over all features or tokens is four times as far from the exact sum at 4096 features.
@@ -372,16 +380,17 @@ __device__ __forceinline__ void apply_terms(f32x16 &acc, f32x16 &lo, const bf16x
   for (int i = 0; i < 3; ++i) y[i] = lds_operand(sb + ((a * CT + ct) * 3 + i) * kTile, lane);
   add_terms<3>(acc, lo, p, y);
 }
-// sum over the levels above four of coef_l * (block sum): levels 5 and 6 from the 16-row sums of a tile
+// sum over the levels above four (up to L) of coef_l * (block sum): levels 5 and 6 from the 16-row sums of a tile
 template <int CW>
-__device__ __forceinline__ float upper_levels(const float (*segsum)[CW], const float *cf, int seg, int c) {
+__device__ __forceinline__ float upper_levels(const float (*segsum)[CW], const float *cf, int seg, int c, int L) {
+  if (L < 5) return 0.f;
   const int b = seg & ~3;
   const float s5 = segsum[seg & ~1][c] + segsum[seg | 1][c];
   const float s6 = (segsum[b][c] + segsum[b + 1][c]) + (segsum[b + 2][c] + segsum[b + 3][c]);
-  return fmaf(cf[5], s5, cf[6] * s6);
+  return fmaf(cf[5], s5, L < 6 ? 0.f : cf[6] * s6);
 }
 template <typename T, int DH, int PT>
-__global__ __launch_bounds__(256) void prep_fwd_kernel(const T *q, const T *k, const T *vv, View v, Dims s, int vec,
+__global__ __launch_bounds__(256) void prep_fwd_kernel(const T *q, const T *k, const T *vv, View v, Dims s, int vec, int L,
                                                       const float *coef, const float *addQ, const float *addK,
                                                       bf16_t *XQ, bf16_t *XK, bf16_t *VC) {
   using G = Geo<DH>;
@@ -419,11 +428,11 @@ __global__ __launch_bounds__(256) void prep_fwd_kernel(const T *q, const T *k, c
     for (int i = 0; i < 16; ++i) vals[i] = tile[(seg * 16 + i) * LS + c];
     segsum[seg][c] = segment_sum<16>(vals);
     __syncthreads();
-    float upper = upper_levels<CW>(segsum, cf, seg, c);
+    float upper = upper_levels<CW>(segsum, cf, seg, c, L);
     const float *add = side ? addK : addQ;
     const int gt = t0 / 64 + seg / 4, ntl = (s.n + 63) / 64;
     if (add && gt < ntl && c0 + c < s.d) upper += add[((int64_t)slice * ntl + gt) * s.d + c0 + c];
-    filter_segment<16>(vals, cf, upper);
+    filter_segment<16>(vals, cf, upper, L);
     // (rows past n must stay zero: they are padding, not output)
 #pragma unroll
     for (int i = 0; i < 16; ++i) tile[(seg * 16 + i) * LS + c] = t0 + seg * 16 + i < s.n ? vals[i] : 0.f;
@@ -1063,8 +1072,8 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void grad_kernel(co
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const float mask = positive(R[i]);
-          Gr[i] *= mask;
-          if (DV) R[i] *= mask;
+          Gr[i] = masked(Gr[i], mask);
+          if (DV) R[i] = masked(R[i], mask);
         }
         with_split<mfma_residuals(DH, PT)>(Gr, ni, [&](int a, const bf16x8 *p) {
 #pragma unroll
@@ -1230,10 +1239,10 @@ __global__ __launch_bounds__(256) void filter_kernel(FilterJob j0, FilterJob j1,
     if (t0 + i >= s.n) v[i] = 0.f;
   segsum[seg][c] = segment_sum<16>(v);
   __syncthreads();
-  float upper = upper_levels<CW>(segsum, cf, seg, c);
+  float upper = upper_levels<CW>(segsum, cf, seg, c, L);
   const int ntl = (s.n + 63) / 64, gt = (rg * TR) / 64 + seg / 4;
   if (j.add && cok && gt < ntl) upper += j.add[((int64_t)slice * ntl + gt) * s.d + col];
-  filter_segment<16>(v, cf, upper);
+  filter_segment<16>(v, cf, upper, L);
   const float extra = (j.addvec && cok) ? addscale * j.addvec[(int64_t)slice * s.d + col] : 0.f;
   TO *yp = (TO *)j.y + vy.slice_base(slice) + (cok ? col : 0);
 #pragma unroll
@@ -1538,7 +1547,7 @@ wersa_status forward_t(const wersa_desc &c, const T *q, const T *k, const T *v, 
     WERSA_STAGE("split_deep", st, deep_addend_kernel<<<dim3(slices, 2, c.d / kCoarseCols), 1024, 0, st>>>(
         qpart, kpart, coef, p.ntl, c.d, c.L, w.pyr, addQ, addK));
   WERSA_STAGE("split_prep_fwd", st, prep_fwd_kernel<T, DH, PT><<<dim3(p.groups, slices, 3), 256, 0, st>>>(
-      q, k, v, tv, p.s, vec, coef, addQ, addK, XQ, XK, w.VC));
+      q, k, v, tv, p.s, vec, c.L, coef, addQ, addK, XQ, XK, w.VC));
   WERSA_STAGE("split_contract", st, contract_kernel<DH, PT><<<dim3(p.splits, p.s.mt / p.FW, slices), 512, 0, st>>>(
       XK, w.VC, nullptr, OAk, p.s, p.FW, p.TW, p.tiles_per_split, w.part, w.zpart));
   WERSA_STAGE("split_reduce", st, reduce_kernel<DH><<<dim3(p.s.mt, slices), 256, 0, st>>>(

@@ -149,3 +149,72 @@ def test_sums_stay_close_to_float64(n, d, m, bound):
     med = {name: sorted(e)[3] for name, e in errs.items()}
     print((n, d, m), {name: f"{e:.2e}" for name, e in med.items()}, flush=True)
     assert all(med[name] < b for name, b in bound.items()), med
+
+
+NONFINITE = [("bf16", 16, 96, 2), ("bf16", 32, 64, 3), ("f32", 16, 64, 0), ("f32", 32, 96, 2), ("f32", 64, 64, 5), ("f32", 128, 64, 3)]
+
+
+@pytest.mark.parametrize("bad", [float("nan"), -float("nan"), float("inf")], ids=["nan", "minus_nan", "inf"])
+@pytest.mark.parametrize("dtype,d,m,L", NONFINITE)
+def test_where_a_value_that_is_not_finite_goes(dtype, d, m, L, bad):
+    """The ReLU of a NaN of either sign is 0, in the features and in their derivative, and nothing crosses to rows outside the
+    2^L rows of the filter's block, to other columns of V and dO or to other slices."""
+    import struct
+    import torch
+    from paper_2507_08637_amd import binding
+    B, H, n, t, j = 1, 2, 200, 77, 5
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    if bad != bad:   # the sign has to reach the tensor
+        bits = torch.tensor([-0x400000 if struct.pack(">d", bad)[0] & 0x80 else 0x7fc00000], dtype=torch.int32)
+        value = bits.view(torch.float32).to(tdt).cuda()[0]
+    else:
+        value = bad
+    g = torch.Generator(device="cuda").manual_seed(d + m)
+
+    def normal(*s):
+        return torch.randn(s, generator=g, device="cuda")
+
+    clean = {k: normal(B, H, n, d).to(tdt) for k in ("q", "k", "v", "do")}
+    par = (normal(d, m).to(tdt), torch.ones(1, device="cuda"), normal(H, L + 1, d) / d ** 0.5, normal(H, L + 1),
+           1 + 0.1 * normal(L + 1))
+
+    def run(where):
+        x = {k: v.clone() for k, v in clean.items()}
+        if where:
+            x[where][0, 0, t, j] = value
+        out, saved = binding.wersa_forward(x["q"], x["k"], x["v"], *par, L, flags=1)
+        g = binding.wersa_backward(x["q"], x["k"], x["v"], *par, out, x["do"], saved, L, flags=1)
+        sv = binding.saved_views(binding.make_desc(x["q"], L, m, flags=1), saved)
+        return dict(g, out=out, **{k: v.clone() for k, v in sv.items()})
+
+    ref = run(None)
+    for where in clean:
+        got = run(where)
+        for name in ("out", "dq", "dk", "dv"):   # the other head
+            assert torch.equal(got[name][0, 1], ref[name][0, 1]), (where, name)
+        o, dv = got["out"][0, 0], got["dv"][0, 0]
+        rest = [c for c in range(d) if c != j]
+        if where == "q" and bad != bad:   # the pooled query makes every filter coefficient NaN: no feature is left
+            assert bool((o == 0).all()) and bool((dv == 0).all()) and bool((got["S"][0] == 0).all())
+        elif where == "k" and bad != bad:   # the rows of its block have no features
+            lo = t >> L << L
+            F = ref["F"][0].double()
+            K = clean["k"][0, 0].double()
+            x = F[0] * K
+            for lvl in range(1, L + 1):
+                z = K[:n >> L << L].view(-1, 1 << lvl, d).mean(1, keepdim=True).expand(-1, 1 << lvl, -1).reshape(-1, d)
+                x[:z.shape[0]] += (F[lvl] - F[lvl - 1]) * z
+                x[z.shape[0]:] = 0   # (an incomplete last block: left out of the comparison below)
+            whole = (n >> L << L) == n
+            phi = torch.relu(x @ par[0].double()) / m ** 0.5
+            phi[lo:lo + (1 << L)] = 0
+            if whole:
+                z = got["z"][0].double()
+                assert float((z - phi.sum(0)).norm() / z.norm()) < 1e-5
+            assert bool(torch.isfinite(o.float()).all())
+        elif where == "v":
+            assert not bool(torch.isfinite(o[:, j].float()).any())
+            assert torch.equal(o[:, rest], ref["out"][0, 0][:, rest])
+        elif where == "do":
+            assert not bool(torch.isfinite(dv[:, j].float()).any())
+            assert torch.equal(dv[:, rest], ref["dv"][0, 0][:, rest])
