@@ -117,7 +117,8 @@ typedef struct {
 size_t wersa_workspace_bytes(const wersa_desc *desc, int for_backward);
 
 /* Bytes of the buffer that carries S, z, qbar, the gate activations, F and the normaliser D
- * from forward to backward. Returns 0 if the descriptor is invalid or unsupported. */
+ * from forward to backward (and, of small float32-arithmetic problems and of bf16 ones with d = 128, the filtered Q and
+ * K). Returns 0 if the descriptor is invalid or unsupported. */
 size_t wersa_saved_bytes(const wersa_desc *desc);
 
 /* Forward pass (Section 3.1 steps 3-8). Writes out (B,H,n,d) and saved. */

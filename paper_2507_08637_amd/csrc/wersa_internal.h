@@ -65,7 +65,7 @@ inline bool use_split(const wersa_desc &c) {
   return split_workspace_bytes(c, 0) <= kStaticScratchBytes || generic_workspace_bytes(c, 0) > kStaticScratchBytes;
 }
 struct SplitSizes {
-  int64_t X, OA, OB, SA;   // floats: packed Q_F or K_F, Omega both ways, S with its features as vectors
+  int64_t X, OA, OB;   // floats: packed Q_F or K_F (0: formed again by the backward), Omega both ways
 };
 SplitSizes split_sizes(const wersa_desc &c);
 
@@ -79,7 +79,7 @@ struct SavedLayout {
   int64_t tileQ, tileK, addQ, addK;
   // Split path only: the operands of the contractions that the backward uses again (with scalars, coef and, for
   // L > 6, the tile sums and addends above).
-  int64_t XQ, XK, OA, OB, SA;
+  int64_t XQ, XK, OA, OB;
 };
 inline SavedLayout saved_layout(const wersa_desc &c) {
   SavedLayout o;
@@ -114,7 +114,7 @@ inline SavedLayout saved_layout(const wersa_desc &c) {
       o.addK = off;  off += up(tiles);
     }
   }
-  o.XQ = o.XK = o.OA = o.OB = o.SA = -1;
+  o.XQ = o.XK = o.OA = o.OB = -1;
   if (use_split(c)) {
     const SplitSizes z = split_sizes(c);
     o.scalars = off; off += 64;
@@ -123,7 +123,6 @@ inline SavedLayout saved_layout(const wersa_desc &c) {
     o.XK = off;      off += up(z.X);
     o.OA = off;      off += up(z.OA);
     o.OB = off;      off += up(z.OB);
-    o.SA = off;      off += up(z.SA);
     if (c.L > kTileL) {
       const int64_t tiles = sl * ((c.n + 63) / 64) * c.d;
       o.tileQ = off; off += up(tiles);

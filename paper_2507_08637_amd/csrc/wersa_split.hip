@@ -28,6 +28,10 @@
 #include <initializer_list>
 #include <type_traits>
 
+// v_mul_legacy_f32 as the compiler's intrinsic (not as inline assembly: the wait states after a matrix instruction are
+// the compiler's to insert).
+extern "C" __device__ float amdgcn_mul_legacy(float, float) __asm("llvm.amdgcn.fmul.legacy");
+
 namespace wersa {
 namespace {
 
@@ -197,8 +201,7 @@ __device__ __forceinline__ float relu(float x) {
   return __builtin_amdgcn_fmed3f(x, 0.f, bound);
 }
 // x where mask is 1, 0 where it is 0, also for NaN and infinities (0 times anything is 0 in this instruction).
-__device__ float mul_legacy(float, float) __asm("llvm.amdgcn.fmul.legacy");
-__device__ __forceinline__ float masked(float x, float mask) { return mul_legacy(x, mask); }
+__device__ __forceinline__ float masked(float x, float mask) { return amdgcn_mul_legacy(x, mask); }
 
 // Product of the 16 values of an accumulator tile that a lane holds with 16 weights.  D and z are sums of these, D of eight
 // at a time: one chain over all features or tokens is four times as far from the exact sum at 4096 features.
@@ -345,10 +348,7 @@ __global__ __launch_bounds__(256) void pool_kernel(const T *q, const T *k, View 
 }
 
 // ------------------------------------------------------------------------------------
-// Forward operands: gated Haar filter of Q and K (steps 3, 5, 6), split and packed with k = columns;
-// V packed with k = tokens.  4096 elements per workgroup: TR rows x CW columns, one thread per
-// (column, 16 rows) in the filter, the 32- and 64-row sums through LDS.
-// Grid (row groups * column pieces, slices, 3: Q, K, V).
+// Operands of n x d, 4096 elements per workgroup.
 // ------------------------------------------------------------------------------------
 template <int DH>
 struct Geo {
@@ -359,7 +359,7 @@ struct Geo {
   static constexpr int NSB = DH == 16 ? 4 : 6 * CT;
 };
 // Phi S for one half of a feature tile and one column tile; sb: the operand tiles of S from lds_operand.  acc takes the
-// product of the leading terms, lo all others (together Phi S): acc is rounded once per 16 features instead of six
+// product of the leading terms, lo all others (together Phi S; lo may be acc): acc is rounded once per 16 features instead of six
 // times, and the slight bias of the matrix cores' rounding towards zero stays in proportion.  In one accumulator O came
 // out 9e-8 too small at 4096 features, the same in all columns of a row, which <dO, O> does not average out.
 // One float32 sequence of 2048 tokens, d 32, 4096 features, error against float64: O 6.9e-7 -> 3.4e-7, dQ 8.9e-7 -> 2.7e-7,
@@ -389,23 +389,22 @@ __device__ __forceinline__ float upper_levels(const float (*segsum)[CW], const f
   const float s6 = (segsum[b][c] + segsum[b + 1][c]) + (segsum[b + 2][c] + segsum[b + 3][c]);
   return fmaf(cf[5], s5, L < 6 ? 0.f : cf[6] * s6);
 }
-template <typename T, int DH, int PT>
-__global__ __launch_bounds__(256) void prep_fwd_kernel(const T *q, const T *k, const T *vv, View v, Dims s, int vec, int L,
-                                                      const float *coef, const float *addQ, const float *addK,
-                                                      bf16_t *XQ, bf16_t *XK, bf16_t *VC) {
+// Scratch of a packing kernel: one tile of rows, the 16-row sums or two values per row, and a few scalars.
+template <int DH>
+struct PrepLds {
   using G = Geo<DH>;
-  constexpr int CW = G::CW, TR = G::TR, LS = G::LS;
-  __shared__ __attribute__((aligned(16))) float tile[TR * LS];
-  __shared__ float segsum[G::SEGS][CW];
-  __shared__ float cf[8];
-  const int tid = threadIdx.x, slice = blockIdx.y, side = blockIdx.z;
-  const int rg = blockIdx.x / G::PIECES, piece = blockIdx.x % G::PIECES;
-  const int t0 = rg * TR, c0 = piece * CW;
-  if (tid < 8) cf[tid] = coef[slice * kCoefStride + tid];
-  const T *xs = (side == 0 ? q : side == 1 ? k : vv) + v.slice_base(slice);
+  static constexpr int RB = 4096 / DH, FILTER = G::TR * G::LS, ROWS = RB * (DH + 4);   // rows of a tile of whole rows
+  float tile[FILTER > ROWS ? FILTER : ROWS];
+  float part[256];
+  float small[8];
+};
+// TR x CW elements of a strided tensor from row t0, column c0 into LDS; zeros past n and d.
+template <typename T, int DH>
+__device__ __forceinline__ void load_tile(const T *xs, const View &v, const Dims &s, int vec, int t0, int c0, float *tile) {
+  using G = Geo<DH>;
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
-    const int e = tid + 256 * u, r = e / (CW / 8), cc = e % (CW / 8) * 8;
+    const int e = threadIdx.x + 256 * u, r = e / (G::CW / 8), cc = e % (G::CW / 8) * 8;
     float x[8];
     if (t0 + r < s.n && c0 + cc < s.d) load8(xs + (int64_t)(t0 + r) * v.sn + c0 + cc, vec, x);
     else
@@ -417,81 +416,130 @@ __global__ __launch_bounds__(256) void prep_fwd_kernel(const T *q, const T *k, c
       a[i] = x[i];
       b[i] = x[4 + i];
     }
-    *reinterpret_cast<f32x4 *>(&tile[r * LS + cc]) = a;
-    *reinterpret_cast<f32x4 *>(&tile[r * LS + cc + 4]) = b;
+    *reinterpret_cast<f32x4 *>(&tile[r * G::LS + cc]) = a;
+    *reinterpret_cast<f32x4 *>(&tile[r * G::LS + cc + 4]) = b;
   }
+}
+// Gated Haar filter of one signal (steps 3, 5, 6), split and packed with k = columns.  One thread per (column, 16
+// rows) in the filter, the 32- and 64-row sums through LDS.  X: X_F (may be nullptr); XS: X_F / D_t (may be nullptr).
+template <typename T, int DH>
+__device__ __forceinline__ void filter_pack(PrepLds<DH> &lds, const T *x, const View &v, const Dims &s, int vec, int L,
+                                            const float *coef, const float *add, const float *D, bf16_t *X, bf16_t *XS) {
+  using G = Geo<DH>;
+  constexpr int CW = G::CW, TR = G::TR, LS = G::LS;
+  float(*segsum)[CW] = reinterpret_cast<float(*)[CW]>(lds.part);
+  const int tid = threadIdx.x, slice = blockIdx.y;
+  const int rg = blockIdx.x / G::PIECES, piece = blockIdx.x % G::PIECES;
+  const int t0 = rg * TR, c0 = piece * CW;
+  if (tid < 8) lds.small[tid] = coef[slice * kCoefStride + tid];
+  load_tile<T, DH>(x + v.slice_base(slice), v, s, vec, t0, c0, lds.tile);
   __syncthreads();
-  if (side < 2) {
-    const int c = tid % CW, seg = tid / CW;
-    float vals[16];
+  const int c = tid % CW, seg = tid / CW;
+  float vals[16];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) vals[i] = tile[(seg * 16 + i) * LS + c];
-    segsum[seg][c] = segment_sum<16>(vals);
-    __syncthreads();
-    float upper = upper_levels<CW>(segsum, cf, seg, c, L);
-    const float *add = side ? addK : addQ;
-    const int gt = t0 / 64 + seg / 4, ntl = (s.n + 63) / 64;
-    if (add && gt < ntl && c0 + c < s.d) upper += add[((int64_t)slice * ntl + gt) * s.d + c0 + c];
-    filter_segment<16>(vals, cf, upper, L);
-    // (rows past n must stay zero: they are padding, not output)
+  for (int i = 0; i < 16; ++i) vals[i] = lds.tile[(seg * 16 + i) * LS + c];
+  segsum[seg][c] = segment_sum<16>(vals);
+  __syncthreads();
+  float upper = upper_levels<CW>(segsum, lds.small, seg, c, L);
+  const int gt = t0 / 64 + seg / 4, ntl = (s.n + 63) / 64;
+  if (add && gt < ntl && c0 + c < s.d) upper += add[((int64_t)slice * ntl + gt) * s.d + c0 + c];
+  filter_segment<16>(vals, lds.small, upper, L);
+  // (rows past n must stay zero: they are padding, not output)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) tile[(seg * 16 + i) * LS + c] = t0 + seg * 16 + i < s.n ? vals[i] : 0.f;
-    __syncthreads();
-    bf16_t *dst = side ? XK : XQ;
-    constexpr int KSL = CW / 16;
+  for (int i = 0; i < 16; ++i) lds.tile[(seg * 16 + i) * LS + c] = t0 + seg * 16 + i < s.n ? vals[i] : 0.f;
+  __syncthreads();
+  constexpr int KSL = CW / 16;
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int p = tid + 256 * u, lane = p & 63, ksl = (p >> 6) % KSL, tb = t0 / 32 + (p >> 6) / KSL;
-      if (tb >= s.nt) continue;
-      float x[8];
-      load8(&tile[(((p >> 6) / KSL) * 32 + (lane & 31)) * LS + 16 * ksl + 8 * (lane >> 5)], true, x);
-      bf16x8 t[3];
-      split8(x, t);
-      bf16_t *o = dst + (((int64_t)slice * s.nt + tb) * G::KS + piece * KSL + ksl) * 3 * kTile;
+  for (int u = 0; u < 2; ++u) {
+    const int p = tid + 256 * u, lane = p & 63, ksl = (p >> 6) % KSL, tb = t0 / 32 + (p >> 6) / KSL;
+    if (tb >= s.nt) continue;
+    float f[8];
+    load8(&lds.tile[(((p >> 6) / KSL) * 32 + (lane & 31)) * LS + 16 * ksl + 8 * (lane >> 5)], true, f);
+    const int64_t off = (((int64_t)slice * s.nt + tb) * G::KS + piece * KSL + ksl) * 3 * kTile;
+    bf16x8 t[3];
+    if (X) {
+      split8(f, t);
 #pragma unroll
-      for (int i = 0; i < 3; ++i) store_operand(o + i * kTile, lane, t[i]);
+      for (int i = 0; i < 3; ++i) store_operand(X + off + i * kTile, lane, t[i]);
     }
-  } else {
-    constexpr int CTL = CW < 32 ? 1 : CW / 32, NP = TR / 32 * 2 * CTL * 64;
+    if (XS) {
+      const int row = 32 * tb + (lane & 31);
+      const float inv = row < s.n ? 1.0f / D[(int64_t)slice * s.n + row] : 1.f;
 #pragma unroll
-    for (int u = 0; u < NP / 256; ++u) {
-      const int p = tid + 256 * u, lane = p & 63, ctl = (p >> 6) % CTL, a = (p >> 6) / CTL % 2, tbl = (p >> 6) / (2 * CTL);
-      const int tb = t0 / 32 + tbl, c = 32 * ctl + (lane & 31), h = lane >> 5;
-      if (tb >= s.nt) continue;
-      float x[8];
+      for (int q = 0; q < 8; ++q) f[q] *= inv;
+      split8(f, t);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int r = tbl * 32 + 16 * a + 8 * (i >> 2) + 4 * h + (i & 3);
-        // (head dimension 16: column 16 of the 32 is the column of ones that gives z)
-        x[i] = c < CW ? tile[r * LS + c] : (c == 16 ? 1.f : 0.f);
-      }
-      bf16x8 t[3];
-      split8(x, t);
-      bf16_t *o = VC + ((((int64_t)slice * s.nt + tb) * 2 + a) * G::CT + piece * CTL + ctl) * PT * kTile;
-#pragma unroll
-      for (int i = 0; i < PT; ++i) store_operand(o + i * kTile, lane, t[i]);
+      for (int i = 0; i < 3; ++i) store_operand(XS + off + i * kTile, lane, t[i]);
     }
   }
 }
 
+// Forward operands: Q_F and K_F packed with k = columns, V packed with k = tokens.
+// Grid (row groups * column pieces, slices, 3: Q, K, V).
+template <typename T, int DH, int PT>
+__global__ __launch_bounds__(256) void prep_fwd_kernel(const T *q, const T *k, const T *vv, View v, Dims s, int vec, int L,
+                                                      const float *coef, const float *addQ, const float *addK,
+                                                      bf16_t *XQ, bf16_t *XK, bf16_t *VC) {
+  using G = Geo<DH>;
+  constexpr int CW = G::CW, TR = G::TR, LS = G::LS;
+  __shared__ __attribute__((aligned(16))) PrepLds<DH> lds;
+  const int side = blockIdx.z;
+  if (side < 2) {
+    filter_pack<T, DH>(lds, side ? k : q, v, s, vec, L, coef, side ? addK : addQ, nullptr, side ? XK : XQ, nullptr);
+    return;
+  }
+  const int tid = threadIdx.x, slice = blockIdx.y;
+  const int rg = blockIdx.x / G::PIECES, piece = blockIdx.x % G::PIECES;
+  const int t0 = rg * TR, c0 = piece * CW;
+  load_tile<T, DH>(vv + v.slice_base(slice), v, s, vec, t0, c0, lds.tile);
+  __syncthreads();
+  constexpr int CTL = CW < 32 ? 1 : CW / 32, NP = TR / 32 * 2 * CTL * 64;
+#pragma unroll
+  for (int u = 0; u < NP / 256; ++u) {
+    const int p = tid + 256 * u, lane = p & 63, ctl = (p >> 6) % CTL, a = (p >> 6) / CTL % 2, tbl = (p >> 6) / (2 * CTL);
+    const int tb = t0 / 32 + tbl, c = 32 * ctl + (lane & 31), h = lane >> 5;
+    if (tb >= s.nt) continue;
+    float x[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int r = tbl * 32 + 16 * a + 8 * (i >> 2) + 4 * h + (i & 3);
+      // (head dimension 16: column 16 of the 32 is the column of ones that gives z)
+      x[i] = c < CW ? lds.tile[r * LS + c] : (c == 16 ? 1.f : 0.f);
+    }
+    bf16x8 t[3];
+    split8(x, t);
+    bf16_t *o = VC + ((((int64_t)slice * s.nt + tb) * 2 + a) * G::CT + piece * CTL + ctl) * PT * kTile;
+#pragma unroll
+    for (int i = 0; i < PT; ++i) store_operand(o + i * kTile, lane, t[i]);
+  }
+}
+
 // ------------------------------------------------------------------------------------
-// Backward operands.  Per row: <dO_t, O_t>, then dN_t and dD_t; dN packed both ways (k = columns for
-// dPhi_Q, k = tokens for dS), V packed with k = columns.
+// Backward operands.  blockIdx.z = 0, per row: <dO_t, O_t>, then dN_t and dD_t; dN packed with k = tokens for dS.
 //   PT == 1 (bf16 storage): dN stays dO, one exact term; 1 / D_t goes into the rows of Q_F of the dS
 //   product (XS; ReLU is positively homogeneous) and into the scale of the rows of dQ_F (rowscale), so
 //   ddw is then -<dO_t, O_t>.   PT == 3: dN = dO / D in float32, ddw = dD_t = -<dO_t, O_t> / D_t.
 //   With the LayerNorm output stage: dN = rstd (dO - mean dO - O mean(dO O)), ddw = 0.
 // part[slice][workgroup]: sum of the per-row term of d sigma (dD_t, or -<dO_t, O_t> rstd_t^2).
-// 4096 elements (whole rows) per workgroup.  Grid (row groups, slices).
+// blockIdx.z = 1: XS or, with three terms, Q_F as the forward packs it; 2: K_F (see keeps_operands).  dN and V with k = columns are not
+// packed: the gradient kernel reads each of their rows once, in the order in which they are stored.
+// Grid (row groups, slices, 1 to 3); the row groups of both forms are the same in number.
 // ------------------------------------------------------------------------------------
 template <typename T, int DH, int PT>
-__global__ __launch_bounds__(256) void prep_bwd_kernel(const T *dout, const T *out, const T *vv, View v, Dims s, int vec,
-                                                      int ln, const float *D, const bf16_t *XQ, bf16_t *NR, bf16_t *NC,
-                                                      bf16_t *VR, bf16_t *XS, float *ddw, float *rowscale, float *part) {
+__global__ __launch_bounds__(256) void prep_bwd_kernel(const T *dout, const T *out, const T *q, const T *k, View v, Dims s, int vec,
+                                                      int ln, int L, const float *coef, const float *addQ, const float *addK,
+                                                      const float *D, bf16_t *NC, bf16_t *XQ, bf16_t *XS, bf16_t *XK, float *ddw,
+                                                      float *rowscale, float *part) {
   using G = Geo<DH>;
-  constexpr int RB = 4096 / DH, PARTS = DH / 16, LS = DH + 4;
-  __shared__ __attribute__((aligned(16))) float tile[RB * LS];
-  __shared__ float wrow[RB], irow[RB], red[4];
+  __shared__ __attribute__((aligned(16))) PrepLds<DH> lds;
+  if (blockIdx.z) {
+    if (blockIdx.z == 1) filter_pack<T, DH>(lds, q, v, s, vec, L, coef, addQ, D, XQ, XS);
+    else filter_pack<T, DH>(lds, k, v, s, vec, L, coef, addK, nullptr, XK, nullptr);
+    return;
+  }
+  constexpr int RB = PrepLds<DH>::RB, PARTS = DH / 16, LS = DH + 4;
+  static_assert(RB <= 256, "one weight per row in LDS");
+  float *tile = lds.tile, *wrow = lds.part, *red = lds.small;
   const int tid = threadIdx.x, slice = blockIdx.y, t0 = blockIdx.x * RB;
   const int r = tid / PARTS, pc = tid % PARTS * 16, t = t0 + r;
   const bool ok = t < s.n && pc < s.d;
@@ -541,10 +589,9 @@ __global__ __launch_bounds__(256) void prep_bwd_kernel(const T *dout, const T *o
   }
   if (pc == 0) {
     wrow[r] = w;
-    irow[r] = inv;
     if (t < 32 * s.nt) {
       ddw[(int64_t)slice * 32 * s.nt + t] = w;
-      rowscale[(int64_t)slice * 32 * s.nt + t] = inv;
+      if (PT == 1) rowscale[(int64_t)slice * 32 * s.nt + t] = inv;
     }
   } else {
     sig = 0.f;
@@ -553,21 +600,6 @@ __global__ __launch_bounds__(256) void prep_bwd_kernel(const T *dout, const T *o
   if ((tid & 63) == 0) red[tid >> 6] = sig;
   __syncthreads();
   if (tid == 0) part[(int64_t)slice * gridDim.x + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
-  auto pack_rows = [&](bf16_t *dst) {   // k = columns
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int p = tid + 256 * u, lane = p & 63, ks = (p >> 6) % G::KS, tbl = (p >> 6) / G::KS, tb = t0 / 32 + tbl;
-      if (tb >= s.nt) continue;
-      float x[8];
-      load8(&tile[(tbl * 32 + (lane & 31)) * LS + 16 * ks + 8 * (lane >> 5)], true, x);
-      bf16x8 tt[3];
-      split8(x, tt);
-      bf16_t *dd = dst + (((int64_t)slice * s.nt + tb) * G::KS + ks) * PT * kTile;
-#pragma unroll
-      for (int i = 0; i < PT; ++i) store_operand(dd + i * kTile, lane, tt[i]);
-    }
-  };
-  pack_rows(NR);
   constexpr int NP = RB / 32 * 2 * G::CT * 64;
 #pragma unroll
   for (int u = 0; u < NP / 256; ++u) {   // k = tokens
@@ -592,35 +624,6 @@ __global__ __launch_bounds__(256) void prep_bwd_kernel(const T *dout, const T *o
 #pragma unroll
     for (int i = 0; i < PT; ++i) store_operand(dd + i * kTile, lane, tt[i]);
   }
-  if (PT == 1) {   // Q_F / D
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int p = tid + 256 * u, lane = p & 63, ks = (p >> 6) % G::KS, tbl = (p >> 6) / G::KS, tb = t0 / 32 + tbl;
-      if (tb >= s.nt) continue;
-      const int64_t off = (((int64_t)slice * s.nt + tb) * G::KS + ks) * 3 * kTile;
-      const bf16x8 x0 = lds_operand(XQ + off, lane), x1 = lds_operand(XQ + off + kTile, lane),
-                   x2 = lds_operand(XQ + off + 2 * kTile, lane);
-      const float iv = irow[tbl * 32 + (lane & 31)];
-      float x[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) x[q] = (((float)x2[q] + (float)x1[q]) + (float)x0[q]) * iv;
-      bf16x8 tt[3];
-      split8(x, tt);
-#pragma unroll
-      for (int i = 0; i < 3; ++i) store_operand(XS + off + i * kTile, lane, tt[i]);
-    }
-  }
-  __syncthreads();
-  {
-    float x[16];
-    const int64_t vb = v.slice_base(slice) + (int64_t)(t < s.n ? t : 0) * v.sn + (pc < s.d ? pc : 0);
-    load8(vv + vb, vec, x);
-    load8(vv + vb + 8, vec, x + 8);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) tile[r * LS + pc + i] = ok ? x[i] : 0.f;
-  }
-  __syncthreads();
-  pack_rows(VR);
 }
 
 // ------------------------------------------------------------------------------------
@@ -732,10 +735,11 @@ __global__ __launch_bounds__(512, 2) void contract_kernel(const bf16_t *X, const
 }
 
 // ------------------------------------------------------------------------------------
-// S (or dS) and z (or dz) of one feature tile: fixed-order sum of the shares, times c; float32 results
-// [m][d] and [m], and the operand tiles of the kernels that follow: features as vectors with the
-// extension tile that carries the rank-one term dD z^T (three-term products in six k-slots), and columns
-// as vectors with k = features.  Grid (feature tiles, slices).
+// S (or dS) and z (or dz) of one feature tile: fixed-order sum of the shares, times c; in the forward the float32
+// results [m][d] and [m], and the operand tiles of the kernels that follow: columns as vectors with k = features (SB);
+// in the backward also features as vectors (SA) with the extension tile that carries the rank-one term dD z^T
+// (three-term products in six k-slots), for dS and, from the forward's S and z (blockIdx.z = 1), SAin.
+// Grid (feature tiles, slices, forward 1, backward 2).
 // ------------------------------------------------------------------------------------
 // Sum of the values at p, p + step, ...: eight at a time (in flight together) as a tree, eight of these in a chain, and a
 // chain of those.  In one chain, the hundreds of shares of a long sequence would lose more than the products do.
@@ -759,45 +763,55 @@ __device__ __forceinline__ V sum_shares(const float *p, int64_t step, int shares
 template <int DH>
 __global__ __launch_bounds__(256) void reduce_kernel(const float *part, const float *zpart, int shares, int zcols,
                                                     const float *scalars, Dims s, float *S, float *z, float *zpad,
-                                                    bf16_t *SA, bf16_t *SB) {
+                                                    bf16_t *SA, bf16_t *SB, bf16_t *SAin) {
   using G = Geo<DH>;
   constexpr int PW = 32 * G::CT, LS = PW + 1;
   __shared__ float tile[32 * LS];
   __shared__ float zt[32];
   const int tid = threadIdx.x, ft = blockIdx.x, slice = blockIdx.y;
+  const bool given = SAin && blockIdx.z;   // S and z are there already
   const float c = scalars[0];
-  const int64_t step = (int64_t)s.mt * 32 * PW;
-  const float *p0 = part + ((int64_t)slice * shares * s.mt + ft) * 32 * PW;
+  if (given) {
+    for (int e = tid; e < 32 * DH; e += 256) {
+      const int f = e / DH, cc = e % DH;
+      tile[f * LS + cc] = (32 * ft + f < s.m && cc < s.d) ? S[((int64_t)slice * s.m + 32 * ft + f) * s.d + cc] : 0.f;
+    }
+    if (tid < 32) zt[tid] = 32 * ft + tid < s.m ? z[(int64_t)slice * s.m + 32 * ft + tid] : 0.f;
+    __syncthreads();
+  } else {
+    const int64_t step = (int64_t)s.mt * 32 * PW;
+    const float *p0 = part + ((int64_t)slice * shares * s.mt + ft) * 32 * PW;
 #pragma unroll
-  for (int u = 0; u < 32 * PW / 1024; ++u) {
-    const int e = (tid + 256 * u) * 4;
-    const f32x4 acc = sum_shares<f32x4>(p0 + e, step, shares);
+    for (int u = 0; u < 32 * PW / 1024; ++u) {
+      const int e = (tid + 256 * u) * 4;
+      const f32x4 acc = sum_shares<f32x4>(p0 + e, step, shares);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) tile[(e / PW) * LS + e % PW + i] = acc[i] * c;
+      for (int i = 0; i < 4; ++i) tile[(e / PW) * LS + e % PW + i] = acc[i] * c;
+    }
+    if (DH > 16 && tid < 32)
+      zt[tid] = sum_shares<float>(zpart + ((int64_t)slice * shares * s.mt + ft) * 32 + tid, (int64_t)s.mt * 32, shares) * c;
+    __syncthreads();
+    if (DH == 16 && tid < 32) {
+      float acc = 0.f;
+      for (int j = zcols - 1; j >= 0; --j) acc += tile[tid * LS + 16 + j];
+      zt[tid] = acc;
+    }
+    __syncthreads();
+    if (!SAin) {   // forward
+      for (int e = tid; e < 32 * s.d; e += 256) {
+        const int f = e / s.d, cc = e % s.d;
+        if (32 * ft + f < s.m) S[((int64_t)slice * s.m + 32 * ft + f) * s.d + cc] = tile[f * LS + cc];
+      }
+      if (tid < 32) {
+        if (32 * ft + tid < s.m) z[(int64_t)slice * s.m + 32 * ft + tid] = zt[tid];
+        zpad[((int64_t)slice * s.mt + ft) * 32 + tid] = zt[tid];
+      }
+    }
   }
-  if (DH > 16 && tid < 32) {
-    const float *zp = zpart + ((int64_t)slice * shares * s.mt + ft) * 32 + tid;
-    const float acc = sum_shares<float>(zp, (int64_t)s.mt * 32, shares);
-    zt[tid] = acc * c;
-  }
-  __syncthreads();
-  if (DH == 16 && tid < 32) {
-    float acc = 0.f;
-    for (int j = zcols - 1; j >= 0; --j) acc += tile[tid * LS + 16 + j];
-    zt[tid] = acc;
-  }
-  __syncthreads();
-  for (int e = tid; e < 32 * s.d; e += 256) {
-    const int f = e / s.d, cc = e % s.d;
-    if (32 * ft + f < s.m) S[((int64_t)slice * s.m + 32 * ft + f) * s.d + cc] = tile[f * LS + cc];
-  }
-  if (tid < 32) {
-    if (32 * ft + tid < s.m) z[(int64_t)slice * s.m + 32 * ft + tid] = zt[tid];
-    zpad[((int64_t)slice * s.mt + ft) * 32 + tid] = zt[tid];
-  }
-  bf16_t *sa = SA + ((int64_t)slice * s.mt + ft) * (3 * G::KS + 1) * kTile;
+  bf16_t *sa = (given ? SAin : SA) + ((int64_t)slice * s.mt + ft) * (3 * G::KS + 1) * kTile;
   bf16_t *sb = SB + ((int64_t)slice * s.mt + ft) * G::NSB * kTile;
-  for (int p = tid; p < 64 * (G::KS + 1 + 2 * G::CT); p += 256) {
+  const int first = SA ? 0 : G::KS + 1, last = given ? G::KS + 1 : G::KS + 1 + 2 * G::CT;   // (the forward needs SB only)
+  for (int p = tid + 64 * first; p < 64 * last; p += 256) {
     const int lane = p & 63, which = p >> 6, l32 = lane & 31, h = lane >> 5;
     bf16x8 t[3];
     if (which < G::KS) {
@@ -864,6 +878,9 @@ struct Stager {
   }
 };
 
+// Whether the small terms have an accumulator of their own (see apply_terms): with one-term operands the results are
+// rounded to bf16, and the registers are worth more (head dimension 16, 8 slices of 131072 tokens: 382 us without, 397 with).
+constexpr bool low_terms(int PT) { return PT == 3; }
 // Waves per SIMD that the register budget is set for.
 constexpr int row_occupancy(int DH, int NW) { return NW >= 4 && DH < 128 ? 2 : 1; }
 
@@ -895,13 +912,17 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(c
   sg.p0 = OA;
   sg.p1 = SB + (int64_t)slice * s.mt * NB * kTile;
   sg.p2 = sg.p3 = nullptr;
-  f32x16 acc[RT][G::CT], lo[RT][G::CT];
+  constexpr bool LO = low_terms(PT);
+  f32x16 acc[RT][G::CT], lo[LO ? RT : 1][G::CT];
   float dsum[RT], dpart[RT];   // Phi z: of all groups of eight feature tiles before, of this one
 #pragma unroll
   for (int r = 0; r < RT; ++r) {
     dsum[r] = dpart[r] = 0.f;
 #pragma unroll
-    for (int ct = 0; ct < G::CT; ++ct) acc[r][ct] = lo[r][ct] = zero16();
+    for (int ct = 0; ct < G::CT; ++ct) {
+      acc[r][ct] = zero16();
+      if (LO) lo[LO ? r : 0][ct] = zero16();
+    }
   }
   const NegIdentity ni(lane);
   const float *zs = zpad + (int64_t)slice * s.mt * 32;
@@ -943,7 +964,7 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(c
         if (ZV) dpart[r] += dot16(R, z4);
         with_split<mfma_residuals(DH, PT)>(R, ni, [&](int a, const bf16x8 *p) {
 #pragma unroll
-          for (int ct = 0; ct < G::CT; ++ct) apply_terms<DH>(acc[r][ct], lo[r][ct], p, lb, a, ct, lane);   // rows: tokens, lanes: columns
+          for (int ct = 0; ct < G::CT; ++ct) apply_terms<DH>(acc[r][ct], LO ? lo[LO ? r : 0][ct] : acc[r][ct], p, lb, a, ct, lane);   // rows: tokens, lanes: columns
         });
       }
     }
@@ -974,8 +995,9 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(c
       const int row = 8 * (i >> 2) + 4 * h + (i & 3), t = 32 * tb + row;
       float Dt = 1.f;
       if (ZV) Dt = __shfl(Dl, row, 64);
+      if (LO)
 #pragma unroll
-      for (int ct = 0; ct < G::CT; ++ct) acc[r][ct][i] += lo[r][ct][i];
+        for (int ct = 0; ct < G::CT; ++ct) acc[r][ct][i] += lo[LO ? r : 0][ct][i];
       if (DH == 16) acc[r][0][i] += __shfl_xor(acc[r][0][i], 16, 64);
 #pragma unroll
       for (int ct = 0; ct < G::CT; ++ct) {
@@ -990,15 +1012,27 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(c
   }
 }
 
-// Whether the gradient kernel keeps an accumulator for the small terms too: where the registers hold it.
+// The gradient kernel: where the registers hold it, too.
 constexpr bool grad_low_terms(int DH, int PT, bool DV, int RT) {
-  return DH == 32 || (DH == 16 && (RT == 1 || (PT == 1 && !DV))) || (DH == 64 && !DV);
+  return low_terms(PT) && (DH == 32 || (DH == 16 && RT == 1) || (DH == 64 && !DV));
 }
 // dX_F of one side: R = X Omega, G = Y S^T + w z^T (Y = dN, S, w = dD on the query side; Y = V, dS, w = 1
-// on the key side), dX_F = c rowscale ((G masked where R > 0) Omega^T) in float32 [slice][32 nt][DH].
-// DV: dV = c ReLU(R) dS rides along.  ddw, rowscale nullptr: 1.
+// on the key side), dX_F = c rowscale ((G masked where R > 0) Omega^T) in float32, row t of a slice at
+// grad_row(t) (in the place of X's operand tiles where these are not needed again: a wave reads its tiles before
+// it writes them, and no other wave does either).  DV: dV = c ReLU(R) dS rides along.  ddw, rowscale nullptr: 1.
+// The rows of Y come from the tensors as they are: y, divided by D (one term: not), or with the LayerNorm output
+// stage (o given) rstd (y - mean y - o mean(y o)).
+template <int DH> constexpr int64_t grad_tile() { return 48 * DH; }   // floats of a tile of 32 rows: its operand tiles' size
+template <int DH>
+__device__ __forceinline__ int64_t grad_row(int t) { return (int64_t)(t >> 5) * grad_tile<DH>() + (t & 31) * DH; }
+template <typename T>
+struct GradRows {
+  const T *y, *o;
+  const float *D;
+  int vec;
+};
 template <typename T, int DH, int PT, bool DV, int RT, int NW>
-__global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void grad_kernel(const bf16_t *X, const bf16_t *Y, const float *ddw,
+__global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void grad_kernel(const bf16_t *X, GradRows<T> Y, const float *ddw,
                                                                       const float *rowscale, const bf16_t *OA,
                                                                       const bf16_t *SA, const bf16_t *OB, const bf16_t *SB,
                                                                       const float *scalars, Dims s, float *dXF, T *dv, View v) {
@@ -1012,14 +1046,60 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void grad_kernel(co
   bf16x8 x[RT][G::KS][3], y[RT][G::KS][PT], ext[RT];
 #pragma unroll
   for (int r = 0; r < RT; ++r) {
-    const int64_t tb = (int64_t)slice * s.nt + min(tb0 + r, s.nt - 1);
-    const bf16_t *xp = X + tb * G::KS * 3 * kTile, *yp = Y + tb * G::KS * PT * kTile;
+    const bool mine = tb0 + r < s.nt;   // (a wave past the last tile only helps to stage)
+    const int64_t tb = (int64_t)slice * s.nt + (mine ? tb0 + r : 0);
+    const bf16_t *xp = X + tb * G::KS * 3 * kTile;
+#pragma unroll
+    for (int ks = 0; ks < G::KS; ++ks)
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        x[r][ks][i] = bf16x8{};
+        if (mine) x[r][ks][i] = lds_operand(xp + (ks * 3 + i) * kTile, lane);
+      }
+    const int t = 32 * (tb0 + r) + l32;
+    const bool ok = t < s.n;
+    const int64_t row = v.slice_base(slice) + (int64_t)(ok ? t : 0) * v.sn;
+    float g[G::KS][8];
 #pragma unroll
     for (int ks = 0; ks < G::KS; ++ks) {
+      const int col = 16 * ks + 8 * h;
+      load8(Y.y + row + (col < s.d ? col : 0), Y.vec, g[ks]);
 #pragma unroll
-      for (int i = 0; i < 3; ++i) x[r][ks][i] = lds_operand(xp + (ks * 3 + i) * kTile, lane);
+      for (int q = 0; q < 8; ++q) g[ks][q] = ok && col < s.d ? g[ks][q] : 0.f;
+    }
+    if (!DV && PT == 3 && Y.D) {
+      const float Dt = ok ? Y.D[(int64_t)slice * s.n + t] : 1.f;
+      if (Y.o) {
+        float sum = 0.f, dot = 0.f, o[G::KS][8];
 #pragma unroll
-      for (int i = 0; i < PT; ++i) y[r][ks][i] = lds_operand(yp + (ks * PT + i) * kTile, lane);
+        for (int ks = 0; ks < G::KS; ++ks) {
+          const int col = 16 * ks + 8 * h;
+          load8(Y.o + row + (col < s.d ? col : 0), Y.vec, o[ks]);
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            o[ks][q] = ok && col < s.d ? o[ks][q] : 0.f;
+            sum += g[ks][q];
+            dot = fmaf(g[ks][q], o[ks][q], dot);
+          }
+        }
+        const float m1 = xor32_sum(sum) / (float)s.d, m2 = xor32_sum(dot) / (float)s.d;
+#pragma unroll
+        for (int ks = 0; ks < G::KS; ++ks)
+#pragma unroll
+          for (int q = 0; q < 8; ++q) g[ks][q] = ok && 16 * ks + 8 * h < s.d ? Dt * (g[ks][q] - m1 - o[ks][q] * m2) : 0.f;
+      } else {
+#pragma unroll
+        for (int ks = 0; ks < G::KS; ++ks)
+#pragma unroll
+          for (int q = 0; q < 8; ++q) g[ks][q] = g[ks][q] / Dt;
+      }
+    }
+#pragma unroll
+    for (int ks = 0; ks < G::KS; ++ks) {
+      bf16x8 t3[3];
+      split8(g[ks], t3);
+#pragma unroll
+      for (int i = 0; i < PT; ++i) y[r][ks][i] = t3[i];
     }
     __bf16 w[3];
     split1(h ? 0.f : (ddw ? ddw[tb * 32 + l32] : 1.f), w);
@@ -1112,7 +1192,7 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void grad_kernel(co
 #pragma unroll
       for (int ct = 0; ct < G::CT; ++ct) {
         const int col = 32 * ct + l32;
-        if (col < DH) dXF[((int64_t)slice * s.nt * 32 + t) * DH + col] = sc * acc[r][ct][i];
+        if (col < DH) dXF[((int64_t)slice * s.nt + tb) * grad_tile<DH>() + row * DH + col] = sc * acc[r][ct][i];
         if (DV && t < s.n && col < s.d) st(vb + (int64_t)t * v.sn + col, c * accv[r][ct][i]);
       }
     }
@@ -1137,13 +1217,14 @@ __global__ __launch_bounds__(256) void dots_kernel(const T *q, const T *k, View 
   const int c = tid % CW, seg = tid / CW, col = piece * CW + c, t0 = rg * TR + seg * 16;
   const bool cok = col < s.d;
   const T *xp = (side ? k : q) + v.slice_base(slice) + (cok ? col : 0);
-  const float *gp = (side ? gk : gq) + (int64_t)slice * s.nt * 32 * DH + col;
+  // (16 rows from a multiple of 16: in one tile of 32, at most the last one)
+  const float *gp = (side ? gk : gq) + (int64_t)slice * s.nt * grad_tile<DH>() + grad_row<DH>(min(t0, 32 * s.nt - 16)) + col;
   float a[16], b[16], e[8];
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int t = t0 + i;
     a[i] = ld(xp + (int64_t)min(t, s.n - 1) * v.sn);
-    b[i] = gp[(int64_t)min(t, s.n - 1) * DH];
+    b[i] = gp[i * DH];
   }
 #pragma unroll
   for (int i = 0; i < 16; ++i)
@@ -1201,53 +1282,40 @@ __global__ __launch_bounds__(256) void dots_kernel(const T *q, const T *k, View 
   }
 }
 
-// y = G_F x (+ addscale * addvec[slice][column]) from float32 [slice][rows][DH] or a strided tensor: the filter's backward
-// (symmetric matrix) with the pooled query's share, and the filter as a stage of its own.  add: the per-tile
-// addends of the levels above 6.  filt: coefficient rows as the gate kernel leaves them (stride
-// kCoefStride), or band weights [slice][L + 1] (raw).  Grid (row groups * column pieces, slices, tensors).
-struct FilterJob {
-  const void *x;
-  void *y;
-  const float *add, *addvec;
-};
-template <typename TI, typename TO, int DH>
-__global__ __launch_bounds__(256) void filter_kernel(FilterJob j0, FilterJob j1, View vx, View vy, Dims s, const float *filt, int raw, int L,
-                                                    float addscale) {
+// dQ = G_F dQ_F + dqbar / n and dK = G_F dK_F: the filter's backward (symmetric matrix) with the pooled query's
+// share.  addq, addk: the per-tile addends of the levels above 6.  Grid (row groups * column pieces, slices, 2: Q, K).
+template <typename T, int DH>
+__global__ __launch_bounds__(256) void filter_bwd_kernel(const float *gq, const float *gk, T *dq, T *dk, View v, Dims s, int L,
+                                                        const float *coef, const float *addq, const float *addk,
+                                                        const float *dqbar, float inv_n) {
   using G = Geo<DH>;
   constexpr int CW = G::CW, TR = G::TR;
   __shared__ float segsum[G::SEGS][CW];
   __shared__ float cf[8];
-  const int tid = threadIdx.x, slice = blockIdx.y;
-  const FilterJob &j = blockIdx.z ? j1 : j0;
-  if (tid < 8) {
-    if (raw) {
-      const float *F = filt + (int64_t)slice * (L + 1);
-      cf[tid] = tid == 0 ? F[0] : (tid <= L ? (F[tid] - F[tid - 1]) / (float)(1 << tid) : 0.f);
-    } else {
-      cf[tid] = filt[slice * kCoefStride + tid];
-    }
-  }
+  const int tid = threadIdx.x, slice = blockIdx.y, side = blockIdx.z;
+  if (tid < 8) cf[tid] = coef[slice * kCoefStride + tid];
   const int rg = blockIdx.x / G::PIECES, piece = blockIdx.x % G::PIECES;
   const int c = tid % CW, seg = tid / CW, col = piece * CW + c, t0 = rg * TR + seg * 16;
   const bool cok = col < s.d;
-  const TI *xp = (const TI *)j.x + vx.slice_base(slice) + (cok ? col : 0);
-  float v[16];
+  const float *xp = (side ? gk : gq) + (int64_t)slice * s.nt * grad_tile<DH>() + grad_row<DH>(min(t0, 32 * s.nt - 16)) + col;
+  float x[16];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) v[i] = ld(xp + (int64_t)min(t0 + i, s.n - 1) * vx.sn);
+  for (int i = 0; i < 16; ++i) x[i] = xp[i * DH];
 #pragma unroll
   for (int i = 0; i < 16; ++i)
-    if (t0 + i >= s.n) v[i] = 0.f;
-  segsum[seg][c] = segment_sum<16>(v);
+    if (t0 + i >= s.n) x[i] = 0.f;
+  segsum[seg][c] = segment_sum<16>(x);
   __syncthreads();
   float upper = upper_levels<CW>(segsum, cf, seg, c, L);
+  const float *add = side ? addk : addq;
   const int ntl = (s.n + 63) / 64, gt = (rg * TR) / 64 + seg / 4;
-  if (j.add && cok && gt < ntl) upper += j.add[((int64_t)slice * ntl + gt) * s.d + col];
-  filter_segment<16>(v, cf, upper, L);
-  const float extra = (j.addvec && cok) ? addscale * j.addvec[(int64_t)slice * s.d + col] : 0.f;
-  TO *yp = (TO *)j.y + vy.slice_base(slice) + (cok ? col : 0);
+  if (add && cok && gt < ntl) upper += add[((int64_t)slice * ntl + gt) * s.d + col];
+  filter_segment<16>(x, cf, upper, L);
+  const float extra = !side && cok ? inv_n * dqbar[(int64_t)slice * s.d + col] : 0.f;
+  T *yp = (side ? dk : dq) + v.slice_base(slice) + (cok ? col : 0);
 #pragma unroll
   for (int i = 0; i < 16; ++i)
-    if (cok && t0 + i < s.n) st(yp + (int64_t)(t0 + i) * vy.sn, v[i] + extra);
+    if (cok && t0 + i < s.n) st(yp + (int64_t)(t0 + i) * v.sn, x[i] + extra);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1359,7 +1427,6 @@ struct Plan {
   int chunks, rows_per_chunk;         // pooling
   int FW, TW, splits, tiles_per_split, shares;
   int groups;                         // 4096-element workgroups per slice
-  int bgroups;                        // the same for whole rows (prep_bwd)
   int ntl;                            // 64-row tiles per slice
 };
 Plan plan_of(const wersa_desc &c) {
@@ -1397,20 +1464,19 @@ Plan plan_of(const wersa_desc &c) {
   p.shares = p.splits * p.TW;
   const int cw = p.DH < 64 ? p.DH : 64, tr = 4096 / cw;
   p.groups = (c.n + tr - 1) / tr * (p.DH / cw);
-  p.bgroups = (p.s.nt * 32 + 4096 / p.DH - 1) / (4096 / p.DH);
   return p;
 }
 
 struct Ws {
   float *qpart, *part, *zpart, *zpad, *Nbuf, *pyr;
-  bf16_t *VC, *SB;
+  bf16_t *VC, *SB, *XQ, *XK;   // (XQ, XK: see keeps_operands)
   // backward
-  bf16_t *NR, *NC, *VR, *XS, *dSA, *dSB;
-  float *ddw, *rowscale, *dpart, *dS, *dz, *gq, *gk, *partQ, *partK, *dF, *dlogit, *dqbar, *tgq, *tgk, *aq, *ak;
+  bf16_t *NC, *XS, *SA, *dSA, *dSB;
+  float *ddw, *rowscale, *dpart, *gq, *gk, *partQ, *partK, *dF, *dlogit, *dqbar, *tgq, *tgk, *aq, *ak;
   int64_t total;
 };
 int64_t tile_floats(int64_t tiles) { return tiles * (kTile / 2); }
-Ws ws_of(const wersa_desc &c, const Plan &p, int bwd, float *base) {
+Ws ws_of(const wersa_desc &c, const Plan &p, int bwd, bool keep, float *base) {
   Ws w{};
   Bump b(base);
   const int64_t sl = (int64_t)c.B * c.H;
@@ -1419,27 +1485,31 @@ Ws ws_of(const wersa_desc &c, const Plan &p, int bwd, float *base) {
   const bool deep = c.L > kTileL;
   w.part = b.take(sl * p.shares * p.s.mt * 32 * 32 * p.CT);
   w.zpart = b.take(sl * p.shares * p.s.mt * 32);
-  w.zpad = b.take(sl * p.s.mt * 32);
   if (!bwd) {
+    w.zpad = b.take(sl * p.s.mt * 32);
     w.qpart = b.take(sl * p.chunks * c.d);
     w.VC = op(rows * 2 * p.CT * p.PT);
+    if (!keep) {
+      w.XQ = op(rows * p.KS * 3);
+      w.XK = op(rows * p.KS * 3);
+    }
     w.SB = op((sl * p.s.mt + 1) * p.NSB);       // (one feature tile more: a stage reads whole groups)
     if (c.flags & WERSA_FLAG_LAYERNORM) w.Nbuf = b.take(sl * c.n * c.d);
     if (deep) w.pyr = b.take(2 * sl * pyramid_floats(p.ntl, c.d));
   } else {
-    w.NR = op(rows * p.KS * p.PT);
     w.NC = op(rows * 2 * p.CT * p.PT);
-    w.VR = op(rows * p.KS * p.PT);
-    if (p.PT == 1) w.XS = op(rows * p.KS * 3);
-    w.dSA = op(sl * p.s.mt * (3 * p.KS + 1) + 3 * p.KS + 1);
+    // dQ_F and dK_F, in the place of operands that nothing else needs
+    w.gq = (float *)op(rows * p.KS * 3);
+    w.gk = (float *)op(rows * p.KS * 3);
+    if (p.PT == 1) w.XS = (bf16_t *)w.gq;
+    else if (!keep) w.XQ = (bf16_t *)w.gq;
+    if (!keep) w.XK = (bf16_t *)w.gk;
+    w.SA = op((sl * p.s.mt + 1) * (3 * p.KS + 1));
+    w.dSA = op((sl * p.s.mt + 1) * (3 * p.KS + 1));
     w.dSB = op((sl * p.s.mt + 1) * p.NSB);
     w.ddw = b.take(rows * 32);
-    w.rowscale = b.take(rows * 32);
-    w.dpart = b.take(sl * p.bgroups);
-    w.dS = b.take(sl * c.m * c.d);
-    w.dz = b.take(sl * c.m);
-    w.gq = b.take(rows * 32 * p.DH);
-    w.gk = b.take(rows * 32 * p.DH);
+    if (p.PT == 1) w.rowscale = b.take(rows * 32);
+    w.dpart = b.take(sl * p.groups);
     const int64_t prow = p.groups + (deep ? c.d / kCoarseCols : 0);
     w.partQ = b.take(sl * prow * (c.L + 1));
     w.partK = b.take(sl * prow * (c.L + 1));
@@ -1456,6 +1526,16 @@ Ws ws_of(const wersa_desc &c, const Plan &p, int bwd, float *base) {
   }
   w.total = b.off;
   return w;
+}
+
+// Where Q_F and K_F, packed (6 bytes per element each), live between the forward and the backward.  In `saved` where the rest
+// of the forward's workspace fits wersa_forward_static's scratch: the backward has less to do where latency counts (64 slices
+// of 1000 tokens, d 64, m 64, float32: 110 us, 122 us where it packs them again), and what the static call takes does not
+// shrink by them.  Beyond, `saved` would hold three times a tensor for every layer of a model (811 MB for 8 slices of 131072
+// tokens, d 64, against 5), and the backward packs them again, from Q and K, in the launch that packs dN: 8 x 16384 tokens, d 64,
+// m 256 367 us -> 374, 128 x 4000, d 32, m 1024 1716 -> 1763.
+bool keeps_operands(const wersa_desc &c, const Plan &p) {
+  return (size_t)ws_of(c, p, 0, true, nullptr).total * sizeof(float) <= kStaticScratchBytes;
 }
 
 // Rows of the strided tensors can be read in 16-byte pieces.
@@ -1499,7 +1579,7 @@ void launch_apply(const wersa_desc &c, const Plan &p, const bf16_t *X, const bf1
   }
 }
 template <typename T, int DH, int PT, bool DV>
-void launch_grad(const wersa_desc &c, const Plan &p, const bf16_t *X, const bf16_t *Y, const float *ddw, const float *rowscale,
+void launch_grad(const wersa_desc &c, const Plan &p, const bf16_t *X, const GradRows<T> &Y, const float *ddw, const float *rowscale,
                  const bf16_t *OA, const bf16_t *SA, const bf16_t *OB, const bf16_t *SB, const float *scalars, float *dXF,
                  T *dv, View v, hipStream_t st) {
   constexpr int RT = DH == 16 && (PT == 1 || !DV) ? 2 : 1;   // (as many token tiles as the registers of two waves per SIMD hold)
@@ -1522,14 +1602,15 @@ wersa_status forward_t(const wersa_desc &c, const T *q, const T *k, const T *v, 
                        const float *gate_w, const float *gate_b, const float *scale_w, T *out, float *saved, float *ws,
                        hipStream_t st) {
   const Plan p = plan_of(c);
-  const Ws w = ws_of(c, p, 0, ws);
+  const bool keep = keeps_operands(c, p);
+  const Ws w = ws_of(c, p, 0, keep, ws);
   const SavedLayout sv = saved_layout(c);
   const int slices = c.B * c.H;
   const View tv{c.stride_b, c.stride_h, c.stride_n, c.H};
   const bool deep = c.L > kTileL, ln = (c.flags & WERSA_FLAG_LAYERNORM) != 0;
   float *scalars = saved + sv.scalars, *coef = saved + sv.coef;
-  bf16_t *XQ = (bf16_t *)(saved + sv.XQ), *XK = (bf16_t *)(saved + sv.XK), *OA = (bf16_t *)(saved + sv.OA),
-         *OB = (bf16_t *)(saved + sv.OB), *SA = (bf16_t *)(saved + sv.SA);
+  bf16_t *XQ = keep ? (bf16_t *)(saved + sv.XQ) : w.XQ, *XK = keep ? (bf16_t *)(saved + sv.XK) : w.XK,
+         *OA = (bf16_t *)(saved + sv.OA), *OB = (bf16_t *)(saved + sv.OB);
   const bf16_t *OAk = OA + (p.matrices == 2 ? (int64_t)p.s.mt * p.KS * PT * kTile : 0);
   float *addQ = deep ? saved + sv.addQ : nullptr, *addK = deep ? saved + sv.addK : nullptr;
   float *qpart = deep ? saved + sv.tileQ : w.qpart, *kpart = deep ? saved + sv.tileK : nullptr;
@@ -1551,7 +1632,7 @@ wersa_status forward_t(const wersa_desc &c, const T *q, const T *k, const T *v, 
   WERSA_STAGE("split_contract", st, contract_kernel<DH, PT><<<dim3(p.splits, p.s.mt / p.FW, slices), 512, 0, st>>>(
       XK, w.VC, nullptr, OAk, p.s, p.FW, p.TW, p.tiles_per_split, w.part, w.zpart));
   WERSA_STAGE("split_reduce", st, reduce_kernel<DH><<<dim3(p.s.mt, slices), 256, 0, st>>>(
-      w.part, w.zpart, p.shares, 1, scalars, p.s, saved + sv.S, saved + sv.z, w.zpad, SA, w.SB));
+      w.part, w.zpart, p.shares, 1, scalars, p.s, saved + sv.S, saved + sv.z, w.zpad, nullptr, w.SB, nullptr));
   if (ln) {
     launch_apply<T, DH, PT, 1>(c, p, XQ, OA, w.SB, w.zpad, scalars, out, tv, w.Nbuf, nullptr, st);
     WERSA_STAGE("split_ln", st, ln_out_kernel<T><<<dim3((c.n + 3) / 4, slices), 256, 0, st>>>(w.Nbuf, out, tv, c.n, c.d, c.eps, saved + sv.D));
@@ -1566,30 +1647,36 @@ wersa_status backward_t(const wersa_desc &c, const T *q, const T *k, const T *v,
                         const T *out, const T *dout, const float *saved, T *dq, T *dk, T *dv, float *dgate_w, float *dgate_b,
                         float *dscale_w, float *dsigma, float *ws, hipStream_t st) {
   const Plan p = plan_of(c);
-  const Ws w = ws_of(c, p, 1, ws);
+  const bool keep = keeps_operands(c, p);
+  const Ws w = ws_of(c, p, 1, keep, ws);
   const SavedLayout sv = saved_layout(c);
   const int slices = c.B * c.H;
   const View tv{c.stride_b, c.stride_h, c.stride_n, c.H};
   const bool deep = c.L > kTileL, ln = (c.flags & WERSA_FLAG_LAYERNORM) != 0;
-  const float *scalars = saved + sv.scalars, *coef = saved + sv.coef;
-  const bf16_t *XQ = (const bf16_t *)(saved + sv.XQ), *XK = (const bf16_t *)(saved + sv.XK), *OA = (const bf16_t *)(saved + sv.OA),
-               *OB = (const bf16_t *)(saved + sv.OB), *SA = (const bf16_t *)(saved + sv.SA);
+  const float *scalars = saved + sv.scalars, *coef = saved + sv.coef, *D = saved + sv.D;
+  // (with one-term operands XS serves the query side's gradient too: of X Omega it needs the sign alone)
+  const bf16_t *XQ = PT == 1 ? w.XS : keep ? (const bf16_t *)(saved + sv.XQ) : w.XQ,
+               *XK = keep ? (const bf16_t *)(saved + sv.XK) : w.XK, *OA = (const bf16_t *)(saved + sv.OA),
+               *OB = (const bf16_t *)(saved + sv.OB);
   const int64_t two = p.matrices == 2 ? p.s.mt : 0;
   const bf16_t *OAk = OA + two * p.KS * PT * kTile, *OBk = OB + two * 2 * p.CT * PT * kTile;
-  const int vec = rows_aligned(c, {v, out, dout});
-  WERSA_STAGE("split_prep_bwd", st, prep_bwd_kernel<T, DH, PT><<<dim3(p.bgroups, slices), 256, 0, st>>>(
-      dout, out, v, tv, p.s, vec, ln, saved + sv.D, XQ, w.NR, w.NC, w.VR, w.XS, w.ddw, w.rowscale, w.dpart));
+  const int vec = rows_aligned(c, {q, k, v, out, dout});
+  WERSA_STAGE("split_prep_bwd", st, prep_bwd_kernel<T, DH, PT><<<dim3(p.groups, slices, keep ? (PT == 1 ? 2 : 1) : 3), 256, 0, st>>>(
+      dout, out, q, k, tv, p.s, vec, ln, c.L, coef, deep ? saved + sv.addQ : nullptr, deep ? saved + sv.addK : nullptr, D, w.NC,
+      w.XQ, w.XS, w.XK, w.ddw, w.rowscale, w.dpart));
   WERSA_STAGE("split_contract", st, contract_kernel<DH, PT><<<dim3(p.splits, p.s.mt / p.FW, slices), 512, 0, st>>>(
-      PT == 1 ? w.XS : XQ, w.NC, w.ddw, OA, p.s, p.FW, p.TW, p.tiles_per_split, w.part, w.zpart));
-  WERSA_STAGE("split_reduce", st, reduce_kernel<DH><<<dim3(p.s.mt, slices), 256, 0, st>>>(
-      w.part, w.zpart, p.shares, PT == 1 ? 3 : 1, scalars, p.s, w.dS, w.dz, w.zpad, w.dSA, w.dSB));
-  if constexpr (DH == 128) {   // (dV on its own: no registers left for its accumulators)
-    launch_grad<T, DH, PT, false>(c, p, XK, w.VR, nullptr, nullptr, OAk, w.dSA, OBk, nullptr, scalars, w.gk, nullptr, tv, st);
-    launch_apply<T, DH, PT, 2>(c, p, XK, OAk, w.dSB, w.zpad, scalars, dv, tv, nullptr, nullptr, st);
+      XQ, w.NC, w.ddw, OA, p.s, p.FW, p.TW, p.tiles_per_split, w.part, w.zpart));
+  WERSA_STAGE("split_reduce", st, reduce_kernel<DH><<<dim3(p.s.mt, slices, 2), 256, 0, st>>>(
+      w.part, w.zpart, p.shares, PT == 1 ? 3 : 1, scalars, p.s, const_cast<float *>(saved + sv.S), const_cast<float *>(saved + sv.z),
+      nullptr, w.dSA, w.dSB, w.SA));
+  const GradRows<T> rowsK{v, nullptr, nullptr, vec}, rowsQ{dout, ln ? out : nullptr, PT == 1 ? nullptr : D, vec};
+  if constexpr (DH == 128) {   // (dV on its own: no registers left for its accumulators; first, dK_F may go in the place of K_F)
+    launch_apply<T, DH, PT, 2>(c, p, XK, OAk, w.dSB, nullptr, scalars, dv, tv, nullptr, nullptr, st);
+    launch_grad<T, DH, PT, false>(c, p, XK, rowsK, nullptr, nullptr, OAk, w.dSA, OBk, nullptr, scalars, w.gk, nullptr, tv, st);
   } else {
-    launch_grad<T, DH, PT, true>(c, p, XK, w.VR, nullptr, nullptr, OAk, w.dSA, OBk, w.dSB, scalars, w.gk, dv, tv, st);
+    launch_grad<T, DH, PT, true>(c, p, XK, rowsK, nullptr, nullptr, OAk, w.dSA, OBk, w.dSB, scalars, w.gk, dv, tv, st);
   }
-  launch_grad<T, DH, PT, false>(c, p, XQ, w.NR, w.ddw, PT == 1 ? w.rowscale : nullptr, OA, SA, OB, nullptr, scalars, w.gq,
+  launch_grad<T, DH, PT, false>(c, p, XQ, rowsQ, w.ddw, PT == 1 ? w.rowscale : nullptr, OA, w.SA, OB, nullptr, scalars, w.gq,
                                 nullptr, tv, st);
   const int prow = p.groups + (deep ? c.d / kCoarseCols : 0);
   WERSA_STAGE("split_dots", st, dots_kernel<T, DH><<<dim3(p.groups, slices, 2), 256, 0, st>>>(
@@ -1601,11 +1688,10 @@ wersa_status backward_t(const wersa_desc &c, const T *q, const T *k, const T *v,
       w.partQ, w.partK, prow, c.L, c.d, c.H, saved + sv.s, gate_w, scale_w, w.dF, w.dlogit, w.dqbar,
       (c.flags & WERSA_FLAG_POOLED_GATE) ? 1 : 0));
   WERSA_STAGE("gate_bwd_params_kernel", st, gate_bwd_params_kernel<<<gate_bwd_params_blocks(c.H, c.L, c.d), 256, 0, st>>>(
-      w.dF, w.dlogit, saved + sv.s, saved + sv.qbar, w.dpart, slices * p.bgroups, c.B, c.H, c.L, c.d, c.eps, scalars, dgate_w,
+      w.dF, w.dlogit, saved + sv.s, saved + sv.qbar, w.dpart, slices * p.groups, c.B, c.H, c.L, c.d, c.eps, scalars, dgate_w,
       dgate_b, dscale_w, dsigma));
-  const View gv{(int64_t)p.s.nt * 32 * DH, 0, DH, 1};
-  WERSA_STAGE("split_filter_bwd", st, filter_kernel<float, T, DH><<<dim3(p.groups, slices, 2), 256, 0, st>>>(
-      FilterJob{w.gq, dq, w.aq, w.dqbar}, FilterJob{w.gk, dk, w.ak, nullptr}, gv, tv, p.s, coef, 0, c.L, 1.0f / (float)c.n));
+  WERSA_STAGE("split_filter_bwd", st, filter_bwd_kernel<T, DH><<<dim3(p.groups, slices, 2), 256, 0, st>>>(
+      w.gq, w.gk, dq, dk, tv, p.s, c.L, coef, w.aq, w.ak, w.dqbar, 1.0f / (float)c.n));
   return hipGetLastError() == hipSuccess ? WERSA_OK : WERSA_ERR_LAUNCH;
 }
 
@@ -1634,14 +1720,14 @@ wersa_status dispatch(const wersa_desc &c, F f) {
 
 SplitSizes split_sizes(const wersa_desc &c) {
   const Plan p = plan_of(c);
-  const int64_t sl = (int64_t)c.B * c.H;
+  const int64_t X = keeps_operands(c, p) ? tile_floats((int64_t)c.B * c.H * p.s.nt * p.KS * 3) : 0;
   // (one feature tile more than there are: a stage of the row kernels reads whole groups of them)
-  return SplitSizes{tile_floats(sl * p.s.nt * p.KS * 3), tile_floats((int64_t)(p.matrices * p.s.mt + 1) * p.KS * p.PT),
-                    tile_floats((int64_t)(p.matrices * p.s.mt + 1) * 2 * p.CT * p.PT),
-                    tile_floats((sl * p.s.mt + 1) * (3 * p.KS + 1))};
+  return SplitSizes{X, tile_floats((int64_t)(p.matrices * p.s.mt + 1) * p.KS * p.PT),
+                    tile_floats((int64_t)(p.matrices * p.s.mt + 1) * 2 * p.CT * p.PT)};
 }
 size_t split_workspace_bytes(const wersa_desc &c, int for_backward) {
-  return (size_t)ws_of(c, plan_of(c), for_backward, nullptr).total * sizeof(float);
+  const Plan p = plan_of(c);
+  return (size_t)ws_of(c, p, for_backward, keeps_operands(c, p), nullptr).total * sizeof(float);
 }
 wersa_status split_forward(const wersa_desc &c, const void *q, const void *k, const void *v, const void *omega_rf,
                            const float *sigma, const float *gate_w, const float *gate_b, const float *scale_w, void *out,

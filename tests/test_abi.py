@@ -56,6 +56,30 @@ def test_few_rows_many_features_fit_the_static_scratch(lib, L, dtype, flags):
     assert 0 < lib.wersa_workspace_bytes(ctypes.byref(d), 0) <= lib.wersa_static_scratch_bytes()
 
 
+def _dense(dtype=0, **kw):
+    kw = dict(dict(B=1, L=3, flags=0), **kw)
+    return _desc(dtype=dtype, stride_b=kw["H"] * kw["n"] * kw["d"], stride_h=kw["n"] * kw["d"], stride_n=kw["d"], **kw)
+
+
+@pytest.mark.parametrize("dtype,H,n,d,m", [(0, 8, 131072, 64, 256), (0, 8, 131072, 80, 256), (0, 128, 4000, 32, 1024),
+                                           (1, 8, 131072, 16, 1024), (0, 32, 4096, 128, 64)])
+def test_saved_of_a_large_problem_is_what_the_backward_cannot_form_again(lib, dtype, H, n, d, m):
+    """S, z, the gate's values, the normaliser and operands of the size of Omega: nothing of n x d."""
+    have = lib.wersa_saved_bytes(ctypes.byref(_dense(dtype, H=H, n=n, d=d, m=m)))
+    padded = 16 if d <= 16 else 32 if d <= 32 else 64 if d <= 64 else 128
+    need = 4 * H * (m * d + m + d + n + 24 + 64 * 6) + 4 * 6 * (m + 32) * max(padded, 32)
+    assert 0 < have <= need, (have, need)
+
+
+@pytest.mark.parametrize("dtype,H,n,d,m", [(0, 64, 1000, 64, 64), (0, 2, 30000, 64, 64), (1, 32, 4000, 32, 256), (1, 8, 24576, 16, 64)])
+def test_medium_problems_fit_the_static_scratch(lib, dtype, H, n, d, m):
+    """Q_F and K_F, packed, would take these beyond it."""
+    padded = 16 if d <= 16 else 32 if d <= 32 else 64
+    assert H * n * padded * 12 + lib.wersa_workspace_bytes(ctypes.byref(_dense(dtype, H=H, n=n, d=d, m=m)), 0) > lib.wersa_static_scratch_bytes()
+    d = _dense(dtype, H=H, n=n, d=d, m=m)
+    assert 0 < lib.wersa_workspace_bytes(ctypes.byref(d), 0) <= lib.wersa_static_scratch_bytes()
+
+
 @pytest.mark.parametrize("kw,status", [
     (dict(B=0), 1), (dict(n=0), 1), (dict(L=-1), 1), (dict(dtype=7), 1), (dict(bw_floor=0.0), 1),
     (dict(stride_n=32), 1), (dict(stride_h=0), 1), (dict(flags=1 << 20), 1),
