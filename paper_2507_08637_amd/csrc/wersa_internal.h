@@ -56,13 +56,28 @@ constexpr size_t kStaticScratchBytes = (size_t)40 << 20;
 size_t generic_workspace_bytes(const wersa_desc &c, int for_backward);
 size_t split_workspace_bytes(const wersa_desc &c, int for_backward);
 
-// Split path (float32 arithmetic on the bf16 matrix cores): what the MFMA path does not take, head
-// dimensions up to 128.  With far fewer rows than features its copies of S (m d) outweigh the feature matrix
-// (n m) that it saves: 32 slices, n 64, d 128, m 1024 take 41 MiB instead of 29, more than wersa_forward_static has.
-// Shapes that fit there on the generic path alone stay on it.
+// Split path (float32 arithmetic on the bf16 matrix cores): what the MFMA path does not take, head dimensions up to 128.
+// It works on whole 64-row blocks and makes three operand copies of S, at 6 bytes per element of m x d (padded to 16,
+// 32, 64 or 128), so with few rows the generic kernels are faster.  Forward + backward, float32, split against
+// generic: 8 slices, d 128, 4096 features, 1 row 1704 us, 927; 32 rows 1718, 1184; 64 rows 1717, 1479 (of these the
+// forward 383, 541); 32 slices, 1024 features, 32 rows 529, 503; 256 slices, 1 row 905, 853, 16 rows 910, 968; 1000 slices,
+// 1 row 3449, 2825, 32 rows 3618, 3467, 256 features, 1 row 1039, 848.  d 80: 256 slices, 1024 features, 1 row 890, 705,
+// 16 rows 892, 783, 32 rows 906, 895.  d 64: 8 slices, 4096 features, 1 row 970,
+// 890, 16 rows 972, 994; 1000 slices, 1024 features, 16 rows 2122, 1823, 32 rows 2129, 2105.
+// d 16 and 32: the split path throughout.
+inline bool few_rows(const wersa_desc &c) {
+  const int DH = c.d > 64 ? 128 : c.d > 32 ? 64 : 32, slices = c.B * c.H;
+  if (DH < 64) return false;
+  if (slices < 128) return c.m * DH >= 1 << 17 && c.n <= (DH == 128 ? 32 : 8);
+  if (slices < 512) return DH - c.d >= 32 && c.m >= 1024 && c.n <= 16;   // (a third of the columns or more are padding)
+  return c.m >= 256 && c.n <= DH / 4;
+}
+// Where one of the two alone fits wersa_forward_static's scratch, that one: what the call takes does not depend on which is
+// the faster (32 slices, n 64, d 128, m 1024: 44 MiB on the split path, 29 on the generic one; 531 against 614 us).
 inline bool use_split(const wersa_desc &c) {
   if (use_fast(c) || c.d > 128) return false;
-  return split_workspace_bytes(c, 0) <= kStaticScratchBytes || generic_workspace_bytes(c, 0) > kStaticScratchBytes;
+  const bool split = split_workspace_bytes(c, 0) <= kStaticScratchBytes, generic = generic_workspace_bytes(c, 0) <= kStaticScratchBytes;
+  return split == generic ? !few_rows(c) : split;
 }
 struct SplitSizes {
   int64_t X, OA, OB;   // floats: packed Q_F or K_F (0: formed again by the backward), Omega both ways

@@ -80,6 +80,18 @@ def test_medium_problems_fit_the_static_scratch(lib, dtype, H, n, d, m):
     assert 0 < lib.wersa_workspace_bytes(ctypes.byref(d), 0) <= lib.wersa_static_scratch_bytes()
 
 
+@pytest.mark.parametrize("H,n,d,m,generic", [
+    (8, 1, 128, 4096, True), (8, 32, 128, 4096, True), (32, 32, 128, 4096, True), (32, 33, 128, 4096, False), (8, 8, 64, 4096, True), (8, 9, 64, 4096, False),
+    (8, 1, 128, 512, False), (8, 16, 80, 1024, True),
+    (256, 1, 128, 1024, False), (256, 16, 80, 1024, True),
+    (256, 17, 80, 1024, False), (1000, 16, 64, 1024, True),
+    (1000, 17, 64, 1024, False), (1000, 32, 112, 256, True), (1000, 1, 64, 240, False), (1000, 1, 32, 4096, False)])
+def test_few_rows_take_the_generic_kernels(lib, H, n, d, m, generic):
+    """Told from `saved`: the split path keeps operands of Omega in it."""
+    plain = sum((k + 63) // 64 * 64 for k in (H * m * d, H * m, H * d, H * 4, H * 4, H * n)) * 4
+    assert (lib.wersa_saved_bytes(ctypes.byref(_dense(H=H, n=n, d=d, m=m))) == plain) == generic
+
+
 @pytest.mark.parametrize("kw,status", [
     (dict(B=0), 1), (dict(n=0), 1), (dict(L=-1), 1), (dict(dtype=7), 1), (dict(bw_floor=0.0), 1),
     (dict(stride_n=32), 1), (dict(stride_h=0), 1), (dict(flags=1 << 20), 1),
