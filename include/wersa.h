@@ -59,7 +59,7 @@ typedef enum { WERSA_F32 = 0, WERSA_BF16 = 1 } wersa_dtype;
 
 /* desc.flags bits. By default the library picks the MFMA path (bf16 storage, fp16/bf16 matrix
  * cores, float32 accumulation) when the shape allows it: dtype bf16, d in {64, 128},
- * m % 128 == 0, strides multiples of 8 elements (any n, any L <= 20; stride_n <= 2^24 where n % 64 != 0);
+ * m % 128 == 0, strides multiples of 8 elements (any n, any L <= 20);
  * otherwise the generic path:
  * float32 arithmetic throughout (contractions on the bf16 matrix cores with every float32 operand as
  * the sum of three bf16 values for d <= 128, float32 matrix instructions above, and where only these

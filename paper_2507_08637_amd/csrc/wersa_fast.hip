@@ -2120,8 +2120,8 @@ FastWs fast_ws(const wersa_desc &c, const FastPlan &p, int bwd, float *base, flo
   FastWs w{};
   Bump b(base);
   const int64_t sl = (int64_t)c.B * c.H, md = (int64_t)c.m * c.d;
-  const SavedLayout sv = saved_layout(c);
-  if (saved) {
+  if (saved) {   // (asked for the size alone, this may be called to find out which path a descriptor takes)
+    const SavedLayout sv = saved_layout(c);
     w.scalars = saved + sv.scalars;
     w.coef = saved + sv.coef;
     w.omT = reinterpret_cast<_Float16 *>(saved + sv.omT);
@@ -2446,6 +2446,36 @@ wersa_status fast_backward_t(const wersa_desc &c, const bf16_t *q, const bf16_t 
   return hipGetLastError() == hipSuccess ? WERSA_OK : WERSA_ERR_LAUNCH;
 }
 
+// A partial last block whose rows lie too far apart for a buffer (kMaxBufferStride): the tensors are copied to dense
+// ones in the workspace and the results back.  Rows of more than 32 MB: there are never many.
+bool rows_far_apart(const wersa_desc &c) { return c.n % 64 != 0 && c.stride_n > kMaxBufferStride; }
+wersa_desc dense_desc(const wersa_desc &c) {
+  wersa_desc o = c;
+  o.stride_n = c.d;
+  o.stride_h = (int64_t)c.n * c.d;
+  o.stride_b = c.H * o.stride_h;
+  return o;
+}
+size_t dense_floats(const wersa_desc &c) { return ((size_t)c.B * c.H * c.n * c.d / 2 + 63) / 64 * 64; }   // of one bf16 tensor
+struct CopyJob {
+  const bf16_t *src[5];
+  bf16_t *dst[5];
+};
+__global__ __launch_bounds__(256) void copy_rows_kernel(CopyJob job, View vs, View vd, int n, int d) {
+  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int pieces = d / 8, slice = blockIdx.y;
+  if (e >= (int64_t)n * pieces) return;
+  const int t = (int)(e / pieces), c = (int)(e % pieces) * 8;
+  *reinterpret_cast<u16x8 *>(job.dst[blockIdx.z] + vd.slice_base(slice) + (int64_t)t * vd.sn + c) =
+      *reinterpret_cast<const u16x8 *>(job.src[blockIdx.z] + vs.slice_base(slice) + (int64_t)t * vs.sn + c);
+}
+void copy_rows(const wersa_desc &from, const wersa_desc &to, const CopyJob &job, int count, hipStream_t st) {
+  const View vs{from.stride_b, from.stride_h, from.stride_n, from.H}, vd{to.stride_b, to.stride_h, to.stride_n, to.H};
+  const int64_t pieces = (int64_t)from.n * (from.d / 8);
+  WERSA_STAGE("wersa_copy_rows", st, copy_rows_kernel<<<dim3((unsigned)((pieces + 255) / 256), from.B * from.H, count), 256, 0, st>>>(
+      job, vs, vd, from.n, from.d));
+}
+
 }  // namespace
 
 bool fast_haar_filter_supported(const wersa_desc &c, const void *x, const void *xf) {
@@ -2462,19 +2492,35 @@ wersa_status fast_haar_filter(const wersa_desc &c, const void *x, const float *f
 }
 
 bool fast_supported(const wersa_desc &c) {
-  return c.dtype == WERSA_BF16 && (c.d == 64 || c.d == 128) && c.m % 128 == 0 &&
-         c.stride_n % 8 == 0 && c.stride_h % 8 == 0 && c.stride_b % 8 == 0 &&
-         (c.n % 64 == 0 || c.stride_n <= kMaxBufferStride);
+  if (c.dtype != WERSA_BF16 || (c.d != 64 && c.d != 128) || c.m % 128 || c.stride_n % 8 || c.stride_h % 8 || c.stride_b % 8)
+    return false;
+  // (the copies do not take a call away from wersa_forward_static)
+  return !rows_far_apart(c) || fast_workspace_bytes(c, 0) <= kStaticScratchBytes ||
+         (split_workspace_bytes(c, 0) > kStaticScratchBytes && generic_workspace_bytes(c, 0) > kStaticScratchBytes);
 }
 
 size_t fast_workspace_bytes(const wersa_desc &c, int for_backward) {
-  return (size_t)fast_ws(c, fast_plan(c), for_backward, nullptr, nullptr).total * sizeof(float);
+  size_t floats = (size_t)fast_ws(c, fast_plan(c), for_backward, nullptr, nullptr).total;
+  if (rows_far_apart(c)) floats += (for_backward ? 8 : 4) * dense_floats(c);
+  return floats * sizeof(float);
 }
 
 wersa_status fast_forward(const wersa_desc &c, const void *q, const void *k, const void *v,
                           const void *omega_rf, const float *sigma, const float *gate_w,
                           const float *gate_b, const float *scale_w, void *out, float *saved,
                           float *ws, hipStream_t st, const PooledSums *pooled) {
+  if (rows_far_apart(c)) {
+    const wersa_desc dc = dense_desc(c);
+    const size_t one = dense_floats(c);
+    float *p = ws + fast_workspace_bytes(dc, 0) / sizeof(float);
+    bf16_t *t[4];
+    for (int i = 0; i < 4; ++i) t[i] = (bf16_t *)(p + i * one);
+    copy_rows(c, dc, CopyJob{{(const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v}, {t[0], t[1], t[2]}}, 3, st);
+    const wersa_status rc = fast_forward(dc, t[0], t[1], t[2], omega_rf, sigma, gate_w, gate_b, scale_w, t[3], saved, ws, st, nullptr);
+    if (rc != WERSA_OK) return rc;
+    copy_rows(dc, c, CopyJob{{t[3]}, {(bf16_t *)out}}, 1, st);
+    return hipGetLastError() == hipSuccess ? WERSA_OK : WERSA_ERR_LAUNCH;
+  }
   if (c.d == 64)
     return fast_forward_t<64>(c, (const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v,
                               (const bf16_t *)omega_rf, sigma, gate_w, gate_b, scale_w, (bf16_t *)out,
@@ -2490,6 +2536,20 @@ wersa_status fast_backward(const wersa_desc &c, const void *q, const void *k, co
                            const float *saved, void *dq, void *dk, void *dv, float *dgate_w,
                            float *dgate_b, float *dscale_w, float *dsigma, float *ws,
                            hipStream_t st) {
+  if (rows_far_apart(c)) {
+    const wersa_desc dc = dense_desc(c);
+    const size_t one = dense_floats(c);
+    float *p = ws + fast_workspace_bytes(dc, 1) / sizeof(float);
+    bf16_t *t[8];
+    for (int i = 0; i < 8; ++i) t[i] = (bf16_t *)(p + i * one);
+    copy_rows(c, dc, CopyJob{{(const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v, (const bf16_t *)out, (const bf16_t *)dout},
+                             {t[0], t[1], t[2], t[3], t[4]}}, 5, st);
+    const wersa_status rc = fast_backward(dc, t[0], t[1], t[2], omega_rf, sigma, gate_w, scale_w, t[3], t[4], saved, t[5], t[6],
+                                          t[7], dgate_w, dgate_b, dscale_w, dsigma, ws, st);
+    if (rc != WERSA_OK) return rc;
+    copy_rows(dc, c, CopyJob{{t[5], t[6], t[7]}, {(bf16_t *)dq, (bf16_t *)dk, (bf16_t *)dv}}, 3, st);
+    return hipGetLastError() == hipSuccess ? WERSA_OK : WERSA_ERR_LAUNCH;
+  }
   if (c.d == 64)
     return fast_backward_t<64>(c, (const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v,
                                (const bf16_t *)omega_rf, sigma, gate_w, scale_w, (const bf16_t *)out,

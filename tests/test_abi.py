@@ -92,6 +92,18 @@ def test_few_rows_take_the_generic_kernels(lib, H, n, d, m, generic):
     assert (lib.wersa_saved_bytes(ctypes.byref(_dense(H=H, n=n, d=d, m=m))) == plain) == generic
 
 
+@pytest.mark.parametrize("n", [1, 63, 64, 1000])
+def test_rows_far_apart_stay_on_the_mfma_path(lib, n):
+    far = (1 << 24) + 8
+    d = _desc(dtype=1, n=n, m=128, stride_b=8, stride_h=64, stride_n=far)
+    assert lib.wersa_selected_path(ctypes.byref(d)) == 1
+    for bwd, copies in ((0, 4), (1, 8)):
+        dense = _desc(dtype=1, n=n, m=128, stride_b=2 * n * 64, stride_h=n * 64, stride_n=64)
+        extra = lib.wersa_workspace_bytes(ctypes.byref(d), bwd) - lib.wersa_workspace_bytes(ctypes.byref(dense), bwd)
+        assert extra == (0 if n % 64 == 0 else copies * ((2 * n * 64 * 2 + 255) // 256 * 256))
+    assert lib.wersa_saved_bytes(ctypes.byref(d)) == lib.wersa_saved_bytes(ctypes.byref(dense))
+
+
 @pytest.mark.parametrize("kw,status", [
     (dict(B=0), 1), (dict(n=0), 1), (dict(L=-1), 1), (dict(dtype=7), 1), (dict(bw_floor=0.0), 1),
     (dict(stride_n=32), 1), (dict(stride_h=0), 1), (dict(flags=1 << 20), 1),

@@ -65,3 +65,37 @@ def test_partial_last_block(n, d, m, L, layout, flags):
     assert all(bool(torch.isfinite(t.float()).all()) for t in res[0].values())
     if n >= 1000 and not flags:
         assert errs["out"] < 6e-3 and errs["dq"] < 2e-2 and errs["dk"] < 2e-2, errs
+
+
+@pytest.mark.parametrize("n,d,flags", [(1, 64, 0), (33, 64, 0), (65, 128, 0), (100, 64, 8), (70, 128, 14)])
+def test_rows_further_apart_than_a_buffer_reaches(n, d, flags):
+    """Row strides of more than 2^24 elements with a partial last block: the MFMA path, the bits of dense tensors."""
+    import torch
+    from paper_2507_08637_amd import binding
+    H, L, m, far = 2, 3, 128, (1 << 24) + 8
+    g = torch.Generator(device="cuda").manual_seed(n)
+
+    def normal(*s):
+        return torch.randn(s, generator=g, device="cuda")
+
+    names = ("q", "k", "v", "dout", "out", "dq", "dk", "dv")
+    buf = torch.empty((n - 1) * far + len(names) * H * d, dtype=torch.bfloat16, device="cuda")   # up to 3.4 GB
+    apart = {x: buf.as_strided((1, H, n, d), (8, d, far, 1), i * H * d) for i, x in enumerate(names)}
+    dense = {x: torch.zeros(1, H, n, d, dtype=torch.bfloat16, device="cuda") for x in names}
+    for x in names[:4]:
+        dense[x].copy_(normal(1, H, n, d) + 0.3)
+        apart[x].copy_(dense[x])
+    par = (normal(2, d, m).to(torch.bfloat16) if flags & 2 else normal(d, m).to(torch.bfloat16), torch.ones(1, device="cuda"),
+           normal(H, L + 1, d) / d ** 0.5, normal(H, L + 1), 1 + 0.1 * normal(L + 1))
+    small = []
+    for t in (dense, apart):
+        desc = binding.make_desc(t["q"], L, m, flags=flags)
+        assert binding.load_library().wersa_selected_path(desc) == 1
+        _, saved = binding.wersa_forward(t["q"], t["k"], t["v"], *par, L, out=t["out"], flags=flags)
+        grads = dict(dq=t["dq"], dk=t["dk"], dv=t["dv"], dgate_w=torch.empty_like(par[2]), dgate_b=torch.empty_like(par[3]),
+                     dscale_w=torch.empty_like(par[4]), dsigma=torch.empty(1, device="cuda"))
+        binding.wersa_backward(t["q"], t["k"], t["v"], *par, t["out"], t["dout"], saved, L, grads=grads, flags=flags)
+        small.append([v for k, v in grads.items() if k not in names])
+    for x in names:
+        assert torch.equal(apart[x], dense[x]), x
+    assert all(torch.equal(a, b) for a, b in zip(*small))
