@@ -379,6 +379,7 @@ constexpr int kMinChunk = 256;   // tokens
 struct BlockPlan {
   int64_t tokens, hidden, act;   // act = tokens * hidden elements
   int splits, k_chunk;           // split of the token axis for the weight gradients
+  int wgrads;                    // weight gradients of Q, K, V per launch: 3 or 1
   wersa_desc core;
 };
 
@@ -387,8 +388,7 @@ BlockPlan block_plan(const wersa_desc &c) {
   p.tokens = (int64_t)c.B * c.n;
   p.hidden = (int64_t)c.H * c.d;
   p.act = p.tokens * p.hidden;
-  // Weight gradients: 1024 workgroups of the large tile per product (the three of Q, K, V share a launch), at least
-  // 256 tokens each.  (512 are as fast but make the float32 chain over the tokens of a split twice as long.)
+  // Weight gradients: 1024 workgroups of the large tile per product, at least 256 tokens each.  (512 are as fast but make the float32 chain over the tokens of a split twice as long.)
   const int64_t tiles = (p.hidden / kBigTile) * (p.hidden / kBigTile);
   int64_t z = 1024 / tiles;
   if (z > kMaxSplit) z = kMaxSplit;
@@ -397,6 +397,9 @@ BlockPlan block_plan(const wersa_desc &c) {
   const int64_t steps = (p.tokens / BK + z - 1) / z;
   p.k_chunk = (int)(steps * BK);
   p.splits = (int)((p.tokens + p.k_chunk - 1) / p.k_chunk);
+  // Three in one launch while their partials stay below 512 MiB (hidden 1024: 402 MB).  At hidden 2048 one product fills the chip
+  // four times over and three launches with a third of the partials (805 -> 268 MB) take the same time (856 us each, 131072 tokens).
+  p.wgrads = (int64_t)kMaxSrc * p.splits * p.hidden * p.hidden * 4 <= (int64_t)512 << 20 ? 3 : 1;
   p.core = c;
   p.core.stride_n = p.hidden;
   p.core.stride_h = c.d;
@@ -434,7 +437,7 @@ BlockWs block_ws(const BlockPlan &p, int bwd) {
     w.dQp = off; off += act;
     w.dKp = off; off += act;
     w.dVp = off; off += act;
-    w.part = off; off += up256((size_t)kMaxSrc * p.splits * p.hidden * p.hidden * 4);
+    w.part = off; off += p.splits == 1 ? 0 : up256((size_t)p.wgrads * p.splits * p.hidden * p.hidden * 4);   // (one: no partials)
   }
   w.core = off; off += up256(wersa_workspace_bytes(&p.core, bwd));
   w.total = off;
@@ -626,7 +629,8 @@ wersa_status wersa_block_backward(const wersa_desc *desc, const void *x, const v
   }
   const bf16_t *const right[3] = {dQp, dKp, dVp};
   float *const outs[3] = {dwq, dwk, dwv};
-  if (!weight_grads((const bf16_t *)x, 3, right, outs)) return WERSA_ERR_LAUNCH;
+  for (int i = 0; i < 3; i += p.wgrads)
+    if (!weight_grads((const bf16_t *)x, p.wgrads, right + i, outs + i)) return WERSA_ERR_LAUNCH;
   return hipGetLastError() == hipSuccess ? WERSA_OK : WERSA_ERR_LAUNCH;
 }
 

@@ -104,6 +104,16 @@ def test_rows_far_apart_stay_on_the_mfma_path(lib, n):
     assert lib.wersa_saved_bytes(ctypes.byref(d)) == lib.wersa_saved_bytes(ctypes.byref(dense))
 
 
+@pytest.mark.parametrize("H,n,partials", [(128, 256, 0), (128, 4096, 0), (4, 256, 0), (4, 512, 3 * 2), (16, 65536, 16)])
+def test_block_workspace_holds_partials_of_the_weight_gradients_only_where_there_are_some(lib, H, n, partials):
+    """None with one split of the tokens; of one product at a time where those of three would be large."""
+    c = _desc(H=H, n=n, d=128, m=128, dtype=1)
+    hidden = H * 128
+    core = _desc(H=H, n=n, d=128, m=128, dtype=1, stride_b=n * hidden, stride_h=128, stride_n=hidden)
+    rest = 4 * n * hidden * 2 + (lib.wersa_workspace_bytes(ctypes.byref(core), 1) + 255) // 256 * 256
+    assert lib.wersa_block_workspace_bytes(ctypes.byref(c), 1) == rest + partials * hidden * hidden * 4
+
+
 @pytest.mark.parametrize("kw,status", [
     (dict(B=0), 1), (dict(n=0), 1), (dict(L=-1), 1), (dict(dtype=7), 1), (dict(bw_floor=0.0), 1),
     (dict(stride_n=32), 1), (dict(stride_h=0), 1), (dict(flags=1 << 20), 1),
