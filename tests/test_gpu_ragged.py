@@ -99,3 +99,27 @@ def test_rows_further_apart_than_a_buffer_reaches(n, d, flags):
     for x in names:
         assert torch.equal(apart[x], dense[x]), x
     assert all(torch.equal(a, b) for a, b in zip(*small))
+
+
+@pytest.mark.parametrize("shape", [dict(B=1, H=2, n=1000, d=128, L=6, m=256), dict(B=2, H=2, n=1087, d=64, L=5, m=512),
+                                   dict(B=1, H=2, n=1000, d=64, L=9, m=256), dict(B=2, H=1, n=1087, d=128, L=8, m=128),
+                                   dict(B=2, H=2, n=65, d=64, L=6, m=256), dict(B=2, H=2, n=33, d=128, L=3, m=128)],
+                         ids=lambda s: "n{n}d{d}L{L}m{m}".format(**s))
+@pytest.mark.parametrize("flags", [0, 8], ids=["plain", "layernorm"])
+def test_partial_last_block_against_the_oracle(shape, flags):
+    """O, the saved normaliser (or rstd) and dV where rows before n, too, could come out wrong: 2e-2, the MFMA path's bar; dQ and dK to
+    the same where they are no small differences of large terms (1000 tokens and more)."""
+    from paper_2507_08637_amd import binding, workloads
+    from tests import helpers as hp
+    cfg = dict(shape, dtype="bf16", flavour="plain", seed_base=8100, q_mean=0.3)
+    p = workloads.make_inputs(**cfg)
+    ln = bool(flags)
+    res = hp.gpu_forward_backward(p, cfg, eps=1e-3, flags=flags)
+    ref = hp.oracle_backward(p, cfg, eps=1e-3, layernorm=ln)
+    fwd = hp.oracle_forward(p, cfg, eps=1e-3, keep=("O", "D"), layernorm=ln)
+    errs = {k: hp.rel_err(res[k], ref[k]) for k in ("O", "dQ", "dK", "dV")}
+    errs["D"] = hp.rel_err(res["saved"]["D"], fwd["D"].reshape(res["saved"]["D"].shape))
+    errs["last"] = hp.err_stats(res["O"][:, :, shape["n"] // 64 * 64:], ref["O"][:, :, shape["n"] // 64 * 64:])["fro"]
+    print(cfg, flags, {k: f"{v:.1e}" for k, v in errs.items()}, flush=True)
+    small = shape["n"] < 1000
+    assert all(v < 2e-2 for k, v in errs.items() if not (small and k in ("dQ", "dK"))), errs
