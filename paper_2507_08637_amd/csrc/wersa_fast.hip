@@ -1446,8 +1446,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
           }
         };
         // The pipelined form keeps two more chain results alive than the plain one: it is used where
-        // the registers allow it without spills (not next to the dV accumulators, not with the
-        // partial-block code).
+        // the registers allow it without spills (not next to the dV accumulators).
         constexpr bool PIPE = !DV;
         if (PIPE) {
           // Software pipeline over the feature tiles: while the matrix pipe works through the

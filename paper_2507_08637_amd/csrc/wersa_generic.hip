@@ -1,7 +1,8 @@
 // Generic WERSA path: float32 arithmetic for every storage dtype, one kernel per step of
-// Section 3.1 (steps 3-8), staged through caller workspace.  It runs head dimensions above 128 (below, the
-// same arithmetic without the n x m arrays in memory is wersa_split.hip) and the filter as a stage of its
-// own where the streaming kernel does not take it.  Reductions are fixed-order two-pass sums.
+// Section 3.1 (steps 3-8), staged through caller workspace.  It runs head dimensions above 128, problems of few rows and
+// those that alone here fit the built-in scratch (see use_split; elsewhere the same arithmetic without the n x m arrays in
+// memory is wersa_split.hip), and the filter as a stage of its own where the streaming kernel does not take it.
+// Reductions are fixed-order two-pass sums.
 #include "wersa_internal.h"
 
 #include <type_traits>

@@ -8,14 +8,16 @@
 // float32 product itself.  A bf16 tensor is one exact term, so products with it take three.  The bf16
 // matrix rate is 16 times the float32 one, so even six products leave a factor of 2.7.
 //
-// What bounds it: per 32 x 32 tile of a feature matrix the matrix cores spend 32 cycles per product and
-// 16 of the contraction's length, the vector units about 5 x 64 cycles on ReLU or mask and the split
-// (7 instructions per pair of elements), so head dimensions 16 and 32 are bound by the vector units and
-// 64 and above by the matrix cores.  Two waves per SIMD let one run under the other.
+// What bounds it: per 32 x 32 tile of a feature matrix the matrix cores spend 32 cycles per product and 16 of the
+// contraction's length (and where they form the residuals, four more products), the vector units 5.5 instructions per
+// element on the split and two on ReLU or mask.  Counters (128 slices of 4000 tokens, d 32, m 1024, float32, and 8 of
+// 131072, d 16, bf16): matrix cores busy 65 to 73 and 72 to 79 % of a SIMD's cycles in the four contraction kernels,
+// vector units 45 to 59 and 44 to 56 %; two waves per SIMD let one run under the other.  From d 64 on the matrix cores
+// alone.  grad_kernel with dV at d 64 keeps 72 bytes per lane in scratch (its accumulators and operands fill the 256 registers).
 //
 // Measured against the generic kernels, which write every n x m feature matrix to memory: float32 training step, 128
-// slices of 4000 tokens, d 32, m 1024: 13990 -> 2464 us; bf16 training step, 8 slices of 131072 tokens, d 16, m 1024:
-// 26290 -> 2264 us; float32 inference, one slice of 1024 tokens, d 64, m 64: 118 -> 38 us.
+// slices of 4000 tokens, d 32, m 1024: 13990 -> 2456 us; bf16 training step, 8 slices of 131072 tokens, d 16, m 1024:
+// 26290 -> 2251 us; float32 inference, one slice of 1024 tokens, d 64, m 64: 118 -> 37 us.
 //
 // Layout: every operand is kept in the order in which a wave loads it ("operand tile": 32 vectors x 16
 // k-values of bf16; lane (l32, h) holds vector l32, k = 8 h .. 8 h + 7, 16 bytes; 1 KiB).  Where k runs

@@ -1,7 +1,8 @@
 """Split path (float32 arithmetic on the bf16 matrix cores: three bf16 terms per float32 operand) at the sizes
 where its kernels change shape: head dimensions padded to 16, 32, 64, 128; feature counts that are not whole
 32-feature tiles, or an odd number of them; token counts around the 32- and 64-row tiles and the
-4096-element workgroups; few rows (2-wave workgroups) and many (8 waves); rows that are not 16-byte aligned."""
+4096-element workgroups; few rows (2-wave workgroups) and many (4 waves, 8 at head dimension 64); rows that are not 16-byte
+aligned."""
 import numpy as np
 import pytest
 
@@ -34,7 +35,7 @@ SHAPES = [
     dict(B=2, H=1, n=2300, d=64, L=9, m=256),    # levels above one tile, ragged
     dict(B=1, H=2, n=97, d=112, L=3, m=160),     # columns padded to 128, five feature tiles
     dict(B=1, H=1, n=700, d=128, L=7, m=48),
-    dict(B=16, H=16, n=520, d=16, L=3, m=64),    # 8-wave workgroups, the last one partly idle
+    dict(B=16, H=16, n=520, d=16, L=3, m=64),    # 4-wave workgroups, the last one partly idle
     dict(B=16, H=16, n=260, d=32, L=4, m=128),
     dict(B=16, H=16, n=200, d=64, L=0, m=32),
 ]
