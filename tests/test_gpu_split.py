@@ -1,4 +1,4 @@
-"""Split path (float32 arithmetic on the bf16 matrix cores: three bf16 terms per float32 operand) at the sizes
+"""Split path (float32 arithmetic on the 16-bit matrix cores: two or three terms per float32 operand) at the sizes
 where its kernels change shape: head dimensions padded to 16, 32, 64, 128; feature counts that are not whole
 32-feature tiles, or an odd number of them; token counts around the 32- and 64-row tiles and the
 4096-element workgroups; few rows (2-wave workgroups) and many (4 waves, 8 at head dimension 64); rows that are not 16-byte
@@ -219,3 +219,56 @@ def test_where_a_value_that_is_not_finite_goes(dtype, d, m, L, bad):
         elif where == "do":
             assert not bool(torch.isfinite(dv[:, j].float()).any())
             assert torch.equal(dv[:, rest], ref["dv"][0, 0][:, rest])
+
+
+@pytest.mark.parametrize("d,m,n", [(16, 96, 200), (32, 64, 500), (64, 96, 330), (128, 64, 200)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_magnitudes_far_apart(dtype, d, m, n):
+    """The powers of two that take the operands into fp16's range: tokens up to 2^20 apart in Q, K and V (token tiles of different
+    exponents, 32 tokens at a time), columns of V and features of Omega 2^8 apart, dO 2^30 above the rest.  Every column of O and dV,
+    every feature of S and z and every row of dQ on its own: the worst of 2^-24 per factor and term grows with the sum's length
+    as sqrt(n + m) at most, times 4 for cancellation; bf16: the output's rounding.  A column 2^-8 below the largest keeps 22 bits in
+    a token tile whose exponent is the least favourable: 2^-22, within that."""
+    import torch
+    from paper_2507_08637_amd import binding
+    g = torch.Generator(device="cuda").manual_seed(d + n)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+
+    def normal(*s):
+        return torch.randn(s, generator=g, device="cuda")
+
+    def spread(lo, hi, *s):
+        return 2.0 ** torch.randint(lo, hi + 1, s, generator=g, device="cuda").float()
+
+    tile = torch.arange(n, device="cuda") // 32
+    steps = spread(-10, 10, int(tile[-1]) + 1)
+    q = (normal(n, d) + 0.3) * spread(-10, 10, n, 1)
+    k = (normal(n, d) + 0.3) * spread(-3, 3, n, 1) * 2.0 ** -20
+    v = (0.3 * normal(n, d) + 1) * steps[tile][:, None] * spread(-4, 4, d)
+    do = (0.3 * normal(n, d) + 0.5) * 2.0 ** 30
+    q, k, v, do = (x.to(tdt)[None, None] for x in (q, k, v, do))
+    omega = (normal(d, m) * spread(-4, 4, m)).to(tdt)
+    par = (omega, torch.ones(1, device="cuda"), torch.zeros(1, 1, d, device="cuda"), torch.zeros(1, 1, device="cuda"),
+           2 * torch.ones(1, device="cuda"))   # no levels, F = 1: rows keep their own magnitudes
+    out, saved = binding.wersa_forward(q, k, v, *par, 0, eps=1e-30, flags=1)
+    got = binding.wersa_backward(q, k, v, *par, out, do, saved, 0, eps=1e-30, flags=1)
+    sv = binding.saved_views(binding.make_desc(q, 0, m, 1e-30, 1e-6, 1), saved)
+    Q, K, V = (x[0, 0].double().requires_grad_() for x in (q, k, v))
+    phi = [torch.relu(x @ omega.double()) / m ** 0.5 for x in (Q, K)]
+    S, z = phi[1].t() @ V, phi[1].sum(0)
+    O = phi[0] @ S / (phi[0] @ z + 1e-30)[:, None]
+    gQ, gK, gV = torch.autograd.grad(O, (Q, K, V), do[0, 0].double())
+
+    def worst(a, r, dim):
+        a, r = a.double(), r.detach()
+        return float(((a - r).norm(dim=dim) / r.norm(dim=dim).clamp_min(1e-300)).max())
+
+    bound = 4 * 2.0 ** -24 * (n + m) ** 0.5
+    errs = dict(S=worst(sv["S"][0], S, 1), S_columns=worst(sv["S"][0], S, 0), z=worst(sv["z"][0][:, None], z[:, None], 1),
+                O=worst(out[0, 0], O, 0), dV=worst(got["dv"][0, 0], gV, 0))
+    print(dtype, d, {k: f"{e:.1e}" for k, e in errs.items()}, f"bound {bound:.1e}", flush=True)
+    for name, e in errs.items():
+        assert e < bound + (2.0 ** -8 if dtype == "bf16" and name in ("O", "dV") else 0), (name, errs)
+    if dtype == "f32":   # (dQ and dK through cancellation: their size, and that nothing overflowed on the way)
+        for a, r in ((got["dq"], gQ), (got["dk"], gK)):
+            assert bool(torch.isfinite(a).all()) and float((a[0, 0].double() - r).norm() / r.norm()) < 1e-4
