@@ -1856,6 +1856,405 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
   }
 }
 
+// ------------------------------------------------------------------------------------
+// The rows kernel of head dimension 128 (modes as above).  A wave owns 32 rows and all 128 columns: X_F and dN or V rows (68
+// registers), the accumulators of the result (64) and of the projection and dPhi (32) fit the 256 registers of two
+// waves per SIMD, so one wave's conversions, masks and LDS latency run under the other's matrix instructions.  Eight waves
+// (256 rows) share the feature-side operands, which pass through LDS in stages of kWideTiles feature tiles, double-buffered,
+// by direct global-to-LDS loads: one barrier per stage, the next stage in flight during it.  A feature tile is
+//   Omega^T rows  [32 features][128] fp16, 256-byte rows: 16-byte piece c of row r at slot c ^ (r % 16);
+//   (M | b) rows  [32][128] bf16 likewise, and the 32 extensions of 32 bytes (gradient modes);
+//   Omega or S^T  [128 columns][32 features] bf16, 64-byte rows: piece c of row r at slot c ^ ((r / 4) % 4).
+// An instruction's row l32 is feature l32 with bits 2 and 3 swapped: the features that accumulator registers 8 a .. 8 a + 7 of
+// half-wave h stand for are then 16 a + 8 h .. + 7, one 16-byte piece of the third array.
+// What bounds it: LDS delivers 1 KiB per matrix instruction and wave (about 145 of the 128 bytes per clock that two waves
+// on each SIMD ask for); the epilogue's 64-row level of the Haar filter, the only one that crosses waves, costs a barrier.
+// Four waves of 64 rows with the whole register file (one per SIMD, 128 staged features, 370 to 400 bytes of scratch per lane)
+// took XXXX
+// ------------------------------------------------------------------------------------
+constexpr int kWideWaves = 8, kWideTiles = 2, kWideRows = 32 * kWideWaves;
+constexpr bool wide_grad(int MODE) { return MODE == 1 || MODE == 2; }
+constexpr int wide_tile_bytes(int MODE) { return wide_grad(MODE) ? 25 * 1024 : 16 * 1024; }
+constexpr int kWidePanel = 32 * 36;   // elements of a wave's tile of 32 rows x 32 columns (or transposed)
+inline size_t wide_smem_bytes(int MODE, int m) {
+  return 2 * kWideTiles * wide_tile_bytes(MODE) + kWideWaves * (kWidePanel * 2 + 32 * 4 + 2 * 128 * 4) + (MODE == 0 ? m * 2 : 0);
+}
+// 16 bytes per lane from base + voff (bytes) to LDS at lds (bytes, wave-uniform) + 16 * lane, without passing through
+// registers.  Written as a statement because the compiler waits for every such load before the next LDS read, whatever it
+// reads; the kernel waits (vmcnt) before its barrier instead.  It has no register outputs.
+__device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t voff, const void *base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base)
+               : "memory", "m0");
+}
+template <int MODE, bool LN, bool RAGGED, bool DEEP>
+__global__ __launch_bounds__(kWideWaves * 64, 2) void wide_rows_kernel(
+    const _Float16 *xf, const bf16_t *x, View vx, const bf16_t *y, View vy, const float *Dsaved, const float *arow,
+    const _Float16 *omT, const bf16_t *omega, const bf16_t *Mx, const bf16_t *MT, const bf16_t *bb, const float *coef, float eps,
+    int n, int m, int row_groups, bf16_t *out, View vo, float *Dout, float *partF, int L, float *tile_gsum) {
+  constexpr int DH = 128, KS = 8, CT = 4, TS = 36;
+  constexpr bool GRAD = wide_grad(MODE);
+  constexpr int TB = wide_tile_bytes(MODE), OM = 8192, OO = GRAD ? 16384 : 8192, OE = 24576;   // a feature tile and its arrays
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  typedef __attribute__((address_space(3))) unsigned char lds_byte;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte *)smem_raw;
+  unsigned char *p = smem_raw + 2 * kWideTiles * TB;
+  float *s_pair = reinterpret_cast<float *>(p);                                  // [waves][2][128]: 32-row sums of dX_F and X
+  float *s_wave = s_pair + kWideWaves * 2 * 128;                                 // [waves][32]
+  bf16_t *s_panel = reinterpret_cast<bf16_t *>(s_wave + kWideWaves * 32);        // [waves][kWidePanel]
+  bf16_t *s_bb = s_panel + kWideWaves * kWidePanel;                              // MODE 0: z
+  const int slice = blockIdx.y, tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const float cscale = coef[slice * kCoefStride + kCoefCscale];
+
+  // ---- staging: wave w moves pieces 4 w .. 4 w + 3 (rows) or 16 w .. 16 w + 15 (columns) of every array
+  const int ra = 4 * wave + (lane >> 4), ca = (lane & 15) ^ (ra & 15), ro = 16 * wave + (lane >> 2), co = (lane & 3) ^ ((ro >> 2) & 3);
+  const uint32_t va = ra * 256 + ca * 16, vm = ra * 288 + ca * 16, vcol = (uint32_t)ro * (uint32_t)(2 * m) + co * 16,
+                 ve = (lane & 31) * 288 + 256 + (lane >> 5) * 16;
+  const bf16_t *mx = GRAD ? Mx + (int64_t)slice * m * (DH + 16) : nullptr;
+  const bf16_t *cols = GRAD ? omega : MT + (int64_t)slice * DH * m;
+  auto request = [&](int buf, int f0) {
+#pragma unroll
+    for (int ft = 0; ft < kWideTiles; ++ft, f0 += 32) {
+      const uint32_t at = lds0 + (uint32_t)((buf * kWideTiles + ft) * TB + wave * 1024);
+      lds_dma16(at, va, omT + (int64_t)f0 * DH);
+      if (GRAD) lds_dma16(at + OM, vm, mx + (int64_t)f0 * (DH + 16));
+      lds_dma16(at + OO, vcol, cols + f0);
+      if (GRAD && wave == ft) lds_dma16(at + OE - wave * 1024, ve, mx + (int64_t)f0 * (DH + 16));
+    }
+  };
+  // (the wait as a builtin: the compiler then knows that the rows' loads have landed, too, and waits for none in the loop)
+  auto landed = [&]() {
+    __builtin_amdgcn_s_waitcnt(0x0070);
+    asm volatile("s_barrier" ::: "memory");
+  };
+
+  float u[kTileBands], cf[kTileBands];   // u_l = sum over blocks of bs_l(g) * bs_l(x), this lane's share
+#pragma unroll
+  for (int l = 0; l < kTileBands; ++l) {
+    u[l] = 0.f;
+    cf[l] = GRAD ? coef[slice * kCoefStride + l] : 0.f;
+  }
+
+  // ---- row-side operands of the wave's 32 rows
+  f16x8 xb[KS];
+  bf16x8 yb[GRAD ? KS + 1 : 1];
+  float dval = 1.f, aval = 1.f;   // D and dD of row l32 (MODE 1)
+  auto load_rows = [&](int t0) {
+    const int valid = RAGGED ? n - t0 : 32;
+    const _Float16 *xs = xf + ((int64_t)slice * n + t0) * DH;
+    if (RAGGED) {
+      const RowBuf xr = row_buffer(xs, DH, valid);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) xb[ks] = buf_load16<f16x8>(xr, (uint32_t)(l32 * DH + 16 * ks + 8 * h) * 2);
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) xb[ks] = *reinterpret_cast<const f16x8 *>(xs + l32 * DH + 16 * ks + 8 * h);
+    }
+    if (GRAD) {
+      const bf16_t *ys = y + vy.slice_base(slice) + (int64_t)t0 * vy.sn;
+      if (RAGGED) {
+        const RowBuf yr = row_buffer(ys, vy.sn, valid);
+        const uint32_t off = l32 * ((uint32_t)vy.sn * 2) + h * 16;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) yb[ks] = buf_load16<bf16x8>(yr, off + 32u * ks);
+        if (MODE == 1) {
+          dval = buf_load4(row_buffer(Dsaved + (int64_t)slice * n + t0, 1, valid), 4 * l32);
+          aval = buf_load4(row_buffer(arow + (int64_t)slice * n + t0, 1, valid), 4 * l32);
+        } else {
+          aval = l32 < valid ? 1.f : 0.f;
+        }
+      } else {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+          yb[ks] = *reinterpret_cast<const bf16x8 *>(ys + (int64_t)l32 * vy.sn + 16 * ks + 8 * h);
+        if (MODE == 1) {
+          dval = Dsaved[(int64_t)slice * n + t0 + l32];
+          aval = arow[(int64_t)slice * n + t0 + l32];
+        }
+      }
+    }
+  };
+  // (with a partial last block both waves of a 64-row block take part: rows past n are zeros)
+  auto in_range = [&](int t0) { return (RAGGED ? t0 & ~63 : t0) < n; };
+
+  const int stages = m / (32 * kWideTiles);
+  int buf = 0;
+  request(0, 0);
+  if (MODE == 0)
+    for (int e = tid; e < m; e += kWideWaves * 64) s_bb[e] = bb[(int64_t)slice * m + e];
+  {
+    const int t_first = blockIdx.x * kWideRows + wave * 32;
+    if ((int)blockIdx.x < row_groups && in_range(t_first)) load_rows(t_first);
+  }
+  const int prow = (l32 & ~12) | (l32 & 4) << 1 | (l32 & 8) >> 1;
+  const int o_row = prow * 256 + ((h ^ (prow & 15)) << 4), o_ext = (h * 32 + prow) * 16;
+  const int o_col0 = l32 * 64 + ((h ^ ((l32 >> 2) & 3)) << 4), i16 = lane & 15, g16 = lane >> 4;
+  bf16_t *tl = s_panel + wave * kWidePanel;
+  float *sw = s_wave + wave * 32, *mine = s_pair + wave * 256, *other = s_pair + (wave ^ 1) * 256;
+
+  for (int rg = blockIdx.x; rg < row_groups; rg += gridDim.x) {
+    const int t0 = rg * kWideRows + wave * 32;
+    const bool active = in_range(t0);
+    const int valid = RAGGED ? n - t0 : 32;
+    if (GRAD && active) {   // the rank-one extension (a_t, 0, ...); MODE 1 works with the raw dO rows: G' = D_t G
+      bf16x8 ext = splat_bf16x8(0.f);
+      if (h == 0) ext[0] = (__bf16)(MODE == 1 ? aval * dval : aval);
+      yb[GRAD ? KS : 0] = ext;
+      // row scale c / D_t (rows past n: D reads as 0 there, and their scale must be finite for the sums over the block)
+      if (MODE == 1 && h == 0) sw[l32] = (RAGGED && l32 >= valid) ? 0.f : cscale * __builtin_amdgcn_rcpf(dval);
+    }
+    f32x16 acc[CT];
+    float dacc = 0.f;
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) acc[ct] = zero16();
+    for (int s = 0; s < stages; ++s, buf ^= 1) {
+      landed();   // stage s is there; every wave is done with the one before it, which is overwritten now
+      request(buf ^ 1, s + 1 < stages ? (s + 1) * 32 * kWideTiles : 0);   // (the last: for the next row group)
+      if (!active) continue;
+#pragma unroll
+      for (int ft = 0; ft < kWideTiles; ++ft) {
+        const unsigned char *st = smem_raw + (buf * kWideTiles + ft) * TB;
+        f32x16 R = zero16(), G = zero16();
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          R = mfma_f16(*reinterpret_cast<const f16x8 *>(st + (o_row ^ (32 * ks))), xb[ks], R);
+          if (GRAD) G = mfma_bf16(*reinterpret_cast<const bf16x8 *>(st + OM + (o_row ^ (32 * ks))), yb[GRAD ? ks : 0], G);
+        }
+        if (GRAD) {
+          G = mfma_bf16(*reinterpret_cast<const bf16x8 *>(st + OE + o_ext), yb[GRAD ? KS : 0], G);
+          // 1[R > 0] as a multiplier: clamp(R * 2^100, 0, 1) is 1 for every R > 2^-100 and 0 for R <= 0
+#pragma unroll
+          for (int i = 0; i < 16; ++i) G[i] *= __builtin_amdgcn_fmed3f(R[i] * 0x1p+100f, 0.f, 1.f);
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          const bf16x8 pa = GRAD ? pack_half(G, a) : relu_bf16x8(pack_half(R, a));
+          if (MODE == 0)
+            dacc = dot8_bf16(pa, *reinterpret_cast<const bf16x8 *>(s_bb + (s * kWideTiles + ft) * 32 + 16 * a + 8 * h), dacc);
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct)
+            acc[ct] = mfma_bf16(pa, *reinterpret_cast<const bf16x8 *>(st + OO + ct * 2048 + (o_col0 ^ (32 * a))), acc[ct]);
+        }
+      }
+      // operand reads kAhead matrix instructions before their use (left alone, the compiler reads one and waits for it)
+      constexpr int kAhead = 6, MF = kWideTiles * (GRAD ? 25 : 16);
+      __builtin_amdgcn_sched_group_barrier(0x100, kAhead, 0);
+#pragma unroll
+      for (int i = 0; i < MF - kAhead; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, kAhead, 0);
+    }
+
+    // ---- epilogues
+    const int t_next = t0 + (int)gridDim.x * kWideRows;
+    bf16_t *os = out + vo.slice_base(slice) + (int64_t)t0 * vo.sn;
+    RowBuf osb;
+    if (RAGGED) osb = row_buffer(os, vo.sn, valid);
+    if (active) {
+      if (MODE == 0 && LN) {   // O_t = (N_t - mean N_t) / sqrt(var N_t + eps), N = c * acc; 1 / sqrt(var + eps) goes to D
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const float mu = half_wave_sum((acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i])) * (1.0f / (float)DH);
+          float q = 0.f;
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) {
+            const float e = (acc[ct][i] - mu) * cscale;
+            acc[ct][i] = e;
+            q = fmaf(e, e, q);
+          }
+          const float rstd = 1.0f / sqrtf(half_wave_sum(q) * (1.0f / (float)DH) + eps);
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) acc[ct][i] *= rstd;
+          if (l32 == 0) sw[acc_row(i, h)] = rstd;
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (l32 < valid) Dout[(int64_t)slice * n + t0 + l32] = sw[l32];
+      } else if (MODE == 0) {   // D_t = c * sum_r relu(R) z + eps, row scale c / D_t
+        const float Dt = fmaf(cscale, xor32_sum(dacc), eps);
+        sw[l32] = cscale * __builtin_amdgcn_rcpf(Dt);   // (both half-waves hold and write the same)
+        if (l32 < valid) Dout[(int64_t)slice * n + t0 + l32] = Dt;
+      }
+      __builtin_amdgcn_wave_barrier();
+      if (!(MODE == 0 && LN)) {
+        float sc[16];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          f32x4 s4 = {cscale, cscale, cscale, cscale};
+          if (MODE <= 1) s4 = *reinterpret_cast<const f32x4 *>(&sw[8 * g + 4 * h]);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) sc[4 * g + q] = s4[q];
+        }
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) acc[ct][i] *= sc[i];
+      }
+    }
+    if (!GRAD) {   // bf16 through the wave's tile, 8-byte row-major stores
+      if (active) {
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+          __builtin_amdgcn_wave_barrier();
+#pragma unroll
+          for (int i = 0; i < 16; ++i) tl[acc_row(i, h) * TS + l32] = cvt_bf16(acc[ct][i]);
+          __builtin_amdgcn_wave_barrier();
+          bf16x4 piece[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) piece[j] = *reinterpret_cast<const bf16x4 *>(&tl[((lane >> 3) + 8 * j) * TS + (lane & 7) * 4]);
+          if (RAGGED) {
+            uint32_t off = (lane >> 3) * ((uint32_t)vo.sn * 2) + (32 * ct + (lane & 7) * 4) * 2;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              buf_store8(osb, off, piece[j]);
+              off += 16 * (uint32_t)vo.sn;
+            }
+          } else {
+            bf16_t *orow = os + (int64_t)(lane >> 3) * vo.sn + 32 * ct + (lane & 7) * 4;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              *reinterpret_cast<bf16x4 *>(orow) = piece[j];
+              orow += 8 * vo.sn;
+            }
+          }
+        }
+      }
+      if (rg + (int)gridDim.x < row_groups && in_range(t_next)) load_rows(t_next);
+      continue;
+    }
+    // Gradient modes: gated Haar filter of dX_F on the accumulator layout and band inner products.  Lane (l32, h) holds
+    // column 32 ct + l32 and rows 8 g + 4 h + e: block sums of 2 and 4 rows are in-lane, 8 rows need the other half-wave, 16 and
+    // 32 are in-lane again, 64 rows the other wave of the pair.
+    const bf16_t *xsrc = x + vx.slice_base(slice) + (int64_t)t0 * vx.sn;
+    if (active) {
+      bf16x4 xp[2][4];   // X of a column tile in 8-byte row-major pieces, and of the next
+      auto load_x = [&](int ct) {
+        if (RAGGED) {
+          const RowBuf xr = row_buffer(xsrc, vx.sn, valid);
+          uint32_t off = (lane >> 3) * ((uint32_t)vx.sn * 2) + (32 * ct + (lane & 7) * 4) * 2;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            xp[ct & 1][j] = buf_load8<bf16x4>(xr, off);
+            off += 16 * (uint32_t)vx.sn;
+          }
+        } else {
+          const bf16_t *xrow = xsrc + (int64_t)(lane >> 3) * vx.sn + 32 * ct + (lane & 7) * 4;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            xp[ct & 1][j] = *reinterpret_cast<const bf16x4 *>(xrow);
+            xrow += 8 * vx.sn;
+          }
+        }
+      };
+      load_x(0);
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        if (ct + 1 < CT) load_x(ct + 1);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) *reinterpret_cast<bf16x4 *>(&tl[((lane >> 3) + 8 * j) * TS + (lane & 7) * 4]) = xp[ct & 1][j];
+        __builtin_amdgcn_wave_barrier();
+        float g1[8], x1[8];
+        bf16x4 xq[4];   // X at this lane's accumulator positions: rows 8 g + 4 h + e of column l32
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          xq[g] = lds_read_tr4(&tl[(8 * g + 4 * h + (i16 >> 2)) * TS + 16 * (g16 & 1) + 4 * (i16 & 3)]);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const float ga = acc[ct][2 * k], gb = acc[ct][2 * k + 1];
+          const float xa = (float)xq[k >> 1][2 * (k & 1)], xb2 = (float)xq[k >> 1][2 * (k & 1) + 1];
+          u[0] = fmaf(ga, xa, fmaf(gb, xb2, u[0]));
+          g1[k] = ga + gb;
+          x1[k] = xa + xb2;
+          u[1] = fmaf(g1[k], x1[k], u[1]);
+        }
+        float g3[4], x3[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float g2 = g1[2 * k] + g1[2 * k + 1], x2 = x1[2 * k] + x1[2 * k + 1];
+          u[2] = fmaf(g2, x2, u[2]);
+          g3[k] = xor32_sum(g2);   // 8-row blocks: both half-waves hold the same sums
+          x3[k] = xor32_sum(x2);
+          u[3] = fmaf(0.5f * g3[k], x3[k], u[3]);
+        }
+        const float g4a = g3[0] + g3[1], g4b = g3[2] + g3[3], x4a = x3[0] + x3[1], x4b = x3[2] + x3[3];
+        u[4] = fmaf(0.5f * g4a, x4a, fmaf(0.5f * g4b, x4b, u[4]));
+        const float g5 = g4a + g4b, x5 = x4a + x4b;
+        u[5] = fmaf(0.5f * g5, x5, u[5]);
+        mine[32 * ct + l32] = g5;   // (both half-waves write the same)
+        mine[128 + 32 * ct + l32] = x5;
+      }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // (the loads of the next stage stay in flight)
+    if (active) {
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        const float g5 = mine[32 * ct + l32], o5 = other[32 * ct + l32];
+        const float g6 = g5 + o5;
+        if ((wave & 1) == 0) {
+          u[6] = fmaf(0.5f * g6, mine[128 + 32 * ct + l32] + other[128 + 32 * ct + l32], u[6]);
+          if (DEEP) tile_gsum[((int64_t)slice * ((n + 63) / 64) + t0 / 64) * DH + 32 * ct + l32] = g6;
+        }
+        const float T5 = fmaf(cf[5], g5, cf[6] * g6);
+        float g1[8], g2[4], g3[4];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) g1[k] = acc[ct][2 * k] + acc[ct][2 * k + 1];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          g2[k] = g1[2 * k] + g1[2 * k + 1];
+          g3[k] = xor32_sum(g2[k]);
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {   // 8-row block k (and this lane's 4-row part of it): one 8-byte column piece
+          const float T4 = fmaf(cf[4], g3[k & ~1] + g3[k | 1], T5), T2 = fmaf(cf[2], g2[k], fmaf(cf[3], g3[k], T4));
+          bf16x4 pk;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) pk[e] = (__bf16)fmaf(cf[0], acc[ct][4 * k + e], fmaf(cf[1], g1[2 * k + (e >> 1)], T2));
+          *reinterpret_cast<bf16x4 *>(&tl[l32 * TS + 8 * k + 4 * h]) = pk;   // the tile transposed: [column][row]
+        }
+        __builtin_amdgcn_wave_barrier();
+        // transposing reads hand back 8-byte row-major pieces: rows 16 (v % 2) + i16, columns 16 (v / 2) + 4 g16 .. + 3
+        bf16x4 piece[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          piece[v] = lds_read_tr4(&tl[(16 * (v >> 1) + 4 * g16 + (i16 >> 2)) * TS + 16 * (v & 1) + 4 * (i16 & 3)]);
+        if (RAGGED) {
+          const uint32_t off = i16 * ((uint32_t)vo.sn * 2) + (32 * ct + 4 * g16) * 2;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) buf_store8(osb, off + (v & 1) * 32 * (uint32_t)vo.sn + (v >> 1) * 32, piece[v]);
+        } else {
+          bf16_t *drow = os + (int64_t)i16 * vo.sn + 32 * ct + 4 * g16;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) *reinterpret_cast<bf16x4 *>(drow + (v & 1) * 16 * vo.sn + (v >> 1) * 16) = piece[v];
+        }
+      }
+    }
+    if (rg + (int)gridDim.x < row_groups && in_range(t_next)) load_rows(t_next);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the last request: nothing reads it, but it must not outlive the workgroup
+  if (!GRAD) return;
+  // With u_l = <dX_F, P_l X> the band gradients are dF_L = u_L and dF_{l-1} = u_{l-1} - u_l (l = 1..L).
+  __syncthreads();
+#pragma unroll
+  for (int l = 0; l < kTileBands; ++l) {
+    const float s = wave_sum64(u[l]) / (float)(1 << l);
+    if (lane == 0) sw[l] = s;
+  }
+  __syncthreads();
+  if (tid <= L) {   // DEEP: see rows_kernel
+    float ul = 0.f, ul1 = 0.f;
+    if (tid < kTileBands)
+      for (int wv = 0; wv < kWideWaves; ++wv) {
+        ul += s_wave[wv * 32 + tid];
+        if (tid < L && tid + 1 < kTileBands) ul1 += s_wave[wv * 32 + tid + 1];
+      }
+    const int rows = DEEP ? gridDim.x + DH / 16 : gridDim.x;
+    partF[((int64_t)slice * rows + blockIdx.x) * (L + 1) + tid] = tid < L ? ul - ul1 : ul;
+  }
+}
+
 // dX[t][:] += dqbar / n (the pooled-query path; dqbar may be nullptr) + tile_add[t / 64][:] (the
 // part of the gated filter above level 6; may be nullptr), bf16 read-modify-write with 16-byte
 // accesses, four independent pieces per thread.
@@ -2191,12 +2590,42 @@ inline bool dv_rides_along(const wersa_desc &c, const FastPlan &p) {
   return c.d == 64 && p.mc == 256;
 }
 
+// Head dimension 128.
+template <int MODE>
+hipError_t launch_wide_rows(const wersa_desc &c, const FastPlan &p, const _Float16 *xf, const bf16_t *x, const bf16_t *y,
+                            const float *Dsaved, const float *arow, const FastWs &w, const bf16_t *omega, const bf16_t *Mx,
+                            const bf16_t *MT, const bf16_t *bb, bf16_t *out0, float *Dout, float *partF, hipStream_t st,
+                            const View *yview) {
+  const int64_t side = ((c.flags & WERSA_FLAG_SEPARATE_OMEGA) && MODE >= 2) ? (int64_t)c.d * c.m : 0;
+  const View tv{c.stride_b, c.stride_h, c.stride_n, c.H};
+  const size_t smem = wide_smem_bytes(MODE, c.m);
+  const char *name = MODE == 0 ? "wersa_rows_fwd"
+                               : (MODE == 1 ? "wersa_rows_bwd_q" : (MODE == 2 ? "wersa_rows_bwd_k" : "wersa_rows_bwd_v"));
+  auto go = [&](auto kern) -> hipError_t {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
+    WERSA_STAGE(name, st,
+                kern<<<dim3(p.rowsWgsG, c.B * c.H), kWideWaves * 64, smem, st>>>(
+                    xf, x, tv, y, yview ? *yview : tv, Dsaved, arow, w.omT + side, omega + side, Mx, MT, bb, w.coef, c.eps, c.n, c.m,
+                    p.rowGroupsG, out0, tv, Dout, partF, c.L, MODE == 1 ? w.gsumQ : w.gsumK));
+    return hipSuccess;
+  };
+  constexpr bool G = wide_grad(MODE);
+  const bool ln = MODE == 0 && (c.flags & WERSA_FLAG_LAYERNORM), ragged = c.n % 64 != 0, deep = G && c.L > kTileL;
+  if (ln) return ragged ? go(&wide_rows_kernel<MODE, MODE == 0, true, false>) : go(&wide_rows_kernel<MODE, MODE == 0, false, false>);
+  if (deep) return ragged ? go(&wide_rows_kernel<MODE, false, true, G>) : go(&wide_rows_kernel<MODE, false, false, G>);
+  return ragged ? go(&wide_rows_kernel<MODE, false, true, false>) : go(&wide_rows_kernel<MODE, false, false, false>);
+}
+
 template <int DH, int MODE>
 hipError_t launch_rows(const wersa_desc &c, const FastPlan &p, const _Float16 *xf, const bf16_t *x,
                        const bf16_t *y, const float *Dsaved, const float *arow, const FastWs &w,
                        const bf16_t *omega, const bf16_t *Mx, const bf16_t *MT, const bf16_t *bb,
                        bf16_t *out0, float *Dout, float *partF, hipStream_t st,
                        const View *yview = nullptr, bf16_t *out1 = nullptr) {
+  if constexpr (DH == 128)
+    return launch_wide_rows<MODE>(c, p, xf, x, y, Dsaved, arow, w, omega, Mx, MT, bb, out0, Dout, partF, st, yview);
+  else {
   constexpr bool IS_GRAD = (MODE == 1 || MODE == 2);
   constexpr int NW = IS_GRAD ? kWavesGrad : waves_apply(DH);
   // key-side modes take the second random matrix when the descriptor has two
@@ -2261,6 +2690,7 @@ hipError_t launch_rows(const wersa_desc &c, const FastPlan &p, const _Float16 *x
                              : go(&rows_kernel<DH, MODE, NW, 128, MODE == 0, false, false>);
   return mcs == 256 ? go(&rows_kernel<DH, MODE, NW, MCH, false, false, false>)
                      : go(&rows_kernel<DH, MODE, NW, 128, false, false, false>);
+  }
 }
 
 // orows != nullptr selects the backward form that derives dD from the rows of O itself;
