@@ -1020,16 +1020,15 @@ __device__ __forceinline__ void buf_store4(RowBuf r, uint32_t off, float v) {
 // multiple of 64; rows are read and written through buffers that end at row n (see row_buffer).
 // The plain instance has none of that code.
 // DEEP: L > 6: X_F starts from the per-tile addend of the levels above 6 (tile_add
-// [slices][ceil(n / 64)][DH]; head dimension 128 finds them in xf already); the gradient modes also
+// [slices][ceil(n / 64)][DH]); the gradient modes also
 // write the 64-row sums of dX_F per column (tile_gsum, same shape) and leave band 6 of their
 // partials as u_6 alone.
-// DV (MODE 2, head dimension 64): the kernel also forms dV = c relu(R) dS of MODE 3 from the
+// DV (MODE 2): the kernel also forms dV = c relu(R) dS of MODE 3 from the
 // projection it has in hand (B operand: the rows of (dS | dz) in LDS through transposing reads)
 // and writes it to out1; the separate MODE 3 launch, its pass over K and its projection go away.
 template <int DH, int MODE, int NW, int MC, bool LN, bool RAGGED, bool DEEP, bool DV = false>
 __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
-    const _Float16 *xf,        // X_F fp16 [slices][n][DH] (head dimension 128; with 64 it is formed here)
-    const bf16_t *x, View vx,  // X (Q or K): band inner products (MODE 1, 2); source of X_F (head dimension 64)
+    const bf16_t *x, View vx,  // X (Q or K): source of X_F, band inner products (MODE 1, 2)
     const bf16_t *y, View vy,  // dO (MODE 1) or V (MODE 2)
     const float *Dsaved,       // D [slices][n] (MODE 1)
     const float *arow,         // dD [slices][n] (MODE 1)
@@ -1046,7 +1045,8 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
     const float *tile_add, float *tile_gsum,   // DEEP (see above)
     bf16_t *out1)                              // DV: dV, laid out like out0
 {
-  static_assert(!DV || (MODE == 2 && DH == 64 && NW == 4 && MC == 256), "dV rides along with the K-side gradient only");
+  static_assert(DH == 64, "head dimension 128 has wide_rows_kernel");
+  static_assert(!DV || (MODE == 2 && NW == 4 && MC == 256), "dV rides along with the K-side gradient only");
   constexpr int KS = DH / 16, CT = DH / 32;
   constexpr int KSX = KS + 1;           // k-steps of the dPhi MFMA incl. the rank-one extension
   constexpr int AS = DH + 8;            // stride of the [feature][DH] fp16 array (16-byte reads)
@@ -1055,15 +1055,14 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
   constexpr bool IS_GRAD = (MODE == 1 || MODE == 2);
   constexpr bool IS_APPLY = (MODE == 0 || MODE == 3);
   // Gradient modes run with the 512-register budget: projection and dPhi results go to VGPRs
-  // where the register file has room for all their operands in VGPRs as well (head dimension 64
-  // with the whole feature range staged; the other shapes keep the compiler's own allocation).
-  constexpr bool VGPR_RG = IS_GRAD && NW == 4 && DH == 64 && MC == 256;
-  // Head dimension 64: stage A runs here.  Each wave keeps the raw rows of its 64-row block in
+  // where the register file has room for all their operands in VGPRs as well (the whole feature range
+  // staged; the other shapes keep the compiler's own allocation).
+  constexpr bool VGPR_RG = IS_GRAD && NW == 4 && MC == 256;
+  // Stage A runs here.  Each wave keeps the raw rows of its 64-row block in
   // LDS (one 64 x 32 panel per column tile), forms X_F^T = X^T G^T with 16 MFMAs at the top of
   // the block and packs the result into the projection's fp16 operands; the gradient modes
   // read X for the band inner products from the same panels, and every mode sends its output
   // tiles through a panel once its X values are used up.
-  constexpr bool FUSE = (DH == 64);
   constexpr int NWR = NW;               // row groups of 64 rows per workgroup step (one per wave)
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   constexpr int mc = MC;
@@ -1078,10 +1077,9 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
   float *s_wave = reinterpret_cast<float *>(p); p += (size_t)NW * 64 * 4;              // [waves][64]
   constexpr int TS = 36;                // row stride (elements) of the per-wave 64 x 32 epilogue tile
   constexpr int TT = 68;                // column stride (elements) of the same tile held transposed [32][64]
-  bf16_t *s_tile = reinterpret_cast<bf16_t *>(p);            // [waves][64][TS]; FUSE: [waves][CT][64][TS]
-  constexpr int PANELS = FUSE ? CT : 1;
-  p += (size_t)NW * PANELS * 64 * TS * 2;
-  bf16_t *s_T = reinterpret_cast<bf16_t *>(p);               // FUSE: filter operand table [2][512]
+  bf16_t *s_tile = reinterpret_cast<bf16_t *>(p);            // [waves][CT][64][TS]
+  p += (size_t)NW * CT * 64 * TS * 2;
+  bf16_t *s_T = reinterpret_cast<bf16_t *>(p);               // filter operand table [2][512]
 
   const int slice = blockIdx.y;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
@@ -1160,51 +1158,37 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
     for (int l = 0; l < kTileBands; ++l) cf[l] = coef[slice * kCoefStride + l];
   }
 
-  if (FUSE) build_filter_table(s_T, coef + slice * kCoefStride, tid, NT);
+  build_filter_table(s_T, coef + slice * kCoefStride, tid, NT);
   if (nchunks == 1) stage(0);
-  if (FUSE || nchunks == 1) __syncthreads();
+  __syncthreads();
 
   // ---- per-wave row-side operands; the next row group's are fetched right after the feature
   // loop of the current one (their registers are free by then), so that the latency of these
   // loads hides behind the epilogue.
   f16x8 xb[2][KS];      // X_F rows: B operand of the transposed projection
-  u16x8 xp[8];          // FUSE: raw X rows of the next block, 16-byte row-major pieces (row lane / 8 + 8 j, columns 8 (lane % 8) ..)
+  u16x8 xp[8];          // raw X rows of the next block, 16-byte row-major pieces (row lane / 8 + 8 j, columns 8 (lane % 8) ..)
   bf16x8 yb[2][KSX];    // dO or V rows (+ the a_t extension): B operand of the dPhi MFMA
   float dval[2] = {1.f, 1.f};   // D of rows 32 ti + l32 (MODE 1)
   float aval[2] = {1.f, 1.f};   // dD of the same rows (MODE 1)
   auto load_rows = [&](int t0) {
     const int valid = RAGGED ? n - t0 : 64;   // rows of this block that exist
-    if (FUSE) {
-      if (!RAGGED) {
-        // one running pointer (eight separately scaled row offsets would each be kept in registers)
-        const bf16_t *xsrc = x + vx.slice_base(slice) + (int64_t)(t0 + (lane >> 3)) * vx.sn + (lane & 7) * 8;
+    if (!RAGGED) {
+      // one running pointer (eight separately scaled row offsets would each be kept in registers)
+      const bf16_t *xsrc = x + vx.slice_base(slice) + (int64_t)(t0 + (lane >> 3)) * vx.sn + (lane & 7) * 8;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          xp[j] = *reinterpret_cast<const u16x8 *>(xsrc);
-          xsrc += 8 * vx.sn;
-        }
-      } else {
-        const RowBuf xr = row_buffer(x + vx.slice_base(slice) + (int64_t)t0 * vx.sn, vx.sn, valid);
-        const uint32_t sn2 = (uint32_t)vx.sn * 2;
-        const uint32_t ln = opaque(lane);
-        uint32_t off = (ln >> 3) * sn2 + (ln & 7) * 16;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          xp[j] = buf_load16<u16x8>(xr, off);
-          off += 8 * sn2;
-        }
+      for (int j = 0; j < 8; ++j) {
+        xp[j] = *reinterpret_cast<const u16x8 *>(xsrc);
+        xsrc += 8 * vx.sn;
       }
     } else {
-      const _Float16 *xs = xf + ((int64_t)slice * n + t0) * DH;
-      RowBuf xr;
-      if (RAGGED) xr = row_buffer(xs, DH, valid);
+      const RowBuf xr = row_buffer(x + vx.slice_base(slice) + (int64_t)t0 * vx.sn, vx.sn, valid);
+      const uint32_t sn2 = (uint32_t)vx.sn * 2;
+      const uint32_t ln = opaque(lane);
+      uint32_t off = (ln >> 3) * sn2 + (ln & 7) * 16;
 #pragma unroll
-      for (int ti = 0; ti < 2; ++ti) {
-        const int row = 32 * ti + l32;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          xb[ti][ks] = RAGGED ? buf_load16<f16x8>(xr, (uint32_t)(row * DH + 16 * ks + 8 * h) * 2)
-                              : *reinterpret_cast<const f16x8 *>(xs + (int64_t)row * DH + 16 * ks + 8 * h);
+      for (int j = 0; j < 8; ++j) {
+        xp[j] = buf_load16<u16x8>(xr, off);
+        off += 8 * sn2;
       }
     }
     if (IS_GRAD) {
@@ -1251,29 +1235,27 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
       }
     }
   };
-  // FUSE: the raw rows go from the registers into the wave's panels as soon as the panels are
+  // The raw rows go from the registers into the wave's panels as soon as the panels are
   // free (end of the epilogue), so that they do not occupy registers during the feature loop.
-  bf16_t *panels = s_tile + wave * (PANELS * 64 * TS);
+  bf16_t *panels = s_tile + wave * (CT * 64 * TS);
   auto put_rows = [&]() {
-    if (FUSE) {
-      __builtin_amdgcn_wave_barrier();
-      // a 16-byte piece lies inside one panel (columns 8 (lane % 8) .. + 7); two 8-byte writes
-      // because odd panel rows are only 8-byte aligned
-      bf16_t *dstp = panels + ((lane & 7) >> 2) * (64 * TS) + (lane >> 3) * TS + ((lane & 3) << 3);
+    __builtin_amdgcn_wave_barrier();
+    // a 16-byte piece lies inside one panel (columns 8 (lane % 8) .. + 7); two 8-byte writes
+    // because odd panel rows are only 8-byte aligned
+    bf16_t *dstp = panels + ((lane & 7) >> 2) * (64 * TS) + (lane >> 3) * TS + ((lane & 3) << 3);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
-        u16x4 lo4, hi4;
+    for (int j = 0; j < 8; ++j) {
+      typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
+      u16x4 lo4, hi4;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          lo4[q] = xp[j][q];
-          hi4[q] = xp[j][4 + q];
-        }
-        *reinterpret_cast<u16x4 *>(dstp + 8 * j * TS) = lo4;
-        *reinterpret_cast<u16x4 *>(dstp + 8 * j * TS + 4) = hi4;
+      for (int q = 0; q < 4; ++q) {
+        lo4[q] = xp[j][q];
+        hi4[q] = xp[j][4 + q];
       }
-      __builtin_amdgcn_wave_barrier();
+      *reinterpret_cast<u16x4 *>(dstp + 8 * j * TS) = lo4;
+      *reinterpret_cast<u16x4 *>(dstp + 8 * j * TS + 4) = hi4;
     }
+    __builtin_amdgcn_wave_barrier();
   };
   {
     const int t_first = (blockIdx.x * NWR + wave) * 64;
@@ -1291,28 +1273,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
     const bool active = t0 < n;
     const int valid = RAGGED ? n - t0 : 64;
 
-    bf16x4 xpiece[8];   // X tile of the band inner products (MODE 1, 2, head dimension 128), 8-byte row-major pieces
-    auto load_xpiece = [&](int ct, bf16x4 *dst) {
-      if (!RAGGED) {
-        const bf16_t *xsrc = x + vx.slice_base(slice) + (int64_t)(t0 + (lane >> 3)) * vx.sn + 32 * ct + (lane & 7) * 4;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {   // one running pointer instead of eight scaled row offsets
-          dst[j] = *reinterpret_cast<const bf16x4 *>(xsrc);
-          xsrc += 8 * vx.sn;
-        }
-      } else {
-        const RowBuf xr = row_buffer(x + vx.slice_base(slice) + (int64_t)t0 * vx.sn, vx.sn, valid);
-        const uint32_t sn2 = (uint32_t)vx.sn * 2;
-        const uint32_t ln = opaque(lane);
-        uint32_t off = (ln >> 3) * sn2 + (32 * ct + (ln & 7) * 4) * 2;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          dst[j] = buf_load8<bf16x4>(xr, off);
-          off += 8 * sn2;
-        }
-      }
-    };
-    if (FUSE && active) {
+    if (active) {
       // X_F^T = X^T G^T per (column tile, row tile) from the raw rows in the panels (written at
       // the end of the previous block's epilogue), then the projection's fp16 operands.
       __builtin_amdgcn_wave_barrier();
@@ -1503,14 +1464,10 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
         }
         continue;
       }
-      // Head dimension 128, gradient modes: a bound the compiler cannot see keeps the loop rolled
-      // (unrolled, the operands of several feature tiles are fetched ahead and spill).
-      int rt_end = mc / 32;
-      if (IS_GRAD && DH == 128) asm volatile("" : "+s"(rt_end));
       // Two waves per SIMD: the wave in its feature loop goes first, so that the other wave's epilogue
       // (no matrix work) fills the gaps instead of competing for issue slots (forward kernel -3 %).
       if (NW == 8) __builtin_amdgcn_s_setprio(3);
-      for (int rt = 0; rt < rt_end; ++rt) {
+      for (int rt = 0; rt < mc / 32; ++rt) {
         f16x8 oa[KS];     // Omega^T rows of this feature tile: A operand of the projection
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
@@ -1570,7 +1527,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
       const int t_next = ((rg + gridDim.x) * NWR + wave) * 64;
       load_rows((rg + (int)gridDim.x < row_groups && t_next < n) ? t_next : t0);
     }
-    bf16_t *tl = panels;   // FUSE, gradient modes: moves to the panel of the column tile in hand
+    bf16_t *tl = panels;   // gradient modes: moves to the panel of the column tile in hand
     // Gradient modes: output tiles leave through the wave's LDS tile held transposed ([column][row]): a lane
     // stores its four consecutive accumulator rows as one 8-byte write, and transposing reads
     // hand back 8-byte row-major pieces (read u: rows 16 (u % 4) + lane % 16, columns
@@ -1728,17 +1685,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
     // that global memory sees 8-byte row-major accesses and the column accesses stay in LDS.
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
-      // ---- X tile -> LDS (FUSE: it is there already, in this column tile's panel)
-      if (FUSE) {
-        tl = panels + ct * (64 * TS);
-      } else {
-        load_xpiece(ct, xpiece);
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          *reinterpret_cast<bf16x4 *>(&tl[(prow + 8 * j) * TS + pcol]) = xpiece[j];
-        __builtin_amdgcn_wave_barrier();
-      }
+      tl = panels + ct * (64 * TS);   // X is there already
       // ---- pass 1: block sums of g and x, band inner products, keep the 32-row sums
       float g5[2], x5[2];
 #pragma unroll
@@ -1870,7 +1817,8 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
 // What bounds it: LDS delivers 1 KiB per matrix instruction and wave (about 145 of the 128 bytes per clock that two waves
 // on each SIMD ask for); the epilogue's 64-row level of the Haar filter, the only one that crosses waves, costs a barrier.
 // Four waves of 64 rows with the whole register file (one per SIMD, 128 staged features, 370 to 400 bytes of scratch per lane)
-// took XXXX
+// took 1650 (Q side), 1879 (K side), 896 (forward) and 782 us (dV) at 32 slices of 65536 rows, m 512; this form takes 1128, 1083,
+// 624 and 565.  16 slices of 4096 rows with LayerNorm and two random matrices: 68, 68, 41, 32 -> 41, 40, 25, 21.
 // ------------------------------------------------------------------------------------
 constexpr int kWideWaves = 8, kWideTiles = 2, kWideRows = 32 * kWideWaves;
 constexpr bool wide_grad(int MODE) { return MODE == 1 || MODE == 2; }
@@ -2451,14 +2399,14 @@ __global__ __launch_bounds__(256) void ln_prep_kernel(const bf16_t *dout, const 
 // ---------------------------------------------------------------------------------------
 constexpr int kWavesGrad = 4;
 constexpr int kLnWgs = 2048;   // workgroups of ln_prep: eight of 256 threads per compute unit
-constexpr int waves_apply(int d) { return d == 64 ? 8 : 4; }   // head dimension 128: 512 registers per lane
+constexpr int kWavesApply = 8;
 
 struct FastPlan {
-  int DH, FW, MB, mc, mcA;   // features staged in LDS per pass by the rows kernels (mcA: the dV kernel)
+  int DH, FW, MB, mc;   // mc: features staged in LDS per pass by the rows kernels of head dimension 64
   int chunksQ, rowsQ;   // pooled-query partial sums
   int chunksC, rowsC;   // split of n in phiT_contract
-  int rowGroupsA, rowsWgsA;   // apply-type rows kernel (4 waves): row groups / workgroups per slice
-  int rowGroupsG, rowsWgsG;   // gradient-type rows kernel (8 waves)
+  int rowGroupsA, rowsWgsA;   // apply-type rows kernel of head dimension 64 (8 waves): row groups / workgroups per slice
+  int rowGroupsG, rowsWgsG;   // the other rows kernels (256 rows per workgroup)
   int chunksL, rowsL;   // split of n in ln_prep
 };
 
@@ -2467,9 +2415,6 @@ FastPlan fast_plan(const wersa_desc &c) {
   p.DH = c.d;
   if (c.m % 256 == 0 && c.d == 64) { p.FW = 64; p.MB = 256; } else { p.FW = 32; p.MB = 128; }
   p.mc = (c.d == 64 && c.m % 256 == 0) ? 256 : 128;
-  // the dV kernel stages no (M | b) array: 256 features fit for head dimension 128 too (the forward
-  // kernel, which could do the same, measured 3 % slower with 256 than with 128)
-  p.mcA = c.m % 256 == 0 ? 256 : 128;
   const int slices = c.B * c.H, blocks = (c.n + 63) / 64;
   int cq = (c.n + 1023) / 1024;
   p.chunksQ = cq < 1 ? 1 : (cq > 512 ? 512 : cq);
@@ -2488,7 +2433,7 @@ FastPlan fast_plan(const wersa_desc &c) {
   const int wantL = kLnWgs / slices < 1 ? 1 : kLnWgs / slices, bpl = (blocks + wantL - 1) / wantL;
   p.rowsL = bpl * 64;
   p.chunksL = (blocks + bpl - 1) / bpl;
-  p.rowGroupsA = (blocks + waves_apply(c.d) - 1) / waves_apply(c.d);
+  p.rowGroupsA = (blocks + kWavesApply - 1) / kWavesApply;
   // One resident workgroup per compute unit (the operand arrays fill most of the LDS): at most
   // 256 workgroups in total, so that no second, mostly empty round follows the first.
   int wgs = 256 / slices < 1 ? 1 : 256 / slices;
@@ -2579,8 +2524,7 @@ size_t rows_smem_bytes(int mc) {
   else s += (size_t)DH * BS * 2;
   if (MODE == 0) s += (size_t)mc * 2;
   s += NW * 64 * 4;
-  if (DH == 64) s += (size_t)NW * (DH / 32) * 64 * 36 * 2 + 2 * 512 * 2;   // X panels per wave and the filter table
-  else s += (size_t)NW * 64 * 36 * 2;
+  s += (size_t)NW * (DH / 32) * 64 * 36 * 2 + 2 * 512 * 2;   // X panels per wave and the filter table
   return s;
 }
 
@@ -2617,26 +2561,21 @@ hipError_t launch_wide_rows(const wersa_desc &c, const FastPlan &p, const _Float
   return ragged ? go(&wide_rows_kernel<MODE, false, true, false>) : go(&wide_rows_kernel<MODE, false, false, false>);
 }
 
-template <int DH, int MODE>
-hipError_t launch_rows(const wersa_desc &c, const FastPlan &p, const _Float16 *xf, const bf16_t *x,
-                       const bf16_t *y, const float *Dsaved, const float *arow, const FastWs &w,
-                       const bf16_t *omega, const bf16_t *Mx, const bf16_t *MT, const bf16_t *bb,
-                       bf16_t *out0, float *Dout, float *partF, hipStream_t st,
-                       const View *yview = nullptr, bf16_t *out1 = nullptr) {
-  if constexpr (DH == 128)
-    return launch_wide_rows<MODE>(c, p, xf, x, y, Dsaved, arow, w, omega, Mx, MT, bb, out0, Dout, partF, st, yview);
-  else {
+// Head dimension 64.  out1: dV of the K-side gradient.
+template <int MODE>
+hipError_t launch_rows64(const wersa_desc &c, const FastPlan &p, const bf16_t *x, const bf16_t *y, const float *Dsaved,
+                         const float *arow, const FastWs &w, const bf16_t *omega, const bf16_t *Mx, const bf16_t *MT,
+                         const bf16_t *bb, bf16_t *out0, float *Dout, float *partF, hipStream_t st, const View *yview,
+                         bf16_t *out1) {
   constexpr bool IS_GRAD = (MODE == 1 || MODE == 2);
-  constexpr int NW = IS_GRAD ? kWavesGrad : waves_apply(DH);
+  constexpr int NW = IS_GRAD ? kWavesGrad : kWavesApply;
   // key-side modes take the second random matrix when the descriptor has two
   const int64_t side = ((c.flags & WERSA_FLAG_SEPARATE_OMEGA) && MODE >= 2) ? (int64_t)c.d * c.m : 0;
   const _Float16 *omT = w.omT + side;
   omega += side;
   const View tv{c.stride_b, c.stride_h, c.stride_n, c.H};
-  const int mcs = MODE == 3 ? p.mcA : p.mc;
-  // (the gradient kernels of head dimension 128 exist with 128 staged features only)
-  constexpr int MCH = (DH == 128 && IS_GRAD) ? 128 : 256;
-  const size_t smem = rows_smem_bytes<DH, MODE, NW>(mcs);
+  const int mcs = p.mc;
+  const size_t smem = rows_smem_bytes<64, MODE, NW>(mcs);
   const char *name = MODE == 0 ? "wersa_rows_fwd"
                                : (MODE == 1 ? "wersa_rows_bwd_q" : (MODE == 2 ? "wersa_rows_bwd_k" : "wersa_rows_bwd_v"));
   const int wgs = IS_GRAD ? p.rowsWgsG : p.rowsWgsA, groups = IS_GRAD ? p.rowGroupsG : p.rowGroupsA;
@@ -2646,51 +2585,44 @@ hipError_t launch_rows(const wersa_desc &c, const FastPlan &p, const _Float16 *x
     if (e != hipSuccess) return e;
     WERSA_STAGE(name, st,
                 kern<<<dim3(wgs, c.B * c.H), NW * 64, smem, st>>>(
-                    xf, x, tv, y, yview ? *yview : tv, Dsaved, arow, omT, omega, Mx, MT, bb, w.coef, w.scalars,
+                    x, tv, y, yview ? *yview : tv, Dsaved, arow, omT, omega, Mx, MT, bb, w.coef, w.scalars,
                     c.eps, c.n, c.m, groups, out0, tv, Dout, partF, c.L,
                     MODE >= 2 ? w.addK : w.addQ, MODE == 1 ? w.gsumQ : w.gsumK, out1));
     return hipSuccess;
   };
-  if (out1) {   // dV rides along with the K-side gradient (see dv_rides_along)
-    constexpr bool OK = MODE == 2 && DH == 64;
-    constexpr int MCV = OK ? 256 : 128;
-    if (c.n % 64 != 0) {
-      if (c.L > kTileL) return go(&rows_kernel<DH, MODE, NW, MCV, false, OK, OK, OK>);
-      return go(&rows_kernel<DH, MODE, NW, MCV, false, OK, false, OK>);
+  if constexpr (MODE == 2) {
+    if (out1) {   // dV rides along with the K-side gradient (see dv_rides_along)
+      if (c.n % 64 != 0)
+        return c.L > kTileL ? go(&rows_kernel<64, 2, NW, 256, false, true, true, true>) : go(&rows_kernel<64, 2, NW, 256, false, true, false, true>);
+      return c.L > kTileL ? go(&rows_kernel<64, 2, NW, 256, false, false, true, true>) : go(&rows_kernel<64, 2, NW, 256, false, false, false, true>);
     }
-    if (c.L > kTileL) return go(&rows_kernel<DH, MODE, NW, MCV, false, false, OK, OK>);
-    return go(&rows_kernel<DH, MODE, NW, MCV, false, false, false, OK>);
   }
-  const bool ln = MODE == 0 && (c.flags & WERSA_FLAG_LAYERNORM), ragged = c.n % 64 != 0;
-  if (DH == 128 && IS_GRAD && c.L > kTileL) {
-    // deeper than one block, head dimension 128: X_F arrives with the levels above 6 in it; the
-    // gradient modes still write the tile sums of dX_F and the extra rows of the band partials
-    if (ragged) return go(&rows_kernel<DH, MODE, NW, 128, false, DH == 128 && IS_GRAD, DH == 128 && IS_GRAD>);
-    return go(&rows_kernel<DH, MODE, NW, 128, false, false, DH == 128 && IS_GRAD>);
-  }
-  if (DH == 64 && c.L > kTileL) {   // deeper than one block, head dimension 64
-    if (ragged) {
-      if (ln) return mcs == 256 ? go(&rows_kernel<DH, MODE, NW, MCH, MODE == 0, DH == 64, DH == 64>)
-                                 : go(&rows_kernel<DH, MODE, NW, 128, MODE == 0, DH == 64, DH == 64>);
-      return mcs == 256 ? go(&rows_kernel<DH, MODE, NW, MCH, false, DH == 64, DH == 64>)
-                         : go(&rows_kernel<DH, MODE, NW, 128, false, DH == 64, DH == 64>);
-    }
-    if (ln) return mcs == 256 ? go(&rows_kernel<DH, MODE, NW, MCH, MODE == 0, false, DH == 64>)
-                               : go(&rows_kernel<DH, MODE, NW, 128, MODE == 0, false, DH == 64>);
-    return mcs == 256 ? go(&rows_kernel<DH, MODE, NW, MCH, false, false, DH == 64>)
-                       : go(&rows_kernel<DH, MODE, NW, 128, false, false, DH == 64>);
-  }
-  if (ragged) {   // the shapes with a partial last block take the guarded instances
-    if (ln) return mcs == 256 ? go(&rows_kernel<DH, MODE, NW, MCH, MODE == 0, true, false>)
-                               : go(&rows_kernel<DH, MODE, NW, 128, MODE == 0, true, false>);
-    return mcs == 256 ? go(&rows_kernel<DH, MODE, NW, MCH, false, true, false>)
-                       : go(&rows_kernel<DH, MODE, NW, 128, false, true, false>);
-  }
-  if (ln) return mcs == 256 ? go(&rows_kernel<DH, MODE, NW, MCH, MODE == 0, false, false>)
-                             : go(&rows_kernel<DH, MODE, NW, 128, MODE == 0, false, false>);
-  return mcs == 256 ? go(&rows_kernel<DH, MODE, NW, MCH, false, false, false>)
-                     : go(&rows_kernel<DH, MODE, NW, 128, false, false, false>);
-  }
+  const bool ln = MODE == 0 && (c.flags & WERSA_FLAG_LAYERNORM), ragged = c.n % 64 != 0, deep = c.L > kTileL;
+  // partial last block, levels above one block: instances of their own
+  auto pick = [&](auto mcv, auto lnv) -> hipError_t {
+    constexpr int MC = decltype(mcv)::value;
+    constexpr bool LNV = decltype(lnv)::value;
+    if (deep) return ragged ? go(&rows_kernel<64, MODE, NW, MC, LNV, true, true>) : go(&rows_kernel<64, MODE, NW, MC, LNV, false, true>);
+    return ragged ? go(&rows_kernel<64, MODE, NW, MC, LNV, true, false>) : go(&rows_kernel<64, MODE, NW, MC, LNV, false, false>);
+  };
+  using M128 = std::integral_constant<int, 128>;
+  if constexpr (MODE >= 2) return pick(M128{}, std::false_type{});   // (256 features: with dV, above)
+  using M256 = std::integral_constant<int, 256>;
+  using LNV = std::bool_constant<MODE == 0>;
+  if (ln) return mcs == 256 ? pick(M256{}, LNV{}) : pick(M128{}, LNV{});
+  return mcs == 256 ? pick(M256{}, std::false_type{}) : pick(M128{}, std::false_type{});
+}
+
+template <int DH, int MODE>
+hipError_t launch_rows(const wersa_desc &c, const FastPlan &p, const _Float16 *xf, const bf16_t *x,
+                       const bf16_t *y, const float *Dsaved, const float *arow, const FastWs &w,
+                       const bf16_t *omega, const bf16_t *Mx, const bf16_t *MT, const bf16_t *bb,
+                       bf16_t *out0, float *Dout, float *partF, hipStream_t st,
+                       const View *yview = nullptr, bf16_t *out1 = nullptr) {
+  if constexpr (DH == 128)
+    return launch_wide_rows<MODE>(c, p, xf, x, y, Dsaved, arow, w, omega, Mx, MT, bb, out0, Dout, partF, st, yview);
+  else
+    return launch_rows64<MODE>(c, p, x, y, Dsaved, arow, w, omega, Mx, MT, bb, out0, Dout, partF, st, yview, out1);
 }
 
 // orows != nullptr selects the backward form that derives dD from the rows of O itself;

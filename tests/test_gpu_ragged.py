@@ -103,7 +103,9 @@ def test_rows_further_apart_than_a_buffer_reaches(n, d, flags):
 
 @pytest.mark.parametrize("shape", [dict(B=1, H=2, n=1000, d=128, L=6, m=256), dict(B=2, H=2, n=1087, d=64, L=5, m=512),
                                    dict(B=1, H=2, n=1000, d=64, L=9, m=256), dict(B=2, H=1, n=1087, d=128, L=8, m=128),
-                                   dict(B=2, H=2, n=65, d=64, L=6, m=256), dict(B=2, H=2, n=33, d=128, L=3, m=128)],
+                                   dict(B=2, H=2, n=65, d=64, L=6, m=256), dict(B=2, H=2, n=33, d=128, L=3, m=128),
+                                   # workgroups of 256 rows: one row in the second, one row of a block's second half
+                                   dict(B=1, H=2, n=257, d=128, L=6, m=384), dict(B=1, H=2, n=289, d=128, L=7, m=128)],
                          ids=lambda s: "n{n}d{d}L{L}m{m}".format(**s))
 @pytest.mark.parametrize("flags", [0, 8], ids=["plain", "layernorm"])
 def test_partial_last_block_against_the_oracle(shape, flags):
