@@ -588,10 +588,10 @@ __device__ __forceinline__ bf16x8 tile_cols_operand(const bf16_t *tile, int stri
 }
 
 // ------------------------------------------------------------------------------------
-// phiT_contract: for the rows of one chunk and the features [f0, f0 + 4*FW) of one slice
+// phiT_contract: for the rows of one chunk and the features [f0, f0 + NW*FW) of one slice
 //   Spart[r][c] = sum_t ReLU(X_F Omega)[t][r] * (Y[t][c] / rowdiv_t)
 //   zpart[r]    = sum_t w_t * ReLU(X_F Omega)[t][r]
-// Four waves split the features; each wave keeps its Omega operands in registers and chains
+// NW waves split the features; each wave keeps its Omega operands in registers and chains
 // the projection's accumulators (rows t on registers) straight into the second MFMA as the
 // A operand.  X_F and Y tiles of 64 rows go through double-buffered LDS (Y transposed so that
 // t runs along the operand's k index); the next tile is fetched while the current one is used.
@@ -603,20 +603,27 @@ __device__ __forceinline__ bf16x8 tile_cols_operand(const bf16_t *tile, int stri
 // Head dimension 64 (FUSE): `xf` is not read; the rows of X (Q or K, bf16, view vx) are staged
 // raw and each step starts with X_F = G X for its tile, one 32 x 32 quarter per wave, written
 // to LDS in fp16 for the projection.
+// NW = 8 (head dimension 128): four waves are two workgroups per compute unit that each bring every row into LDS, divide
+// it by D and take its product with O, for 128 features; eight do that once for 256, and keep the matrix cores fed by
+// halves (see next_tile).  32 slices of 65536 rows, m 512, training step of the attention block: 16708 -> 16441 us; per launch
+// (forward, backward form) 12 slices of 16384 rows, m 512: 69.2, 95.6 -> 59.0, 72.8 us; 256 of 1024, m 256: 55.6, 73.5 -> 45.3, 56.7;
+// 8 of 4096, m 512: 17.2, 20.6 -> 17.1, 18.6.  The sums are the same bits.
 // RAGGED: n % 64 != 0, rows past n count as zeros with weight 0.  DEEP: L > 6, the filter's levels
 // above 6 enter as the per-tile addend tile_add [slices][ceil(n / 64)][DH] (the accumulators of X_F start there).
-template <int DH, int FW, bool PREP, bool RAGGED, bool DEEP>
-__global__ __launch_bounds__(256, 2) void phiT_contract_kernel(
+template <int DH, int FW, bool PREP, bool RAGGED, bool DEEP, int NW = 4>
+__global__ __launch_bounds__(64 * NW, 2) void phiT_contract_kernel(
     const _Float16 *xf, const bf16_t *xraw, View vx, const float *coef, const float *tile_add,
     const bf16_t *y, View vy, const float *rowdiv, const float *w,
     const bf16_t *orows, float *dDout, float *dDpart,
     const _Float16 *omT, int n, int m, int rows_per_chunk, float *Spart, float *zpart) {
   constexpr bool FUSE = (DH == 64);
+  static_assert(NW == 4 || (NW == 8 && !FUSE), "the filter of head dimension 64 is dealt to four waves");
+  constexpr int NT = 64 * NW;
   constexpr int KS = DH / 16;   // k-steps of the projection
   constexpr int RT = FW / 32;   // feature tiles per wave
   constexpr int CT = DH / 32;   // column tiles of Y
   constexpr int CPR = DH / 8;   // 16-byte pieces per row
-  constexpr int LPT = 64 * CPR / 256;   // pieces per thread per tile
+  constexpr int LPT = 64 * CPR / NT;   // pieces per thread per tile
   constexpr int YS = DH + 32;   // row stride (elements) of the Y tile [t][column]: 64 bytes past a multiple
                                 // of 256, so the four rows of a transposing read fall into different bank quarters
   constexpr int XS = DH + 8;    // row stride (elements) of the X_F tile
@@ -627,7 +634,7 @@ __global__ __launch_bounds__(256, 2) void phiT_contract_kernel(
   __shared__ __attribute__((aligned(16))) bf16_t wl[2][64];
   const int slice = blockIdx.z, chunk = blockIdx.x, chunks = gridDim.x;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
-  const int f0 = blockIdx.y * (4 * FW) + wave * FW;
+  const int f0 = blockIdx.y * (NW * FW) + wave * FW;
   const int t_begin = chunk * rows_per_chunk, t_end = min(n, t_begin + rows_per_chunk);
   const int steps = (t_end - t_begin + 63) / 64;   // the last tile of the sequence may be partial
 
@@ -666,8 +673,8 @@ __global__ __launch_bounds__(256, 2) void phiT_contract_kernel(
   // RAGGED: rows past n (partial last tile) count as zeros with weight 0: the address is clamped
   // to the last row and the value replaced.
   // Whole tiles (the plain instances): one running pointer per tensor, advanced by a tile per
-  // call (the tiles are requested in order); piece i sits i * (256 / CPR) rows further on.
-  constexpr int RPP = 256 / CPR;   // rows between a thread's pieces
+  // call (the tiles are requested in order); piece i sits i * (NT / CPR) rows further on.
+  constexpr int RPP = NT / CPR;   // rows between a thread's pieces
   const int r0 = tid / CPR, c0 = (tid % CPR) * 8;
   const int64_t xsn = FUSE ? vx.sn : DH;
   const u16x8 *px = reinterpret_cast<const u16x8 *>((FUSE ? xrs : reinterpret_cast<const bf16_t *>(xs)) +
@@ -696,7 +703,7 @@ __global__ __launch_bounds__(256, 2) void phiT_contract_kernel(
     const int last = RAGGED ? n - t0 - 1 : 63;
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
-      const int e = tid + 256 * i, r = e / CPR, cc = e % CPR;
+      const int e = tid + NT * i, r = e / CPR, cc = e % CPR;
       const bool bad = RAGGED && r > last;
       const int rc = t0 + (RAGGED ? min(r, last) : r);
       xr[i] = FUSE ? *reinterpret_cast<const u16x8 *>(xrs + (int64_t)rc * vx.sn + cc * 8)
@@ -716,7 +723,7 @@ __global__ __launch_bounds__(256, 2) void phiT_contract_kernel(
   auto stash = [&](int buf) {
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
-      const int e = tid + 256 * i, r = e / CPR, cc = e % CPR;
+      const int e = tid + NT * i, r = e / CPR, cc = e % CPR;
       *reinterpret_cast<u16x8 *>(&xt[buf][r * XS + cc * 8]) = xr[i];
       if (rd) {
         const float rinv = 1.0f / inv[i];
@@ -732,7 +739,7 @@ __global__ __launch_bounds__(256, 2) void phiT_contract_kernel(
       static_assert(!PREP || CPR == 8 || CPR == 16, "row pieces sit in 8 or 16 neighbouring lanes");
 #pragma unroll
       for (int i = 0; i < LPT; ++i) {
-        const int e = tid + 256 * i, r = e / CPR, cc = e % CPR;
+        const int e = tid + NT * i, r = e / CPR, cc = e % CPR;
         // (rows past n hold zeros in yr and 1 in inv: their dD is 0)
         float dot = dot8_bf16(__builtin_bit_cast(bf16x8, orw[i]), __builtin_bit_cast(bf16x8, yr[i]), 0.f);
         dot += dpp_move<0xB1>(dot);    // lane ^ 1
@@ -770,10 +777,27 @@ __global__ __launch_bounds__(256, 2) void phiT_contract_kernel(
       glo[u] = filter_operand(gt, 1, 32 * (wave >> 1) + l32, 2 * (ks_own + u) + h);
     }
   }
+  // Eight waves: the registers hold the tile after the current one when a step begins.  The waves of one half put it into
+  // LDS (and request the one after it) before their matrix instructions, those of the other half, their partners on the
+  // same SIMDs, after them.
+  auto next_tile = [&](int s) {
+    if (s + 1 >= steps) return;
+    stash((s & 1) ^ 1);
+    if (s + 2 < steps) {
+      t_stash = t_begin + 64 * (s + 2);
+      fetch(t_stash);
+    }
+  };
+  if (NW == 8 && steps > 1) {
+    t_stash = t_begin + 64;
+    fetch(t_stash);
+  }
   for (int s = 0; s < steps; ++s) {
     const int buf = s & 1;
     const bool more = s + 1 < steps;
-    if (more) {
+    if (NW == 8) {
+      if (wave < 4) next_tile(s);
+    } else if (more) {
       t_stash = t_begin + 64 * (s + 1);
       fetch(t_stash);
     }
@@ -854,7 +878,11 @@ __global__ __launch_bounds__(256, 2) void phiT_contract_kernel(
       }
     }
     __builtin_amdgcn_s_setprio(0);
-    if (more) stash(buf ^ 1);
+    if (NW == 8) {
+      if (wave >= 4) next_tile(s);
+    } else if (more) {
+      stash(buf ^ 1);
+    }
     __syncthreads();
   }
   float *sp = Spart + ((int64_t)slice * chunks + chunk) * (int64_t)m * DH;
@@ -869,11 +897,15 @@ __global__ __launch_bounds__(256, 2) void phiT_contract_kernel(
     if (h == 0) zpart[((int64_t)slice * chunks + chunk) * m + f0 + 32 * rt + l32] = zt;
   }
   if (PREP && blockIdx.y == 0) {   // sum of dD over this chunk's rows, fixed order
-    __shared__ float red[4];
+    __shared__ float red[NW];
     const float wsum = wave_sum64(dsum);
     if (lane == 0) red[wave] = wsum;
     __syncthreads();
-    if (tid == 0) dDpart[(int64_t)slice * chunks + chunk] = (red[0] + red[1]) + (red[2] + red[3]);
+    if (tid == 0) {
+      float sum = (red[0] + red[1]) + (red[2] + red[3]);
+      if constexpr (NW == 8) sum += (red[4] + red[5]) + (red[6] + red[7]);
+      dDpart[(int64_t)slice * chunks + chunk] = sum;
+    }
   }
 }
 
@@ -2402,7 +2434,7 @@ constexpr int kLnWgs = 2048;   // workgroups of ln_prep: eight of 256 threads pe
 constexpr int kWavesApply = 8;
 
 struct FastPlan {
-  int DH, FW, MB, mc;   // mc: features staged in LDS per pass by the rows kernels of head dimension 64
+  int DH, FW, NWC, MB, mc;   // NWC: waves of a phiT_contract workgroup; mc: features staged in LDS per pass by the rows kernels of head dimension 64
   int chunksQ, rowsQ;   // pooled-query partial sums
   int chunksC, rowsC;   // split of n in phiT_contract
   int rowGroupsA, rowsWgsA;   // apply-type rows kernel of head dimension 64 (8 waves): row groups / workgroups per slice
@@ -2427,6 +2459,11 @@ FastPlan fast_plan(const wersa_desc &c) {
   int want = 512 / (slices * (c.m / p.MB));   // two resident workgroups per compute unit, one round
   if (want < 1) want = 1;
   if (want > blocks) want = blocks;
+  // Eight waves per workgroup (256 features) as soon as three quarters of the compute units get one: at 192 (12 slices of 512 or
+  // 640 rows, m 512) both forms take 10 to 13 us, with four blocks per workgroup the eight waves are 11 to 24 % faster, and below, where
+  // each workgroup has one block, four waves on twice the compute units have less to wait for.
+  p.NWC = 4;
+  if (c.d == 128 && c.m % 256 == 0 && (int64_t)slices * (c.m / 256) * want >= 192) { p.NWC = 8; p.MB = 256; }
   const int bpc = (blocks + want - 1) / want;
   p.rowsC = bpc * 64;
   p.chunksC = (blocks + bpc - 1) / bpc;
@@ -2637,7 +2674,7 @@ void launch_contract(const wersa_desc &c, const FastPlan &p, const _Float16 *xf,
   const _Float16 *omT = w.omT + (((c.flags & WERSA_FLAG_SEPARATE_OMEGA) && key_side) ? (int64_t)c.d * c.m : 0);
   auto go = [&](auto kern) {
     WERSA_STAGE("wersa_phiT_contract", st,
-                kern<<<grid, 256, 0, st>>>(xf, xraw, View{c.stride_b, c.stride_h, c.stride_n, c.H}, w.coef,
+                kern<<<grid, 64 * p.NWC, 0, st>>>(xf, xraw, View{c.stride_b, c.stride_h, c.stride_n, c.H}, w.coef,
                                            key_side ? w.addK : w.addQ, y, yv,
                                            rowdiv, wts, orows, w.dD, w.dDpart, omT, c.n, c.m, p.rowsC, w.Spart,
                                            w.zpart));
@@ -2646,7 +2683,12 @@ void launch_contract(const wersa_desc &c, const FastPlan &p, const _Float16 *xf,
   constexpr int FWB = DH == 64 ? 64 : 32;   // 64 features per wave exist for head dimension 64 only (see fast_plan)
   constexpr bool D64 = DH == 64;
   const bool wide = p.FW == 64;
-  if (deep && ragged) {
+  if (DH == 128 && p.NWC == 8) {
+    if constexpr (DH == 128) {
+      if (orows) ragged ? go(&phiT_contract_kernel<DH, 32, true, true, false, 8>) : go(&phiT_contract_kernel<DH, 32, true, false, false, 8>);
+      else ragged ? go(&phiT_contract_kernel<DH, 32, false, true, false, 8>) : go(&phiT_contract_kernel<DH, 32, false, false, false, 8>);
+    }
+  } else if (deep && ragged) {
     if (wide) orows ? go(&phiT_contract_kernel<DH, FWB, true, D64, D64>) : go(&phiT_contract_kernel<DH, FWB, false, D64, D64>);
     else orows ? go(&phiT_contract_kernel<DH, 32, true, D64, D64>) : go(&phiT_contract_kernel<DH, 32, false, D64, D64>);
   } else if (deep) {

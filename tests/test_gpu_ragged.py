@@ -125,3 +125,36 @@ def test_partial_last_block_against_the_oracle(shape, flags):
     print(cfg, flags, {k: f"{v:.1e}" for k, v in errs.items()}, flush=True)
     small = shape["n"] < 1000
     assert all(v < 2e-2 for k, v in errs.items() if not (small and k in ("dQ", "dK"))), errs
+
+
+# The contraction kernel of head dimension 128 runs eight waves per workgroup from 192 such workgroups on: twelve slices and 512
+# features are 24 per chunk of the rows, so eight 64-row blocks are the line.
+@pytest.mark.parametrize("flags", [0, 8])
+@pytest.mark.parametrize("n", [448, 449, 512, 1100, 1344, 2000])   # 7 blocks; 8, the last one row; 8; chunks of 2, 3 and 4 blocks
+def test_contraction_with_eight_waves(n, flags):
+    """S and z (K side), dK (the dS and dz that the Q side leaves) and d sigma (its sum of dD) against float32 arithmetic on the
+    same inputs; the bounds are those above: bf16 features and rows, 2^-9 each."""
+    import torch
+    from paper_2507_08637_amd import binding
+    B, H, d, m, L = 3, 4, 128, 512, 3
+    g = torch.Generator(device="cuda").manual_seed(n + flags)
+
+    def normal(*s):
+        return torch.randn(s, generator=g, device="cuda")
+
+    wave = torch.sin(torch.arange(n, device="cuda") / 40.0)[:, None]
+    q, k, v, dout = ((normal(B, H, n, d) + c + wave).to(torch.bfloat16) for c in (0.2, 0.2, 1.0, 0.5))
+    par = (normal(d, m).to(torch.bfloat16), torch.ones(1, device="cuda"), normal(H, L + 1, d) / d ** 0.5, 0.5 * normal(H, L + 1),
+           1.0 + 0.1 * normal(L + 1))
+    res = []
+    for path in (0, binding.FLAG_GENERIC_PATH):
+        fl = dict(flags=flags | path, eps=1e-3)
+        out, saved = binding.wersa_forward(q, k, v, *par, L, **fl)
+        views = binding.saved_views(binding.make_desc(q, L, m, **fl), saved)
+        grads = binding.wersa_backward(q, k, v, *par, out, dout, saved, L, **fl)
+        res.append(dict(grads, S=views["S"].clone(), z=views["z"].clone()))
+    errs = {name: float((res[0][name].double() - r.double()).norm() / r.double().norm().clamp_min(1e-30)) for name, r in res[1].items()}
+    print((n, flags), {x: f"{e:.1e}" for x, e in errs.items()}, flush=True)
+    assert errs["S"] < 6e-3 and errs["z"] < 6e-3 and errs["dv"] < 6e-3, errs
+    if not flags:
+        assert errs["dk"] < 2e-2 and errs["dq"] < 2e-2, errs
