@@ -1789,10 +1789,10 @@ Ws ws_of(const wersa_desc &c, const Plan &p, int bwd, bool keep, float *base) {
   return w;
 }
 
-// Where Q_F and K_F, packed (6 bytes per element each), live between the forward and the backward.  In `saved` where the rest
+// Where Q_F and K_F, packed (6 bytes per element each, 4 from head dimension 64 on), live between the forward and the backward.  In `saved` where the rest
 // of the forward's workspace fits wersa_forward_static's scratch: the backward has less to do where latency counts (64 slices
 // of 1000 tokens, d 64, m 64, float32: 110 us, 122 us where it packs them again), and what the static call takes does not
-// shrink by them.  Beyond, `saved` would hold three times a tensor for every layer of a model (811 MB for 8 slices of 131072
+// shrink by them.  Beyond, `saved` would hold two or three times a tensor for every layer of a model (542 MB for 8 slices of 131072
 // tokens, d 64, against 5), and the backward packs them again, from Q and K, in the launch that packs dN: 8 x 16384 tokens, d 64,
 // m 256 367 us -> 374, 128 x 4000, d 32, m 1024 1716 -> 1763.
 bool keeps_operands(const wersa_desc &c, const Plan &p) {
