@@ -606,7 +606,7 @@ __device__ __forceinline__ bf16x8 tile_cols_operand(const bf16_t *tile, int stri
 // NW = 8 (head dimension 128): four waves are two workgroups per compute unit that each bring every row into LDS, divide
 // it by D and take its product with O, for 128 features; eight do that once for 256, and keep the matrix cores fed by
 // halves (see next_tile).  32 slices of 65536 rows, m 512, training step of the attention block: 16708 -> 16441 us; per launch
-// (forward, backward form) 12 slices of 16384 rows, m 512: 69.2, 95.6 -> 59.0, 72.8 us; 256 of 1024, m 256: 55.6, 73.5 -> 45.3, 56.7;
+// (forward, backward form) there 628, 908 -> 521, 667; 12 slices of 16384 rows, m 512: 69.2, 95.6 -> 59.0, 72.8 us; 256 of 1024, m 256: 55.6, 73.5 -> 45.3, 56.7;
 // 8 of 4096, m 512: 17.2, 20.6 -> 17.1, 18.6.  The sums are the same bits.
 // RAGGED: n % 64 != 0, rows past n count as zeros with weight 0.  DEEP: L > 6, the filter's levels
 // above 6 enter as the per-tile addend tile_add [slices][ceil(n / 64)][DH] (the accumulators of X_F start there).

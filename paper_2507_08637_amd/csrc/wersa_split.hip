@@ -22,8 +22,8 @@
 // What bounds it: per 32 x 32 tile of a feature matrix the matrix cores spend 32 cycles per product and 16 of the
 // contraction's length, the vector units two instructions per element on the split (5.5 for three bf16 terms) and two or
 // three on ReLU, mask and normaliser: 2.4 cycles of a SIMD each in the short encoding, 4.5 in the long one, with two waves or more.
-// Counters (128 slices of 4000 tokens, d 32, m 1024, float32, and 8 of 131072, d 16, bf16): matrix cores busy 58 to 70 and 44 to 64 % of
-// a SIMD's cycles in the four contraction kernels, vector units 40 to 48 and 67 to 76 %.
+// Counters (128 slices of 4000 tokens, d 32, m 1024, float32, and 8 of 131072, d 16, bf16): matrix cores busy 60 to 65 and 44 to 64 % of
+// a SIMD's cycles in the four contraction kernels, vector units 48 to 53 and 68 to 76 %.
 //
 // Measured, three bf16 terms and six products for every operand against this: the two cases above 2405 -> 1965 and
 // 2215 -> 1700 us per training step; float32, 8 slices of 16384 tokens, d 64, m 256: 562 -> 428; 16 of 4096, d 128, m 512: 966 -> 705; bf16,
