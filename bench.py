@@ -75,8 +75,8 @@ def kernel_models(cfg):
         "wersa_ln_prep": ("hbm", "hbm", 3 * nd * e),
         "wersa_add_pooled": ("hbm", "hbm", 2 * nd * e),
     }
-    # float32 arithmetic on the 16-bit matrix cores (d <= 128): the method's contractions, each of which takes two
-    # products (one operand a bf16 tensor) or three, the projection of head dimensions up to 32 three or six
+    # float32 arithmetic on the bf16 matrix cores (d <= 128): the method's contractions, each of which takes
+    # three bf16 products (one operand a bf16 tensor) or six
     models["split_contract"] = ("mfma", "mfma_bf16", 2 * unit)   # projection + Phi^T Y
     models["split_apply"] = ("mfma", "mfma_bf16", 2 * unit)      # projection + Phi S
     models["split_apply_dv"] = ("mfma", "mfma_bf16", 2 * unit)   # projection + Phi dS

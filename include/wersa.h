@@ -62,7 +62,7 @@ typedef enum { WERSA_F32 = 0, WERSA_BF16 = 1 } wersa_dtype;
  * m % 128 == 0, strides multiples of 8 elements (any n, any L <= 20);
  * otherwise the generic path:
  * float32 arithmetic throughout (contractions on the bf16 matrix cores with every float32 operand as
- * a sum of 16-bit values for d <= 128, float32 matrix instructions above, with few rows, and where only these
+ * the sum of three bf16 values for d <= 128, float32 matrix instructions above, with few rows, and where only these
  * keep the forward's workspace within wersa_static_scratch_bytes()).
  * WERSA_FLAG_GENERIC_PATH forces the generic path. */
 #define WERSA_FLAG_GENERIC_PATH 1

@@ -80,8 +80,7 @@ inline bool use_split(const wersa_desc &c) {
   return split == generic ? !few_rows(c) : split;
 }
 struct SplitSizes {
-  int64_t X, OA, OB;           // floats: packed Q_F or K_F (0: formed again by the backward), Omega both ways
-  int64_t rows, tiles, shares, S, f;   // exponents: of rows, of token tiles, of shares of S and z (these three with X only), of S and z, of features
+  int64_t X, OA, OB;   // floats: packed Q_F or K_F (0: formed again by the backward), Omega both ways
 };
 SplitSizes split_sizes(const wersa_desc &c);
 
@@ -96,7 +95,6 @@ struct SavedLayout {
   // Split path only: the operands of the contractions that the backward uses again (with scalars, coef and, for
   // L > 6, the tile sums and addends above).
   int64_t XQ, XK, OA, OB;
-  int64_t exQ, exK, eV, pe, eS, ge;   // exponents of the rows of Q_F and K_F, the token tiles of V, the shares of S and z, S and z, the features
 };
 inline SavedLayout saved_layout(const wersa_desc &c) {
   SavedLayout o;
@@ -131,7 +129,7 @@ inline SavedLayout saved_layout(const wersa_desc &c) {
       o.addK = off;  off += up(tiles);
     }
   }
-  o.XQ = o.XK = o.OA = o.OB = o.exQ = o.exK = o.eV = o.pe = o.eS = o.ge = -1;
+  o.XQ = o.XK = o.OA = o.OB = -1;
   if (use_split(c)) {
     const SplitSizes z = split_sizes(c);
     o.scalars = off; off += 64;
@@ -140,12 +138,6 @@ inline SavedLayout saved_layout(const wersa_desc &c) {
     o.XK = off;      off += up(z.X);
     o.OA = off;      off += up(z.OA);
     o.OB = off;      off += up(z.OB);
-    o.exQ = off;     off += up(z.rows);
-    o.exK = off;     off += up(z.rows);
-    o.eV = off;      off += up(z.tiles);
-    o.pe = off;      off += up(z.shares);
-    o.eS = off;      off += up(z.S);
-    o.ge = off;      off += up(z.f);
     if (c.L > kTileL) {
       const int64_t tiles = sl * ((c.n + 63) / 64) * c.d;
       o.tileQ = off; off += up(tiles);

@@ -1,36 +1,26 @@
-// Split path: float32 arithmetic on the 16-bit matrix cores, the n x m feature matrices in registers
+// Split path: float32 arithmetic on the bf16 matrix cores, the n x m feature matrices in registers
 // (Section 3.1 steps 3-8 and their derivatives; every dtype, head dimensions up to 128, any m).
 //
-// Every float32 operand of a contraction is a power of two times a sum of two fp16 values,
-//   2^-e x = h + l,  h = fp16(2^-e x), l = fp16(2^-e x - h)   (22 to 24 significant bits),
-// and a product of two such operands is the three fp16 products h l', l h', h h' accumulated in float32; the fourth is
-// at most 2^-22 of the whole and 2^-24.7 in the mean.  A bf16 tensor is one exact term, so products with it take two.  The
-// projection X_F Omega of head dimensions up to 32 takes three bf16 terms and six products (three with a bf16 Omega)
-// instead: a pre-activation that falls on the other side of zero costs a whole term of a gradient, and sums that short
-// show the operands' rounding (below).
-//
-// The powers of two, all exact: one per row of X_F (ReLU is positively homogeneous; the exponent comes back in the weights
-// of S and z and in the rows of the result), one per feature of Omega (back in S and z), one per row of dN or V in the
-// gradient kernel, the slice's for S, from the largest share of it, and one per 32-token tile where the contraction runs over
-// tokens.  Those are multiples of 8, so tiles of like magnitude share theirs; a tile whose exponent is not the largest of its
-// workgroup is multiplied by the difference (a branch that the whole wave takes).
-//
-// Error of a sum against float64, relative to the root mean square (normal values; six bf16 products in one
-// accumulator, three fp16 products with the small ones added first): projection d 16 3.4e-8, 8.7e-8; d 32 6.8e-8, 9.2e-8;
-// d 64 1.11e-7, 9.9e-8; d 128 1.63e-7, 1.10e-7.  Contraction over 4096 tokens in 8 shares 9.1e-8, 4.6e-8.
+// Every float32 operand of a contraction is written as a sum of three bf16 values,
+//   x = x0 + x1 + x2,  x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1)   (24 significant bits),
+// and a product of two such operands is the six bf16 products x0 y0, x0 y1, x1 y0, x0 y2, x1 y1, x2 y0
+// accumulated in float32; what is left out (x1 y2, x2 y1, x2 y2) is at most 2^-24 of |x y|, a rounding error of the
+// float32 product itself.  A bf16 tensor is one exact term, so products with it take three.  The bf16
+// matrix rate is 16 times the float32 one, so even six products leave a factor of 2.7.
 //
 // What bounds it: per 32 x 32 tile of a feature matrix the matrix cores spend 32 cycles per product and 16 of the
-// contraction's length, the vector units two instructions per element on the split (5.5 for three bf16 terms) and two or
-// three on ReLU, mask and normaliser: 2.4 cycles of a SIMD each in the short encoding, 4.5 in the long one, with two waves or more.
-// Counters (128 slices of 4000 tokens, d 32, m 1024, float32, and 8 of 131072, d 16, bf16): matrix cores busy 60 to 65 and 44 to 64 % of
-// a SIMD's cycles in the four contraction kernels, vector units 48 to 53 and 68 to 76 %.
+// contraction's length (and where they form the residuals, four more products), the vector units 5.5 instructions per
+// element on the split and two on ReLU or mask.  Counters (128 slices of 4000 tokens, d 32, m 1024, float32, and 8 of
+// 131072, d 16, bf16): matrix cores busy 65 to 73 and 72 to 79 % of a SIMD's cycles in the four contraction kernels,
+// vector units 45 to 59 and 44 to 56 %; two waves per SIMD let one run under the other.  From d 64 on the matrix cores
+// alone.  grad_kernel with dV at d 64 keeps 72 bytes per lane in scratch (its accumulators and operands fill the 256 registers).
 //
-// Measured, three bf16 terms and six products for every operand against this: the two cases above 2405 -> 1965 and
-// 2215 -> 1700 us per training step; float32, 8 slices of 16384 tokens, d 64, m 256: 562 -> 428; 16 of 4096, d 128, m 512: 966 -> 705; bf16,
-// 128 of 4000, d 32, m 1024: 1779 -> 1411.
+// Measured against the generic kernels, which write every n x m feature matrix to memory: float32 training step, 128
+// slices of 4000 tokens, d 32, m 1024: 13990 -> 2456 us; bf16 training step, 8 slices of 131072 tokens, d 16, m 1024:
+// 26290 -> 2251 us; float32 inference, one slice of 1024 tokens, d 64, m 64: 118 -> 37 us.
 //
 // Layout: every operand is kept in the order in which a wave loads it ("operand tile": 32 vectors x 16
-// k-values of 16 bits; lane (l32, h) holds vector l32, k = 8 h .. 8 h + 7, 16 bytes; 1 KiB).  Where k runs
+// k-values of bf16; lane (l32, h) holds vector l32, k = 8 h .. 8 h + 7, 16 bytes; 1 KiB).  Where k runs
 // over the rows of an accumulator tile (features, or tokens), the k-slots stand for the rows in the
 // order in which the accumulator registers hold them: slot (h, q) of half a is row 16 a + 8 (q / 4)
 // + 4 h + q % 4.  The tensors of n x d (a small share of the time: m / 16 feature tiles are formed per
@@ -52,23 +42,16 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
-typedef u32x4 op_t;       // what a lane holds of an operand tile: eight bf16 or fp16 values
-typedef uint16_t half_t;  // one value of an operand tile
 
-constexpr int kTile = 512;   // values of one operand tile
+constexpr int kTile = 512;   // bf16 values of one operand tile
 
-__device__ __forceinline__ f32x16 mfma_b(op_t a, op_t b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-__device__ __forceinline__ f32x16 mfma_h(op_t a, op_t b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+__device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 __device__ __forceinline__ f32x16 zero16() {
   f32x16 z;
@@ -82,66 +65,8 @@ __device__ __forceinline__ float xor32_sum(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// ------------------------------------------------------------------------------------
-// Exponents.  A power of two takes the largest finite value of its row or tile to the top of a range: 2^top >= |2^-e x|.
-// Zeros and what is not finite have no say in it.
-// ------------------------------------------------------------------------------------
-constexpr int kNone = -4096;   // of a row or tile without a finite value other than zero
-constexpr int log2_dh(int DH) { return DH == 16 ? 4 : DH == 32 ? 5 : DH == 64 ? 6 : 7; }
-// A feature is a sum of DH products of a row of X_F and a column of Omega and has to stay below 2^16 to be an fp16 value.
-constexpr int kOmegaTop = 4;
-constexpr int x_top(int DH) { return 11 - log2_dh(DH); }
-// So does the derivative of a feature: DH products of a row of dN or V and a row of S, and the rank-one term.
-constexpr int kSTop = 6;
-constexpr int y_top(int DH) { return 9 - log2_dh(DH); }
-constexpr int kRankOneTop = 14;
-// V or dN with tokens, S with features as the contraction's length: nothing but the operand has to be an fp16 value.
-constexpr int kTokensTop = 15, kSBTop = 14, kSBShift = kSBTop - kSTop;
-// As they are kept in memory: numbers that, read as floats (as a caller may read `saved`), are finite.
-struct stored_exp {
-  int bits;
-  __device__ __forceinline__ operator int() const { return bits - 8192; }
-  __device__ __forceinline__ void operator=(int e) { bits = e + 8192; }
-};
-// magnitude as an integer (its order is that of the values), 0 for what is not finite
-__device__ __forceinline__ unsigned magnitude(float x) {
-  const unsigned u = __float_as_uint(x) & 0x7fffffffu;
-  return u < 0x7f800000u ? u : 0u;
-}
-__device__ __forceinline__ unsigned umax(unsigned a, unsigned b) { return a > b ? a : b; }
-// e with 2^(e - 1) <= x < 2^e
-__device__ __forceinline__ int exponent(unsigned mag) {
-  return mag ? __builtin_amdgcn_frexp_expf(__uint_as_float(mag)) : kNone;
-}
-__device__ __forceinline__ float scaled(float x, int e) { return __builtin_amdgcn_ldexpf(x, e); }
-template <int STEP>
-__device__ __forceinline__ int round_up(int e) { return (e + STEP - 1) & -STEP; }
-// Of a row of X_F or a feature, from the largest |x| as an integer; the limits keep 2^e a float.  A value that is not finite makes all
-// pre-activations of its row or feature NaN, and the ReLU of a NaN is 0: zeros in its place, kNone, do the same, and no
-// pre-activation is NaN.
-__device__ __forceinline__ unsigned any_magnitude(float x) { return __float_as_uint(x) & 0x7fffffffu; }
-__device__ __forceinline__ int row_exponent(unsigned mag, int top) {
-  return mag >= 0x7f800000u ? kNone : mag ? min(max(exponent(mag) - top, -100), 120) : 0;
-}
-__device__ __forceinline__ float scaled_down(float x, int e) { return e == kNone ? 0.f : scaled(x, -e); }
-__device__ __forceinline__ int wave_max(int v) {
-  for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
-  return __builtin_amdgcn_readfirstlane(v);
-}
-
-// ------------------------------------------------------------------------------------
-// Terms
-// ------------------------------------------------------------------------------------
-// of X_F in the projection, and of Omega there (PT: of the tensors' storage type)
-constexpr int x_terms(int DH) { return DH <= 32 ? 3 : 2; }
-constexpr int o_terms(int DH, int PT) { return PT == 1 ? 1 : x_terms(DH); }
-// Operand tiles per 16 x 32 piece of an operand with its columns as vectors.  Head dimension 16 leaves half of
-// the 32 columns free: they hold the second term, [y0 | y1], and the two halves of the result are added at the end.
-constexpr int c_tiles(int DH, int terms) { return DH == 16 ? 1 : terms; }
-
-// Three bf16 terms of eight floats.
-__device__ __forceinline__ void split8b(const float *v, op_t *t) {
-  bf16x8 y[3];
+// Split of eight floats.
+__device__ __forceinline__ void split8(const float *v, bf16x8 *t) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     f32x2 x;
@@ -150,112 +75,132 @@ __device__ __forceinline__ void split8b(const float *v, op_t *t) {
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
       const bf16x2 p = __builtin_convertvector(x, bf16x2);
-      y[i][2 * j] = p[0];
-      y[i][2 * j + 1] = p[1];
+      t[i][2 * j] = p[0];
+      t[i][2 * j + 1] = p[1];
       x[0] -= (float)p[0];
       x[1] -= (float)p[1];
     }
   }
-#pragma unroll
-  for (int i = 0; i < 3; ++i) t[i] = __builtin_bit_cast(op_t, y[i]);
 }
-// Two fp16 terms of eight floats, two vector instructions per float: the residual is one multiply-add that reads
-// the packed term (with a factor that the compiler cannot see to be -1; otherwise it unpacks and subtracts).
-__device__ __forceinline__ void split8h(const float *v, op_t *t) {
-  float neg = -1.f;
-  asm("" : "+s"(neg));
-  f16x8 y[2];
+// Split of an accumulator tile into operands (t[a][i]: half a, term i).  The vector units take 5.5 instructions per
+// element for it, most of them for the two residuals x - x0 and x - x0 - x1.  LV of these come from the matrix
+// cores instead: x - bf16(x) is the accumulator plus the product of the packed term with a negated identity
+// matrix whose columns are in the order of the k-slots, two instructions for the 16 values per lane, and exact (one
+// non-zero product per element).  Measured (one SIMD, four waves): a matrix instruction takes 32 cycles of its
+// own pipe and keeps the vector units from issuing for about 15, a vector instruction takes 4; a pair dot
+// product (v_dot2c_f32_bf16, which would do a residual in one instruction) does not run beside matrix
+// instructions at all.
+struct NegIdentity {
+  bf16x8 half[2];
+  __device__ __forceinline__ explicit NegIdentity(int lane) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    f32x2 x;
-    x[0] = v[2 * j];
-    x[1] = v[2 * j + 1];
-    const f16x2 p = __builtin_convertvector(x, f16x2);
-    x[0] = fmaf((float)p[0], neg, x[0]);
-    x[1] = fmaf((float)p[1], neg, x[1]);
-    const f16x2 q = __builtin_convertvector(x, f16x2);
-    y[0][2 * j] = p[0];
-    y[0][2 * j + 1] = p[1];
-    y[1][2 * j] = q[0];
-    y[1][2 * j + 1] = q[1];
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        half[a][q] = (__bf16)((lane & 31) == 16 * a + 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3) ? -1.f : 0.f);
   }
-  t[0] = __builtin_bit_cast(op_t, y[0]);
-  t[1] = __builtin_bit_cast(op_t, y[1]);
-}
-// An accumulator tile as operands: calls use(a, terms) for both halves.
-template <typename F>
-__device__ __forceinline__ void with_split(const f32x16 &x, F use) {
+};
+// Calls use(a, terms) for both halves.
+template <int LV, typename F>
+__device__ __forceinline__ void with_split(f32x16 x, const NegIdentity &ni, F use) {
+  if (LV == 0) {   // one half at a time: fewer registers
 #pragma unroll
-  for (int a = 0; a < 2; ++a) {
-    float v[8];
-    op_t t[2];
+    for (int a = 0; a < 2; ++a) {
+      float v[8];
+      bf16x8 t[3];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = x[8 * a + q];
-    split8h(v, t);
-    use(a, t);
+      for (int q = 0; q < 8; ++q) v[q] = x[8 * a + q];
+      split8(v, t);
+      use(a, t);
+    }
+    return;
   }
+  bf16x8 t[2][3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        f32x2 f;
+        f[0] = x[8 * a + 2 * j];
+        f[1] = x[8 * a + 2 * j + 1];
+        const bf16x2 p = __builtin_convertvector(f, bf16x2);
+        t[a][i][2 * j] = p[0];
+        t[a][i][2 * j + 1] = p[1];
+        if (i < 2 && i >= LV) {
+          x[8 * a + 2 * j] -= (float)p[0];
+          x[8 * a + 2 * j + 1] -= (float)p[1];
+        }
+      }
+    if (i < LV) {
+      x = mfma(ni.half[0], t[0][i], x);
+      x = mfma(ni.half[1], t[1][i], x);
+    }
+  }
+  use(0, t[0]);
+  use(1, t[1]);
 }
-__device__ __forceinline__ void split1b(float x, __bf16 *t) {
+// Residuals left to the matrix cores, by what is idle: with head dimensions 16 and 32 the contractions are too short to
+// fill them.
+constexpr int mfma_residuals(int DH, int PT) { return DH == 16 || (DH == 32 && PT == 1) ? 2 : 0; }
+__device__ __forceinline__ void split1(float x, __bf16 *t) {
   t[0] = (__bf16)x;
   const float r = x - (float)t[0];
   t[1] = (__bf16)r;
   t[2] = (__bf16)(r - (float)t[1]);
 }
 
-// Pre-activations of a 32 x 32 tile: x(ks, i), o(ks, i) are the operand pieces.  The small products of the whole sum come
-// first: while they are added the accumulator is small, and so is its rounding (d 32, six products: 6.8e-8 -> 3.9e-8).
-// SWAP: Omega is the first operand of the instruction (the features are the result's rows).
-template <int DH, int PT, bool SWAP, typename FX, typename FO>
-__device__ __forceinline__ f32x16 project(FX x, FO o) {
-  constexpr int KS = DH / 16;
-  f32x16 R = zero16();
-  auto go = [&](int ks, int i, int j) {
-    const op_t a = x(ks, i), b = o(ks, j);
-    R = DH <= 32 ? (SWAP ? mfma_b(b, a, R) : mfma_b(a, b, R)) : (SWAP ? mfma_h(b, a, R) : mfma_h(a, b, R));
-  };
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    if (DH <= 32) {
-      if (PT == 2) {
-        go(ks, 0, 2);
-        go(ks, 1, 1);
-      }
-      go(ks, 2, 0);
-    }
-    if (PT == 2) go(ks, 0, 1);
-    go(ks, 1, 0);
+// acc + the product of a three-term operand with one of NB terms, smallest products first.
+// SWAP: the NB-term operand is the first one of the instruction (its vectors are the result's rows).
+template <int NB, bool SWAP>
+__device__ __forceinline__ f32x16 mfma_terms(f32x16 acc, const bf16x8 *x, const bf16x8 *y) {
+  auto go = [&](int i, int j) { acc = SWAP ? mfma(y[j], x[i], acc) : mfma(x[i], y[j], acc); };
+  if (NB == 3) {
+    go(0, 2);
+    go(1, 1);
+    go(2, 0);
+    go(0, 1);
+    go(1, 0);
+    go(0, 0);
+  } else {
+    go(2, 0);
+    go(1, 0);
+    go(0, 0);
   }
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) go(ks, 0, 0);
-  return R;
+  return acc;
 }
-// acc + lo += the product of a two-term operand with one of NB tiles (c_tiles).  acc takes the product of the leading terms, lo
-// the others (lo may be acc).
+// The same products with the leading one in acc and the others in lo (see apply_terms); lo may be acc.
 template <int NB>
-__device__ __forceinline__ void add_terms(f32x16 &acc, f32x16 &lo, const op_t *x, const op_t *y) {
-  lo = mfma_h(x[1], y[0], lo);
-  if (NB == 2) lo = mfma_h(x[0], y[1], lo);
-  acc = mfma_h(x[0], y[0], acc);
+__device__ __forceinline__ void add_terms(f32x16 &acc, f32x16 &lo, const bf16x8 *x, const bf16x8 *y) {
+  if (NB == 3) {
+    lo = mfma(x[0], y[2], lo);
+    lo = mfma(x[1], y[1], lo);
+  }
+  lo = mfma(x[2], y[0], lo);
+  if (NB == 3) lo = mfma(x[0], y[1], lo);
+  lo = mfma(x[1], y[0], lo);
+  acc = mfma(x[0], y[0], acc);
 }
-__device__ __forceinline__ op_t lds_operand(const half_t *tile, int lane) {
-  return *reinterpret_cast<const op_t *>(tile + lane * 8);
+__device__ __forceinline__ bf16x8 lds_operand(const bf16_t *tile, int lane) {
+  return *reinterpret_cast<const bf16x8 *>(tile + lane * 8);
 }
 // All loads from memory have arrived.  Before a loop that requests its next stage first and works on operands loaded
 // before it: the compiler would otherwise wait, in the loop, for those and with them for the stage just requested.
 __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
-__device__ __forceinline__ void store_operand(half_t *tile, int lane, op_t v) {
-  *reinterpret_cast<op_t *>(tile + lane * 8) = v;
+__device__ __forceinline__ void store_operand(bf16_t *tile, int lane, bf16x8 v) {
+  *reinterpret_cast<bf16x8 *>(tile + lane * 8) = v;
 }
 
-// 1 where x > 0, else 0, exact for every float: one multiplication with output clamp.
+// 1 where x > 0, else 0 (also for NaN), exact for every float: one multiplication with output clamp.  With
+// additions and plain moves it runs at twice the rate of the other vector instructions (measured: 2 cycles against 4).
 __device__ __forceinline__ float positive(float x) { return __builtin_amdgcn_fmed3f(x * __builtin_inff(), 0.f, 1.f); }
-// max(x, 0) of a finite x, as integers: one instruction of the short encoding, 2.4 cycles of a SIMD with two waves or more (the
-// median 4.5; fmaxf is two, as it quiets a NaN first).
-__device__ __forceinline__ float relu(float x) { return __int_as_float(max(__float_as_int(x), 0)); }
-// a / b with r = 1 / b at hand: one residual corrects the product's rounding (and adds nothing to what is not finite).
-__device__ __forceinline__ float quotient(float a, float b, float r) {
-  const float q = a * r, e = fmaf(-q, b, a);
-  return magnitude(e) ? fmaf(e, r, q) : q;
+// max(x, 0), 0 for NaN of either sign as fmaxf gives.  One instruction: fmaxf is two (it quiets a NaN first), and so is
+// the median where the compiler sees that its bound is infinity.
+__device__ __forceinline__ float relu(float x) {
+  float bound = __builtin_inff();
+  asm("" : "+s"(bound));
+  return __builtin_amdgcn_fmed3f(x, 0.f, bound);
 }
 // x where mask is 1, 0 where it is 0, also for NaN and infinities (0 times anything is 0 in this instruction).
 __device__ __forceinline__ float masked(float x, float mask) { return amdgcn_mul_legacy(x, mask); }
@@ -303,7 +248,7 @@ struct Dims {
 
 // ------------------------------------------------------------------------------------
 // Column sums of Q (and, for L > 6, of K) per chunk of rows; workgroups past `chunks` of slice 0 carry the
-// per-call constants and pack Omega, four operand pieces of a feature tile each.  Grid (chunks + extra, slices, tensors).
+// per-call constants and pack Omega.  Grid (chunks + extra, slices, tensors).
 // ------------------------------------------------------------------------------------
 template <typename T>
 struct OmegaPack {
@@ -311,9 +256,8 @@ struct OmegaPack {
   const float *sigma;
   float bw_floor;
   float *scalars;
-  half_t *OA, *OB;     // features as vectors (k = columns), columns as vectors (k = features)
-  stored_exp *ge;      // [matrices][32 mt]: exponents of the features
-  int matrices, DH, KS, CT, PT, blocks;
+  bf16_t *OA, *OB;     // features as vectors (k = columns), columns as vectors (k = features)
+  int matrices, KS, CT, PT, blocks;
 };
 template <typename T>
 __device__ void omega_pack_body(const OmegaPack<T> &o, const Dims &s, int block) {
@@ -324,57 +268,32 @@ __device__ void omega_pack_body(const OmegaPack<T> &o, const Dims &s, int block)
     o.scalars[2] = sg > o.bw_floor ? 1.0f : 0.0f;
     o.scalars[3] = 1.0f;
   }
-  __shared__ float om[128][33];
-  __shared__ unsigned big[8][32];
-  __shared__ int ex[32];
-  const int tid = threadIdx.x, piece = block / (o.matrices * s.mt), mat = block / s.mt % o.matrices, ft = block % s.mt;
-  const int f0 = tid & 31, c0 = tid >> 5;
-  const T *src = o.omega + (int64_t)mat * s.d * s.m;
-  unsigned mag = 0;
-  for (int c = c0; c < o.DH; c += 8) {
-    const float x = c < s.d && 32 * ft + f0 < s.m ? ld(src + (int64_t)c * s.m + 32 * ft + f0) : 0.f;
-    om[c][f0] = x;
-    mag = umax(mag, any_magnitude(x));
-  }
-  big[c0][f0] = mag;
-  __syncthreads();
-  if (tid < 32) {
+  const int per_ft = 64 * (o.KS + 2 * o.CT), per_mat = s.mt * per_ft;
+  const int e = block * 256 + threadIdx.x;
+  if (e >= o.matrices * per_mat) return;
+  const int mat = e / per_mat, ft = e % per_mat / per_ft, piece = e % per_ft, lane = piece & 63, which = piece >> 6;
+  const int l32 = lane & 31, h = lane >> 5;
+  const T *om = o.omega + (int64_t)mat * s.d * s.m;
+  float v[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) mag = umax(mag, big[i][tid]);
-    ex[tid] = row_exponent(mag, kOmegaTop);
-    if (piece == 0) o.ge[(mat * s.mt + ft) * 32 + tid] = ex[tid];
-  }
-  __syncthreads();
-  const int OT = o_terms(o.DH, o.PT), CTT = c_tiles(o.DH, o.PT);
-  const int p = piece * 256 + tid;
-  if (p < 64 * (o.KS + 2 * o.CT)) {
-    const int lane = p & 63, which = p >> 6, l32 = lane & 31, h = lane >> 5;
-    float v[8];
-    op_t t[3];
+  for (int q = 0; q < 8; ++q) {
+    int f, c;
     if (which < o.KS) {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) v[q] = scaled_down(om[16 * which + 8 * h + q][l32], ex[l32]);
-      if (o.DH <= 32) split8b(v, t);
-      else split8h(v, t);
-      half_t *dst = o.OA + ((int64_t)(mat * s.mt + ft) * o.KS + which) * OT * kTile;
-      for (int i = 0; i < OT; ++i) store_operand(dst + i * kTile, lane, i == 0 ? t[0] : i == 1 ? t[1] : t[2]);
+      f = 32 * ft + l32;
+      c = 16 * which + 8 * h + q;
     } else {
       const int a = (which - o.KS) / o.CT, ct = (which - o.KS) % o.CT;
-      const int c = o.DH == 16 ? l32 & 15 : 32 * ct + l32;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int f = 16 * a + 8 * (q >> 2) + 4 * h + (q & 3);
-        v[q] = scaled_down(om[c][f], ex[f]);
-      }
-      split8h(v, t);
-      half_t *dst = o.OB + (((int64_t)(mat * s.mt + ft) * 2 + a) * o.CT + ct) * CTT * kTile;
-      if (o.DH == 16) {
-        store_operand(dst, lane, l32 < 16 ? t[0] : o.PT == 2 ? t[1] : op_t{});
-      } else {
-        for (int i = 0; i < CTT; ++i) store_operand(dst + i * kTile, lane, i == 0 ? t[0] : t[1]);
-      }
+      f = 32 * ft + 16 * a + 8 * (q >> 2) + 4 * h + (q & 3);
+      c = 32 * ct + l32;
     }
+    v[q] = (f < s.m && c < s.d) ? ld(om + (int64_t)c * s.m + f) : 0.f;
   }
+  bf16x8 t[3];
+  split8(v, t);
+  const int64_t tile = which < o.KS ? ((int64_t)(mat * s.mt + ft) * o.KS + which) * o.PT
+                                    : ((int64_t)(mat * s.mt + ft) * 2 * o.CT + which - o.KS) * o.PT;
+  bf16_t *dst = (which < o.KS ? o.OA : o.OB) + tile * kTile;
+  for (int i = 0; i < o.PT; ++i) store_operand(dst + i * kTile, lane, t[i]);
 }
 template <typename T>
 __global__ __launch_bounds__(256) void pool_kernel(const T *q, const T *k, View v, Dims s, int vec, int rows_per_chunk,
@@ -431,20 +350,38 @@ __global__ __launch_bounds__(256) void pool_kernel(const T *q, const T *k, View 
 }
 
 // ------------------------------------------------------------------------------------
-// Operands of n x d.  A workgroup holds whole rows (their exponents) and whole 64-row blocks (the filter): 4096 elements, 8192
-// at head dimension 128.
+// Operands of n x d, 4096 elements per workgroup.
 // ------------------------------------------------------------------------------------
 template <int DH>
 struct Geo {
-  static constexpr int KS = DH / 16, CT = DH < 32 ? 1 : DH / 32, XT = x_terms(DH);
-  // packing kernels: threads, rows, and the sixteens of columns of a row, of which a thread takes one
-  static constexpr int NT = DH == 128 ? 512 : 256, RB = 16 * NT / DH, PARTS = DH / 16, LS = DH + 4;
-  // kernels of the filter's backward: 64 columns at most, 4096 elements
-  static constexpr int CW = DH < 64 ? DH : 64, TR = 4096 / CW, PIECES = DH / CW, SEGS = 256 / CW;
-  static constexpr int NSA = 2 * KS + 1, NSB = 2 * CT * c_tiles(DH, 2);   // operand tiles of S per feature tile, both ways
+  static constexpr int KS = DH / 16, CT = DH < 32 ? 1 : DH / 32, CW = DH < 64 ? DH : 64, TR = 4096 / CW,
+                       PIECES = DH / CW, LS = CW + 4, SEGS = 256 / CW;
+  // Operand tiles per feature tile of S with its columns as vectors.  Head dimension 16 leaves half of the 32 columns
+  // free: [S0 | S1] and [S2 | 0] take four products instead of six (see apply_terms).
+  static constexpr int NSB = DH == 16 ? 4 : 6 * CT;
 };
-// Columns of the contraction's partial sums.
-constexpr int part_width(int DH, int PT) { return DH == 16 && PT == 1 ? 16 : DH < 32 ? 32 : DH; }
+// Phi S for one half of a feature tile and one column tile; sb: the operand tiles of S from lds_operand.  acc takes the
+// product of the leading terms, lo all others (together Phi S; lo may be acc): acc is rounded once per 16 features instead of six
+// times, and the slight bias of the matrix cores' rounding towards zero stays in proportion.  In one accumulator O came
+// out 9e-8 too small at 4096 features, the same in all columns of a row, which <dO, O> does not average out.
+// One float32 sequence of 2048 tokens, d 32, 4096 features, error against float64: O 6.9e-7 -> 3.4e-7, dQ 8.9e-7 -> 2.7e-7,
+// dW_g 4.3e-7 -> 1.3e-7; 4000 tokens, 1024 features: 3.8e-7 -> 1.7e-7, 5.0e-7 -> 2.2e-7, 1.7e-7 -> 1.2e-7.  Same time: the products are as many.
+template <int DH>
+__device__ __forceinline__ void apply_terms(f32x16 &acc, f32x16 &lo, const bf16x8 *p, const bf16_t *sb, int a, int ct, int lane) {
+  if (DH == 16) {   // columns 0-15: p0 S2 + (p2 + p1 + p0) S0; columns 16-31: (p2 + p1 + p0) S1; added at the end
+    const bf16x8 s01 = lds_operand(sb + 2 * a * kTile, lane), s2 = lds_operand(sb + (2 * a + 1) * kTile, lane);
+    lo = mfma(p[0], s2, lo);
+    lo = mfma(p[2], s01, lo);
+    lo = mfma(p[1], s01, lo);
+    acc = mfma(p[0], s01, acc);
+    return;
+  }
+  constexpr int CT = DH < 32 ? 1 : DH / 32;
+  bf16x8 y[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) y[i] = lds_operand(sb + ((a * CT + ct) * 3 + i) * kTile, lane);
+  add_terms<3>(acc, lo, p, y);
+}
 // sum over the levels above four (up to L) of coef_l * (block sum): levels 5 and 6 from the 16-row sums of a tile
 template <int CW>
 __device__ __forceinline__ float upper_levels(const float (*segsum)[CW], const float *cf, int seg, int c, int L) {
@@ -454,25 +391,24 @@ __device__ __forceinline__ float upper_levels(const float (*segsum)[CW], const f
   const float s6 = (segsum[b][c] + segsum[b + 1][c]) + (segsum[b + 2][c] + segsum[b + 3][c]);
   return fmaf(cf[5], s5, L < 6 ? 0.f : cf[6] * s6);
 }
-// Scratch of a packing kernel.
+// Scratch of a packing kernel: one tile of rows, the 16-row sums or two values per row, and a few scalars.
 template <int DH>
 struct PrepLds {
   using G = Geo<DH>;
-  float tile[G::RB * G::LS];
-  float part[G::NT];       // 16-row sums of the filter
+  static constexpr int RB = 4096 / DH, FILTER = G::TR * G::LS, ROWS = RB * (DH + 4);   // rows of a tile of whole rows
+  float tile[FILTER > ROWS ? FILTER : ROWS];
+  float part[256];
   float small[8];
-  int rexp[G::RB];         // exponents of the rows of X_F
-  int texp[G::RB / 32];    // of the token tiles of V or dN
 };
-// Whole rows of a strided tensor from row t0 into LDS; zeros past n and d.
+// TR x CW elements of a strided tensor from row t0, column c0 into LDS; zeros past n and d.
 template <typename T, int DH>
-__device__ __forceinline__ void load_tile(const T *xs, const View &v, const Dims &s, int vec, int t0, float *tile) {
+__device__ __forceinline__ void load_tile(const T *xs, const View &v, const Dims &s, int vec, int t0, int c0, float *tile) {
   using G = Geo<DH>;
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
-    const int e = threadIdx.x + G::NT * u, r = e / (DH / 8), cc = e % (DH / 8) * 8;
+    const int e = threadIdx.x + 256 * u, r = e / (G::CW / 8), cc = e % (G::CW / 8) * 8;
     float x[8];
-    if (t0 + r < s.n && cc < s.d) load8(xs + (int64_t)(t0 + r) * v.sn + cc, vec, x);
+    if (t0 + r < s.n && c0 + cc < s.d) load8(xs + (int64_t)(t0 + r) * v.sn + c0 + cc, vec, x);
     else
 #pragma unroll
       for (int i = 0; i < 8; ++i) x[i] = 0.f;
@@ -486,181 +422,130 @@ __device__ __forceinline__ void load_tile(const T *xs, const View &v, const Dims
     *reinterpret_cast<f32x4 *>(&tile[r * G::LS + cc + 4]) = b;
   }
 }
-// Largest magnitude of a row; thread tid has 16 columns of row tid / PARTS.  ANY: with what is not finite.
-template <int DH, bool ANY>
-__device__ __forceinline__ unsigned row_magnitude(const float *x) {
-  unsigned mag = 0;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) mag = umax(mag, ANY ? any_magnitude(x[i]) : magnitude(x[i]));
-#pragma unroll
-  for (int w = 1; w < Geo<DH>::PARTS; w <<= 1) mag = umax(mag, (unsigned)__shfl_xor((int)mag, w, 64));
-  return mag;
-}
-template <int DH, bool ANY>
-__device__ __forceinline__ unsigned tile_row_magnitude(const float *tile) {
-  float x[16];
-  const float *p = tile + threadIdx.x / Geo<DH>::PARTS * Geo<DH>::LS + threadIdx.x % Geo<DH>::PARTS * 16;
-  load8(p, true, x);
-  load8(p + 8, true, x + 8);
-  return row_magnitude<DH, ANY>(x);
-}
-// Rows of a tile of V or dN, times 2^(exponents of the rows), packed with k = tokens: lds.rexp is there, and lds.texp has the
-// largest exponents of the products per token tile, which leave rounded (ey) and go into the operands.
-template <int DH, int PT>
-__device__ __forceinline__ void pack_tokens(PrepLds<DH> &lds, const Dims &s, int t0, half_t *Y, stored_exp *ey) {
-  using G = Geo<DH>;
-  constexpr int NP = G::RB / 32 * 2 * G::CT * 64, NB = c_tiles(DH, PT);
-  const int tid = threadIdx.x, slice = blockIdx.y;
-  auto tile_exponent = [&](int tbl) { return lds.texp[tbl] <= kNone / 2 ? kNone : round_up<8>(lds.texp[tbl]) - kTokensTop; };
-  if (tid < G::RB / 32 && t0 / 32 + tid < s.nt) ey[(int64_t)slice * s.nt + t0 / 32 + tid] = tile_exponent(tid);
-#pragma unroll
-  for (int u = 0; u < NP / G::NT; ++u) {
-    const int p = tid + G::NT * u, lane = p & 63, ct = (p >> 6) % G::CT, a = (p >> 6) / G::CT % 2, tbl = (p >> 6) / (2 * G::CT);
-    const int tb = t0 / 32 + tbl, c = DH == 16 ? lane & 15 : 32 * ct + (lane & 31), h = lane >> 5;
-    if (tb >= s.nt) continue;
-    const int te = max(tile_exponent(tbl), kNone / 2);   // (rows without features become zeros)
-    float x[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int r = tbl * 32 + 16 * a + 8 * (i >> 2) + 4 * h + (i & 3);
-      x[i] = scaled(lds.tile[r * G::LS + c], lds.rexp[r] - te);
-    }
-    op_t t[2];
-    split8h(x, t);
-    half_t *o = Y + ((((int64_t)slice * s.nt + tb) * 2 + a) * G::CT + ct) * NB * kTile;
-    if (DH == 16) {
-      store_operand(o, lane, (lane & 31) < 16 ? t[0] : PT == 2 ? t[1] : op_t{});
-    } else {
-#pragma unroll
-      for (int i = 0; i < NB; ++i) store_operand(o + i * kTile, lane, t[i]);
-    }
-  }
-}
 // Gated Haar filter of one signal (steps 3, 5, 6), split and packed with k = columns.  One thread per (column, 16
-// rows) in the filter, the 32- and 64-row sums through LDS.  X: X_F (may be nullptr); XS: X_F / D_t (may be nullptr), its exponent
-// that of X_F less that of D_t.  The rows' exponents stay in lds.rexp and go to ex (may be nullptr).
+// rows) in the filter, the 32- and 64-row sums through LDS.  X: X_F (may be nullptr); XS: X_F / D_t (may be nullptr).
 template <typename T, int DH>
 __device__ __forceinline__ void filter_pack(PrepLds<DH> &lds, const T *x, const View &v, const Dims &s, int vec, int L,
-                                            const float *coef, const float *add, const float *D, half_t *X, half_t *XS, stored_exp *ex) {
+                                            const float *coef, const float *add, const float *D, bf16_t *X, bf16_t *XS) {
   using G = Geo<DH>;
-  constexpr int LS = G::LS;
-  float(*segsum)[DH] = reinterpret_cast<float(*)[DH]>(lds.part);
-  const int tid = threadIdx.x, slice = blockIdx.y, t0 = blockIdx.x * G::RB;
+  constexpr int CW = G::CW, TR = G::TR, LS = G::LS;
+  float(*segsum)[CW] = reinterpret_cast<float(*)[CW]>(lds.part);
+  const int tid = threadIdx.x, slice = blockIdx.y;
+  const int rg = blockIdx.x / G::PIECES, piece = blockIdx.x % G::PIECES;
+  const int t0 = rg * TR, c0 = piece * CW;
   if (tid < 8) lds.small[tid] = coef[slice * kCoefStride + tid];
-  load_tile<T, DH>(x + v.slice_base(slice), v, s, vec, t0, lds.tile);
+  load_tile<T, DH>(x + v.slice_base(slice), v, s, vec, t0, c0, lds.tile);
   __syncthreads();
-  const int c = tid % DH, seg = tid / DH;
+  const int c = tid % CW, seg = tid / CW;
   float vals[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) vals[i] = lds.tile[(seg * 16 + i) * LS + c];
   segsum[seg][c] = segment_sum<16>(vals);
   __syncthreads();
-  float upper = upper_levels<DH>(segsum, lds.small, seg, c, L);
+  float upper = upper_levels<CW>(segsum, lds.small, seg, c, L);
   const int gt = t0 / 64 + seg / 4, ntl = (s.n + 63) / 64;
-  if (add && gt < ntl && c < s.d) upper += add[((int64_t)slice * ntl + gt) * s.d + c];
+  if (add && gt < ntl && c0 + c < s.d) upper += add[((int64_t)slice * ntl + gt) * s.d + c0 + c];
   filter_segment<16>(vals, lds.small, upper, L);
   // (rows past n must stay zero: they are padding, not output)
 #pragma unroll
   for (int i = 0; i < 16; ++i) lds.tile[(seg * 16 + i) * LS + c] = t0 + seg * 16 + i < s.n ? vals[i] : 0.f;
   __syncthreads();
-  const unsigned mag = tile_row_magnitude<DH, true>(lds.tile);
-  if (tid % G::PARTS == 0) {
-    const int r = tid / G::PARTS, e = row_exponent(mag, x_top(DH));
-    lds.rexp[r] = e;
-    if (ex && t0 + r < 32 * s.nt) ex[(int64_t)slice * 32 * s.nt + t0 + r] = e;
-  }
-  __syncthreads();
+  constexpr int KSL = CW / 16;
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
-    const int p = tid + G::NT * u, lane = p & 63, ks = (p >> 6) % G::KS, tbl = (p >> 6) / G::KS, tb = t0 / 32 + tbl;
+    const int p = tid + 256 * u, lane = p & 63, ksl = (p >> 6) % KSL, tb = t0 / 32 + (p >> 6) / KSL;
     if (tb >= s.nt) continue;
-    const int r = tbl * 32 + (lane & 31);
     float f[8];
-    load8(&lds.tile[r * LS + 16 * ks + 8 * (lane >> 5)], true, f);
-#pragma unroll
-    for (int q = 0; q < 8; ++q) f[q] = scaled_down(f[q], lds.rexp[r]);
-    const int64_t off = (((int64_t)slice * s.nt + tb) * G::KS + ks) * G::XT * kTile;
-    op_t t[3];
+    load8(&lds.tile[(((p >> 6) / KSL) * 32 + (lane & 31)) * LS + 16 * ksl + 8 * (lane >> 5)], true, f);
+    const int64_t off = (((int64_t)slice * s.nt + tb) * G::KS + piece * KSL + ksl) * 3 * kTile;
+    bf16x8 t[3];
     if (X) {
-      if (DH <= 32) split8b(f, t);
-      else split8h(f, t);
+      split8(f, t);
 #pragma unroll
-      for (int i = 0; i < G::XT; ++i) store_operand(X + off + i * kTile, lane, t[i]);
+      for (int i = 0; i < 3; ++i) store_operand(X + off + i * kTile, lane, t[i]);
     }
     if (XS) {
-      const float Dt = t0 + r < s.n ? D[(int64_t)slice * s.n + t0 + r] : 1.f;
-      const float inv = 1.0f / scaled(Dt, 1 - __builtin_amdgcn_frexp_expf(Dt));
+      const int row = 32 * tb + (lane & 31);
+      const float inv = row < s.n ? 1.0f / D[(int64_t)slice * s.n + row] : 1.f;
 #pragma unroll
-      for (int q = 0; q < 8; ++q) f[q] = any_magnitude(inv) < 0x7f800000u ? f[q] * inv : 0.f;   // (D_t = 0 or not finite: see row_exponent)
-      if (DH <= 32) split8b(f, t);
-      else split8h(f, t);
+      for (int q = 0; q < 8; ++q) f[q] *= inv;
+      split8(f, t);
 #pragma unroll
-      for (int i = 0; i < G::XT; ++i) store_operand(XS + off + i * kTile, lane, t[i]);
+      for (int i = 0; i < 3; ++i) store_operand(XS + off + i * kTile, lane, t[i]);
     }
   }
 }
 
-// Forward operands: Q_F and K_F packed with k = columns, V times 2^(exponents of K_F's rows) packed with k = tokens.
-// Grid (row groups, slices, 2: Q; K and V).
+// Forward operands: Q_F and K_F packed with k = columns, V packed with k = tokens.
+// Grid (row groups * column pieces, slices, 3: Q, K, V).
 template <typename T, int DH, int PT>
-__global__ __launch_bounds__(Geo<DH>::NT) void prep_fwd_kernel(const T *q, const T *k, const T *vv, View v, Dims s, int vec, int L,
-                                                              const float *coef, const float *addQ, const float *addK,
-                                                              half_t *XQ, half_t *XK, half_t *VC, stored_exp *exQ, stored_exp *exK,
-                                                              stored_exp *ey) {
+__global__ __launch_bounds__(256) void prep_fwd_kernel(const T *q, const T *k, const T *vv, View v, Dims s, int vec, int L,
+                                                      const float *coef, const float *addQ, const float *addK,
+                                                      bf16_t *XQ, bf16_t *XK, bf16_t *VC) {
   using G = Geo<DH>;
+  constexpr int CW = G::CW, TR = G::TR, LS = G::LS;
   __shared__ __attribute__((aligned(16))) PrepLds<DH> lds;
-  if (blockIdx.z == 0) {
-    filter_pack<T, DH>(lds, q, v, s, vec, L, coef, addQ, nullptr, XQ, nullptr, exQ);
+  const int side = blockIdx.z;
+  if (side < 2) {
+    filter_pack<T, DH>(lds, side ? k : q, v, s, vec, L, coef, side ? addK : addQ, nullptr, side ? XK : XQ, nullptr);
     return;
   }
-  filter_pack<T, DH>(lds, k, v, s, vec, L, coef, addK, nullptr, XK, nullptr, exK);
-  const int tid = threadIdx.x, t0 = blockIdx.x * G::RB;
-  if (tid < G::RB / 32) lds.texp[tid] = kNone;
+  const int tid = threadIdx.x, slice = blockIdx.y;
+  const int rg = blockIdx.x / G::PIECES, piece = blockIdx.x % G::PIECES;
+  const int t0 = rg * TR, c0 = piece * CW;
+  load_tile<T, DH>(vv + v.slice_base(slice), v, s, vec, t0, c0, lds.tile);
   __syncthreads();
-  load_tile<T, DH>(vv + v.slice_base(blockIdx.y), v, s, vec, t0, lds.tile);
-  __syncthreads();
-  const unsigned mag = tile_row_magnitude<DH, false>(lds.tile);
-  const int r = tid / G::PARTS;
-  if (tid % G::PARTS == 0) atomicMax(&lds.texp[r / 32], exponent(mag) + lds.rexp[r]);
-  __syncthreads();
-  pack_tokens<DH, PT>(lds, s, t0, VC, ey);
+  constexpr int CTL = CW < 32 ? 1 : CW / 32, NP = TR / 32 * 2 * CTL * 64;
+#pragma unroll
+  for (int u = 0; u < NP / 256; ++u) {
+    const int p = tid + 256 * u, lane = p & 63, ctl = (p >> 6) % CTL, a = (p >> 6) / CTL % 2, tbl = (p >> 6) / (2 * CTL);
+    const int tb = t0 / 32 + tbl, c = 32 * ctl + (lane & 31), h = lane >> 5;
+    if (tb >= s.nt) continue;
+    float x[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int r = tbl * 32 + 16 * a + 8 * (i >> 2) + 4 * h + (i & 3);
+      // (head dimension 16: column 16 of the 32 is the column of ones that gives z)
+      x[i] = c < CW ? lds.tile[r * LS + c] : (c == 16 ? 1.f : 0.f);
+    }
+    bf16x8 t[3];
+    split8(x, t);
+    bf16_t *o = VC + ((((int64_t)slice * s.nt + tb) * 2 + a) * G::CT + piece * CTL + ctl) * PT * kTile;
+#pragma unroll
+    for (int i = 0; i < PT; ++i) store_operand(o + i * kTile, lane, t[i]);
+  }
 }
 
 // ------------------------------------------------------------------------------------
 // Backward operands.  blockIdx.z = 0, per row: <dO_t, O_t>, then dN_t and dD_t; dN packed with k = tokens for dS.
 //   PT == 1 (bf16 storage): dN stays dO, one exact term; 1 / D_t goes into the rows of Q_F of the dS
 //   product (XS; ReLU is positively homogeneous) and into the scale of the rows of dQ_F (rowscale), so
-//   ddw is then -<dO_t, O_t>.   PT == 2: dN = dO / D in float32, ddw = dD_t = -<dO_t, O_t> / D_t.
+//   ddw is then -<dO_t, O_t>.   PT == 3: dN = dO / D in float32, ddw = dD_t = -<dO_t, O_t> / D_t.
 //   With the LayerNorm output stage: dN = rstd (dO - mean dO - O mean(dO O)), ddw = 0.
-// wz: the weights of dz, ddw times 2^(exponent of the row of the dS product).
 // part[slice][workgroup]: sum of the per-row term of d sigma (dD_t, or -<dO_t, O_t> rstd_t^2).
-// XS or, with two terms and where the forward has not kept it (see keeps_operands), Q_F as the forward packs it, comes first: the
-// exponents of its rows go into dN.  blockIdx.z = 1: K_F and its exponents, likewise.  dN and V with k = columns are not
+// blockIdx.z = 1: XS or, with three terms, Q_F as the forward packs it; 2: K_F (see keeps_operands).  dN and V with k = columns are not
 // packed: the gradient kernel reads each of their rows once, in the order in which they are stored.
-// Grid (row groups, slices, 1 or 2).
+// Grid (row groups, slices, 1 to 3); the row groups of both forms are the same in number.
 // ------------------------------------------------------------------------------------
 template <typename T, int DH, int PT>
-__global__ __launch_bounds__(Geo<DH>::NT) void prep_bwd_kernel(const T *dout, const T *out, const T *q, const T *k, View v, Dims s, int vec,
-                                                              int ln, int L, const float *coef, const float *addQ, const float *addK,
-                                                              const float *D, const stored_exp *exQ, half_t *NC, stored_exp *ey, half_t *XQ,
-                                                              half_t *XS, half_t *XK, stored_exp *exK, float *ddw, float *wz, float *rowscale, float *part) {
+__global__ __launch_bounds__(256) void prep_bwd_kernel(const T *dout, const T *out, const T *q, const T *k, View v, Dims s, int vec,
+                                                      int ln, int L, const float *coef, const float *addQ, const float *addK,
+                                                      const float *D, bf16_t *NC, bf16_t *XQ, bf16_t *XS, bf16_t *XK, float *ddw,
+                                                      float *rowscale, float *part) {
   using G = Geo<DH>;
   __shared__ __attribute__((aligned(16))) PrepLds<DH> lds;
   if (blockIdx.z) {
-    filter_pack<T, DH>(lds, k, v, s, vec, L, coef, addK, nullptr, XK, nullptr, exK);
+    if (blockIdx.z == 1) filter_pack<T, DH>(lds, q, v, s, vec, L, coef, addQ, D, XQ, XS);
+    else filter_pack<T, DH>(lds, k, v, s, vec, L, coef, addK, nullptr, XK, nullptr);
     return;
   }
-  if (XQ || XS) {
-    filter_pack<T, DH>(lds, q, v, s, vec, L, coef, addQ, D, XQ, XS, nullptr);
-    __syncthreads();
-  }
-  constexpr int PARTS = G::PARTS, LS = G::LS;
-  float *tile = lds.tile, *red = lds.small;
-  const int tid = threadIdx.x, slice = blockIdx.y, t0 = blockIdx.x * G::RB;
+  constexpr int RB = PrepLds<DH>::RB, PARTS = DH / 16, LS = DH + 4;
+  static_assert(RB <= 256, "one weight per row in LDS");
+  float *tile = lds.tile, *wrow = lds.part, *red = lds.small;
+  const int tid = threadIdx.x, slice = blockIdx.y, t0 = blockIdx.x * RB;
   const int r = tid / PARTS, pc = tid % PARTS * 16, t = t0 + r;
   const bool ok = t < s.n && pc < s.d;
   const int64_t base = v.slice_base(slice) + (int64_t)(t < s.n ? t : 0) * v.sn + (pc < s.d ? pc : 0);
-  if (tid < G::RB / 32) lds.texp[tid] = kNone;
   float g[16], o[16];
   load8(dout + base, vec, g);
   load8(dout + base + 8, vec, g + 8);
@@ -681,7 +566,6 @@ __global__ __launch_bounds__(Geo<DH>::NT) void prep_bwd_kernel(const T *dout, co
     sum += __shfl_xor(sum, w, 64);
   }
   const float Dt = t < s.n ? D[(int64_t)slice * s.n + t] : 1.f;
-  int ex = XQ || XS ? lds.rexp[r] : t < 32 * s.nt ? (int)exQ[(int64_t)slice * 32 * s.nt + t] : 0;
   float w = 0.f, sig, inv = 1.f;
   if (ln) {
     const float m1 = sum / (float)s.d, m2 = dot / (float)s.d;
@@ -692,14 +576,12 @@ __global__ __launch_bounds__(Geo<DH>::NT) void prep_bwd_kernel(const T *dout, co
     w = -dot;
     inv = 1.0f / Dt;
     sig = w * inv;
-    ex += 1 - __builtin_amdgcn_frexp_expf(Dt);   // (of XS)
   } else {
 #pragma unroll
     for (int i = 0; i < 16; ++i) g[i] = g[i] / Dt;
     w = sig = -dot / Dt;
   }
   if (t >= s.n) w = sig = 0.f;
-  const unsigned mag = row_magnitude<DH, false>(g);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     f32x4 x;
@@ -707,15 +589,11 @@ __global__ __launch_bounds__(Geo<DH>::NT) void prep_bwd_kernel(const T *dout, co
     for (int j = 0; j < 4; ++j) x[j] = g[4 * i + j];
     *reinterpret_cast<f32x4 *>(&tile[r * LS + pc + 4 * i]) = x;
   }
-  __syncthreads();
   if (pc == 0) {
-    lds.rexp[r] = ex;
-    atomicMax(&lds.texp[r / 32], exponent(mag) + ex);
+    wrow[r] = w;
     if (t < 32 * s.nt) {
-      const int64_t row = (int64_t)slice * 32 * s.nt + t;
-      ddw[row] = w;
-      wz[row] = scaled(w, ex);
-      if (PT == 1) rowscale[row] = inv;
+      ddw[(int64_t)slice * 32 * s.nt + t] = w;
+      if (PT == 1) rowscale[(int64_t)slice * 32 * s.nt + t] = inv;
     }
   } else {
     sig = 0.f;
@@ -723,87 +601,88 @@ __global__ __launch_bounds__(Geo<DH>::NT) void prep_bwd_kernel(const T *dout, co
   sig = wave_sum(sig);
   if ((tid & 63) == 0) red[tid >> 6] = sig;
   __syncthreads();
-  if (tid == 0) {
-    float sum_all = (red[0] + red[1]) + (red[2] + red[3]);
-    if (G::NT == 512) sum_all += (red[4] + red[5]) + (red[6] + red[7]);
-    part[(int64_t)slice * gridDim.x + blockIdx.x] = sum_all;
+  if (tid == 0) part[(int64_t)slice * gridDim.x + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+  constexpr int NP = RB / 32 * 2 * G::CT * 64;
+#pragma unroll
+  for (int u = 0; u < NP / 256; ++u) {   // k = tokens
+    const int p = tid + 256 * u, lane = p & 63, ct = (p >> 6) % G::CT, a = (p >> 6) / G::CT % 2, tbl = (p >> 6) / (2 * G::CT);
+    const int tb = t0 / 32 + tbl, c = 32 * ct + (lane & 31), h = lane >> 5;
+    if (tb >= s.nt) continue;
+    float x[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int rr = tbl * 32 + 16 * a + 8 * (i >> 2) + 4 * h + (i & 3);
+      // (head dimension 16: the weights w_t of dz = Phi^T w sit in column 16, with one term per operand in
+      // columns 16, 17, 18)
+      x[i] = c < DH ? tile[rr * LS + (c < DH ? c : 0)] : (c < (PT == 1 ? 19 : 17) ? wrow[rr] : 0.f);
+    }
+    bf16x8 tt[3];
+    split8(x, tt);
+    if (DH == 16 && PT == 1) {
+      if (c == 17) tt[0] = tt[1];
+      if (c == 18) tt[0] = tt[2];
+    }
+    bf16_t *dd = NC + ((((int64_t)slice * s.nt + tb) * 2 + a) * G::CT + ct) * PT * kTile;
+#pragma unroll
+    for (int i = 0; i < PT; ++i) store_operand(dd + i * kTile, lane, tt[i]);
   }
-  pack_tokens<DH, PT>(lds, s, t0, NC, ey);
 }
 
 // ------------------------------------------------------------------------------------
 // part[slice][p][f][c] = sum over the p-th share of the tokens of ReLU(X Omega)[t, f] Y[t, c], and the
-// same against the weights w_t (w, or 2^(exponent of the row) where it is nullptr) into zpart[slice][p][f].  Eight waves: FW of
-// them own one feature tile each, and TW such groups take the token
+// same against the weights w_t (1 where w is nullptr) into zpart[slice][p][f]; head dimension 16 has that
+// column among the 32 of Y.  Eight waves: FW of them own one feature tile each, and TW such groups take the token
 // tiles of a stage in turn (each group a share of its own).  X and Y go through LDS, one stage of SG token
 // tiles ahead in registers; Omega stays in registers.  Grid (splits, feature tiles / FW, slices).
 // ------------------------------------------------------------------------------------
 // Token tiles (32 rows) per stage: the double-buffered stage stays below 100 KiB of LDS, and below 50 KiB where that lets
-// the registers of a second workgroup in.
-constexpr int stage_tokens(int DH, int PT) { return DH == 128 ? 1 : (DH == 64 || (DH == 32 && PT == 2) ? 2 : 4); }
-// Exponents of the largest values of the shares' tiles of S and z, [slices][shares][feature tiles], times 2^(exponent of the
-// feature that they will meet).
-struct ShareExps {
-  stored_exp *S, *z;
-};
+// the registers of a second workgroup in (head dimension 32 with three terms: 359 -> 334 us with half the stage).
+constexpr int stage_tokens(int DH, int PT) { return DH == 128 ? 1 : (DH == 64 || (DH == 32 && PT == 3) ? 2 : 4); }
 template <int DH, int PT>
-__global__ __launch_bounds__(512, 2) void contract_kernel(const half_t *X, const half_t *Y, const stored_exp *ey, const float *w, const stored_exp *ex,
-                                                         const half_t *OA, const stored_exp *ge, const stored_exp *go, Dims s, int FW, int TW,
-                                                         int tiles_per_split, float *part, float *zpart, ShareExps pe) {
+__global__ __launch_bounds__(512, 2) void contract_kernel(const bf16_t *X, const bf16_t *Y, const float *w, const bf16_t *OA,
+                                                         Dims s, int FW, int TW, int tiles_per_split, float *part, float *zpart) {
   using G = Geo<DH>;
-  constexpr int SG = stage_tokens(DH, PT), OT = o_terms(DH, PT), NB = c_tiles(DH, PT), NX = G::KS * G::XT, NY = 2 * G::CT * NB,
-                NS = SG * (NX + NY), NW = 8, U = (NS + NW - 1) / NW;
-  constexpr bool LO = DH <= 64 && !(DH == 32 && PT == 2);   // (where its registers cost no wave)
-  __shared__ __attribute__((aligned(16))) half_t lds[2][NS * kTile];
+  constexpr int SG = stage_tokens(DH, PT), NX = G::KS * 3, NY = 2 * G::CT * PT, NS = SG * (NX + NY),
+                NW = 8, U = (NS + NW - 1) / NW;
+  __shared__ __attribute__((aligned(16))) bf16_t lds[2][NS * kTile];
   __shared__ __attribute__((aligned(16))) float lw[2][SG * 32];
-  __shared__ stored_exp le[2][SG];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slice = blockIdx.z, fw = wave % FW, tw = wave / FW;
   const int ft = blockIdx.y * FW + fw;
   const int tb0 = blockIdx.x * tiles_per_split, tb1 = min(s.nt, tb0 + tiles_per_split);
-  const half_t *xs = X + (int64_t)slice * s.nt * NX * kTile, *ys = Y + (int64_t)slice * s.nt * NY * kTile;
-  const stored_exp *es = ey + (int64_t)slice * s.nt;
-  op_t om[G::KS][OT];
+  const bf16_t *xs = X + (int64_t)slice * s.nt * NX * kTile, *ys = Y + (int64_t)slice * s.nt * NY * kTile;
+  bf16x8 om[G::KS][PT];
 #pragma unroll
   for (int ks = 0; ks < G::KS; ++ks)
 #pragma unroll
-    for (int i = 0; i < OT; ++i) om[ks][i] = lds_operand(OA + (((int64_t)ft * G::KS + ks) * OT + i) * kTile, lane);
-  op_t st[U];
+    for (int i = 0; i < PT; ++i) om[ks][i] = lds_operand(OA + (((int64_t)ft * G::KS + ks) * PT + i) * kTile, lane);
+  u32x4 st[U];
   float stw = 0.f;
-  stored_exp ste = {0};
   auto fetch = [&](int tb) {   // (consecutive token tiles are contiguous; what lies past the slice is clamped and not used)
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int i = min(wave + NW * u, NS - 1);   // (no branch: a last tile may be moved twice)
       const int64_t tile = i < SG * NX ? min(tb * NX + i, s.nt * NX - 1) : min(tb * NY + i - SG * NX, s.nt * NY - 1);
-      st[u] = *reinterpret_cast<const op_t *>((i < SG * NX ? xs : ys) + tile * kTile + lane * 8);
+      st[u] = *reinterpret_cast<const u32x4 *>((i < SG * NX ? xs : ys) + tile * kTile + lane * 8);
     }
-    const int64_t row = (int64_t)slice * s.nt * 32 + min(tb * 32 + (tid & (SG * 32 - 1)), s.nt * 32 - 1);
-    stw = w ? w[row] : scaled(1.f, ex[row]);
-    ste = es[min(tb + (tid & (SG - 1)), s.nt - 1)];
+    if (DH > 16 && w) stw = w[(int64_t)slice * s.nt * 32 + min(tb * 32 + (tid & (SG * 32 - 1)), s.nt * 32 - 1)];
   };
   auto put = [&](int b) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int i = min(wave + NW * u, NS - 1);
-      *reinterpret_cast<op_t *>(&lds[b][i * kTile + lane * 8]) = st[u];
+      *reinterpret_cast<u32x4 *>(&lds[b][i * kTile + lane * 8]) = st[u];
     }
-    lw[b][tid & (SG * 32 - 1)] = stw;
-    le[b][tid & (SG - 1)] = ste;
+    if (DH > 16) lw[b][tid & (SG * 32 - 1)] = w ? stw : 1.f;
   };
-  f32x16 acc[G::CT], lo[LO ? G::CT : 1];
+  f32x16 acc[G::CT];
 #pragma unroll
-  for (int ct = 0; ct < G::CT; ++ct) {
-    acc[ct] = zero16();
-    if (LO) lo[ct] = zero16();
-  }
+  for (int ct = 0; ct < G::CT; ++ct) acc[ct] = zero16();
   float zacc = 0.f;
-  int E = kNone;   // of this workgroup's tiles of Y, the largest
+  const NegIdentity ni(lane);
   if (tb0 < tb1) {
     fetch(tb0);
-    for (int tb = tb0 + lane; tb < tb1; tb += 64) E = max(E, (int)es[tb]);
-    E = wave_max(E);
     put(0);
     wait_loads();
     __syncthreads();
@@ -812,30 +691,30 @@ __global__ __launch_bounds__(512, 2) void contract_kernel(const half_t *X, const
       const bool more = tb + SG < tb1;
       if (more) fetch(tb + SG);
       for (int g = tw < TW ? tw : SG; g < SG && tb + g < tb1; g += TW) {
-        const half_t *lx = &lds[b][g * NX * kTile], *ly = &lds[b][(SG * NX + g * NY) * kTile];
-        const int e = __builtin_amdgcn_readfirstlane((int)le[b][g]);
-        f32x16 R = project<DH, PT, false>([&](int ks, int i) { return lds_operand(lx + (ks * G::XT + i) * kTile, lane); },
-                                          [&](int ks, int i) { return om[ks][i]; });   // rows: tokens, columns (lanes): features
+        const bf16_t *lx = &lds[b][g * NX * kTile], *ly = &lds[b][(SG * NX + g * NY) * kTile];
+        f32x16 R = zero16();
+#pragma unroll
+        for (int ks = 0; ks < G::KS; ++ks) {
+          bf16x8 x[3];
+#pragma unroll
+          for (int i = 0; i < 3; ++i) x[i] = lds_operand(lx + (ks * 3 + i) * kTile, lane);
+          R = mfma_terms<PT, false>(R, x, om[ks]);   // rows: tokens, columns (lanes): features
+        }
 #pragma unroll
         for (int i = 0; i < 16; ++i) R[i] = relu(R[i]);
-        f32x4 w4[4];
+        if (DH > 16) {
+          f32x4 w4[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) w4[j] = *reinterpret_cast<const f32x4 *>(&lw[b][g * 32 + 8 * j + 4 * h]);
-        zacc += dot16(R, w4);
-        asm volatile("" : "+v"(zacc));   // (a branch, with the product before it: multiplying and selecting always doubles the vector units' work)
-        if (e != E) {
-          asm volatile("");
-          const float f = scaled(1.f, e - E);
-#pragma unroll
-          for (int i = 0; i < 16; ++i) R[i] *= f;
+          for (int j = 0; j < 4; ++j) w4[j] = *reinterpret_cast<const f32x4 *>(&lw[b][g * 32 + 8 * j + 4 * h]);
+          zacc += dot16(R, w4);
         }
-        with_split(R, [&](int a, const op_t *p) {
+        with_split<mfma_residuals(DH, PT)>(R, ni, [&](int a, const bf16x8 *p) {
 #pragma unroll
           for (int ct = 0; ct < G::CT; ++ct) {
-            op_t y[NB];
+            bf16x8 y[PT];
 #pragma unroll
-            for (int i = 0; i < NB; ++i) y[i] = lds_operand(ly + ((a * G::CT + ct) * NB + i) * kTile, lane);
-            add_terms<NB>(acc[ct], LO ? lo[ct] : acc[ct], p, y);   // rows: features, columns: columns of Y
+            for (int i = 0; i < PT; ++i) y[i] = lds_operand(ly + ((a * G::CT + ct) * PT + i) * kTile, lane);
+            acc[ct] = mfma_terms<PT, false>(acc[ct], p, y);   // rows: features, columns: columns of Y
           }
         });
       }
@@ -845,28 +724,15 @@ __global__ __launch_bounds__(512, 2) void contract_kernel(const half_t *X, const
   }
   if (tw >= TW) return;
   const int64_t pidx = (int64_t)slice * gridDim.x * TW + blockIdx.x * TW + tw;
-  constexpr int PW = part_width(DH, PT);
+  constexpr int PW = 32 * G::CT;
   float *po = part + (pidx * s.mt + ft) * 32 * PW;
-  int big = kNone;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int f = 8 * (i >> 2) + 4 * h + (i & 3), e = E + ge[ft * 32 + f];
-    unsigned mag = 0;
+  for (int ct = 0; ct < G::CT; ++ct)
 #pragma unroll
-    for (int ct = 0; ct < G::CT; ++ct) {
-      const float x = scaled(LO ? acc[ct][i] + lo[ct][i] : acc[ct][i], e);
-      if (PW >= 32 || l32 < PW) po[f * PW + 32 * ct + l32] = x;
-      mag = umax(mag, magnitude(x));
-    }
-    big = max(big, exponent(mag) + go[ft * 32 + f]);
-  }
-  zacc = scaled(xor32_sum(zacc), ge[ft * 32 + l32]);
-  if (h == 0) zpart[(pidx * s.mt + ft) * 32 + l32] = zacc;
-  big = wave_max(big);
-  const int zbig = wave_max(exponent(magnitude(zacc)) + go[ft * 32 + l32]);
-  if (lane == 0) {
-    pe.S[pidx * s.mt + ft] = big;
-    pe.z[pidx * s.mt + ft] = zbig;
+    for (int i = 0; i < 16; ++i) po[(8 * (i >> 2) + 4 * h + (i & 3)) * PW + 32 * ct + l32] = acc[ct][i];
+  if (DH > 16) {
+    zacc = xor32_sum(zacc);
+    if (h == 0) zpart[(pidx * s.mt + ft) * 32 + l32] = zacc;
   }
 }
 
@@ -874,9 +740,7 @@ __global__ __launch_bounds__(512, 2) void contract_kernel(const half_t *X, const
 // S (or dS) and z (or dz) of one feature tile: fixed-order sum of the shares, times c; in the forward the float32
 // results [m][d] and [m], and the operand tiles of the kernels that follow: columns as vectors with k = features (SB);
 // in the backward also features as vectors (SA) with the extension tile that carries the rank-one term dD z^T
-// (three-term bf16 products in six k-slots: its two sides differ in magnitude by what V has), for dS and, from the forward's S
-// and z (blockIdx.z = 1), S.  All of these times 2^(ge - es): ge of the features that they will meet, es of the slice, so that no
-// value of S is above 2^kSTop: from the largest value of a share, times their number.  ez: the same of z, without the top.
+// (three-term products in six k-slots), for dS and, from the forward's S and z (blockIdx.z = 1), SAin.
 // Grid (feature tiles, slices, forward 1, backward 2).
 // ------------------------------------------------------------------------------------
 // Sum of the values at p, p + step, ...: eight at a time (in flight together) as a tree, eight of these in a chain, and a
@@ -898,26 +762,18 @@ __device__ __forceinline__ V sum_shares(const float *p, int64_t step, int shares
   for (; sh < shares; ++sh) part += *reinterpret_cast<const V *>(p + sh * step);
   return acc + part;
 }
-struct SOperands {
-  const stored_exp *ge;   // exponents of the features
-  half_t *SA, *SB;        // (SA: backward only)
-  stored_exp *es, *ez;    // [slices]
-};
-template <int DH, int PT>
-__global__ __launch_bounds__(256) void reduce_kernel(const float *part, const float *zpart, int shares, const float *scalars, Dims s,
-                                                    float *S, float *z, float *zpad, ShareExps pe, SOperands main, SOperands fwd) {
+template <int DH>
+__global__ __launch_bounds__(256) void reduce_kernel(const float *part, const float *zpart, int shares, int zcols,
+                                                    const float *scalars, Dims s, float *S, float *z, float *zpad,
+                                                    bf16_t *SA, bf16_t *SB, bf16_t *SAin) {
   using G = Geo<DH>;
-  constexpr int PW = part_width(DH, PT), LS = PW + 1;
+  constexpr int PW = 32 * G::CT, LS = PW + 1;
   __shared__ float tile[32 * LS];
   __shared__ float zt[32];
-  __shared__ int red[8], ges[32];
   const int tid = threadIdx.x, ft = blockIdx.x, slice = blockIdx.y;
-  const bool given = blockIdx.z;   // S and z are there already
-  const SOperands &o = given ? fwd : main;
+  const bool given = SAin && blockIdx.z;   // S and z are there already
   const float c = scalars[0];
-  if (tid < 32) ges[tid] = o.ge[ft * 32 + tid];
   if (given) {
-    if (tid == 0) red[0] = o.es[slice];
     for (int e = tid; e < 32 * DH; e += 256) {
       const int f = e / DH, cc = e % DH;
       tile[f * LS + cc] = (32 * ft + f < s.m && cc < s.d) ? S[((int64_t)slice * s.m + 32 * ft + f) * s.d + cc] : 0.f;
@@ -927,82 +783,67 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float *part, const fl
   } else {
     const int64_t step = (int64_t)s.mt * 32 * PW;
     const float *p0 = part + ((int64_t)slice * shares * s.mt + ft) * 32 * PW;
-    for (int e = tid * 4; e < 32 * PW; e += 1024) {
+#pragma unroll
+    for (int u = 0; u < 32 * PW / 1024; ++u) {
+      const int e = (tid + 256 * u) * 4;
       const f32x4 acc = sum_shares<f32x4>(p0 + e, step, shares);
 #pragma unroll
       for (int i = 0; i < 4; ++i) tile[(e / PW) * LS + e % PW + i] = acc[i] * c;
     }
-    if (tid < 32)
+    if (DH > 16 && tid < 32)
       zt[tid] = sum_shares<float>(zpart + ((int64_t)slice * shares * s.mt + ft) * 32 + tid, (int64_t)s.mt * 32, shares) * c;
-    int big = kNone, zbig = kNone;
-    for (int e = tid; e < shares * s.mt; e += 256) {
-      big = max(big, (int)pe.S[(int64_t)slice * shares * s.mt + e]);
-      zbig = max(zbig, (int)pe.z[(int64_t)slice * shares * s.mt + e]);
-    }
-    big = wave_max(big);
-    zbig = wave_max(zbig);
-    if ((tid & 63) == 0) {
-      red[tid >> 6] = big;
-      red[4 + (tid >> 6)] = zbig;
+    __syncthreads();
+    if (DH == 16 && tid < 32) {
+      float acc = 0.f;
+      for (int j = zcols - 1; j >= 0; --j) acc += tile[tid * LS + 16 + j];
+      zt[tid] = acc;
     }
     __syncthreads();
-    if (DH < PW) {   // the columns of the second term
-      for (int e = tid; e < 32 * DH; e += 256) tile[e / DH * LS + e % DH] += tile[e / DH * LS + DH + e % DH];
-      __syncthreads();
-    }
-    if (zpad) {   // forward
+    if (!SAin) {   // forward
       for (int e = tid; e < 32 * s.d; e += 256) {
         const int f = e / s.d, cc = e % s.d;
         if (32 * ft + f < s.m) S[((int64_t)slice * s.m + 32 * ft + f) * s.d + cc] = tile[f * LS + cc];
       }
       if (tid < 32) {
         if (32 * ft + tid < s.m) z[(int64_t)slice * s.m + 32 * ft + tid] = zt[tid];
-        zpad[((int64_t)slice * s.mt + ft) * 32 + tid] = scaled(zt[tid], ges[tid]);
+        zpad[((int64_t)slice * s.mt + ft) * 32 + tid] = zt[tid];
       }
     }
   }
-  int es = red[0];
-  if (!given) {
-    const int more = 32 - __clz(shares) + __builtin_amdgcn_frexp_expf(c);
-    const int ez = max(max(red[4], red[5]), max(red[6], red[7])) + more;
-    es = max(max(max(red[0], red[1]), max(red[2], red[3])) + more - kSTop, ez - 110);   // (z in the units of S is a float)
-    if (tid == 0 && ft == 0) {
-      o.es[slice] = es;
-      o.ez[slice] = ez;
-    }
-  }
-  half_t *sa = o.SA + ((int64_t)slice * s.mt + ft) * G::NSA * kTile;
-  half_t *sb = o.SB + ((int64_t)slice * s.mt + ft) * G::NSB * kTile;
-  const int first = o.SA ? 0 : G::KS + 1, last = o.SB ? G::KS + 1 + 2 * G::CT : G::KS + 1;
+  bf16_t *sa = (given ? SAin : SA) + ((int64_t)slice * s.mt + ft) * (3 * G::KS + 1) * kTile;
+  bf16_t *sb = SB + ((int64_t)slice * s.mt + ft) * G::NSB * kTile;
+  const int first = SA ? 0 : G::KS + 1, last = given ? G::KS + 1 : G::KS + 1 + 2 * G::CT;   // (the forward needs SB only)
   for (int p = tid + 64 * first; p < 64 * last; p += 256) {
     const int lane = p & 63, which = p >> 6, l32 = lane & 31, h = lane >> 5;
-    float x[8];
-    op_t t[2];
+    bf16x8 t[3];
     if (which < G::KS) {
+      float x[8];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) x[q] = scaled(tile[l32 * LS + 16 * which + 8 * h + q], ges[l32] - es);
-      split8h(x, t);
+      for (int q = 0; q < 8; ++q) x[q] = tile[l32 * LS + 16 * which + 8 * h + q];
+      split8(x, t);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) store_operand(sa + (2 * which + i) * kTile, lane, t[i]);
+      for (int i = 0; i < 3; ++i) store_operand(sa + (3 * which + i) * kTile, lane, t[i]);
     } else if (which == G::KS) {
       __bf16 zz[3];
-      split1b(h == 0 ? scaled(zt[l32], ges[l32] - es) : 0.f, zz);
-      const __bf16 none = (__bf16)0.f;
-      const bf16x8 e = {zz[0], zz[1], zz[0], zz[2], zz[0], zz[1], none, none};
-      store_operand(sa + 2 * G::KS * kTile, lane, __builtin_bit_cast(op_t, e));
+      split1(h == 0 ? zt[l32] : 0.f, zz);
+      const __bf16 o = (__bf16)0.f;
+      const bf16x8 e = {zz[0], zz[1], zz[0], zz[2], zz[0], zz[1], o, o};
+      store_operand(sa + 3 * G::KS * kTile, lane, e);
     } else {
       const int a = (which - G::KS - 1) / G::CT, ct = (which - G::KS - 1) % G::CT, cc = 32 * ct + l32;
+      float x[8];
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
-        const int f = 16 * a + 8 * (q >> 2) + 4 * h + (q & 3);
-        x[q] = scaled(tile[f * LS + (DH == 16 ? cc & 15 : cc)], ges[f] - es + kSBShift);
+        x[q] = tile[(16 * a + 8 * (q >> 2) + 4 * h + (q & 3)) * LS + (DH == 16 ? cc & 15 : cc)];
       }
-      split8h(x, t);
+      split8(x, t);
       if (DH == 16) {
-        store_operand(sb + a * kTile, lane, cc < 16 ? t[0] : t[1]);
+        const bf16x8 none = {};
+        store_operand(sb + 2 * a * kTile, lane, cc < 16 ? t[0] : t[1]);
+        store_operand(sb + (2 * a + 1) * kTile, lane, cc < 16 ? t[2] : none);
       } else {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) store_operand(sb + ((a * G::CT + ct) * 2 + i) * kTile, lane, t[i]);
+        for (int i = 0; i < 3; ++i) store_operand(sb + ((a * G::CT + ct) * 3 + i) * kTile, lane, t[i]);
       }
     }
   }
@@ -1017,67 +858,64 @@ template <int N0, int N1, int N2, int N3, int FC, int NW>
 struct Stager {
   static constexpr int NS = FC * (N0 + N1 + N2 + N3), U = (NS + NW - 1) / NW;
   static constexpr int O1 = FC * N0, O2 = O1 + FC * N1, O3 = O2 + FC * N2;   // first tile of each section in LDS
-  const half_t *p0, *p1, *p2, *p3;
-  op_t st[U];
+  const bf16_t *p0, *p1, *p2, *p3;
+  u32x4 st[U];
   __device__ __forceinline__ void fetch(int ft, int wave, int lane) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int i = min(wave + NW * u, NS - 1);   // (no branch: a last tile may be moved twice)
-      const half_t *src = i < O1   ? p0 + ((int64_t)ft * N0 + i) * kTile
+      const bf16_t *src = i < O1   ? p0 + ((int64_t)ft * N0 + i) * kTile
                           : i < O2 ? p1 + ((int64_t)ft * N1 + (i - O1)) * kTile
                           : i < O3 ? p2 + ((int64_t)ft * N2 + (i - O2)) * kTile
                                    : p3 + ((int64_t)ft * N3 + (i - O3)) * kTile;
-      st[u] = *reinterpret_cast<const op_t *>(src + lane * 8);
+      st[u] = *reinterpret_cast<const u32x4 *>(src + lane * 8);
     }
   }
-  __device__ __forceinline__ void put(half_t *lds, int wave, int lane) const {
+  __device__ __forceinline__ void put(bf16_t *lds, int wave, int lane) const {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int i = min(wave + NW * u, NS - 1);
-      *reinterpret_cast<op_t *>(&lds[i * kTile + lane * 8]) = st[u];
+      *reinterpret_cast<u32x4 *>(&lds[i * kTile + lane * 8]) = st[u];
     }
   }
 };
 
-// A sum over the features is taken sum_tiles feature tiles at a time where the registers hold a second accumulator: the
-// matrix cores round an accumulator after every product (and a little towards zero), and with one for the whole sum its error
-// grows with the square root of m.  With one-term operands the results are rounded to bf16, and the registers are worth more.
-constexpr int sum_tiles(int DH) { return DH <= 32 ? 4 : 1; }
-constexpr bool sum_in_parts(int PT) { return PT == 2; }
+// Whether the small terms have an accumulator of their own (see apply_terms): with one-term operands the results are
+// rounded to bf16, and the registers are worth more (head dimension 16, 8 slices of 131072 tokens: 382 us without, 397 with).
+constexpr bool low_terms(int PT) { return PT == 3; }
 // Waves per SIMD that the register budget is set for.
 constexpr int row_occupancy(int DH, int NW) { return NW >= 4 && DH < 128 ? 2 : 1; }
 
 // MODE 0: O = (Phi S) / (Phi z + eps) and D.   1: N = Phi S in float32 (LayerNorm follows).
-// MODE 2: dV = Phi_K dS.     X: operand tiles of Q_F or K_F, ex their rows' exponents.  Grid (row groups, slices).
+// MODE 2: dV = Phi_K dS.     X: operand tiles of Q_F or K_F.  Grid (row groups, slices).
 template <typename T, int DH, int PT, int MODE, int RT, int NW>
-__global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(const half_t *X, const stored_exp *ex, const half_t *OA,
-                                                                       const half_t *SB, const stored_exp *es, const float *zpad,
-                                                                       const float *scalars, float eps, Dims s, T *out, View v,
-                                                                       float *N, float *D) {
+__global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(const bf16_t *X, const bf16_t *OA, const bf16_t *SB,
+                                                                       const float *zpad, const float *scalars, float eps,
+                                                                       Dims s, T *out, View v, float *N, float *D) {
   using G = Geo<DH>;
-  constexpr int FC = DH <= 32 ? 2 : 1, OT = o_terms(DH, PT), NA = G::KS * OT, NB = G::NSB, NBT = c_tiles(DH, 2);
+  constexpr int FC = DH <= 32 ? 2 : 1, NA = G::KS * PT, NB = G::NSB;
   constexpr bool ZV = MODE == 0;   // the normaliser, on the vector units
   typedef Stager<NA, NB, 0, 0, FC, NW> Stg;
-  __shared__ __attribute__((aligned(16))) half_t lds[2][Stg::NS * kTile];
+  __shared__ __attribute__((aligned(16))) bf16_t lds[2][Stg::NS * kTile];
   __shared__ __attribute__((aligned(16))) float lz[2][ZV ? FC * 32 : 1];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slice = blockIdx.y, tb0 = (blockIdx.x * NW + wave) * RT;
-  op_t x[RT][G::KS][G::XT];
+  bf16x8 x[RT][G::KS][3];
 #pragma unroll
   for (int r = 0; r < RT; ++r) {
-    const half_t *xp = X + ((int64_t)slice * s.nt + min(tb0 + r, s.nt - 1)) * G::KS * G::XT * kTile;
+    const bf16_t *xp = X + ((int64_t)slice * s.nt + min(tb0 + r, s.nt - 1)) * G::KS * 3 * kTile;
 #pragma unroll
     for (int ks = 0; ks < G::KS; ++ks)
 #pragma unroll
-      for (int i = 0; i < G::XT; ++i) x[r][ks][i] = lds_operand(xp + (ks * G::XT + i) * kTile, lane);
+      for (int i = 0; i < 3; ++i) x[r][ks][i] = lds_operand(xp + (ks * 3 + i) * kTile, lane);
   }
   Stg sg;
   sg.p0 = OA;
   sg.p1 = SB + (int64_t)slice * s.mt * NB * kTile;
   sg.p2 = sg.p3 = nullptr;
-  constexpr bool PARTS = sum_in_parts(PT);
-  f32x16 acc[RT][G::CT], total[PARTS ? RT : 1][G::CT];
+  constexpr bool LO = low_terms(PT);
+  f32x16 acc[RT][G::CT], lo[LO ? RT : 1][G::CT];
   float dsum[RT], dpart[RT];   // Phi z: of all groups of eight feature tiles before, of this one
 #pragma unroll
   for (int r = 0; r < RT; ++r) {
@@ -1085,9 +923,10 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(c
 #pragma unroll
     for (int ct = 0; ct < G::CT; ++ct) {
       acc[r][ct] = zero16();
-      if (PARTS) total[PARTS ? r : 0][ct] = zero16();
+      if (LO) lo[LO ? r : 0][ct] = zero16();
     }
   }
+  const NegIdentity ni(lane);
   const float *zs = zpad + (int64_t)slice * s.mt * 32;
   const int zi = tid & (FC * 32 - 1);
   float zr = 0.f;
@@ -1107,46 +946,27 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(c
 #pragma unroll
     for (int fi = 0; fi < FC; ++fi) {
       if (f0 + fi >= s.mt) break;
-      const half_t *la = &lds[b][fi * NA * kTile], *lb = &lds[b][(Stg::O1 + fi * NB) * kTile];
+      const bf16_t *la = &lds[b][fi * NA * kTile], *lb = &lds[b][(Stg::O1 + fi * NB) * kTile];
       f32x4 z4[4];
       if (ZV)
 #pragma unroll
         for (int j = 0; j < 4; ++j) z4[j] = *reinterpret_cast<const f32x4 *>(&lz[b][fi * 32 + 8 * j + 4 * h]);
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
-        f32x16 R = project<DH, PT, true>([&](int ks, int i) { return x[r][ks][i]; },
-                                         [&](int ks, int i) { return lds_operand(la + (ks * OT + i) * kTile, lane); });   // rows: features, lanes: tokens
+        f32x16 R = zero16();
+#pragma unroll
+        for (int ks = 0; ks < G::KS; ++ks) {
+          bf16x8 o[PT];
+#pragma unroll
+          for (int i = 0; i < PT; ++i) o[i] = lds_operand(la + (ks * PT + i) * kTile, lane);
+          R = mfma_terms<PT, true>(R, x[r][ks], o);   // rows: features, lanes: tokens
+        }
 #pragma unroll
         for (int i = 0; i < 16; ++i) R[i] = relu(R[i]);
         if (ZV) dpart[r] += dot16(R, z4);
-        if constexpr (MODE != 2 && DH >= 64) {   // all four products, the small ones of a feature tile first
-          op_t p[2][2];
-          with_split(R, [&](int a, const op_t *t) {
-            p[a][0] = t[0];
-            p[a][1] = t[1];
-          });
+        with_split<mfma_residuals(DH, PT)>(R, ni, [&](int a, const bf16x8 *p) {
 #pragma unroll
-          for (int ct = 0; ct < G::CT; ++ct) {
-            auto go = [&](int a, int i, int j) {
-              acc[r][ct] = mfma_h(p[a][i], lds_operand(lb + ((a * G::CT + ct) * NBT + j) * kTile, lane), acc[r][ct]);
-            };
-#pragma unroll
-            for (int a = 0; a < 2; ++a) {
-              go(a, 1, 1);
-              go(a, 0, 1);
-              go(a, 1, 0);
-            }
-            go(0, 0, 0);
-            go(1, 0, 0);
-          }
-        } else with_split(R, [&](int a, const op_t *p) {
-#pragma unroll
-          for (int ct = 0; ct < G::CT; ++ct) {
-            op_t y[NBT];
-#pragma unroll
-            for (int i = 0; i < NBT; ++i) y[i] = lds_operand(lb + ((a * G::CT + ct) * NBT + i) * kTile, lane);
-            add_terms<NBT>(acc[r][ct], acc[r][ct], p, y);   // rows: tokens, lanes: columns
-          }
+          for (int ct = 0; ct < G::CT; ++ct) apply_terms<DH>(acc[r][ct], LO ? lo[LO ? r : 0][ct] : acc[r][ct], p, lb, a, ct, lane);   // rows: tokens, lanes: columns
         });
       }
     }
@@ -1157,15 +977,6 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(c
         dpart[r] = 0.f;
       }
     }
-    if (PARTS && (!more || (f0 + FC) % sum_tiles(DH) == 0)) {
-#pragma unroll
-      for (int r = 0; r < RT; ++r)
-#pragma unroll
-        for (int ct = 0; ct < G::CT; ++ct) {
-          total[PARTS ? r : 0][ct] += acc[r][ct];
-          acc[r][ct] = zero16();
-        }
-    }
     if (more) {
       sg.put(lds[b ^ 1], wave, lane);
       if (ZV) lz[b ^ 1][zi] = zr;
@@ -1173,58 +984,47 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(c
     __syncthreads();
   }
   const float c = scalars[0];
-  const int E = es[slice] - kSBShift;
   T *const ob = MODE == 1 ? nullptr : out + v.slice_base(slice);
 #pragma unroll
   for (int r = 0; r < RT; ++r) {
     const int tb = tb0 + r;
     if (tb >= s.nt) continue;
-    const int xe = ex[((int64_t)slice * s.nt + tb) * 32 + l32];   // token l32
     float Dl = 0.f;
-    if (ZV) Dl = fmaf(scaled(c, xe), xor32_sum(dsum[r]), eps);
-    const float Dc = Dl / scaled(c, xe), inv = 1.f / Dc;   // (in the units of the accumulators: one rounding per element less)
+    if (ZV) Dl = fmaf(c, xor32_sum(dsum[r]), eps);   // token l32
     if (ZV && h == 0 && 32 * tb + l32 < s.n) D[(int64_t)slice * s.n + 32 * tb + l32] = Dl;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int row = 8 * (i >> 2) + 4 * h + (i & 3), t = 32 * tb + row;
-      const int e = MODE == 0 ? E : E + __shfl(xe, row, 64);
-      float Dt = 1.f, it = 1.f;
-      if (ZV) {
-        Dt = __shfl(Dc, row, 64);
-        it = __shfl(inv, row, 64);
-      }
-      if (PARTS)
+      float Dt = 1.f;
+      if (ZV) Dt = __shfl(Dl, row, 64);
+      if (LO)
 #pragma unroll
-        for (int ct = 0; ct < G::CT; ++ct) acc[r][ct][i] = total[PARTS ? r : 0][ct][i];
+        for (int ct = 0; ct < G::CT; ++ct) acc[r][ct][i] += lo[LO ? r : 0][ct][i];
       if (DH == 16) acc[r][0][i] += __shfl_xor(acc[r][0][i], 16, 64);
 #pragma unroll
       for (int ct = 0; ct < G::CT; ++ct) {
         const int col = 32 * ct + l32;
         if (t < s.n && col < s.d) {
-          if (MODE == 0) {
-            st(ob + (int64_t)t * v.sn + col, scaled(quotient(acc[r][ct][i], Dt, it), e));
-          } else {
-            const float val = scaled(c * acc[r][ct][i], e);
-            if (MODE == 1) N[((int64_t)slice * s.n + t) * s.d + col] = val;
-            else st(ob + (int64_t)t * v.sn + col, val);
-          }
+          const float val = c * acc[r][ct][i];
+          if (MODE == 1) N[((int64_t)slice * s.n + t) * s.d + col] = val;
+          else st(ob + (int64_t)t * v.sn + col, MODE == 0 ? val / Dt : val);
         }
       }
     }
   }
 }
 
-// The gradient kernel's dX_F likewise.
-constexpr bool grad_in_parts(int DH, int PT, bool DV) { return sum_in_parts(PT) && (DH <= 32 || (DH == 64 && !DV)); }
+// The gradient kernel: where the registers hold it, too.
+constexpr bool grad_low_terms(int DH, int PT, bool DV, int RT) {
+  return low_terms(PT) && (DH == 32 || (DH == 16 && RT == 1) || (DH == 64 && !DV));
+}
 // dX_F of one side: R = X Omega, G = Y S^T + w z^T (Y = dN, S, w = dD on the query side; Y = V, dS, w = 1
 // on the key side), dX_F = c rowscale ((G masked where R > 0) Omega^T) in float32, row t of a slice at
 // grad_row(t) (in the place of X's operand tiles where these are not needed again: a wave reads its tiles before
-// it writes them, and no other wave does either).  DV: dV = c ReLU(R) dS rides along, ex the exponents of X's rows.  ddw, rowscale
-// nullptr: 1.
+// it writes them, and no other wave does either).  DV: dV = c ReLU(R) dS rides along.  ddw, rowscale nullptr: 1.
 // The rows of Y come from the tensors as they are: y, divided by D (one term: not), or with the LayerNorm output
 // stage (o given) rstd (y - mean y - o mean(y o)).
-// Exponents: es of S and ez of z; a row of Y has one that keeps both parts of G below 2^16.
-template <int DH> constexpr int64_t grad_tile() { return 16 * x_terms(DH) * DH; }   // floats of a tile of 32 rows: its operand tiles' size
+template <int DH> constexpr int64_t grad_tile() { return 48 * DH; }   // floats of a tile of 32 rows: its operand tiles' size
 template <int DH>
 __device__ __forceinline__ int64_t grad_row(int t) { return (int64_t)(t >> 5) * grad_tile<DH>() + (t & 31) * DH; }
 template <typename T>
@@ -1233,41 +1033,30 @@ struct GradRows {
   const float *D;
   int vec;
 };
-// (three waves per SIMD at head dimension 32: 488 -> 464 us, 128 slices of 4000 tokens, m 1024, with dV)
-constexpr int grad_occupancy(int DH, int NW) { return DH == 32 && NW >= 4 ? 3 : row_occupancy(DH, NW); }
 template <typename T, int DH, int PT, bool DV, int RT, int NW>
-__global__ __launch_bounds__(NW * 64, grad_occupancy(DH, NW)) void grad_kernel(const half_t *X, const stored_exp *ex, GradRows<T> Y,
-                                                                      const float *ddw, const float *rowscale, const half_t *OA,
-                                                                      const half_t *SA, const half_t *OB, const half_t *SB,
-                                                                      const stored_exp *es, const stored_exp *ez, const float *scalars, Dims s,
-                                                                      float *dXF, T *dv, View v) {
+__global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void grad_kernel(const bf16_t *X, GradRows<T> Y, const float *ddw,
+                                                                      const float *rowscale, const bf16_t *OA,
+                                                                      const bf16_t *SA, const bf16_t *OB, const bf16_t *SB,
+                                                                      const float *scalars, Dims s, float *dXF, T *dv, View v) {
   using G = Geo<DH>;
-  constexpr int FC = DH == 16 ? 2 : 1, OT = o_terms(DH, PT), NA = G::KS * OT, NSA = G::NSA, NOT = c_tiles(DH, PT),
-                NOB = 2 * G::CT * NOT, NSB = DV ? G::NSB : 0, NBT = c_tiles(DH, 2);
+  constexpr int FC = DH == 16 ? 2 : 1, NA = G::KS * PT, NSA = 3 * G::KS + 1, NOB = 2 * G::CT * PT, NSB = DV ? G::NSB : 0;
   typedef Stager<NA, NSA, NOB, NSB, FC, NW> Stg;
-  __shared__ __attribute__((aligned(16))) half_t lds[2][Stg::NS * kTile];
+  __shared__ __attribute__((aligned(16))) bf16_t lds[2][Stg::NS * kTile];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slice = blockIdx.y, tb0 = (blockIdx.x * NW + wave) * RT;
-  Stg sg;
-  sg.p0 = OA;
-  sg.p1 = SA + (int64_t)slice * s.mt * NSA * kTile;
-  sg.p2 = OB;
-  sg.p3 = DV ? SB + (int64_t)slice * s.mt * NSB * kTile : nullptr;
-  const int E = es[slice], Ez = ez[slice];
-  op_t x[RT][G::KS][G::XT], y[RT][G::KS][PT], ext[RT];
-  int ye[RT];
+  bf16x8 x[RT][G::KS][3], y[RT][G::KS][PT], ext[RT];
 #pragma unroll
   for (int r = 0; r < RT; ++r) {
     const bool mine = tb0 + r < s.nt;   // (a wave past the last tile only helps to stage)
     const int64_t tb = (int64_t)slice * s.nt + (mine ? tb0 + r : 0);
-    const half_t *xp = X + tb * G::KS * G::XT * kTile;
+    const bf16_t *xp = X + tb * G::KS * 3 * kTile;
 #pragma unroll
     for (int ks = 0; ks < G::KS; ++ks)
 #pragma unroll
-      for (int i = 0; i < G::XT; ++i) {
-        x[r][ks][i] = op_t{};
-        if (mine) x[r][ks][i] = lds_operand(xp + (ks * G::XT + i) * kTile, lane);
+      for (int i = 0; i < 3; ++i) {
+        x[r][ks][i] = bf16x8{};
+        if (mine) x[r][ks][i] = lds_operand(xp + (ks * 3 + i) * kTile, lane);
       }
     const int t = 32 * (tb0 + r) + l32;
     const bool ok = t < s.n;
@@ -1280,7 +1069,7 @@ __global__ __launch_bounds__(NW * 64, grad_occupancy(DH, NW)) void grad_kernel(c
 #pragma unroll
       for (int q = 0; q < 8; ++q) g[ks][q] = ok && col < s.d ? g[ks][q] : 0.f;
     }
-    if (!DV && PT == 2 && Y.D) {
+    if (!DV && PT == 3 && Y.D) {
       const float Dt = ok ? Y.D[(int64_t)slice * s.n + t] : 1.f;
       if (Y.o) {
         float sum = 0.f, dot = 0.f, o[G::KS][8];
@@ -1307,40 +1096,34 @@ __global__ __launch_bounds__(NW * 64, grad_occupancy(DH, NW)) void grad_kernel(c
           for (int q = 0; q < 8; ++q) g[ks][q] = g[ks][q] / Dt;
       }
     }
-    unsigned mag = 0;
-#pragma unroll
-    for (int ks = 0; ks < G::KS; ++ks)
-#pragma unroll
-      for (int q = 0; q < 8; ++q) mag = umax(mag, magnitude(g[ks][q]));
-    mag = umax(mag, (unsigned)__shfl_xor((int)mag, 32, 64));
-    const float wt = ddw ? ddw[tb * 32 + l32] : 1.f;
-    const int eg = exponent(mag) - y_top(DH), ew = exponent(magnitude(wt)) + Ez - E - kRankOneTop;
-    ye[r] = max(eg, ew);
-    if (ye[r] < kNone / 2) ye[r] = 0;   // (nothing but zeros)
 #pragma unroll
     for (int ks = 0; ks < G::KS; ++ks) {
+      bf16x8 t3[3];
+      split8(g[ks], t3);
 #pragma unroll
-      for (int q = 0; q < 8; ++q) g[ks][q] = scaled(g[ks][q], -ye[r]);
-      op_t t2[2];
-      split8h(g[ks], t2);
-#pragma unroll
-      for (int i = 0; i < PT; ++i) y[r][ks][i] = t2[i];
+      for (int i = 0; i < PT; ++i) y[r][ks][i] = t3[i];
     }
     __bf16 w[3];
-    split1b(h ? 0.f : scaled(wt, -ye[r]), w);
+    split1(h ? 0.f : (ddw ? ddw[tb * 32 + l32] : 1.f), w);
     const __bf16 o = (__bf16)0.f;
-    ext[r] = __builtin_bit_cast(op_t, bf16x8{w[0], w[0], w[1], w[0], w[2], w[1], o, o});   // against z0, z1, z0, z2, z0, z1
+    ext[r] = bf16x8{w[0], w[0], w[1], w[0], w[2], w[1], o, o};   // against z0, z1, z0, z2, z0, z1
   }
-  constexpr bool PARTS = grad_in_parts(DH, PT, DV);
-  f32x16 acc[RT][G::CT], total[PARTS ? RT : 1][G::CT], accv[DV ? RT : 1][G::CT];
+  Stg sg;
+  sg.p0 = OA;
+  sg.p1 = SA + (int64_t)slice * s.mt * NSA * kTile;
+  sg.p2 = OB;
+  sg.p3 = DV ? SB + (int64_t)slice * s.mt * NSB * kTile : nullptr;
+  constexpr bool LO = grad_low_terms(DH, PT, DV, RT);
+  f32x16 acc[RT][G::CT], low[LO ? RT : 1][G::CT], accv[DV ? RT : 1][G::CT];
 #pragma unroll
   for (int r = 0; r < RT; ++r)
 #pragma unroll
     for (int ct = 0; ct < G::CT; ++ct) {
       acc[r][ct] = zero16();
-      if (PARTS) total[PARTS ? r : 0][ct] = zero16();
+      if (LO) low[LO ? r : 0][ct] = zero16();
       if (DV) accv[r][ct] = zero16();
     }
+  const NegIdentity ni(lane);
   sg.fetch(0, wave, lane);
   sg.put(lds[0], wave, lane);
   wait_loads();
@@ -1352,57 +1135,43 @@ __global__ __launch_bounds__(NW * 64, grad_occupancy(DH, NW)) void grad_kernel(c
 #pragma unroll
     for (int fi = 0; fi < FC; ++fi) {
       if (f0 + fi >= s.mt) break;
-      const half_t *la = &lds[b][fi * NA * kTile], *ls = &lds[b][(Stg::O1 + fi * NSA) * kTile],
+      const bf16_t *la = &lds[b][fi * NA * kTile], *ls = &lds[b][(Stg::O1 + fi * NSA) * kTile],
                    *lo = &lds[b][(Stg::O2 + fi * NOB) * kTile], *lv = &lds[b][(Stg::O3 + fi * NSB) * kTile];
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
-        f32x16 R = project<DH, PT, true>([&](int ks, int i) { return x[r][ks][i]; },
-                                         [&](int ks, int i) { return lds_operand(la + (ks * OT + i) * kTile, lane); });   // rows: features, lanes: tokens
-        f32x16 Gr = zero16();
+        f32x16 R = zero16(), Gr = zero16();
 #pragma unroll
         for (int ks = 0; ks < G::KS; ++ks) {
-          const op_t s0 = lds_operand(ls + 2 * ks * kTile, lane), s1 = lds_operand(ls + (2 * ks + 1) * kTile, lane);
-          Gr = mfma_h(s1, y[r][ks][0], Gr);
-          if (PT == 2) Gr = mfma_h(s0, y[r][ks][PT - 1], Gr);
-        }
+          bf16x8 o[PT], sa[3];
 #pragma unroll
-        for (int ks = 0; ks < G::KS; ++ks) Gr = mfma_h(lds_operand(ls + 2 * ks * kTile, lane), y[r][ks][0], Gr);
-        Gr = mfma_b(lds_operand(ls + 2 * G::KS * kTile, lane), ext[r], Gr);
+          for (int i = 0; i < PT; ++i) o[i] = lds_operand(la + (ks * PT + i) * kTile, lane);
+          R = mfma_terms<PT, true>(R, x[r][ks], o);   // rows: features, lanes: tokens
+#pragma unroll
+          for (int i = 0; i < 3; ++i) sa[i] = lds_operand(ls + (ks * 3 + i) * kTile, lane);
+          Gr = mfma_terms<PT, false>(Gr, sa, y[r][ks]);
+        }
+        Gr = mfma(lds_operand(ls + 3 * G::KS * kTile, lane), ext[r], Gr);
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const float mask = positive(R[i]);
           Gr[i] = masked(Gr[i], mask);
-          if (DV) R[i] = relu(R[i]);
+          if (DV) R[i] = masked(R[i], mask);
         }
-        with_split(Gr, [&](int a, const op_t *p) {
+        with_split<mfma_residuals(DH, PT)>(Gr, ni, [&](int a, const bf16x8 *p) {
 #pragma unroll
           for (int ct = 0; ct < G::CT; ++ct) {
-            op_t o[NOT];
+            bf16x8 o[PT];
 #pragma unroll
-            for (int i = 0; i < NOT; ++i) o[i] = lds_operand(lo + ((a * G::CT + ct) * NOT + i) * kTile, lane);
-            add_terms<NOT>(acc[r][ct], acc[r][ct], p, o);   // rows: tokens, lanes: columns
+            for (int i = 0; i < PT; ++i) o[i] = lds_operand(lo + ((a * G::CT + ct) * PT + i) * kTile, lane);
+            add_terms<PT>(acc[r][ct], LO ? low[LO ? r : 0][ct] : acc[r][ct], p, o);   // rows: tokens, lanes: columns
           }
         });
         if (DV)
-          with_split(R, [&](int a, const op_t *p) {
+          with_split<mfma_residuals(DH, PT)>(R, ni, [&](int a, const bf16x8 *p) {
 #pragma unroll
-            for (int ct = 0; ct < G::CT; ++ct) {
-              op_t o[NBT];
-#pragma unroll
-              for (int i = 0; i < NBT; ++i) o[i] = lds_operand(lv + ((a * G::CT + ct) * NBT + i) * kTile, lane);
-              add_terms<NBT>(accv[r][ct], accv[r][ct], p, o);
-            }
+            for (int ct = 0; ct < G::CT; ++ct) apply_terms<DH>(accv[r][ct], accv[r][ct], p, lv, a, ct, lane);
           });
       }
-    }
-    if (PARTS && (!more || (f0 + FC) % sum_tiles(DH) == 0)) {
-#pragma unroll
-      for (int r = 0; r < RT; ++r)
-#pragma unroll
-        for (int ct = 0; ct < G::CT; ++ct) {
-          total[PARTS ? r : 0][ct] += acc[r][ct];
-          acc[r][ct] = zero16();
-        }
     }
     if (more) sg.put(lds[b ^ 1], wave, lane);
     __syncthreads();
@@ -1413,29 +1182,24 @@ __global__ __launch_bounds__(NW * 64, grad_occupancy(DH, NW)) void grad_kernel(c
   for (int r = 0; r < RT; ++r) {
     const int tb = tb0 + r;
     if (tb >= s.nt) continue;
-    const int64_t trow = ((int64_t)slice * s.nt + tb) * 32 + l32;   // token l32
-    const float rs = rowscale ? c * rowscale[trow] : c;
-    const int xe = DV ? (int)ex[trow] : 0;
+    const float rs = rowscale ? c * rowscale[((int64_t)slice * s.nt + tb) * 32 + l32] : c;   // token l32
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int row = 8 * (i >> 2) + 4 * h + (i & 3), t = 32 * tb + row;
       const float sc = rowscale ? __shfl(rs, row, 64) : c;
-      const int e = E + __shfl(ye[r], row, 64), ev = DV ? E - kSBShift + __shfl(xe, row, 64) : 0;
-      if (PARTS)
+      if (LO)
 #pragma unroll
-        for (int ct = 0; ct < G::CT; ++ct) acc[r][ct][i] = total[PARTS ? r : 0][ct][i];
-      if (DH == 16 && PT == 2) acc[r][0][i] += __shfl_xor(acc[r][0][i], 16, 64);
+        for (int ct = 0; ct < G::CT; ++ct) acc[r][ct][i] += low[LO ? r : 0][ct][i];
       if (DV && DH == 16) accv[r][0][i] += __shfl_xor(accv[r][0][i], 16, 64);
 #pragma unroll
       for (int ct = 0; ct < G::CT; ++ct) {
         const int col = 32 * ct + l32;
-        if (col < DH) dXF[((int64_t)slice * s.nt + tb) * grad_tile<DH>() + row * DH + col] = scaled(sc * acc[r][ct][i], e);
-        if (DV && t < s.n && col < s.d) st(vb + (int64_t)t * v.sn + col, scaled(c * accv[r][ct][i], ev));
+        if (col < DH) dXF[((int64_t)slice * s.nt + tb) * grad_tile<DH>() + row * DH + col] = sc * acc[r][ct][i];
+        if (DV && t < s.n && col < s.d) st(vb + (int64_t)t * v.sn + col, c * accv[r][ct][i]);
       }
     }
   }
 }
-
 
 // ------------------------------------------------------------------------------------
 // Band inner products of X and dX_F on 64-row tiles (band l - 1: details of level l; band L: the
@@ -1655,17 +1419,16 @@ constexpr int kFillBlocks = 1024;   // workgroups of the contraction: four per c
 
 int dh_of(int d) { return d <= 16 ? 16 : d <= 32 ? 32 : d <= 64 ? 64 : 128; }
 // One term for what comes in as bf16 (head dimensions up to 32, where that pays for instances of its own; the LayerNorm
-// output stage has a float32 dN); otherwise two terms for every operand (three for Omega in the projection, see o_terms).
+// output stage has a float32 dN); otherwise three terms for every operand.
 int terms_of(const wersa_desc &c) {
-  return c.dtype == WERSA_BF16 && c.d <= 32 && !(c.flags & WERSA_FLAG_LAYERNORM) ? 1 : 2;
+  return c.dtype == WERSA_BF16 && c.d <= 32 && !(c.flags & WERSA_FLAG_LAYERNORM) ? 1 : 3;
 }
 struct Plan {
   Dims s;
-  int DH, KS, CT, PT, XT, OT, PW, NSA, NSB, matrices;
+  int DH, KS, CT, PT, NSB, matrices;
   int chunks, rows_per_chunk;         // pooling
   int FW, TW, splits, tiles_per_split, shares;
-  int row_groups;                     // workgroups of the packing kernels per slice
-  int groups;                         // of the filter's backward: 4096 elements, 64 columns at most
+  int groups;                         // 4096-element workgroups per slice
   int ntl;                            // 64-row tiles per slice
 };
 Plan plan_of(const wersa_desc &c) {
@@ -1675,11 +1438,7 @@ Plan plan_of(const wersa_desc &c) {
   p.KS = p.DH / 16;
   p.CT = p.DH < 32 ? 1 : p.DH / 32;
   p.PT = terms_of(c);
-  p.XT = x_terms(p.DH);
-  p.OT = o_terms(p.DH, p.PT);
-  p.PW = part_width(p.DH, p.PT);
-  p.NSA = 2 * p.KS + 1;
-  p.NSB = 2 * p.CT * c_tiles(p.DH, 2);
+  p.NSB = p.DH == 16 ? 4 : 6 * p.CT;
   p.matrices = (c.flags & WERSA_FLAG_SEPARATE_OMEGA) ? 2 : 1;
   p.s = Dims{c.n, c.d, c.m, (c.n + 63) / 64 * 2, (c.m + 31) / 32};
   p.ntl = (c.n + 63) / 64;
@@ -1707,20 +1466,15 @@ Plan plan_of(const wersa_desc &c) {
   p.shares = p.splits * p.TW;
   const int cw = p.DH < 64 ? p.DH : 64, tr = 4096 / cw;
   p.groups = (c.n + tr - 1) / tr * (p.DH / cw);
-  const int rb = 16 * (p.DH == 128 ? 512 : 256) / p.DH;
-  p.row_groups = (c.n + rb - 1) / rb;
   return p;
 }
 
 struct Ws {
   float *qpart, *part, *zpart, *zpad, *Nbuf, *pyr;
-  half_t *VC, *SB, *XQ, *XK;   // (XQ, XK, exQ, exK, eV, eS: see keeps_operands)
-  ShareExps pe;
-  stored_exp *exQ, *exK, *eV;  // exponents of the rows of Q_F and K_F, of the token tiles of V
+  bf16_t *VC, *SB, *XQ, *XK;   // (XQ, XK: see keeps_operands)
   // backward
-  half_t *NC, *XS, *SA, *dSA, *dSB;
-  stored_exp *eN, *edS, *edz;   // of the token tiles of dN, of dS and dz
-  float *ddw, *wz, *rowscale, *dpart, *gq, *gk, *partQ, *partK, *dF, *dlogit, *dqbar, *tgq, *tgk, *aq, *ak;
+  bf16_t *NC, *XS, *SA, *dSA, *dSB;
+  float *ddw, *rowscale, *dpart, *gq, *gk, *partQ, *partK, *dF, *dlogit, *dqbar, *tgq, *tgk, *aq, *ak;
   int64_t total;
 };
 int64_t tile_floats(int64_t tiles) { return tiles * (kTile / 2); }
@@ -1728,49 +1482,36 @@ Ws ws_of(const wersa_desc &c, const Plan &p, int bwd, bool keep, float *base) {
   Ws w{};
   Bump b(base);
   const int64_t sl = (int64_t)c.B * c.H;
-  auto op = [&](int64_t tiles) { return (half_t *)b.take(tile_floats(tiles)); };
-  auto exps = [&](int64_t count) { return (stored_exp *)b.take(count); };
+  auto op = [&](int64_t tiles) { return (bf16_t *)b.take(tile_floats(tiles)); };
   const int64_t rows = sl * p.s.nt;
   const bool deep = c.L > kTileL;
-  w.part = b.take(sl * p.shares * p.s.mt * 32 * p.PW);
+  w.part = b.take(sl * p.shares * p.s.mt * 32 * 32 * p.CT);
   w.zpart = b.take(sl * p.shares * p.s.mt * 32);
   if (!bwd) {
     w.zpad = b.take(sl * p.s.mt * 32);
     w.qpart = b.take(sl * p.chunks * c.d);
-    w.VC = op(rows * 2 * p.CT * c_tiles(p.DH, p.PT));
+    w.VC = op(rows * 2 * p.CT * p.PT);
     if (!keep) {
-      w.XQ = op(rows * p.KS * p.XT);
-      w.XK = op(rows * p.KS * p.XT);
-      w.exQ = exps(rows * 32);
-      w.exK = exps(rows * 32);
-      w.eV = exps(rows);
-      w.pe = ShareExps{exps(sl * p.shares * p.s.mt), exps(sl * p.shares * p.s.mt)};
+      w.XQ = op(rows * p.KS * 3);
+      w.XK = op(rows * p.KS * 3);
     }
     w.SB = op((sl * p.s.mt + 1) * p.NSB);       // (one feature tile more: a stage reads whole groups)
     if (c.flags & WERSA_FLAG_LAYERNORM) w.Nbuf = b.take(sl * c.n * c.d);
     if (deep) w.pyr = b.take(2 * sl * pyramid_floats(p.ntl, c.d));
   } else {
-    w.NC = op(rows * 2 * p.CT * c_tiles(p.DH, p.PT));
+    w.NC = op(rows * 2 * p.CT * p.PT);
     // dQ_F and dK_F, in the place of operands that nothing else needs
-    w.gq = (float *)op(rows * p.KS * p.XT);
-    w.gk = (float *)op(rows * p.KS * p.XT);
-    if (p.PT == 1) w.XS = (half_t *)w.gq;
-    else if (!keep) w.XQ = (half_t *)w.gq;
-    if (!keep) {
-      w.XK = (half_t *)w.gk;
-      w.exK = exps(rows * 32);
-    }
-    w.SA = op((sl * p.s.mt + 1) * p.NSA);
-    w.dSA = op((sl * p.s.mt + 1) * p.NSA);
+    w.gq = (float *)op(rows * p.KS * 3);
+    w.gk = (float *)op(rows * p.KS * 3);
+    if (p.PT == 1) w.XS = (bf16_t *)w.gq;
+    else if (!keep) w.XQ = (bf16_t *)w.gq;
+    if (!keep) w.XK = (bf16_t *)w.gk;
+    w.SA = op((sl * p.s.mt + 1) * (3 * p.KS + 1));
+    w.dSA = op((sl * p.s.mt + 1) * (3 * p.KS + 1));
     w.dSB = op((sl * p.s.mt + 1) * p.NSB);
-    w.eN = exps(rows);
-    w.edS = exps(sl);
-    w.edz = exps(sl);
-    w.pe = ShareExps{exps(sl * p.shares * p.s.mt), exps(sl * p.shares * p.s.mt)};
     w.ddw = b.take(rows * 32);
-    w.wz = b.take(rows * 32);
     if (p.PT == 1) w.rowscale = b.take(rows * 32);
-    w.dpart = b.take(sl * p.row_groups);
+    w.dpart = b.take(sl * p.groups);
     const int64_t prow = p.groups + (deep ? c.d / kCoarseCols : 0);
     w.partQ = b.take(sl * prow * (c.L + 1));
     w.partK = b.take(sl * prow * (c.L + 1));
@@ -1789,10 +1530,10 @@ Ws ws_of(const wersa_desc &c, const Plan &p, int bwd, bool keep, float *base) {
   return w;
 }
 
-// Where Q_F and K_F, packed (6 bytes per element each, 4 from head dimension 64 on), live between the forward and the backward.  In `saved` where the rest
+// Where Q_F and K_F, packed (6 bytes per element each), live between the forward and the backward.  In `saved` where the rest
 // of the forward's workspace fits wersa_forward_static's scratch: the backward has less to do where latency counts (64 slices
 // of 1000 tokens, d 64, m 64, float32: 110 us, 122 us where it packs them again), and what the static call takes does not
-// shrink by them.  Beyond, `saved` would hold two or three times a tensor for every layer of a model (542 MB for 8 slices of 131072
+// shrink by them.  Beyond, `saved` would hold three times a tensor for every layer of a model (811 MB for 8 slices of 131072
 // tokens, d 64, against 5), and the backward packs them again, from Q and K, in the launch that packs dN: 8 x 16384 tokens, d 64,
 // m 256 367 us -> 374, 128 x 4000, d 32, m 1024 1716 -> 1763.
 bool keeps_operands(const wersa_desc &c, const Plan &p) {
@@ -1823,14 +1564,14 @@ int row_waves(const Plan &p, int slices) {
 template <int DH> constexpr int row_tiles() { return DH <= 32 ? 2 : 1; }
 
 template <typename T, int DH, int PT, int MODE>
-void launch_apply(const wersa_desc &c, const Plan &p, const half_t *X, const stored_exp *ex, const half_t *OA, const half_t *SB,
-                  const stored_exp *es, const float *zpad, const float *scalars, T *out, View v, float *N, float *D, hipStream_t st) {
+void launch_apply(const wersa_desc &c, const Plan &p, const bf16_t *X, const bf16_t *OA, const bf16_t *SB, const float *zpad,
+                  const float *scalars, T *out, View v, float *N, float *D, hipStream_t st) {
   constexpr int RT = row_tiles<DH>();
   const int slices = c.B * c.H, nw = row_waves<DH, RT>(p, slices);
   const dim3 grid((p.s.nt + nw * RT - 1) / (nw * RT), slices);
   auto go = [&](auto NW) {
     WERSA_STAGE(MODE == 2 ? "split_apply_dv" : "split_apply", st, apply_kernel<T, DH, PT, MODE, RT, NW.value><<<grid, 64 * NW.value, 0, st>>>(
-        X, ex, OA, SB, es, zpad, scalars, c.eps, p.s, out, v, N, D));
+        X, OA, SB, zpad, scalars, c.eps, p.s, out, v, N, D));
   };
   if constexpr (DH == 128) {
     go(std::integral_constant<int, 4>());
@@ -1840,15 +1581,15 @@ void launch_apply(const wersa_desc &c, const Plan &p, const half_t *X, const sto
   }
 }
 template <typename T, int DH, int PT, bool DV>
-void launch_grad(const wersa_desc &c, const Plan &p, const half_t *X, const stored_exp *ex, const GradRows<T> &Y, const float *ddw,
-                 const float *rowscale, const half_t *OA, const half_t *SA, const half_t *OB, const half_t *SB, const stored_exp *es,
-                 const stored_exp *ez, const float *scalars, float *dXF, T *dv, View v, hipStream_t st) {
+void launch_grad(const wersa_desc &c, const Plan &p, const bf16_t *X, const GradRows<T> &Y, const float *ddw, const float *rowscale,
+                 const bf16_t *OA, const bf16_t *SA, const bf16_t *OB, const bf16_t *SB, const float *scalars, float *dXF,
+                 T *dv, View v, hipStream_t st) {
   constexpr int RT = DH == 16 && (PT == 1 || !DV) ? 2 : 1;   // (as many token tiles as the registers of two waves per SIMD hold)
   const int slices = c.B * c.H, nw = row_waves<DH, RT>(p, slices);
   const dim3 grid((p.s.nt + nw * RT - 1) / (nw * RT), slices);
   auto go = [&](auto NW) {
     WERSA_STAGE(DV ? "split_grad_k" : "split_grad", st, grad_kernel<T, DH, PT, DV, RT, NW.value><<<grid, 64 * NW.value, 0, st>>>(
-        X, ex, Y, ddw, rowscale, OA, SA, OB, SB, es, ez, scalars, p.s, dXF, dv, v));
+        X, Y, ddw, rowscale, OA, SA, OB, SB, scalars, p.s, dXF, dv, v));
   };
   if constexpr (DH == 128) {
     go(std::integral_constant<int, 4>());
@@ -1870,19 +1611,14 @@ wersa_status forward_t(const wersa_desc &c, const T *q, const T *k, const T *v, 
   const View tv{c.stride_b, c.stride_h, c.stride_n, c.H};
   const bool deep = c.L > kTileL, ln = (c.flags & WERSA_FLAG_LAYERNORM) != 0;
   float *scalars = saved + sv.scalars, *coef = saved + sv.coef;
-  half_t *XQ = keep ? (half_t *)(saved + sv.XQ) : w.XQ, *XK = keep ? (half_t *)(saved + sv.XK) : w.XK,
-         *OA = (half_t *)(saved + sv.OA), *OB = (half_t *)(saved + sv.OB);
-  auto exps = [&](int64_t at, stored_exp *other) { return keep ? (stored_exp *)(saved + at) : other; };
-  stored_exp *exQ = exps(sv.exQ, w.exQ), *exK = exps(sv.exK, w.exK), *ey = exps(sv.eV, w.eV), *ge = (stored_exp *)(saved + sv.ge),
-             *es = (stored_exp *)(saved + sv.eS), *ez = es + slices;
-  const ShareExps pe{exps(sv.pe, w.pe.S), exps(sv.pe + (int64_t)slices * p.shares * p.s.mt, w.pe.z)};
-  const int64_t two = p.matrices == 2 ? p.s.mt : 0;
-  const half_t *OAk = OA + two * p.KS * p.OT * kTile;
+  bf16_t *XQ = keep ? (bf16_t *)(saved + sv.XQ) : w.XQ, *XK = keep ? (bf16_t *)(saved + sv.XK) : w.XK,
+         *OA = (bf16_t *)(saved + sv.OA), *OB = (bf16_t *)(saved + sv.OB);
+  const bf16_t *OAk = OA + (p.matrices == 2 ? (int64_t)p.s.mt * p.KS * PT * kTile : 0);
   float *addQ = deep ? saved + sv.addQ : nullptr, *addK = deep ? saved + sv.addK : nullptr;
   float *qpart = deep ? saved + sv.tileQ : w.qpart, *kpart = deep ? saved + sv.tileK : nullptr;
   const int vec = rows_aligned(c, {q, k, v});
-  const OmegaPack<T> om{omega, sigma, c.bw_floor, scalars, OA, OB, ge, p.matrices, DH, p.KS, p.CT, PT,
-                        (p.KS + 2 * p.CT + 3) / 4 * p.matrices * p.s.mt};
+  const int pieces = p.matrices * p.s.mt * 64 * (p.KS + 2 * p.CT);
+  const OmegaPack<T> om{omega, sigma, c.bw_floor, scalars, OA, OB, p.matrices, p.KS, p.CT, PT, (pieces + 255) / 256};
   WERSA_STAGE("split_pool", st, pool_kernel<T><<<dim3(p.chunks + om.blocks, slices, deep ? 2 : 1), 256, 0, st>>>(
       q, k, tv, p.s, vec, p.rows_per_chunk, p.chunks, qpart, kpart, om));
   WERSA_STAGE("gate_fwd_kernel", st, gate_fwd_kernel<<<slices, kGateFwdThreads, 0, st>>>(
@@ -1893,17 +1629,17 @@ wersa_status forward_t(const wersa_desc &c, const T *q, const T *k, const T *v, 
   if (deep)
     WERSA_STAGE("split_deep", st, deep_addend_kernel<<<dim3(slices, 2, c.d / kCoarseCols), 1024, 0, st>>>(
         qpart, kpart, coef, p.ntl, c.d, c.L, w.pyr, addQ, addK));
-  WERSA_STAGE("split_prep_fwd", st, prep_fwd_kernel<T, DH, PT><<<dim3(p.row_groups, slices, 2), Geo<DH>::NT, 0, st>>>(
-      q, k, v, tv, p.s, vec, c.L, coef, addQ, addK, XQ, XK, w.VC, exQ, exK, ey));
+  WERSA_STAGE("split_prep_fwd", st, prep_fwd_kernel<T, DH, PT><<<dim3(p.groups, slices, 3), 256, 0, st>>>(
+      q, k, v, tv, p.s, vec, c.L, coef, addQ, addK, XQ, XK, w.VC));
   WERSA_STAGE("split_contract", st, contract_kernel<DH, PT><<<dim3(p.splits, p.s.mt / p.FW, slices), 512, 0, st>>>(
-      XK, w.VC, ey, nullptr, exK, OAk, ge + two * 32, ge, p.s, p.FW, p.TW, p.tiles_per_split, w.part, w.zpart, pe));
-  WERSA_STAGE("split_reduce", st, reduce_kernel<DH, PT><<<dim3(p.s.mt, slices), 256, 0, st>>>(
-      w.part, w.zpart, p.shares, scalars, p.s, saved + sv.S, saved + sv.z, w.zpad, pe, SOperands{ge, nullptr, w.SB, es, ez}, SOperands{}));
+      XK, w.VC, nullptr, OAk, p.s, p.FW, p.TW, p.tiles_per_split, w.part, w.zpart));
+  WERSA_STAGE("split_reduce", st, reduce_kernel<DH><<<dim3(p.s.mt, slices), 256, 0, st>>>(
+      w.part, w.zpart, p.shares, 1, scalars, p.s, saved + sv.S, saved + sv.z, w.zpad, nullptr, w.SB, nullptr));
   if (ln) {
-    launch_apply<T, DH, PT, 1>(c, p, XQ, exQ, OA, w.SB, es, w.zpad, scalars, out, tv, w.Nbuf, nullptr, st);
+    launch_apply<T, DH, PT, 1>(c, p, XQ, OA, w.SB, w.zpad, scalars, out, tv, w.Nbuf, nullptr, st);
     WERSA_STAGE("split_ln", st, ln_out_kernel<T><<<dim3((c.n + 3) / 4, slices), 256, 0, st>>>(w.Nbuf, out, tv, c.n, c.d, c.eps, saved + sv.D));
   } else {
-    launch_apply<T, DH, PT, 0>(c, p, XQ, exQ, OA, w.SB, es, w.zpad, scalars, out, tv, nullptr, saved + sv.D, st);
+    launch_apply<T, DH, PT, 0>(c, p, XQ, OA, w.SB, w.zpad, scalars, out, tv, nullptr, saved + sv.D, st);
   }
   return hipGetLastError() == hipSuccess ? WERSA_OK : WERSA_ERR_LAUNCH;
 }
@@ -1921,33 +1657,29 @@ wersa_status backward_t(const wersa_desc &c, const T *q, const T *k, const T *v,
   const bool deep = c.L > kTileL, ln = (c.flags & WERSA_FLAG_LAYERNORM) != 0;
   const float *scalars = saved + sv.scalars, *coef = saved + sv.coef, *D = saved + sv.D;
   // (with one-term operands XS serves the query side's gradient too: of X Omega it needs the sign alone)
-  const half_t *XQ = PT == 1 ? w.XS : keep ? (const half_t *)(saved + sv.XQ) : w.XQ,
-               *XK = keep ? (const half_t *)(saved + sv.XK) : w.XK, *OA = (const half_t *)(saved + sv.OA),
-               *OB = (const half_t *)(saved + sv.OB);
-  const stored_exp *ge = (const stored_exp *)(saved + sv.ge), *exK = keep ? (const stored_exp *)(saved + sv.exK) : w.exK;
-  stored_exp *eS = (stored_exp *)const_cast<float *>(saved + sv.eS);
+  const bf16_t *XQ = PT == 1 ? w.XS : keep ? (const bf16_t *)(saved + sv.XQ) : w.XQ,
+               *XK = keep ? (const bf16_t *)(saved + sv.XK) : w.XK, *OA = (const bf16_t *)(saved + sv.OA),
+               *OB = (const bf16_t *)(saved + sv.OB);
   const int64_t two = p.matrices == 2 ? p.s.mt : 0;
-  const half_t *OAk = OA + two * p.KS * p.OT * kTile, *OBk = OB + two * 2 * p.CT * c_tiles(DH, PT) * kTile;
+  const bf16_t *OAk = OA + two * p.KS * PT * kTile, *OBk = OB + two * 2 * p.CT * PT * kTile;
   const int vec = rows_aligned(c, {q, k, v, out, dout});
-  WERSA_STAGE("split_prep_bwd", st, prep_bwd_kernel<T, DH, PT><<<dim3(p.row_groups, slices, keep ? 1 : 2), Geo<DH>::NT, 0, st>>>(
-      dout, out, q, k, tv, p.s, vec, ln, c.L, coef, deep ? saved + sv.addQ : nullptr, deep ? saved + sv.addK : nullptr, D,
-      keep ? (const stored_exp *)(saved + sv.exQ) : nullptr, w.NC, w.eN, w.XQ, w.XS, w.XK, w.exK, w.ddw, w.wz, w.rowscale, w.dpart));
+  WERSA_STAGE("split_prep_bwd", st, prep_bwd_kernel<T, DH, PT><<<dim3(p.groups, slices, keep ? (PT == 1 ? 2 : 1) : 3), 256, 0, st>>>(
+      dout, out, q, k, tv, p.s, vec, ln, c.L, coef, deep ? saved + sv.addQ : nullptr, deep ? saved + sv.addK : nullptr, D, w.NC,
+      w.XQ, w.XS, w.XK, w.ddw, w.rowscale, w.dpart));
   WERSA_STAGE("split_contract", st, contract_kernel<DH, PT><<<dim3(p.splits, p.s.mt / p.FW, slices), 512, 0, st>>>(
-      XQ, w.NC, w.eN, w.wz, nullptr, OA, ge, ge + two * 32, p.s, p.FW, p.TW, p.tiles_per_split, w.part, w.zpart, w.pe));
-  WERSA_STAGE("split_reduce", st, reduce_kernel<DH, PT><<<dim3(p.s.mt, slices, 2), 256, 0, st>>>(
-      w.part, w.zpart, p.shares, scalars, p.s, const_cast<float *>(saved + sv.S), const_cast<float *>(saved + sv.z), nullptr, w.pe,
-      SOperands{ge + two * 32, w.dSA, w.dSB, w.edS, w.edz}, SOperands{ge, w.SA, nullptr, eS, nullptr}));
+      XQ, w.NC, w.ddw, OA, p.s, p.FW, p.TW, p.tiles_per_split, w.part, w.zpart));
+  WERSA_STAGE("split_reduce", st, reduce_kernel<DH><<<dim3(p.s.mt, slices, 2), 256, 0, st>>>(
+      w.part, w.zpart, p.shares, PT == 1 ? 3 : 1, scalars, p.s, const_cast<float *>(saved + sv.S), const_cast<float *>(saved + sv.z),
+      nullptr, w.dSA, w.dSB, w.SA));
   const GradRows<T> rowsK{v, nullptr, nullptr, vec}, rowsQ{dout, ln ? out : nullptr, PT == 1 ? nullptr : D, vec};
   if constexpr (DH == 128) {   // (dV on its own: no registers left for its accumulators; first, dK_F may go in the place of K_F)
-    launch_apply<T, DH, PT, 2>(c, p, XK, exK, OAk, w.dSB, w.edS, nullptr, scalars, dv, tv, nullptr, nullptr, st);
-    launch_grad<T, DH, PT, false>(c, p, XK, exK, rowsK, nullptr, nullptr, OAk, w.dSA, OBk, nullptr, w.edS, w.edz, scalars, w.gk,
-                                  nullptr, tv, st);
+    launch_apply<T, DH, PT, 2>(c, p, XK, OAk, w.dSB, nullptr, scalars, dv, tv, nullptr, nullptr, st);
+    launch_grad<T, DH, PT, false>(c, p, XK, rowsK, nullptr, nullptr, OAk, w.dSA, OBk, nullptr, scalars, w.gk, nullptr, tv, st);
   } else {
-    launch_grad<T, DH, PT, true>(c, p, XK, exK, rowsK, nullptr, nullptr, OAk, w.dSA, OBk, w.dSB, w.edS, w.edz, scalars, w.gk, dv, tv,
-                                 st);
+    launch_grad<T, DH, PT, true>(c, p, XK, rowsK, nullptr, nullptr, OAk, w.dSA, OBk, w.dSB, scalars, w.gk, dv, tv, st);
   }
-  launch_grad<T, DH, PT, false>(c, p, XQ, nullptr, rowsQ, w.ddw, PT == 1 ? w.rowscale : nullptr, OA, w.SA, OB, nullptr, eS, eS + slices,
-                                scalars, w.gq, nullptr, tv, st);
+  launch_grad<T, DH, PT, false>(c, p, XQ, rowsQ, w.ddw, PT == 1 ? w.rowscale : nullptr, OA, w.SA, OB, nullptr, scalars, w.gq,
+                                nullptr, tv, st);
   const int prow = p.groups + (deep ? c.d / kCoarseCols : 0);
   WERSA_STAGE("split_dots", st, dots_kernel<T, DH><<<dim3(p.groups, slices, 2), 256, 0, st>>>(
       q, k, tv, w.gq, w.gk, p.s, c.L, prow, w.partQ, w.partK, w.tgq, w.tgk));
@@ -1958,7 +1690,7 @@ wersa_status backward_t(const wersa_desc &c, const T *q, const T *k, const T *v,
       w.partQ, w.partK, prow, c.L, c.d, c.H, saved + sv.s, gate_w, scale_w, w.dF, w.dlogit, w.dqbar,
       (c.flags & WERSA_FLAG_POOLED_GATE) ? 1 : 0));
   WERSA_STAGE("gate_bwd_params_kernel", st, gate_bwd_params_kernel<<<gate_bwd_params_blocks(c.H, c.L, c.d), 256, 0, st>>>(
-      w.dF, w.dlogit, saved + sv.s, saved + sv.qbar, w.dpart, slices * p.row_groups, c.B, c.H, c.L, c.d, c.eps, scalars, dgate_w,
+      w.dF, w.dlogit, saved + sv.s, saved + sv.qbar, w.dpart, slices * p.groups, c.B, c.H, c.L, c.d, c.eps, scalars, dgate_w,
       dgate_b, dscale_w, dsigma));
   WERSA_STAGE("split_filter_bwd", st, filter_bwd_kernel<T, DH><<<dim3(p.groups, slices, 2), 256, 0, st>>>(
       w.gq, w.gk, dq, dk, tv, p.s, c.L, coef, w.aq, w.ak, w.dqbar, 1.0f / (float)c.n));
@@ -1977,10 +1709,10 @@ wersa_status dispatch(const wersa_desc &c, F f) {
                                    : f(tag, integral_constant<int, 32>(), integral_constant<int, 1>());
     }
     switch (DH) {
-      case 16: return f(tag, integral_constant<int, 16>(), integral_constant<int, 2>());
-      case 32: return f(tag, integral_constant<int, 32>(), integral_constant<int, 2>());
-      case 64: return f(tag, integral_constant<int, 64>(), integral_constant<int, 2>());
-      default: return f(tag, integral_constant<int, 128>(), integral_constant<int, 2>());
+      case 16: return f(tag, integral_constant<int, 16>(), integral_constant<int, 3>());
+      case 32: return f(tag, integral_constant<int, 32>(), integral_constant<int, 3>());
+      case 64: return f(tag, integral_constant<int, 64>(), integral_constant<int, 3>());
+      default: return f(tag, integral_constant<int, 128>(), integral_constant<int, 3>());
     }
   };
   return c.dtype == WERSA_F32 ? by_dh(float()) : by_dh(bf16_t());
@@ -1990,11 +1722,10 @@ wersa_status dispatch(const wersa_desc &c, F f) {
 
 SplitSizes split_sizes(const wersa_desc &c) {
   const Plan p = plan_of(c);
-  const int64_t slices = (int64_t)c.B * c.H, kept = keeps_operands(c, p) ? slices : 0, X = tile_floats(kept * p.s.nt * p.KS * p.XT);
+  const int64_t X = keeps_operands(c, p) ? tile_floats((int64_t)c.B * c.H * p.s.nt * p.KS * 3) : 0;
   // (one feature tile more than there are: a stage of the row kernels reads whole groups of them)
-  return SplitSizes{X, tile_floats((int64_t)(p.matrices * p.s.mt + 1) * p.KS * p.OT),
-                    tile_floats((int64_t)(p.matrices * p.s.mt + 1) * 2 * p.CT * c_tiles(p.DH, p.PT)), kept * p.s.nt * 32,
-                    kept * p.s.nt, 2 * kept * p.shares * p.s.mt, 2 * slices, (int64_t)p.matrices * p.s.mt * 32};
+  return SplitSizes{X, tile_floats((int64_t)(p.matrices * p.s.mt + 1) * p.KS * p.PT),
+                    tile_floats((int64_t)(p.matrices * p.s.mt + 1) * 2 * p.CT * p.PT)};
 }
 size_t split_workspace_bytes(const wersa_desc &c, int for_backward) {
   const Plan p = plan_of(c);

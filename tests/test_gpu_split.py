@@ -1,4 +1,4 @@
-"""Split path (float32 arithmetic on the 16-bit matrix cores: two or three terms per float32 operand) at the sizes
+"""Split path (float32 arithmetic on the bf16 matrix cores: three bf16 terms per float32 operand) at the sizes
 where its kernels change shape: head dimensions padded to 16, 32, 64, 128; feature counts that are not whole
 32-feature tiles, or an odd number of them; token counts around the 32- and 64-row tiles and the
 4096-element workgroups; few rows (2-wave workgroups) and many (4 waves, 8 at head dimension 64); rows that are not 16-byte
@@ -224,11 +224,10 @@ def test_where_a_value_that_is_not_finite_goes(dtype, d, m, L, bad):
 @pytest.mark.parametrize("d,m,n", [(16, 96, 200), (32, 64, 500), (64, 96, 330), (128, 64, 200)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_magnitudes_far_apart(dtype, d, m, n):
-    """The powers of two that take the operands into fp16's range: tokens up to 2^20 apart in Q, K and V (token tiles of different
-    exponents, 32 tokens at a time), columns of V and features of Omega 2^8 apart, dO 2^30 above the rest.  Every column of O and dV,
-    every feature of S and z and every row of dQ on its own: the worst of 2^-24 per factor and term grows with the sum's length
-    as sqrt(n + m) at most, times 4 for cancellation; bf16: the output's rounding.  A column 2^-8 below the largest keeps 22 bits in
-    a token tile whose exponent is the least favourable: 2^-22, within that."""
+    """Tokens up to 2^20 apart in Q, K and V, columns of V and features of Omega 2^8 apart, dO 2^30 above the rest.  Every row and
+    column of S, every feature of z, every row of O and every column of dV on its own: the worst of 2^-24 per factor and term grows
+    with the sum's length as sqrt(n + m) at most, times 4 for cancellation; bf16: the output's rounding.  dQ and dK as a whole here,
+    element by element in test_columns_of_unlike_size."""
     import torch
     from paper_2507_08637_amd import binding
     g = torch.Generator(device="cuda").manual_seed(d + n)
@@ -272,3 +271,87 @@ def test_magnitudes_far_apart(dtype, d, m, n):
     if dtype == "f32":   # (dQ and dK through cancellation: their size, and that nothing overflowed on the way)
         for a, r in ((got["dq"], gQ), (got["dk"], gK)):
             assert bool(torch.isfinite(a).all()) and float((a[0, 0].double() - r).norm() / r.norm()) < 1e-4
+
+
+@pytest.mark.parametrize("d,m,n", [(16, 64, 8200), (32, 64, 4100), (64, 64, 8200), (128, 96, 4100)])   # 33 to 129 shares of the tokens
+@pytest.mark.parametrize("kind,k", [("columns", 24), ("columns", 40), ("classes", 40), ("projection", 40)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_columns_of_unlike_size(dtype, kind, k, d, m, n):
+    """Every operand has float32's exponent range element by element, so no element of a result loses to a larger one beside it.
+    columns: half of the columns of V times 2^-k, of dO times 2^k, so both halves have the same weight in dPhi.
+    classes: the small columns of one half of the tokens are the large ones of the other half, and no feature sees both, so no power
+    of two per row and column makes the tokens alike.
+    projection: half of the columns of Q and K times 2^-k, of Omega's rows times 2^k.
+    Each element is held to its own sum of absolute values: 2^-24 for each rounding on its way, all of them the same way round.
+    Accumulators: d / 16 steps (projection, dPhi), 2 * 8 of a share, 129 shares at most, m / 16, six products each (three of them below 2^-16);
+    operands and scalings 20.  bf16 storage: O, which the backward reads, and the result are rounded by 2^-9 each; the rounding of O
+    comes back in dD, and through dz in dK: 2^-7.  Rows of dQ and dK with a pre-activation within 2^-16 of its own sum of absolute
+    values are left out: it may fall on the other side of the ReLU's step."""
+    import torch
+    from paper_2507_08637_amd import binding
+    g = torch.Generator(device="cuda").manual_seed(d + n + k)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+
+    def normal(*s):
+        return torch.randn(s, generator=g, device="cuda")
+
+    q, k_, v, do = normal(n, d) + 0.3, normal(n, d) + 0.3, 0.3 * normal(n, d) + 1, 0.3 * normal(n, d) + 0.5
+    omega = normal(d, m)
+    half = torch.arange(d, device="cuda") % 2 == 0
+    if kind == "projection":
+        q[:, half] *= 2.0 ** -k
+        k_[:, half] *= 2.0 ** -k
+        omega[half] *= 2.0 ** k
+    else:
+        small = half.expand(n, d)
+        if kind == "classes":
+            second = torch.arange(n, device="cuda") % 2 == 1
+            small = small ^ second[:, None]
+            for x in (q, k_):
+                x *= 0.2
+                x[:, 0] = torch.where(second, -30.0, 30.0)
+            omega[0] = torch.where(torch.arange(m, device="cuda") % 2 == 1, -1.0, 1.0)
+        v[small] *= 2.0 ** -k
+        do[small] *= 2.0 ** k
+    q, k_, v, do = (x.to(tdt)[None, None] for x in (q, k_, v, do))
+    omega = omega.to(tdt)
+    par = (omega, torch.ones(1, device="cuda"), torch.zeros(1, 1, d, device="cuda"), torch.zeros(1, 1, device="cuda"),
+           2 * torch.ones(1, device="cuda"))   # no levels, F = 1
+    out, saved = binding.wersa_forward(q, k_, v, *par, 0, eps=1e-30, flags=1)
+    got = binding.wersa_backward(q, k_, v, *par, out, do, saved, 0, eps=1e-30, flags=1)
+    sv = binding.saved_views(binding.make_desc(q, 0, m, 1e-30, 1e-6, 1), saved)
+
+    # the exact values and, with the same products of absolute values, what each element is a sum of
+    def chain(sign):
+        f = (lambda x: x) if sign else torch.abs
+        Q, K, V, dO, W = (f(x.double().reshape(-1, x.shape[-1])) for x in (q, k_, v, do, omega))
+        phi = [(X @ W / m ** 0.5) * on for X, on in ((Q, on_q), (K, on_k))]
+        S, z = phi[1].t() @ V, phi[1].sum(0)
+        D = phi[0] @ z if sign else real["D"]
+        O = phi[0] @ S / D[:, None]
+        dN, dD = dO / D[:, None], f(-(dO * O).sum(1) / D)
+        dS, dz = phi[0].t() @ dN, phi[0].t() @ dD
+        dQ = ((dN @ S.t() + dD[:, None] * z) * on_q) @ W.t() / m ** 0.5
+        dK = ((V @ dS.t() + dz) * on_k) @ W.t() / m ** 0.5
+        return dict(S=S, z=z, D=D, O=O, dq=dQ, dk=dK, dv=phi[1] @ dS)
+
+    W = omega.double()
+    R = [x[0, 0].double() @ W for x in (q, k_)]
+    on_q, on_k = ((r > 0).double() for r in R)
+    sure = [(r.abs() > 2.0 ** -16 * (x[0, 0].double().abs() @ W.abs())).all(1) for r, x in zip(R, (q, k_))]
+    real = chain(True)
+    size = chain(False)
+    roundings = 6 * (2 * (d // 16) + 2 * 8 + m // 16) + 129 + 20
+    bound = roundings * 2.0 ** -24
+    errs = {}
+    for name, a in dict(S=sv["S"][0], z=sv["z"][0], O=out[0, 0], dq=got["dq"][0, 0], dk=got["dk"][0, 0], dv=got["dv"][0, 0]).items():
+        assert bool(torch.isfinite(a).all()), name
+        e = (a.double() - real[name]).abs() / size[name]
+        if name in ("dq", "dk"):
+            keep = sure[name == "dk"]
+            assert int(keep.sum()) > n // 2
+            e = e[keep]
+        errs[name] = float(e.max())
+    print(dtype, kind, k, d, {x: f"{e:.1e}" for x, e in errs.items()}, f"bound {bound:.1e}", flush=True)
+    for name, e in errs.items():
+        assert e < bound + (2.0 ** -7 if dtype == "bf16" and name not in ("S", "z") else 0), (name, errs)
