@@ -2459,12 +2459,15 @@ FastPlan fast_plan(const wersa_desc &c) {
   int want = 512 / (slices * (c.m / p.MB));   // two resident workgroups per compute unit, one round
   if (want < 1) want = 1;
   if (want > blocks) want = blocks;
-  // Eight waves per workgroup (256 features) as soon as three quarters of the compute units get one: at 192 (12 slices of 512 or
-  // 640 rows, m 512) both forms take 10 to 13 us, with four blocks per workgroup the eight waves are 11 to 24 % faster, and below, where
-  // each workgroup has one block, four waves on twice the compute units have less to wait for.
-  p.NWC = 4;
-  if (c.d == 128 && c.m % 256 == 0 && (int64_t)slices * (c.m / 256) * want >= 192) { p.NWC = 8; p.MB = 256; }
   const int bpc = (blocks + want - 1) / want;
+  // Eight waves per workgroup (256 features) from two 64-row blocks per workgroup on: what they save is the second time that a row
+  // is brought in and prepared, and from the second block on loads run under products.  With one block four waves on twice the
+  // workgroups have less to wait for.  Both kernels' time (forward and backward form), eight waves against four, at 96 to 256
+  // workgroups of eight: one block 1.18 times at 96 to 128 workgroups, 0.92 to 1.11 at 140 to 256 (10.9 + 12.9 us against 10.5 + 12.9 in
+  // the mean); two blocks 0.92 to 0.99, from 129 workgroups (43 slices of 384 rows, m 256: 24.2 us against 24.8) to 256; three 0.86 to 0.97,
+  // four 0.86 to 0.98, six and more 0.73 to 0.89.  (More blocks than one always make 128 workgroups or more.)
+  p.NWC = 4;
+  if (c.d == 128 && c.m % 256 == 0 && bpc >= 2) { p.NWC = 8; p.MB = 256; }
   p.rowsC = bpc * 64;
   p.chunksC = (blocks + bpc - 1) / bpc;
   const int wantL = kLnWgs / slices < 1 ? 1 : kLnWgs / slices, bpl = (blocks + wantL - 1) / wantL;

@@ -127,10 +127,10 @@ def test_partial_last_block_against_the_oracle(shape, flags):
     assert all(v < 2e-2 for k, v in errs.items() if not (small and k in ("dQ", "dK"))), errs
 
 
-# The contraction kernel of head dimension 128 runs eight waves per workgroup from 192 such workgroups on: twelve slices and 512
-# features are 24 per chunk of the rows, so eight 64-row blocks are the line.
+# The contraction kernel of head dimension 128 runs eight waves per workgroup where each has two 64-row blocks or more: twelve slices
+# and 512 features leave ten chunks of the rows per slice, so eleven blocks are the line.
 @pytest.mark.parametrize("flags", [0, 8])
-@pytest.mark.parametrize("n", [448, 449, 512, 1100, 1344, 2000])   # 7 blocks; 8, the last one row; 8; chunks of 2, 3 and 4 blocks
+@pytest.mark.parametrize("n", [448, 449, 512, 640, 641, 1100, 1344, 2000])   # one block each; 11 blocks, the last one row; chunks of 2, 3, 4
 def test_contraction_with_eight_waves(n, flags):
     """S and z (K side), dK (the dS and dz that the Q side leaves) and d sigma (its sum of dD) against float32 arithmetic on the
     same inputs; the bounds are those above: bf16 features and rows, 2^-9 each."""
