@@ -13,11 +13,12 @@
 // element on the split and two on ReLU or mask.  Counters (128 slices of 4000 tokens, d 32, m 1024, float32, and 8 of
 // 131072, d 16, bf16): matrix cores busy 65 to 73 and 72 to 79 % of a SIMD's cycles in the four contraction kernels,
 // vector units 45 to 59 and 44 to 56 %; two waves per SIMD let one run under the other.  From d 64 on the matrix cores
-// alone.  grad_kernel with dV at d 64 keeps 72 bytes per lane in scratch (its accumulators and operands fill the 256 registers).
+// alone.  Scratch: grad_kernel with dV at d 64 88 bytes per lane, without dV at d 16 with three-term operands 16 (accumulators
+// and operands fill the 256 registers).
 //
 // Measured against the generic kernels, which write every n x m feature matrix to memory: float32 training step, 128
-// slices of 4000 tokens, d 32, m 1024: 13990 -> 2456 us; bf16 training step, 8 slices of 131072 tokens, d 16, m 1024:
-// 26290 -> 2251 us; float32 inference, one slice of 1024 tokens, d 64, m 64: 118 -> 37 us.
+// slices of 4000 tokens, d 32, m 1024: 13990 -> 2463 us; bf16 training step, 8 slices of 131072 tokens, d 16, m 1024:
+// 26290 -> 2271 us; float32 inference, one slice of 1024 tokens, d 64, m 64: 118 -> 34 us.
 //
 // Layout: every operand is kept in the order in which a wave loads it ("operand tile": 32 vectors x 16
 // k-values of bf16; lane (l32, h) holds vector l32, k = 8 h .. 8 h + 7, 16 bytes; 1 KiB).  Where k runs
@@ -170,7 +171,8 @@ __device__ __forceinline__ f32x16 mfma_terms(f32x16 acc, const bf16x8 *x, const 
   }
   return acc;
 }
-// The same products with the leading one in acc and the others in lo (see apply_terms); lo may be acc.
+// acc + lo += the product of a three-term operand with one of NB terms, smallest products first.  acc takes the product of the
+// leading terms, lo the others (lo may be acc).
 template <int NB>
 __device__ __forceinline__ void add_terms(f32x16 &acc, f32x16 &lo, const bf16x8 *x, const bf16x8 *y) {
   if (NB == 3) {
@@ -362,19 +364,14 @@ struct Geo {
   // free: [S0 | S1] and [S2 | 0] take four products instead of six (see apply_terms).
   static constexpr int NSB = DH == 16 ? 4 : 6 * CT;
 };
-// Phi S for one half of a feature tile and one column tile; sb: the operand tiles of S from lds_operand.  acc takes the
-// product of the leading terms, lo all others (together Phi S; lo may be acc): acc is rounded once per 16 features instead of six
-// times, and the slight bias of the matrix cores' rounding towards zero stays in proportion.  In one accumulator O came
-// out 9e-8 too small at 4096 features, the same in all columns of a row, which <dO, O> does not average out.
-// One float32 sequence of 2048 tokens, d 32, 4096 features, error against float64: O 6.9e-7 -> 3.4e-7, dQ 8.9e-7 -> 2.7e-7,
-// dW_g 4.3e-7 -> 1.3e-7; 4000 tokens, 1024 features: 3.8e-7 -> 1.7e-7, 5.0e-7 -> 2.2e-7, 1.7e-7 -> 1.2e-7.  Same time: the products are as many.
+// acc + Phi S for one half of a feature tile and one column tile; sb: the operand tiles of S from lds_operand.
 template <int DH>
-__device__ __forceinline__ void apply_terms(f32x16 &acc, f32x16 &lo, const bf16x8 *p, const bf16_t *sb, int a, int ct, int lane) {
+__device__ __forceinline__ void apply_terms(f32x16 &acc, const bf16x8 *p, const bf16_t *sb, int a, int ct, int lane) {
   if (DH == 16) {   // columns 0-15: p0 S2 + (p2 + p1 + p0) S0; columns 16-31: (p2 + p1 + p0) S1; added at the end
     const bf16x8 s01 = lds_operand(sb + 2 * a * kTile, lane), s2 = lds_operand(sb + (2 * a + 1) * kTile, lane);
-    lo = mfma(p[0], s2, lo);
-    lo = mfma(p[2], s01, lo);
-    lo = mfma(p[1], s01, lo);
+    acc = mfma(p[0], s2, acc);
+    acc = mfma(p[2], s01, acc);
+    acc = mfma(p[1], s01, acc);
     acc = mfma(p[0], s01, acc);
     return;
   }
@@ -382,7 +379,7 @@ __device__ __forceinline__ void apply_terms(f32x16 &acc, f32x16 &lo, const bf16x
   bf16x8 y[3];
 #pragma unroll
   for (int i = 0; i < 3; ++i) y[i] = lds_operand(sb + ((a * CT + ct) * 3 + i) * kTile, lane);
-  add_terms<3>(acc, lo, p, y);
+  add_terms<3>(acc, acc, p, y);
 }
 // sum over the levels above four (up to L) of coef_l * (block sum): levels 5 and 6 from the 16-row sums of a tile
 template <int CW>
@@ -646,6 +643,9 @@ __global__ __launch_bounds__(512, 2) void contract_kernel(const bf16_t *X, const
   using G = Geo<DH>;
   constexpr int SG = stage_tokens(DH, PT), NX = G::KS * 3, NY = 2 * G::CT * PT, NS = SG * (NX + NY),
                 NW = 8, U = (NS + NW - 1) / NW;
+  // The leading product in an accumulator of its own, where its registers cost no wave: S (4096 tokens, d 16) 0.70e-7 -> 0.49e-7 from
+  // the exact sum, d 64, 3000 tokens 0.92e-7 -> 0.71e-7; 118 -> 120 us, 48.9 -> 49.0.
+  constexpr bool LO = DH <= 64 && !(DH == 32 && PT == 3);
   __shared__ __attribute__((aligned(16))) bf16_t lds[2][NS * kTile];
   __shared__ __attribute__((aligned(16))) float lw[2][SG * 32];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
@@ -678,9 +678,12 @@ __global__ __launch_bounds__(512, 2) void contract_kernel(const bf16_t *X, const
     }
     if (DH > 16) lw[b][tid & (SG * 32 - 1)] = w ? stw : 1.f;
   };
-  f32x16 acc[G::CT];
+  f32x16 acc[G::CT], lo[LO ? G::CT : 1];
 #pragma unroll
-  for (int ct = 0; ct < G::CT; ++ct) acc[ct] = zero16();
+  for (int ct = 0; ct < G::CT; ++ct) {
+    acc[ct] = zero16();
+    if (LO) lo[LO ? ct : 0] = zero16();
+  }
   float zacc = 0.f;
   const NegIdentity ni(lane);
   if (tb0 < tb1) {
@@ -716,7 +719,7 @@ __global__ __launch_bounds__(512, 2) void contract_kernel(const bf16_t *X, const
             bf16x8 y[PT];
 #pragma unroll
             for (int i = 0; i < PT; ++i) y[i] = lds_operand(ly + ((a * G::CT + ct) * PT + i) * kTile, lane);
-            acc[ct] = mfma_terms<PT, false>(acc[ct], p, y);   // rows: features, columns: columns of Y
+            add_terms<PT>(acc[ct], LO ? lo[LO ? ct : 0] : acc[ct], p, y);   // rows: features, columns: columns of Y
           }
         });
       }
@@ -731,7 +734,7 @@ __global__ __launch_bounds__(512, 2) void contract_kernel(const bf16_t *X, const
 #pragma unroll
   for (int ct = 0; ct < G::CT; ++ct)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) po[(8 * (i >> 2) + 4 * h + (i & 3)) * PW + 32 * ct + l32] = acc[ct][i];
+    for (int i = 0; i < 16; ++i) po[(8 * (i >> 2) + 4 * h + (i & 3)) * PW + 32 * ct + l32] = LO ? acc[ct][i] + lo[LO ? ct : 0][i] : acc[ct][i];
   if (DH > 16) {
     zacc = xor32_sum(zacc);
     if (h == 0) zpart[(pidx * s.mt + ft) * 32 + l32] = zacc;
@@ -882,9 +885,15 @@ struct Stager {
   }
 };
 
-// Whether the small terms have an accumulator of their own (see apply_terms): with one-term operands the results are
+// A sum over the features is taken sum_tiles feature tiles at a time where the registers hold a second accumulator: the
+// matrix cores round an accumulator after every product (and a little towards zero: the same in all columns of a row, which
+// <dO, O> does not average out), and with one for the whole sum its error grows with the square root of m.  An accumulator for the
+// leading products and one for the others are as many registers, but halve the error only.  2048 tokens, d 32, 4096 features, against float64:
+// O 3.4e-7 -> 1.1e-7, dK 3.1e-7 -> 1.0e-7, dV (one accumulator) 5.9e-7 -> 0.9e-7; 4000 tokens, 1024 features: 1.7e-7 -> 0.8e-7,
+// 1.3e-7 -> 0.9e-7, 3.3e-7 -> 0.7e-7.  Their training step (128 slices of the latter) 2430 -> 2463 us.  With one-term operands the results are
 // rounded to bf16, and the registers are worth more (head dimension 16, 8 slices of 131072 tokens: 382 us without, 397 with).
-constexpr bool low_terms(int PT) { return PT == 3; }
+constexpr int sum_tiles(int DH) { return DH <= 32 ? 4 : 1; }
+constexpr bool sum_in_parts(int PT) { return PT == 3; }
 // Waves per SIMD that the register budget is set for.
 constexpr int row_occupancy(int DH, int NW) { return NW >= 4 && DH < 128 ? 2 : 1; }
 
@@ -916,8 +925,8 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(c
   sg.p0 = OA;
   sg.p1 = SB + (int64_t)slice * s.mt * NB * kTile;
   sg.p2 = sg.p3 = nullptr;
-  constexpr bool LO = low_terms(PT);
-  f32x16 acc[RT][G::CT], lo[LO ? RT : 1][G::CT];
+  constexpr bool PARTS = sum_in_parts(PT);
+  f32x16 acc[RT][G::CT], total[PARTS ? RT : 1][G::CT];
   float dsum[RT], dpart[RT];   // Phi z: of all groups of eight feature tiles before, of this one
 #pragma unroll
   for (int r = 0; r < RT; ++r) {
@@ -925,7 +934,7 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(c
 #pragma unroll
     for (int ct = 0; ct < G::CT; ++ct) {
       acc[r][ct] = zero16();
-      if (LO) lo[LO ? r : 0][ct] = zero16();
+      if (PARTS) total[PARTS ? r : 0][ct] = zero16();
     }
   }
   const NegIdentity ni(lane);
@@ -968,7 +977,7 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(c
         if (ZV) dpart[r] += dot16(R, z4);
         with_split<mfma_residuals(DH, PT)>(R, ni, [&](int a, const bf16x8 *p) {
 #pragma unroll
-          for (int ct = 0; ct < G::CT; ++ct) apply_terms<DH>(acc[r][ct], LO ? lo[LO ? r : 0][ct] : acc[r][ct], p, lb, a, ct, lane);   // rows: tokens, lanes: columns
+          for (int ct = 0; ct < G::CT; ++ct) apply_terms<DH>(acc[r][ct], p, lb, a, ct, lane);   // rows: tokens, lanes: columns
         });
       }
     }
@@ -978,6 +987,15 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(c
         dsum[r] += dpart[r];
         dpart[r] = 0.f;
       }
+    }
+    if (PARTS && (!more || (f0 + FC) % sum_tiles(DH) == 0)) {
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int ct = 0; ct < G::CT; ++ct) {
+          total[PARTS ? r : 0][ct] += acc[r][ct];
+          acc[r][ct] = zero16();
+        }
     }
     if (more) {
       sg.put(lds[b ^ 1], wave, lane);
@@ -999,9 +1017,9 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(c
       const int row = 8 * (i >> 2) + 4 * h + (i & 3), t = 32 * tb + row;
       float Dt = 1.f;
       if (ZV) Dt = __shfl(Dl, row, 64);
-      if (LO)
+      if (PARTS)
 #pragma unroll
-        for (int ct = 0; ct < G::CT; ++ct) acc[r][ct][i] += lo[LO ? r : 0][ct][i];
+        for (int ct = 0; ct < G::CT; ++ct) acc[r][ct][i] = total[PARTS ? r : 0][ct][i];
       if (DH == 16) acc[r][0][i] += __shfl_xor(acc[r][0][i], 16, 64);
 #pragma unroll
       for (int ct = 0; ct < G::CT; ++ct) {
@@ -1016,10 +1034,8 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(c
   }
 }
 
-// The gradient kernel: where the registers hold it, too.
-constexpr bool grad_low_terms(int DH, int PT, bool DV, int RT) {
-  return low_terms(PT) && (DH == 32 || (DH == 16 && RT == 1) || (DH == 64 && !DV));
-}
+// The gradient kernel's dX_F likewise, and dV where it rides along (at head dimension 64 it has no registers left for either).
+constexpr bool grad_in_parts(int DH, int PT, bool DV) { return sum_in_parts(PT) && (DH <= 32 || (DH == 64 && !DV)); }
 // dX_F of one side: R = X Omega, G = Y S^T + w z^T (Y = dN, S, w = dD on the query side; Y = V, dS, w = 1
 // on the key side), dX_F = c rowscale ((G masked where R > 0) Omega^T) in float32, row t of a slice at
 // grad_row(t) (in the place of X's operand tiles where these are not needed again: a wave reads its tiles before
@@ -1115,15 +1131,16 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void grad_kernel(co
   sg.p1 = SA + (int64_t)slice * s.mt * NSA * kTile;
   sg.p2 = OB;
   sg.p3 = DV ? SB + (int64_t)slice * s.mt * NSB * kTile : nullptr;
-  constexpr bool LO = grad_low_terms(DH, PT, DV, RT);
-  f32x16 acc[RT][G::CT], low[LO ? RT : 1][G::CT], accv[DV ? RT : 1][G::CT];
+  constexpr bool PARTS = grad_in_parts(DH, PT, DV), VPARTS = PARTS && DV;
+  f32x16 acc[RT][G::CT], total[PARTS ? RT : 1][G::CT], accv[DV ? RT : 1][G::CT], totalv[VPARTS ? RT : 1][G::CT];
 #pragma unroll
   for (int r = 0; r < RT; ++r)
 #pragma unroll
     for (int ct = 0; ct < G::CT; ++ct) {
       acc[r][ct] = zero16();
-      if (LO) low[LO ? r : 0][ct] = zero16();
-      if (DV) accv[r][ct] = zero16();
+      if (PARTS) total[PARTS ? r : 0][ct] = zero16();
+      if (DV) accv[DV ? r : 0][ct] = zero16();
+      if (VPARTS) totalv[VPARTS ? r : 0][ct] = zero16();
     }
   const NegIdentity ni(lane);
   sg.fetch(0, wave, lane);
@@ -1144,14 +1161,25 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void grad_kernel(co
         f32x16 R = zero16(), Gr = zero16();
 #pragma unroll
         for (int ks = 0; ks < G::KS; ++ks) {
-          bf16x8 o[PT], sa[3];
+          bf16x8 o[PT];
 #pragma unroll
           for (int i = 0; i < PT; ++i) o[i] = lds_operand(la + (ks * PT + i) * kTile, lane);
           R = mfma_terms<PT, true>(R, x[r][ks], o);   // rows: features, lanes: tokens
-#pragma unroll
-          for (int i = 0; i < 3; ++i) sa[i] = lds_operand(ls + (ks * 3 + i) * kTile, lane);
-          Gr = mfma_terms<PT, false>(Gr, sa, y[r][ks]);
         }
+        // (the small products of the whole sum first: while they are added the accumulator is small, and so is its rounding)
+        auto go = [&](int ks, int i, int j) { Gr = mfma(lds_operand(ls + (ks * 3 + i) * kTile, lane), y[r][ks][j], Gr); };
+#pragma unroll
+        for (int ks = 0; ks < G::KS; ++ks) {
+          if (PT == 3) {
+            go(ks, 0, PT - 1);
+            go(ks, 1, PT / 2);
+          }
+          go(ks, 2, 0);
+          if (PT == 3) go(ks, 0, PT / 2);
+          go(ks, 1, 0);
+        }
+#pragma unroll
+        for (int ks = 0; ks < G::KS; ++ks) go(ks, 0, 0);
         Gr = mfma(lds_operand(ls + 3 * G::KS * kTile, lane), ext[r], Gr);
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
@@ -1165,15 +1193,28 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void grad_kernel(co
             bf16x8 o[PT];
 #pragma unroll
             for (int i = 0; i < PT; ++i) o[i] = lds_operand(lo + ((a * G::CT + ct) * PT + i) * kTile, lane);
-            add_terms<PT>(acc[r][ct], LO ? low[LO ? r : 0][ct] : acc[r][ct], p, o);   // rows: tokens, lanes: columns
+            add_terms<PT>(acc[r][ct], acc[r][ct], p, o);   // rows: tokens, lanes: columns
           }
         });
         if (DV)
           with_split<mfma_residuals(DH, PT)>(R, ni, [&](int a, const bf16x8 *p) {
 #pragma unroll
-            for (int ct = 0; ct < G::CT; ++ct) apply_terms<DH>(accv[r][ct], accv[r][ct], p, lv, a, ct, lane);
+            for (int ct = 0; ct < G::CT; ++ct) apply_terms<DH>(accv[r][ct], p, lv, a, ct, lane);
           });
       }
+    }
+    if (PARTS && (!more || (f0 + FC) % sum_tiles(DH) == 0)) {
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int ct = 0; ct < G::CT; ++ct) {
+          total[PARTS ? r : 0][ct] += acc[r][ct];
+          acc[r][ct] = zero16();
+          if (VPARTS) {
+            totalv[VPARTS ? r : 0][ct] += accv[DV ? r : 0][ct];
+            accv[DV ? r : 0][ct] = zero16();
+          }
+        }
     }
     if (more) sg.put(lds[b ^ 1], wave, lane);
     __syncthreads();
@@ -1189,9 +1230,12 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void grad_kernel(co
     for (int i = 0; i < 16; ++i) {
       const int row = 8 * (i >> 2) + 4 * h + (i & 3), t = 32 * tb + row;
       const float sc = rowscale ? __shfl(rs, row, 64) : c;
-      if (LO)
+      if (PARTS)
 #pragma unroll
-        for (int ct = 0; ct < G::CT; ++ct) acc[r][ct][i] += low[LO ? r : 0][ct][i];
+        for (int ct = 0; ct < G::CT; ++ct) acc[r][ct][i] = total[PARTS ? r : 0][ct][i];
+      if (VPARTS)
+#pragma unroll
+        for (int ct = 0; ct < G::CT; ++ct) accv[DV ? r : 0][ct][i] = totalv[VPARTS ? r : 0][ct][i];
       if (DV && DH == 16) accv[r][0][i] += __shfl_xor(accv[r][0][i], 16, 64);
 #pragma unroll
       for (int ct = 0; ct < G::CT; ++ct) {

@@ -355,3 +355,18 @@ def test_columns_of_unlike_size(dtype, kind, k, d, m, n):
     print(dtype, kind, k, d, {x: f"{e:.1e}" for x, e in errs.items()}, f"bound {bound:.1e}", flush=True)
     for name, e in errs.items():
         assert e < bound + (2.0 ** -7 if dtype == "bf16" and name not in ("S", "z") else 0), (name, errs)
+
+
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
+def test_sums_over_many_features(d):
+    """Sums over 4096 features are taken in parts (128 features, 32 from d 64 on), so their error does not grow with every product:
+    32 or 128 roundings of the total, 2^-24 of it at most and of random sign, add up to 2^-24 * sqrt(128 / 3) / 2 = 2e-7; the
+    parts' own roundings (24 products each, 48 or more parts) and the operands are below a third of it, D and the rest of O's way
+    2^-24 twice.  Together 3e-7; in one accumulator: O 3.4e-7 and dV 5.9e-7 at 2048 tokens, d 32.  (d 64: dV in one accumulator.)"""
+    cfg = dict(B=1, H=1, n=512, d=d, L=2, m=4096, dtype="f32", flavour="plain", seed_base=6200 + d, q_mean=0.5)
+    p = workloads.make_inputs(**cfg)
+    res = hp.gpu_forward_backward(p, cfg, flags=1)
+    ref = hp.oracle_backward(p, cfg)
+    errs = {k: hp.rel_err(res[k], ref[k]) for k in ("O", "dV")}
+    print(cfg, {k: f"{e:.2e}" for k, e in errs.items()}, flush=True)
+    assert errs["O"] < 3e-7 and (d == 64 or errs["dV"] < 3e-7), errs
