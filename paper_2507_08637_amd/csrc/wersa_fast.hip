@@ -1837,8 +1837,9 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
 
 // ------------------------------------------------------------------------------------
 // The rows kernel of head dimension 128 (modes as above).  A wave owns 32 rows and all 128 columns: X_F and dN or V rows (68
-// registers), the accumulators of the result (64) and of the projection and dPhi (32) fit the 256 registers of two
-// waves per SIMD, so one wave's conversions, masks and LDS latency run under the other's matrix instructions.  Eight waves
+// registers), the accumulators of the result (64) and of the projection and dPhi (32) are for the 256 registers of two
+// waves per SIMD (the gradient modes keep some more in scratch: 116 bytes per lane on the Q side, 136 with a partial last block, 124 and
+// 148 with L > 6, and 28, 76, 36 and 84 on the K side), so one wave's conversions, masks and LDS latency run under the other's matrix instructions.  Eight waves
 // (256 rows) share the feature-side operands, which pass through LDS in stages of kWideTiles feature tiles, double-buffered,
 // by direct global-to-LDS loads: one barrier per stage, the next stage in flight during it.  A feature tile is
 //   Omega^T rows  [32 features][128] fp16, 256-byte rows: 16-byte piece c of row r at slot c ^ (r % 16);
@@ -1846,11 +1847,13 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
 //   Omega or S^T  [128 columns][32 features] bf16, 64-byte rows: piece c of row r at slot c ^ ((r / 4) % 4).
 // An instruction's row l32 is feature l32 with bits 2 and 3 swapped: the features that accumulator registers 8 a .. 8 a + 7 of
 // half-wave h stand for are then 16 a + 8 h .. + 7, one 16-byte piece of the third array.
-// What bounds it: LDS delivers 1 KiB per matrix instruction and wave (about 145 of the 128 bytes per clock that two waves
-// on each SIMD ask for); the epilogue's 64-row level of the Haar filter, the only one that crosses waves, costs a barrier.
+// What bounds it: no unit is full.  32 slices of 65536 rows, m 512 (Q side, K side, forward, dV): matrix cores 39, 43, 46, 53 % busy,
+// vector units 26, 28, 22, 21 %, LDS 24, 26, 32, 33 %; a wave spends 42, 38, 57, 40 % of its cycles at wait counts and barriers.  An
+// operand of 1 KiB read from LDS serves one matrix instruction: at full matrix rate the four SIMDs would ask for 128 bytes per
+// clock, and eight waves that do nothing but read get about 145, so there is little to spare for latency.  The epilogue's 64-row level of the Haar filter, the only one that crosses waves, costs a barrier.
 // Four waves of 64 rows with the whole register file (one per SIMD, 128 staged features, 370 to 400 bytes of scratch per lane)
-// took 1650 (Q side), 1879 (K side), 896 (forward) and 782 us (dV) at 32 slices of 65536 rows, m 512; this form takes 1128, 1083,
-// 624 and 565.  16 slices of 4096 rows with LayerNorm and two random matrices: 68, 68, 41, 32 -> 41, 40, 25, 21.
+// took 1650 (Q side), 1879 (K side), 896 (forward) and 782 us (dV) there; this form takes 1131, 1095,
+// 626 and 576.  16 slices of 4096 rows with LayerNorm and two random matrices: 68, 68, 41, 32 -> 41, 40, 25, 21.
 // ------------------------------------------------------------------------------------
 constexpr int kWideWaves = 8, kWideTiles = 2, kWideRows = 32 * kWideWaves;
 constexpr bool wide_grad(int MODE) { return MODE == 1 || MODE == 2; }

@@ -11,8 +11,8 @@
 // What bounds it: per 32 x 32 tile of a feature matrix the matrix cores spend 32 cycles per product and 16 of the
 // contraction's length (and where they form the residuals, four more products), the vector units 5.5 instructions per
 // element on the split and two on ReLU or mask.  Counters (128 slices of 4000 tokens, d 32, m 1024, float32, and 8 of
-// 131072, d 16, bf16): matrix cores busy 65 to 73 and 72 to 79 % of a SIMD's cycles in the four contraction kernels,
-// vector units 45 to 59 and 44 to 56 %; two waves per SIMD let one run under the other.  From d 64 on the matrix cores
+// 131072, d 16, bf16): matrix cores busy 63 to 73 and 72 to 80 % of a SIMD's cycles in the four contraction kernels,
+// vector units 50 to 60 and 45 to 56 %; two waves per SIMD let one run under the other.  From d 64 on the matrix cores
 // alone.  Scratch: grad_kernel with dV at d 64 88 bytes per lane, without dV at d 16 with three-term operands 16 (accumulators
 // and operands fill the 256 registers).
 //
