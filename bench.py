@@ -67,10 +67,9 @@ def kernel_models(cfg):
         "wersa_haar_stage": ("hbm", "hbm", nd * (e + 2)),       # head dimension 128: one tensor in (bf16), one out (fp16)
         "wersa_phiT_contract": ("mfma", "mfma_bf16", 2 * unit),  # projection + Phi^T Y
         "wersa_rows_fwd": ("mfma", "mfma_bf16", 2 * unit),       # projection + Phi S
-        "wersa_rows_bwd_q": ("mfma", "mfma_bf16", 3 * unit),     # projection, dPhi, dX_F
-        # projection, dPhi, dX_F; with head dimension 64, 256 features per pass and whole 64-row
-        # blocks the kernel also forms dV = Phi dS (a fourth contraction) and no rows_bwd_v launch follows
-        "wersa_rows_bwd_k": ("mfma", "mfma_bf16", (4 if (d == 64 and m % 256 == 0 and n % 64 == 0) else 3) * unit),
+        # dPhi, dX_F; at head dimension 128 the projection, too (64 has its decisions from the kernels before)
+        "wersa_rows_bwd_q": ("mfma", "mfma_bf16", (2 if d == 64 else 3) * unit),
+        "wersa_rows_bwd_k": ("mfma", "mfma_bf16", (2 if d == 64 else 3) * unit),
         "wersa_rows_bwd_v": ("mfma", "mfma_bf16", 2 * unit),     # projection, Phi dS
         "wersa_ln_prep": ("hbm", "hbm", 3 * nd * e),
         "wersa_add_pooled": ("hbm", "hbm", 2 * nd * e),

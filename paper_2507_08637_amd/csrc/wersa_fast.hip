@@ -11,7 +11,8 @@
 //   rows            per 64-row block: ReLU(X_F Omega) again, then either the step-8 apply +
 //                   normaliser (forward; the same apply form gives dV = Phi_K dS), or
 //                   dPhi -> mask -> dX_F -> gated Haar filter of the gradient + per-band
-//                   inner products (backward, Q side and K side)
+//                   inner products (backward, Q side and K side; at head dimension 64 the mask comes as bits
+//                   from the kernel that formed the projection before: phiT_contract and the dV rows)
 // The projection uses fp16 MFMA operands (X_F in fp16 keeps the sign of X_F Omega right to
 // 2^-12, which the ReLU derivative needs); everything downstream of the ReLU uses bf16 MFMA.
 #include "wersa_internal.h"
@@ -41,164 +42,6 @@ __device__ __forceinline__ f32x16 mfma_f16(f16x8 a, f16x8 b, f32x16 c) {
 }
 __device__ __forceinline__ f32x16 mfma_bf16(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-// Projection and dPhi chains with their accumulators forced into architectural VGPRs.  In a
-// kernel that is given the 512-register budget the compiler keeps every MFMA result in
-// accumulation registers, and VALU work on a result then costs one v_accvgpr_read per element;
-// the projection (R) and dPhi (G) tiles of the gradient kernel are consumed by VALU at once, so
-// they are better off in VGPRs.  The compiler does not see through an asm statement, so each
-// statement is hazard-safe on its own: dependent MFMAs are never adjacent (the two chains
-// alternate), and the statement ends with the wait states an 8-pass MFMA needs before anything
-// (VALU, a copy, a spill) may read its result.
-//   chain_first: G = sum_{k<5} ma_k yb_k, R = sum_{k<4} oa_k xb_k.
-__device__ __forceinline__ void chain_first(f32x16 &R, f32x16 &G, const f16x8 *oa, const f16x8 *xb,
-                                            const bf16x8 *ma, const bf16x8 *yb) {
-  asm volatile(
-      "v_mfma_f32_32x32x16_bf16 %1, %10, %15, 0\n\t"
-      "v_mfma_f32_32x32x16_f16 %0, %2, %6, 0\n\t"
-      "v_mfma_f32_32x32x16_bf16 %1, %11, %16, %1\n\t"
-      "v_mfma_f32_32x32x16_f16 %0, %3, %7, %0\n\t"
-      "v_mfma_f32_32x32x16_bf16 %1, %12, %17, %1\n\t"
-      "v_mfma_f32_32x32x16_f16 %0, %4, %8, %0\n\t"
-      "v_mfma_f32_32x32x16_bf16 %1, %13, %18, %1\n\t"
-      "v_mfma_f32_32x32x16_f16 %0, %5, %9, %0\n\t"
-      "v_mfma_f32_32x32x16_bf16 %1, %14, %19, %1\n\t"
-      "s_nop 11"
-      : "=&v"(R), "=&v"(G)
-      : "v"(oa[0]), "v"(oa[1]), "v"(oa[2]), "v"(oa[3]), "v"(xb[0]), "v"(xb[1]), "v"(xb[2]), "v"(xb[3]),
-        "v"(ma[0]), "v"(ma[1]), "v"(ma[2]), "v"(ma[3]), "v"(ma[4]), "v"(yb[0]), "v"(yb[1]), "v"(yb[2]),
-        "v"(yb[3]), "v"(yb[4]));
-}
-// The same chains with their results in fixed registers (tile 0 of a 64-row block: R, G in
-// v[192:207], v[208:223]; tile 1: v[224:239], v[240:255]), so that a chain's statement can also
-// carry the mask multiplies of the OTHER tile's finished chain, G_i *= clamp(R_i * 2^100, 0, 1),
-// written on those registers between its MFMAs: the VALU work runs while the matrix pipe works
-// through the chain instead of after it.  Hazards: the masked registers were written by the
-// previous chain statement, which ends with the wait states its last MFMA needs; no MFMA here
-// reads a register the multiplies write.
-__device__ __forceinline__ void chain0_first(f32x16 &R0, f32x16 &G0, const f16x8 *oa, const f16x8 *xb,
-                                             const bf16x8 *ma, const bf16x8 *yb) {
-  asm volatile(
-      "v_mfma_f32_32x32x16_bf16 %1, %10, %15, 0\n\t"
-      "v_mfma_f32_32x32x16_f16 %0, %2, %6, 0\n\t"
-      "v_mfma_f32_32x32x16_bf16 %1, %11, %16, %1\n\t"
-      "v_mfma_f32_32x32x16_f16 %0, %3, %7, %0\n\t"
-      "v_mfma_f32_32x32x16_bf16 %1, %12, %17, %1\n\t"
-      "v_mfma_f32_32x32x16_f16 %0, %4, %8, %0\n\t"
-      "v_mfma_f32_32x32x16_bf16 %1, %13, %18, %1\n\t"
-      "v_mfma_f32_32x32x16_f16 %0, %5, %9, %0\n\t"
-      "v_mfma_f32_32x32x16_bf16 %1, %14, %19, %1\n\t"
-      "s_nop 11"
-      : "=&{v[192:207]}"(R0), "=&{v[208:223]}"(G0)
-      : "v"(oa[0]), "v"(oa[1]), "v"(oa[2]), "v"(oa[3]), "v"(xb[0]), "v"(xb[1]), "v"(xb[2]), "v"(xb[3]),
-        "v"(ma[0]), "v"(ma[1]), "v"(ma[2]), "v"(ma[3]), "v"(ma[4]), "v"(yb[0]), "v"(yb[1]), "v"(yb[2]),
-        "v"(yb[3]), "v"(yb[4]));
-}
-// chain of tile 1 (R1, G1) with the mask of tile 0 (G0 *= 1[R0 > 0])
-__device__ __forceinline__ void chain1_mask0(f32x16 &R1, f32x16 &G1, f32x16 &G0, const f32x16 &R0,
-                                             const f16x8 *oa, const f16x8 *xb, const bf16x8 *ma,
-                                             const bf16x8 *yb, float big) {
-  float tmp;
-  asm volatile(
-      "v_mfma_f32_32x32x16_bf16 %1, %12, %17, 0\n\t"
-      "v_mul_f32_e64 %3, v192, %23 clamp\n\t"
-      "v_mul_f32_e32 v208, v208, %3\n\t"
-      "v_mul_f32_e64 %3, v193, %23 clamp\n\t"
-      "v_mul_f32_e32 v209, v209, %3\n\t"
-      "v_mfma_f32_32x32x16_f16 %0, %4, %8, 0\n\t"
-      "v_mul_f32_e64 %3, v194, %23 clamp\n\t"
-      "v_mul_f32_e32 v210, v210, %3\n\t"
-      "v_mul_f32_e64 %3, v195, %23 clamp\n\t"
-      "v_mul_f32_e32 v211, v211, %3\n\t"
-      "v_mfma_f32_32x32x16_bf16 %1, %13, %18, %1\n\t"
-      "v_mul_f32_e64 %3, v196, %23 clamp\n\t"
-      "v_mul_f32_e32 v212, v212, %3\n\t"
-      "v_mul_f32_e64 %3, v197, %23 clamp\n\t"
-      "v_mul_f32_e32 v213, v213, %3\n\t"
-      "v_mfma_f32_32x32x16_f16 %0, %5, %9, %0\n\t"
-      "v_mul_f32_e64 %3, v198, %23 clamp\n\t"
-      "v_mul_f32_e32 v214, v214, %3\n\t"
-      "v_mul_f32_e64 %3, v199, %23 clamp\n\t"
-      "v_mul_f32_e32 v215, v215, %3\n\t"
-      "v_mfma_f32_32x32x16_bf16 %1, %14, %19, %1\n\t"
-      "v_mul_f32_e64 %3, v200, %23 clamp\n\t"
-      "v_mul_f32_e32 v216, v216, %3\n\t"
-      "v_mul_f32_e64 %3, v201, %23 clamp\n\t"
-      "v_mul_f32_e32 v217, v217, %3\n\t"
-      "v_mfma_f32_32x32x16_f16 %0, %6, %10, %0\n\t"
-      "v_mul_f32_e64 %3, v202, %23 clamp\n\t"
-      "v_mul_f32_e32 v218, v218, %3\n\t"
-      "v_mul_f32_e64 %3, v203, %23 clamp\n\t"
-      "v_mul_f32_e32 v219, v219, %3\n\t"
-      "v_mfma_f32_32x32x16_bf16 %1, %15, %20, %1\n\t"
-      "v_mul_f32_e64 %3, v204, %23 clamp\n\t"
-      "v_mul_f32_e32 v220, v220, %3\n\t"
-      "v_mul_f32_e64 %3, v205, %23 clamp\n\t"
-      "v_mul_f32_e32 v221, v221, %3\n\t"
-      "v_mfma_f32_32x32x16_f16 %0, %7, %11, %0\n\t"
-      "v_mul_f32_e64 %3, v206, %23 clamp\n\t"
-      "v_mul_f32_e32 v222, v222, %3\n\t"
-      "v_mul_f32_e64 %3, v207, %23 clamp\n\t"
-      "v_mul_f32_e32 v223, v223, %3\n\t"
-      "v_mfma_f32_32x32x16_bf16 %1, %16, %21, %1\n\t"
-      "s_nop 11"
-      : "=&{v[224:239]}"(R1), "=&{v[240:255]}"(G1), "+{v[208:223]}"(G0), "=&v"(tmp)
-      : "v"(oa[0]), "v"(oa[1]), "v"(oa[2]), "v"(oa[3]), "v"(xb[0]), "v"(xb[1]), "v"(xb[2]), "v"(xb[3]),
-        "v"(ma[0]), "v"(ma[1]), "v"(ma[2]), "v"(ma[3]), "v"(ma[4]), "v"(yb[0]), "v"(yb[1]), "v"(yb[2]),
-        "v"(yb[3]), "v"(yb[4]), "{v[192:207]}"(R0), "s"(big));
-}
-// chain of tile 0 (R0, G0) of the next feature tile with the mask of tile 1 (G1 *= 1[R1 > 0])
-__device__ __forceinline__ void chain0_mask1(f32x16 &R0, f32x16 &G0, f32x16 &G1, const f32x16 &R1,
-                                             const f16x8 *oa, const f16x8 *xb, const bf16x8 *ma,
-                                             const bf16x8 *yb, float big) {
-  float tmp;
-  asm volatile(
-      "v_mfma_f32_32x32x16_bf16 %1, %12, %17, 0\n\t"
-      "v_mul_f32_e64 %3, v224, %23 clamp\n\t"
-      "v_mul_f32_e32 v240, v240, %3\n\t"
-      "v_mul_f32_e64 %3, v225, %23 clamp\n\t"
-      "v_mul_f32_e32 v241, v241, %3\n\t"
-      "v_mfma_f32_32x32x16_f16 %0, %4, %8, 0\n\t"
-      "v_mul_f32_e64 %3, v226, %23 clamp\n\t"
-      "v_mul_f32_e32 v242, v242, %3\n\t"
-      "v_mul_f32_e64 %3, v227, %23 clamp\n\t"
-      "v_mul_f32_e32 v243, v243, %3\n\t"
-      "v_mfma_f32_32x32x16_bf16 %1, %13, %18, %1\n\t"
-      "v_mul_f32_e64 %3, v228, %23 clamp\n\t"
-      "v_mul_f32_e32 v244, v244, %3\n\t"
-      "v_mul_f32_e64 %3, v229, %23 clamp\n\t"
-      "v_mul_f32_e32 v245, v245, %3\n\t"
-      "v_mfma_f32_32x32x16_f16 %0, %5, %9, %0\n\t"
-      "v_mul_f32_e64 %3, v230, %23 clamp\n\t"
-      "v_mul_f32_e32 v246, v246, %3\n\t"
-      "v_mul_f32_e64 %3, v231, %23 clamp\n\t"
-      "v_mul_f32_e32 v247, v247, %3\n\t"
-      "v_mfma_f32_32x32x16_bf16 %1, %14, %19, %1\n\t"
-      "v_mul_f32_e64 %3, v232, %23 clamp\n\t"
-      "v_mul_f32_e32 v248, v248, %3\n\t"
-      "v_mul_f32_e64 %3, v233, %23 clamp\n\t"
-      "v_mul_f32_e32 v249, v249, %3\n\t"
-      "v_mfma_f32_32x32x16_f16 %0, %6, %10, %0\n\t"
-      "v_mul_f32_e64 %3, v234, %23 clamp\n\t"
-      "v_mul_f32_e32 v250, v250, %3\n\t"
-      "v_mul_f32_e64 %3, v235, %23 clamp\n\t"
-      "v_mul_f32_e32 v251, v251, %3\n\t"
-      "v_mfma_f32_32x32x16_bf16 %1, %15, %20, %1\n\t"
-      "v_mul_f32_e64 %3, v236, %23 clamp\n\t"
-      "v_mul_f32_e32 v252, v252, %3\n\t"
-      "v_mul_f32_e64 %3, v237, %23 clamp\n\t"
-      "v_mul_f32_e32 v253, v253, %3\n\t"
-      "v_mfma_f32_32x32x16_f16 %0, %7, %11, %0\n\t"
-      "v_mul_f32_e64 %3, v238, %23 clamp\n\t"
-      "v_mul_f32_e32 v254, v254, %3\n\t"
-      "v_mul_f32_e64 %3, v239, %23 clamp\n\t"
-      "v_mul_f32_e32 v255, v255, %3\n\t"
-      "v_mfma_f32_32x32x16_bf16 %1, %16, %21, %1\n\t"
-      "s_nop 11"
-      : "=&{v[192:207]}"(R0), "=&{v[208:223]}"(G0), "+{v[240:255]}"(G1), "=&v"(tmp)
-      : "v"(oa[0]), "v"(oa[1]), "v"(oa[2]), "v"(oa[3]), "v"(xb[0]), "v"(xb[1]), "v"(xb[2]), "v"(xb[3]),
-        "v"(ma[0]), "v"(ma[1]), "v"(ma[2]), "v"(ma[3]), "v"(ma[4]), "v"(yb[0]), "v"(yb[1]), "v"(yb[2]),
-        "v"(yb[3]), "v"(yb[4]), "{v[224:239]}"(R1), "s"(big));
 }
 __device__ __forceinline__ f32x16 zero16() {
   f32x16 z;
@@ -587,6 +430,79 @@ __device__ __forceinline__ bf16x8 tile_cols_operand(const bf16_t *tile, int stri
   return r;
 }
 
+// A value that the compiler re-derives from in every block: offsets that depend on the lane alone would otherwise be
+// kept in registers across the feature loop and spill (60 bytes per lane in the kernel with dV).
+__device__ __forceinline__ uint32_t opaque(uint32_t v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+// ------------------------------------------------------------------------------------
+// The ReLU's decisions 1[R > 0] of the backward as bits: the kernel that forms the projection of a side for dS (queries) or dV
+// (keys) leaves them for the gradient kernel of that side, which then needs neither X_F nor the projection.
+// One 32-bit word per (64-row block, half ti of its rows, 64 features 64 w ..) and position p:
+//   bits[slice][block][ti][w / 2][p][w % 2]; n m / 8 bytes per slice.
+// With r, f the row and the feature inside 32 (r_k, f_k: their bits) and u the feature tile inside 64, p and the bit are
+//   from a kernel that has rows on lanes:     p = r0 + 2 r1 + 4 f3 + 8 r3 + 16 r4 + 32 r2, bit 16 f0 + 8 u + 4 f4 + 2 f2 + f1;
+//   from one that has features on lanes:      p = f0 + 2 f1 + 4 f3 + 8 f2 + 16 f4 + 32 r2, bit 16 r0 + 8 u + 4 r4 + 2 r3 + r1
+// (transpose_bits takes the second form to the first).  In memory bytes 1 and 2 of a word are exchanged, so that the bits of a
+// feature tile are one half of it.
+// ------------------------------------------------------------------------------------
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+typedef short s16x2 __attribute__((ext_vector_type(2)));
+// Features (operand rows) with bits 2 and 3 exchanged: accumulator register i of half-wave h then is feature
+// 16 (i / 8) + 8 h + i % 8 of its tile, and the packed registers 8 a .. 8 a + 7 contract with one 16-byte piece.
+__device__ __forceinline__ int swap23(int r) { return (r & ~12) | (r & 4) << 1 | (r & 8) >> 1; }
+// One bit per element of a packed accumulator tile after the ReLU: register pair (2 j, 2 j + 1) gives bits j and 16 + j.  A
+// positive bf16 is at least 2^7 as an integer (R is a sum of fp16 products, multiples of 2^-48, and never a denormal).
+__device__ __forceinline__ uint32_t positive_bits(const bf16x8 *pa) {
+  uint32_t w = 0;
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      bf16x2 e;
+      e[0] = pa[a][2 * jj];
+      e[1] = pa[a][2 * jj + 1];
+      const unsigned short one = (unsigned short)(1u << (4 * a + jj));
+      u16x2 bit = {one, one};
+      if (one == 1) asm("" : "+s"(bit));   // (of min(x, 1) the compiler makes two comparisons and two selections)
+      w |= __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, e), bit));
+    }
+  return w;
+}
+__device__ __forceinline__ uint32_t swap_bytes12(uint32_t w) { return __builtin_amdgcn_perm(w, w, 0x03010200); }
+// Rows on word bits and features on lanes -> features on word bits and rows on lanes, for a lane that sits at position p (bits 0 to 5:
+// l0, l1, l5, l4, l2, l3 of its number): lane bits 0, 1, 4, 2 change places with the word's bits 16, 1, 2, 4 (place values), one
+// exchange between two lanes each.
+__device__ __forceinline__ uint32_t transpose_bits(uint32_t w, int lane) {
+  auto merge = [](uint32_t own, int other, bool upper, uint32_t mask, int shift) {
+    const uint32_t m = upper ? ~mask : mask, t = (uint32_t)other;
+    return (own & m) | (__builtin_amdgcn_alignbit(t, t, upper ? shift : 32 - shift) & ~m);
+  };
+  const uint32_t t = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0xB1, 0xF, 0xF, false);   // lane ^ 1
+  w = __builtin_amdgcn_perm(w, t, lane & 1 ? 0x07060302u : 0x01000504u);
+  w = merge(w, __builtin_amdgcn_update_dpp(0, (int)w, 0x4E, 0xF, 0xF, false), lane & 2, 0x55555555u, 1);   // lane ^ 2
+  w = merge(w, __builtin_amdgcn_ds_swizzle((int)w, 0x401F), lane & 16, 0x33333333u, 2);                    // lane ^ 16
+  return merge(w, __builtin_amdgcn_ds_swizzle((int)w, 0x101F), lane & 4, 0x0F0F0F0Fu, 4);                  // lane ^ 4
+}
+// Half a of an accumulator tile packed to bf16, elements whose bit is not set as zero; w in register form, u: which feature tile of the word.
+__device__ __forceinline__ bf16x8 pack_masked(const f32x16 &v, int a, uint32_t w, int u) {
+  const bf16x8 p = pack_half(v, a);
+  bf16x8 r;
+#pragma unroll
+  for (int jj = 0; jj < 4; ++jj) {
+    bf16x2 e;
+    e[0] = p[2 * jj];
+    e[1] = p[2 * jj + 1];
+    const s16x2 m = (__builtin_bit_cast(s16x2, w) << (short)(15 - 8 * u - 4 * a - jj)) >> (short)15;
+    e = __builtin_bit_cast(bf16x2, (uint32_t)(__builtin_bit_cast(uint32_t, e) & __builtin_bit_cast(uint32_t, m)));
+    r[2 * jj] = e[0];
+    r[2 * jj + 1] = e[1];
+  }
+  return r;
+}
+
 // ------------------------------------------------------------------------------------
 // phiT_contract: for the rows of one chunk and the features [f0, f0 + NW*FW) of one slice
 //   Spart[r][c] = sum_t ReLU(X_F Omega)[t][r] * (Y[t][c] / rowdiv_t)
@@ -610,12 +526,12 @@ __device__ __forceinline__ bf16x8 tile_cols_operand(const bf16_t *tile, int stri
 // 8 of 4096, m 512: 17.2, 20.6 -> 17.1, 18.6.  The sums are the same bits.
 // RAGGED: n % 64 != 0, rows past n count as zeros with weight 0.  DEEP: L > 6, the filter's levels
 // above 6 enter as the per-tile addend tile_add [slices][ceil(n / 64)][DH] (the accumulators of X_F start there).
-template <int DH, int FW, bool PREP, bool RAGGED, bool DEEP, int NW = 4>
+template <int DH, int FW, bool PREP, bool RAGGED, bool DEEP, bool BITS, int NW = 4>
 __global__ __launch_bounds__(64 * NW, 2) void phiT_contract_kernel(
     const _Float16 *xf, const bf16_t *xraw, View vx, const float *coef, const float *tile_add,
     const bf16_t *y, View vy, const float *rowdiv, const float *w,
     const bf16_t *orows, float *dDout, float *dDpart,
-    const _Float16 *omT, int n, int m, int rows_per_chunk, float *Spart, float *zpart) {
+    const _Float16 *omT, int n, int m, int rows_per_chunk, float *Spart, float *zpart, uint32_t *bits) {
   constexpr bool FUSE = (DH == 64);
   static_assert(NW == 4 || (NW == 8 && !FUSE), "the filter of head dimension 64 is dealt to four waves");
   constexpr int NT = 64 * NW;
@@ -638,13 +554,14 @@ __global__ __launch_bounds__(64 * NW, 2) void phiT_contract_kernel(
   const int t_begin = chunk * rows_per_chunk, t_end = min(n, t_begin + rows_per_chunk);
   const int steps = (t_end - t_begin + 63) / 64;   // the last tile of the sequence may be partial
 
-  // Omega^T operands of this wave's features: B operand, column = feature, k = 8h + q.
+  // Omega^T operands of this wave's features: B operand, column = feature (in the order of swap23), k = 8h + q.
+  const int fl = swap23(l32);
   f16x8 om[RT][KS];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-      om[rt][ks] = *reinterpret_cast<const f16x8 *>(omT + (int64_t)(f0 + 32 * rt + l32) * DH + 16 * ks + 8 * h);
+      om[rt][ks] = *reinterpret_cast<const f16x8 *>(omT + (int64_t)(f0 + 32 * rt + fl) * DH + 16 * ks + 8 * h);
 
   f32x16 S[RT][CT];
   float zacc[RT];
@@ -767,16 +684,19 @@ __global__ __launch_bounds__(64 * NW, 2) void phiT_contract_kernel(
   // registers (high part for the four k-steps, low part for the two of the quarter's own half).
   // The k-steps are taken own half first (ks_own, ks_own + 1: high and low part), then the other
   // half (high part only), so that the step loop has no branch and its LDS reads go out together.
+  // (BITS: read again in every step, kept they would be spilled.)
   bf16x8 ghi[4], glo[2];
   const int ks_own = 2 * (wave >> 1), ks_oth = ks_own ^ 2;
-  if (FUSE) {
+  auto read_filter = [&](int ln) {
+    const int trow = 32 * (wave >> 1) + (ln & 31), hh = ln >> 5;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      ghi[u] = filter_operand(gt, 0, 32 * (wave >> 1) + l32, 2 * (ks_own + u) + h);
-      ghi[2 + u] = filter_operand(gt, 0, 32 * (wave >> 1) + l32, 2 * (ks_oth + u) + h);
-      glo[u] = filter_operand(gt, 1, 32 * (wave >> 1) + l32, 2 * (ks_own + u) + h);
+      ghi[u] = filter_operand(gt, 0, trow, 2 * (ks_own + u) + hh);
+      ghi[2 + u] = filter_operand(gt, 0, trow, 2 * (ks_oth + u) + hh);
+      glo[u] = filter_operand(gt, 1, trow, 2 * (ks_own + u) + hh);
     }
-  }
+  };
+  if (FUSE && !BITS) read_filter(lane);
   // Eight waves: the registers hold the tile after the current one when a step begins.  The waves of one half put it into
   // LDS (and request the one after it) before their matrix instructions, those of the other half, their partners on the
   // same SIMDs, after them.
@@ -792,6 +712,13 @@ __global__ __launch_bounds__(64 * NW, 2) void phiT_contract_kernel(
     t_stash = t_begin + 64;
     fetch(t_stash);
   }
+  // BITS: the words of this wave's features, block by block
+  // (a buffer of the slice's words, n m / 8 bytes: the running offset stays scalar)
+  const int fb = __builtin_amdgcn_readfirstlane(f0);
+  __amdgpu_buffer_rsrc_t bb;
+  if (BITS)
+    bb = __builtin_amdgcn_make_buffer_rsrc(bits + (int64_t)slice * ((n + 63) / 64) * 2 * m, 0, (int)((uint32_t)((n + 63) / 64) * 8 * (uint32_t)m), 0x00020000);
+  uint32_t bo = (uint32_t)(t_begin / 64) * 8 * m + fb / 128 * 512 + (fb / 64 & 1) * 4 + (RT == 1 ? (fb / 32 & 1) * 2 : 0);
   for (int s = 0; s < steps; ++s) {
     const int buf = s & 1;
     const bool more = s + 1 < steps;
@@ -804,6 +731,7 @@ __global__ __launch_bounds__(64 * NW, 2) void phiT_contract_kernel(
     if (FUSE) {
       // X_F^T quarter: columns 32 (wave % 2) .. + 31 of the tile, rows 32 (wave / 2) .. + 31.
       const bf16_t *raw = reinterpret_cast<const bf16_t *>(&xt[buf][0]);
+      if (BITS) read_filter((int)opaque(lane));
       f32x16 q = zero16(), q2 = zero16();
       if (DEEP) {   // register i is column 32 (wave % 2) + acc_row(i, h) for every row of the quarter
         const float *ta = tile_add + ((int64_t)slice * ((n + 63) / 64) + (t_begin / 64 + s)) * DH + 32 * (wave & 1);
@@ -837,6 +765,7 @@ __global__ __launch_bounds__(64 * NW, 2) void phiT_contract_kernel(
       __syncthreads();
     }
     const _Float16 *xcur = FUSE ? &xq[0] : &xt[buf][0];
+    uint32_t word = 0;   // BITS
     __builtin_amdgcn_s_setprio(3);   // the matrix phase goes ahead of the other workgroup's tile traffic (-1 %)
 #pragma unroll
     for (int ti = 0; ti < 2; ++ti) {
@@ -868,14 +797,28 @@ __global__ __launch_bounds__(64 * NW, 2) void phiT_contract_kernel(
         f32x16 R = zero16();
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) R = mfma_f16(xa[ks], om[rt][ks], R);
+        bf16x8 pa[2];
 #pragma unroll
         for (int a = 0; a < 2; ++a) {
-          const bf16x8 pa = relu_bf16x8(pack_half(R, a));
-          zacc[rt] = dot8_bf16(pa, wp[a], zacc[rt]);
+          pa[a] = relu_bf16x8(pack_half(R, a));
+          zacc[rt] = dot8_bf16(pa[a], wp[a], zacc[rt]);
 #pragma unroll
-          for (int ct = 0; ct < CT; ++ct) S[rt][ct] = mfma_bf16(pa, yb[a][ct], S[rt][ct]);
+          for (int ct = 0; ct < CT; ++ct) S[rt][ct] = mfma_bf16(pa[a], yb[a][ct], S[rt][ct]);
+        }
+        if (BITS) {   // two feature tiles, or two row tiles of one, share a word
+          const uint32_t b = positive_bits(pa);
+          word = (RT == 2 ? rt : ti) == 0 ? b : word | b << 8;
         }
       }
+      if (BITS && RT == 2) __builtin_amdgcn_raw_buffer_store_b32(swap_bytes12(word), bb, 8 * opaque(lane), bo + ti * 4 * m, 0);
+    }
+    if (BITS) {
+      if (RT == 1) {
+        word = swap_bytes12(word);
+        __builtin_amdgcn_raw_buffer_store_b16((unsigned short)word, bb, 8 * opaque(lane), bo, 0);
+        __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(word >> 16), bb, 8 * opaque(lane), bo + 4 * m, 0);
+      }
+      bo += 8 * m;
     }
     __builtin_amdgcn_s_setprio(0);
     if (NW == 8) {
@@ -892,9 +835,9 @@ __global__ __launch_bounds__(64 * NW, 2) void phiT_contract_kernel(
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
       for (int i = 0; i < 16; ++i)
-        sp[(int64_t)(f0 + 32 * rt + acc_row(i, h)) * DH + 32 * ct + l32] = S[rt][ct][i];
+        sp[(int64_t)(f0 + 32 * rt + swap23(acc_row(i, h))) * DH + 32 * ct + l32] = S[rt][ct][i];
     const float zt = xor32_sum(zacc[rt]);
-    if (h == 0) zpart[((int64_t)slice * chunks + chunk) * m + f0 + 32 * rt + l32] = zt;
+    if (h == 0) zpart[((int64_t)slice * chunks + chunk) * m + f0 + 32 * rt + fl] = zt;
   }
   if (PREP && blockIdx.y == 0) {   // sum of dD over this chunk's rows, fixed order
     __shared__ float red[NW];
@@ -995,8 +938,8 @@ __global__ __launch_bounds__(256) void reduce_contract_kernel(const float *Spart
 }
 
 // ------------------------------------------------------------------------------------
-// rows kernel. One wave owns 64 consecutive rows at a time (one Haar block of the largest
-// size); the workgroup's waves share the feature-side operands in LDS and walk over the
+// rows kernels.  A wave owns 64 consecutive rows at a time (one Haar block of the largest
+// size; 32 at head dimension 128); the workgroup's waves share the feature-side operands in LDS and walk over the
 // row groups of their slice (the operands are staged once when all features fit).  The
 // projection is computed transposed (features on the accumulator's register index, rows on
 // lanes) so that the ReLU output chains into MFMAs that contract over the features.
@@ -1016,6 +959,7 @@ __global__ __launch_bounds__(256) void reduce_contract_kernel(const float *Spart
 // stay below 2^32 bytes (see kMaxBufferStride).
 typedef __amdgpu_buffer_rsrc_t RowBuf;
 constexpr int64_t kMaxBufferStride = 1 << 24;   // row stride (elements) up to which a partial last block is a buffer
+constexpr int64_t kMaxGroupStride = 1 << 26;    // and up to which a lane reaches 16 rows with a 32-bit offset in bytes
 template <typename T>
 __device__ __forceinline__ RowBuf row_buffer(const T *rows, int64_t sn, int valid) {
   const uint64_t a = reinterpret_cast<uint64_t>(rows);   // (the compiler does not see that a wave's index is uniform)
@@ -1034,81 +978,55 @@ template <typename V> __device__ __forceinline__ V buf_load8(RowBuf r, uint32_t 
 __device__ __forceinline__ float buf_load4(RowBuf r, uint32_t off) {
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
 }
-// A value that the compiler re-derives from in every block: offsets that depend on the lane alone would otherwise be
-// kept in registers across the feature loop and spill (60 bytes per lane in the kernel with dV).
-__device__ __forceinline__ uint32_t opaque(uint32_t v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
 typedef unsigned int u32x2v __attribute__((ext_vector_type(2)));
 template <typename V> __device__ __forceinline__ void buf_store8(RowBuf r, uint32_t off, V v) {
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2v, v), r, off, 0, 0);
+}
+typedef unsigned int u32x4v __attribute__((ext_vector_type(4)));
+template <typename V> __device__ __forceinline__ void buf_store16(RowBuf r, uint32_t off, V v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4v, v), r, off, 0, 0);
 }
 __device__ __forceinline__ void buf_store4(RowBuf r, uint32_t off, float v) {
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, off, 0, 0);
 }
 
-// LN (MODE 0): LayerNorm over the columns of a row instead of the normaliser.  RAGGED: n is not a
-// multiple of 64; rows are read and written through buffers that end at row n (see row_buffer).
-// The plain instance has none of that code.
-// DEEP: L > 6: X_F starts from the per-tile addend of the levels above 6 (tile_add
-// [slices][ceil(n / 64)][DH]); the gradient modes also
-// write the 64-row sums of dX_F per column (tile_gsum, same shape) and leave band 6 of their
-// partials as u_6 alone.
-// DV (MODE 2): the kernel also forms dV = c relu(R) dS of MODE 3 from the
-// projection it has in hand (B operand: the rows of (dS | dz) in LDS through transposing reads)
-// and writes it to out1; the separate MODE 3 launch, its pass over K and its projection go away.
-template <int DH, int MODE, int NW, int MC, bool LN, bool RAGGED, bool DEEP, bool DV = false>
-__global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
-    const bf16_t *x, View vx,  // X (Q or K): source of X_F, band inner products (MODE 1, 2)
-    const bf16_t *y, View vy,  // dO (MODE 1) or V (MODE 2)
-    const float *Dsaved,       // D [slices][n] (MODE 1)
-    const float *arow,         // dD [slices][n] (MODE 1)
+// The apply modes of head dimension 64.  LN (MODE 0): LayerNorm over the columns of a row instead of the normaliser.  RAGGED: n is
+// not a multiple of 64; rows are read and written through buffers that end at row n (see row_buffer).  The plain instance has
+// none of that code.  DEEP: L > 6: X_F starts from the per-tile addend of the levels above 6 (tile_add
+// [slices][ceil(n / 64)][DH]).
+constexpr int kWavesApply = 8;   // two per SIMD: one's epilogue runs under the other's matrix instructions
+template <int MODE, int MC, bool LN, bool RAGGED, bool DEEP>
+__global__ __launch_bounds__(kWavesApply * 64, 2) void rows_kernel(
+    const bf16_t *x, View vx,  // X (Q or K)
     const _Float16 *omT,       // Omega^T fp16 [m][DH]
-    const bf16_t *omega,       // Omega bf16 [DH][m]
-    const bf16_t *Mx,          // (S | z) (MODE 1) / (dS | dz) (MODE 2), bf16 [slices][m][DH+16]
     const bf16_t *MT,          // S^T (MODE 0) / dS^T (MODE 3), bf16 [slices][DH][m]
     const bf16_t *bb,          // z bf16 [slices][m] (MODE 0)
     const float *coef,         // block-mean filter coefficients [slices][kCoefStride]
-    const float *scalars, float eps, int n, int m, int row_groups,
-    bf16_t *out0, View vo,     // O (MODE 0) / dQ or dK (MODE 1, 2) / dV (MODE 3)
+    float eps, int n, int m, int row_groups,
+    bf16_t *out, View vo,      // O (MODE 0) / dV (MODE 3)
     float *Dout,               // D (MODE 0)
-    float *partF, int L,       // [slices][gridDim.x][L+1] band partials (MODE 1, 2)
-    const float *tile_add, float *tile_gsum,   // DEEP (see above)
-    bf16_t *out1)                              // DV: dV, laid out like out0
+    const float *tile_add,     // DEEP (see above)
+    uint32_t *bits)            // MODE 3: the ReLU's decisions (see positive_bits)
 {
-  static_assert(DH == 64, "head dimension 128 has wide_rows_kernel");
-  static_assert(!DV || (MODE == 2 && NW == 4 && MC == 256), "dV rides along with the K-side gradient only");
+  static_assert(MODE == 0 || MODE == 3, "the gradient modes have masked_rows_kernel");
+  constexpr int DH = 64, NW = kWavesApply;
   constexpr int KS = DH / 16, CT = DH / 32;
-  constexpr int KSX = KS + 1;           // k-steps of the dPhi MFMA incl. the rank-one extension
   constexpr int AS = DH + 8;            // stride of the [feature][DH] fp16 array (16-byte reads)
-  constexpr int AM = DH + 16 + 8;       // stride of the [feature][DH+16] bf16 array
   constexpr int NT = NW * 64;
-  constexpr bool IS_GRAD = (MODE == 1 || MODE == 2);
-  constexpr bool IS_APPLY = (MODE == 0 || MODE == 3);
-  // Gradient modes run with the 512-register budget: projection and dPhi results go to VGPRs
-  // where the register file has room for all their operands in VGPRs as well (the whole feature range
-  // staged; the other shapes keep the compiler's own allocation).
-  constexpr bool VGPR_RG = IS_GRAD && NW == 4 && MC == 256;
   // Stage A runs here.  Each wave keeps the raw rows of its 64-row block in
   // LDS (one 64 x 32 panel per column tile), forms X_F^T = X^T G^T with 16 MFMAs at the top of
-  // the block and packs the result into the projection's fp16 operands; the gradient modes
-  // read X for the band inner products from the same panels, and every mode sends its output
-  // tiles through a panel once its X values are used up.
-  constexpr int NWR = NW;               // row groups of 64 rows per workgroup step (one per wave)
+  // the block and packs the result into the projection's fp16 operands; the output tiles go through a panel once its X
+  // values are used up.
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   constexpr int mc = MC;
-  constexpr int BS = MC + 4;            // stride of [DH][feature] arrays (8-byte permuted reads)
+  constexpr int BS = MC + 8;            // stride of [DH][feature] arrays (16-byte reads)
   _Float16 *s_omT = reinterpret_cast<_Float16 *>(smem_raw);                 // [mc][AS]
   unsigned char *p = smem_raw + (size_t)mc * AS * 2;
-  bf16_t *s_Mx = nullptr, *s_MT = nullptr, *s_om = nullptr, *s_bb = nullptr;
-  if (IS_GRAD) { s_Mx = reinterpret_cast<bf16_t *>(p); p += (size_t)mc * AM * 2; }   // [mc][AM]
-  if (IS_APPLY) { s_MT = reinterpret_cast<bf16_t *>(p); p += (size_t)DH * BS * 2; }   // [DH][BS]
-  if (IS_GRAD) { s_om = reinterpret_cast<bf16_t *>(p); p += (size_t)DH * BS * 2; }   // [DH][BS]
+  bf16_t *s_bb = nullptr, *s_MT = reinterpret_cast<bf16_t *>(p);                       // [DH][BS]
+  p += (size_t)DH * BS * 2;
   if (MODE == 0) { s_bb = reinterpret_cast<bf16_t *>(p); p += (size_t)mc * 2; }        // [mc]
   float *s_wave = reinterpret_cast<float *>(p); p += (size_t)NW * 64 * 4;              // [waves][64]
   constexpr int TS = 36;                // row stride (elements) of the per-wave 64 x 32 epilogue tile
-  constexpr int TT = 68;                // column stride (elements) of the same tile held transposed [32][64]
   bf16_t *s_tile = reinterpret_cast<bf16_t *>(p);            // [waves][CT][64][TS]
   p += (size_t)NW * CT * 64 * TS * 2;
   bf16_t *s_T = reinterpret_cast<bf16_t *>(p);               // filter operand table [2][512]
@@ -1122,7 +1040,6 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
   // constant, loads go out in batches of eight before the first LDS write.
   auto stage = [&](int m0) {
     constexpr int CPRX = DH / 8;          // 16-byte pieces per Omega^T row
-    constexpr int CPRM = (DH + 16) / 8;   // 16-byte pieces per extended M row
     constexpr int CPC = MC / 4;           // 8-byte pieces per column row (padded stride is 8-byte aligned)
     constexpr int B = 8;
     for (int e0 = 0; e0 < MC * CPRX; e0 += NT * B) {
@@ -1139,23 +1056,6 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
         if (e < MC * CPRX) *reinterpret_cast<u16x8 *>(&s_omT[(e / CPRX) * AS + (e % CPRX) * 8]) = tmp[u];
       }
     }
-    if (IS_GRAD) {
-      for (int e0 = 0; e0 < MC * CPRM; e0 += NT * B) {
-        u16x8 tmp[B];
-#pragma unroll
-        for (int u = 0; u < B; ++u) {
-          const int e = e0 + NT * u + tid;
-          if (e < MC * CPRM)
-            tmp[u] = *reinterpret_cast<const u16x8 *>(Mx + ((int64_t)slice * m + m0 + e / CPRM) * (DH + 16) +
-                                                      (e % CPRM) * 8);
-        }
-#pragma unroll
-        for (int u = 0; u < B; ++u) {
-          const int e = e0 + NT * u + tid;
-          if (e < MC * CPRM) *reinterpret_cast<u16x8 *>(&s_Mx[(e / CPRM) * AM + (e % CPRM) * 8]) = tmp[u];
-        }
-      }
-    }
     for (int e0 = 0; e0 < DH * CPC; e0 += NT * B) {
       bf16x4 t1[B];
 #pragma unroll
@@ -1163,8 +1063,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
         const int e = e0 + NT * u + tid;
         if (e < DH * CPC) {
           const int cidx = e / CPC, cc = e % CPC;
-          t1[u] = IS_APPLY ? *reinterpret_cast<const bf16x4 *>(MT + ((int64_t)slice * DH + cidx) * m + m0 + cc * 4)
-                           : *reinterpret_cast<const bf16x4 *>(omega + (int64_t)cidx * m + m0 + cc * 4);
+          t1[u] = *reinterpret_cast<const bf16x4 *>(MT + ((int64_t)slice * DH + cidx) * m + m0 + cc * 4);
         }
       }
 #pragma unroll
@@ -1172,23 +1071,13 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
         const int e = e0 + NT * u + tid;
         if (e < DH * CPC) {
           const int cidx = e / CPC, cc = e % CPC;
-          if (IS_APPLY) *reinterpret_cast<bf16x4 *>(&s_MT[cidx * BS + cc * 4]) = t1[u];
-          else *reinterpret_cast<bf16x4 *>(&s_om[cidx * BS + cc * 4]) = t1[u];
+          *reinterpret_cast<bf16x4 *>(&s_MT[cidx * BS + cc * 4]) = t1[u];
         }
       }
     }
     if (MODE == 0)
       for (int e = tid; e < MC; e += NT) s_bb[e] = bb[(int64_t)slice * m + m0 + e];
   };
-
-  float u[kTileBands];   // u_l = sum over blocks of bs_l(g) * bs_l(x), this lane's share
-#pragma unroll
-  for (int l = 0; l < kTileBands; ++l) u[l] = 0.f;
-  float cf[kTileBands];
-  if (IS_GRAD) {
-#pragma unroll
-    for (int l = 0; l < kTileBands; ++l) cf[l] = coef[slice * kCoefStride + l];
-  }
 
   build_filter_table(s_T, coef + slice * kCoefStride, tid, NT);
   if (nchunks == 1) stage(0);
@@ -1199,9 +1088,6 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
   // loads hides behind the epilogue.
   f16x8 xb[2][KS];      // X_F rows: B operand of the transposed projection
   u16x8 xp[8];          // raw X rows of the next block, 16-byte row-major pieces (row lane / 8 + 8 j, columns 8 (lane % 8) ..)
-  bf16x8 yb[2][KSX];    // dO or V rows (+ the a_t extension): B operand of the dPhi MFMA
-  float dval[2] = {1.f, 1.f};   // D of rows 32 ti + l32 (MODE 1)
-  float aval[2] = {1.f, 1.f};   // dD of the same rows (MODE 1)
   auto load_rows = [&](int t0) {
     const int valid = RAGGED ? n - t0 : 64;   // rows of this block that exist
     if (!RAGGED) {
@@ -1221,49 +1107,6 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
       for (int j = 0; j < 8; ++j) {
         xp[j] = buf_load16<u16x8>(xr, off);
         off += 8 * sn2;
-      }
-    }
-    if (IS_GRAD) {
-      // MODE 1 works with the raw dO rows: G' = D_t * G (the extension carries dD_t * D_t), and
-      // row t of dX_F is scaled by c / D_t at the end; MODE 2 scales by c (extension 1, or 0 for
-      // a row past n, which must not pick up the vector part).
-      const bf16_t *ys = y + vy.slice_base(slice);
-      RowBuf yr, dr, ar;
-      uint32_t yoff = 0;
-      if (RAGGED) {
-        const uint32_t ln = opaque(lane);
-        yoff = (ln & 31) * ((uint32_t)vy.sn * 2) + (ln >> 5) * 16;
-        yr = row_buffer(ys + (int64_t)t0 * vy.sn, vy.sn, valid);
-        if (MODE == 1) {
-          dr = row_buffer(Dsaved + (int64_t)slice * n + t0, 1, valid);
-          ar = row_buffer(arow + (int64_t)slice * n + t0, 1, valid);
-        }
-      }
-#pragma unroll
-      for (int ti = 0; ti < 2; ++ti) {
-        const int row = 32 * ti + l32, t = t0 + row;
-        const bool bad = RAGGED && row >= valid;
-        if (MODE == 1) {   // only requested here: used at the top of the next round (finish_rows)
-          dval[ti] = RAGGED ? buf_load4(dr, 4 * row) : Dsaved[(int64_t)slice * n + t];
-          aval[ti] = RAGGED ? buf_load4(ar, 4 * row) : arow[(int64_t)slice * n + t];
-        } else if (RAGGED) {
-          aval[ti] = bad ? 0.f : 1.f;
-        }
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          yb[ti][ks] = RAGGED ? buf_load16<bf16x8>(yr, yoff + (uint32_t)ti * ((uint32_t)vy.sn * 64) + 32u * ks)
-                              : *reinterpret_cast<const bf16x8 *>(ys + (int64_t)t * vy.sn + 16 * ks + 8 * h);
-      }
-    }
-  };
-  // The rank-one extension (a_t, 0, ...) of the dPhi operand, built when the values have landed.
-  auto finish_rows = [&]() {
-    if (IS_GRAD) {
-#pragma unroll
-      for (int ti = 0; ti < 2; ++ti) {
-        bf16x8 ext = splat_bf16x8(0.f);
-        if (h == 0) ext[0] = (__bf16)(MODE == 1 ? aval[ti] * dval[ti] : (RAGGED ? aval[ti] : 1.0f));
-        yb[ti][KSX - 1] = ext;
       }
     }
   };
@@ -1290,7 +1133,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
     __builtin_amdgcn_wave_barrier();
   };
   {
-    const int t_first = (blockIdx.x * NWR + wave) * 64;
+    const int t_first = (blockIdx.x * NW + wave) * 64;
     if ((int)blockIdx.x < row_groups && t_first < n) {
       load_rows(t_first);
       put_rows();
@@ -1301,7 +1144,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
   // group, used before the priorities were there, no longer gains anything.)
 
   for (int rg = blockIdx.x; rg < row_groups; rg += gridDim.x) {
-    const int t0 = (rg * NWR + wave) * 64;
+    const int t0 = (rg * NW + wave) * 64;
     const bool active = t0 < n;
     const int valid = RAGGED ? n - t0 : 64;
 
@@ -1309,9 +1152,9 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
       // X_F^T = X^T G^T per (column tile, row tile) from the raw rows in the panels (written at
       // the end of the previous block's epilogue), then the projection's fp16 operands.
       __builtin_amdgcn_wave_barrier();
-      // (apply modes: one column tile at a time, their 256-register budget has no room for four
-      // accumulators next to the operands being built)
-      constexpr int CG = IS_APPLY ? 1 : CT;   // column tiles per pass
+      // (one column tile at a time: the 256-register budget has no room for four accumulators next to the operands
+      // being built)
+      constexpr int CG = 1;   // column tiles per pass
 #pragma unroll
       for (int c0 = 0; c0 < CT; c0 += CG) {
         f32x16 q[CG][2];
@@ -1355,25 +1198,12 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
           }
       }
     }
-    if (active) finish_rows();
-    if (MODE == 1 && active) {   // row scales c / D_t for the epilogue, before the next rows' D replace them
-#pragma unroll
-      for (int ti = 0; ti < 2; ++ti)
-        // (rows past n: D reads as 0 there, and their scale must be finite for the sums over the block)
-        if (h == 0)
-          s_wave[wave * 64 + 32 * ti + l32] =
-              (RAGGED && 32 * ti + l32 >= valid) ? 0.f : cscale * __builtin_amdgcn_rcpf(dval[ti]);
-    }
-    f32x16 acc0[2][CT];   // N, dV (MODE 0, 3) or dX_F (MODE 1, 2): rows on registers, columns on lanes
-    f32x16 acc1[DV ? 2 : 1][DV ? CT : 1];   // DV: dV
+    f32x16 acc0[2][CT];   // N or dV: rows on registers, columns on lanes
     float dacc[2] = {0.f, 0.f};   // D partial of this lane's row (MODE 0)
 #pragma unroll
     for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) {
-        acc0[ti][ct] = zero16();
-        if (DV) acc1[ti][ct] = zero16();
-      }
+      for (int ct = 0; ct < CT; ++ct) acc0[ti][ct] = zero16();
 
     for (int m0 = 0; m0 < m; m0 += mc) {
       if (nchunks > 1) {
@@ -1383,172 +1213,43 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
       }
       if (!active) continue;
 
-      if (VGPR_RG) {
-        // The feature-side A operands of the next feature tile are read from LDS as soon as the
-        // current tile's second chain has taken them.
-        auto load_ops = [&](int rt, f16x8 *oa, bf16x8 *ma) {
-#pragma unroll
-          for (int ks = 0; ks < KS; ++ks)
-            oa[ks] = *reinterpret_cast<const f16x8 *>(&s_omT[(32 * rt + l32) * AS + 16 * ks + 8 * h]);
-#pragma unroll
-          for (int ks = 0; ks < KSX; ++ks)
-            ma[ks] = *reinterpret_cast<const bf16x8 *>(&s_Mx[(32 * rt + l32) * AM + 16 * ks + 8 * h]);
-        };
-        // The B operands of what follows a chain are read from LDS BEFORE the chain's statement
-        // (the compiler moves no LDS read across it): Omega[c][f] for dX_F, and for dV the rows of
-        // (dS | dz) through transposing reads (k-slot (h, q) stands for feature
-        // 32 rt + 16 a + 8 (q / 4) + 4 h + (q % 4): two reads of four consecutive rows each, at
-        // column 32 ct + l32).  Both row tiles of a feature tile use the same operands.
-        auto read_ob = [&](int rt, bf16x8 (*ob)[CT]) {
-#pragma unroll
-          for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
-              ob[a][ct] = lds_perm8(&s_om[(32 * ct + l32) * BS], 32 * rt + 16 * a, h);
-        };
-        auto read_sb = [&](int rt, bf16x8 (*sb)[CT]) {
-          const int i16 = lane & 15, c16 = 16 * ((lane >> 4) & 1) + 4 * (i16 & 3);
-#pragma unroll
-          for (int a = 0; a < 2; ++a) {
-            const int frow = 32 * rt + 16 * a + 4 * h + (i16 >> 2);
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct) {
-              const bf16x4 lo = lds_read_tr4(&s_Mx[frow * AM + 32 * ct + c16]);
-              const bf16x4 hi = lds_read_tr4(&s_Mx[(frow + 8) * AM + 32 * ct + c16]);
-#pragma unroll
-              for (int q = 0; q < 4; ++q) {
-                sb[a][ct][q] = lo[q];
-                sb[a][ct][4 + q] = hi[q];
-              }
-            }
-          }
-        };
-        // What follows a masked chain: pack to bf16, dX_F += dR Omega^T (and dV += relu(R) dS).
-        auto consume = [&](int ti, const f32x16 &Rt, const f32x16 &Gt, const bf16x8 (*ob)[CT],
-                           const bf16x8 (*sb)[CT]) {
-#pragma unroll
-          for (int a = 0; a < 2; ++a) {
-            const bf16x8 pg = pack_half(Gt, a);
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct) acc0[ti][ct] = mfma_bf16(pg, ob[a][ct], acc0[ti][ct]);
-            if (DV) {
-              const bf16x8 pa = relu_bf16x8(pack_half(Rt, a));
-#pragma unroll
-              for (int ct = 0; ct < CT; ++ct) acc1[ti][ct] = mfma_bf16(pa, sb[a][ct], acc1[ti][ct]);
-            }
-          }
-        };
-        // The pipelined form keeps two more chain results alive than the plain one: it is used where
-        // the registers allow it without spills (not next to the dV accumulators).
-        constexpr bool PIPE = !DV;
-        if (PIPE) {
-          // Software pipeline over the feature tiles: while the matrix pipe works through the
-          // chain of one row tile, the VALU masks the other row tile's finished chain (inside the
-          // chain statements above); pack and dX_F MFMAs of a masked tile follow.  Per feature tile:
-          //   chain of row tile 1 | mask of row tile 0, consume row tile 0,
-          //   chain of row tile 0 of the NEXT feature tile | mask of row tile 1, consume row tile 1.
-          constexpr int TILES = MC / 32;
-          constexpr float kBig = 0x1p+100f;   // clamp(R * 2^100, 0, 1) = 1[R > 0] for every R > 2^-100
-          f16x8 oa[KS];     // Omega^T rows of a feature tile: A operand of the projection
-          bf16x8 ma[KSX];   // (M | b) rows of the same tile: A operand of the dPhi MFMA
-          bf16x8 ob[2][CT];
-          f32x16 R0, G0, R1, G1;
-          load_ops(0, oa, ma);
-          chain0_first(R0, G0, oa, xb[0], ma, yb[0]);
-          for (int rt = 0; rt < TILES - 1; ++rt) {
-            read_ob(rt, ob);
-            chain1_mask0(R1, G1, G0, R0, oa, xb[1], ma, yb[1], kBig);
-            load_ops(rt + 1, oa, ma);   // (lands while row tile 0 is consumed)
-            consume(0, R0, G0, ob, nullptr);
-            chain0_mask1(R0, G0, G1, R1, oa, xb[0], ma, yb[0], kBig);
-            consume(1, R1, G1, ob, nullptr);
-          }
-          {   // the last feature tile: no chain follows it
-            read_ob(TILES - 1, ob);
-            chain1_mask0(R1, G1, G0, R0, oa, xb[1], ma, yb[1], kBig);
-            consume(0, R0, G0, ob, nullptr);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) G1[i] *= __builtin_amdgcn_fmed3f(R1[i] * kBig, 0.f, 1.f);
-            consume(1, R1, G1, ob, nullptr);
-          }
-        } else {
-          // Both row tiles' chains first, then mask, pack and the MFMAs that follow, tile by tile.
-          constexpr int TILES = MC / 32;
-          f16x8 oa[KS];
-          bf16x8 ma[KSX];
-          load_ops(0, oa, ma);
-          for (int rt = 0; rt < TILES; ++rt) {
-            bf16x8 ob[2][CT], sb[DV ? 2 : 1][CT];
-            read_ob(rt, ob);
-            if (DV) read_sb(rt, sb);
-            f32x16 Rv[2], Gv[2];
-            chain_first(Rv[0], Gv[0], oa, xb[0], ma, yb[0]);
-            chain_first(Rv[1], Gv[1], oa, xb[1], ma, yb[1]);
-            load_ops((rt + 1) & (TILES - 1), oa, ma);   // (the last round re-reads tile 0: in bounds, unused)
-#pragma unroll
-            for (int ti = 0; ti < 2; ++ti) {
-#pragma unroll
-              for (int i = 0; i < 16; ++i)
-                Gv[ti][i] *= __builtin_amdgcn_fmed3f(Rv[ti][i] * 0x1p+100f, 0.f, 1.f);
-              consume(ti, Rv[ti], Gv[ti], ob, sb);
-            }
-          }
-        }
-        continue;
-      }
       // Two waves per SIMD: the wave in its feature loop goes first, so that the other wave's epilogue
       // (no matrix work) fills the gaps instead of competing for issue slots (forward kernel -3 %).
-      if (NW == 8) __builtin_amdgcn_s_setprio(3);
+      __builtin_amdgcn_s_setprio(3);
+      uint32_t word[2], *bw = nullptr;   // MODE 3
+      if (MODE == 3) {
+        const int ln = (int)opaque(lane);   // the lane's position: row l32, half h of the features
+        bw = bits + ((int64_t)slice * ((n + 63) / 64) + t0 / 64) * 2 * m + m0 + 2 * ((ln & 27) | (ln & 4) << 3 | (ln >> 5) << 2);
+      }
+#pragma unroll 2
       for (int rt = 0; rt < mc / 32; ++rt) {
         f16x8 oa[KS];     // Omega^T rows of this feature tile: A operand of the projection
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
-          oa[ks] = *reinterpret_cast<const f16x8 *>(&s_omT[(32 * rt + l32) * AS + 16 * ks + 8 * h]);
-        bf16x8 ma[KSX];   // (M | b) rows of this feature tile: A operand of the dPhi MFMA
-        if (IS_GRAD) {
-#pragma unroll
-          for (int ks = 0; ks < KSX; ++ks)
-            ma[ks] = *reinterpret_cast<const bf16x8 *>(&s_Mx[(32 * rt + l32) * AM + 16 * ks + 8 * h]);
-        }
+          oa[ks] = *reinterpret_cast<const f16x8 *>(&s_omT[(32 * rt + swap23(l32)) * AS + 16 * ks + 8 * h]);
 #pragma unroll
         for (int ti = 0; ti < 2; ++ti) {
           f32x16 R = zero16();
 #pragma unroll
           for (int ks = 0; ks < KS; ++ks) R = mfma_f16(oa[ks], xb[ti][ks], R);
-          if (IS_APPLY) {
+          bf16x8 pa[2];
 #pragma unroll
-            for (int a = 0; a < 2; ++a) {
-              const bf16x8 pa = relu_bf16x8(pack_half(R, a));
-              if (MODE == 0) dacc[ti] = dot8_bf16(pa, lds_perm8(s_bb, 32 * rt + 16 * a, h), dacc[ti]);
+          for (int a = 0; a < 2; ++a) {
+            pa[a] = relu_bf16x8(pack_half(R, a));
+            if (MODE == 0) dacc[ti] = dot8_bf16(pa[a], *reinterpret_cast<const bf16x8 *>(&s_bb[32 * rt + 16 * a + 8 * h]), dacc[ti]);
 #pragma unroll
-              for (int ct = 0; ct < CT; ++ct) {
-                const bf16x8 sb = lds_perm8(&s_MT[(32 * ct + l32) * BS], 32 * rt + 16 * a, h);
-                acc0[ti][ct] = mfma_bf16(pa, sb, acc0[ti][ct]);
-              }
-            }
-          } else {
-            f32x16 G = zero16();
-#pragma unroll
-            for (int ks = 0; ks < KSX; ++ks) G = mfma_bf16(ma[ks], yb[ti][ks], G);
-            // 1[R > 0] as a multiplier without going through the condition register:
-            // clamp(R * 2^100, 0, 1) is 1 for every R > 2^-100 and 0 for R <= 0.
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-              G[i] *= __builtin_amdgcn_fmed3f(R[i] * 0x1p+100f, 0.f, 1.f);
-#pragma unroll
-            for (int a = 0; a < 2; ++a) {
-              const bf16x8 pg = pack_half(G, a);
-#pragma unroll
-              for (int ct = 0; ct < CT; ++ct) {
-                const bf16x8 ob = lds_perm8(&s_om[(32 * ct + l32) * BS], 32 * rt + 16 * a, h);
-                acc0[ti][ct] = mfma_bf16(pg, ob, acc0[ti][ct]);
-              }
-            }
+            for (int ct = 0; ct < CT; ++ct)
+              acc0[ti][ct] = mfma_bf16(pa[a], *reinterpret_cast<const bf16x8 *>(&s_MT[(32 * ct + l32) * BS + 32 * rt + 16 * a + 8 * h]), acc0[ti][ct]);
+          }
+          if (MODE == 3) {
+            const uint32_t b = positive_bits(pa);
+            if ((rt & 1) == 0) word[ti] = b;
+            else bw[ti * m + (rt >> 2) * 128 + (rt >> 1 & 1)] = swap_bytes12(word[ti] | b << 8);
           }
         }
       }
     }
-    if (NW == 8) __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_s_setprio(0);
     if (!active) continue;
 
     // ---- epilogues -----------------------------------------------------------------
@@ -1556,57 +1257,17 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
       // Unconditional (the last round re-requests its own rows): a branch around these loads
       // would leave two paths with different numbers of outstanding memory operations, and the
       // waits the compiler then places further down would cover the loads just issued.
-      const int t_next = ((rg + gridDim.x) * NWR + wave) * 64;
+      const int t_next = ((rg + gridDim.x) * NW + wave) * 64;
       load_rows((rg + (int)gridDim.x < row_groups && t_next < n) ? t_next : t0);
     }
-    bf16_t *tl = panels;   // gradient modes: moves to the panel of the column tile in hand
-    // Gradient modes: output tiles leave through the wave's LDS tile held transposed ([column][row]): a lane
-    // stores its four consecutive accumulator rows as one 8-byte write, and transposing reads
-    // hand back 8-byte row-major pieces (read u: rows 16 (u % 4) + lane % 16, columns
-    // 16 (u / 4) + 4 (lane / 16) .. + 3) for the global stores.
-    const int i16 = lane & 15, g16 = lane >> 4;
-    auto tile_put = [&](int ti, const float *v16) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        bf16x4 pk;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) pk[e] = (__bf16)v16[4 * g + e];
-        *reinterpret_cast<bf16x4 *>(&tl[l32 * TT + 32 * ti + 8 * g + 4 * h]) = pk;
-      }
-    };
-    auto tile_store = [&](bf16_t *dst, RowBuf buf, int64_t sn, int col0) {
-      bf16x4 piece[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        piece[u] = lds_read_tr4(&tl[(16 * (u >> 2) + 4 * g16 + (i16 >> 2)) * TT + 16 * (u & 3) + 4 * (i16 & 3)]);
-      if (RAGGED) {
-        const uint32_t ln = opaque(lane);
-        uint32_t off = (ln & 15) * ((uint32_t)sn * 2) + ((uint32_t)col0 + 4 * (ln >> 4)) * 2;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          buf_store8(buf, off, piece[u]);
-          buf_store8(buf, off + 32, piece[u + 4]);
-          off += 32 * (uint32_t)sn;
-        }
-        return;
-      }
-      bf16_t *drow = dst + (int64_t)i16 * sn + col0 + 4 * g16;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {   // one running pointer instead of four scaled row offsets
-        *reinterpret_cast<bf16x4 *>(drow) = piece[u];
-        *reinterpret_cast<bf16x4 *>(drow + 16) = piece[u + 4];
-        drow += 16 * sn;
-      }
-    };
+    bf16_t *tl = panels;
     const int prow = lane >> 3, pcol = (lane & 7) * 4;   // this lane's 8-byte piece: rows prow + 8 j
-    bf16_t *os = out0 + vo.slice_base(slice) + (int64_t)t0 * vo.sn;
+    bf16_t *os = out + vo.slice_base(slice) + (int64_t)t0 * vo.sn;
     const int64_t osn = vo.sn;   // row stride of the output rows
     float *Dp = MODE == 0 ? Dout + (int64_t)slice * n + t0 : nullptr;
-    bf16_t *os1 = !DV ? nullptr : out1 + vo.slice_base(slice) + (int64_t)t0 * vo.sn;   // DV: the second output's rows
-    RowBuf osb, osb1, Dpb;
+    RowBuf osb, Dpb;
     if (RAGGED) {
       osb = row_buffer(os, osn, valid);
-      if (DV) osb1 = row_buffer(os1, osn, valid);
       if (MODE == 0) Dpb = row_buffer(Dp, 1, valid);
     }
 
@@ -1651,13 +1312,13 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
       }
     }
     // Row scale of the accumulators (rows on registers): c / D_t (MODE 0 from the per-wave LDS
-    // array written just above; LDS operations of one wave stay in order; MODE 1 from D), or c.
+    // array written just above; LDS operations of one wave stay in order), or c.
     __builtin_amdgcn_wave_barrier();
     if (!(MODE == 0 && LN))
 #pragma unroll
     for (int ti = 0; ti < 2; ++ti) {
       float sc[16];
-      if (MODE == 0 || MODE == 1) {
+      if (MODE == 0) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const f32x4 s4 = *reinterpret_cast<const f32x4 *>(&s_wave[wave * 64 + 32 * ti + 8 * g + 4 * h]);
@@ -1674,147 +1335,461 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
         for (int i = 0; i < 16; ++i) acc0[ti][ct][i] *= sc[i];
     }
 
-    if (IS_APPLY) {   // O (MODE 0) or dV (MODE 3): bf16 through the wave's LDS tile, 8-byte row-major stores
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) {
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-          for (int i = 0; i < 16; ++i)
-            tl[(32 * ti + acc_row(i, h)) * TS + l32] = cvt_bf16(acc0[ti][ct][i]);
-        __builtin_amdgcn_wave_barrier();
-        bf16x4 piece[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          piece[j] = *reinterpret_cast<const bf16x4 *>(&tl[(prow + 8 * j) * TS + pcol]);
-        if (RAGGED) {
-          const uint32_t ln = opaque(lane);
-          uint32_t off = (ln >> 3) * ((uint32_t)osn * 2) + (32 * ct + (ln & 7) * 4) * 2;
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            buf_store8(osb, off, piece[j]);
-            off += 16 * (uint32_t)osn;
-          }
-          continue;
-        }
-        bf16_t *orow = os + (int64_t)prow * osn + 32 * ct + pcol;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          *reinterpret_cast<bf16x4 *>(orow) = piece[j];
-          orow += 8 * osn;
-        }
-      }
-      put_rows();
-      continue;
-    }
-
-    // MODE 1, 2: gated Haar filter of dX_F on the accumulator layout and band inner products.
-    // Lane (l32, h) holds column 32 ct + l32 and rows 32 ti + 8 g + 4 h + e (g, e = 0..3):
-    //   block sums of 2 and 4 rows are in-lane, 8 rows need the other half-wave (lane ^ 32),
-    //   16 and 32 rows are in-lane again over g, 64 rows over ti.
-    // X comes in and dX goes out through a wave-private LDS tile of 64 rows x 32 columns, so
-    // that global memory sees 8-byte row-major accesses and the column accesses stay in LDS.
+    // O (MODE 0) or dV (MODE 3): bf16 through the wave's LDS tile, 8-byte row-major stores
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
-      tl = panels + ct * (64 * TS);   // X is there already
-      // ---- pass 1: block sums of g and x, band inner products, keep the 32-row sums
-      float g5[2], x5[2];
-#pragma unroll
-      for (int ti = 0; ti < 2; ++ti) {
-        float g1[8], x1[8];
-        bf16x4 xq[4];   // X at this lane's accumulator positions: rows 8 g + 4 h + e of column l32
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-          xq[g] = lds_read_tr4(&tl[(32 * ti + 8 * g + 4 * h + (i16 >> 2)) * TS + 16 * (g16 & 1) + 4 * (i16 & 3)]);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const float ga = acc0[ti][ct][2 * k], gb = acc0[ti][ct][2 * k + 1];
-          const float xa = (float)xq[k >> 1][2 * (k & 1)];
-          const float xb2 = (float)xq[k >> 1][2 * (k & 1) + 1];
-          u[0] = fmaf(ga, xa, fmaf(gb, xb2, u[0]));
-          g1[k] = ga + gb;
-          x1[k] = xa + xb2;
-          u[1] = fmaf(g1[k], x1[k], u[1]);
-        }
-        float g3[4], x3[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const float g2 = g1[2 * k] + g1[2 * k + 1], x2 = x1[2 * k] + x1[2 * k + 1];
-          u[2] = fmaf(g2, x2, u[2]);
-          g3[k] = xor32_sum(g2);   // 8-row blocks: both half-waves hold the same sums
-          x3[k] = xor32_sum(x2);
-          u[3] = fmaf(0.5f * g3[k], x3[k], u[3]);
-        }
-        const float g4a = g3[0] + g3[1], g4b = g3[2] + g3[3];
-        const float x4a = x3[0] + x3[1], x4b = x3[2] + x3[3];
-        u[4] = fmaf(0.5f * g4a, x4a, fmaf(0.5f * g4b, x4b, u[4]));
-        g5[ti] = g4a + g4b;
-        x5[ti] = x4a + x4b;
-        u[5] = fmaf(0.5f * g5[ti], x5[ti], u[5]);
-      }
-      const float g6 = g5[0] + g5[1], x6 = x5[0] + x5[1];
-      u[6] = fmaf(0.5f * g6, x6, u[6]);
-      // both half-waves hold the same sum and write the same value: no branch around the store
-      if (DEEP) tile_gsum[((int64_t)slice * ((n + 63) / 64) + t0 / 64) * DH + 32 * ct + l32] = g6;
-      const float T6 = cf[6] * g6;
       __builtin_amdgcn_wave_barrier();
-      // ---- pass 2: filtered gradient, top-down (block sums of g rebuilt), bf16 into the tile
 #pragma unroll
-      for (int ti = 0; ti < 2; ++ti) {
-        const float T5 = fmaf(cf[5], g5[ti], T6);
-        float g1[8], g2[4], g3[4], o16[16];
+      for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
-        for (int k = 0; k < 8; ++k) g1[k] = acc0[ti][ct][2 * k] + acc0[ti][ct][2 * k + 1];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          g2[k] = g1[2 * k] + g1[2 * k + 1];
-          g3[k] = xor32_sum(g2[k]);
-        }
-#pragma unroll
-        for (int k2 = 0; k2 < 2; ++k2) {
-          const float T4 = fmaf(cf[4], g3[2 * k2] + g3[2 * k2 + 1], T5);
-#pragma unroll
-          for (int k1 = 0; k1 < 2; ++k1) {
-            const int k = 2 * k2 + k1;   // 8-row block (and this lane's 4-row part of it)
-            const float T2 = fmaf(cf[2], g2[k], fmaf(cf[3], g3[k], T4));
-#pragma unroll
-            for (int k0 = 0; k0 < 2; ++k0) {
-              const int kk = 2 * k + k0;   // row pair
-              const float T1 = fmaf(cf[1], g1[kk], T2);
-#pragma unroll
-              for (int e = 0; e < 2; ++e) {
-                const int i = 2 * kk + e;
-                o16[i] = fmaf(cf[0], acc0[ti][ct][i], T1);
-              }
-            }
-          }
-        }
-        tile_put(ti, o16);
-      }
+        for (int i = 0; i < 16; ++i)
+          tl[(32 * ti + acc_row(i, h)) * TS + l32] = cvt_bf16(acc0[ti][ct][i]);
       __builtin_amdgcn_wave_barrier();
-      // ---- LDS -> dX
-      tile_store(os, osb, osn, 32 * ct);
-      if (DV) {   // dV tile through the same panel (its X values are used up)
-        __builtin_amdgcn_wave_barrier();
+      bf16x4 piece[8];
 #pragma unroll
-        for (int ti = 0; ti < 2; ++ti) {
-          float o16[16];
+      for (int j = 0; j < 8; ++j)
+        piece[j] = *reinterpret_cast<const bf16x4 *>(&tl[(prow + 8 * j) * TS + pcol]);
+      if (RAGGED) {
+        const uint32_t ln = opaque(lane);
+        uint32_t off = (ln >> 3) * ((uint32_t)osn * 2) + (32 * ct + (ln & 7) * 4) * 2;
 #pragma unroll
-          for (int i = 0; i < 16; ++i) o16[i] = cscale * acc1[ti][ct][i];
-          tile_put(ti, o16);
+        for (int j = 0; j < 8; ++j) {
+          buf_store8(osb, off, piece[j]);
+          off += 16 * (uint32_t)osn;
         }
-        __builtin_amdgcn_wave_barrier();
-        tile_store(os1, osb1, osn, 32 * ct);
+        continue;
+      }
+      bf16_t *orow = os + (int64_t)prow * osn + 32 * ct + pcol;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        *reinterpret_cast<bf16x4 *>(orow) = piece[j];
+        orow += 8 * osn;
       }
     }
     put_rows();
   }
-  if (IS_APPLY) return;
+}
 
-  // With u_l = <dX_F, P_l X> (P_l = mean over aligned 2^l blocks) the band gradients are
-  // dF_L = u_L and dF_{l-1} = u_{l-1} - u_l (l = 1..L); one partial per workgroup.
-  __syncthreads();   // operand arrays are no longer read; s_wave is free for the reduction
+// 16 bytes per lane from base + voff (bytes) to LDS at lds (bytes, wave-uniform) + 16 * lane, without passing through
+// registers.  Written as a statement because the compiler waits for every such load before the next LDS read, whatever it
+// reads; the kernel waits (vmcnt) before its barrier instead.  It has no register outputs.
+__device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t voff, const void *base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base)
+               : "memory", "m0");
+}
+// ------------------------------------------------------------------------------------
+// Gradient rows kernel of head dimension 64 (MODE 1: query side, MODE 2: key side, as above) where the ReLU's decisions are
+// there as bits (see positive_bits): two contractions per feature tile, dPhi and dX_F, and no filter of the rows at the top.
+// Eight waves of 64 rows, two per SIMD with 256 registers each, so that one wave's epilogue runs under the other's matrix
+// instructions; the feature-side operands of MC features are staged once per workgroup (once per pass and row group
+// where there are more).
+// What bounds it: memory.  8 slices of 131072 rows, m 256 move 417 MB (key side: X and V in, bits in, dX out), 73 us at the rate of a
+// large copy, in 107; without seven eighths of the feature loop it takes 87, without the epilogue's arithmetic 102.
+// The kernel before it formed the projection, too, with one wave of 512 registers per SIMD: 175 us on the query side, 235 on the key
+// side with dV beside dX_F; now 116 and 107, and 90 for dV (its kernel has the projection in hand and leaves the bits).
+// A lane's row: operand row l32 of dN or V is row 32 ti + r with r's bits (l0, l1, l3, l4, l2), so that the accumulator registers of
+// dX_F hold 16 consecutive rows 32 ti + 16 h + i of column 32 ct + l32: of the Haar filter's levels only 32 and 64 rows leave the lane.
+// X comes straight from memory into the wave's panels, one of 4 KiB per 32 columns ([64 rows][32], requested a row group ahead), and
+// dX goes out through the same panel ([32 columns][64 rows]: 16-byte piece q of column c at slot q ^ (c % 8)).
+// ------------------------------------------------------------------------------------
+template <int MODE, int MC, int NW, bool RAGGED, bool DEEP>
+__global__ __launch_bounds__(NW * 64, 2) void masked_rows_kernel(
+    const bf16_t *x, View vx, const bf16_t *y, View vy, const float *Dsaved, const float *arow, const uint32_t *bits,
+    const bf16_t *omega, const bf16_t *Mx, const float *coef, int n, int m, int row_groups, bf16_t *out, View vo,
+    float *partF, int L, float *tile_gsum) {
+  constexpr int DH = 64, KS = 4, KSX = 5, CT = 2, NT = NW * 64;
+  constexpr int AM = DH + 16 + 8, BS = MC + 8, WORDS = MC / 64;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  bf16_t *s_Mx = reinterpret_cast<bf16_t *>(smem_raw);                      // [MC][AM]: (S | z) or (dS | dz)
+  bf16_t *s_om = s_Mx + MC * AM;                                            // [DH][BS]: Omega
+  float *s_wave = reinterpret_cast<float *>(s_om + DH * BS);                // [waves][64]
+  bf16_t *s_panel = reinterpret_cast<bf16_t *>(s_wave + NW * 64);           // [waves][CT][2048]
+  typedef __attribute__((address_space(3))) unsigned char lds_byte;
+  const int slice = blockIdx.y, tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const float cscale = coef[slice * kCoefStride + kCoefCscale];
+  const int nchunks = m / MC, blocks = (n + 63) / 64;
+  // A lane's row among 32, and the position of its words.  (What depends on the lane alone is formed anew where it is used, from a
+  // value that the compiler does not see through: kept across the feature loop, it would be spilled.)
+  auto row_of = [](int ln) { return (ln & 3) | (ln >> 3 & 3) << 2 | (ln & 4) << 2; };
+  auto position_of = [](int ln) { return (ln & 3) | (ln >> 5) << 2 | (ln & 16) >> 1 | (ln & 4) << 2 | (ln & 8) << 2; };
+  auto stage = [&](int m0) {
+    // 16-byte pieces per row, pieces, and pieces per thread (all requested before the first is stored)
+    constexpr int CPRM = (DH + 16) / 8, CPC = MC / 8, PM = MC * CPRM, PO = DH * CPC, UM = (PM + NT - 1) / NT, UO = (PO + NT - 1) / NT;
+    u16x8 tm[UM], to[UO];
+    const int tid = (int)opaque(threadIdx.x);
+#pragma unroll
+    for (int u = 0; u < UM; ++u) {
+      const int e = NT * u + tid;
+      if (e < PM) tm[u] = *reinterpret_cast<const u16x8 *>(Mx + ((int64_t)slice * m + m0 + e / CPRM) * (DH + 16) + (e % CPRM) * 8);
+    }
+#pragma unroll
+    for (int u = 0; u < UO; ++u) {
+      const int e = NT * u + tid;
+      if (e < PO) to[u] = *reinterpret_cast<const u16x8 *>(omega + (int64_t)(e / CPC) * m + m0 + (e % CPC) * 8);
+    }
+#pragma unroll
+    for (int u = 0; u < UM; ++u) {
+      const int e = NT * u + tid;
+      if (e < PM) *reinterpret_cast<u16x8 *>(&s_Mx[(e / CPRM) * AM + (e % CPRM) * 8]) = tm[u];
+    }
+#pragma unroll
+    for (int u = 0; u < UO; ++u) {
+      const int e = NT * u + tid;
+      if (e < PO) *reinterpret_cast<u16x8 *>(&s_om[(e / CPC) * BS + (e % CPC) * 8]) = to[u];
+    }
+  };
+  float u[kTileBands], cf[kTileBands];   // u_l = sum over blocks of bs_l(g) * bs_l(x), this lane's share
+#pragma unroll
+  for (int l = 0; l < kTileBands; ++l) {
+    u[l] = 0.f;
+    cf[l] = coef[slice * kCoefStride + l];
+  }
+  // Row-side operands; those of the next row group are requested after the feature loop of the current one.
+  bf16x8 yb[2][KSX];    // dO or V rows (+ the a_t extension): B operand of dPhi
+  float dval[2] = {1.f, 1.f}, aval[2] = {1.f, 1.f};   // D and dD of the lane's rows (MODE 1)
+  uint32_t words[2][WORDS];
+  const uint32_t *wrow = bits + (int64_t)slice * blocks * 2 * (m / 64) * 64;
+  auto load_words = [&](int t0, int m0) {
+    const uint32_t *p = wrow + (int64_t)(t0 >> 6) * 2 * m + m0;
+    const uint32_t off = 8 * (uint32_t)position_of((int)opaque(lane));
+#pragma unroll
+    for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+      for (int w = 0; w < WORDS; w += 2) {
+        const u32x2v pair = *reinterpret_cast<const u32x2v *>(reinterpret_cast<const char *>(p + ti * m + w * 64) + off);
+        words[ti][w] = pair[0];
+        words[ti][w + 1] = pair[1];
+      }
+  };
+  auto finish_words = [&]() {
+    const int ln = (int)opaque(lane);
+#pragma unroll
+    for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+      for (int w = 0; w < WORDS; ++w) {
+        words[ti][w] = swap_bytes12(words[ti][w]);
+        if (MODE == 1) words[ti][w] = transpose_bits(words[ti][w], ln);   // (from the contraction: features on lanes)
+      }
+  };
+  u16x8 yraw[8];   // rows of dO or V on their way: 16-byte row-major pieces (row 8 j + lane / 8, columns 8 (lane % 8) ..)
+  auto load_rows = [&](int t0) {
+    const int valid = RAGGED ? n - t0 : 64;
+    const bf16_t *ys = y + vy.slice_base(slice) + (int64_t)t0 * vy.sn;
+    const int ln = (int)opaque(lane), lrow = row_of(ln);
+    const uint32_t yoff = (uint32_t)(ln >> 3) * ((uint32_t)vy.sn * 2) + (ln & 7) * 16;
+    if (RAGGED) {
+      const RowBuf yr = row_buffer(ys, vy.sn, valid);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) yraw[j] = buf_load16<u16x8>(yr, yoff + (uint32_t)j * ((uint32_t)vy.sn * 16));
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) yraw[j] = *reinterpret_cast<const u16x8 *>(reinterpret_cast<const char *>(ys + 8 * j * vy.sn) + yoff);
+    }
+    RowBuf dr, ar;
+    if (RAGGED && MODE == 1) {
+      dr = row_buffer(Dsaved + (int64_t)slice * n + t0, 1, valid);
+      ar = row_buffer(arow + (int64_t)slice * n + t0, 1, valid);
+    }
+#pragma unroll
+    for (int ti = 0; ti < 2; ++ti) {
+      const int row = 32 * ti + lrow;
+      if (MODE == 1) {   // only requested here: used at the top of the next round
+        const uint32_t off = 4 * (uint32_t)row;
+        dval[ti] = RAGGED ? buf_load4(dr, off) : *reinterpret_cast<const float *>(reinterpret_cast<const char *>(Dsaved + (int64_t)slice * n + t0) + off);
+        aval[ti] = RAGGED ? buf_load4(ar, off) : *reinterpret_cast<const float *>(reinterpret_cast<const char *>(arow + (int64_t)slice * n + t0) + off);
+      } else if (RAGGED) {
+        aval[ti] = row >= valid ? 0.f : 1.f;
+      }
+    }
+    if (nchunks == 1) load_words(t0, 0);
+  };
+  bf16_t *panels = s_panel + wave * (CT * 2048);
+  // The rows of Y through the (free) panels, [64 rows][64], into the order of the operand; then X into its panels, 16 rows of 32
+  // columns per request (rows past n: the last one, see below).  (A load of the operand as it is used would touch 32 rows of memory with
+  // 32 bytes each; with such loads and stores the kernel took 120 us, with these 107.)
+  auto turn_rows = [&](int t0) {
+    const int ln = (int)opaque(lane), lrow = row_of(ln), hh = ln >> 5;
+    auto key = [](int row) { return (row & 3) | (row >> 2 & 4); };
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int row = 8 * j + (ln >> 3);
+      *reinterpret_cast<u16x8 *>(panels + row * 64 + (((ln & 7) ^ key(row)) << 3)) = yraw[j];
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        yb[ti][ks] = *reinterpret_cast<const bf16x8 *>(panels + (32 * ti + lrow) * 64 + (((2 * ks + hh) ^ key(lrow)) << 3));
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (what is read from the panels has arrived)
+    const uint32_t at = (uint32_t)(uintptr_t)(lds_byte *)panels;
+    const bf16_t *xs = x + vx.slice_base(slice) + (int64_t)t0 * vx.sn;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int ct = i >> 2, j = i & 3, r = ln >> 2;
+      if (RAGGED)
+        lds_dma16(at + 1024 * i, (uint32_t)min(16 * j + r, n - t0 - 1) * ((uint32_t)vx.sn * 2) + (ln & 3) * 16, xs + 32 * ct);
+      else
+        lds_dma16(at + 1024 * i, (uint32_t)r * ((uint32_t)vx.sn * 2) + (ln & 3) * 16, xs + 16 * j * vx.sn + 32 * ct);
+    }
+  };
+  {
+    const int t_first = (blockIdx.x * NW + wave) * 64;
+    const bool any = (int)blockIdx.x < row_groups && t_first < n;
+    if (any) load_rows(t_first);
+    if (nchunks == 1) stage(0);
+    if (any) turn_rows(t_first);
+  }
+  __syncthreads();
+  const int frow = swap23(l32);   // feature-side operand rows (see swap23)
+
+  for (int rg = blockIdx.x; rg < row_groups; rg += gridDim.x) {
+    const int t0 = (rg * NW + wave) * 64;
+    const bool active = t0 < n;
+    const int valid = RAGGED ? n - t0 : 64;
+    if (active) {
+      const int lrow = row_of((int)opaque(lane));
+      // MODE 1 works with the raw dO rows: G' = D_t * G (the extension carries dD_t * D_t), and row t of dX_F is scaled by
+      // c / D_t at the end; MODE 2 scales by c (extension 1, or 0 for a row past n, which must not pick up the vector part).
+#pragma unroll
+      for (int ti = 0; ti < 2; ++ti) {
+        bf16x8 ext = splat_bf16x8(0.f);
+        if (h == 0) ext[0] = (__bf16)(MODE == 1 ? aval[ti] * dval[ti] : (RAGGED ? aval[ti] : 1.0f));
+        yb[ti][KS] = ext;
+        if (MODE == 1 && h == 0)   // (rows past n: D reads as 0 there, and their scale must be finite for the sums over the block)
+          s_wave[wave * 64 + 32 * ti + lrow] =
+              (RAGGED && 32 * ti + lrow >= valid) ? 0.f : cscale * __builtin_amdgcn_rcpf(dval[ti]);
+      }
+    }
+    f32x16 acc[2][CT];   // dX_F: rows on registers, columns on lanes
+#pragma unroll
+    for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) acc[ti][ct] = zero16();
+    for (int m0 = 0; m0 < m; m0 += MC) {
+      if (nchunks > 1) {
+        if (active) load_words(t0, m0);
+        __syncthreads();
+        stage(m0);
+        __syncthreads();
+      }
+      if (!active) continue;
+      finish_words();
+      __builtin_amdgcn_s_setprio(3);   // ahead of the other wave's epilogue
+      // Software pipeline over the row tiles of the feature tiles: the dPhi chain of the next one among the vector instructions
+      // that mask and pack the current one (a matrix instruction takes 32 cycles and leaves room for four vector instructions).
+      bf16x8 ma[KSX], ob[2][CT];   // (M | b) rows: A operand of dPhi; Omega: B operand of dX_F
+      auto read_ma = [&](int ft) {
+#pragma unroll
+        for (int ks = 0; ks < KSX; ++ks) ma[ks] = *reinterpret_cast<const bf16x8 *>(&s_Mx[(32 * ft + frow) * AM + 16 * ks + 8 * h]);
+      };
+      auto read_ob = [&](int ft) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct)
+            ob[a][ct] = *reinterpret_cast<const bf16x8 *>(&s_om[(32 * ct + l32) * BS + 32 * ft + 16 * a + 8 * h]);
+      };
+      auto chain = [&](int ti) {
+        f32x16 G = zero16();
+#pragma unroll
+        for (int ks = 0; ks < KSX; ++ks) G = mfma_bf16(ma[ks], yb[ti][ks], G);
+        return G;
+      };
+      auto consume = [&](int ti, const f32x16 &G, uint32_t word, int uu) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          const bf16x8 pg = pack_masked(G, a, word, uu);
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) acc[ti][ct] = mfma_bf16(pg, ob[a][ct], acc[ti][ct]);
+        }
+      };
+      // five matrix instructions of the chain, four of the product; the first half is packed when 16 vector instructions are through
+      auto pattern = [&](auto early, auto late) {   // LDS reads after the chain, and after the first half's product
+#pragma unroll
+        for (int i = 0; i < 7; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+          if (i == 4) __builtin_amdgcn_sched_group_barrier(0x100, decltype(early)::value, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x100, decltype(late)::value, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      constexpr int TILES = MC / 32;
+      read_ma(0);
+      read_ob(0);
+      f32x16 G0 = chain(0), G1;
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int ft = 0; ft < TILES; ++ft) {
+        G1 = chain(1);
+        consume(0, G0, words[0][ft / 2], ft & 1);
+        if (ft + 1 < TILES) read_ma(ft + 1);
+        pattern(std::integral_constant<int, KSX>{}, std::integral_constant<int, 0>{});
+        if (ft + 1 < TILES) G0 = chain(0);
+        consume(1, G1, words[1][ft / 2], ft & 1);
+        if (ft + 1 < TILES) {
+          read_ob(ft + 1);
+          pattern(std::integral_constant<int, 0>{}, std::integral_constant<int, 2 * CT>{});
+        }
+      }
+      __builtin_amdgcn_s_setprio(0);
+    }
+    if (!active) continue;
+
+    // ---- epilogue.  The next rows' request is unconditional (the last round re-requests its own): see rows_kernel.
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // X is in its panels
+    asm volatile("" ::: "memory");
+    const int t_after = ((rg + (int)gridDim.x) * NW + wave) * 64;
+    const int t_next = (rg + (int)gridDim.x < row_groups && t_after < n) ? t_after : t0;
+    if (RAGGED && valid < 64) {   // rows past n are zeros
+      const u16x8 zero = {};
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (16 * (j & 3) + (lane >> 2) >= valid) *reinterpret_cast<u16x8 *>(panels + (j >> 2) * 2048 + 512 * (j & 3) + lane * 8) = zero;
+    }
+    load_rows(t_next);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int ti = 0; ti < 2; ++ti) {   // row scale of dX_F
+      float sc[16];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        f32x4 s4 = {cscale, cscale, cscale, cscale};
+        if (MODE == 1) s4 = *reinterpret_cast<const f32x4 *>(&s_wave[wave * 64 + 32 * ti + 16 * h + 4 * g]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sc[4 * g + q] = s4[q];
+      }
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[ti][ct][i] *= sc[i];
+    }
+    // Gated Haar filter of dX_F and band inner products, per column tile: X comes out of the wave's panel, dX goes in (transposed,
+    // [column][row]) and leaves in 16-byte row-major pieces through transposing reads.
+    bf16_t *os = out + vo.slice_base(slice) + (int64_t)t0 * vo.sn;
+    RowBuf osb;
+    if (RAGGED) osb = row_buffer(os, vo.sn, valid);
+    u16x8 piece[CT][4];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      const int ln = (int)opaque(lane), i16 = ln & 15, g16 = ln >> 4, l32 = ln & 31, h = ln >> 5;
+      bf16_t *tl = panels + ct * 2048;
+      float g5[2], x5[2];
+#pragma unroll
+      for (int ti = 0; ti < 2; ++ti) {
+        float g1[8], x1[8];
+        bf16x4 xq[4];   // X at this lane's accumulator positions: rows 32 ti + 16 h + 4 g .. + 3 of column l32
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          xq[g] = lds_read_tr4(&tl[(32 * ti + 16 * h + 4 * g + (i16 >> 2)) * 32 + 16 * (g16 & 1) + 4 * (i16 & 3)]);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const float ga = acc[ti][ct][2 * k], gb = acc[ti][ct][2 * k + 1];
+          const float xa = (float)xq[k >> 1][2 * (k & 1)], xb = (float)xq[k >> 1][2 * (k & 1) + 1];
+          u[0] = fmaf(ga, xa, fmaf(gb, xb, u[0]));
+          g1[k] = ga + gb;
+          x1[k] = xa + xb;
+          u[1] = fmaf(g1[k], x1[k], u[1]);
+        }
+        float g2[4], x2[4], g3[2], x3[2];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          g2[k] = g1[2 * k] + g1[2 * k + 1];
+          x2[k] = x1[2 * k] + x1[2 * k + 1];
+          u[2] = fmaf(g2[k], x2[k], u[2]);
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          g3[k] = g2[2 * k] + g2[2 * k + 1];
+          x3[k] = x2[2 * k] + x2[2 * k + 1];
+          u[3] = fmaf(g3[k], x3[k], u[3]);
+        }
+        const float g4 = g3[0] + g3[1], x4 = x3[0] + x3[1];
+        u[4] = fmaf(g4, x4, u[4]);
+        g5[ti] = xor32_sum(g4);   // 32 rows: both half-waves hold the same sums
+        x5[ti] = xor32_sum(x4);
+        u[5] = fmaf(0.5f * g5[ti], x5[ti], u[5]);
+      }
+      const float g6 = g5[0] + g5[1], x6 = x5[0] + x5[1];
+      u[6] = fmaf(0.5f * g6, x6, u[6]);
+      // (both half-waves hold the same sum and write the same value)
+      if (DEEP) tile_gsum[((int64_t)slice * blocks + t0 / 64) * DH + 32 * ct + l32] = g6;
+      __builtin_amdgcn_wave_barrier();
+      // filtered gradient, top-down (block sums rebuilt), bf16 into the panel
+#pragma unroll
+      for (int ti = 0; ti < 2; ++ti) {
+        const float T5 = fmaf(cf[5], g5[ti], cf[6] * g6);
+        float g1[8], g2[4], g3[2], o16[16];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) g1[k] = acc[ti][ct][2 * k] + acc[ti][ct][2 * k + 1];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) g2[k] = g1[2 * k] + g1[2 * k + 1];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) g3[k] = g2[2 * k] + g2[2 * k + 1];
+        const float T4 = fmaf(cf[4], g3[0] + g3[1], T5);
+#pragma unroll
+        for (int k3 = 0; k3 < 2; ++k3) {
+          const float T3 = fmaf(cf[3], g3[k3], T4);
+#pragma unroll
+          for (int k2 = 2 * k3; k2 < 2 * k3 + 2; ++k2) {
+            const float T2 = fmaf(cf[2], g2[k2], T3);
+#pragma unroll
+            for (int k1 = 2 * k2; k1 < 2 * k2 + 2; ++k1) {
+              const float T1 = fmaf(cf[1], g1[k1], T2);
+#pragma unroll
+              for (int e = 0; e < 2; ++e) o16[2 * k1 + e] = fmaf(cf[0], acc[ti][ct][2 * k1 + e], T1);
+            }
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          bf16x8 pk;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) pk[e] = (__bf16)o16[8 * q + e];
+          *reinterpret_cast<bf16x8 *>(&tl[l32 * 64 + (((4 * ti + 2 * h + q) ^ (l32 & 7)) << 3)]) = pk;
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+      // back as rows 16 v + i16, columns 8 g16 .. + 7 of the tile
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int c = i16 >> 2, q = 2 * v + ((i16 & 3) >> 1), e = 4 * (i16 & 1);
+        const bf16x4 lo = lds_read_tr4(&tl[(8 * g16 + c) * 64 + ((q ^ c) << 3) + e]);
+        const bf16x4 hi = lds_read_tr4(&tl[(8 * g16 + 4 + c) * 64 + ((q ^ (4 + c)) << 3) + e]);
+        piece[ct][v] = __builtin_bit_cast(u16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+      }
+    }
+    // whole rows through the panels once more, so that a store covers 8 rows of 128 bytes
+    __builtin_amdgcn_wave_barrier();
+    {
+      const int ln = (int)opaque(lane), i16 = ln & 15, g16 = ln >> 4;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          *reinterpret_cast<u16x8 *>(panels + (16 * v + i16) * 64 + (((4 * ct + g16) ^ (i16 & 7)) << 3)) = piece[ct][v];
+      __builtin_amdgcn_wave_barrier();
+      const uint32_t off = (uint32_t)(ln >> 3) * ((uint32_t)vo.sn * 2) + (ln & 7) * 16;
+      u16x8 row[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) row[j] = *reinterpret_cast<const u16x8 *>(panels + (8 * j + (ln >> 3)) * 64 + (((ln & 7) ^ (ln >> 3)) << 3));
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        if (RAGGED) buf_store16(osb, off + (uint32_t)j * ((uint32_t)vo.sn * 16), row[j]);
+        else *reinterpret_cast<u16x8 *>(reinterpret_cast<char *>(os + 8 * j * vo.sn) + off) = row[j];
+      }
+    }
+    turn_rows(t_next);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the last request: nothing reads it, but it must not outlive the workgroup
+
+  // With u_l = <dX_F, P_l X> the band gradients are dF_L = u_L and dF_{l-1} = u_{l-1} - u_l (l = 1..L).
+  __syncthreads();
 #pragma unroll
   for (int l = 0; l < kTileBands; ++l) {
     const float s = wave_sum64(u[l]) / (float)(1 << l);
@@ -1822,17 +1797,20 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void rows_kernel(
   }
   __syncthreads();
   if (tid <= L) {
-    // DEEP: levels above 6 are not seen here; band 6 keeps u_6 alone (its -u_7, and the bands
-    // above, come from the tile-sum kernel in one extra row of the partials), bands above get 0.
+    // DEEP: levels above 6 are not seen here; band 6 keeps u_6 alone (its -u_7, and the bands above, come from the tile-sum
+    // kernel in extra rows of the partials), bands above get 0.
     float ul = 0.f, ul1 = 0.f;
     if (tid < kTileBands)
       for (int wv = 0; wv < NW; ++wv) {
         ul += s_wave[wv * 8 + tid];
         if (tid < L && tid + 1 < kTileBands) ul1 += s_wave[wv * 8 + tid + 1];
       }
-    const int rows = DEEP ? gridDim.x + DH / 16 : gridDim.x;   // (extra rows: one per workgroup of the tile-sum kernel)
+    const int rows = DEEP ? gridDim.x + DH / 16 : gridDim.x;
     partF[((int64_t)slice * rows + blockIdx.x) * (L + 1) + tid] = tid < L ? ul - ul1 : ul;
   }
+}
+constexpr size_t masked_smem_bytes(int mc, int nw) {
+  return (size_t)mc * 88 * 2 + (size_t)64 * (mc + 8) * 2 + nw * 64 * 4 + (size_t)nw * 8192;
 }
 
 // ------------------------------------------------------------------------------------
@@ -1861,13 +1839,6 @@ constexpr int wide_tile_bytes(int MODE) { return wide_grad(MODE) ? 25 * 1024 : 1
 constexpr int kWidePanel = 32 * 36;   // elements of a wave's tile of 32 rows x 32 columns (or transposed)
 inline size_t wide_smem_bytes(int MODE, int m) {
   return 2 * kWideTiles * wide_tile_bytes(MODE) + kWideWaves * (kWidePanel * 2 + 32 * 4 + 2 * 128 * 4) + (MODE == 0 ? m * 2 : 0);
-}
-// 16 bytes per lane from base + voff (bytes) to LDS at lds (bytes, wave-uniform) + 16 * lane, without passing through
-// registers.  Written as a statement because the compiler waits for every such load before the next LDS read, whatever it
-// reads; the kernel waits (vmcnt) before its barrier instead.  It has no register outputs.
-__device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t voff, const void *base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base)
-               : "memory", "m0");
 }
 template <int MODE, bool LN, bool RAGGED, bool DEEP>
 __global__ __launch_bounds__(kWideWaves * 64, 2) void wide_rows_kernel(
@@ -2432,16 +2403,13 @@ __global__ __launch_bounds__(256) void ln_prep_kernel(const bf16_t *dout, const 
 // ---------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------
-constexpr int kWavesGrad = 4;
 constexpr int kLnWgs = 2048;   // workgroups of ln_prep: eight of 256 threads per compute unit
-constexpr int kWavesApply = 8;
 
 struct FastPlan {
   int DH, FW, NWC, MB, mc;   // NWC: waves of a phiT_contract workgroup; mc: features staged in LDS per pass by the rows kernels of head dimension 64
   int chunksQ, rowsQ;   // pooled-query partial sums
   int chunksC, rowsC;   // split of n in phiT_contract
-  int rowGroupsA, rowsWgsA;   // apply-type rows kernel of head dimension 64 (8 waves): row groups / workgroups per slice
-  int rowGroupsG, rowsWgsG;   // the other rows kernels (256 rows per workgroup)
+  int rowGroups, rowsWgs;   // rows kernels: groups of 512 rows (head dimension 64) or 256 (128), workgroups per slice
   int chunksL, rowsL;   // split of n in ln_prep
 };
 
@@ -2476,13 +2444,11 @@ FastPlan fast_plan(const wersa_desc &c) {
   const int wantL = kLnWgs / slices < 1 ? 1 : kLnWgs / slices, bpl = (blocks + wantL - 1) / wantL;
   p.rowsL = bpl * 64;
   p.chunksL = (blocks + bpl - 1) / bpl;
-  p.rowGroupsA = (blocks + kWavesApply - 1) / kWavesApply;
+  p.rowGroups = c.d == 64 ? (blocks + kWavesApply - 1) / kWavesApply : (c.n + kWideRows - 1) / kWideRows;
   // One resident workgroup per compute unit (the operand arrays fill most of the LDS): at most
   // 256 workgroups in total, so that no second, mostly empty round follows the first.
-  int wgs = 256 / slices < 1 ? 1 : 256 / slices;
-  p.rowsWgsA = wgs < p.rowGroupsA ? wgs : p.rowGroupsA;
-  p.rowGroupsG = (blocks + kWavesGrad - 1) / kWavesGrad;
-  p.rowsWgsG = wgs < p.rowGroupsG ? wgs : p.rowGroupsG;
+  const int wgs = 256 / slices < 1 ? 1 : 256 / slices;
+  p.rowsWgs = wgs < p.rowGroups ? wgs : p.rowGroups;
   return p;
 }
 
@@ -2497,6 +2463,7 @@ struct FastWs {
   // L > 6: tile sums of Q and K and the addends of the levels above 6 (saved buffer); tile sums
   // of dQ_F and dK_F, the addends of dQ and dK, and the pyramids (workspace)
   float *tileQ, *tileK, *addQ, *addK, *gsumQ, *gsumK, *gaddQ, *gaddK, *pyr;
+  uint32_t *bitsQ, *bitsK;   // the ReLU's decisions of the two sides (see positive_bits)
   int64_t total;
 };
 
@@ -2536,14 +2503,18 @@ FastWs fast_ws(const wersa_desc &c, const FastPlan &p, int bwd, float *base, flo
     w.dSx = reinterpret_cast<bf16_t *>(b.take(sl * mx / 2));
     w.dST = reinterpret_cast<bf16_t *>(b.take(sl * md / 2));
     w.dzb = reinterpret_cast<bf16_t *>(b.take(sl * c.m / 2));
-    w.partQ = b.take(sl * (p.rowsWgsG + c.d / kCoarseCols) * (c.L + 1));   // (+ the rows of the levels above 6)
-    w.partK = b.take(sl * (p.rowsWgsG + c.d / kCoarseCols) * (c.L + 1));
+    w.partQ = b.take(sl * (p.rowsWgs + c.d / kCoarseCols) * (c.L + 1));   // (+ the rows of the levels above 6)
+    w.partK = b.take(sl * (p.rowsWgs + c.d / kCoarseCols) * (c.L + 1));
     if (deep) {
       const int64_t tiles = sl * ntiles * c.d;
       w.gsumQ = b.take(tiles);
       w.gsumK = b.take(tiles);
       w.gaddQ = b.take(tiles);
       w.gaddK = b.take(tiles);
+    }
+    if (c.d == 64) {
+      w.bitsQ = reinterpret_cast<uint32_t *>(b.take(sl * ntiles * 2 * c.m));
+      w.bitsK = reinterpret_cast<uint32_t *>(b.take(sl * ntiles * 2 * c.m));
     }
     w.dF = b.take(sl * (c.L + 1));
     w.dlogit = b.take(sl * (c.L + 1));
@@ -2558,23 +2529,14 @@ FastWs fast_ws(const wersa_desc &c, const FastPlan &p, int bwd, float *base, flo
   return w;
 }
 
-template <int DH, int MODE, int NW>
-size_t rows_smem_bytes(int mc) {
-  constexpr bool IS_GRAD = (MODE == 1 || MODE == 2);
-  const size_t AS = DH + 8, AM = DH + 16 + 8, BS = (size_t)mc + 4;
-  size_t s = (size_t)mc * AS * 2;
-  if (IS_GRAD) s += (size_t)mc * AM * 2 + (size_t)DH * BS * 2;
-  else s += (size_t)DH * BS * 2;
+template <int MODE>
+size_t rows_smem_bytes(int mc) {   // of rows_kernel
+  constexpr int DH = 64, NW = kWavesApply;
+  size_t s = (size_t)mc * (DH + 8) * 2 + (size_t)DH * (mc + 8) * 2;
   if (MODE == 0) s += (size_t)mc * 2;
   s += NW * 64 * 4;
   s += (size_t)NW * (DH / 32) * 64 * 36 * 2 + 2 * 512 * 2;   // X panels per wave and the filter table
   return s;
-}
-
-// dV formed by the K-side gradient kernel instead of a launch of its own: head dimension 64 with
-// 256 features staged per pass.
-inline bool dv_rides_along(const wersa_desc &c, const FastPlan &p) {
-  return c.d == 64 && p.mc == 256;
 }
 
 // Head dimension 128.
@@ -2592,9 +2554,9 @@ hipError_t launch_wide_rows(const wersa_desc &c, const FastPlan &p, const _Float
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
     WERSA_STAGE(name, st,
-                kern<<<dim3(p.rowsWgsG, c.B * c.H), kWideWaves * 64, smem, st>>>(
+                kern<<<dim3(p.rowsWgs, c.B * c.H), kWideWaves * 64, smem, st>>>(
                     xf, x, tv, y, yview ? *yview : tv, Dsaved, arow, w.omT + side, omega + side, Mx, MT, bb, w.coef, c.eps, c.n, c.m,
-                    p.rowGroupsG, out0, tv, Dout, partF, c.L, MODE == 1 ? w.gsumQ : w.gsumK));
+                    p.rowGroups, out0, tv, Dout, partF, c.L, MODE == 1 ? w.gsumQ : w.gsumK));
     return hipSuccess;
   };
   constexpr bool G = wide_grad(MODE);
@@ -2604,68 +2566,75 @@ hipError_t launch_wide_rows(const wersa_desc &c, const FastPlan &p, const _Float
   return ragged ? go(&wide_rows_kernel<MODE, false, true, false>) : go(&wide_rows_kernel<MODE, false, false, false>);
 }
 
-// Head dimension 64.  out1: dV of the K-side gradient.
+// Head dimension 64, MODE 0 and 3.
 template <int MODE>
-hipError_t launch_rows64(const wersa_desc &c, const FastPlan &p, const bf16_t *x, const bf16_t *y, const float *Dsaved,
-                         const float *arow, const FastWs &w, const bf16_t *omega, const bf16_t *Mx, const bf16_t *MT,
-                         const bf16_t *bb, bf16_t *out0, float *Dout, float *partF, hipStream_t st, const View *yview,
-                         bf16_t *out1) {
-  constexpr bool IS_GRAD = (MODE == 1 || MODE == 2);
-  constexpr int NW = IS_GRAD ? kWavesGrad : kWavesApply;
+hipError_t launch_rows64(const wersa_desc &c, const FastPlan &p, const bf16_t *x, const FastWs &w, const bf16_t *MT, const bf16_t *bb,
+                         bf16_t *out, float *Dout, hipStream_t st) {
   // key-side modes take the second random matrix when the descriptor has two
-  const int64_t side = ((c.flags & WERSA_FLAG_SEPARATE_OMEGA) && MODE >= 2) ? (int64_t)c.d * c.m : 0;
-  const _Float16 *omT = w.omT + side;
-  omega += side;
+  const _Float16 *omT = w.omT + (((c.flags & WERSA_FLAG_SEPARATE_OMEGA) && MODE >= 2) ? (int64_t)c.d * c.m : 0);
   const View tv{c.stride_b, c.stride_h, c.stride_n, c.H};
-  const int mcs = p.mc;
-  const size_t smem = rows_smem_bytes<64, MODE, NW>(mcs);
-  const char *name = MODE == 0 ? "wersa_rows_fwd"
-                               : (MODE == 1 ? "wersa_rows_bwd_q" : (MODE == 2 ? "wersa_rows_bwd_k" : "wersa_rows_bwd_v"));
-  const int wgs = IS_GRAD ? p.rowsWgsG : p.rowsWgsA, groups = IS_GRAD ? p.rowGroupsG : p.rowGroupsA;
+  const size_t smem = rows_smem_bytes<MODE>(p.mc);
   auto go = [&](auto kern) -> hipError_t {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
-    WERSA_STAGE(name, st,
-                kern<<<dim3(wgs, c.B * c.H), NW * 64, smem, st>>>(
-                    x, tv, y, yview ? *yview : tv, Dsaved, arow, omT, omega, Mx, MT, bb, w.coef, w.scalars,
-                    c.eps, c.n, c.m, groups, out0, tv, Dout, partF, c.L,
-                    MODE >= 2 ? w.addK : w.addQ, MODE == 1 ? w.gsumQ : w.gsumK, out1));
+    WERSA_STAGE(MODE == 0 ? "wersa_rows_fwd" : "wersa_rows_bwd_v", st,
+                kern<<<dim3(p.rowsWgs, c.B * c.H), kWavesApply * 64, smem, st>>>(
+                    x, tv, omT, MT, bb, w.coef, c.eps, c.n, c.m, p.rowGroups, out, tv, Dout, MODE == 3 ? w.addK : w.addQ, w.bitsK));
     return hipSuccess;
   };
-  if constexpr (MODE == 2) {
-    if (out1) {   // dV rides along with the K-side gradient (see dv_rides_along)
-      if (c.n % 64 != 0)
-        return c.L > kTileL ? go(&rows_kernel<64, 2, NW, 256, false, true, true, true>) : go(&rows_kernel<64, 2, NW, 256, false, true, false, true>);
-      return c.L > kTileL ? go(&rows_kernel<64, 2, NW, 256, false, false, true, true>) : go(&rows_kernel<64, 2, NW, 256, false, false, false, true>);
-    }
-  }
   const bool ln = MODE == 0 && (c.flags & WERSA_FLAG_LAYERNORM), ragged = c.n % 64 != 0, deep = c.L > kTileL;
   // partial last block, levels above one block: instances of their own
   auto pick = [&](auto mcv, auto lnv) -> hipError_t {
     constexpr int MC = decltype(mcv)::value;
     constexpr bool LNV = decltype(lnv)::value;
-    if (deep) return ragged ? go(&rows_kernel<64, MODE, NW, MC, LNV, true, true>) : go(&rows_kernel<64, MODE, NW, MC, LNV, false, true>);
-    return ragged ? go(&rows_kernel<64, MODE, NW, MC, LNV, true, false>) : go(&rows_kernel<64, MODE, NW, MC, LNV, false, false>);
+    if (deep) return ragged ? go(&rows_kernel<MODE, MC, LNV, true, true>) : go(&rows_kernel<MODE, MC, LNV, false, true>);
+    return ragged ? go(&rows_kernel<MODE, MC, LNV, true, false>) : go(&rows_kernel<MODE, MC, LNV, false, false>);
   };
   using M128 = std::integral_constant<int, 128>;
-  if constexpr (MODE >= 2) return pick(M128{}, std::false_type{});   // (256 features: with dV, above)
   using M256 = std::integral_constant<int, 256>;
   using LNV = std::bool_constant<MODE == 0>;
-  if (ln) return mcs == 256 ? pick(M256{}, LNV{}) : pick(M128{}, LNV{});
-  return mcs == 256 ? pick(M256{}, std::false_type{}) : pick(M128{}, std::false_type{});
+  if (ln) return p.mc == 256 ? pick(M256{}, LNV{}) : pick(M128{}, LNV{});
+  return p.mc == 256 ? pick(M256{}, std::false_type{}) : pick(M128{}, std::false_type{});
+}
+
+// Gradient of one side at head dimension 64 with the ReLU's decisions given.
+template <int MODE>
+hipError_t launch_masked64(const wersa_desc &c, const FastPlan &p, const bf16_t *x, const bf16_t *y, const float *Dsaved,
+                           const float *arow, const FastWs &w, const bf16_t *omega, const bf16_t *Mx, bf16_t *out, float *partF,
+                           hipStream_t st, const View *yview) {
+  if ((c.flags & WERSA_FLAG_SEPARATE_OMEGA) && MODE == 2) omega += (int64_t)c.d * c.m;
+  const View tv{c.stride_b, c.stride_h, c.stride_n, c.H};
+  auto go = [&](auto kern) -> hipError_t {
+    const size_t smem = masked_smem_bytes(p.mc, 8);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
+    WERSA_STAGE(MODE == 1 ? "wersa_rows_bwd_q" : "wersa_rows_bwd_k", st,
+                kern<<<dim3(p.rowsWgs, c.B * c.H), 8 * 64, smem, st>>>(
+                    x, tv, y, yview ? *yview : tv, Dsaved, arow, MODE == 1 ? w.bitsQ : w.bitsK, omega, Mx, w.coef, c.n, c.m,
+                    p.rowGroups, out, tv, partF, c.L, MODE == 1 ? w.gsumQ : w.gsumK));
+    return hipSuccess;
+  };
+  const bool ragged = c.n % 64 != 0, deep = c.L > kTileL;
+  auto pick = [&](auto MC) -> hipError_t {
+    constexpr int M = MC.value;
+    if (deep) return ragged ? go(&masked_rows_kernel<MODE, M, 8, true, true>) : go(&masked_rows_kernel<MODE, M, 8, false, true>);
+    return ragged ? go(&masked_rows_kernel<MODE, M, 8, true, false>) : go(&masked_rows_kernel<MODE, M, 8, false, false>);
+  };
+  return p.mc == 256 ? pick(std::integral_constant<int, 256>{}) : pick(std::integral_constant<int, 128>{});
 }
 
 template <int DH, int MODE>
 hipError_t launch_rows(const wersa_desc &c, const FastPlan &p, const _Float16 *xf, const bf16_t *x,
                        const bf16_t *y, const float *Dsaved, const float *arow, const FastWs &w,
                        const bf16_t *omega, const bf16_t *Mx, const bf16_t *MT, const bf16_t *bb,
-                       bf16_t *out0, float *Dout, float *partF, hipStream_t st,
-                       const View *yview = nullptr, bf16_t *out1 = nullptr) {
+                       bf16_t *out, float *Dout, float *partF, hipStream_t st, const View *yview = nullptr) {
   if constexpr (DH == 128)
-    return launch_wide_rows<MODE>(c, p, xf, x, y, Dsaved, arow, w, omega, Mx, MT, bb, out0, Dout, partF, st, yview);
+    return launch_wide_rows<MODE>(c, p, xf, x, y, Dsaved, arow, w, omega, Mx, MT, bb, out, Dout, partF, st, yview);
+  else if constexpr (MODE == 1 || MODE == 2)
+    return launch_masked64<MODE>(c, p, x, y, Dsaved, arow, w, omega, Mx, out, partF, st, yview);
   else
-    return launch_rows64<MODE>(c, p, x, y, Dsaved, arow, w, omega, Mx, MT, bb, out0, Dout, partF, st, yview, out1);
+    return launch_rows64<MODE>(c, p, x, w, MT, bb, out, Dout, st);
 }
 
 // orows != nullptr selects the backward form that derives dD from the rows of O itself;
@@ -2678,34 +2647,37 @@ void launch_contract(const wersa_desc &c, const FastPlan &p, const _Float16 *xf,
   const int slices = c.B * c.H;
   dim3 grid(p.chunksC, c.m / p.MB, slices);
   const _Float16 *omT = w.omT + (((c.flags & WERSA_FLAG_SEPARATE_OMEGA) && key_side) ? (int64_t)c.d * c.m : 0);
+  // The backward's launch is the one on the query side; at head dimension 64 it leaves the ReLU's decisions for the gradient kernel.
+  const bool bwd = !key_side;
   auto go = [&](auto kern) {
     WERSA_STAGE("wersa_phiT_contract", st,
                 kern<<<grid, 64 * p.NWC, 0, st>>>(xf, xraw, View{c.stride_b, c.stride_h, c.stride_n, c.H}, w.coef,
                                            key_side ? w.addK : w.addQ, y, yv,
                                            rowdiv, wts, orows, w.dD, w.dDpart, omT, c.n, c.m, p.rowsC, w.Spart,
-                                           w.zpart));
+                                           w.zpart, bwd ? w.bitsQ : nullptr));
   };
   const bool ragged = c.n % 64 != 0, deep = DH == 64 && c.L > kTileL;
-  constexpr int FWB = DH == 64 ? 64 : 32;   // 64 features per wave exist for head dimension 64 only (see fast_plan)
   constexpr bool D64 = DH == 64;
-  const bool wide = p.FW == 64;
-  if (DH == 128 && p.NWC == 8) {
-    if constexpr (DH == 128) {
-      if (orows) ragged ? go(&phiT_contract_kernel<DH, 32, true, true, false, 8>) : go(&phiT_contract_kernel<DH, 32, true, false, false, 8>);
-      else ragged ? go(&phiT_contract_kernel<DH, 32, false, true, false, 8>) : go(&phiT_contract_kernel<DH, 32, false, false, false, 8>);
-    }
-  } else if (deep && ragged) {
-    if (wide) orows ? go(&phiT_contract_kernel<DH, FWB, true, D64, D64>) : go(&phiT_contract_kernel<DH, FWB, false, D64, D64>);
-    else orows ? go(&phiT_contract_kernel<DH, 32, true, D64, D64>) : go(&phiT_contract_kernel<DH, 32, false, D64, D64>);
-  } else if (deep) {
-    if (wide) orows ? go(&phiT_contract_kernel<DH, FWB, true, false, D64>) : go(&phiT_contract_kernel<DH, FWB, false, false, D64>);
-    else orows ? go(&phiT_contract_kernel<DH, 32, true, false, D64>) : go(&phiT_contract_kernel<DH, 32, false, false, D64>);
-  } else if (wide) {
-    if (orows) ragged ? go(&phiT_contract_kernel<DH, FWB, true, true, false>) : go(&phiT_contract_kernel<DH, FWB, true, false, false>);
-    else ragged ? go(&phiT_contract_kernel<DH, FWB, false, true, false>) : go(&phiT_contract_kernel<DH, FWB, false, false, false>);
-  } else {
-    if (orows) ragged ? go(&phiT_contract_kernel<DH, 32, true, true, false>) : go(&phiT_contract_kernel<DH, 32, true, false, false>);
-    else ragged ? go(&phiT_contract_kernel<DH, 32, false, true, false>) : go(&phiT_contract_kernel<DH, 32, false, false, false>);
+  // forward; backward with the rows of O (dD derived here); backward after the LayerNorm output stage
+  auto form = [&](auto FW, auto NW, auto RAG, auto DEEP) {
+    constexpr int F = FW.value, N = NW.value;
+    if (!bwd) go(&phiT_contract_kernel<DH, F, false, RAG.value, DEEP.value, false, N>);
+    else if (orows) go(&phiT_contract_kernel<DH, F, true, RAG.value, DEEP.value, D64, N>);
+    else go(&phiT_contract_kernel<DH, F, false, RAG.value, DEEP.value, D64, N>);
+  };
+  using Yes = std::true_type;
+  using No = std::false_type;
+  auto shape = [&](auto FW, auto NW) {
+    if (deep) ragged ? form(FW, NW, Yes{}, std::bool_constant<D64>{}) : form(FW, NW, No{}, std::bool_constant<D64>{});
+    else ragged ? form(FW, NW, Yes{}, No{}) : form(FW, NW, No{}, No{});
+  };
+  using I4 = std::integral_constant<int, 4>;
+  if constexpr (DH == 128) {
+    if (p.NWC == 8) shape(std::integral_constant<int, 32>{}, std::integral_constant<int, 8>{});
+    else shape(std::integral_constant<int, 32>{}, I4{});
+  } else {   // (64 features per wave exist for head dimension 64 only, see fast_plan)
+    if (p.FW == 64) shape(std::integral_constant<int, 64>{}, I4{});
+    else shape(std::integral_constant<int, 32>{}, I4{});
   }
   const int64_t W = (int64_t)c.m * DH;
   auto reduce = [&](auto VEC) {
@@ -2813,12 +2785,9 @@ wersa_status fast_backward_t(const wersa_desc &c, const bf16_t *q, const bf16_t 
   }
   // K side first: the Q-side kernel then is the last writer of a large tensor before the pass
   // that adds the pooled-query term to dQ, which finds part of dQ still in the last-level cache.
-  const bool dv_too = dv_rides_along(c, p);
-  if (launch_rows<DH, 2>(c, p, KF, k, v, nullptr, nullptr, w, omega, w.dSx, nullptr, nullptr, dk, nullptr,
-                         w.partK, st, nullptr, dv_too ? dv : nullptr) != hipSuccess)
-    return WERSA_ERR_LAUNCH;
-  if (!dv_too && launch_rows<DH, 3>(c, p, KF, k, nullptr, nullptr, nullptr, w, omega, nullptr, w.dST, nullptr, dv,
-                                    nullptr, nullptr, st) != hipSuccess)
+  if (launch_rows<DH, 3>(c, p, KF, k, nullptr, nullptr, nullptr, w, omega, nullptr, w.dST, nullptr, dv, nullptr, nullptr, st) !=
+          hipSuccess ||
+      launch_rows<DH, 2>(c, p, KF, k, v, nullptr, nullptr, w, omega, w.dSx, nullptr, nullptr, dk, nullptr, w.partK, st) != hipSuccess)
     return WERSA_ERR_LAUNCH;
   if (ln) {
     if (launch_rows<DH, 1>(c, p, QF, q, w.dN, w.ones, w.dD, w, omega, w.Sx, nullptr, nullptr, dq, nullptr,
@@ -2834,9 +2803,9 @@ wersa_status fast_backward_t(const wersa_desc &c, const bf16_t *q, const bf16_t 
     WERSA_STAGE("wersa_coarse_bwd", st,
                 coarse_bwd_kernel<<<dim3(slices, 2, DH / kCoarseCols), 1024, 0, st>>>(w.gsumQ, w.gsumK, w.tileQ, w.tileK, w.coef,
                                                                    (c.n + 63) / 64, DH, c.L, w.pyr, w.gaddQ, w.gaddK,
-                                                                   w.partQ, w.partK, p.rowsWgsG));
+                                                                   w.partQ, w.partK, p.rowsWgs));
   WERSA_STAGE("gate_bwd_slice_kernel", st,
-              gate_bwd_slice_kernel<<<slices, kGateBwdThreads, 0, st>>>(w.partQ, w.partK, deep ? p.rowsWgsG + DH / kCoarseCols : p.rowsWgsG, c.L,
+              gate_bwd_slice_kernel<<<slices, kGateBwdThreads, 0, st>>>(w.partQ, w.partK, deep ? p.rowsWgs + DH / kCoarseCols : p.rowsWgs, c.L,
                                                            c.d, c.H, s, gate_w, scale_w, w.dF, w.dlogit, w.dqbar,
                                                            (c.flags & WERSA_FLAG_POOLED_GATE) ? 1 : 0, w.coef));
   WERSA_STAGE("gate_bwd_params_kernel", st,
@@ -2857,7 +2826,7 @@ wersa_status fast_backward_t(const wersa_desc &c, const bf16_t *q, const bf16_t 
 
 // A partial last block whose rows lie too far apart for a buffer (kMaxBufferStride): the tensors are copied to dense
 // ones in the workspace and the results back.  Rows of more than 32 MB: there are never many.
-bool rows_far_apart(const wersa_desc &c) { return c.n % 64 != 0 && c.stride_n > kMaxBufferStride; }
+bool rows_far_apart(const wersa_desc &c) { return c.stride_n > (c.n % 64 != 0 ? kMaxBufferStride : kMaxGroupStride); }
 wersa_desc dense_desc(const wersa_desc &c) {
   wersa_desc o = c;
   o.stride_n = c.d;

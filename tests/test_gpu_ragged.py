@@ -67,19 +67,20 @@ def test_partial_last_block(n, d, m, L, layout, flags):
         assert errs["out"] < 6e-3 and errs["dq"] < 2e-2 and errs["dk"] < 2e-2, errs
 
 
-@pytest.mark.parametrize("n,d,flags", [(1, 64, 0), (33, 64, 0), (65, 128, 0), (100, 64, 8), (70, 128, 14)])
+@pytest.mark.parametrize("n,d,flags", [(1, 64, 0), (33, 64, 0), (65, 128, 0), (100, 64, 8), (70, 128, 14), (64, 64, 0), (64, 128, 0)])
 def test_rows_further_apart_than_a_buffer_reaches(n, d, flags):
-    """Row strides of more than 2^24 elements with a partial last block: the MFMA path, the bits of dense tensors."""
+    """Row strides of more than 2^24 elements with a partial last block, and of more than 2^26 without one: the MFMA path, the
+    bits of dense tensors."""
     import torch
     from paper_2507_08637_amd import binding
-    H, L, m, far = 2, 3, 128, (1 << 24) + 8
+    H, L, m, far = 2, 3, 128, (1 << (26 if n % 64 == 0 else 24)) + 8
     g = torch.Generator(device="cuda").manual_seed(n)
 
     def normal(*s):
         return torch.randn(s, generator=g, device="cuda")
 
     names = ("q", "k", "v", "dout", "out", "dq", "dk", "dv")
-    buf = torch.empty((n - 1) * far + len(names) * H * d, dtype=torch.bfloat16, device="cuda")   # up to 3.4 GB
+    buf = torch.empty((n - 1) * far + len(names) * H * d, dtype=torch.bfloat16, device="cuda")   # up to 8.5 GB
     apart = {x: buf.as_strided((1, H, n, d), (8, d, far, 1), i * H * d) for i, x in enumerate(names)}
     dense = {x: torch.zeros(1, H, n, d, dtype=torch.bfloat16, device="cuda") for x in names}
     for x in names[:4]:

@@ -1,0 +1,50 @@
+"""The ReLU's decisions that the backward's contraction and dV kernels leave as bits for the gradient kernels (MFMA path): every bit is
+seen.  Rows and random features of +-1 with an odd number of non-zero columns and a transform of no levels make every
+pre-activation an odd multiple of the filter's one coefficient: no decision is at the edge of a rounding, and a row of dQ or dK
+misses or has too much by one of about m / 2 terms where a bit is wrong, sqrt(2 / m) >= 5.5e-2 of its norm (m <= 640).  Against
+float64: rounding of dPhi's 2^-9 per term, of O and of the row itself, below 2e-2 of a row's norm."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# tiles of 32 and 64 rows, groups of 256 and 512 rows, several groups per workgroup; 128 and 256 features per pass, one to five passes
+CASES = ([(n, 64, m) for n, m in ((32, 256), (64, 128), (97, 384), (513, 256), (1000, 512), (1025, 640), (8200, 256), (8200, 128))]
+         + [(n, 128, m) for n, m in ((32, 256), (65, 128), (257, 384), (1000, 512), (4100, 256))])
+
+
+def reference(q, k, v, dout, omega, sigma, gw, gb, sw, eps):
+    import torch
+    x = [t.double().requires_grad_(True) for t in (q, k, v)]
+    qd, kd, vd = x
+    f = torch.sigmoid(torch.einsum("hd,bhd->bh", gw[:, 0].double(), qd.mean(2)) + gb[:, 0].double()) * sw.double()
+    om = omega.double() / sigma.double() / omega.shape[-1] ** 0.5
+    pq, pk = (torch.relu((f[..., None, None] * t) @ om) for t in (qd, kd))
+    s, z = pk.transpose(2, 3) @ vd, pk.sum(2)
+    out = (pq @ s) / (pq @ z[..., None] + eps)
+    return torch.autograd.grad(out, x, dout.double())
+
+
+@pytest.mark.parametrize("n,d,m", CASES)
+def test_every_decision(n, d, m):
+    import torch
+    from paper_2507_08637_amd import binding
+    B, H, L = (1, 3, 0) if n > 4000 else (2, 3, 0)
+    g = torch.Generator(device="cuda").manual_seed(n + d + m)
+
+    def normal(*s):
+        return torch.randn(s, generator=g, device="cuda")
+
+    q, k, omega = ((1 - 2 * (normal(*s) < 0).float()).to(torch.bfloat16) for s in ((B, H, n, d), (B, H, n, d), (d, m)))
+    omega[0] = 0   # 63 or 127 columns count
+    v, dout = (normal(B, H, n, d).to(torch.bfloat16) for _ in range(2))
+    sigma, gw, gb, sw = torch.ones(1, device="cuda"), normal(H, 1, d) / d ** 0.5, normal(H, 1), torch.ones(1, device="cuda")
+    assert binding.load_library().wersa_selected_path(binding.make_desc(q, L, m)) == 1
+    out, saved = binding.wersa_forward(q, k, v, omega, sigma, gw, gb, sw, L)
+    got = binding.wersa_backward(q, k, v, omega, sigma, gw, gb, sw, out, dout, saved, L)
+    ref = reference(q, k, v, dout, omega, sigma, gw, gb, sw, 1e-6)
+    worst = {}
+    for name, r in zip(("dq", "dk", "dv"), ref):
+        e = (got[name].double() - r).norm(dim=-1) / r.norm(dim=-1).clamp_min(0.1 * float(r.norm(dim=-1).mean()))
+        worst[name] = float(e.max())
+    print((n, d, m), {x: f"{e:.1e}" for x, e in worst.items()}, flush=True)
+    assert max(worst.values()) < 2e-2, worst
