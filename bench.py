@@ -67,9 +67,8 @@ def kernel_models(cfg):
         "wersa_haar_stage": ("hbm", "hbm", nd * (e + 2)),       # head dimension 128: one tensor in (bf16), one out (fp16)
         "wersa_phiT_contract": ("mfma", "mfma_bf16", 2 * unit),  # projection + Phi^T Y
         "wersa_rows_fwd": ("mfma", "mfma_bf16", 2 * unit),       # projection + Phi S
-        # dPhi, dX_F; at head dimension 128 the projection, too (64 has its decisions from the kernels before)
-        "wersa_rows_bwd_q": ("mfma", "mfma_bf16", (2 if d == 64 else 3) * unit),
-        "wersa_rows_bwd_k": ("mfma", "mfma_bf16", (2 if d == 64 else 3) * unit),
+        "wersa_rows_bwd_q": ("mfma", "mfma_bf16", 2 * unit),     # dPhi, dX_F (the ReLU's decisions come as bits)
+        "wersa_rows_bwd_k": ("mfma", "mfma_bf16", 2 * unit),
         "wersa_rows_bwd_v": ("mfma", "mfma_bf16", 2 * unit),     # projection, Phi dS
         "wersa_ln_prep": ("hbm", "hbm", 3 * nd * e),
         "wersa_add_pooled": ("hbm", "hbm", 2 * nd * e),

@@ -11,8 +11,8 @@
 //   rows            per 64-row block: ReLU(X_F Omega) again, then either the step-8 apply +
 //                   normaliser (forward; the same apply form gives dV = Phi_K dS), or
 //                   dPhi -> mask -> dX_F -> gated Haar filter of the gradient + per-band
-//                   inner products (backward, Q side and K side; at head dimension 64 the mask comes as bits
-//                   from the kernel that formed the projection before: phiT_contract and the dV rows)
+//                   inner products (backward, Q side and K side; the mask comes as bits from the kernel
+//                   that formed the projection before: phiT_contract and the dV rows)
 // The projection uses fp16 MFMA operands (X_F in fp16 keeps the sign of X_F Omega right to
 // 2^-12, which the ReLU derivative needs); everything downstream of the ReLU uses bf16 MFMA.
 #include "wersa_internal.h"
@@ -335,6 +335,23 @@ __device__ __forceinline__ bf16x8 relu_bf16x8(bf16x8 p) {
   s = __builtin_elementwise_max(s, zero);
   return __builtin_bit_cast(bf16x8, s);
 }
+// A weighted sum over the k-slots of a packed operand (D = Phi z) beside the products: the 4 x 4 x 4 matrix instruction,
+// sixteen blocks of four lanes, with the weights of the lane's half-wave in every column.  Accumulator i of a lane is the sum of lane
+// 4 (lane / 4) + i; own() picks its own.  Two of them per eight values take 8 cycles each of the matrix pipe; pair dot products do not run
+// beside matrix instructions either and take 7.5 each, four per eight values.  Forward rows kernel, 8 slices of 131072 rows, m 256: 94.9 -> 90.0 us,
+// 64 of 4096, m 128: 20.8 -> 19.8; in phiT_contract, which waits at its barriers, and at head dimension 128 nothing or less.
+struct WeightedSum {
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  __device__ __forceinline__ void add(bf16x8 p, bf16x8 w) {
+    const s16x8 a = __builtin_bit_cast(s16x8, p), b = __builtin_bit_cast(s16x8, w);
+    acc = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_shufflevector(a, a, 0, 1, 2, 3), __builtin_shufflevector(b, b, 0, 1, 2, 3), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_shufflevector(a, a, 4, 5, 6, 7), __builtin_shufflevector(b, b, 4, 5, 6, 7), acc, 0, 0, 0);
+  }
+  __device__ __forceinline__ float own(int lane) const {
+    const float lo = lane & 1 ? acc[1] : acc[0], hi = lane & 1 ? acc[3] : acc[2];
+    return lane & 2 ? hi : lo;
+  }
+};
 // acc + sum_q p[q] * w[q] with bf16 pair dot products (float32 accumulate)
 __device__ __forceinline__ float dot8_bf16(bf16x8 p, bf16x8 w, float acc) {
 #pragma unroll
@@ -486,6 +503,12 @@ __device__ __forceinline__ uint32_t transpose_bits(uint32_t w, int lane) {
   w = merge(w, __builtin_amdgcn_ds_swizzle((int)w, 0x401F), lane & 16, 0x33333333u, 2);                    // lane ^ 16
   return merge(w, __builtin_amdgcn_ds_swizzle((int)w, 0x101F), lane & 4, 0x0F0F0F0Fu, 4);                  // lane ^ 4
 }
+// Row of 32 that operand lane l32 takes where the accumulator registers of the result shall hold 16 consecutive rows 16 h + i.
+__device__ __forceinline__ int lane_row(int ln) { return (ln & 3) | (ln >> 3 & 3) << 2 | (ln & 4) << 2; }
+// The position (see above) at which such a lane's words are.
+__device__ __forceinline__ int lane_position(int ln) {
+  return (ln & 3) | (ln >> 5) << 2 | (ln & 16) >> 1 | (ln & 4) << 2 | (ln & 8) << 2;
+}
 // Half a of an accumulator tile packed to bf16, elements whose bit is not set as zero; w in register form, u: which feature tile of the word.
 __device__ __forceinline__ bf16x8 pack_masked(const f32x16 &v, int a, uint32_t w, int u) {
   const bf16x8 p = pack_half(v, a);
@@ -524,6 +547,8 @@ __device__ __forceinline__ bf16x8 pack_masked(const f32x16 &v, int a, uint32_t w
 // halves (see next_tile).  32 slices of 65536 rows, m 512, training step of the attention block: 16708 -> 16441 us; per launch
 // (forward, backward form) there 628, 908 -> 521, 667; 12 slices of 16384 rows, m 512: 69.2, 95.6 -> 59.0, 72.8 us; 256 of 1024, m 256: 55.6, 73.5 -> 45.3, 56.7;
 // 8 of 4096, m 512: 17.2, 20.6 -> 17.1, 18.6.  The sums are the same bits.
+// BITS (the backward): the ReLU's decisions go to `bits` for the gradient kernel (see positive_bits), 12.5 vector instructions per 32 x 32 tile
+// (8 slices of 131072 rows, d 64, m 256: 118 -> 121 us; 32 of 65536, d 128, m 512: 682 -> 715).
 // RAGGED: n % 64 != 0, rows past n count as zeros with weight 0.  DEEP: L > 6, the filter's levels
 // above 6 enter as the per-tile addend tile_add [slices][ceil(n / 64)][DH] (the accumulators of X_F start there).
 template <int DH, int FW, bool PREP, bool RAGGED, bool DEEP, bool BITS, int NW = 4>
@@ -1199,7 +1224,7 @@ __global__ __launch_bounds__(kWavesApply * 64, 2) void rows_kernel(
       }
     }
     f32x16 acc0[2][CT];   // N or dV: rows on registers, columns on lanes
-    float dacc[2] = {0.f, 0.f};   // D partial of this lane's row (MODE 0)
+    WeightedSum dacc[2];   // D partial of this lane's row (MODE 0)
 #pragma unroll
     for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
@@ -1236,7 +1261,7 @@ __global__ __launch_bounds__(kWavesApply * 64, 2) void rows_kernel(
 #pragma unroll
           for (int a = 0; a < 2; ++a) {
             pa[a] = relu_bf16x8(pack_half(R, a));
-            if (MODE == 0) dacc[ti] = dot8_bf16(pa[a], *reinterpret_cast<const bf16x8 *>(&s_bb[32 * rt + 16 * a + 8 * h]), dacc[ti]);
+            if (MODE == 0) dacc[ti].add(pa[a], *reinterpret_cast<const bf16x8 *>(&s_bb[32 * rt + 16 * a + 8 * h]));
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct)
               acc0[ti][ct] = mfma_bf16(pa[a], *reinterpret_cast<const bf16x8 *>(&s_MT[(32 * ct + l32) * BS + 32 * rt + 16 * a + 8 * h]), acc0[ti][ct]);
@@ -1303,7 +1328,7 @@ __global__ __launch_bounds__(kWavesApply * 64, 2) void rows_kernel(
       float *dl = s_wave + wave * 64;
 #pragma unroll
       for (int ti = 0; ti < 2; ++ti) {
-        const float dsum = xor32_sum(dacc[ti]);
+        const float dsum = xor32_sum(dacc[ti].own(lane));
         const float Dt = fmaf(cscale, dsum, eps);
         // both half-waves hold the same sum and write the same values: no branch around the store
         dl[32 * ti + l32] = cscale * __builtin_amdgcn_rcpf(Dt);
@@ -1409,10 +1434,8 @@ __global__ __launch_bounds__(NW * 64, 2) void masked_rows_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const float cscale = coef[slice * kCoefStride + kCoefCscale];
   const int nchunks = m / MC, blocks = (n + 63) / 64;
-  // A lane's row among 32, and the position of its words.  (What depends on the lane alone is formed anew where it is used, from a
-  // value that the compiler does not see through: kept across the feature loop, it would be spilled.)
-  auto row_of = [](int ln) { return (ln & 3) | (ln >> 3 & 3) << 2 | (ln & 4) << 2; };
-  auto position_of = [](int ln) { return (ln & 3) | (ln >> 5) << 2 | (ln & 16) >> 1 | (ln & 4) << 2 | (ln & 8) << 2; };
+  // (What depends on the lane alone is formed anew where it is used, from a value that the compiler does not see through: kept
+  // across the feature loop, it would be spilled.)
   auto stage = [&](int m0) {
     // 16-byte pieces per row, pieces, and pieces per thread (all requested before the first is stored)
     constexpr int CPRM = (DH + 16) / 8, CPC = MC / 8, PM = MC * CPRM, PO = DH * CPC, UM = (PM + NT - 1) / NT, UO = (PO + NT - 1) / NT;
@@ -1452,7 +1475,7 @@ __global__ __launch_bounds__(NW * 64, 2) void masked_rows_kernel(
   const uint32_t *wrow = bits + (int64_t)slice * blocks * 2 * (m / 64) * 64;
   auto load_words = [&](int t0, int m0) {
     const uint32_t *p = wrow + (int64_t)(t0 >> 6) * 2 * m + m0;
-    const uint32_t off = 8 * (uint32_t)position_of((int)opaque(lane));
+    const uint32_t off = 8 * (uint32_t)lane_position((int)opaque(lane));
 #pragma unroll
     for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
@@ -1476,7 +1499,7 @@ __global__ __launch_bounds__(NW * 64, 2) void masked_rows_kernel(
   auto load_rows = [&](int t0) {
     const int valid = RAGGED ? n - t0 : 64;
     const bf16_t *ys = y + vy.slice_base(slice) + (int64_t)t0 * vy.sn;
-    const int ln = (int)opaque(lane), lrow = row_of(ln);
+    const int ln = (int)opaque(lane), lrow = lane_row(ln);
     const uint32_t yoff = (uint32_t)(ln >> 3) * ((uint32_t)vy.sn * 2) + (ln & 7) * 16;
     if (RAGGED) {
       const RowBuf yr = row_buffer(ys, vy.sn, valid);
@@ -1509,7 +1532,7 @@ __global__ __launch_bounds__(NW * 64, 2) void masked_rows_kernel(
   // columns per request (rows past n: the last one, see below).  (A load of the operand as it is used would touch 32 rows of memory with
   // 32 bytes each; with such loads and stores the kernel took 120 us, with these 107.)
   auto turn_rows = [&](int t0) {
-    const int ln = (int)opaque(lane), lrow = row_of(ln), hh = ln >> 5;
+    const int ln = (int)opaque(lane), lrow = lane_row(ln), hh = ln >> 5;
     auto key = [](int row) { return (row & 3) | (row >> 2 & 4); };
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -1550,7 +1573,7 @@ __global__ __launch_bounds__(NW * 64, 2) void masked_rows_kernel(
     const bool active = t0 < n;
     const int valid = RAGGED ? n - t0 : 64;
     if (active) {
-      const int lrow = row_of((int)opaque(lane));
+      const int lrow = lane_row((int)opaque(lane));
       // MODE 1 works with the raw dO rows: G' = D_t * G (the extension carries dD_t * D_t), and row t of dX_F is scaled by
       // c / D_t at the end; MODE 2 scales by c (extension 1, or 0 for a row past n, which must not pick up the vector part).
 #pragma unroll
@@ -1814,66 +1837,85 @@ constexpr size_t masked_smem_bytes(int mc, int nw) {
 }
 
 // ------------------------------------------------------------------------------------
-// The rows kernel of head dimension 128 (modes as above).  A wave owns 32 rows and all 128 columns: X_F and dN or V rows (68
-// registers), the accumulators of the result (64) and of the projection and dPhi (32) are for the 256 registers of two
-// waves per SIMD (the gradient modes keep some more in scratch: 116 bytes per lane on the Q side, 136 with a partial last block, 124 and
-// 148 with L > 6, and 28, 76, 36 and 84 on the K side), so one wave's conversions, masks and LDS latency run under the other's matrix instructions.  Eight waves
-// (256 rows) share the feature-side operands, which pass through LDS in stages of kWideTiles feature tiles, double-buffered,
+// The rows kernels of head dimension 128 (modes as above).  A wave owns 32 rows and all 128 columns, eight waves per workgroup
+// (256 rows), two per SIMD with 256 registers each, so one wave's conversions, masks and LDS latency run under the other's matrix
+// instructions.  They share the feature-side operands, which pass through LDS in stages of kWideTiles feature tiles, double-buffered,
 // by direct global-to-LDS loads: one barrier per stage, the next stage in flight during it.  A feature tile is
-//   Omega^T rows  [32 features][128] fp16, 256-byte rows: 16-byte piece c of row r at slot c ^ (r % 16);
-//   (M | b) rows  [32][128] bf16 likewise, and the 32 extensions of 32 bytes (gradient modes);
-//   Omega or S^T  [128 columns][32 features] bf16, 64-byte rows: piece c of row r at slot c ^ ((r / 4) % 4).
-// An instruction's row l32 is feature l32 with bits 2 and 3 swapped: the features that accumulator registers 8 a .. 8 a + 7 of
-// half-wave h stand for are then 16 a + 8 h .. + 7, one 16-byte piece of the third array.
-// What bounds it: no unit is full.  32 slices of 65536 rows, m 512 (Q side, K side, forward, dV): matrix cores 39, 43, 46, 53 % busy,
-// vector units 26, 28, 22, 21 %, LDS 24, 26, 32, 33 %; a wave spends 42, 38, 57, 40 % of its cycles at wait counts and barriers.  An
-// operand of 1 KiB read from LDS serves one matrix instruction: at full matrix rate the four SIMDs would ask for 128 bytes per
-// clock, and eight waves that do nothing but read get about 145, so there is little to spare for latency.  The epilogue's 64-row level of the Haar filter, the only one that crosses waves, costs a barrier.
-// Four waves of 64 rows with the whole register file (one per SIMD, 128 staged features, 370 to 400 bytes of scratch per lane)
-// took 1650 (Q side), 1879 (K side), 896 (forward) and 782 us (dV) there; this form takes 1131, 1095,
-// 626 and 576.  16 slices of 4096 rows with LayerNorm and two random matrices: 68, 68, 41, 32 -> 41, 40, 25, 21.
+//   Omega^T rows (apply modes) or (M | b) rows (gradient modes)  [32 features][128], 256-byte rows: 16-byte piece c of row r at
+//   slot c ^ (r % 16); gradient modes also the 32 extensions of 32 bytes;
+//   S^T or Omega  [128 columns][32 features] bf16, 64-byte rows: piece c of row r at slot c ^ ((r / 4) % 4).
+// An instruction's row l32 is feature swap23(l32): the features that accumulator registers 8 a .. 8 a + 7 of
+// half-wave h stand for are then 16 a + 8 h .. + 7, one 16-byte piece of the second array.
+// Rows of X_F, dN or V come in as whole 256-byte lines, a row group ahead, and go through the wave's panel into the order of the operand.
 // ------------------------------------------------------------------------------------
 constexpr int kWideWaves = 8, kWideTiles = 2, kWideRows = 32 * kWideWaves;
 constexpr bool wide_grad(int MODE) { return MODE == 1 || MODE == 2; }
-constexpr int wide_tile_bytes(int MODE) { return wide_grad(MODE) ? 25 * 1024 : 16 * 1024; }
-constexpr int kWidePanel = 32 * 36;   // elements of a wave's tile of 32 rows x 32 columns (or transposed)
+constexpr int wide_tile_bytes(int MODE) { return (wide_grad(MODE) ? 17 : 16) * 1024; }
+constexpr int kWidePanel = 8192;   // bytes of a wave's panel
 inline size_t wide_smem_bytes(int MODE, int m) {
-  return 2 * kWideTiles * wide_tile_bytes(MODE) + kWideWaves * (kWidePanel * 2 + 32 * 4 + 2 * 128 * 4) + (MODE == 0 ? m * 2 : 0);
+  return 2 * kWideTiles * wide_tile_bytes(MODE) + kWideWaves * (kWidePanel + 32 * 4 + (wide_grad(MODE) ? 2 * 128 * 4 : 0)) + (MODE == 0 ? m * 2 : 0);
 }
-template <int MODE, bool LN, bool RAGGED, bool DEEP>
+// A panel of 32 rows of 256 bytes: 16-byte piece c of row r at slot c ^ wide_key(r).  Rows in the order of a lane's number (natural, or as
+// lane_row gives them) meet all eight keys in eight lanes.
+__device__ __forceinline__ int wide_key(int r) { return (r & 3) | (r >> 2 & 4) | (r & 4) << 1; }
+// The rows' raw pieces (row 4 j + lane / 16, piece lane % 16) -> operands (row `row`, k = 16 ks + 8 h ..).
+__device__ __forceinline__ void wide_turn(unsigned char *panel, const u16x8 (&raw)[8], int ln, int row, u16x8 (&op)[8]) {
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int r = 4 * j + (ln >> 4);
+    *reinterpret_cast<u16x8 *>(panel + r * 256 + (((ln & 15) ^ wide_key(r)) << 4)) = raw[j];
+  }
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks)
+    op[ks] = *reinterpret_cast<const u16x8 *>(panel + row * 256 + (((2 * ks + (ln >> 5)) ^ wide_key(row)) << 4));
+  __builtin_amdgcn_wave_barrier();
+}
+// 32 rows of 128 columns from `rows`, row stride sn elements, as raw pieces (RAGGED: zeros from row `valid` on).
+template <bool RAGGED, typename T>
+__device__ __forceinline__ void wide_load(const T *rows, int64_t sn, int valid, int ln, u16x8 (&raw)[8]) {
+  const uint32_t off = (uint32_t)(ln >> 4) * ((uint32_t)sn * 2) + (ln & 15) * 16;
+  if (RAGGED) {
+    const RowBuf b = row_buffer(rows, sn, valid);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) raw[j] = buf_load16<u16x8>(b, off + (uint32_t)j * ((uint32_t)sn * 8));
+  } else {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) raw[j] = *reinterpret_cast<const u16x8 *>(reinterpret_cast<const char *>(rows + 4 * j * sn) + off);
+  }
+}
+
+// Apply modes.  32 slices of 65536 rows, m 512 (forward, dV): 559 and 592 us (with rows of X_F read in the order of the operand, 32 bytes
+// of a line at a time, and without the bits: 617 and 584; four waves of 64 rows and 512 registers: 896 and 782).  Matrix cores busy about half of
+// the time: an operand of 1 KiB read from LDS serves one matrix instruction, and the waits of two waves per SIMD are not all covered.
+template <int MODE, bool LN, bool RAGGED>
 __global__ __launch_bounds__(kWideWaves * 64, 2) void wide_rows_kernel(
-    const _Float16 *xf, const bf16_t *x, View vx, const bf16_t *y, View vy, const float *Dsaved, const float *arow,
-    const _Float16 *omT, const bf16_t *omega, const bf16_t *Mx, const bf16_t *MT, const bf16_t *bb, const float *coef, float eps,
-    int n, int m, int row_groups, bf16_t *out, View vo, float *Dout, float *partF, int L, float *tile_gsum) {
-  constexpr int DH = 128, KS = 8, CT = 4, TS = 36;
-  constexpr bool GRAD = wide_grad(MODE);
-  constexpr int TB = wide_tile_bytes(MODE), OM = 8192, OO = GRAD ? 16384 : 8192, OE = 24576;   // a feature tile and its arrays
+    const _Float16 *xf, const _Float16 *omT, const bf16_t *MT, const bf16_t *bb, const float *coef, float eps,
+    int n, int m, int row_groups, bf16_t *out, View vo, float *Dout, uint32_t *bits) {
+  static_assert(!wide_grad(MODE), "the gradient modes have wide_grad_kernel");
+  constexpr int DH = 128, KS = 8, CT = 4, TS = 36, TB = wide_tile_bytes(MODE), OO = 8192;   // a feature tile and its second array
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   typedef __attribute__((address_space(3))) unsigned char lds_byte;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte *)smem_raw;
   unsigned char *p = smem_raw + 2 * kWideTiles * TB;
-  float *s_pair = reinterpret_cast<float *>(p);                                  // [waves][2][128]: 32-row sums of dX_F and X
-  float *s_wave = s_pair + kWideWaves * 2 * 128;                                 // [waves][32]
-  bf16_t *s_panel = reinterpret_cast<bf16_t *>(s_wave + kWideWaves * 32);        // [waves][kWidePanel]
-  bf16_t *s_bb = s_panel + kWideWaves * kWidePanel;                              // MODE 0: z
   const int slice = blockIdx.y, tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  unsigned char *panel = p + wave * kWidePanel;
+  float *sw = reinterpret_cast<float *>(p + kWideWaves * kWidePanel) + wave * 32;
+  bf16_t *s_bb = reinterpret_cast<bf16_t *>(p + kWideWaves * (kWidePanel + 128));   // MODE 0: z
   const float cscale = coef[slice * kCoefStride + kCoefCscale];
 
   // ---- staging: wave w moves pieces 4 w .. 4 w + 3 (rows) or 16 w .. 16 w + 15 (columns) of every array
   const int ra = 4 * wave + (lane >> 4), ca = (lane & 15) ^ (ra & 15), ro = 16 * wave + (lane >> 2), co = (lane & 3) ^ ((ro >> 2) & 3);
-  const uint32_t va = ra * 256 + ca * 16, vm = ra * 288 + ca * 16, vcol = (uint32_t)ro * (uint32_t)(2 * m) + co * 16,
-                 ve = (lane & 31) * 288 + 256 + (lane >> 5) * 16;
-  const bf16_t *mx = GRAD ? Mx + (int64_t)slice * m * (DH + 16) : nullptr;
-  const bf16_t *cols = GRAD ? omega : MT + (int64_t)slice * DH * m;
+  const uint32_t va = ra * 256 + ca * 16, vcol = (uint32_t)ro * (uint32_t)(2 * m) + co * 16;
+  const bf16_t *cols = MT + (int64_t)slice * DH * m;
   auto request = [&](int buf, int f0) {
 #pragma unroll
     for (int ft = 0; ft < kWideTiles; ++ft, f0 += 32) {
       const uint32_t at = lds0 + (uint32_t)((buf * kWideTiles + ft) * TB + wave * 1024);
       lds_dma16(at, va, omT + (int64_t)f0 * DH);
-      if (GRAD) lds_dma16(at + OM, vm, mx + (int64_t)f0 * (DH + 16));
       lds_dma16(at + OO, vcol, cols + f0);
-      if (GRAD && wave == ft) lds_dma16(at + OE - wave * 1024, ve, mx + (int64_t)f0 * (DH + 16));
     }
   };
   // (the wait as a builtin: the compiler then knows that the rows' loads have landed, too, and waits for none in the loop)
@@ -1881,52 +1923,11 @@ __global__ __launch_bounds__(kWideWaves * 64, 2) void wide_rows_kernel(
     __builtin_amdgcn_s_waitcnt(0x0070);
     asm volatile("s_barrier" ::: "memory");
   };
-
-  float u[kTileBands], cf[kTileBands];   // u_l = sum over blocks of bs_l(g) * bs_l(x), this lane's share
-#pragma unroll
-  for (int l = 0; l < kTileBands; ++l) {
-    u[l] = 0.f;
-    cf[l] = GRAD ? coef[slice * kCoefStride + l] : 0.f;
-  }
-
-  // ---- row-side operands of the wave's 32 rows
-  f16x8 xb[KS];
-  bf16x8 yb[GRAD ? KS + 1 : 1];
-  float dval = 1.f, aval = 1.f;   // D and dD of row l32 (MODE 1)
-  auto load_rows = [&](int t0) {
-    const int valid = RAGGED ? n - t0 : 32;
-    const _Float16 *xs = xf + ((int64_t)slice * n + t0) * DH;
-    if (RAGGED) {
-      const RowBuf xr = row_buffer(xs, DH, valid);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) xb[ks] = buf_load16<f16x8>(xr, (uint32_t)(l32 * DH + 16 * ks + 8 * h) * 2);
-    } else {
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) xb[ks] = *reinterpret_cast<const f16x8 *>(xs + l32 * DH + 16 * ks + 8 * h);
-    }
-    if (GRAD) {
-      const bf16_t *ys = y + vy.slice_base(slice) + (int64_t)t0 * vy.sn;
-      if (RAGGED) {
-        const RowBuf yr = row_buffer(ys, vy.sn, valid);
-        const uint32_t off = l32 * ((uint32_t)vy.sn * 2) + h * 16;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) yb[ks] = buf_load16<bf16x8>(yr, off + 32u * ks);
-        if (MODE == 1) {
-          dval = buf_load4(row_buffer(Dsaved + (int64_t)slice * n + t0, 1, valid), 4 * l32);
-          aval = buf_load4(row_buffer(arow + (int64_t)slice * n + t0, 1, valid), 4 * l32);
-        } else {
-          aval = l32 < valid ? 1.f : 0.f;
-        }
-      } else {
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          yb[ks] = *reinterpret_cast<const bf16x8 *>(ys + (int64_t)l32 * vy.sn + 16 * ks + 8 * h);
-        if (MODE == 1) {
-          dval = Dsaved[(int64_t)slice * n + t0 + l32];
-          aval = arow[(int64_t)slice * n + t0 + l32];
-        }
-      }
-    }
+  u16x8 raw[8], xb[KS];
+  auto load_rows = [&](int t0) { wide_load<RAGGED>(xf + ((int64_t)slice * n + t0) * DH, DH, n - t0, (int)opaque(lane), raw); };
+  auto turn_rows = [&]() {
+    const int ln = (int)opaque(lane);
+    wide_turn(panel, raw, ln, ln & 31, xb);
   };
   // (with a partial last block both waves of a 64-row block take part: rows past n are zeros)
   auto in_range = [&](int t0) { return (RAGGED ? t0 & ~63 : t0) < n; };
@@ -1938,60 +1939,52 @@ __global__ __launch_bounds__(kWideWaves * 64, 2) void wide_rows_kernel(
     for (int e = tid; e < m; e += kWideWaves * 64) s_bb[e] = bb[(int64_t)slice * m + e];
   {
     const int t_first = blockIdx.x * kWideRows + wave * 32;
-    if ((int)blockIdx.x < row_groups && in_range(t_first)) load_rows(t_first);
+    if ((int)blockIdx.x < row_groups && in_range(t_first)) {
+      load_rows(t_first);
+      turn_rows();
+    }
   }
-  const int prow = (l32 & ~12) | (l32 & 4) << 1 | (l32 & 8) >> 1;
-  const int o_row = prow * 256 + ((h ^ (prow & 15)) << 4), o_ext = (h * 32 + prow) * 16;
-  const int o_col0 = l32 * 64 + ((h ^ ((l32 >> 2) & 3)) << 4), i16 = lane & 15, g16 = lane >> 4;
-  bf16_t *tl = s_panel + wave * kWidePanel;
-  float *sw = s_wave + wave * 32, *mine = s_pair + wave * 256, *other = s_pair + (wave ^ 1) * 256;
+  const int prow = swap23(l32), o_row = prow * 256 + ((h ^ (prow & 15)) << 4), o_col0 = l32 * 64 + ((h ^ ((l32 >> 2) & 3)) << 4);
+  bf16_t *tl = reinterpret_cast<bf16_t *>(panel);
 
   for (int rg = blockIdx.x; rg < row_groups; rg += gridDim.x) {
     const int t0 = rg * kWideRows + wave * 32;
     const bool active = in_range(t0);
     const int valid = RAGGED ? n - t0 : 32;
-    if (GRAD && active) {   // the rank-one extension (a_t, 0, ...); MODE 1 works with the raw dO rows: G' = D_t G
-      bf16x8 ext = splat_bf16x8(0.f);
-      if (h == 0) ext[0] = (__bf16)(MODE == 1 ? aval * dval : aval);
-      yb[GRAD ? KS : 0] = ext;
-      // row scale c / D_t (rows past n: D reads as 0 there, and their scale must be finite for the sums over the block)
-      if (MODE == 1 && h == 0) sw[l32] = (RAGGED && l32 >= valid) ? 0.f : cscale * __builtin_amdgcn_rcpf(dval);
-    }
     f32x16 acc[CT];
     float dacc = 0.f;
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) acc[ct] = zero16();
+    uint32_t *bw = nullptr;   // MODE 3: the lane's words (row l32, half h of the features), see positive_bits
+    if (MODE == 3)
+      bw = bits + (((int64_t)slice * ((n + 63) / 64) + (t0 >> 6)) * 2 + (t0 >> 5 & 1)) * m + 2 * ((l32 & 27) | (l32 & 4) << 3 | h << 2);
     for (int s = 0; s < stages; ++s, buf ^= 1) {
       landed();   // stage s is there; every wave is done with the one before it, which is overwritten now
       request(buf ^ 1, s + 1 < stages ? (s + 1) * 32 * kWideTiles : 0);   // (the last: for the next row group)
       if (!active) continue;
+      uint32_t word = 0;
 #pragma unroll
       for (int ft = 0; ft < kWideTiles; ++ft) {
         const unsigned char *st = smem_raw + (buf * kWideTiles + ft) * TB;
-        f32x16 R = zero16(), G = zero16();
+        f32x16 R = zero16();
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          R = mfma_f16(*reinterpret_cast<const f16x8 *>(st + (o_row ^ (32 * ks))), xb[ks], R);
-          if (GRAD) G = mfma_bf16(*reinterpret_cast<const bf16x8 *>(st + OM + (o_row ^ (32 * ks))), yb[GRAD ? ks : 0], G);
-        }
-        if (GRAD) {
-          G = mfma_bf16(*reinterpret_cast<const bf16x8 *>(st + OE + o_ext), yb[GRAD ? KS : 0], G);
-          // 1[R > 0] as a multiplier: clamp(R * 2^100, 0, 1) is 1 for every R > 2^-100 and 0 for R <= 0
-#pragma unroll
-          for (int i = 0; i < 16; ++i) G[i] *= __builtin_amdgcn_fmed3f(R[i] * 0x1p+100f, 0.f, 1.f);
-        }
+        for (int ks = 0; ks < KS; ++ks)
+          R = mfma_f16(*reinterpret_cast<const f16x8 *>(st + (o_row ^ (32 * ks))), __builtin_bit_cast(f16x8, xb[ks]), R);
+        bf16x8 pa[2];
 #pragma unroll
         for (int a = 0; a < 2; ++a) {
-          const bf16x8 pa = GRAD ? pack_half(G, a) : relu_bf16x8(pack_half(R, a));
+          pa[a] = relu_bf16x8(pack_half(R, a));
           if (MODE == 0)
-            dacc = dot8_bf16(pa, *reinterpret_cast<const bf16x8 *>(s_bb + (s * kWideTiles + ft) * 32 + 16 * a + 8 * h), dacc);
+            dacc = dot8_bf16(pa[a], *reinterpret_cast<const bf16x8 *>(s_bb + (s * kWideTiles + ft) * 32 + 16 * a + 8 * h), dacc);
 #pragma unroll
           for (int ct = 0; ct < CT; ++ct)
-            acc[ct] = mfma_bf16(pa, *reinterpret_cast<const bf16x8 *>(st + OO + ct * 2048 + (o_col0 ^ (32 * a))), acc[ct]);
+            acc[ct] = mfma_bf16(pa[a], *reinterpret_cast<const bf16x8 *>(st + OO + ct * 2048 + (o_col0 ^ (32 * a))), acc[ct]);
         }
+        if (MODE == 3) word |= positive_bits(pa) << 8 * ft;
       }
+      if (MODE == 3) bw[(s >> 1) * 128 + (s & 1)] = swap_bytes12(word);
       // operand reads kAhead matrix instructions before their use (left alone, the compiler reads one and waits for it)
-      constexpr int kAhead = 6, MF = kWideTiles * (GRAD ? 25 : 16);
+      constexpr int kAhead = 6, MF = kWideTiles * 16;
       __builtin_amdgcn_sched_group_barrier(0x100, kAhead, 0);
 #pragma unroll
       for (int i = 0; i < MF - kAhead; ++i) {
@@ -2001,140 +1994,289 @@ __global__ __launch_bounds__(kWideWaves * 64, 2) void wide_rows_kernel(
       __builtin_amdgcn_sched_group_barrier(0x008, kAhead, 0);
     }
 
-    // ---- epilogues
+    // ---- epilogue
+    if (!active) continue;   // (no later row group of the wave is in range either)
     const int t_next = t0 + (int)gridDim.x * kWideRows;
+    const bool more = rg + (int)gridDim.x < row_groups && in_range(t_next);
+    if (more) load_rows(t_next);
     bf16_t *os = out + vo.slice_base(slice) + (int64_t)t0 * vo.sn;
     RowBuf osb;
     if (RAGGED) osb = row_buffer(os, vo.sn, valid);
-    if (active) {
-      if (MODE == 0 && LN) {   // O_t = (N_t - mean N_t) / sqrt(var N_t + eps), N = c * acc; 1 / sqrt(var + eps) goes to D
+    if (MODE == 0 && LN) {   // O_t = (N_t - mean N_t) / sqrt(var N_t + eps), N = c * acc; 1 / sqrt(var + eps) goes to D
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const float mu = half_wave_sum((acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i])) * (1.0f / (float)DH);
-          float q = 0.f;
-#pragma unroll
-          for (int ct = 0; ct < CT; ++ct) {
-            const float e = (acc[ct][i] - mu) * cscale;
-            acc[ct][i] = e;
-            q = fmaf(e, e, q);
-          }
-          const float rstd = 1.0f / sqrtf(half_wave_sum(q) * (1.0f / (float)DH) + eps);
-#pragma unroll
-          for (int ct = 0; ct < CT; ++ct) acc[ct][i] *= rstd;
-          if (l32 == 0) sw[acc_row(i, h)] = rstd;
-        }
-        __builtin_amdgcn_wave_barrier();
-        if (l32 < valid) Dout[(int64_t)slice * n + t0 + l32] = sw[l32];
-      } else if (MODE == 0) {   // D_t = c * sum_r relu(R) z + eps, row scale c / D_t
-        const float Dt = fmaf(cscale, xor32_sum(dacc), eps);
-        sw[l32] = cscale * __builtin_amdgcn_rcpf(Dt);   // (both half-waves hold and write the same)
-        if (l32 < valid) Dout[(int64_t)slice * n + t0 + l32] = Dt;
-      }
-      __builtin_amdgcn_wave_barrier();
-      if (!(MODE == 0 && LN)) {
-        float sc[16];
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          f32x4 s4 = {cscale, cscale, cscale, cscale};
-          if (MODE <= 1) s4 = *reinterpret_cast<const f32x4 *>(&sw[8 * g + 4 * h]);
-#pragma unroll
-          for (int q = 0; q < 4; ++q) sc[4 * g + q] = s4[q];
-        }
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) acc[ct][i] *= sc[i];
-      }
-    }
-    if (!GRAD) {   // bf16 through the wave's tile, 8-byte row-major stores
-      if (active) {
+      for (int i = 0; i < 16; ++i) {
+        const float mu = half_wave_sum((acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i])) * (1.0f / (float)DH);
+        float q = 0.f;
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
-          __builtin_amdgcn_wave_barrier();
+          const float e = (acc[ct][i] - mu) * cscale;
+          acc[ct][i] = e;
+          q = fmaf(e, e, q);
+        }
+        const float rstd = 1.0f / sqrtf(half_wave_sum(q) * (1.0f / (float)DH) + eps);
 #pragma unroll
-          for (int i = 0; i < 16; ++i) tl[acc_row(i, h) * TS + l32] = cvt_bf16(acc[ct][i]);
-          __builtin_amdgcn_wave_barrier();
-          bf16x4 piece[4];
+        for (int ct = 0; ct < CT; ++ct) acc[ct][i] *= rstd;
+        if (l32 == 0) sw[acc_row(i, h)] = rstd;
+      }
+      __builtin_amdgcn_wave_barrier();
+      if (l32 < valid) Dout[(int64_t)slice * n + t0 + l32] = sw[l32];
+    } else if (MODE == 0) {   // D_t = c * sum_r relu(R) z + eps, row scale c / D_t
+      const float Dt = fmaf(cscale, xor32_sum(dacc), eps);
+      sw[l32] = cscale * __builtin_amdgcn_rcpf(Dt);   // (both half-waves hold and write the same)
+      if (l32 < valid) Dout[(int64_t)slice * n + t0 + l32] = Dt;
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (!(MODE == 0 && LN)) {
+      float sc[16];
 #pragma unroll
-          for (int j = 0; j < 4; ++j) piece[j] = *reinterpret_cast<const bf16x4 *>(&tl[((lane >> 3) + 8 * j) * TS + (lane & 7) * 4]);
-          if (RAGGED) {
-            uint32_t off = (lane >> 3) * ((uint32_t)vo.sn * 2) + (32 * ct + (lane & 7) * 4) * 2;
+      for (int g = 0; g < 4; ++g) {
+        f32x4 s4 = {cscale, cscale, cscale, cscale};
+        if (MODE == 0) s4 = *reinterpret_cast<const f32x4 *>(&sw[8 * g + 4 * h]);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              buf_store8(osb, off, piece[j]);
-              off += 16 * (uint32_t)vo.sn;
-            }
-          } else {
-            bf16_t *orow = os + (int64_t)(lane >> 3) * vo.sn + 32 * ct + (lane & 7) * 4;
+        for (int q = 0; q < 4; ++q) sc[4 * g + q] = s4[q];
+      }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              *reinterpret_cast<bf16x4 *>(orow) = piece[j];
-              orow += 8 * vo.sn;
-            }
-          }
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[ct][i] *= sc[i];
+    }
+    // bf16 through the wave's panel, 8-byte row-major stores
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int i = 0; i < 16; ++i) tl[acc_row(i, h) * TS + l32] = cvt_bf16(acc[ct][i]);
+      __builtin_amdgcn_wave_barrier();
+      bf16x4 piece[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) piece[j] = *reinterpret_cast<const bf16x4 *>(&tl[((lane >> 3) + 8 * j) * TS + (lane & 7) * 4]);
+      if (RAGGED) {
+        uint32_t off = (lane >> 3) * ((uint32_t)vo.sn * 2) + (32 * ct + (lane & 7) * 4) * 2;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          buf_store8(osb, off, piece[j]);
+          off += 16 * (uint32_t)vo.sn;
+        }
+      } else {
+        bf16_t *orow = os + (int64_t)(lane >> 3) * vo.sn + 32 * ct + (lane & 7) * 4;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          *reinterpret_cast<bf16x4 *>(orow) = piece[j];
+          orow += 8 * vo.sn;
         }
       }
-      if (rg + (int)gridDim.x < row_groups && in_range(t_next)) load_rows(t_next);
-      continue;
     }
-    // Gradient modes: gated Haar filter of dX_F on the accumulator layout and band inner products.  Lane (l32, h) holds
-    // column 32 ct + l32 and rows 8 g + 4 h + e: block sums of 2 and 4 rows are in-lane, 8 rows need the other half-wave, 16 and
-    // 32 are in-lane again, 64 rows the other wave of the pair.
-    const bf16_t *xsrc = x + vx.slice_base(slice) + (int64_t)t0 * vx.sn;
-    if (active) {
-      bf16x4 xp[2][4];   // X of a column tile in 8-byte row-major pieces, and of the next
-      auto load_x = [&](int ct) {
-        if (RAGGED) {
-          const RowBuf xr = row_buffer(xsrc, vx.sn, valid);
-          uint32_t off = (lane >> 3) * ((uint32_t)vx.sn * 2) + (32 * ct + (lane & 7) * 4) * 2;
+    if (more) turn_rows();
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the last request: nothing reads it, but it must not outlive the workgroup
+}
+
+// Gradient modes, with the ReLU's decisions given (see masked_rows_kernel, whose epilogue this one shares): the 64-row level of the
+// Haar filter, the only one that crosses waves, goes through LDS and costs a barrier.
+// 32 slices of 65536 rows, m 512 (Q side, K side): 808 and 797 us.  With the projection in the kernel, X_F among the operands (28 to 148
+// bytes per lane of scratch) and rows read and written 16 and 8 bytes at a time: 1132 and 1096.  16 slices of 4096 rows: 40, 36 -> 30, 29.
+template <int MODE, bool RAGGED, bool DEEP>
+__global__ __launch_bounds__(kWideWaves * 64, 2) void wide_grad_kernel(
+    const bf16_t *x, View vx, const bf16_t *y, View vy, const float *Dsaved, const float *arow, const uint32_t *bits,
+    const bf16_t *omega, const bf16_t *Mx, const float *coef, int n, int m, int row_groups, bf16_t *out, View vo,
+    float *partF, int L, float *tile_gsum) {
+  constexpr int DH = 128, KS = 8, CT = 4, TB = wide_tile_bytes(MODE), OO = 8192, OE = 16384;   // a feature tile and its arrays
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  typedef __attribute__((address_space(3))) unsigned char lds_byte;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte *)smem_raw;
+  unsigned char *p = smem_raw + 2 * kWideTiles * TB;
+  const int slice = blockIdx.y, tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  unsigned char *panel = p + wave * kWidePanel;
+  float *s_wave = reinterpret_cast<float *>(p + kWideWaves * kWidePanel), *s_pair = s_wave + kWideWaves * 32;   // [waves][32]; [waves][2][128]: 32-row sums of dX_F and X
+  float *sw = s_wave + wave * 32, *mine = s_pair + wave * 256, *other = s_pair + (wave ^ 1) * 256;
+  const float cscale = coef[slice * kCoefStride + kCoefCscale];
+
+  // ---- staging, as above
+  const int ra = 4 * wave + (lane >> 4), ca = (lane & 15) ^ (ra & 15), ro = 16 * wave + (lane >> 2), co = (lane & 3) ^ ((ro >> 2) & 3);
+  const uint32_t vm = ra * 288 + ca * 16, vcol = (uint32_t)ro * (uint32_t)(2 * m) + co * 16, ve = (lane & 31) * 288 + 256 + (lane >> 5) * 16;
+  const bf16_t *mx = Mx + (int64_t)slice * m * (DH + 16);
+  auto request = [&](int buf, int f0) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            xp[ct & 1][j] = buf_load8<bf16x4>(xr, off);
-            off += 16 * (uint32_t)vx.sn;
-          }
-        } else {
-          const bf16_t *xrow = xsrc + (int64_t)(lane >> 3) * vx.sn + 32 * ct + (lane & 7) * 4;
+    for (int ft = 0; ft < kWideTiles; ++ft, f0 += 32) {
+      const uint32_t at = lds0 + (uint32_t)((buf * kWideTiles + ft) * TB + wave * 1024);
+      lds_dma16(at, vm, mx + (int64_t)f0 * (DH + 16));
+      lds_dma16(at + OO, vcol, omega + f0);
+      if (wave == ft) lds_dma16(at + OE - wave * 1024, ve, mx + (int64_t)f0 * (DH + 16));
+    }
+  };
+  auto landed = [&]() {
+    __builtin_amdgcn_s_waitcnt(0x0070);
+    asm volatile("s_barrier" ::: "memory");
+  };
+  float u[kTileBands], cf[kTileBands];   // u_l = sum over blocks of bs_l(g) * bs_l(x), this lane's share
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            xp[ct & 1][j] = *reinterpret_cast<const bf16x4 *>(xrow);
-            xrow += 8 * vx.sn;
-          }
+  for (int l = 0; l < kTileBands; ++l) {
+    u[l] = 0.f;
+    cf[l] = coef[slice * kCoefStride + l];
+  }
+
+  // ---- row-side operands of the wave's 32 rows, and X in the panel as [4 column tiles][32 rows][32]
+  u16x8 raw[8], yb[KS];
+  float dval = 1.f, aval = 1.f;   // D and dD of the lane's row (MODE 1)
+  auto load_rows = [&](int t0) {
+    const int ln = (int)opaque(lane), lrow = lane_row(ln), valid = RAGGED ? n - t0 : 32;
+    wide_load<RAGGED>(y + vy.slice_base(slice) + (int64_t)t0 * vy.sn, vy.sn, valid, ln, raw);
+    if (MODE == 1) {
+      const float *Dp = Dsaved + (int64_t)slice * n + t0, *ap = arow + (int64_t)slice * n + t0;
+      const uint32_t off = 4 * (uint32_t)lrow;
+      dval = RAGGED ? buf_load4(row_buffer(Dp, 1, valid), off) : *reinterpret_cast<const float *>(reinterpret_cast<const char *>(Dp) + off);
+      aval = RAGGED ? buf_load4(row_buffer(ap, 1, valid), off) : *reinterpret_cast<const float *>(reinterpret_cast<const char *>(ap) + off);
+    } else if (RAGGED) {
+      aval = lrow < valid ? 1.f : 0.f;
+    }
+  };
+  auto turn_rows = [&](int t0) {
+    const int ln = (int)opaque(lane);
+    wide_turn(panel, raw, ln, lane_row(ln), yb);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (what is read from the panel has arrived)
+    const uint32_t at = (uint32_t)(uintptr_t)(lds_byte *)panel;
+    // (a wave past row n whose block's other half is there: any rows in range will do, they are replaced by zeros)
+    const int last = RAGGED ? max(n - t0 - 1, 0) : 31;
+    const bf16_t *xs = x + vx.slice_base(slice) + (int64_t)(RAGGED ? min(t0, n - 1) : t0) * vx.sn;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int ct = i >> 1, r = 16 * (i & 1) + (ln >> 2);
+      lds_dma16(at + 1024 * i, (uint32_t)(RAGGED ? min(r, last) : r) * ((uint32_t)vx.sn * 2) + (ln & 3) * 16, xs + 32 * ct);
+    }
+  };
+  // (with a partial last block both waves of a 64-row block take part: rows past n are zeros)
+  auto in_range = [&](int t0) { return (RAGGED ? t0 & ~63 : t0) < n; };
+
+  const int stages = m / (32 * kWideTiles);
+  int buf = 0;
+  request(0, 0);
+  {
+    const int t_first = blockIdx.x * kWideRows + wave * 32;
+    if ((int)blockIdx.x < row_groups && in_range(t_first)) {
+      load_rows(t_first);
+      turn_rows(t_first);
+    }
+  }
+  const int prow = swap23(l32), o_row = prow * 256 + ((h ^ (prow & 15)) << 4), o_ext = (h * 32 + prow) * 16;
+  const int o_col0 = l32 * 64 + ((h ^ ((l32 >> 2) & 3)) << 4);
+
+  for (int rg = blockIdx.x; rg < row_groups; rg += gridDim.x) {
+    const int t0 = rg * kWideRows + wave * 32;
+    const bool active = in_range(t0);
+    const int valid = RAGGED ? n - t0 : 32;
+    bf16x8 ext = splat_bf16x8(0.f);
+    const uint32_t *wp = bits;
+    uint32_t next_word = 0;
+    if (active) {   // the rank-one extension (a_t, 0, ...); MODE 1 works with the raw dO rows: G' = D_t G
+      const int ln = (int)opaque(lane), lrow = lane_row(ln);
+      if (h == 0) ext[0] = (__bf16)(MODE == 1 ? aval * dval : aval);
+      // row scale c / D_t (rows past n: D reads as 0 there, and their scale must be finite for the sums over the block)
+      if (MODE == 1 && h == 0) sw[lrow] = (RAGGED && lrow >= valid) ? 0.f : cscale * __builtin_amdgcn_rcpf(dval);
+      wp = bits + (((int64_t)slice * ((n + 63) / 64) + (t0 >> 6)) * 2 + (t0 >> 5 & 1)) * m +
+           2 * lane_position(ln);
+      next_word = wp[0];
+    }
+    f32x16 acc[CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) acc[ct] = zero16();
+    for (int s = 0; s < stages; ++s, buf ^= 1) {
+      landed();   // stage s is there; every wave is done with the one before it, which is overwritten now
+      request(buf ^ 1, s + 1 < stages ? (s + 1) * 32 * kWideTiles : 0);   // (the last: for the next row group)
+      if (!active) continue;
+      uint32_t word = swap_bytes12(next_word);
+      if (MODE == 1) word = transpose_bits(word, (int)opaque(lane));   // (from the contraction: features on lanes)
+      const int sn = s + 1 < stages ? s + 1 : s;
+      next_word = wp[(sn >> 1) * 128 + (sn & 1)];
+      f32x16 G[kWideTiles];
+#pragma unroll
+      for (int ft = 0; ft < kWideTiles; ++ft) {
+        const unsigned char *st = smem_raw + (buf * kWideTiles + ft) * TB;
+        G[ft] = zero16();
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+          G[ft] = mfma_bf16(*reinterpret_cast<const bf16x8 *>(st + (o_row ^ (32 * ks))), __builtin_bit_cast(bf16x8, yb[ks]), G[ft]);
+        G[ft] = mfma_bf16(*reinterpret_cast<const bf16x8 *>(st + OE + o_ext), ext, G[ft]);
+      }
+#pragma unroll
+      for (int ft = 0; ft < kWideTiles; ++ft) {
+        const unsigned char *st = smem_raw + (buf * kWideTiles + ft) * TB;
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          const bf16x8 pg = pack_masked(G[ft], a, word, ft);
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct)
+            acc[ct] = mfma_bf16(pg, *reinterpret_cast<const bf16x8 *>(st + OO + ct * 2048 + (o_col0 ^ (32 * a))), acc[ct]);
         }
-      };
-      load_x(0);
+      }
+      // operand reads kAhead matrix instructions before their use (left alone, the compiler reads one and waits for it)
+      constexpr int kAhead = 6, MF = kWideTiles * 17;
+      __builtin_amdgcn_sched_group_barrier(0x100, kAhead, 0);
+#pragma unroll
+      for (int i = 0; i < MF - kAhead; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, kAhead, 0);
+    }
+
+    // ---- epilogue.  Lane (l32, h) holds column 32 ct + l32 and rows 16 h + i.
+    const int t_next = t0 + (int)gridDim.x * kWideRows;
+    const bool more = active && rg + (int)gridDim.x < row_groups && in_range(t_next);
+    if (active) {
+      // (X is in the panel: the stages' waits were for every load)
+      if (RAGGED && valid < 32) {   // rows past n are zeros
+        const u16x8 zero = {};
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (16 * (i & 1) + (lane >> 2) >= valid) *reinterpret_cast<u16x8 *>(panel + 1024 * i + lane * 16) = zero;
+      }
+      if (more) load_rows(t_next);
+      __builtin_amdgcn_wave_barrier();
+      float sc[16];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        f32x4 s4 = {cscale, cscale, cscale, cscale};
+        if (MODE == 1) s4 = *reinterpret_cast<const f32x4 *>(&sw[16 * h + 4 * g]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sc[4 * g + q] = s4[q];
+      }
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) {
-        if (ct + 1 < CT) load_x(ct + 1);
-        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int j = 0; j < 4; ++j) *reinterpret_cast<bf16x4 *>(&tl[((lane >> 3) + 8 * j) * TS + (lane & 7) * 4]) = xp[ct & 1][j];
-        __builtin_amdgcn_wave_barrier();
+        for (int i = 0; i < 16; ++i) acc[ct][i] *= sc[i];
+        const int ln = (int)opaque(lane), i16 = ln & 15, g16 = ln >> 4;
+        const bf16_t *tl = reinterpret_cast<const bf16_t *>(panel) + ct * 1024;
         float g1[8], x1[8];
-        bf16x4 xq[4];   // X at this lane's accumulator positions: rows 8 g + 4 h + e of column l32
+        bf16x4 xq[4];   // X at this lane's accumulator positions: rows 16 h + 4 g .. + 3 of column l32
 #pragma unroll
         for (int g = 0; g < 4; ++g)
-          xq[g] = lds_read_tr4(&tl[(8 * g + 4 * h + (i16 >> 2)) * TS + 16 * (g16 & 1) + 4 * (i16 & 3)]);
+          xq[g] = lds_read_tr4(&tl[(16 * (ln >> 5) + 4 * g + (i16 >> 2)) * 32 + 16 * (g16 & 1) + 4 * (i16 & 3)]);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
           const float ga = acc[ct][2 * k], gb = acc[ct][2 * k + 1];
-          const float xa = (float)xq[k >> 1][2 * (k & 1)], xb2 = (float)xq[k >> 1][2 * (k & 1) + 1];
-          u[0] = fmaf(ga, xa, fmaf(gb, xb2, u[0]));
+          const float xa = (float)xq[k >> 1][2 * (k & 1)], xb = (float)xq[k >> 1][2 * (k & 1) + 1];
+          u[0] = fmaf(ga, xa, fmaf(gb, xb, u[0]));
           g1[k] = ga + gb;
-          x1[k] = xa + xb2;
+          x1[k] = xa + xb;
           u[1] = fmaf(g1[k], x1[k], u[1]);
         }
-        float g3[4], x3[4];
+        float g2[4], x2[4], g3[2], x3[2];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-          const float g2 = g1[2 * k] + g1[2 * k + 1], x2 = x1[2 * k] + x1[2 * k + 1];
-          u[2] = fmaf(g2, x2, u[2]);
-          g3[k] = xor32_sum(g2);   // 8-row blocks: both half-waves hold the same sums
-          x3[k] = xor32_sum(x2);
-          u[3] = fmaf(0.5f * g3[k], x3[k], u[3]);
+          g2[k] = g1[2 * k] + g1[2 * k + 1];
+          x2[k] = x1[2 * k] + x1[2 * k + 1];
+          u[2] = fmaf(g2[k], x2[k], u[2]);
         }
-        const float g4a = g3[0] + g3[1], g4b = g3[2] + g3[3], x4a = x3[0] + x3[1], x4b = x3[2] + x3[3];
-        u[4] = fmaf(0.5f * g4a, x4a, fmaf(0.5f * g4b, x4b, u[4]));
-        const float g5 = g4a + g4b, x5 = x4a + x4b;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          g3[k] = g2[2 * k] + g2[2 * k + 1];
+          x3[k] = x2[2 * k] + x2[2 * k + 1];
+          u[3] = fmaf(g3[k], x3[k], u[3]);
+        }
+        const float g4 = g3[0] + g3[1], x4 = x3[0] + x3[1];
+        u[4] = fmaf(g4, x4, u[4]);
+        const float g5 = xor32_sum(g4), x5 = xor32_sum(x4);   // 32 rows: both half-waves hold the same sums
         u[5] = fmaf(0.5f * g5, x5, u[5]);
         mine[32 * ct + l32] = g5;   // (both half-waves write the same)
         mine[128 + 32 * ct + l32] = x5;
@@ -2142,53 +2284,81 @@ __global__ __launch_bounds__(kWideWaves * 64, 2) void wide_rows_kernel(
     }
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // (the loads of the next stage stay in flight)
     if (active) {
+      bf16_t *os = out + vo.slice_base(slice) + (int64_t)t0 * vo.sn;
+      RowBuf osb;
+      if (RAGGED) osb = row_buffer(os, vo.sn, valid);
+      u16x8 piece[CT][2];
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) {
-        const float g5 = mine[32 * ct + l32], o5 = other[32 * ct + l32];
+        const int ln = (int)opaque(lane), i16 = ln & 15, g16 = ln >> 4, c32 = ln & 31, hh = ln >> 5;
+        bf16_t *tl = reinterpret_cast<bf16_t *>(panel) + ct * 1024;
+        const float g5 = mine[32 * ct + c32], o5 = other[32 * ct + c32];
         const float g6 = g5 + o5;
         if ((wave & 1) == 0) {
-          u[6] = fmaf(0.5f * g6, mine[128 + 32 * ct + l32] + other[128 + 32 * ct + l32], u[6]);
-          if (DEEP) tile_gsum[((int64_t)slice * ((n + 63) / 64) + t0 / 64) * DH + 32 * ct + l32] = g6;
+          u[6] = fmaf(0.5f * g6, mine[128 + 32 * ct + c32] + other[128 + 32 * ct + c32], u[6]);
+          if (DEEP) tile_gsum[((int64_t)slice * ((n + 63) / 64) + t0 / 64) * DH + 32 * ct + c32] = g6;
         }
         const float T5 = fmaf(cf[5], g5, cf[6] * g6);
-        float g1[8], g2[4], g3[4];
+        float g1[8], g2[4], g3[2], o16[16];
 #pragma unroll
         for (int k = 0; k < 8; ++k) g1[k] = acc[ct][2 * k] + acc[ct][2 * k + 1];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          g2[k] = g1[2 * k] + g1[2 * k + 1];
-          g3[k] = xor32_sum(g2[k]);
+        for (int k = 0; k < 4; ++k) g2[k] = g1[2 * k] + g1[2 * k + 1];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) g3[k] = g2[2 * k] + g2[2 * k + 1];
+        const float T4 = fmaf(cf[4], g3[0] + g3[1], T5);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const float T1 = fmaf(cf[1], g1[k], fmaf(cf[2], g2[k >> 1], fmaf(cf[3], g3[k >> 2], T4)));
+#pragma unroll
+          for (int e = 0; e < 2; ++e) o16[2 * k + e] = fmaf(cf[0], acc[ct][2 * k + e], T1);
         }
         __builtin_amdgcn_wave_barrier();
+        // the tile transposed, [32 columns][32 rows]: 16-byte piece q of column c at slot q ^ (c / 2 % 4)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {   // 8-row block k (and this lane's 4-row part of it): one 8-byte column piece
-          const float T4 = fmaf(cf[4], g3[k & ~1] + g3[k | 1], T5), T2 = fmaf(cf[2], g2[k], fmaf(cf[3], g3[k], T4));
-          bf16x4 pk;
+        for (int q = 0; q < 2; ++q) {
+          bf16x8 pk;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) pk[e] = (__bf16)fmaf(cf[0], acc[ct][4 * k + e], fmaf(cf[1], g1[2 * k + (e >> 1)], T2));
-          *reinterpret_cast<bf16x4 *>(&tl[l32 * TS + 8 * k + 4 * h]) = pk;   // the tile transposed: [column][row]
+          for (int e = 0; e < 8; ++e) pk[e] = (__bf16)o16[8 * q + e];
+          *reinterpret_cast<bf16x8 *>(&tl[c32 * 32 + (((2 * hh + q) ^ (c32 >> 1 & 3)) << 3)]) = pk;
         }
         __builtin_amdgcn_wave_barrier();
-        // transposing reads hand back 8-byte row-major pieces: rows 16 (v % 2) + i16, columns 16 (v / 2) + 4 g16 .. + 3
-        bf16x4 piece[4];
+        // back as rows 16 v + i16, columns 8 g16 .. + 7
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-          piece[v] = lds_read_tr4(&tl[(16 * (v >> 1) + 4 * g16 + (i16 >> 2)) * TS + 16 * (v & 1) + 4 * (i16 & 3)]);
-        if (RAGGED) {
-          const uint32_t off = i16 * ((uint32_t)vo.sn * 2) + (32 * ct + 4 * g16) * 2;
-#pragma unroll
-          for (int v = 0; v < 4; ++v) buf_store8(osb, off + (v & 1) * 32 * (uint32_t)vo.sn + (v >> 1) * 32, piece[v]);
-        } else {
-          bf16_t *drow = os + (int64_t)i16 * vo.sn + 32 * ct + 4 * g16;
-#pragma unroll
-          for (int v = 0; v < 4; ++v) *reinterpret_cast<bf16x4 *>(drow + (v & 1) * 16 * vo.sn + (v >> 1) * 16) = piece[v];
+        for (int v = 0; v < 2; ++v) {
+          const int c = i16 >> 2, q = 2 * v + ((i16 & 3) >> 1), e = 4 * (i16 & 1);
+          const bf16x4 lo = lds_read_tr4(&tl[(8 * g16 + c) * 32 + ((q ^ (c >> 1)) << 3) + e]);
+          const bf16x4 hi = lds_read_tr4(&tl[(8 * g16 + 4 + c) * 32 + ((q ^ (2 + (c >> 1))) << 3) + e]);
+          piece[ct][v] = __builtin_bit_cast(u16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
         }
       }
+      // whole rows through the panel once more, so that a store covers 4 rows of 256 bytes
+      __builtin_amdgcn_wave_barrier();
+      {
+        const int ln = (int)opaque(lane), i16 = ln & 15, g16 = ln >> 4;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+          for (int v = 0; v < 2; ++v)
+            *reinterpret_cast<u16x8 *>(panel + (16 * v + i16) * 256 + (((4 * ct + g16) ^ i16) << 4)) = piece[ct][v];
+        __builtin_amdgcn_wave_barrier();
+        const uint32_t off = (uint32_t)(ln >> 4) * ((uint32_t)vo.sn * 2) + i16 * 16;
+        u16x8 row[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int r = 4 * j + (ln >> 4);
+          row[j] = *reinterpret_cast<const u16x8 *>(panel + r * 256 + ((i16 ^ (r & 15)) << 4));
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          if (RAGGED) buf_store16(osb, off + (uint32_t)j * ((uint32_t)vo.sn * 8), row[j]);
+          else *reinterpret_cast<u16x8 *>(reinterpret_cast<char *>(os + 4 * j * vo.sn) + off) = row[j];
+        }
+      }
+      if (more) turn_rows(t_next);
     }
-    if (rg + (int)gridDim.x < row_groups && in_range(t_next)) load_rows(t_next);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the last request: nothing reads it, but it must not outlive the workgroup
-  if (!GRAD) return;
   // With u_l = <dX_F, P_l X> the band gradients are dF_L = u_L and dF_{l-1} = u_{l-1} - u_l (l = 1..L).
   __syncthreads();
 #pragma unroll
@@ -2197,7 +2367,7 @@ __global__ __launch_bounds__(kWideWaves * 64, 2) void wide_rows_kernel(
     if (lane == 0) sw[l] = s;
   }
   __syncthreads();
-  if (tid <= L) {   // DEEP: see rows_kernel
+  if (tid <= L) {   // DEEP: see masked_rows_kernel
     float ul = 0.f, ul1 = 0.f;
     if (tid < kTileBands)
       for (int wv = 0; wv < kWideWaves; ++wv) {
@@ -2512,10 +2682,8 @@ FastWs fast_ws(const wersa_desc &c, const FastPlan &p, int bwd, float *base, flo
       w.gaddQ = b.take(tiles);
       w.gaddK = b.take(tiles);
     }
-    if (c.d == 64) {
-      w.bitsQ = reinterpret_cast<uint32_t *>(b.take(sl * ntiles * 2 * c.m));
-      w.bitsK = reinterpret_cast<uint32_t *>(b.take(sl * ntiles * 2 * c.m));
-    }
+    w.bitsQ = reinterpret_cast<uint32_t *>(b.take(sl * ntiles * 2 * c.m));
+    w.bitsK = reinterpret_cast<uint32_t *>(b.take(sl * ntiles * 2 * c.m));
     w.dF = b.take(sl * (c.L + 1));
     w.dlogit = b.take(sl * (c.L + 1));
     w.dqbar = b.take(sl * c.d);
@@ -2543,27 +2711,41 @@ size_t rows_smem_bytes(int mc) {   // of rows_kernel
 template <int MODE>
 hipError_t launch_wide_rows(const wersa_desc &c, const FastPlan &p, const _Float16 *xf, const bf16_t *x, const bf16_t *y,
                             const float *Dsaved, const float *arow, const FastWs &w, const bf16_t *omega, const bf16_t *Mx,
-                            const bf16_t *MT, const bf16_t *bb, bf16_t *out0, float *Dout, float *partF, hipStream_t st,
+                            const bf16_t *MT, const bf16_t *bb, bf16_t *out, float *Dout, float *partF, hipStream_t st,
                             const View *yview) {
   const int64_t side = ((c.flags & WERSA_FLAG_SEPARATE_OMEGA) && MODE >= 2) ? (int64_t)c.d * c.m : 0;
   const View tv{c.stride_b, c.stride_h, c.stride_n, c.H};
   const size_t smem = wide_smem_bytes(MODE, c.m);
-  const char *name = MODE == 0 ? "wersa_rows_fwd"
-                               : (MODE == 1 ? "wersa_rows_bwd_q" : (MODE == 2 ? "wersa_rows_bwd_k" : "wersa_rows_bwd_v"));
-  auto go = [&](auto kern) -> hipError_t {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-    WERSA_STAGE(name, st,
-                kern<<<dim3(p.rowsWgs, c.B * c.H), kWideWaves * 64, smem, st>>>(
-                    xf, x, tv, y, yview ? *yview : tv, Dsaved, arow, w.omT + side, omega + side, Mx, MT, bb, w.coef, c.eps, c.n, c.m,
-                    p.rowGroups, out0, tv, Dout, partF, c.L, MODE == 1 ? w.gsumQ : w.gsumK));
-    return hipSuccess;
+  const dim3 grid(p.rowsWgs, c.B * c.H);
+  auto allow = [&](auto kern) {
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   };
-  constexpr bool G = wide_grad(MODE);
-  const bool ln = MODE == 0 && (c.flags & WERSA_FLAG_LAYERNORM), ragged = c.n % 64 != 0, deep = G && c.L > kTileL;
-  if (ln) return ragged ? go(&wide_rows_kernel<MODE, MODE == 0, true, false>) : go(&wide_rows_kernel<MODE, MODE == 0, false, false>);
-  if (deep) return ragged ? go(&wide_rows_kernel<MODE, false, true, G>) : go(&wide_rows_kernel<MODE, false, false, G>);
-  return ragged ? go(&wide_rows_kernel<MODE, false, true, false>) : go(&wide_rows_kernel<MODE, false, false, false>);
+  const bool ragged = c.n % 64 != 0;
+  if constexpr (wide_grad(MODE)) {
+    auto go = [&](auto kern) -> hipError_t {
+      const hipError_t e = allow(kern);
+      if (e != hipSuccess) return e;
+      WERSA_STAGE(MODE == 1 ? "wersa_rows_bwd_q" : "wersa_rows_bwd_k", st,
+                  kern<<<grid, kWideWaves * 64, smem, st>>>(x, tv, y, yview ? *yview : tv, Dsaved, arow, MODE == 1 ? w.bitsQ : w.bitsK,
+                                                            omega + side, Mx, w.coef, c.n, c.m, p.rowGroups, out, tv, partF, c.L,
+                                                            MODE == 1 ? w.gsumQ : w.gsumK));
+      return hipSuccess;
+    };
+    if (c.L > kTileL) return ragged ? go(&wide_grad_kernel<MODE, true, true>) : go(&wide_grad_kernel<MODE, false, true>);
+    return ragged ? go(&wide_grad_kernel<MODE, true, false>) : go(&wide_grad_kernel<MODE, false, false>);
+  } else {
+    auto go = [&](auto kern) -> hipError_t {
+      const hipError_t e = allow(kern);
+      if (e != hipSuccess) return e;
+      WERSA_STAGE(MODE == 0 ? "wersa_rows_fwd" : "wersa_rows_bwd_v", st,
+                  kern<<<grid, kWideWaves * 64, smem, st>>>(xf, w.omT + side, MT, bb, w.coef, c.eps, c.n, c.m, p.rowGroups, out, tv, Dout,
+                                                            w.bitsK));
+      return hipSuccess;
+    };
+    if (MODE == 0 && (c.flags & WERSA_FLAG_LAYERNORM))
+      return ragged ? go(&wide_rows_kernel<MODE, MODE == 0, true>) : go(&wide_rows_kernel<MODE, MODE == 0, false>);
+    return ragged ? go(&wide_rows_kernel<MODE, false, true>) : go(&wide_rows_kernel<MODE, false, false>);
+  }
 }
 
 // Head dimension 64, MODE 0 and 3.
@@ -2647,7 +2829,7 @@ void launch_contract(const wersa_desc &c, const FastPlan &p, const _Float16 *xf,
   const int slices = c.B * c.H;
   dim3 grid(p.chunksC, c.m / p.MB, slices);
   const _Float16 *omT = w.omT + (((c.flags & WERSA_FLAG_SEPARATE_OMEGA) && key_side) ? (int64_t)c.d * c.m : 0);
-  // The backward's launch is the one on the query side; at head dimension 64 it leaves the ReLU's decisions for the gradient kernel.
+  // The backward's launch is the one on the query side: it leaves the ReLU's decisions for the gradient kernel.
   const bool bwd = !key_side;
   auto go = [&](auto kern) {
     WERSA_STAGE("wersa_phiT_contract", st,
@@ -2662,8 +2844,8 @@ void launch_contract(const wersa_desc &c, const FastPlan &p, const _Float16 *xf,
   auto form = [&](auto FW, auto NW, auto RAG, auto DEEP) {
     constexpr int F = FW.value, N = NW.value;
     if (!bwd) go(&phiT_contract_kernel<DH, F, false, RAG.value, DEEP.value, false, N>);
-    else if (orows) go(&phiT_contract_kernel<DH, F, true, RAG.value, DEEP.value, D64, N>);
-    else go(&phiT_contract_kernel<DH, F, false, RAG.value, DEEP.value, D64, N>);
+    else if (orows) go(&phiT_contract_kernel<DH, F, true, RAG.value, DEEP.value, true, N>);
+    else go(&phiT_contract_kernel<DH, F, false, RAG.value, DEEP.value, true, N>);
   };
   using Yes = std::true_type;
   using No = std::false_type;
