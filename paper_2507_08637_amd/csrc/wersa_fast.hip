@@ -204,14 +204,17 @@ __global__ __launch_bounds__(256) void qbar_partial_kernel(const bf16_t *q, View
     amax_part[(int64_t)slice * chunks + chunk] = fmaxf(fmaxf(amax_w[0], amax_w[1]), fmaxf(amax_w[2], amax_w[3]));
 }
 
-// X (bf16, strided) -> X_F (fp16, contiguous [slices][n][DH]); one 64-row tile per workgroup.
+// Q and K (bf16, strided; blockIdx.z) -> Q_F, K_F (fp16, contiguous [slices][n][DH]); one 64-row tile per workgroup.
 // Steps: coalesced 16-byte loads into LDS; one thread per (column, row segment) computes the
 // nested block sums (in registers up to the segment, through LDS above it) and the filtered
 // values; fp16 results go back to LDS and leave with coalesced 16-byte stores.
 // tile_add (L > 6, else nullptr): [slices][ceil(n / 64)][DH], the per-tile addend of the levels above 6.
 template <int DH>
-__global__ __launch_bounds__(256) void haar_stage_kernel(const bf16_t *x, View v, int n,
-                                                        const float *coef, const float *tile_add, _Float16 *xf) {
+__global__ __launch_bounds__(256) void haar_stage_kernel(const bf16_t *q, const bf16_t *k, View v, int n, const float *coef,
+                                                        const float *addQ, const float *addK, _Float16 *qf, _Float16 *kf) {
+  const bf16_t *x = blockIdx.z ? k : q;
+  const float *tile_add = blockIdx.z ? addK : addQ;
+  _Float16 *xf = blockIdx.z ? kf : qf;
   constexpr int SEGS = 256 / DH;   // row segments per column: 4 (DH=64) or 2 (DH=128)
   constexpr int RS = 64 / SEGS;    // rows per segment: 16 or 32
   constexpr int CPR = DH / 8;
@@ -2384,12 +2387,18 @@ __global__ __launch_bounds__(kWideWaves * 64, 2) void wide_grad_kernel(
 // accesses, four independent pieces per thread.
 // TILE: tile_add is given (the plain instance has none of its code), and blockIdx.z = 1 is dK with its own addends and
 // without the pooled term (a launch of its own before: 8 slices of 30000 rows, 17 + 14 us for the two, 26 us now).
+// Grid (chunks, slices + 1, 1 or 2); the last slice row is the gate's parameter gradients.
 template <int DH, bool TILE>
 __global__ __launch_bounds__(256) void add_pooled_kernel(bf16_t *dq, View v, const float *dqbar, int n,
                                                         float inv_n, const float *tile_add, bf16_t *dk,
-                                                        const float *tile_add_k) {
+                                                        const float *tile_add_k, GateBwdParams gp) {
   constexpr int CPR = DH / 8;
   const int slice = blockIdx.y;
+  if (blockIdx.y == gridDim.y - 1) {
+    if (blockIdx.z == 0)
+      for (int b = blockIdx.x; b < gp.blocks; b += gridDim.x) gate_bwd_params_body(gp, b);
+    return;
+  }
   if (TILE && blockIdx.z) {
     dq = dk;
     tile_add = tile_add_k;
@@ -2925,9 +2934,8 @@ wersa_status fast_forward_t(const wersa_desc &c, const bf16_t *q, const bf16_t *
   }
   if (DH != 64) {   // head dimension 64 runs stage A inside the kernels that consume X_F
     WERSA_STAGE("wersa_haar_stage", st,
-                haar_stage_kernel<DH><<<dim3((c.n + 63) / 64, slices), 256, 0, st>>>(q, tv, c.n, w.coef, deep ? w.addQ : nullptr, QF));
-    WERSA_STAGE("wersa_haar_stage", st,
-                haar_stage_kernel<DH><<<dim3((c.n + 63) / 64, slices), 256, 0, st>>>(k, tv, c.n, w.coef, deep ? w.addK : nullptr, KF));
+                haar_stage_kernel<DH><<<dim3((c.n + 63) / 64, slices, 2), 256, 0, st>>>(q, k, tv, c.n, w.coef, deep ? w.addQ : nullptr,
+                                                                                       deep ? w.addK : nullptr, QF, KF));
   }
   launch_contract<DH>(c, p, KF, k, v, tv, nullptr, nullptr, nullptr, true, w, S, z, w.Sx, w.ST, w.zb, st);
   if (launch_rows<DH, 0>(c, p, QF, q, nullptr, nullptr, nullptr, w, omega, nullptr, w.ST, w.zb, out, D,
@@ -2990,18 +2998,16 @@ wersa_status fast_backward_t(const wersa_desc &c, const bf16_t *q, const bf16_t 
               gate_bwd_slice_kernel<<<slices, kGateBwdThreads, 0, st>>>(w.partQ, w.partK, deep ? p.rowsWgs + DH / kCoarseCols : p.rowsWgs, c.L,
                                                            c.d, c.H, s, gate_w, scale_w, w.dF, w.dlogit, w.dqbar,
                                                            (c.flags & WERSA_FLAG_POOLED_GATE) ? 1 : 0, w.coef));
-  WERSA_STAGE("gate_bwd_params_kernel", st,
-              gate_bwd_params_kernel<<<gate_bwd_params_blocks(c.H, c.L, c.d), 256, 0, st>>>(w.dF, w.dlogit, s, qbar, w.dDpart, slices * (ln ? p.chunksL : p.chunksC),
-                                                        c.B, c.H, c.L, c.d, c.eps, w.scalars, dgate_w,
-                                                        dgate_b, dscale_w, dsigma));
+  const GateBwdParams gp{w.dF, w.dlogit, s, qbar, w.dDpart, slices * (ln ? p.chunksL : p.chunksC), c.B, c.H, c.L, c.d, c.eps, w.scalars,
+                         dgate_w, dgate_b, dscale_w, dsigma, gate_bwd_params_blocks(c.H, c.L, c.d)};
   const int64_t chunks = (int64_t)c.n * (DH / 8);
-  const dim3 agrid((unsigned)((chunks + 1023) / 1024), slices, deep ? 2 : 1);
+  const dim3 agrid((unsigned)((chunks + 1023) / 1024), slices + 1, deep ? 2 : 1);
   if (deep) {
     WERSA_STAGE("wersa_add_pooled", st,
-                (add_pooled_kernel<DH, true><<<agrid, 256, 0, st>>>(dq, tv, w.dqbar, c.n, 1.0f / (float)c.n, w.gaddQ, dk, w.gaddK)));
+                (add_pooled_kernel<DH, true><<<agrid, 256, 0, st>>>(dq, tv, w.dqbar, c.n, 1.0f / (float)c.n, w.gaddQ, dk, w.gaddK, gp)));
   } else {
     WERSA_STAGE("wersa_add_pooled", st,
-                (add_pooled_kernel<DH, false><<<agrid, 256, 0, st>>>(dq, tv, w.dqbar, c.n, 1.0f / (float)c.n, nullptr, nullptr, nullptr)));
+                (add_pooled_kernel<DH, false><<<agrid, 256, 0, st>>>(dq, tv, w.dqbar, c.n, 1.0f / (float)c.n, nullptr, nullptr, nullptr, gp)));
   }
   return hipGetLastError() == hipSuccess ? WERSA_OK : WERSA_ERR_LAUNCH;
 }

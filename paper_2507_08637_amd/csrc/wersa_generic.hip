@@ -745,9 +745,9 @@ wersa_status backward_t(const wersa_desc &c, const T *q, const T *k, const T *v,
   launch_band_dots<T>(c, k, tv, w.KF, w.partK, w.deepA, w.deepB, st);
   WERSA_STAGE("gate_bwd_slice_kernel", st, gate_bwd_slice_kernel<<<slices, kGateBwdThreads, 0, st>>>(w.partQ, w.partK, tiles, c.L, c.d, c.H, s, gate_w,
                                                scale_w, w.dF, w.dlogit, w.dqbar, (c.flags & WERSA_FLAG_POOLED_GATE) ? 1 : 0));
-  WERSA_STAGE("gate_bwd_params_kernel", st, gate_bwd_params_kernel<<<gate_bwd_params_blocks(c.H, c.L, c.d), 256, 0, st>>>(w.dF, w.dlogit, s, qbar, w.dDpart,
-                                            slices * colsum_chunks(c.n), c.B, c.H, c.L, c.d, c.eps,
-                                            w.scalars, dgate_w, dgate_b, dscale_w, dsigma));
+  const GateBwdParams gp{w.dF, w.dlogit, s, qbar, w.dDpart, slices * colsum_chunks(c.n), c.B, c.H, c.L, c.d, c.eps, w.scalars,
+                         dgate_w, dgate_b, dscale_w, dsigma, gate_bwd_params_blocks(c.H, c.L, c.d)};
+  WERSA_STAGE("gate_bwd_params_kernel", st, gate_bwd_params_kernel<<<gp.blocks, 256, 0, st>>>(gp));
   launch_filter<float, T>(c, w.QF, cv, dq, tv, F, w.dqbar, 1.0f / (float)c.n, w.deepA, st);
   launch_filter<float, T>(c, w.KF, cv, dk, tv, F, nullptr, 0.f, w.deepA, st);
   return hipGetLastError() == hipSuccess ? WERSA_OK : WERSA_ERR_LAUNCH;
