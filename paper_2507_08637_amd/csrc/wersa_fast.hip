@@ -90,19 +90,9 @@ __device__ __forceinline__ bf16x8 lds_perm8(const bf16_t *row, int base, int h) 
   return r;
 }
 
-// Sum over the 32 lanes of a half-wave, result in every lane: two quad exchanges and two row
-// rotations inside each group of 16 lanes (DPP), then one swap of the two groups (swizzle).
 template <int CTRL>
 __device__ __forceinline__ float dpp_move(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
-}
-__device__ __forceinline__ float half_wave_sum(float v) {
-  v += dpp_move<0xB1>(v);    // quad_perm [1,0,3,2]
-  v += dpp_move<0x4E>(v);    // quad_perm [2,3,0,1]
-  v += dpp_move<0x124>(v);   // row_ror 4
-  v += dpp_move<0x128>(v);   // row_ror 8
-  v += __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), 0x401F));   // lane ^ 16
-  return v;
 }
 
 // ------------------------------------------------------------------------------------
@@ -1000,16 +990,10 @@ __device__ __forceinline__ RowBuf row_buffer(const T *rows, int64_t sn, int vali
 template <typename V> __device__ __forceinline__ V buf_load16(RowBuf r, uint32_t off) {
   return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
 }
-template <typename V> __device__ __forceinline__ V buf_load8(RowBuf r, uint32_t off) {
-  return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
-}
 __device__ __forceinline__ float buf_load4(RowBuf r, uint32_t off) {
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
 }
 typedef unsigned int u32x2v __attribute__((ext_vector_type(2)));
-template <typename V> __device__ __forceinline__ void buf_store8(RowBuf r, uint32_t off, V v) {
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2v, v), r, off, 0, 0);
-}
 typedef unsigned int u32x4v __attribute__((ext_vector_type(4)));
 template <typename V> __device__ __forceinline__ void buf_store16(RowBuf r, uint32_t off, V v) {
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4v, v), r, off, 0, 0);
@@ -1053,7 +1037,6 @@ __global__ __launch_bounds__(kWavesApply * 64, 2) void rows_kernel(
   bf16_t *s_bb = nullptr, *s_MT = reinterpret_cast<bf16_t *>(p);                       // [DH][BS]
   p += (size_t)DH * BS * 2;
   if (MODE == 0) { s_bb = reinterpret_cast<bf16_t *>(p); p += (size_t)mc * 2; }        // [mc]
-  float *s_wave = reinterpret_cast<float *>(p); p += (size_t)NW * 64 * 4;              // [waves][64]
   constexpr int TS = 36;                // row stride (elements) of the per-wave 64 x 32 epilogue tile
   bf16_t *s_tile = reinterpret_cast<bf16_t *>(p);            // [waves][CT][64][TS]
   p += (size_t)NW * CT * 64 * TS * 2;
@@ -1171,6 +1154,7 @@ __global__ __launch_bounds__(kWavesApply * 64, 2) void rows_kernel(
   // wave's epilogue run under the other's matrix work; an explicit start delay for the second wave
   // group, used before the priorities were there, no longer gains anything.)
 
+  const int frow = swap23(l32);   // operand rows of features and of columns (see swap23)
   for (int rg = blockIdx.x; rg < row_groups; rg += gridDim.x) {
     const int t0 = (rg * NW + wave) * 64;
     const bool active = t0 < n;
@@ -1226,7 +1210,9 @@ __global__ __launch_bounds__(kWavesApply * 64, 2) void rows_kernel(
           }
       }
     }
-    f32x16 acc0[2][CT];   // N or dV: rows on registers, columns on lanes
+    // N or dV, rows on lanes: register i of half-wave h is column 32 ct + 16 (i / 8) + 8 h + i % 8 of row 32 ti + l32, so that the row's
+    // scale is one value per lane and a lane's registers are two 16-byte pieces of its row.
+    f32x16 acc0[2][CT];
     WeightedSum dacc[2];   // D partial of this lane's row (MODE 0)
 #pragma unroll
     for (int ti = 0; ti < 2; ++ti)
@@ -1254,7 +1240,7 @@ __global__ __launch_bounds__(kWavesApply * 64, 2) void rows_kernel(
         f16x8 oa[KS];     // Omega^T rows of this feature tile: A operand of the projection
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
-          oa[ks] = *reinterpret_cast<const f16x8 *>(&s_omT[(32 * rt + swap23(l32)) * AS + 16 * ks + 8 * h]);
+          oa[ks] = *reinterpret_cast<const f16x8 *>(&s_omT[(32 * rt + frow) * AS + 16 * ks + 8 * h]);
 #pragma unroll
         for (int ti = 0; ti < 2; ++ti) {
           f32x16 R = zero16();
@@ -1267,7 +1253,7 @@ __global__ __launch_bounds__(kWavesApply * 64, 2) void rows_kernel(
             if (MODE == 0) dacc[ti].add(pa[a], *reinterpret_cast<const bf16x8 *>(&s_bb[32 * rt + 16 * a + 8 * h]));
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct)
-              acc0[ti][ct] = mfma_bf16(pa[a], *reinterpret_cast<const bf16x8 *>(&s_MT[(32 * ct + l32) * BS + 32 * rt + 16 * a + 8 * h]), acc0[ti][ct]);
+              acc0[ti][ct] = mfma_bf16(*reinterpret_cast<const bf16x8 *>(&s_MT[(32 * ct + frow) * BS + 32 * rt + 16 * a + 8 * h]), pa[a], acc0[ti][ct]);
           }
           if (MODE == 3) {
             const uint32_t b = positive_bits(pa);
@@ -1288,111 +1274,64 @@ __global__ __launch_bounds__(kWavesApply * 64, 2) void rows_kernel(
       const int t_next = ((rg + gridDim.x) * NW + wave) * 64;
       load_rows((rg + (int)gridDim.x < row_groups && t_next < n) ? t_next : t0);
     }
-    bf16_t *tl = panels;
-    const int prow = lane >> 3, pcol = (lane & 7) * 4;   // this lane's 8-byte piece: rows prow + 8 j
     bf16_t *os = out + vo.slice_base(slice) + (int64_t)t0 * vo.sn;
-    const int64_t osn = vo.sn;   // row stride of the output rows
     float *Dp = MODE == 0 ? Dout + (int64_t)slice * n + t0 : nullptr;
     RowBuf osb, Dpb;
     if (RAGGED) {
-      osb = row_buffer(os, osn, valid);
+      osb = row_buffer(os, vo.sn, valid);
       if (MODE == 0) Dpb = row_buffer(Dp, 1, valid);
     }
-
-    if (MODE == 0 && LN) {
-      // Output stage of Algorithm 1: O_t = (N_t - mean N_t) / sqrt(var N_t + eps), N = c * acc.
-      // A row lives on one register index across the 32 lanes of a half-wave (and the CT column
-      // tiles): mean first, then the centred second moment.  1 / sqrt(var + eps) goes to D.
-      float *dl = s_wave + wave * 64;
+    const int ln = (int)opaque(lane), row32 = ln & 31, hh = ln >> 5;
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int ti = 0; ti < 2; ++ti)
+    for (int ti = 0; ti < 2; ++ti) {
+      float scale = cscale, Dt = 0.f;
+      if (MODE == 0 && LN) {
+        // Output stage of Algorithm 1: O_t = (N_t - mean N_t) / sqrt(var N_t + eps), N = c * acc: mean first, then the centred
+        // second moment (the other half of the row is in the other half-wave).  1 / sqrt(var + eps) goes to D.
+        float v = 0.f, q = 0.f;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          float v = 0.f;
+        for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-          for (int ct = 0; ct < CT; ++ct) v += acc0[ti][ct][i];
-          const float mu = half_wave_sum(v) * (1.0f / (float)DH);
-          float q = 0.f;
+          for (int i = 0; i < 16; ++i) v += acc0[ti][ct][i];
+        const float mu = xor32_sum(v) * (1.0f / (float)DH);
 #pragma unroll
-          for (int ct = 0; ct < CT; ++ct) {
+        for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
             const float e = (acc0[ti][ct][i] - mu) * cscale;
             acc0[ti][ct][i] = e;
             q = fmaf(e, e, q);
           }
-          const float rstd = 1.0f / sqrtf(half_wave_sum(q) * (1.0f / (float)DH) + eps);
-#pragma unroll
-          for (int ct = 0; ct < CT; ++ct) acc0[ti][ct][i] *= rstd;
-          if (l32 == 0) dl[32 * ti + acc_row(i, h)] = rstd;
-        }
-      __builtin_amdgcn_wave_barrier();
-      if (RAGGED) buf_store4(Dpb, 4 * lane, dl[lane]);
-      else Dp[lane] = dl[lane];
-    } else if (MODE == 0) {   // normaliser D_t = c * sum_r relu(R) z + eps, row scale c / D_t
-      float *dl = s_wave + wave * 64;
-#pragma unroll
-      for (int ti = 0; ti < 2; ++ti) {
-        const float dsum = xor32_sum(dacc[ti].own(lane));
-        const float Dt = fmaf(cscale, dsum, eps);
-        // both half-waves hold the same sum and write the same values: no branch around the store
-        dl[32 * ti + l32] = cscale * __builtin_amdgcn_rcpf(Dt);
-        if (RAGGED) buf_store4(Dpb, 4 * (32 * ti + l32), Dt);
-        else Dp[32 * ti + l32] = Dt;
+        scale = Dt = 1.0f / sqrtf(xor32_sum(q) * (1.0f / (float)DH) + eps);
+      } else if (MODE == 0) {   // normaliser D_t = c * sum_r relu(R) z + eps, row scale c / D_t
+        Dt = fmaf(cscale, xor32_sum(dacc[ti].own(ln)), eps);
+        scale = cscale * __builtin_amdgcn_rcpf(Dt);
       }
-    }
-    // Row scale of the accumulators (rows on registers): c / D_t (MODE 0 from the per-wave LDS
-    // array written just above; LDS operations of one wave stay in order), or c.
-    __builtin_amdgcn_wave_barrier();
-    if (!(MODE == 0 && LN))
-#pragma unroll
-    for (int ti = 0; ti < 2; ++ti) {
-      float sc[16];
-      if (MODE == 0) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x4 s4 = *reinterpret_cast<const f32x4 *>(&s_wave[wave * 64 + 32 * ti + 8 * g + 4 * h]);
-#pragma unroll
-          for (int q = 0; q < 4; ++q) sc[4 * g + q] = s4[q];
-        }
-      } else {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) sc[i] = cscale;
+      if (MODE == 0) {   // (both half-waves write the same values: no branch around the store)
+        if (RAGGED) buf_store4(Dpb, 4 * (32 * ti + row32), Dt);
+        else Dp[32 * ti + row32] = Dt;
       }
+      // bf16 through the wave's panel, [64 rows][64]: 16-byte piece c of row r at slot c ^ (r % 8)
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc0[ti][ct][i] *= sc[i];
-    }
-
-    // O (MODE 0) or dV (MODE 3): bf16 through the wave's LDS tile, 8-byte row-major stores
+        for (int a = 0; a < 2; ++a) {
+          bf16x8 pk;
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-          tl[(32 * ti + acc_row(i, h)) * TS + l32] = cvt_bf16(acc0[ti][ct][i]);
-      __builtin_amdgcn_wave_barrier();
-      bf16x4 piece[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        piece[j] = *reinterpret_cast<const bf16x4 *>(&tl[(prow + 8 * j) * TS + pcol]);
-      if (RAGGED) {
-        const uint32_t ln = opaque(lane);
-        uint32_t off = (ln >> 3) * ((uint32_t)osn * 2) + (32 * ct + (ln & 7) * 4) * 2;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          buf_store8(osb, off, piece[j]);
-          off += 16 * (uint32_t)osn;
+          for (int e = 0; e < 8; ++e) pk[e] = (__bf16)(acc0[ti][ct][8 * a + e] * scale);
+          *reinterpret_cast<bf16x8 *>(panels + (32 * ti + row32) * 64 + (((4 * ct + 2 * a + hh) ^ (row32 & 7)) << 3)) = pk;
         }
-        continue;
-      }
-      bf16_t *orow = os + (int64_t)prow * osn + 32 * ct + pcol;
+    }
+    __builtin_amdgcn_wave_barrier();
+    u16x8 piece[8];   // row 8 j + lane / 8, columns 8 (lane % 8) ..
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        *reinterpret_cast<bf16x4 *>(orow) = piece[j];
-        orow += 8 * osn;
-      }
+    for (int j = 0; j < 8; ++j) piece[j] = *reinterpret_cast<const u16x8 *>(panels + (8 * j + (ln >> 3)) * 64 + (((ln & 7) ^ (ln >> 3)) << 3));
+    const uint32_t off = (uint32_t)(ln >> 3) * ((uint32_t)vo.sn * 2) + (ln & 7) * 16;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if (RAGGED) buf_store16(osb, off + (uint32_t)j * ((uint32_t)vo.sn * 16), piece[j]);
+      else *reinterpret_cast<u16x8 *>(reinterpret_cast<char *>(os + 8 * j * vo.sn) + off) = piece[j];
     }
     put_rows();
   }
@@ -1856,7 +1795,7 @@ constexpr bool wide_grad(int MODE) { return MODE == 1 || MODE == 2; }
 constexpr int wide_tile_bytes(int MODE) { return (wide_grad(MODE) ? 17 : 16) * 1024; }
 constexpr int kWidePanel = 8192;   // bytes of a wave's panel
 inline size_t wide_smem_bytes(int MODE, int m) {
-  return 2 * kWideTiles * wide_tile_bytes(MODE) + kWideWaves * (kWidePanel + 32 * 4 + (wide_grad(MODE) ? 2 * 128 * 4 : 0)) + (MODE == 0 ? m * 2 : 0);
+  return 2 * kWideTiles * wide_tile_bytes(MODE) + kWideWaves * (kWidePanel + (wide_grad(MODE) ? 32 * 4 + 2 * 128 * 4 : 0)) + (MODE == 0 ? m * 2 : 0);
 }
 // A panel of 32 rows of 256 bytes: 16-byte piece c of row r at slot c ^ wide_key(r).  Rows in the order of a lane's number (natural, or as
 // lane_row gives them) meet all eight keys in eight lanes.
@@ -1897,7 +1836,7 @@ __global__ __launch_bounds__(kWideWaves * 64, 2) void wide_rows_kernel(
     const _Float16 *xf, const _Float16 *omT, const bf16_t *MT, const bf16_t *bb, const float *coef, float eps,
     int n, int m, int row_groups, bf16_t *out, View vo, float *Dout, uint32_t *bits) {
   static_assert(!wide_grad(MODE), "the gradient modes have wide_grad_kernel");
-  constexpr int DH = 128, KS = 8, CT = 4, TS = 36, TB = wide_tile_bytes(MODE), OO = 8192;   // a feature tile and its second array
+  constexpr int DH = 128, KS = 8, CT = 4, TB = wide_tile_bytes(MODE), OO = 8192;   // a feature tile and its second array
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   typedef __attribute__((address_space(3))) unsigned char lds_byte;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte *)smem_raw;
@@ -1905,8 +1844,7 @@ __global__ __launch_bounds__(kWideWaves * 64, 2) void wide_rows_kernel(
   const int slice = blockIdx.y, tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   unsigned char *panel = p + wave * kWidePanel;
-  float *sw = reinterpret_cast<float *>(p + kWideWaves * kWidePanel) + wave * 32;
-  bf16_t *s_bb = reinterpret_cast<bf16_t *>(p + kWideWaves * (kWidePanel + 128));   // MODE 0: z
+  bf16_t *s_bb = reinterpret_cast<bf16_t *>(p + kWideWaves * kWidePanel);   // MODE 0: z
   const float cscale = coef[slice * kCoefStride + kCoefCscale];
 
   // ---- staging: wave w moves pieces 4 w .. 4 w + 3 (rows) or 16 w .. 16 w + 15 (columns) of every array
@@ -1947,14 +1885,13 @@ __global__ __launch_bounds__(kWideWaves * 64, 2) void wide_rows_kernel(
       turn_rows();
     }
   }
-  const int prow = swap23(l32), o_row = prow * 256 + ((h ^ (prow & 15)) << 4), o_col0 = l32 * 64 + ((h ^ ((l32 >> 2) & 3)) << 4);
-  bf16_t *tl = reinterpret_cast<bf16_t *>(panel);
+  const int prow = swap23(l32), o_row = prow * 256 + ((h ^ (prow & 15)) << 4), o_col0 = prow * 64 + ((h ^ ((prow >> 2) & 3)) << 4);
 
   for (int rg = blockIdx.x; rg < row_groups; rg += gridDim.x) {
     const int t0 = rg * kWideRows + wave * 32;
     const bool active = in_range(t0);
     const int valid = RAGGED ? n - t0 : 32;
-    f32x16 acc[CT];
+    f32x16 acc[CT];   // rows on lanes, as in rows_kernel
     float dacc = 0.f;
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) acc[ct] = zero16();
@@ -1981,7 +1918,7 @@ __global__ __launch_bounds__(kWideWaves * 64, 2) void wide_rows_kernel(
             dacc = dot8_bf16(pa[a], *reinterpret_cast<const bf16x8 *>(s_bb + (s * kWideTiles + ft) * 32 + 16 * a + 8 * h), dacc);
 #pragma unroll
           for (int ct = 0; ct < CT; ++ct)
-            acc[ct] = mfma_bf16(pa[a], *reinterpret_cast<const bf16x8 *>(st + OO + ct * 2048 + (o_col0 ^ (32 * a))), acc[ct]);
+            acc[ct] = mfma_bf16(*reinterpret_cast<const bf16x8 *>(st + OO + ct * 2048 + (o_col0 ^ (32 * a))), pa[a], acc[ct]);
         }
         if (MODE == 3) word |= positive_bits(pa) << 8 * ft;
       }
@@ -2005,69 +1942,52 @@ __global__ __launch_bounds__(kWideWaves * 64, 2) void wide_rows_kernel(
     bf16_t *os = out + vo.slice_base(slice) + (int64_t)t0 * vo.sn;
     RowBuf osb;
     if (RAGGED) osb = row_buffer(os, vo.sn, valid);
+    const int ln = (int)opaque(lane), row32 = ln & 31, hh = ln >> 5;
+    float scale = cscale, Dt = 0.f;
     if (MODE == 0 && LN) {   // O_t = (N_t - mean N_t) / sqrt(var N_t + eps), N = c * acc; 1 / sqrt(var + eps) goes to D
+      float v = 0.f, q = 0.f;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const float mu = half_wave_sum((acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i])) * (1.0f / (float)DH);
-        float q = 0.f;
+      for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
+        for (int i = 0; i < 16; ++i) v += acc[ct][i];
+      const float mu = xor32_sum(v) * (1.0f / (float)DH);
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
           const float e = (acc[ct][i] - mu) * cscale;
           acc[ct][i] = e;
           q = fmaf(e, e, q);
         }
-        const float rstd = 1.0f / sqrtf(half_wave_sum(q) * (1.0f / (float)DH) + eps);
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) acc[ct][i] *= rstd;
-        if (l32 == 0) sw[acc_row(i, h)] = rstd;
-      }
-      __builtin_amdgcn_wave_barrier();
-      if (l32 < valid) Dout[(int64_t)slice * n + t0 + l32] = sw[l32];
+      scale = Dt = 1.0f / sqrtf(xor32_sum(q) * (1.0f / (float)DH) + eps);
     } else if (MODE == 0) {   // D_t = c * sum_r relu(R) z + eps, row scale c / D_t
-      const float Dt = fmaf(cscale, xor32_sum(dacc), eps);
-      sw[l32] = cscale * __builtin_amdgcn_rcpf(Dt);   // (both half-waves hold and write the same)
-      if (l32 < valid) Dout[(int64_t)slice * n + t0 + l32] = Dt;
+      Dt = fmaf(cscale, xor32_sum(dacc), eps);
+      scale = cscale * __builtin_amdgcn_rcpf(Dt);
     }
+    if (MODE == 0 && row32 < valid) Dout[(int64_t)slice * n + t0 + row32] = Dt;   // (both half-waves hold and write the same)
+    // bf16 through the wave's panel, [32 rows][128]: 16-byte piece c of row r at slot c ^ (r % 16); a store covers 4 rows of 256 bytes
     __builtin_amdgcn_wave_barrier();
-    if (!(MODE == 0 && LN)) {
-      float sc[16];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        f32x4 s4 = {cscale, cscale, cscale, cscale};
-        if (MODE == 0) s4 = *reinterpret_cast<const f32x4 *>(&sw[8 * g + 4 * h]);
+    for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) sc[4 * g + q] = s4[q];
+      for (int a = 0; a < 2; ++a) {
+        bf16x8 pk;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pk[e] = (__bf16)(acc[ct][8 * a + e] * scale);
+        *reinterpret_cast<bf16x8 *>(panel + row32 * 256 + (((4 * ct + 2 * a + hh) ^ (row32 & 15)) << 4)) = pk;
       }
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t off = (uint32_t)(ln >> 4) * ((uint32_t)vo.sn * 2) + (ln & 15) * 16;
+    u16x8 piece[8];
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[ct][i] *= sc[i];
+    for (int j = 0; j < 8; ++j) {
+      const int r = 4 * j + (ln >> 4);
+      piece[j] = *reinterpret_cast<const u16x8 *>(panel + r * 256 + (((ln & 15) ^ (r & 15)) << 4));
     }
-    // bf16 through the wave's panel, 8-byte row-major stores
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (int i = 0; i < 16; ++i) tl[acc_row(i, h) * TS + l32] = cvt_bf16(acc[ct][i]);
-      __builtin_amdgcn_wave_barrier();
-      bf16x4 piece[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) piece[j] = *reinterpret_cast<const bf16x4 *>(&tl[((lane >> 3) + 8 * j) * TS + (lane & 7) * 4]);
-      if (RAGGED) {
-        uint32_t off = (lane >> 3) * ((uint32_t)vo.sn * 2) + (32 * ct + (lane & 7) * 4) * 2;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          buf_store8(osb, off, piece[j]);
-          off += 16 * (uint32_t)vo.sn;
-        }
-      } else {
-        bf16_t *orow = os + (int64_t)(lane >> 3) * vo.sn + 32 * ct + (lane & 7) * 4;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          *reinterpret_cast<bf16x4 *>(orow) = piece[j];
-          orow += 8 * vo.sn;
-        }
-      }
+    for (int j = 0; j < 8; ++j) {
+      if (RAGGED) buf_store16(osb, off + (uint32_t)j * ((uint32_t)vo.sn * 8), piece[j]);
+      else *reinterpret_cast<u16x8 *>(reinterpret_cast<char *>(os + 4 * j * vo.sn) + off) = piece[j];
     }
     if (more) turn_rows();
   }
@@ -2711,7 +2631,6 @@ size_t rows_smem_bytes(int mc) {   // of rows_kernel
   constexpr int DH = 64, NW = kWavesApply;
   size_t s = (size_t)mc * (DH + 8) * 2 + (size_t)DH * (mc + 8) * 2;
   if (MODE == 0) s += (size_t)mc * 2;
-  s += NW * 64 * 4;
   s += (size_t)NW * (DH / 32) * 64 * 36 * 2 + 2 * 512 * 2;   // X panels per wave and the filter table
   return s;
 }
