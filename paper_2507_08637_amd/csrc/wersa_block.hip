@@ -36,6 +36,12 @@ struct GemmJob {
   int count, batch;
 };
 
+// A value the compiler cannot follow: what is derived from it is computed where it is used, not kept in registers.
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
 __device__ __forceinline__ bf16_t to_bf16(float f) { return __builtin_bit_cast(bf16_t, (__bf16)f); }
 
 // 16 bytes per lane from base + voff (bytes) to LDS at lds (bytes, wave-uniform) + 16 * lane, without passing
@@ -59,9 +65,19 @@ __device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t voff, const bf1
 // reads 64 B/clk and writes 32 of about 128; with two waves of 128 x 64 per SIMD (the form before) it was 96 + 32,
 // the whole LDS bandwidth.  One wave per SIMD hides nothing by itself, so nothing may stall: operands of the next
 // 16 k are read between the matrix instructions of the current ones, across the stage boundary too (a stage is
-// known to have landed one step before it is needed), and global loads have two steps (2048 cycles) to land.
-// Measured (131072 tokens, hidden 2048): NN, which ran as NT on transposed copies, and NT 0.97 - 1.01 -> 1.18 and
-// 1.21 PFLOP/s, TN 0.96 - 1.0 -> 1.31; 1.9 is what a bare loop of the matrix instruction sustains.
+// known to have landed one step before it is needed), and global loads have two steps (2048 cycles) to land.  Reads and
+// requests are spread over the 16 instructions of a half, one or the other after most of them: all reads in the first half
+// of them and all requests in the second met the peak rates of LDS and of the load path.  Beyond that it is power: per tile of
+// 256 x 256 x 2048 (65.5 thousand cycles of matrix instructions) NN takes 91.1 thousand cycles at 1665 MHz, and took 95.4 at
+// 1720 before, TN 8 % fewer at a clock 5 % lower; a fifth stage, or one workgroup per tile, is slower.
+//
+// A workgroup of WT = 128 takes several tiles, one after the other (one per compute unit in flight).  The stages of its tiles are one
+// sequence, so the first stages of the next tile are on their way while the last products and the stores of this one are made;
+// the tile leaves through the stage that was computed on last.  bf16 output without column sums: the operands of the matrix
+// instruction are exchanged, and B's rows or columns taken with bits 2 and 3 of their number exchanged, so that a lane holds 16-byte
+// pieces of its own row of C (32 LDS writes per wave and tile of 128 x 128 instead of 256 two-byte ones).
+// Measured (131072 tokens, hidden 2048, us per product): NN 877 -> 813 (905 with column sums), NT 874 -> 826, TN 831 -> 786;
+// block training step 15344 -> 14980.  1.1 PFLOP takes 580 us at the 1.9 PFLOP/s that a bare loop of the instruction sustains.
 //
 // Logical tiles are dealt to the eight XCDs in contiguous runs (workgroup w runs on XCD w % 8); a run goes down
 // kGroupM row panels before it takes the next column panel, so that the 32 workgroups of an XCD at a time share
@@ -73,7 +89,7 @@ __device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t voff, const bf1
 // |accumulator| of 128 rows x 64 columns; the core derives the fp16 operand scale of a (batch, head) slice from them.
 constexpr int kGroupM = 4;
 
-template <int WT, bool TA, bool TB, bool OUT_F32, bool DMA>
+template <int WT, bool TA, bool TB, bool OUT_F32, bool DMA, bool COLSUM>
 __global__ __launch_bounds__(64 * kGemmWaves, WT == 128 ? 1 : 2) void gemm_bf16_kernel(
     GemmJob job, int lda, int ldb, int ldc, int M, int N, int K, int k_chunk, int splits, float *colsum, float *colmax) {
   constexpr int T = 2 * WT;              // workgroup tile, rows and columns
@@ -82,22 +98,25 @@ __global__ __launch_bounds__(64 * kGemmWaves, WT == 128 ? 1 : 2) void gemm_bf16_
   constexpr int SB = 2 * OPB;            // bytes of a stage
   constexpr int G = OPB / 1024 / kGemmWaves;   // 1 KB loads per wave, operand and stage
   constexpr int RB = T * 2;              // bytes of a row of a [k][row] stage
+  constexpr bool ROWS = !OUT_F32 && !COLSUM;   // accumulators with rows of C on lanes
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   typedef __attribute__((address_space(3))) unsigned char lds_byte;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte *)smem_raw;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31,
             h = lane >> 5;
   const int tm = M / T, tn = N / T * job.batch, tiles = tm * tn, total = tiles * splits;
-  const int per = (total + 7) / 8;
-  const int lt = (blockIdx.x % 8) * per + blockIdx.x / 8;
-  if ((int)(blockIdx.x / 8) >= per || lt >= total) return;
-  const int split = lt / tiles, tile = lt % tiles;
-  const int grp = tile / (kGroupM * tn), rest = tile - grp * kGroupM * tn, rows = min(kGroupM, tm - grp * kGroupM);
-  const int nb = rest / rows, mt = grp * kGroupM + rest % rows;
-  const int which = nb / (N / T);        // product of the batch
-  const int m0 = mt * T, n0 = (nb - which * (N / T)) * T;
-  const int k_begin = split * k_chunk, k_end = min(K, k_begin + k_chunk);
-  const int steps = (k_end - k_begin) / BK * job.count;
+  const int per = (total + 7) / 8, end = min(per, total - (int)(blockIdx.x % 8) * per);   // of this XCD's run of tiles
+  struct Place {
+    int m0, n0, which, split, k_begin, k_end;   // which: product of the batch
+  };
+  auto place = [&](int li) {   // tile li of the run
+    const int lt = (blockIdx.x % 8) * per + li, split = lt / tiles, tile = lt % tiles;
+    const int grp = tile / (kGroupM * tn), rest = tile - grp * kGroupM * tn, rows = min(kGroupM, tm - grp * kGroupM);
+    const int nb = rest / rows, mt = grp * kGroupM + rest % rows, which = nb / (N / T);
+    return Place{mt * T, (nb - which * (N / T)) * T, which, split, split * k_chunk, min(K, split * k_chunk + k_chunk)};
+  };
+  const int stride = gridDim.x / 8;
+  if ((int)(blockIdx.x / 8) >= end) return;
   const int wm = (wave >> 1) * WT, wn = (wave & 1) * WT;
 
   // Source offsets of this lane's piece in the wave's G loads of each operand (bytes from the stage's corner).
@@ -117,23 +136,27 @@ __global__ __launch_bounds__(64 * kGemmWaves, WT == 128 ? 1 : 2) void gemm_bf16_
     va[u] = off(TA, lda);
     vb[u] = off(TB, ldb);
   }
-  int src = which, k_next = k_begin;     // the next stage to request
+  // The next stage to request; requests run ahead of the products, over the end of a tile into the next one.
+  int li_next = blockIdx.x / 8;
+  Place rq = place(li_next);
+  int src = rq.which, left = (rq.k_end - rq.k_begin) / BK;   // stages of this source to request, this one counted
   auto corner = [&](const bf16_t *p, bool kmajor, int ld, int o0) {
-    return p + (kmajor ? (int64_t)k_next * ld + o0 : (int64_t)o0 * ld + k_next);
+    return p + (kmajor ? (int64_t)rq.k_begin * ld + o0 : (int64_t)o0 * ld + rq.k_begin);
   };
-  const bf16_t *pa = corner(job.a[src], TA, lda, m0), *pb = corner(job.b[src], TB, ldb, n0);
+  const bf16_t *pa = corner(job.a[src], TA, lda, rq.m0), *pb = corner(job.b[src], TB, ldb, rq.n0);
   const int64_t da = TA ? (int64_t)BK * lda : BK, db = TB ? (int64_t)BK * ldb : BK;
-  auto next_source = [&]() {   // after the last stage the same one is requested again, and never read
-    if (k_next + BK < k_end) {
-      k_next += BK;
-      pa += da;
-      pb += db;
-    } else if (src - which + 1 < job.count) {
+  auto next_source = [&]() {   // pa and pb already point to the next stage of this source
+    if (__builtin_expect(--left > 0, 1)) return;
+    if (src - rq.which + 1 < job.count) {
       ++src;
-      k_next = k_begin;
-      pa = corner(job.a[src], TA, lda, m0);
-      pb = corner(job.b[src], TB, ldb, n0);
-    }
+    } else if (li_next + stride < end) {
+      li_next += stride;
+      rq = place(li_next);
+      src = rq.which;
+    }   // after the last stage of the last tile the last source is requested again, and never read
+    left = (rq.k_end - rq.k_begin) / BK;
+    pa = corner(job.a[src], TA, lda, rq.m0);
+    pb = corner(job.b[src], TB, ldb, rq.n0);
   };
   typedef u16x8 u16x8_any __attribute__((aligned(2)));
   auto request = [&](int stage, int u, bool is_b) {
@@ -154,16 +177,21 @@ __global__ __launch_bounds__(64 * kGemmWaves, WT == 128 ? 1 : 2) void gemm_bf16_
   typedef __attribute__((address_space(3))) s16x4 *lds_s16x4_ptr;
   typedef __attribute__((address_space(3))) bf16x8 *lds_bf16x8_ptr;
   const int i16 = lane & 15, g16 = (lane >> 4) & 1;
-  auto lane_off = [&](bool kmajor, int w0, int i) -> uint32_t {   // of operand i at ks = 0
-    if (!kmajor) return (uint32_t)((w0 + 32 * i + l32) * 64 + (h ^ ((l32 >> 2) & 3)) * 16);
-    const int piece = (w0 / 8 + 4 * i + 2 * g16 + ((i16 & 3) >> 1)) ^ ((i16 >> 2) << 2);
-    return (uint32_t)((8 * h + (i16 >> 2)) * RB + piece * 16 + (i16 & 1) * 8);
+  // swap: lane l32 takes row or column l32 with bits 2 and 3 exchanged.
+  auto lane_off = [&](bool kmajor, int w0, int i, bool swap) -> uint32_t {   // of operand i at ks = 0
+    if (!kmajor) {
+      const int r = swap ? (l32 & 19) | (l32 & 4) << 1 | (l32 & 8) >> 1 : l32;
+      return (uint32_t)((w0 + 32 * i + r) * 64 + (h ^ ((r >> 2) & 3)) * 16);
+    }
+    const int four = swap ? (i16 & 1) << 1 | (i16 & 2) >> 1 : i16 & 3;
+    const int piece = (w0 / 8 + 4 * i + 2 * g16 + (four >> 1)) ^ ((i16 >> 2) << 2);
+    return (uint32_t)((8 * h + (i16 >> 2)) * RB + piece * 16 + (four & 1) * 8);
   };
   uint32_t oa[TI], ob[TI];
 #pragma unroll
   for (int i = 0; i < TI; ++i) {
-    oa[i] = lds0 + lane_off(TA, wm, i);
-    ob[i] = lds0 + OPB + lane_off(TB, wn, i);
+    oa[i] = lds0 + lane_off(TA, wm, i, false);
+    ob[i] = lds0 + OPB + lane_off(TB, wn, i, ROWS);
   }
   auto operand = [&](bool kmajor, uint32_t base, int ks) -> bf16x8 {
     if (!kmajor) return *(lds_bf16x8_ptr)(ks ? base ^ 32u : base);   // piece 2 ks + h, permuted
@@ -180,16 +208,16 @@ __global__ __launch_bounds__(64 * kGemmWaves, WT == 128 ? 1 : 2) void gemm_bf16_
   };
 
   f32x16 acc[TI][TI];
-#pragma unroll
-  for (int i = 0; i < TI; ++i)
-#pragma unroll
-    for (int j = 0; j < TI; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  // A wave's own loads up to the last `2 G` have landed and all its LDS reads have returned; then every wave's.
-  auto arrive = [&]() {
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * G) : "memory");
+  // A wave's own loads up to the last `2 G` have landed; then every wave's.  (Its reads of the stage that is requested next went
+  // into matrix instructions that are issued.)  Loads and stores are counted in order: the two steps after a tile's stores let
+  // as many more operations be under way.
+  constexpr int STORES = OUT_F32 ? TI * TI * 16 : TI * WT / 16, LATER = 2 * G + STORES < 63 ? 2 * G + STORES : 63;
+  auto arrive = [&](bool stored) {
+    if (!DMA) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // pieces written through registers
+    if (stored)
+      asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(LATER) : "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * G) : "memory");
   };
 #pragma unroll
   for (int s = 0; s < kStages - 1; ++s) {
@@ -198,96 +226,177 @@ __global__ __launch_bounds__(64 * kGemmWaves, WT == 128 ? 1 : 2) void gemm_bf16_
       request(s, u, false);
       request(s, u, true);
     }
+    pa += da;
+    pb += db;
     next_source();
   }
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(4 * G) : "memory");
   bf16x8 a0[TI], b0[TI], a1[TI], b1[TI];
-#pragma unroll
-  for (int i = 0; i < TI; ++i) {
-    a0[i] = operand(TA, oa[i], 0);
-    b0[i] = operand(TB, ob[i], 0);
-  }
-  // Sixteen (four) matrix instructions on one set of operands with the reads of the next set between the first
-  // half of them and the requests of a later stage between the others.
-  auto half = [&](const bf16x8 *a, const bf16x8 *b, bf16x8 *an, bf16x8 *bn, uint32_t stage, int ks, int into, bool req_b) {
+  // Sixteen (four) matrix instructions on one set of operands with the reads of the next set and the requests of a later
+  // stage between them.
+  auto half = [&](auto first, const bf16x8 *a, const bf16x8 *b, bf16x8 *an, bf16x8 *bn, uint32_t stage, int ks, int into, bool req_b) {
     constexpr int MM = TI * TI;
 #pragma unroll
     for (int x = 0; x < MM; ++x) {
       const int i = x / TI, j = x % TI;
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-      if (x < TI) an[x] = operand(TA, oa[x] + stage, ks);
-      else if (x < 2 * TI) bn[x - TI] = operand(TB, ob[x - TI] + stage, ks);
-      if (MM == 16 ? (x >= 8 && (x & 1)) : x >= 2) {
-        const int u = MM == 16 ? (x - 8) / 2 : x - 2;
+      const f32x16 c = decltype(first)::value ? f32x16{} : acc[i][j];
+      acc[i][j] = ROWS ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j], a[i], c, 0, 0, 0)
+                       : __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], c, 0, 0, 0);
+      if (MM == 16 ? (x & 1) == 0 : true) {   // A 0, B 0 .. TI - 1, A 1 ..: the order in which the next half takes them
+        const int e = MM == 16 ? x / 2 : x;
+        if (e == 0 || e > TI) an[e ? e - TI : 0] = operand(TA, oa[e ? e - TI : 0] + stage, ks);
+        else bn[e - 1] = operand(TB, ob[e - 1] + stage, ks);
+      }
+      if (MM == 16 ? (x & 3) == 1 : x >= 2) {
+        const int u = MM == 16 ? x / 4 : x - 2;
         if (u < G) request(into, u, req_b);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  for (int s = 0; s < steps; ++s) {
-    const int cur = s % kStages, nxt = (s + 1) % kStages, into = (s + kStages - 1) % kStages;
-    arrive();   // stage s + 1 has landed; every wave is done with stage s - 1, which `into` overwrites
-    half(a0, b0, a1, b1, (uint32_t)(cur * SB), 1, into, false);
-    half(a1, b1, a0, b0, (uint32_t)(nxt * SB), 0, into, true);
+  int slot = 0;   // of the current stage
+  auto step = [&](auto first, bool stored) {
+    const int cur = slot, nxt = (slot + 1) % kStages, into = (slot + kStages - 1) % kStages;
+    arrive(stored);   // the next stage has landed; every wave is done with the stage before, which `into` overwrites
+    half(first, a0, b0, a1, b1, (uint32_t)(cur * SB), 1, into, false);
+    pa += da;
+    half(std::false_type{}, a1, b1, a0, b0, (uint32_t)(nxt * SB), 0, into, true);
+    pb += db;
+    slot = nxt;
     next_source();
-  }
-  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the stages are free
+  };
+  for (int li = blockIdx.x / 8; li < end; li += stride) {
+    const bool later = li != (int)(blockIdx.x / 8);
+    const Place at = place(li);
+    const int m0 = at.m0, n0 = at.n0, which = at.which;
+    const int steps = (at.k_end - at.k_begin) / BK * job.count;
+    // The last step of the tile before has read these operands too; a second time here costs less than their registers while
+    // the tile is written.
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      a0[i] = operand(TA, oa[i] + slot * SB, 0);
+      b0[i] = operand(TB, ob[i] + slot * SB, 0);
+    }
+    step(std::true_type{}, later);
+    for (int s = 1; s < steps; ++s) step(std::false_type{}, later && s == 1);
+    unsigned char *const free_stage = smem_raw + (slot + kStages - 1) % kStages * SB;   // the next request into it is after the next barrier
 
-  // acc[i][j][r]: row wm + 32 i + 8 (r / 4) + 4 h + (r % 4), column wn + 32 j + l32.
-  if (OUT_F32) {
-    float *C = splits == 1 ? reinterpret_cast<float *>(job.c[which])
-                           : reinterpret_cast<float *>(job.c[0]) + ((int64_t)which * splits + split) * M * ldc;
+    if (OUT_F32) {
+      // acc[i][j][r]: row wm + 32 i + 8 (r / 4) + 4 h + (r % 4), column wn + 32 j + l32.
+      const int lane = opaque(threadIdx.x & 63), l32 = lane & 31, h = lane >> 5;
+      float *C = splits == 1 ? reinterpret_cast<float *>(job.c[which])
+                             : reinterpret_cast<float *>(job.c[0]) + ((int64_t)which * splits + at.split) * M * ldc;
 #pragma unroll
-    for (int i = 0; i < TI; ++i)
+      for (int i = 0; i < TI; ++i)
 #pragma unroll
-      for (int j = 0; j < TI; ++j)
+        for (int j = 0; j < TI; ++j) {
+          if (WT == 128) asm volatile("" : "+a"(acc[i][j]));   // stays where the products leave it until here
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = m0 + wm + 32 * i + 8 * (r >> 2) + 4 * h + (r & 3);
-          C[(int64_t)row * ldc + n0 + wn + 32 * j + l32] = acc[i][j][r];
+          for (int r = 0; r < 16; ++r) {
+            const int row = m0 + wm + 32 * i + 8 * (r >> 2) + 4 * h + (r & 3);
+            C[(int64_t)row * ldc + n0 + wn + 32 * j + l32] = acc[i][j][r];
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
-  } else {
-    // bf16 through a wave-private LDS tile of 32 rows x WT columns: 16-byte row-major stores.
-    constexpr int ES = WT + 8, PPR = WT / 8;   // tile row stride; 16-byte pieces per row
+      continue;
+    }
+    const int lane = opaque(threadIdx.x & 63), l32 = lane & 31, h = lane >> 5;   // addresses of this part are not kept over the products
     bf16_t *C = reinterpret_cast<bf16_t *>(job.c[which]);
-    if (colsum && which == 0) {
-      // Per column one chain over a lane's 64 of the 128 rows; with WT = 64 rows 64 .. 127 are another wave's, which goes
-      // on from where the first one stopped, so that the sums have the same bits with either tile.
-      float sum[TI], mx[TI];
+    asm volatile("s_barrier" ::: "memory");   // every wave is done with the free stage
+    // Column sums: per column one chain over a lane's 64 of the 128 rows.  WT = 128 adds while the rows are written (for every
+    // product: the sums cost less than a second reading of the accumulators); with WT = 64 rows 64 .. 127 are another wave's,
+    // which goes on from where the first one stopped, so that the sums have the same bits with either tile.
+    float sum[TI], mx[TI];
+#pragma unroll
+    for (int j = 0; j < TI; ++j) sum[j] = mx[j] = 0.f;
+    auto add = [&](int j, float v) {
+      sum[j] += v;
+      mx[j] = fmaxf(mx[j], fabsf(v));
+    };
+    if (COLSUM && WT == 64 && which == 0) {
       auto add_rows = [&]() {
 #pragma unroll
         for (int j = 0; j < TI; ++j)
 #pragma unroll
           for (int i = 0; i < TI; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              sum[j] += acc[i][j][r];
-              mx[j] = fmaxf(mx[j], fabsf(acc[i][j][r]));
-            }
+            for (int r = 0; r < 16; ++r) add(j, acc[i][j][r]);
       };
+      float *carry = reinterpret_cast<float *>(free_stage) + (wave & 1) * (2 * TI * 64) + lane;
+      if (wave < 2) {
+        add_rows();
 #pragma unroll
-      for (int j = 0; j < TI; ++j) sum[j] = mx[j] = 0.f;
-      if (WT == 128 || wave < 2) add_rows();
-      if (WT == 64) {
-        float *carry = reinterpret_cast<float *>(smem_raw) + (wave & 1) * (2 * TI * 64) + lane;
-        if (wave < 2) {
-#pragma unroll
-          for (int j = 0; j < TI; ++j) {
-            carry[64 * j] = sum[j];
-            carry[64 * (TI + j)] = mx[j];
-          }
+        for (int j = 0; j < TI; ++j) {
+          carry[64 * j] = sum[j];
+          carry[64 * (TI + j)] = mx[j];
         }
-        __syncthreads();
-        if (wave >= 2) {
-#pragma unroll
-          for (int j = 0; j < TI; ++j) {
-            sum[j] = carry[64 * j];
-            mx[j] = carry[64 * (TI + j)];
-          }
-          add_rows();
-        }
-        __syncthreads();
       }
+      __syncthreads();
+      if (wave >= 2) {
+#pragma unroll
+        for (int j = 0; j < TI; ++j) {
+          sum[j] = carry[64 * j];
+          mx[j] = carry[64 * (TI + j)];
+        }
+        add_rows();
+      }
+      __syncthreads();
+    }
+    // bf16 through a wave-private tile of 32 rows x WT columns: rows as whole lines.  Piece c (16 bytes) of row r at slot
+    // c ^ f(r), where f separates the rows that one write covers.
+    constexpr int PPR = WT / 8, RPS = 64 / PPR;   // pieces per row, rows per store
+    unsigned char *tl = free_stage + wave * (32 * WT * 2);
+    auto at_piece = [&](int r, int c) {
+      const int f = ROWS ? (WT == 128 ? r & 15 : r >> 1 & 7) : (WT == 128 ? (r & 1) << 2 | (r & 4) << 1 : r & 4);
+      return r * (WT * 2) + (c ^ f) * 16;
+    };
+    auto put = [&](int i) {
+#pragma unroll
+      for (int j = 0; j < TI; ++j) {
+        if (WT == 128) asm volatile("" : "+a"(acc[i][j]));   // stays where the products leave it until here
+        if (ROWS) {   // acc[i][j][r]: row wm + 32 i + l32, column wn + 32 j + 16 (r / 8) + 8 h + (r % 8)
+#pragma unroll
+          for (int g = 0; g < 2; ++g) {
+            u16x8 piece;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) piece[e] = to_bf16(acc[i][j][8 * g + e]);
+            *reinterpret_cast<u16x8 *>(tl + at_piece(l32, 4 * j + 2 * g + h)) = piece;
+          }
+        } else {
+          // acc[i][j][r]: row wm + 32 i + 8 (r / 4) + 4 h + (r % 4), column wn + 32 j + l32.  Of rows r and r + 1 an even lane takes
+          // row r of its column and the next, an odd lane row r + 1 of its column and the one before.
+#pragma unroll
+          for (int r = 0; r < 16; r += 2) {
+            if (COLSUM && WT == 128) {
+              add(j, acc[i][j][r]);
+              add(j, acc[i][j][r + 1]);
+            }
+            typedef __bf16 pair __attribute__((ext_vector_type(2)));
+            const uint32_t own = __builtin_bit_cast(uint32_t, pair{(__bf16)acc[i][j][r], (__bf16)acc[i][j][r + 1]});
+            const uint32_t other = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xB1, 0xF, 0xF, true);   // lane ^ 1
+            const uint32_t word = __builtin_amdgcn_perm(other, own, lane & 1 ? 0x03020706u : 0x05040100u);
+            const int row = 8 * (r >> 2) + 4 * h + (r & 3) + (lane & 1);
+            *reinterpret_cast<uint32_t *>(tl + at_piece(row, 4 * j + (l32 >> 3)) + (l32 & 6) * 2) = word;
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    put(0);
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      u16x8 piece[32 / RPS];
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int u = 0; u < 32 / RPS; ++u)
+        piece[u] = *reinterpret_cast<const u16x8 *>(tl + at_piece(RPS * u + lane / PPR, lane % PPR));
+      __builtin_amdgcn_wave_barrier();
+      if (i + 1 < TI) put(i + 1);
+#pragma unroll
+      for (int u = 0; u < 32 / RPS; ++u)
+        *reinterpret_cast<u16x8 *>(C + (int64_t)(m0 + wm + 32 * i + RPS * u + lane / PPR) * ldc + n0 + wn + lane % PPR * 8) = piece[u];
+    }
+    if (COLSUM && which == 0) {
 #pragma unroll
       for (int j = 0; j < TI; ++j)
         sum[j] += __shfl_xor(sum[j], 32, 64);   // the two half-waves hold the two halves of every 8-row group
@@ -306,24 +415,8 @@ __global__ __launch_bounds__(64 * kGemmWaves, WT == 128 ? 1 : 2) void gemm_bf16_
         }
       }
     }
-    bf16_t *tl = reinterpret_cast<bf16_t *>(smem_raw) + wave * (32 * ES);
-#pragma unroll
-    for (int i = 0; i < TI; ++i) {
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (int j = 0; j < TI; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          tl[(8 * (r >> 2) + 4 * h + (r & 3)) * ES + 32 * j + l32] = to_bf16(acc[i][j][r]);
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (int u = 0; u < 32 * PPR / 64; ++u) {
-        const int e = lane + 64 * u, r = e / PPR, cc = e % PPR;
-        const u16x8 piece = *reinterpret_cast<const u16x8 *>(&tl[r * ES + cc * 8]);
-        *reinterpret_cast<u16x8 *>(C + (int64_t)(m0 + wm + 32 * i + r) * ldc + n0 + wn + cc * 8) = piece;
-      }
-    }
   }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no load may land in LDS that is no longer this workgroup's
 }
 
 // out[e] = sum over splits of part[split][e], fixed order; blockIdx.y: product of the batch.
@@ -340,27 +433,28 @@ __global__ void splitk_reduce_kernel(const float *part, int splits, int64_t coun
   *reinterpret_cast<float4 *>(out + e) = acc;
 }
 
-// Large tiles from one per compute unit on; fewer leave units idle.  Block inference, all products in large tiles against
+// A grid of large tiles is one workgroup per compute unit, each takes several tiles.  Large tiles from one per compute unit on; fewer leave units idle.  Block inference, all products in large tiles against
 // this rule: 2048 tokens, hidden 512 (48 and 16 large tiles) 68.7 -> 53.2 us; 4096 tokens, hidden 1024 (192 and 64)
 // 115.9 -> 106.8; 8192 tokens (384, large either way, and 128) 161.8 -> 156.2; 16384 tokens (all large) 251.9, 251.8.
-constexpr int kBigTileMin = 256;
+constexpr int kBigTileMin = 256, kComputeUnits = 256;
 
-template <int WT, bool TA, bool TB, bool OUT_F32, bool DMA>
+template <int WT, bool TA, bool TB, bool OUT_F32, bool DMA, bool COLSUM>
 hipError_t launch_gemm_tile(const char *name, const GemmJob &job, int ld, int M, int N, int K, int k_chunk, int splits,
                             hipStream_t st, float *colsum, float *colmax) {
-  constexpr size_t smem = (size_t)kStages * 2 * (2 * WT) * BK * sizeof(bf16_t);
-  static_assert(smem >= (size_t)kGemmWaves * 32 * (WT + 8) * sizeof(bf16_t), "the epilogue's tiles fit into the stages");
-  auto kern = &gemm_bf16_kernel<WT, TA, TB, OUT_F32, DMA>;
+  constexpr size_t stage = (size_t)2 * (2 * WT) * BK * sizeof(bf16_t);
+  constexpr size_t smem = kStages * stage;
+  static_assert(stage >= (size_t)kGemmWaves * 32 * WT * sizeof(bf16_t), "the tiles on their way out fit into a stage");
+  auto kern = &gemm_bf16_kernel<WT, TA, TB, OUT_F32, DMA, COLSUM>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
   const int total = (M / (2 * WT)) * (N / (2 * WT)) * job.batch * splits;
-  const int grid = ((total + 7) / 8) * 8;
+  const int grid = min(((total + 7) / 8) * 8, WT == 128 ? kComputeUnits : INT_MAX);
   WERSA_STAGE(name, st, kern<<<grid, 64 * kGemmWaves, smem, st>>>(job, ld, ld, ld, M, N, K, k_chunk, splits, colsum, colmax));
   return hipSuccess;
 }
 
-template <bool TA, bool TB, bool OUT_F32>
+template <bool TA, bool TB, bool OUT_F32, bool COLSUM = false>
 hipError_t launch_gemm(const char *name, const GemmJob &job, int ld, int M, int N, int K, int k_chunk, int splits,
                        hipStream_t st, float *colsum = nullptr, float *colmax = nullptr) {
   bool aligned = true;   // direct loads to LDS take 16-byte aligned sources
@@ -368,10 +462,10 @@ hipError_t launch_gemm(const char *name, const GemmJob &job, int ld, int M, int 
     aligned = aligned && ((uintptr_t)job.a[i] | (uintptr_t)job.b[i]) % 16 == 0;
   const int64_t big = (int64_t)(M / kBigTile) * (N / kBigTile) * job.batch * splits;
   if (!aligned)
-    return launch_gemm_tile<64, TA, TB, OUT_F32, false>(name, job, ld, M, N, K, k_chunk, splits, st, colsum, colmax);
+    return launch_gemm_tile<64, TA, TB, OUT_F32, false, COLSUM>(name, job, ld, M, N, K, k_chunk, splits, st, colsum, colmax);
   if (big >= kBigTileMin)
-    return launch_gemm_tile<128, TA, TB, OUT_F32, true>(name, job, ld, M, N, K, k_chunk, splits, st, colsum, colmax);
-  return launch_gemm_tile<64, TA, TB, OUT_F32, true>(name, job, ld, M, N, K, k_chunk, splits, st, colsum, colmax);
+    return launch_gemm_tile<128, TA, TB, OUT_F32, true, COLSUM>(name, job, ld, M, N, K, k_chunk, splits, st, colsum, colmax);
+  return launch_gemm_tile<64, TA, TB, OUT_F32, true, COLSUM>(name, job, ld, M, N, K, k_chunk, splits, st, colsum, colmax);
 }
 
 constexpr int kMinChunk = 256;   // tokens
@@ -532,7 +626,7 @@ wersa_status wersa_block_forward(const wersa_desc *desc, const void *x, const vo
     }
     job.count = 1;
     job.batch = 3;
-    if (launch_gemm<false, true, false>("wersa_gemm_nn", job, hid, M, hid, hid, hid, 1, st, (float *)(ws + w.qsums),
+    if (launch_gemm<false, true, false, true>("wersa_gemm_nn", job, hid, M, hid, hid, hid, 1, st, (float *)(ws + w.qsums),
                                         (float *)(ws + w.qmax)) != hipSuccess)
       return WERSA_ERR_LAUNCH;
   }

@@ -1828,8 +1828,9 @@ __device__ __forceinline__ void wide_load(const T *rows, int64_t sn, int valid, 
   }
 }
 
-// Apply modes.  32 slices of 65536 rows, m 512 (forward, dV): 559 and 592 us (with rows of X_F read in the order of the operand, 32 bytes
-// of a line at a time, and without the bits: 617 and 584; four waves of 64 rows and 512 registers: 896 and 782).  Matrix cores busy about half of
+// Apply modes.  32 slices of 65536 rows, m 512 (forward, dV): 528 and 544 us (with rows of the accumulators on registers, written
+// to LDS two bytes at a time: 559 and 592; with rows of X_F read in the order of the operand, 32 bytes of a line at a time, and without
+// the bits: 617 and 584; four waves of 64 rows and 512 registers: 896 and 782).  Matrix cores busy about half of
 // the time: an operand of 1 KiB read from LDS serves one matrix instruction, and the waits of two waves per SIMD are not all covered.
 template <int MODE, bool LN, bool RAGGED>
 __global__ __launch_bounds__(kWideWaves * 64, 2) void wide_rows_kernel(

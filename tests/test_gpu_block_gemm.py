@@ -16,6 +16,8 @@ SHAPES = [
     (1, 16, 5632, 128),
     (3, 16, 4352, 128),
     (1, 8, 24576, 64),
+    # 256-wide tiles of eight steps, three of them in one workgroup and four in others
+    (1, 4, 65792, 64),
 ]
 
 
