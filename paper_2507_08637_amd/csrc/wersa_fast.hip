@@ -2654,7 +2654,7 @@ hipError_t launch_wide_rows(const wersa_desc &c, const FastPlan &p, const _Float
     auto go = [&](auto kern) -> hipError_t {
       const hipError_t e = allow(kern);
       if (e != hipSuccess) return e;
-      WERSA_STAGE(MODE == 1 ? "wersa_rows_bwd_q" : "wersa_rows_bwd_k", st,
+      WERSA_STAGE(MODE == 1 ? "wersa_grad_q" : "wersa_grad_k", st,
                   kern<<<grid, kWideWaves * 64, smem, st>>>(x, tv, y, yview ? *yview : tv, Dsaved, arow, MODE == 1 ? w.bitsQ : w.bitsK,
                                                             omega + side, Mx, w.coef, c.n, c.m, p.rowGroups, out, tv, partF, c.L,
                                                             MODE == 1 ? w.gsumQ : w.gsumK));
@@ -2720,7 +2720,7 @@ hipError_t launch_masked64(const wersa_desc &c, const FastPlan &p, const bf16_t 
     const size_t smem = masked_smem_bytes(p.mc, 8);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
-    WERSA_STAGE(MODE == 1 ? "wersa_rows_bwd_q" : "wersa_rows_bwd_k", st,
+    WERSA_STAGE(MODE == 1 ? "wersa_grad_q" : "wersa_grad_k", st,
                 kern<<<dim3(p.rowsWgs, c.B * c.H), 8 * 64, smem, st>>>(
                     x, tv, y, yview ? *yview : tv, Dsaved, arow, MODE == 1 ? w.bitsQ : w.bitsK, omega, Mx, w.coef, c.n, c.m,
                     p.rowGroups, out, tv, partF, c.L, MODE == 1 ? w.gsumQ : w.gsumK));
