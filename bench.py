@@ -26,10 +26,10 @@ PEAK = {"hbm": (8000.0, "GB/s"), "mfma_bf16": (2500.0, "TFLOP/s"), "fp32": (157.
 MIB = 1024.0 * 1024.0
 RANKING_STEPS = 20   # untimed steps with every launch bracketed, to rank the kernels
 MEASURED_TRAFFIC_CONFIG4 = {
-    "wersa_rows_fwd": (137.7 + 134.8) * MIB, "wersa_rows_bwd_q": (272.0 + 130.1) * MIB,
-    "wersa_rows_bwd_k": (275.2 + 260.4) * MIB,   # with dV
-    "wersa_phiT_contract": ((256.4 + 32.5) + (388.4 + 36.5)) / 2 * MIB,   # average of the two launches
-    "wersa_qbar": 128.6 * MIB, "wersa_add_pooled": 256.1 * MIB,
+    "wersa_rows_fwd": (136.0 + 132.0) * MIB, "wersa_rows_bwd_v": (141.5 + 160.9) * MIB,
+    "wersa_grad_q": (333.6 + 128.0) * MIB, "wersa_grad_k": (325.8 + 128.0) * MIB,
+    "wersa_phiT_contract": ((256.4 + 32.5) + (388.4 + 68.5)) / 2 * MIB,   # average of the two launches
+    "wersa_qbar": 128.6 * MIB, "wersa_add_pooled": 256.2 * MIB,
 }
 
 

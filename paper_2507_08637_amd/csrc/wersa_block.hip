@@ -76,7 +76,7 @@ __device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t voff, const bf1
 // the tile leaves through the stage that was computed on last.  bf16 output without column sums: the operands of the matrix
 // instruction are exchanged, and B's rows or columns taken with bits 2 and 3 of their number exchanged, so that a lane holds 16-byte
 // pieces of its own row of C (32 LDS writes per wave and tile of 128 x 128 instead of 256 two-byte ones).
-// Measured (131072 tokens, hidden 2048, us per product): NN 877 -> 813 (905 with column sums), NT 874 -> 826, TN 831 -> 786;
+// Measured (131072 tokens, hidden 2048, us per product): NN 877 -> 813 (890 with column sums), NT 874 -> 826, TN 831 -> 786;
 // block training step 15344 -> 14980.  1.1 PFLOP takes 580 us at the 1.9 PFLOP/s that a bare loop of the instruction sustains.
 //
 // Logical tiles are dealt to the eight XCDs in contiguous runs (workgroup w runs on XCD w % 8); a run goes down
