@@ -441,7 +441,7 @@ __device__ __forceinline__ bf16x8 tile_cols_operand(const bf16_t *tile, int stri
 }
 
 // A value that the compiler re-derives from in every block: offsets that depend on the lane alone would otherwise be
-// kept in registers across the feature loop and spill (60 bytes per lane in the kernel with dV).
+// kept in registers across the feature loop and spill (the gradient kernels).
 __device__ __forceinline__ uint32_t opaque(uint32_t v) {
   asm volatile("" : "+v"(v));
   return v;
@@ -1002,7 +1002,8 @@ __device__ __forceinline__ void buf_store4(RowBuf r, uint32_t off, float v) {
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, off, 0, 0);
 }
 
-// The apply modes of head dimension 64.  LN (MODE 0): LayerNorm over the columns of a row instead of the normaliser.  RAGGED: n is
+// The apply modes of head dimension 64.  8 slices of 131072 rows, m 256 (forward, dV): 86 and 84 us; with the accumulators' rows on
+// registers (128 two-byte LDS writes per block, 8-byte stores, D through LDS) 90 and 90.  LN (MODE 0): LayerNorm over the columns of a row instead of the normaliser.  RAGGED: n is
 // not a multiple of 64; rows are read and written through buffers that end at row n (see row_buffer).  The plain instance has
 // none of that code.  DEEP: L > 6: X_F starts from the per-tile addend of the levels above 6 (tile_add
 // [slices][ceil(n / 64)][DH]).
@@ -1353,7 +1354,7 @@ __device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t voff, const voi
 // What bounds it: memory.  8 slices of 131072 rows, m 256 move 417 MB (key side: X and V in, bits in, dX out), 73 us at the rate of a
 // large copy, in 107; without seven eighths of the feature loop it takes 87, without the epilogue's arithmetic 102.
 // The kernel before it formed the projection, too, with one wave of 512 registers per SIMD: 175 us on the query side, 235 on the key
-// side with dV beside dX_F; now 116 and 107, and 90 for dV (its kernel has the projection in hand and leaves the bits).
+// side with dV beside dX_F; now 116 and 107, and 84 for dV (its kernel has the projection in hand and leaves the bits).
 // A lane's row: operand row l32 of dN or V is row 32 ti + r with r's bits (l0, l1, l3, l4, l2), so that the accumulator registers of
 // dX_F hold 16 consecutive rows 32 ti + 16 h + i of column 32 ct + l32: of the Haar filter's levels only 32 and 64 rows leave the lane.
 // X comes straight from memory into the wave's panels, one of 4 KiB per 32 columns ([64 rows][32], requested a row group ahead), and
