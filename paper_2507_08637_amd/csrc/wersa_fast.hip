@@ -698,11 +698,14 @@ __global__ __launch_bounds__(64 * NW, 2) void phiT_contract_kernel(
     stash(0);
   }
   __syncthreads();
-  // FUSE: rows 32 (wave / 2) + l32 of G are this wave's B operands in every step: kept in
-  // registers (high part for the four k-steps, low part for the two of the quarter's own half).
-  // The k-steps are taken own half first (ks_own, ks_own + 1: high and low part), then the other
-  // half (high part only), so that the step loop has no branch and its LDS reads go out together.
-  // (BITS: read again in every step, kept they would be spilled.)
+  // FUSE: rows 32 (wave / 2) + l32 of G are this wave's B operands in every step: high part for the four k-steps, low part for
+  // the two of the quarter's own half.  Forward: kept in registers, own half first (ks_own, ks_own + 1: high and low part),
+  // then the other half (high part only), so that the step loop has no branch and its LDS reads go out together.
+  // BITS: read again in every step (kept they would be spilled), and the sum is that of rows_kernel, k-steps upwards and the low part
+  // after the high one: X_F then has the bits it has in the forward, and dQ the forward's decisions.  (Own half first, a pre-activation
+  // within a rounding of zero went the other way here and there: dQ was further from float64, 4.74494e-3 against 4.74480e-3 at 8 slices of
+  // 131072 rows, m 256, 3.04324e-3 against 3.04244e-3 at 12 of 6000, m 1024, L 7.  The time is the same, with L > 6 less: 297 -> 292 us
+  // per training step at 8 slices of 30000 rows, L 10.)
   bf16x8 ghi[4], glo[2];
   const int ks_own = 2 * (wave >> 1), ks_oth = ks_own ^ 2;
   auto read_filter = [&](int ln) {
@@ -749,28 +752,44 @@ __global__ __launch_bounds__(64 * NW, 2) void phiT_contract_kernel(
     if (FUSE) {
       // X_F^T quarter: columns 32 (wave % 2) .. + 31 of the tile, rows 32 (wave / 2) .. + 31.
       const bf16_t *raw = reinterpret_cast<const bf16_t *>(&xt[buf][0]);
-      if (BITS) read_filter((int)opaque(lane));
-      f32x16 q = zero16(), q2 = zero16();
+      f32x16 q = zero16();
       if (DEEP) {   // register i is column 32 (wave % 2) + acc_row(i, h) for every row of the quarter
         const float *ta = tile_add + ((int64_t)slice * ((n + 63) / 64) + (t_begin / 64 + s)) * DH + 32 * (wave & 1);
 #pragma unroll
         for (int i = 0; i < 16; ++i) q[i] = ta[acc_row(i, h)];
       }
-      bf16x8 xa[4];
+      if (BITS) {
+        const int ln = (int)opaque(lane), trow = 32 * (wave >> 1) + (ln & 31), hh = ln >> 5, lower = wave >> 1;   // 1: rows 32 ..
+        // (k-step, part) of the six products, without a branch: (0, hi), (0, lo | 1, hi), (k23, hi), (k23, lo), (2 | 3, hi), (3, hi | lo)
+        const int k1 = lower, k23 = 1 + lower, k4 = 2 + lower;
+        auto rows = [&](int ks) { return tile_cols_operand<false>(raw, XS, 32 * (wave & 1), ks, ln); };
+        auto gop = [&](int part, int ks) { return filter_operand(gt, part, trow, 2 * ks + hh); };
+        const bf16x8 x0 = rows(0), x1 = rows(k1), x23 = rows(k23), x4 = rows(k4), x5 = rows(3);
+        const bf16x8 g0 = gop(0, 0), g1 = gop(1 - lower, k1), g2 = gop(0, k23), g3 = gop(1, k23), g4 = gop(0, k4), g5 = gop(lower, 3);
+        q = mfma_bf16(x0, g0, q);
+        q = mfma_bf16(x1, g1, q);
+        q = mfma_bf16(x23, g2, q);
+        q = mfma_bf16(x23, g3, q);
+        q = mfma_bf16(x4, g4, q);
+        q = mfma_bf16(x5, g5, q);
+      } else {
+        f32x16 q2 = zero16();
+        bf16x8 xa[4];
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        xa[u] = tile_cols_operand<false>(raw, XS, 32 * (wave & 1), ks_own + u, lane);
-        xa[2 + u] = tile_cols_operand<false>(raw, XS, 32 * (wave & 1), ks_oth + u, lane);
+        for (int u = 0; u < 2; ++u) {
+          xa[u] = tile_cols_operand<false>(raw, XS, 32 * (wave & 1), ks_own + u, lane);
+          xa[2 + u] = tile_cols_operand<false>(raw, XS, 32 * (wave & 1), ks_oth + u, lane);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {   // the low part matters inside the quarter's own 32-row half only
+          q = mfma_bf16(xa[u], ghi[u], q);
+          q2 = mfma_bf16(xa[u], glo[u], q2);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) q = mfma_bf16(xa[2 + u], ghi[2 + u], q);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) q[i] += q2[i];
       }
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {   // the low part matters inside the quarter's own 32-row half only
-        q = mfma_bf16(xa[u], ghi[u], q);
-        q2 = mfma_bf16(xa[u], glo[u], q2);
-      }
-#pragma unroll
-      for (int u = 0; u < 2; ++u) q = mfma_bf16(xa[2 + u], ghi[2 + u], q);
-#pragma unroll
-      for (int i = 0; i < 16; ++i) q[i] += q2[i];
       // accumulator register i is column 32 (wave % 2) + acc_row(i, h), lane l32 is row 32 (wave / 2) + l32
 #pragma unroll
       for (int g = 0; g < 4; ++g) {

@@ -48,3 +48,45 @@ def test_every_decision(n, d, m):
         worst[name] = float(e.max())
     print((n, d, m), {x: f"{e:.1e}" for x, e in worst.items()}, flush=True)
     assert max(worst.values()) < 2e-2, worst
+
+
+@pytest.mark.parametrize("n,m", [(131072, 256), (131072, 128), (65544, 256)])
+def test_queries_decide_as_the_forward(n, m):
+    """Head dimension 64: dQ uses the decisions that the forward's rows kernel takes, bit for bit: the filtered queries that leave the bits are summed in
+    that kernel's order.  The key side's decisions come from a rows kernel, so a problem with Q = K that is the same on both sides must give
+    the same decisions on both: one value per slice for all of V and dO and an eps far above the normaliser make the two gradients of a
+    feature equal (d z_r / eps) up to rounding.  A feature's decision is read from a column of its own (0 in Q, 1 in its
+    column of Omega).  The signal's columns are constant over 64 rows and their band is weighted with 1e-3 against the others' 1.4, so
+    that the filter's sums cancel and a sum in another order gives other bits, and some other decisions: one is worth up to 1 of `size` in its row,
+    rounding a few times 2^-9."""
+    import torch
+    from paper_2507_08637_amd import binding
+    H, d, L, tags = 8, 64, 6, 56
+    g = torch.Generator(device="cuda").manual_seed(n + m + L)
+
+    def normal(*s):
+        return torch.randn(s, generator=g, device="cuda")
+
+    q = torch.zeros(1, H, n, d, device="cuda")
+    q[..., tags:] = normal(1, H, -(-n // 2 ** L), 8).repeat_interleave(2 ** L, 2)[:, :, :n]
+    q = q.to(torch.bfloat16)
+    omega = torch.zeros(d, m, device="cuda")
+    omega[tags:, :tags] = normal(8, tags)
+    omega[:tags, :tags] = torch.eye(tags, device="cuda")
+    omega = omega.to(torch.bfloat16)
+    ones = torch.ones_like(q)
+    scale = torch.full((L + 1,), 2.7913, device="cuda")
+    scale[L] = 2.1e-3
+    par = (torch.ones(1, device="cuda"), torch.zeros(H, L + 1, d, device="cuda"), torch.zeros(H, L + 1, device="cuda"), scale)
+    opt = dict(eps=1e6)
+    assert binding.load_library().wersa_selected_path(binding.make_desc(q, L, m)) == 1
+    out, saved = binding.wersa_forward(q, q, ones, omega, *par, L, **opt)
+    got = binding.wersa_backward(q, q, ones, omega, *par, out, ones, saved, L, **opt)
+    z = binding.saved_views(binding.make_desc(q, L, m, eps=1e6), saved)["z"].double()[:, :tags]
+    size = 0.5 * float(scale[0]) * d * z / 1e6 / m ** 0.5   # of a feature's decision, in its column of dQ
+    assert float(size.min()) > 0
+    differ = (got["dq"].double() - got["dk"].double())[0, ..., :tags].abs().amax(1) / size
+    mixed = (got["dk"][0, ..., :tags].double().abs().amax(1) / size > 0.5).sum()   # features whose rows of a block do not all agree
+    print((n, m), f"worst {float(differ.max()):.1e}, mixed {int(mixed)} of {size.numel()}", flush=True)
+    assert int(mixed) > 10   # (otherwise nothing is seen)
+    assert float(differ.max()) < 0.1
