@@ -55,6 +55,28 @@ __device__ __forceinline__ float xor32_sum(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
+// Sum over the 32 columns of a tile, which a row holds as s[i] = column 16 (i / 8) + 8 h + i % 8 in lanes of half-wave h (rows on
+// lanes): pairs, quads, then the four quads of a sixteen two by two, then the two sixteens; 7 roundings in a row where a chain over the lane's
+// registers has 32 and 64.  even: quads added as (Q0 + Q3) + (Q1 + Q2), odd: as (Q0 + Q1) + (Q2 + Q3).  The columns of even and of odd quads
+// take their own: that is what a butterfly over lanes gives with columns on the lanes, and the results are its bits.
+struct TileSum {
+  float even, odd;
+  __device__ __forceinline__ float of(int i) const { return i & 4 ? odd : even; }   // for the column of register i
+};
+__device__ __forceinline__ TileSum tile_sum(const float (&s)[16]) {
+  float e[2], o[2];
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    const float u = (s[8 * g] + s[8 * g + 1]) + (s[8 * g + 2] + s[8 * g + 3]);
+    const float v = (s[8 * g + 4] + s[8 * g + 5]) + (s[8 * g + 6] + s[8 * g + 7]);
+    const auto q02 = __builtin_amdgcn_permlane32_swap(__float_as_uint(u), __float_as_uint(u), false, false);
+    const auto q13 = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    const float q0 = __uint_as_float(q02[0]), q1 = __uint_as_float(q13[0]), q2 = __uint_as_float(q02[1]), q3 = __uint_as_float(q13[1]);
+    e[g] = (q0 + q3) + (q1 + q2);
+    o[g] = (q0 + q1) + (q2 + q3);
+  }
+  return TileSum{e[0] + e[1], o[0] + o[1]};
+}
 __device__ __forceinline__ float wave_sum64(float v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
@@ -1305,25 +1327,27 @@ __global__ __launch_bounds__(kWavesApply * 64, 2) void rows_kernel(
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int ti = 0; ti < 2; ++ti) {
-      float scale = cscale, Dt = 0.f;
+      float scale = cscale, scale_odd = 0.f, Dt = 0.f;   // scale_odd: LN, columns of odd quads (see tile_sum)
       if (MODE == 0 && LN) {
         // Output stage of Algorithm 1: O_t = (N_t - mean N_t) / sqrt(var N_t + eps), N = c * acc: mean first, then the centred
         // second moment (the other half of the row is in the other half-wave).  1 / sqrt(var + eps) goes to D.
-        float v = 0.f, q = 0.f;
+        float v[16];
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
+        for (int i = 0; i < 16; ++i) v[i] = acc0[ti][0][i] + acc0[ti][1][i];
+        const TileSum mu = tile_sum(v);
 #pragma unroll
-          for (int i = 0; i < 16; ++i) v += acc0[ti][ct][i];
-        const float mu = xor32_sum(v) * (1.0f / (float)DH);
+        for (int i = 0; i < 16; ++i) {
+          v[i] = 0.f;
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const float e = (acc0[ti][ct][i] - mu) * cscale;
+          for (int ct = 0; ct < CT; ++ct) {
+            const float e = (acc0[ti][ct][i] - mu.of(i) * (1.0f / (float)DH)) * cscale;
             acc0[ti][ct][i] = e;
-            q = fmaf(e, e, q);
+            v[i] = fmaf(e, e, v[i]);
           }
-        scale = Dt = 1.0f / sqrtf(xor32_sum(q) * (1.0f / (float)DH) + eps);
+        }
+        const TileSum q = tile_sum(v);
+        scale = Dt = 1.0f / sqrtf(q.even * (1.0f / (float)DH) + eps);
+        scale_odd = 1.0f / sqrtf(q.odd * (1.0f / (float)DH) + eps);
       } else if (MODE == 0) {   // normaliser D_t = c * sum_r relu(R) z + eps, row scale c / D_t
         Dt = fmaf(cscale, xor32_sum(dacc[ti].own(ln)), eps);
         scale = cscale * __builtin_amdgcn_rcpf(Dt);
@@ -1339,7 +1363,7 @@ __global__ __launch_bounds__(kWavesApply * 64, 2) void rows_kernel(
         for (int a = 0; a < 2; ++a) {
           bf16x8 pk;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) pk[e] = (__bf16)(acc0[ti][ct][8 * a + e] * scale);
+          for (int e = 0; e < 8; ++e) pk[e] = (__bf16)(acc0[ti][ct][8 * a + e] * (LN && (e & 4) ? scale_odd : scale));
           *reinterpret_cast<bf16x8 *>(panels + (32 * ti + row32) * 64 + (((4 * ct + 2 * a + hh) ^ (row32 & 7)) << 3)) = pk;
         }
     }
@@ -1964,23 +1988,25 @@ __global__ __launch_bounds__(kWideWaves * 64, 2) void wide_rows_kernel(
     RowBuf osb;
     if (RAGGED) osb = row_buffer(os, vo.sn, valid);
     const int ln = (int)opaque(lane), row32 = ln & 31, hh = ln >> 5;
-    float scale = cscale, Dt = 0.f;
+    float scale = cscale, scale_odd = 0.f, Dt = 0.f;   // scale_odd: LN, columns of odd quads (see tile_sum)
     if (MODE == 0 && LN) {   // O_t = (N_t - mean N_t) / sqrt(var N_t + eps), N = c * acc; 1 / sqrt(var + eps) goes to D
-      float v = 0.f, q = 0.f;
+      float v[16];
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct)
+      for (int i = 0; i < 16; ++i) v[i] = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
+      const TileSum mu = tile_sum(v);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) v += acc[ct][i];
-      const float mu = xor32_sum(v) * (1.0f / (float)DH);
+      for (int i = 0; i < 16; ++i) {
+        v[i] = 0.f;
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const float e = (acc[ct][i] - mu) * cscale;
+        for (int ct = 0; ct < CT; ++ct) {
+          const float e = (acc[ct][i] - mu.of(i) * (1.0f / (float)DH)) * cscale;
           acc[ct][i] = e;
-          q = fmaf(e, e, q);
+          v[i] = fmaf(e, e, v[i]);
         }
-      scale = Dt = 1.0f / sqrtf(xor32_sum(q) * (1.0f / (float)DH) + eps);
+      }
+      const TileSum q = tile_sum(v);
+      scale = Dt = 1.0f / sqrtf(q.even * (1.0f / (float)DH) + eps);
+      scale_odd = 1.0f / sqrtf(q.odd * (1.0f / (float)DH) + eps);
     } else if (MODE == 0) {   // D_t = c * sum_r relu(R) z + eps, row scale c / D_t
       Dt = fmaf(cscale, xor32_sum(dacc), eps);
       scale = cscale * __builtin_amdgcn_rcpf(Dt);
@@ -1994,7 +2020,7 @@ __global__ __launch_bounds__(kWideWaves * 64, 2) void wide_rows_kernel(
       for (int a = 0; a < 2; ++a) {
         bf16x8 pk;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) pk[e] = (__bf16)(acc[ct][8 * a + e] * scale);
+        for (int e = 0; e < 8; ++e) pk[e] = (__bf16)(acc[ct][8 * a + e] * (LN && (e & 4) ? scale_odd : scale));
         *reinterpret_cast<bf16x8 *>(panel + row32 * 256 + (((4 * ct + 2 * a + hh) ^ (row32 & 15)) << 4)) = pk;
       }
     __builtin_amdgcn_wave_barrier();
