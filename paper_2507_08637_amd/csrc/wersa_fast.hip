@@ -2354,18 +2354,14 @@ __global__ __launch_bounds__(kWideWaves * 64, 2) void wide_grad_kernel(
 // accesses, four independent pieces per thread.
 // TILE: tile_add is given (the plain instance has none of its code), and blockIdx.z = 1 is dK with its own addends and
 // without the pooled term (a launch of its own before: 8 slices of 30000 rows, 17 + 14 us for the two, 26 us now).
-// Grid (chunks, slices + 1, 1 or 2); the last slice row is the gate's parameter gradients.
+// Grid (chunks, slices + rows of the gate's parameter gradients (see gate_bwd_params_rows), 1 or 2).
 template <int DH, bool TILE>
 __global__ __launch_bounds__(256) void add_pooled_kernel(bf16_t *dq, View v, const float *dqbar, int n,
                                                         float inv_n, const float *tile_add, bf16_t *dk,
                                                         const float *tile_add_k, GateBwdParams gp) {
   constexpr int CPR = DH / 8;
   const int slice = blockIdx.y;
-  if (blockIdx.y == gridDim.y - 1) {
-    if (blockIdx.z == 0)
-      for (int b = blockIdx.x; b < gp.blocks; b += gridDim.x) gate_bwd_params_body(gp, b);
-    return;
-  }
+  if (gate_bwd_params_rows(gp)) return;
   if (TILE && blockIdx.z) {
     dq = dk;
     tile_add = tile_add_k;
@@ -2967,7 +2963,7 @@ wersa_status fast_backward_t(const wersa_desc &c, const bf16_t *q, const bf16_t 
   const GateBwdParams gp{w.dF, w.dlogit, s, qbar, w.dDpart, slices * (ln ? p.chunksL : p.chunksC), c.B, c.H, c.L, c.d, c.eps, w.scalars,
                          dgate_w, dgate_b, dscale_w, dsigma, gate_bwd_params_blocks(c.H, c.L, c.d)};
   const int64_t chunks = (int64_t)c.n * (DH / 8);
-  const dim3 agrid((unsigned)((chunks + 1023) / 1024), slices + 1, deep ? 2 : 1);
+  const dim3 agrid = with_gate_bwd_params(dim3((unsigned)((chunks + 1023) / 1024), slices, deep ? 2 : 1), gp);
   if (deep) {
     WERSA_STAGE("wersa_add_pooled", st,
                 (add_pooled_kernel<DH, true><<<agrid, 256, 0, st>>>(dq, tv, w.dqbar, c.n, 1.0f / (float)c.n, w.gaddQ, dk, w.gaddK, gp)));

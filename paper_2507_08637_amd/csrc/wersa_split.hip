@@ -1331,17 +1331,13 @@ __global__ __launch_bounds__(256) void dots_kernel(const T *q, const T *k, View 
 }
 
 // dQ = G_F dQ_F + dqbar / n and dK = G_F dK_F: the filter's backward (symmetric matrix) with the pooled query's
-// share.  addq, addk: the per-tile addends of the levels above 6.  Grid (row groups * column pieces, slices + 1, 2: Q, K); the last slice
-// row is the gate's parameter gradients.
+// share.  addq, addk: the per-tile addends of the levels above 6.  Grid (row groups * column pieces, slices + rows of
+// the gate's parameter gradients (see gate_bwd_params_rows), 2: Q, K).
 template <typename T, int DH>
 __global__ __launch_bounds__(256) void filter_bwd_kernel(const float *gq, const float *gk, T *dq, T *dk, View v, Dims s, int L,
                                                         const float *coef, const float *addq, const float *addk,
                                                         const float *dqbar, float inv_n, GateBwdParams gp) {
-  if (blockIdx.y == gridDim.y - 1) {
-    if (blockIdx.z == 0)
-      for (int b = blockIdx.x; b < gp.blocks; b += gridDim.x) gate_bwd_params_body(gp, b);
-    return;
-  }
+  if (gate_bwd_params_rows(gp)) return;
   using G = Geo<DH>;
   constexpr int CW = G::CW, TR = G::TR;
   __shared__ float segsum[G::SEGS][CW];
@@ -1743,7 +1739,7 @@ wersa_status backward_t(const wersa_desc &c, const T *q, const T *k, const T *v,
       (c.flags & WERSA_FLAG_POOLED_GATE) ? 1 : 0));
   const GateBwdParams gp{w.dF, w.dlogit, saved + sv.s, saved + sv.qbar, w.dpart, slices * p.groups, c.B, c.H, c.L, c.d, c.eps, scalars,
                          dgate_w, dgate_b, dscale_w, dsigma, gate_bwd_params_blocks(c.H, c.L, c.d)};
-  WERSA_STAGE("split_filter_bwd", st, filter_bwd_kernel<T, DH><<<dim3(p.groups, slices + 1, 2), 256, 0, st>>>(
+  WERSA_STAGE("split_filter_bwd", st, filter_bwd_kernel<T, DH><<<with_gate_bwd_params(dim3(p.groups, slices, 2), gp), 256, 0, st>>>(
       w.gq, w.gk, dq, dk, tv, p.s, c.L, coef, w.aq, w.ak, w.dqbar, 1.0f / (float)c.n, gp));
   return hipGetLastError() == hipSuccess ? WERSA_OK : WERSA_ERR_LAUNCH;
 }
