@@ -2611,6 +2611,14 @@ struct FastWs {
 
 // Workspace pieces; the per-call constants and the forward's bf16 operand copies live in the
 // saved buffer (the backward reads them back instead of rebuilding them).
+// 32-bit words of the ReLU's decisions of one side: n m / 8 bytes per slice (n to the next 64).
+inline int64_t bits_words(const wersa_desc &c) { return (int64_t)c.B * c.H * ((c.n + 63) / 64) * 2 * c.m; }
+// Tensors from 512 MiB on, twice the last-level cache: the two sides' decisions share one buffer, and the query side goes first.
+// Below it goes last, so that the pass that adds the pooled query's share finds part of dQ in the cache, and the second buffer
+// is 2 GiB at most (d 64, m 4096).  us per training step with two buffers and with one: tensors of 512 MiB, d 64, m 256 2483, 2488,
+// m 512 4333, 4345, d 128, m 256 3024, 3019; of 256 MiB, m 256 1285, 1296; of 128 MiB, m 1024 1848, 1853, m 2048 3318, 3345.
+inline bool one_bits_buffer(const wersa_desc &c) { return (int64_t)c.B * c.H * c.n * c.d * 2 >= ((int64_t)512 << 20); }
+
 FastWs fast_ws(const wersa_desc &c, const FastPlan &p, int bwd, float *base, float *saved) {
   FastWs w{};
   Bump b(base);
@@ -2654,8 +2662,8 @@ FastWs fast_ws(const wersa_desc &c, const FastPlan &p, int bwd, float *base, flo
       w.gaddQ = b.take(tiles);
       w.gaddK = b.take(tiles);
     }
-    w.bitsQ = reinterpret_cast<uint32_t *>(b.take(sl * ntiles * 2 * c.m));
-    w.bitsK = reinterpret_cast<uint32_t *>(b.take(sl * ntiles * 2 * c.m));
+    w.bitsQ = reinterpret_cast<uint32_t *>(b.take(bits_words(c)));
+    w.bitsK = one_bits_buffer(c) ? w.bitsQ : reinterpret_cast<uint32_t *>(b.take(bits_words(c)));
     w.dF = b.take(sl * (c.L + 1));
     w.dlogit = b.take(sl * (c.L + 1));
     w.dqbar = b.take(sl * c.d);
@@ -2935,21 +2943,19 @@ wersa_status fast_backward_t(const wersa_desc &c, const bf16_t *q, const bf16_t 
   } else {
     launch_contract<DH>(c, p, QF, q, dout, tv, D, nullptr, out, false, w, w.dS, w.dz, w.dSx, w.dST, w.dzb, st);
   }
+  auto key_side = [&]() {
+    const hipError_t e = launch_rows<DH, 3>(c, p, KF, k, nullptr, nullptr, nullptr, w, omega, nullptr, w.dST, nullptr, dv, nullptr, nullptr, st);
+    if (e != hipSuccess) return e;
+    return launch_rows<DH, 2>(c, p, KF, k, v, nullptr, nullptr, w, omega, w.dSx, nullptr, nullptr, dk, nullptr, w.partK, st);
+  };
+  auto query_side = [&]() {
+    return ln ? launch_rows<DH, 1>(c, p, QF, q, w.dN, w.ones, w.dD, w, omega, w.Sx, nullptr, nullptr, dq, nullptr, w.partQ, st, &nv)
+              : launch_rows<DH, 1>(c, p, QF, q, dout, D, w.dD, w, omega, w.Sx, nullptr, nullptr, dq, nullptr, w.partQ, st);
+  };
   // K side first: the Q-side kernel then is the last writer of a large tensor before the pass
   // that adds the pooled-query term to dQ, which finds part of dQ still in the last-level cache.
-  if (launch_rows<DH, 3>(c, p, KF, k, nullptr, nullptr, nullptr, w, omega, nullptr, w.dST, nullptr, dv, nullptr, nullptr, st) !=
-          hipSuccess ||
-      launch_rows<DH, 2>(c, p, KF, k, v, nullptr, nullptr, w, omega, w.dSx, nullptr, nullptr, dk, nullptr, w.partK, st) != hipSuccess)
-    return WERSA_ERR_LAUNCH;
-  if (ln) {
-    if (launch_rows<DH, 1>(c, p, QF, q, w.dN, w.ones, w.dD, w, omega, w.Sx, nullptr, nullptr, dq, nullptr,
-                           w.partQ, st, &nv) != hipSuccess)
-      return WERSA_ERR_LAUNCH;
-  } else {
-    if (launch_rows<DH, 1>(c, p, QF, q, dout, D, w.dD, w, omega, w.Sx, nullptr, nullptr, dq, nullptr,
-                           w.partQ, st) != hipSuccess)
-      return WERSA_ERR_LAUNCH;
-  }
+  const bool q_first = one_bits_buffer(c);
+  if ((q_first && query_side() != hipSuccess) || key_side() != hipSuccess || (!q_first && query_side() != hipSuccess)) return WERSA_ERR_LAUNCH;
   const bool deep = c.L > kTileL;
   if (deep)   // levels above 6: addends of dQ and dK and the bands' extra row, from the tile sums
     WERSA_STAGE("wersa_coarse_bwd", st,

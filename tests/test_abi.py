@@ -187,3 +187,10 @@ def test_stated_limits_alignment_and_block_strides(lib):
     # the microbenchmarks refuse bad arguments without touching the device
     assert lib.wersa_peak_copy(None, ok, 1 << 20, 1, None) == -1.0
     assert lib.wersa_peak_mfma(None, 1, None) == -1.0
+
+
+@pytest.mark.parametrize("d,m", [(64, 1024), (64, 4096), (128, 512), (128, 4096)])
+def test_backward_workspace_of_large_problems_holds_the_decisions_of_one_side(lib, d, m):
+    """MFMA path, per row and slice: a bit per feature for one side's ReLU, dD and, by whole splits of n at most, nothing else."""
+    a, b = (lib.wersa_workspace_bytes(ctypes.byref(_dense(1, H=8, n=n, d=d, m=m)), 1) for n in (524288, 1048576))
+    assert 0 < b - a <= 8 * 524288 * (m // 8 + 4 + 4)
