@@ -1018,7 +1018,7 @@ __global__ __launch_bounds__(256) void reduce_contract_kernel(const float *Spart
 // stay below 2^32 bytes (see kMaxBufferStride).
 typedef __amdgpu_buffer_rsrc_t RowBuf;
 constexpr int64_t kMaxBufferStride = 1 << 24;   // row stride (elements) up to which a partial last block is a buffer
-constexpr int64_t kMaxGroupStride = 1 << 26;    // and up to which a lane reaches 16 rows with a 32-bit offset in bytes
+constexpr int64_t kMaxGroupStride = 1 << 26;    // and up to which a lane of the gradient kernels reaches 32 rows with a 32-bit offset in bytes
 template <typename T>
 __device__ __forceinline__ RowBuf row_buffer(const T *rows, int64_t sn, int valid) {
   const uint64_t a = reinterpret_cast<uint64_t>(rows);   // (the compiler does not see that a wave's index is uniform)
@@ -1371,11 +1371,17 @@ __global__ __launch_bounds__(kWavesApply * 64, 2) void rows_kernel(
     u16x8 piece[8];   // row 8 j + lane / 8, columns 8 (lane % 8) ..
 #pragma unroll
     for (int j = 0; j < 8; ++j) piece[j] = *reinterpret_cast<const u16x8 *>(panels + (8 * j + (ln >> 3)) * 64 + (((ln & 7) ^ (ln >> 3)) << 3));
-    const uint32_t off = (uint32_t)(ln >> 3) * ((uint32_t)vo.sn * 2) + (ln & 7) * 16;
+    if (RAGGED) {
+      const uint32_t off = (uint32_t)(ln >> 3) * ((uint32_t)vo.sn * 2) + (ln & 7) * 16;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      if (RAGGED) buf_store16(osb, off + (uint32_t)j * ((uint32_t)vo.sn * 16), piece[j]);
-      else *reinterpret_cast<u16x8 *>(reinterpret_cast<char *>(os + 8 * j * vo.sn) + off) = piece[j];
+      for (int j = 0; j < 8; ++j) buf_store16(osb, off + (uint32_t)j * ((uint32_t)vo.sn * 16), piece[j]);
+    } else {   // (64-bit: the forward takes rows any distance apart)
+      bf16_t *orow = os + (int64_t)(ln >> 3) * vo.sn + (ln & 7) * 8;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        *reinterpret_cast<u16x8 *>(orow) = piece[j];
+        orow += 8 * vo.sn;
+      }
     }
     put_rows();
   }
@@ -2024,17 +2030,23 @@ __global__ __launch_bounds__(kWideWaves * 64, 2) void wide_rows_kernel(
         *reinterpret_cast<bf16x8 *>(panel + row32 * 256 + (((4 * ct + 2 * a + hh) ^ (row32 & 15)) << 4)) = pk;
       }
     __builtin_amdgcn_wave_barrier();
-    const uint32_t off = (uint32_t)(ln >> 4) * ((uint32_t)vo.sn * 2) + (ln & 15) * 16;
     u16x8 piece[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int r = 4 * j + (ln >> 4);
       piece[j] = *reinterpret_cast<const u16x8 *>(panel + r * 256 + (((ln & 15) ^ (r & 15)) << 4));
     }
+    if (RAGGED) {
+      const uint32_t off = (uint32_t)(ln >> 4) * ((uint32_t)vo.sn * 2) + (ln & 15) * 16;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      if (RAGGED) buf_store16(osb, off + (uint32_t)j * ((uint32_t)vo.sn * 8), piece[j]);
-      else *reinterpret_cast<u16x8 *>(reinterpret_cast<char *>(os + 4 * j * vo.sn) + off) = piece[j];
+      for (int j = 0; j < 8; ++j) buf_store16(osb, off + (uint32_t)j * ((uint32_t)vo.sn * 8), piece[j]);
+    } else {   // (64-bit: the forward takes rows any distance apart)
+      bf16_t *orow = os + (int64_t)(ln >> 4) * vo.sn + (ln & 15) * 8;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        *reinterpret_cast<u16x8 *>(orow) = piece[j];
+        orow += 4 * vo.sn;
+      }
     }
     if (more) turn_rows();
   }
@@ -2980,9 +2992,12 @@ wersa_status fast_backward_t(const wersa_desc &c, const bf16_t *q, const bf16_t 
   return hipGetLastError() == hipSuccess ? WERSA_OK : WERSA_ERR_LAUNCH;
 }
 
-// A partial last block whose rows lie too far apart for a buffer (kMaxBufferStride): the tensors are copied to dense
-// ones in the workspace and the results back.  Rows of more than 32 MB: there are never many.
-bool rows_far_apart(const wersa_desc &c) { return c.stride_n > (c.n % 64 != 0 ? kMaxBufferStride : kMaxGroupStride); }
+// Rows too far apart for a buffer with a partial last block (kMaxBufferStride), or, in the backward, for the gradient kernels' 32-bit offsets
+// (kMaxGroupStride): the tensors are copied to dense ones in the workspace and the results back.  Rows of more than 32 MB: there are
+// never many.
+bool rows_far_apart(const wersa_desc &c, int for_backward) {
+  return c.n % 64 ? c.stride_n > kMaxBufferStride : for_backward && c.stride_n > kMaxGroupStride;
+}
 wersa_desc dense_desc(const wersa_desc &c) {
   wersa_desc o = c;
   o.stride_n = c.d;
@@ -3029,13 +3044,13 @@ bool fast_supported(const wersa_desc &c) {
   if (c.dtype != WERSA_BF16 || (c.d != 64 && c.d != 128) || c.m % 128 || c.stride_n % 8 || c.stride_h % 8 || c.stride_b % 8)
     return false;
   // (the copies do not take a call away from wersa_forward_static)
-  return !rows_far_apart(c) || fast_workspace_bytes(c, 0) <= kStaticScratchBytes ||
+  return !rows_far_apart(c, 0) || fast_workspace_bytes(c, 0) <= kStaticScratchBytes ||
          (split_workspace_bytes(c, 0) > kStaticScratchBytes && generic_workspace_bytes(c, 0) > kStaticScratchBytes);
 }
 
 size_t fast_workspace_bytes(const wersa_desc &c, int for_backward) {
   size_t floats = (size_t)fast_ws(c, fast_plan(c), for_backward, nullptr, nullptr).total;
-  if (rows_far_apart(c)) floats += (for_backward ? 8 : 4) * dense_floats(c);
+  if (rows_far_apart(c, for_backward)) floats += (for_backward ? 8 : 4) * dense_floats(c);
   return floats * sizeof(float);
 }
 
@@ -3043,7 +3058,7 @@ wersa_status fast_forward(const wersa_desc &c, const void *q, const void *k, con
                           const void *omega_rf, const float *sigma, const float *gate_w,
                           const float *gate_b, const float *scale_w, void *out, float *saved,
                           float *ws, hipStream_t st, const PooledSums *pooled) {
-  if (rows_far_apart(c)) {
+  if (rows_far_apart(c, 0)) {
     const wersa_desc dc = dense_desc(c);
     const size_t one = dense_floats(c);
     float *p = ws + fast_workspace_bytes(dc, 0) / sizeof(float);
@@ -3070,7 +3085,7 @@ wersa_status fast_backward(const wersa_desc &c, const void *q, const void *k, co
                            const float *saved, void *dq, void *dk, void *dv, float *dgate_w,
                            float *dgate_b, float *dscale_w, float *dsigma, float *ws,
                            hipStream_t st) {
-  if (rows_far_apart(c)) {
+  if (rows_far_apart(c, 1)) {
     const wersa_desc dc = dense_desc(c);
     const size_t one = dense_floats(c);
     float *p = ws + fast_workspace_bytes(dc, 1) / sizeof(float);

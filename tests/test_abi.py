@@ -194,3 +194,14 @@ def test_backward_workspace_of_large_problems_holds_the_decisions_of_one_side(li
     """MFMA path, per row and slice: a bit per feature for one side's ReLU, dD and, by whole splits of n at most, nothing else."""
     a, b = (lib.wersa_workspace_bytes(ctypes.byref(_dense(1, H=8, n=n, d=d, m=m)), 1) for n in (524288, 1048576))
     assert 0 < b - a <= 8 * 524288 * (m // 8 + 4 + 4)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,n", [(2, 64), (64, 2048)])
+def test_forward_of_whole_blocks_needs_no_dense_copies_however_far_rows_are_apart(lib, d, H, n):
+    """The MFMA path's forward takes whole 64-row blocks at any row stride with the workspace of dense tensors, so that
+    wersa_forward_static takes them too."""
+    dense = _dense(1, H=H, n=n, d=d, m=256)
+    apart = _desc(dtype=1, H=H, n=n, d=d, m=256, stride_b=8, stride_h=d, stride_n=(1 << 27) + 8)
+    assert lib.wersa_selected_path(ctypes.byref(dense)) == lib.wersa_selected_path(ctypes.byref(apart)) == 1
+    assert lib.wersa_workspace_bytes(ctypes.byref(apart), 0) == lib.wersa_workspace_bytes(ctypes.byref(dense), 0) > 0

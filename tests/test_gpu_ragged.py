@@ -164,3 +164,31 @@ def test_contraction_with_eight_waves(n, flags):
     if not flags:
         assert spread < 4 and errs["dsigma"] < 3 * 2.0 ** -9 * spread, (spread, errs)
         assert all(errs[x] < 2e-2 for x in ("dk", "dq", "dgate_w", "dgate_b", "dscale_w")), errs
+
+
+@pytest.mark.parametrize("flags", [0, 8])
+def test_whole_blocks_with_rows_a_gibibyte_apart(flags):
+    """Eight rows of a store are further apart than 32 bits of bytes: the forward, with the library's own scratch, gives the bits of dense tensors."""
+    import torch
+    from paper_2507_08637_amd import binding
+    n, d, H, L, m, far = 64, 64, 2, 6, 128, (1 << 29) + 8
+    g = torch.Generator(device="cuda").manual_seed(n + flags)
+
+    def normal(*s):
+        return torch.randn(s, generator=g, device="cuda")
+
+    names = ("q", "k", "v", "out")
+    buf = torch.empty((n - 1) * far + len(names) * H * d, dtype=torch.bfloat16, device="cuda")   # 68 GB, of which four rows a GiB are touched
+    apart = {x: buf.as_strided((1, H, n, d), (8, d, far, 1), i * H * d) for i, x in enumerate(names)}
+    dense = {x: torch.zeros(1, H, n, d, dtype=torch.bfloat16, device="cuda") for x in names}
+    for x in names[:3]:
+        dense[x].copy_(normal(1, H, n, d) + 0.3)
+        apart[x].copy_(dense[x])
+    par = (normal(d, m).to(torch.bfloat16), torch.ones(1, device="cuda"), normal(H, L + 1, d) / d ** 0.5, normal(H, L + 1), 1 + 0.1 * normal(L + 1))
+    kept = []
+    for t in (dense, apart):
+        saved = torch.zeros(binding.wersa_saved_bytes(binding.make_desc(t["q"], L, m, flags=flags)) // 4, device="cuda")
+        binding.wersa_forward_static(t["q"], t["k"], t["v"], *par, L, t["out"], saved, flags=flags)
+        kept.append(saved)
+    torch.cuda.synchronize()
+    assert torch.equal(apart["out"], dense["out"]) and torch.equal(kept[0], kept[1])
