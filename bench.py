@@ -69,10 +69,6 @@ def kernel_models(cfg):
         "wersa_rows_fwd": ("mfma", "mfma_bf16", 2 * unit),       # projection + Phi S
         "wersa_grad_q": ("mfma", "mfma_bf16", 2 * unit),         # dPhi, dX_F (the ReLU's decisions come as bits)
         "wersa_grad_k": ("mfma", "mfma_bf16", 2 * unit),
-        # the same launches as they were while they repeated the projection (K side: with dV for whole 64-row blocks of
-        # head dimension 64 and 256 features per pass), for timings of such builds
-        "wersa_rows_bwd_q": ("mfma", "mfma_bf16", 3 * unit),
-        "wersa_rows_bwd_k": ("mfma", "mfma_bf16", (4 if (d == 64 and m % 256 == 0 and n % 64 == 0) else 3) * unit),
         "wersa_rows_bwd_v": ("mfma", "mfma_bf16", 2 * unit),     # projection, Phi dS
         "wersa_ln_prep": ("hbm", "hbm", 3 * nd * e),
         "wersa_add_pooled": ("hbm", "hbm", 2 * nd * e),

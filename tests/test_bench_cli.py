@@ -23,8 +23,9 @@ def test_kernel_models_count_the_contractions():
     unit = 2.0 * cfg["n"] * cfg["d"] * cfg["m"] * cfg["B"] * cfg["H"]
     m = bench.kernel_models(cfg)
     assert m["wersa_phiT_contract"][2] == 2 * unit and m["wersa_rows_fwd"][2] == 2 * unit
-    assert m["wersa_rows_bwd_q"][2] == 3 * unit and m["wersa_rows_bwd_k"][2] == 4 * unit   # with dV
+    assert m["wersa_grad_q"][2] == m["wersa_grad_k"][2] == m["wersa_rows_bwd_v"][2] == 2 * unit
     nd = cfg["n"] * cfg["d"] * cfg["B"] * cfg["H"]
     assert m["wersa_qbar"][2] == 2 * nd and m["wersa_add_pooled"][2] == 4 * nd            # bf16 bytes
     cfg3 = dict(cfg, n=cfg["n"] + 1)                                                       # partial last block:
-    assert bench.kernel_models(cfg3)["wersa_rows_bwd_k"][2] == 3 * 2.0 * cfg3["n"] * cfg["d"] * cfg["m"] * 8   # dV is its own launch
+    m3, unit3 = bench.kernel_models(cfg3), 2.0 * cfg3["n"] * cfg["d"] * cfg["m"] * 8
+    assert m3["wersa_grad_q"][2] == m3["wersa_grad_k"][2] == m3["wersa_rows_bwd_v"][2] == 2 * unit3

@@ -16,8 +16,10 @@ SHAPES = [
     (1, 16, 5632, 128),
     (3, 16, 4352, 128),
     (1, 8, 24576, 64),
-    # 256-wide tiles of eight steps, three of them in one workgroup and four in others
+    # 256-wide tiles of eight steps, 97 per XCD on 32 workgroups: four of them in one workgroup and three in the others
     (1, 4, 65792, 64),
+    # weight gradients: 31 splits of nine steps and one of a single step, two tiles per workgroup
+    (1, 16, 8960, 64),
 ]
 
 

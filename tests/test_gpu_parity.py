@@ -184,7 +184,7 @@ def _signal_problem(cfg, eps=1e-6, pooled=False, layernorm=False, separate_omega
 
 SIGNAL_CASES = {
     # one per kernel variant of the MFMA path (all at the plain 2e-2 on every output)
-    "d64_m256_dv_inside": (dict(B=1, H=2, n=2048, d=64, L=4, m=256), {}),
+    "d64_m256": (dict(B=1, H=2, n=2048, d=64, L=4, m=256), {}),
     "d64_m128": (dict(B=1, H=2, n=2048, d=64, L=5, m=128), {}),
     "d64_m512_two_chunks": (dict(B=1, H=2, n=2048, d=64, L=5, m=512), {}),
     "d64_one_level": (dict(B=1, H=2, n=2560, d=64, L=1, m=256), {}),
@@ -453,7 +453,7 @@ def test_separate_query_and_key_random_matrices(path):
     two matrices; both paths against the oracle given the same pair."""
     dtype = "f32" if path == "generic_f32" else "bf16"
     cfg = dict(B=2, H=2, n=256, d=64, L=4, m=128, dtype=dtype, flavour="plain", seed_base=3100, q_mean=0.4)
-    if path == "mfma256":   # 256 features per pass: the gradient kernels' other loop forms, dV inside the K-side kernel
+    if path == "mfma256":   # 256 features per pass: the rows and gradient kernels' other instances
         cfg.update(m=256)
         path = "mfma"
     p = workloads.make_inputs(**cfg)
@@ -557,7 +557,7 @@ def test_layernorm_output_stage_mfma_shapes(shape):
                                    dict(B=1, H=2, n=640, d=64, L=7, m=128),       # 10 tiles, pairs
                                    dict(B=1, H=2, n=1000, d=64, L=9, m=256),      # partial last tile: 15 tiles + 40 rows
                                    dict(B=1, H=1, n=100, d=64, L=7, m=128, noise=True),       # two tiles, the second partial (6.4e-2)
-                                   dict(B=1, H=1, n=2048, d=64, L=8, m=512, noise=True),      # two passes of 256 features (dV inside the K-side kernel) (2.7e-2)
+                                   dict(B=1, H=1, n=2048, d=64, L=8, m=512, noise=True),      # two passes of 256 features (2.7e-2)
                                    dict(B=1, H=2, n=1024, d=128, L=9, m=128),     # head dimension 128: stage A kernel takes the addends
                                    dict(B=2, H=1, n=4160, d=128, L=12, m=256),
                                    dict(B=1, H=1, n=1000, d=128, L=8, m=128)])    # ... with a partial last tile
@@ -598,7 +598,7 @@ def test_deep_transform_outside_the_mfma_shapes_takes_the_generic_path():
     _check_all(res, ref, TOL["bf16"], where="deep transform, default path")
 
 
-@pytest.mark.parametrize("shape", [dict(B=2, H=2, n=4096, d=64, L=6, m=256, dtype="bf16"),     # dV inside the K-side kernel
+@pytest.mark.parametrize("shape", [dict(B=2, H=2, n=4096, d=64, L=6, m=256, dtype="bf16"),     # 256 features per pass
                                    dict(B=1, H=2, n=1000, d=64, L=9, m=256, dtype="bf16"),     # partial last block, deep
                                    dict(B=1, H=2, n=2048, d=128, L=5, m=256, dtype="bf16"),
                                    dict(B=1, H=2, n=1500, d=48, L=4, m=80, dtype="f32")])      # generic path
@@ -617,7 +617,7 @@ def test_results_are_bitwise_reproducible(shape):
 
 
 @pytest.mark.parametrize("zero", ["K", "V", "Q"])
-@pytest.mark.parametrize("shape", [dict(B=1, H=2, n=320, d=64, L=4, m=256, dtype="bf16"),     # MFMA path, dV inside the K-side kernel
+@pytest.mark.parametrize("shape", [dict(B=1, H=2, n=320, d=64, L=4, m=256, dtype="bf16"),     # MFMA path, 256 features per pass
                                    dict(B=1, H=2, n=200, d=128, L=5, m=128, dtype="bf16"),    # head dimension 128, partial last block
                                    dict(B=1, H=2, n=200, d=32, L=3, m=48, dtype="f32")])      # generic path
 def test_degenerate_all_zero_operand(shape, zero):

@@ -2,17 +2,23 @@
 seen.  Rows and random features of +-1 with an odd number of non-zero columns and a transform of no levels make every
 pre-activation an odd multiple of the filter's one coefficient: no decision is at the edge of a rounding, and a row of dQ or dK
 misses or has too much by one of about m / 2 terms where a bit is wrong, sqrt(2 / m) >= 5.5e-2 of its norm (m <= 640).  Against
-float64: rounding of dPhi's 2^-9 per term, of O and of the row itself, below 2e-2 of a row's norm."""
+float64: rounding of dPhi's 2^-9 per term, of O and of the row itself, below 2e-2 of a row's norm.
+
+FEW slices: one 64-row block per contraction workgroup and one row group per workgroup of the gradient kernels.  MANY slices: several of
+both (asserted), so that running offsets, requests for the next group and words read anew in every pass are seen, and eight waves
+per contraction workgroup at head dimension 128 with whole 256s of features."""
 import pytest
 
 pytestmark = pytest.mark.gpu
 
-# tiles of 32 and 64 rows, groups of 256 and 512 rows, several groups per workgroup; 128 and 256 features per pass, one to five passes
-CASES = ([(n, 64, m) for n, m in ((32, 256), (64, 128), (97, 384), (513, 256), (1000, 512), (1025, 640), (8200, 256), (8200, 128))]
-         + [(n, 128, m) for n, m in ((32, 256), (65, 128), (257, 384), (1000, 512), (4100, 256))])
+# tiles of 32 and 64 rows, up to 17 groups of 512 or 256 rows; 128 and 256 features per pass, one to five passes
+FEW = ([(6 if n <= 4000 else 3, n, 64, m) for n, m in ((32, 256), (64, 128), (97, 384), (513, 256), (1000, 512), (1025, 640), (8200, 256), (8200, 128))]
+       + [(6 if n <= 4000 else 3, n, 128, m) for n, m in ((32, 256), (65, 128), (257, 384), (1000, 512), (4100, 256))])
+MANY = ([(96, n, 64, m) for n, m in ((1088, 128), (1100, 256), (1100, 384), (1088, 512))]
+        + [(64, n, 128, m) for n, m in ((1088, 256), (1100, 256), (1100, 384), (1121, 512))])
 
 
-def reference(q, k, v, dout, omega, sigma, gw, gb, sw, eps):
+def reference(q, k, v, dout, omega, sigma, gw, gb, sw, eps, layernorm):
     import torch
     x = [t.double().requires_grad_(True) for t in (q, k, v)]
     qd, kd, vd = x
@@ -20,15 +26,31 @@ def reference(q, k, v, dout, omega, sigma, gw, gb, sw, eps):
     om = omega.double() / sigma.double() / omega.shape[-1] ** 0.5
     pq, pk = (torch.relu((f[..., None, None] * t) @ om) for t in (qd, kd))
     s, z = pk.transpose(2, 3) @ vd, pk.sum(2)
-    out = (pq @ s) / (pq @ z[..., None] + eps)
+    out = pq @ s
+    if layernorm:
+        out = (out - out.mean(-1, keepdim=True)) / (out.var(-1, unbiased=False, keepdim=True) + eps).sqrt()
+    else:
+        out = out / (pq @ z[..., None] + eps)
     return torch.autograd.grad(out, x, dout.double())
 
 
-@pytest.mark.parametrize("n,d,m", CASES)
-def test_every_decision(n, d, m):
+def plan(slices, n, d, m):
+    """Blocks per contraction workgroup and row groups of a gradient kernel's workgroup with the most: the library's split."""
+    blocks = -(-n // 64)
+    features = 256 if d == 64 and m % 256 == 0 else 128
+    want = min(max(512 // (slices * (m // features)), 1), blocks)
+    groups = -(-n // (512 if d == 64 else 256))
+    return -(-blocks // want), -(-groups // min(max(256 // slices, 1), groups))
+
+
+@pytest.mark.parametrize("slices,n,d,m,flags", [c + (0,) for c in FEW + MANY] + [c + (8,) for c in MANY])
+def test_every_decision(slices, n, d, m, flags):
     import torch
     from paper_2507_08637_amd import binding
-    B, H, L = (1, 3, 0) if n > 4000 else (2, 3, 0)
+    B, H, L = slices // 3, 3, 0
+    if slices > 6:
+        B, H = slices // 4, 4
+        assert min(plan(slices, n, d, m)) >= 2
     g = torch.Generator(device="cuda").manual_seed(n + d + m)
 
     def normal(*s):
@@ -39,14 +61,14 @@ def test_every_decision(n, d, m):
     v, dout = (normal(B, H, n, d).to(torch.bfloat16) for _ in range(2))
     sigma, gw, gb, sw = torch.ones(1, device="cuda"), normal(H, 1, d) / d ** 0.5, normal(H, 1), torch.ones(1, device="cuda")
     assert binding.load_library().wersa_selected_path(binding.make_desc(q, L, m)) == 1
-    out, saved = binding.wersa_forward(q, k, v, omega, sigma, gw, gb, sw, L)
-    got = binding.wersa_backward(q, k, v, omega, sigma, gw, gb, sw, out, dout, saved, L)
-    ref = reference(q, k, v, dout, omega, sigma, gw, gb, sw, 1e-6)
+    out, saved = binding.wersa_forward(q, k, v, omega, sigma, gw, gb, sw, L, flags=flags)
+    got = binding.wersa_backward(q, k, v, omega, sigma, gw, gb, sw, out, dout, saved, L, flags=flags)
+    ref = reference(q, k, v, dout, omega, sigma, gw, gb, sw, 1e-6, flags == 8)
     worst = {}
     for name, r in zip(("dq", "dk", "dv"), ref):
         e = (got[name].double() - r).norm(dim=-1) / r.norm(dim=-1).clamp_min(0.1 * float(r.norm(dim=-1).mean()))
         worst[name] = float(e.max())
-    print((n, d, m), {x: f"{e:.1e}" for x, e in worst.items()}, flush=True)
+    print((slices, n, d, m, flags), {x: f"{e:.1e}" for x, e in worst.items()}, flush=True)
     assert max(worst.values()) < 2e-2, worst
 
 
