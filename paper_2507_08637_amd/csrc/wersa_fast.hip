@@ -1208,21 +1208,17 @@ __global__ __launch_bounds__(kWavesApply * 64, 2) void rows_kernel(
       __builtin_amdgcn_wave_barrier();
       // (one column tile at a time: the 256-register budget has no room for four accumulators next to the operands
       // being built)
-      constexpr int CG = 1;   // column tiles per pass
 #pragma unroll
-      for (int c0 = 0; c0 < CT; c0 += CG) {
-        f32x16 q[CG][2];
+      for (int ct = 0; ct < CT; ++ct) {
+        f32x16 q[2];
+        q[0] = zero16();
+        if (DEEP) {
+          // register i stands for column 32 ct + (acc_row(i, h) with bits 2 and 3 swapped), every lane's row alike
+          const float *ta = tile_add + ((int64_t)slice * ((n + 63) / 64) + t0 / 64) * DH + 32 * ct;
 #pragma unroll
-        for (int cg = 0; cg < CG; ++cg) {
-          q[cg][0] = zero16();
-          if (DEEP) {
-            // register i stands for column 32 ct + (acc_row(i, h) with bits 2 and 3 swapped), every lane's row alike
-            const float *ta = tile_add + ((int64_t)slice * ((n + 63) / 64) + t0 / 64) * DH + 32 * (c0 + cg);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) q[cg][0][i] = ta[16 * (i >> 3) + 8 * h + 4 * ((i >> 2) & 1) + (i & 3)];
-          }
-          q[cg][1] = q[cg][0];
+          for (int i = 0; i < 16; ++i) q[0][i] = ta[16 * (i >> 3) + 8 * h + 4 * ((i >> 2) & 1) + (i & 3)];
         }
+        q[1] = q[0];
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
           bf16x8 gop[2][2];
@@ -1231,25 +1227,20 @@ __global__ __launch_bounds__(kWavesApply * 64, 2) void rows_kernel(
             gop[tt][0] = filter_operand(s_T, 0, 32 * tt + l32, 2 * ks + h);
             gop[tt][1] = filter_operand(s_T, 1, 32 * tt + l32, 2 * ks + h);
           }
+          const bf16x8 xa = tile_cols_operand<true>(panels + ct * (64 * TS), TS, 0, ks, lane);
+          // The low part matters inside the row tile's own 32-row half only: across the halves
+          // every entry of G is the single coarsest-level coefficient.
 #pragma unroll
-          for (int cg = 0; cg < CG; ++cg) {
-            const bf16x8 xa = tile_cols_operand<true>(panels + (c0 + cg) * (64 * TS), TS, 0, ks, lane);
-            // The low part matters inside the row tile's own 32-row half only: across the halves
-            // every entry of G is the single coarsest-level coefficient.
-#pragma unroll
-            for (int tt = 0; tt < 2; ++tt) {
-              q[cg][tt] = mfma_bf16(xa, gop[tt][0], q[cg][tt]);
-              if ((ks >> 1) == tt) q[cg][tt] = mfma_bf16(xa, gop[tt][1], q[cg][tt]);
-            }
+          for (int tt = 0; tt < 2; ++tt) {
+            q[tt] = mfma_bf16(xa, gop[tt][0], q[tt]);
+            if ((ks >> 1) == tt) q[tt] = mfma_bf16(xa, gop[tt][1], q[tt]);
           }
         }
 #pragma unroll
-        for (int cg = 0; cg < CG; ++cg)
-#pragma unroll
-          for (int tt = 0; tt < 2; ++tt) {
-            xb[tt][2 * (c0 + cg)] = pack_half_f16(q[cg][tt], 0);
-            xb[tt][2 * (c0 + cg) + 1] = pack_half_f16(q[cg][tt], 1);
-          }
+        for (int tt = 0; tt < 2; ++tt) {
+          xb[tt][2 * ct] = pack_half_f16(q[tt], 0);
+          xb[tt][2 * ct + 1] = pack_half_f16(q[tt], 1);
+        }
       }
     }
     // N or dV, rows on lanes: register i of half-wave h is column 32 ct + 16 (i / 8) + 8 h + i % 8 of row 32 ti + l32, so that the row's
@@ -1409,12 +1400,12 @@ __device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t voff, const voi
 // X comes straight from memory into the wave's panels, one of 4 KiB per 32 columns ([64 rows][32], requested a row group ahead), and
 // dX goes out through the same panel ([32 columns][64 rows]: 16-byte piece q of column c at slot q ^ (c % 8)).
 // ------------------------------------------------------------------------------------
-template <int MODE, int MC, int NW, bool RAGGED, bool DEEP>
-__global__ __launch_bounds__(NW * 64, 2) void masked_rows_kernel(
+template <int MODE, int MC, bool RAGGED, bool DEEP>
+__global__ __launch_bounds__(kWavesApply * 64, 2) void masked_rows_kernel(
     const bf16_t *x, View vx, const bf16_t *y, View vy, const float *Dsaved, const float *arow, const uint32_t *bits,
     const bf16_t *omega, const bf16_t *Mx, const float *coef, int n, int m, int row_groups, bf16_t *out, View vo,
     float *partF, int L, float *tile_gsum) {
-  constexpr int DH = 64, KS = 4, KSX = 5, CT = 2, NT = NW * 64;
+  constexpr int DH = 64, KS = 4, KSX = 5, CT = 2, NW = kWavesApply, NT = NW * 64;
   constexpr int AM = DH + 16 + 8, BS = MC + 8, WORDS = MC / 64;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   bf16_t *s_Mx = reinterpret_cast<bf16_t *>(smem_raw);                      // [MC][AM]: (S | z) or (dS | dz)
@@ -1824,8 +1815,8 @@ __global__ __launch_bounds__(NW * 64, 2) void masked_rows_kernel(
     partF[((int64_t)slice * rows + blockIdx.x) * (L + 1) + tid] = tid < L ? ul - ul1 : ul;
   }
 }
-constexpr size_t masked_smem_bytes(int mc, int nw) {
-  return (size_t)mc * 88 * 2 + (size_t)64 * (mc + 8) * 2 + nw * 64 * 4 + (size_t)nw * 8192;
+constexpr size_t masked_smem_bytes(int mc) {
+  return (size_t)mc * 88 * 2 + (size_t)64 * (mc + 8) * 2 + kWavesApply * 64 * 4 + (size_t)kWavesApply * 8192;
 }
 
 // ------------------------------------------------------------------------------------
@@ -2779,11 +2770,11 @@ hipError_t launch_masked64(const wersa_desc &c, const FastPlan &p, const bf16_t 
   if ((c.flags & WERSA_FLAG_SEPARATE_OMEGA) && MODE == 2) omega += (int64_t)c.d * c.m;
   const View tv{c.stride_b, c.stride_h, c.stride_n, c.H};
   auto go = [&](auto kern) -> hipError_t {
-    const size_t smem = masked_smem_bytes(p.mc, 8);
+    const size_t smem = masked_smem_bytes(p.mc);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
     WERSA_STAGE(MODE == 1 ? "wersa_grad_q" : "wersa_grad_k", st,
-                kern<<<dim3(p.rowsWgs, c.B * c.H), 8 * 64, smem, st>>>(
+                kern<<<dim3(p.rowsWgs, c.B * c.H), kWavesApply * 64, smem, st>>>(
                     x, tv, y, yview ? *yview : tv, Dsaved, arow, MODE == 1 ? w.bitsQ : w.bitsK, omega, Mx, w.coef, c.n, c.m,
                     p.rowGroups, out, tv, partF, c.L, MODE == 1 ? w.gsumQ : w.gsumK));
     return hipSuccess;
@@ -2791,8 +2782,8 @@ hipError_t launch_masked64(const wersa_desc &c, const FastPlan &p, const bf16_t 
   const bool ragged = c.n % 64 != 0, deep = c.L > kTileL;
   auto pick = [&](auto MC) -> hipError_t {
     constexpr int M = MC.value;
-    if (deep) return ragged ? go(&masked_rows_kernel<MODE, M, 8, true, true>) : go(&masked_rows_kernel<MODE, M, 8, false, true>);
-    return ragged ? go(&masked_rows_kernel<MODE, M, 8, true, false>) : go(&masked_rows_kernel<MODE, M, 8, false, false>);
+    if (deep) return ragged ? go(&masked_rows_kernel<MODE, M, true, true>) : go(&masked_rows_kernel<MODE, M, false, true>);
+    return ragged ? go(&masked_rows_kernel<MODE, M, true, false>) : go(&masked_rows_kernel<MODE, M, false, false>);
   };
   return p.mc == 256 ? pick(std::integral_constant<int, 256>{}) : pick(std::integral_constant<int, 128>{});
 }
