@@ -67,17 +67,20 @@ __device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t voff, const bf1
 // 16 k are read between the matrix instructions of the current ones, across the stage boundary too (a stage is
 // known to have landed one step before it is needed), and global loads have two steps (2048 cycles) to land.  Reads and
 // requests are spread over the 16 instructions of a half, one or the other after most of them: all reads in the first half
-// of them and all requests in the second met the peak rates of LDS and of the load path.  Beyond that it is power: per tile of
-// 256 x 256 x 2048 (65.5 thousand cycles of matrix instructions) NN takes 91.1 thousand cycles at 1665 MHz, and took 95.4 at
-// 1720 before, TN 8 % fewer at a clock 5 % lower; a fifth stage, or one workgroup per tile, is slower.
+// of them and all requests in the second met the peak rates of LDS and of the load path.  The clock falls as the matrix
+// units get busier: per tile of 256 x 256 x 2048 (65.5 thousand cycles of matrix instructions) NN takes 91.1 thousand cycles at 1665 MHz, and
+// took 95.4 at 1720 before, TN 8 % fewer at a clock 5 % lower.  TN, its matrix cores 85 % busy, is limited by power; NN and NT leave them idle
+// for 28 and 32 % of the cycles, why is not shown (requests of operands contiguous along k are half lines: TN has none, NN one, NT two).  A
+// fifth stage, or one workgroup per tile, is slower.
 //
 // A workgroup of WT = 128 takes several tiles, one after the other (one per compute unit in flight).  The stages of its tiles are one
 // sequence, so the first stages of the next tile are on their way while the last products and the stores of this one are made;
 // the tile leaves through the stage that was computed on last.  bf16 output without column sums: the operands of the matrix
 // instruction are exchanged, and B's rows or columns taken with bits 2 and 3 of their number exchanged, so that a lane holds 16-byte
 // pieces of its own row of C (32 LDS writes per wave and tile of 128 x 128 instead of 256 two-byte ones).
-// Measured (131072 tokens, hidden 2048, us per product): NN 877 -> 813 (890 with column sums), NT 874 -> 826, TN 831 -> 786;
-// block training step 15344 -> 14980.  1.1 PFLOP takes 580 us at the 1.9 PFLOP/s that a bare loop of the instruction sustains.
+// Measured against one tile per workgroup and rows on registers (131072 tokens, hidden 2048, 25 training steps of each in turn on one card,
+// us per product): NN with column sums 953 -> 921, without 957 -> 858; NT one product 1016 -> 964, sum of three 915 -> 890; TN
+// 846 -> 822.  1.1 TFLOP takes 580 us at the 1.9 PFLOP/s that a bare loop of the instruction sustains.
 //
 // Logical tiles are dealt to the eight XCDs in contiguous runs (workgroup w runs on XCD w % 8); a run goes down
 // kGroupM row panels before it takes the next column panel, so that the 32 workgroups of an XCD at a time share

@@ -354,7 +354,8 @@ __device__ __forceinline__ bf16x8 relu_bf16x8(bf16x8 p) {
 // sixteen blocks of four lanes, with the weights of the lane's half-wave in every column.  Accumulator i of a lane is the sum of lane
 // 4 (lane / 4) + i; own() picks its own.  Two of them per eight values take 8 cycles each of the matrix pipe; pair dot products do not run
 // beside matrix instructions either and take 7.5 each, four per eight values.  Forward rows kernel, 8 slices of 131072 rows, m 256: 94.9 -> 90.0 us,
-// 64 of 4096, m 128: 20.8 -> 19.8; in phiT_contract, which waits at its barriers, and at head dimension 128 nothing or less.
+// 64 of 4096, m 128: 20.8 -> 19.8; in phiT_contract, which waits at its barriers, and at head dimension 128 nothing or less.  D against
+// float64 sums of the same operands: 2.2e-7 rms at 4096 features, 2.55e-7 with pair dot products.
 struct WeightedSum {
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   __device__ __forceinline__ void add(bf16x8 p, bf16x8 w) {
@@ -1391,8 +1392,10 @@ __device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t voff, const voi
 // Eight waves of 64 rows, two per SIMD with 256 registers each, so that one wave's epilogue runs under the other's matrix
 // instructions; the feature-side operands of MC features are staged once per workgroup (once per pass and row group
 // where there are more).
-// What bounds it: memory.  8 slices of 131072 rows, m 256 move 417 MB (key side: X and V in, bits in, dX out), 73 us at the rate of a
-// large copy, in 107; without seven eighths of the feature loop it takes 87, without the epilogue's arithmetic 102.
+// What bounds it: no single unit.  8 slices of 131072 rows, m 256, key side (query side): 384 MiB of X, V (dO) and dX and 32 (40) of bits (dD
+// and D too) are necessary in this form, 453 (461) move by the counters (in its last round a wave requests its own rows again), 83 (85) us at the 5.7 TB/s of
+// a large copy; it takes 107 (116).  Without seven eighths of the feature loop the key side takes 87, without the epilogue's arithmetic 102; matrix cores 38 %
+// busy, vector units 55 %.
 // The kernel before it formed the projection, too, with one wave of 512 registers per SIMD: 175 us on the query side, 235 on the key
 // side with dV beside dX_F; now 116 and 107, and 84 for dV (its kernel has the projection in hand and leaves the bits).
 // A lane's row: operand row l32 of dN or V is row 32 ti + r with r's bits (l0, l1, l3, l4, l2), so that the accumulator registers of
