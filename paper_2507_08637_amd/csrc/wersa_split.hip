@@ -9,16 +9,15 @@
 // matrix rate is 16 times the float32 one, so even six products leave a factor of 2.7.
 //
 // What bounds it: per 32 x 32 tile of a feature matrix the matrix cores spend 32 cycles per product and 16 of the
-// contraction's length (and where they form the residuals, four more products), the vector units 5.5 instructions per
+// contraction's length (and where they form the residuals, two sparse ones), the vector units 5.5 instructions per
 // element on the split and two on ReLU or mask.  Counters (128 slices of 4000 tokens, d 32, m 1024, float32, and 8 of
 // 131072, d 16, bf16): matrix cores busy 63 to 73 and 72 to 80 % of a SIMD's cycles in the four contraction kernels,
 // vector units 50 to 60 and 45 to 56 %; two waves per SIMD let one run under the other.  From d 64 on the matrix cores
-// alone.  Scratch: grad_kernel with dV at d 64 88 bytes per lane, without dV at d 16 with three-term operands 16 (accumulators
-// and operands fill the 256 registers).
+// alone.  Scratch: grad_kernel with dV at d 64 88 bytes per lane (accumulators and operands fill the 256 registers).
 //
 // Measured against the generic kernels, which write every n x m feature matrix to memory: float32 training step, 128
 // slices of 4000 tokens, d 32, m 1024: 13990 -> 2463 us; bf16 training step, 8 slices of 131072 tokens, d 16, m 1024:
-// 26290 -> 2271 us; float32 inference, one slice of 1024 tokens, d 64, m 64: 118 -> 34 us.
+// 26290 -> 2150 us; float32 inference, one slice of 1024 tokens, d 64, m 64: 118 -> 34 us.
 //
 // Layout: every operand is kept in the order in which a wave loads it ("operand tile": 32 vectors x 16
 // k-values of bf16; lane (l32, h) holds vector l32, k = 8 h .. 8 h + 7, 16 bytes; 1 KiB).  Where k runs
@@ -42,6 +41,7 @@ namespace {
 #include "wersa_filter.inc"
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -85,20 +85,25 @@ __device__ __forceinline__ void split8(const float *v, bf16x8 *t) {
 }
 // Split of an accumulator tile into operands (t[a][i]: half a, term i).  The vector units take 5.5 instructions per
 // element for it, most of them for the two residuals x - x0 and x - x0 - x1.  LV of these come from the matrix
-// cores instead: x - bf16(x) is the accumulator plus the product of the packed term with a negated identity
-// matrix whose columns are in the order of the k-slots, two instructions for the 16 values per lane, and exact (one
-// non-zero product per element).  Measured (one SIMD, four waves): a matrix instruction takes 32 cycles of its
+// cores instead: x - bf16(x) is the accumulator plus the product of a negated identity matrix, its columns in the order of the
+// k-slots, with the packed term.  One entry per row is sparse enough for the 2:4 instruction, which takes all 32 rows of the term
+// at once, and it is exact (one non-zero product per element; every value of 131072 with exponents from -125 to 124 equal to
+// the subtraction's).  Measured (one SIMD, four waves): a matrix instruction takes 32 cycles of its
 // own pipe and keeps the vector units from issuing for about 15, a vector instruction takes 4; a pair dot
 // product (v_dot2c_f32_bf16, which would do a residual in one instruction) does not run beside matrix
-// instructions at all.
+// instructions at all.  A loop of split and products, two waves per SIMD, ns per 32 x 32 tile with both residuals from the vector
+// units / from two dense 32 x 32 x 16 products each / four 4 x 4 x 4 / one sparse one: 24 products 477 / 447 / 439 / 395,
+// 8 products 241 / 207 / 226 / 193.
 struct NegIdentity {
-  bf16x8 half[2];
+  bf16x8 a;    // the stored two of every four entries: lane (row, half of the 32 k-slots)
+  int index;   // which two, 2 bits each
   __device__ __forceinline__ explicit NegIdentity(int lane) {
+    // Row r of the tile is in k-slot 16 (r / 16) + 8 (r / 4 % 2) + 4 (r / 8 % 2) + r % 4; a lane stores two entries, their places
+    // ascending, of each of its four groups of four slots.
+    const int r = lane & 31, place = r & 3, entry = 4 * (r >> 2 & 1) + 2 * (r >> 3 & 1) + (place == 3);
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int q = 0; q < 8; ++q)
-        half[a][q] = (__bf16)((lane & 31) == 16 * a + 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3) ? -1.f : 0.f);
+    for (int q = 0; q < 8; ++q) a[q] = (__bf16)(lane >> 5 == r >> 4 && q == entry ? -1.f : 0.f);
+    index = (place == 3 ? 0xC : 0xC | place) * 0x1111;
   }
 };
 // Calls use(a, terms) for both halves.
@@ -135,15 +140,18 @@ __device__ __forceinline__ void with_split(f32x16 x, const NegIdentity &ni, F us
         }
       }
     if (i < LV) {
-      x = mfma(ni.half[0], t[0][i], x);
-      x = mfma(ni.half[1], t[1][i], x);
+      const bf16x16 term = __builtin_shufflevector(t[0][i], t[1][i], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
+      x = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(ni.a, term, x, ni.index, 0, 0);
     }
   }
   use(0, t[0]);
   use(1, t[1]);
 }
-// Residuals left to the matrix cores, by what is idle: with head dimensions 16 and 32 the contractions are too short to
-// fill them.
+// Residuals left to the matrix cores, by what is idle: with head dimension 16, and 32 with one-term operands, the contractions are
+// too short to fill them.  Training step, both residuals as two dense products each -> one sparse product each, the same bits: 8 slices of
+// 131072 tokens, d 16, m 1024, bf16 2286 -> 2150 us; 32 of 16384, d 32, m 512, bf16 1042 -> 1018; d 16, float32 1054 -> 1025.  The vector units'
+// residuals against sparse ones with d 32 and three terms: contraction 333, 331 us, gradients 747, 730 and 525, 572, apply 344, 371
+// (registers); with d 64 and 128 equal.
 constexpr int mfma_residuals(int DH, int PT) { return DH == 16 || (DH == 32 && PT == 1) ? 2 : 0; }
 __device__ __forceinline__ void split1(float x, __bf16 *t) {
   t[0] = (__bf16)x;
