@@ -10,14 +10,12 @@
 //
 // What bounds it: per 32 x 32 tile of a feature matrix the matrix cores spend 32 cycles per product and 16 of the
 // contraction's length (and where they form the residuals, two sparse ones), the vector units 5.5 instructions per
-// element on the split and two on ReLU or mask.  Counters (128 slices of 4000 tokens, d 32, m 1024, float32, and 8 of
-// 131072, d 16, bf16): matrix cores busy 63 to 73 and 72 to 80 % of a SIMD's cycles in the four contraction kernels,
-// vector units 50 to 60 and 45 to 56 %; two waves per SIMD let one run under the other.  From d 64 on the matrix cores
+// element on the split and two on ReLU or mask; two waves per SIMD let one run under the other.  From d 64 on the matrix cores
 // alone.  Scratch: grad_kernel with dV at d 64 88 bytes per lane (accumulators and operands fill the 256 registers).
 //
 // Measured against the generic kernels, which write every n x m feature matrix to memory: float32 training step, 128
-// slices of 4000 tokens, d 32, m 1024: 13990 -> 2463 us; bf16 training step, 8 slices of 131072 tokens, d 16, m 1024:
-// 26290 -> 2150 us; float32 inference, one slice of 1024 tokens, d 64, m 64: 118 -> 34 us.
+// slices of 4000 tokens, d 32, m 1024: 13990 -> 2350 us; bf16 training step, 8 slices of 131072 tokens, d 16, m 1024:
+// 26290 -> 2100 us; float32 inference, one slice of 1024 tokens, d 64, m 64: 118 -> 34 us.
 //
 // Layout: every operand is kept in the order in which a wave loads it ("operand tile": 32 vectors x 16
 // k-values of bf16; lane (l32, h) holds vector l32, k = 8 h .. 8 h + 7, 16 bytes; 1 KiB).  Where k runs
@@ -150,9 +148,12 @@ __device__ __forceinline__ void with_split(f32x16 x, const NegIdentity &ni, F us
 // Residuals left to the matrix cores, by what is idle: with head dimension 16, and 32 with one-term operands, the contractions are
 // too short to fill them.  Training step, both residuals as two dense products each -> one sparse product each, the same bits: 8 slices of
 // 131072 tokens, d 16, m 1024, bf16 2286 -> 2150 us; 32 of 16384, d 32, m 512, bf16 1042 -> 1018; d 16, float32 1054 -> 1025.  The vector units'
-// residuals against sparse ones with d 32 and three terms: contraction 333, 331 us, gradients 747, 730 and 525, 572, apply 344, 371
-// (registers); with d 64 and 128 equal.
-constexpr int mfma_residuals(int DH, int PT) { return DH == 16 || (DH == 32 && PT == 1) ? 2 : 0; }
+// residuals against one and two sparse ones with d 32 and three terms: contraction 333, 329, 331 us, key side's gradient 747, 729, 730, apply
+// 344, 358, 371 (registers); with d 64 and 128 equal.
+// spare: a kernel with registers for one of them at head dimension 32 with three terms.
+constexpr int mfma_residuals(int DH, int PT, bool spare = false) {
+  return DH == 16 || (DH == 32 && PT == 1) ? 2 : (DH == 32 && spare ? 1 : 0);
+}
 __device__ __forceinline__ void split1(float x, __bf16 *t) {
   t[0] = (__bf16)x;
   const float r = x - (float)t[0];
@@ -214,6 +215,67 @@ __device__ __forceinline__ float relu(float x) {
 }
 // x where mask is 1, 0 where it is 0, also for NaN and infinities (0 times anything is 0 in this instruction).
 __device__ __forceinline__ float masked(float x, float mask) { return amdgcn_mul_legacy(x, mask); }
+
+// ------------------------------------------------------------------------------------
+// The ReLU's decisions as bits.  A gradient kernel needs of the projection only which elements were positive, and the kernel that has the
+// projection in hand anyway (the contraction on the query side, the one of dV at head dimension 128 on the key side) writes it down:
+// one 16-bit word per lane and 32 x 32 tile, n m / 8 bytes per slice, bits[slice][token tile][feature tile][64].  That is a third of
+// the gradient kernel's products, its operands in LDS and the rows of X in registers less.
+// A lane has 16 elements of a tile, with features on registers its token l32 and the features f with f / 4 % 2 = h, with tokens on registers
+// the other way round; with r the register's number, word bit 8 (r % 2) + r / 2 % 2 + 2 (r / 4 % 2) + 4 (r / 8) is its element.
+// Word bits 3, 0, 1, 2 and lane bits 0, 1, 3, 4 thus are bits 0, 1, 3, 4 of token and feature, or of feature and token: to go from one
+// form to the other they change places, and lane bits 2 and 5 too (by where a lane's word is stored).  In memory: tokens on word bits,
+// bit 2 of the token on bit 2 of the place.
+// ------------------------------------------------------------------------------------
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ int decision_bit(int r) { return 8 * (r & 1) + (r >> 1 & 1) + 2 * (r >> 2 & 1) + 4 * (r >> 3); }
+// Of the leading terms of the two halves of a tile after the ReLU, two instructions per pair (a positive value that is no zero in bf16
+// counts as one: above 2^-134).
+__device__ __forceinline__ uint32_t decisions(const bf16x8 (&lead)[2]) {
+  u16x2 one = {1, 1};
+  asm("" : "+s"(one));   // (of min(x, 1) the compiler makes two comparisons and two selections)
+  uint32_t w = 0;
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {   // elements 2 j, 2 j + 1 of half a: bits 4 a + j % 2 + 2 (j / 2) of the two halves of the word
+      bf16x2 e;
+      e[0] = lead[a][2 * j];
+      e[1] = lead[a][2 * j + 1];
+      const uint32_t b = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, e), one));
+      w |= b << (4 * a + j);
+    }
+  return __builtin_amdgcn_perm(w, w, 0x0C0C0200);
+}
+// Exchanges word bits 3, 0, 1, 2 with lane bits 0, 1, 3, 4, in both halves of the word.
+struct TransposeDecisions {
+  uint32_t sel, mask[3], rot[3];
+  __device__ __forceinline__ explicit TransposeDecisions(int lane) {
+    sel = lane & 1 ? 0x03070105u : 0x06020400u;
+    const uint32_t m[3] = {0x55555555u, 0x33333333u, 0x0F0F0F0Fu};
+    const int bit[3] = {2, 8, 16};
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      mask[i] = lane & bit[i] ? ~m[i] : m[i];
+      rot[i] = lane & bit[i] ? 1u << i : 32u - (1u << i);
+    }
+  }
+  __device__ __forceinline__ uint32_t operator()(uint32_t w) const {
+    // bytes 0 and 2: word bit 3 clear.  An even lane keeps them and takes the other's as its bytes 1 and 3.
+    const uint32_t t = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0xB1, 0xF, 0xF, false);   // lane ^ 1
+    w = __builtin_amdgcn_perm(t, w, sel);
+    auto merge = [&](uint32_t other, int i) { w = (w & mask[i]) | (__builtin_amdgcn_alignbit(other, other, rot[i]) & ~mask[i]); };
+    merge((uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x4E, 0xF, 0xF, false), 0);    // lane ^ 2
+    merge((uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x128, 0xF, 0xF, false), 1);   // lane ^ 8
+    const auto r = __builtin_amdgcn_permlane16_swap(w, w, false, false);                  // lane ^ 16: the row that is not this lane's
+    merge(mask[2] & 1 ? r[1] : r[0], 2);
+    return w;
+  }
+};
+// x where the word's bit of register r is set, 0 where it is not (also for NaN and infinities); half: which half of the word.
+__device__ __forceinline__ float masked(float x, uint32_t word, int r, int half) {
+  return __uint_as_float(__float_as_uint(x) & (uint32_t)__builtin_amdgcn_sbfe((int)word, 16 * half + decision_bit(r), 1));
+}
 
 // Product of the 16 values of an accumulator tile that a lane holds with 16 weights.  D and z are sums of these, D of eight
 // at a time: one chain over all features or tokens is four times as far from the exact sum at 4096 features.
@@ -645,9 +707,10 @@ __global__ __launch_bounds__(256) void prep_bwd_kernel(const T *dout, const T *o
 // Token tiles (32 rows) per stage: the double-buffered stage stays below 100 KiB of LDS, and below 50 KiB where that lets
 // the registers of a second workgroup in (head dimension 32 with three terms: 359 -> 334 us with half the stage).
 constexpr int stage_tokens(int DH, int PT) { return DH == 128 ? 1 : (DH == 64 || (DH == 32 && PT == 3) ? 2 : 4); }
-template <int DH, int PT>
+template <int DH, int PT, bool BITS>
 __global__ __launch_bounds__(512, 2) void contract_kernel(const bf16_t *X, const bf16_t *Y, const float *w, const bf16_t *OA,
-                                                         Dims s, int FW, int TW, int tiles_per_split, float *part, float *zpart) {
+                                                         Dims s, int FW, int TW, int tiles_per_split, float *part, float *zpart,
+                                                         unsigned short *bits) {
   using G = Geo<DH>;
   constexpr int SG = stage_tokens(DH, PT), NX = G::KS * 3, NY = 2 * G::CT * PT, NS = SG * (NX + NY),
                 NW = 8, U = (NS + NW - 1) / NW;
@@ -721,7 +784,9 @@ __global__ __launch_bounds__(512, 2) void contract_kernel(const bf16_t *X, const
           for (int j = 0; j < 4; ++j) w4[j] = *reinterpret_cast<const f32x4 *>(&lw[b][g * 32 + 8 * j + 4 * h]);
           zacc += dot16(R, w4);
         }
-        with_split<mfma_residuals(DH, PT)>(R, ni, [&](int a, const bf16x8 *p) {
+        bf16x8 lead[2];
+        with_split<mfma_residuals(DH, PT, true)>(R, ni, [&](int a, const bf16x8 *p) {
+          if (BITS) lead[a] = p[0];
 #pragma unroll
           for (int ct = 0; ct < G::CT; ++ct) {
             bf16x8 y[PT];
@@ -730,6 +795,9 @@ __global__ __launch_bounds__(512, 2) void contract_kernel(const bf16_t *X, const
             add_terms<PT>(acc[ct], LO ? lo[LO ? ct : 0] : acc[ct], p, y);   // rows: features, columns: columns of Y
           }
         });
+        if (BITS)
+          bits[(((int64_t)slice * s.nt + tb + g) * s.mt + ft) * 64 + ((lane & ~36) | (lane & 4) << 3 | (lane & 32) >> 3)] =
+              (unsigned short)decisions(lead);
       }
       if (more) put(b ^ 1);
       __syncthreads();
@@ -910,8 +978,10 @@ constexpr int row_occupancy(int DH, int NW) { return NW >= 4 && DH < 128 ? 2 : 1
 template <typename T, int DH, int PT, int MODE, int RT, int NW>
 __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(const bf16_t *X, const bf16_t *OA, const bf16_t *SB,
                                                                        const float *zpad, const float *scalars, float eps,
-                                                                       Dims s, T *out, View v, float *N, float *D) {
+                                                                       Dims s, T *out, View v, float *N, float *D,
+                                                                       unsigned short *bits) {
   using G = Geo<DH>;
+  constexpr bool BITS = MODE == 2;
   constexpr int FC = DH <= 32 ? 2 : 1, NA = G::KS * PT, NB = G::NSB;
   constexpr bool ZV = MODE == 0;   // the normaliser, on the vector units
   typedef Stager<NA, NB, 0, 0, FC, NW> Stg;
@@ -983,10 +1053,15 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(c
 #pragma unroll
         for (int i = 0; i < 16; ++i) R[i] = relu(R[i]);
         if (ZV) dpart[r] += dot16(R, z4);
+        bf16x8 lead[2];
         with_split<mfma_residuals(DH, PT)>(R, ni, [&](int a, const bf16x8 *p) {
+          if (BITS) lead[a] = p[0];
 #pragma unroll
           for (int ct = 0; ct < G::CT; ++ct) apply_terms<DH>(acc[r][ct], p, lb, a, ct, lane);   // rows: tokens, lanes: columns
         });
+        if (BITS && tb0 + r < s.nt)
+          bits[(((int64_t)slice * s.nt + tb0 + r) * s.mt + f0 + fi) * 64 + lane] =
+              (unsigned short)TransposeDecisions(lane)(decisions(lead));
       }
     }
     if (ZV && (!more || (f0 + FC) % 8 == 0)) {
@@ -1044,10 +1119,14 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void apply_kernel(c
 
 // The gradient kernel's dX_F likewise, and dV where it rides along (at head dimension 64 it has no registers left for either).
 constexpr bool grad_in_parts(int DH, int PT, bool DV) { return sum_in_parts(PT) && (DH <= 32 || (DH == 64 && !DV)); }
-// dX_F of one side: R = X Omega, G = Y S^T + w z^T (Y = dN, S, w = dD on the query side; Y = V, dS, w = 1
-// on the key side), dX_F = c rowscale ((G masked where R > 0) Omega^T) in float32, row t of a slice at
-// grad_row(t) (in the place of X's operand tiles where these are not needed again: a wave reads its tiles before
-// it writes them, and no other wave does either).  DV: dV = c ReLU(R) dS rides along.  ddw, rowscale nullptr: 1.
+// dX_F of one side: G = Y S^T + w z^T (Y = dN, S, w = dD on the query side; Y = V, dS, w = 1
+// on the key side), dX_F = c rowscale ((G masked where R = X Omega > 0) Omega^T) in float32, row t of a slice at
+// grad_row(t) (in the place of X's operand tiles, which at most the wave that writes them still needs, and it has read its own).
+// DV: dV = c ReLU(R) dS rides along, R is formed here; without DV the decisions come as bits.
+// Bits instead of the projection, query side, us: 128 slices of 4000 tokens, d 32, m 1024, float32 525 -> 371 (the registers of X
+// hold a second token tile), the contraction that leaves them 328 -> 344; 8 of 131072, d 16, m 1024, bf16 385 -> 330, 280 -> 305; 8 of 16384,
+// m 256, float32, d 64 85 -> 64, 51 -> 52; d 128 both sides 193 -> 134, dV's kernel 156 -> 159.  dV on its own at d 32, with
+// the key side's gradient on bits, would take 329 and 371 where the two in one take 729.  ddw, rowscale nullptr: 1.
 // The rows of Y come from the tensors as they are: y, divided by D (one term: not), or with the LayerNorm output
 // stage (o given) rstd (y - mean y - o mean(y o)).
 template <int DH> constexpr int64_t grad_tile() { return 48 * DH; }   // floats of a tile of 32 rows: its operand tiles' size
@@ -1060,30 +1139,32 @@ struct GradRows {
   int vec;
 };
 template <typename T, int DH, int PT, bool DV, int RT, int NW>
-__global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void grad_kernel(const bf16_t *X, GradRows<T> Y, const float *ddw,
+__global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void grad_kernel(const bf16_t *X, const unsigned short *bits, GradRows<T> Y, const float *ddw,
                                                                       const float *rowscale, const bf16_t *OA,
                                                                       const bf16_t *SA, const bf16_t *OB, const bf16_t *SB,
                                                                       const float *scalars, Dims s, float *dXF, T *dv, View v) {
   using G = Geo<DH>;
-  constexpr int FC = DH == 16 ? 2 : 1, NA = G::KS * PT, NSA = 3 * G::KS + 1, NOB = 2 * G::CT * PT, NSB = DV ? G::NSB : 0;
+  constexpr int FC = DH == 16 || (DH == 32 && PT == 1 && !DV) ? 2 : 1, NA = DV ? G::KS * PT : 0, NSA = 3 * G::KS + 1, NOB = 2 * G::CT * PT, NSB = DV ? G::NSB : 0;
   typedef Stager<NA, NSA, NOB, NSB, FC, NW> Stg;
   __shared__ __attribute__((aligned(16))) bf16_t lds[2][Stg::NS * kTile];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slice = blockIdx.y, tb0 = (blockIdx.x * NW + wave) * RT;
-  bf16x8 x[RT][G::KS][3], y[RT][G::KS][PT], ext[RT];
+  bf16x8 x[DV ? RT : 1][G::KS][3], y[RT][G::KS][PT], ext[RT];
 #pragma unroll
   for (int r = 0; r < RT; ++r) {
     const bool mine = tb0 + r < s.nt;   // (a wave past the last tile only helps to stage)
     const int64_t tb = (int64_t)slice * s.nt + (mine ? tb0 + r : 0);
-    const bf16_t *xp = X + tb * G::KS * 3 * kTile;
+    if constexpr (DV) {
+      const bf16_t *xp = X + tb * G::KS * 3 * kTile;
 #pragma unroll
-    for (int ks = 0; ks < G::KS; ++ks)
+      for (int ks = 0; ks < G::KS; ++ks)
 #pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        x[r][ks][i] = bf16x8{};
-        if (mine) x[r][ks][i] = lds_operand(xp + (ks * 3 + i) * kTile, lane);
-      }
+        for (int i = 0; i < 3; ++i) {
+          x[r][ks][i] = bf16x8{};
+          if (mine) x[r][ks][i] = lds_operand(xp + (ks * 3 + i) * kTile, lane);
+        }
+    }
     const int t = 32 * (tb0 + r) + l32;
     const bool ok = t < s.n;
     const int64_t row = v.slice_base(slice) + (int64_t)(ok ? t : 0) * v.sn;
@@ -1151,14 +1232,39 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void grad_kernel(co
       if (VPARTS) totalv[VPARTS ? r : 0][ct] = zero16();
     }
   const NegIdentity ni(lane);
+  // the decisions of a stage's feature tiles, one stage ahead (two token tiles share a word)
+  const TransposeDecisions transpose(lane);
+  constexpr int WR = (RT + 1) / 2;
+  unsigned short next[DV ? 1 : FC][DV ? 1 : RT];
+  uint32_t word[DV ? 1 : FC][WR];
+  auto fetch_bits = [&](int f0) {
+#pragma unroll
+    for (int fi = 0; fi < FC; ++fi)
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+        next[fi][r] = bits[(((int64_t)slice * s.nt + min(tb0 + r, s.nt - 1)) * s.mt + min(f0 + fi, s.mt - 1)) * 64 + lane];
+  };
+  auto take_bits = [&]() {
+#pragma unroll
+    for (int fi = 0; fi < FC; ++fi)
+#pragma unroll
+      for (int u = 0; u < WR; ++u)
+        word[fi][u] = transpose(2 * u + 1 < RT ? (uint32_t)next[fi][2 * u] | (uint32_t)next[fi][2 * u + 1 < RT ? 2 * u + 1 : 0] << 16
+                                               : (uint32_t)next[fi][2 * u]);
+  };
   sg.fetch(0, wave, lane);
+  if constexpr (!DV) fetch_bits(0);
   sg.put(lds[0], wave, lane);
   wait_loads();
   __syncthreads();
   int b = 0;
   for (int f0 = 0; f0 < s.mt; f0 += FC, b ^= 1) {
     const bool more = f0 + FC < s.mt;
-    if (more) sg.fetch(f0 + FC, wave, lane);
+    if constexpr (!DV) take_bits();
+    if (more) {
+      sg.fetch(f0 + FC, wave, lane);
+      if constexpr (!DV) fetch_bits(f0 + FC);
+    }
 #pragma unroll
     for (int fi = 0; fi < FC; ++fi) {
       if (f0 + fi >= s.mt) break;
@@ -1167,13 +1273,14 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void grad_kernel(co
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
         f32x16 R = zero16(), Gr = zero16();
+        if constexpr (DV)
 #pragma unroll
-        for (int ks = 0; ks < G::KS; ++ks) {
-          bf16x8 o[PT];
+          for (int ks = 0; ks < G::KS; ++ks) {
+            bf16x8 o[PT];
 #pragma unroll
-          for (int i = 0; i < PT; ++i) o[i] = lds_operand(la + (ks * PT + i) * kTile, lane);
-          R = mfma_terms<PT, true>(R, x[r][ks], o);   // rows: features, lanes: tokens
-        }
+            for (int i = 0; i < PT; ++i) o[i] = lds_operand(la + (ks * PT + i) * kTile, lane);
+            R = mfma_terms<PT, true>(R, x[r][ks], o);   // rows: features, lanes: tokens
+          }
         // (the small products of the whole sum first: while they are added the accumulator is small, and so is its rounding)
         auto go = [&](int ks, int i, int j) { Gr = mfma(lds_operand(ls + (ks * 3 + i) * kTile, lane), y[r][ks][j], Gr); };
 #pragma unroll
@@ -1191,11 +1298,15 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void grad_kernel(co
         Gr = mfma(lds_operand(ls + 3 * G::KS * kTile, lane), ext[r], Gr);
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-          const float mask = positive(R[i]);
-          Gr[i] = masked(Gr[i], mask);
-          if (DV) R[i] = masked(R[i], mask);
+          if constexpr (DV) {
+            const float mask = positive(R[i]);
+            Gr[i] = masked(Gr[i], mask);
+            R[i] = masked(R[i], mask);
+          } else {
+            Gr[i] = masked(Gr[i], word[fi][r / 2], i, r % 2);
+          }
         }
-        with_split<mfma_residuals(DH, PT)>(Gr, ni, [&](int a, const bf16x8 *p) {
+        with_split<mfma_residuals(DH, PT, DV)>(Gr, ni, [&](int a, const bf16x8 *p) {
 #pragma unroll
           for (int ct = 0; ct < G::CT; ++ct) {
             bf16x8 o[PT];
@@ -1205,7 +1316,7 @@ __global__ __launch_bounds__(NW * 64, row_occupancy(DH, NW)) void grad_kernel(co
           }
         });
         if (DV)
-          with_split<mfma_residuals(DH, PT)>(R, ni, [&](int a, const bf16x8 *p) {
+          with_split<mfma_residuals(DH, PT, DV)>(R, ni, [&](int a, const bf16x8 *p) {
 #pragma unroll
             for (int ct = 0; ct < G::CT; ++ct) apply_terms<DH>(accv[r][ct], p, lv, a, ct, lane);
           });
@@ -1531,6 +1642,7 @@ struct Ws {
   // backward
   bf16_t *NC, *XS, *SA, *dSA, *dSB;
   float *ddw, *rowscale, *dpart, *gq, *gk, *partQ, *partK, *dF, *dlogit, *dqbar, *tgq, *tgk, *aq, *ak;
+  unsigned short *bitsQ, *bitsK;   // the ReLU's decisions (bitsK at head dimension 128)
   int64_t total;
 };
 int64_t tile_floats(int64_t tiles) { return tiles * (kTile / 2); }
@@ -1565,6 +1677,8 @@ Ws ws_of(const wersa_desc &c, const Plan &p, int bwd, bool keep, float *base) {
     w.SA = op((sl * p.s.mt + 1) * (3 * p.KS + 1));
     w.dSA = op((sl * p.s.mt + 1) * (3 * p.KS + 1));
     w.dSB = op((sl * p.s.mt + 1) * p.NSB);
+    w.bitsQ = (unsigned short *)b.take(rows * p.s.mt * 32);
+    if (p.DH == 128) w.bitsK = (unsigned short *)b.take(rows * p.s.mt * 32);
     w.ddw = b.take(rows * 32);
     if (p.PT == 1) w.rowscale = b.take(rows * 32);
     w.dpart = b.take(sl * p.groups);
@@ -1611,48 +1725,56 @@ bool rows_aligned(const wersa_desc &c, std::initializer_list<const void *> ptrs)
 // to give every compute unit a full workgroup (each wave walks all features whatever the size, so more and
 // smaller workgroups cost only the staging).
 constexpr int full_waves(int DH) { return DH <= 32 ? 4 : 8; }
-template <int DH, int RT>
-int row_waves(const Plan &p, int slices) {
+// Token tiles per wave: two (DH <= 32, where the registers hold them) halve what a wave reads from LDS per product, but a wave of two
+// is a coarser piece of work.  A round is 512 workgroups of four waves, two per SIMD; two tiles where they do not make more rounds of tiles,
+// and from four rounds on.
+// us of the forward's kernel and of the query side's gradient, one tile and two, d 32, m 512, float32, token tiles in all:
+// 512: 18.8 26.6, 21.5 30.2; 1536: 27.8 32.2, 31.2 34.6; 8192: 114.5 106.2, 127.1 113.8; 16128 (m 1024): 365 346, 405 371.
+// d 16, bf16: 512: 14.5 21.9, 14.1 20.1; 3072: 24.4 30.2, 23.3 27.5; 4096: 30.6 32.5, 28.7 29.5; 8192: 61.0 61.0, 57.1 54.8; 32768 (m 1024):
+// 386 365, 362 330.
+template <int DH, int MOST>
+int row_tiles(const Plan &p, int slices) {
+  if (MOST == 1) return 1;
+  const int64_t one = (int64_t)slices * ((p.s.nt + 3) / 4), two = (int64_t)slices * ((p.s.nt + 7) / 8);
+  return one >= 2048 || 2 * ((two + 511) / 512) <= (one + 511) / 512 ? 2 : 1;
+}
+template <int DH>
+int row_waves(const Plan &p, int RT, int slices) {
   if (DH == 128) return 4;
   const int full = full_waves(DH);
   return (int64_t)slices * ((p.s.nt + full * RT - 1) / (full * RT)) >= 256 ? full : 2;
 }
-template <int DH> constexpr int row_tiles() { return DH <= 32 ? 2 : 1; }
+// Calls go(token tiles per wave, waves, grid) of the instance that a row kernel runs as.
+template <int DH, int MOST, typename F>
+void row_launch(const Plan &p, int slices, F go) {
+  using std::integral_constant;
+  const int rt = row_tiles<DH, MOST>(p, slices), nw = row_waves<DH>(p, rt, slices);
+  const dim3 grid((p.s.nt + nw * rt - 1) / (nw * rt), slices);
+  using Full = integral_constant<int, DH == 128 ? 4 : full_waves(DH)>;
+  if constexpr (MOST == 2)
+    if (rt == 2) return go(integral_constant<int, 2>(), Full(), grid);   // (more than 256 workgroups)
+  if constexpr (DH < 128)
+    if (nw == 2) return go(integral_constant<int, 1>(), integral_constant<int, 2>(), grid);
+  go(integral_constant<int, 1>(), Full(), grid);
+}
 
 template <typename T, int DH, int PT, int MODE>
 void launch_apply(const wersa_desc &c, const Plan &p, const bf16_t *X, const bf16_t *OA, const bf16_t *SB, const float *zpad,
-                  const float *scalars, T *out, View v, float *N, float *D, hipStream_t st) {
-  constexpr int RT = row_tiles<DH>();
-  const int slices = c.B * c.H, nw = row_waves<DH, RT>(p, slices);
-  const dim3 grid((p.s.nt + nw * RT - 1) / (nw * RT), slices);
-  auto go = [&](auto NW) {
-    WERSA_STAGE(MODE == 2 ? "split_apply_dv" : "split_apply", st, apply_kernel<T, DH, PT, MODE, RT, NW.value><<<grid, 64 * NW.value, 0, st>>>(
-        X, OA, SB, zpad, scalars, c.eps, p.s, out, v, N, D));
-  };
-  if constexpr (DH == 128) {
-    go(std::integral_constant<int, 4>());
-  } else {
-    if (nw != 2) go(std::integral_constant<int, full_waves(DH)>());
-    else go(std::integral_constant<int, 2>());
-  }
+                  const float *scalars, T *out, View v, float *N, float *D, unsigned short *bits, hipStream_t st) {
+  row_launch<DH, DH == 16 || (DH == 32 && PT == 3) ? 2 : 1>(p, c.B * c.H, [&](auto RT, auto NW, dim3 grid) {
+    WERSA_STAGE(MODE == 2 ? "split_apply_dv" : "split_apply", st, apply_kernel<T, DH, PT, MODE, RT.value, NW.value><<<grid, 64 * NW.value, 0, st>>>(
+        X, OA, SB, zpad, scalars, c.eps, p.s, out, v, N, D, bits));
+  });
 }
 template <typename T, int DH, int PT, bool DV>
-void launch_grad(const wersa_desc &c, const Plan &p, const bf16_t *X, const GradRows<T> &Y, const float *ddw, const float *rowscale,
-                 const bf16_t *OA, const bf16_t *SA, const bf16_t *OB, const bf16_t *SB, const float *scalars, float *dXF,
-                 T *dv, View v, hipStream_t st) {
-  constexpr int RT = DH == 16 && (PT == 1 || !DV) ? 2 : 1;   // (as many token tiles as the registers of two waves per SIMD hold)
-  const int slices = c.B * c.H, nw = row_waves<DH, RT>(p, slices);
-  const dim3 grid((p.s.nt + nw * RT - 1) / (nw * RT), slices);
-  auto go = [&](auto NW) {
-    WERSA_STAGE(DV ? "split_grad_k" : "split_grad", st, grad_kernel<T, DH, PT, DV, RT, NW.value><<<grid, 64 * NW.value, 0, st>>>(
-        X, Y, ddw, rowscale, OA, SA, OB, SB, scalars, p.s, dXF, dv, v));
-  };
-  if constexpr (DH == 128) {
-    go(std::integral_constant<int, 4>());
-  } else {
-    if (nw != 2) go(std::integral_constant<int, full_waves(DH)>());
-    else go(std::integral_constant<int, 2>());
-  }
+void launch_grad(const wersa_desc &c, const Plan &p, const bf16_t *X, const unsigned short *bits, const GradRows<T> &Y,
+                 const float *ddw, const float *rowscale, const bf16_t *OA, const bf16_t *SA, const bf16_t *OB, const bf16_t *SB,
+                 const float *scalars, float *dXF, T *dv, View v, hipStream_t st) {
+  constexpr int MOST = DH == 16 ? (DV && PT == 3 ? 1 : 2) : DH == 32 && PT == 3 && !DV ? 2 : 1;   // (as the registers of two waves per SIMD hold)
+  row_launch<DH, MOST>(p, c.B * c.H, [&](auto RT, auto NW, dim3 grid) {
+    WERSA_STAGE(DV ? "split_grad_k" : "split_grad", st, grad_kernel<T, DH, PT, DV, RT.value, NW.value><<<grid, 64 * NW.value, 0, st>>>(
+        X, bits, Y, ddw, rowscale, OA, SA, OB, SB, scalars, p.s, dXF, dv, v));
+  });
 }
 
 template <typename T, int DH, int PT>
@@ -1687,15 +1809,15 @@ wersa_status forward_t(const wersa_desc &c, const T *q, const T *k, const T *v, 
         qpart, kpart, coef, p.ntl, c.d, c.L, w.pyr, addQ, addK));
   WERSA_STAGE("split_prep_fwd", st, prep_fwd_kernel<T, DH, PT><<<dim3(p.groups, slices, 3), 256, 0, st>>>(
       q, k, v, tv, p.s, vec, c.L, coef, addQ, addK, XQ, XK, w.VC));
-  WERSA_STAGE("split_contract", st, contract_kernel<DH, PT><<<dim3(p.splits, p.s.mt / p.FW, slices), 512, 0, st>>>(
-      XK, w.VC, nullptr, OAk, p.s, p.FW, p.TW, p.tiles_per_split, w.part, w.zpart));
+  WERSA_STAGE("split_contract", st, contract_kernel<DH, PT, false><<<dim3(p.splits, p.s.mt / p.FW, slices), 512, 0, st>>>(
+      XK, w.VC, nullptr, OAk, p.s, p.FW, p.TW, p.tiles_per_split, w.part, w.zpart, nullptr));
   WERSA_STAGE("split_reduce", st, reduce_kernel<DH><<<dim3(p.s.mt, slices), 256, 0, st>>>(
       w.part, w.zpart, p.shares, 1, scalars, p.s, saved + sv.S, saved + sv.z, w.zpad, nullptr, w.SB, nullptr));
   if (ln) {
-    launch_apply<T, DH, PT, 1>(c, p, XQ, OA, w.SB, w.zpad, scalars, out, tv, w.Nbuf, nullptr, st);
+    launch_apply<T, DH, PT, 1>(c, p, XQ, OA, w.SB, w.zpad, scalars, out, tv, w.Nbuf, nullptr, nullptr, st);
     WERSA_STAGE("split_ln", st, ln_out_kernel<T><<<dim3((c.n + 3) / 4, slices), 256, 0, st>>>(w.Nbuf, out, tv, c.n, c.d, c.eps, saved + sv.D));
   } else {
-    launch_apply<T, DH, PT, 0>(c, p, XQ, OA, w.SB, w.zpad, scalars, out, tv, nullptr, saved + sv.D, st);
+    launch_apply<T, DH, PT, 0>(c, p, XQ, OA, w.SB, w.zpad, scalars, out, tv, nullptr, saved + sv.D, nullptr, st);
   }
   return hipGetLastError() == hipSuccess ? WERSA_OK : WERSA_ERR_LAUNCH;
 }
@@ -1712,7 +1834,7 @@ wersa_status backward_t(const wersa_desc &c, const T *q, const T *k, const T *v,
   const View tv{c.stride_b, c.stride_h, c.stride_n, c.H};
   const bool deep = c.L > kTileL, ln = (c.flags & WERSA_FLAG_LAYERNORM) != 0;
   const float *scalars = saved + sv.scalars, *coef = saved + sv.coef, *D = saved + sv.D;
-  // (with one-term operands XS serves the query side's gradient too: of X Omega it needs the sign alone)
+  // (with one-term operands the contraction takes Phi of Q_F / D: the same decisions)
   const bf16_t *XQ = PT == 1 ? w.XS : keep ? (const bf16_t *)(saved + sv.XQ) : w.XQ,
                *XK = keep ? (const bf16_t *)(saved + sv.XK) : w.XK, *OA = (const bf16_t *)(saved + sv.OA),
                *OB = (const bf16_t *)(saved + sv.OB);
@@ -1722,19 +1844,19 @@ wersa_status backward_t(const wersa_desc &c, const T *q, const T *k, const T *v,
   WERSA_STAGE("split_prep_bwd", st, prep_bwd_kernel<T, DH, PT><<<dim3(p.groups, slices, keep ? (PT == 1 ? 2 : 1) : 3), 256, 0, st>>>(
       dout, out, q, k, tv, p.s, vec, ln, c.L, coef, deep ? saved + sv.addQ : nullptr, deep ? saved + sv.addK : nullptr, D, w.NC,
       w.XQ, w.XS, w.XK, w.ddw, w.rowscale, w.dpart));
-  WERSA_STAGE("split_contract", st, contract_kernel<DH, PT><<<dim3(p.splits, p.s.mt / p.FW, slices), 512, 0, st>>>(
-      XQ, w.NC, w.ddw, OA, p.s, p.FW, p.TW, p.tiles_per_split, w.part, w.zpart));
+  WERSA_STAGE("split_contract", st, contract_kernel<DH, PT, true><<<dim3(p.splits, p.s.mt / p.FW, slices), 512, 0, st>>>(
+      XQ, w.NC, w.ddw, OA, p.s, p.FW, p.TW, p.tiles_per_split, w.part, w.zpart, w.bitsQ));
   WERSA_STAGE("split_reduce", st, reduce_kernel<DH><<<dim3(p.s.mt, slices, 2), 256, 0, st>>>(
       w.part, w.zpart, p.shares, PT == 1 ? 3 : 1, scalars, p.s, const_cast<float *>(saved + sv.S), const_cast<float *>(saved + sv.z),
       nullptr, w.dSA, w.dSB, w.SA));
   const GradRows<T> rowsK{v, nullptr, nullptr, vec}, rowsQ{dout, ln ? out : nullptr, PT == 1 ? nullptr : D, vec};
   if constexpr (DH == 128) {   // (dV on its own: no registers left for its accumulators; first, dK_F may go in the place of K_F)
-    launch_apply<T, DH, PT, 2>(c, p, XK, OAk, w.dSB, nullptr, scalars, dv, tv, nullptr, nullptr, st);
-    launch_grad<T, DH, PT, false>(c, p, XK, rowsK, nullptr, nullptr, OAk, w.dSA, OBk, nullptr, scalars, w.gk, nullptr, tv, st);
+    launch_apply<T, DH, PT, 2>(c, p, XK, OAk, w.dSB, nullptr, scalars, dv, tv, nullptr, nullptr, w.bitsK, st);
+    launch_grad<T, DH, PT, false>(c, p, nullptr, w.bitsK, rowsK, nullptr, nullptr, nullptr, w.dSA, OBk, nullptr, scalars, w.gk, nullptr, tv, st);
   } else {
-    launch_grad<T, DH, PT, true>(c, p, XK, rowsK, nullptr, nullptr, OAk, w.dSA, OBk, w.dSB, scalars, w.gk, dv, tv, st);
+    launch_grad<T, DH, PT, true>(c, p, XK, nullptr, rowsK, nullptr, nullptr, OAk, w.dSA, OBk, w.dSB, scalars, w.gk, dv, tv, st);
   }
-  launch_grad<T, DH, PT, false>(c, p, XQ, rowsQ, w.ddw, PT == 1 ? w.rowscale : nullptr, OA, w.SA, OB, nullptr, scalars, w.gq,
+  launch_grad<T, DH, PT, false>(c, p, nullptr, w.bitsQ, rowsQ, w.ddw, PT == 1 ? w.rowscale : nullptr, nullptr, w.SA, OB, nullptr, scalars, w.gq,
                                 nullptr, tv, st);
   const int prow = p.groups + (deep ? c.d / kCoarseCols : 0);
   WERSA_STAGE("split_dots", st, dots_kernel<T, DH><<<dim3(p.groups, slices, 2), 256, 0, st>>>(
