@@ -572,8 +572,9 @@ __global__ __launch_bounds__(64 * NW, 2) void phiT_contract_kernel(
     const _Float16 *xf, const bf16_t *xraw, View vx, const float *coef, const float *tile_add,
     const bf16_t *y, View vy, const float *rowdiv, const float *w,
     const bf16_t *orows, float *dDout, float *dDpart,
-    const _Float16 *omT, int n, int m, int rows_per_chunk, float *Spart, float *zpart, uint32_t *bits) {
+    const _Float16 *omT, int n, int m, int rows_per_chunk, float *Spart, float *zpart, uint32_t *bits, GateFwdArgs gate) {
   constexpr bool FUSE = (DH == 64);
+  constexpr bool GATE = FUSE && !BITS && !DEEP;   // (the forward) `gate` may be given: the first launch that filters
   static_assert(NW == 4 || (NW == 8 && !FUSE), "the filter of head dimension 64 is dealt to four waves");
   constexpr int NT = 64 * NW;
   constexpr int KS = DH / 16;   // k-steps of the projection
@@ -616,7 +617,6 @@ __global__ __launch_bounds__(64 * NW, 2) void phiT_contract_kernel(
   const bf16_t *xrs = FUSE ? xraw + vx.slice_base(slice) : nullptr;
   const bf16_t *ys = y + vy.slice_base(slice);
   const float *rd = rowdiv ? rowdiv + (int64_t)slice * n : nullptr;
-  if (FUSE) build_filter_table(gt, coef + slice * kCoefStride, tid, 256);   // visible after the first barrier below
   const float *ws = w ? w + (int64_t)slice * n : nullptr;
 
   // X_F and Y pieces are taken row-major (coalesced) and stored as they are; the Y operand
@@ -716,10 +716,18 @@ __global__ __launch_bounds__(64 * NW, 2) void phiT_contract_kernel(
     }
   };
 
-  if (steps > 0) {
-    fetch(t_begin);
-    stash(0);
+  if (steps > 0) fetch(t_begin);
+  // (the table is visible after the barrier below)
+  if (GATE && gate.qpart) {
+    typedef GateLds<4, 64> Lds;
+    static_assert(sizeof(Lds) <= sizeof(xq) || !GATE, "the gate's scratch lies where X_F goes later");
+    Lds &lds = *reinterpret_cast<Lds *>(&xq[0]);
+    gate_prologue<4, 64>(gate, slice, chunk == 0 && blockIdx.y == 0, lds);
+    build_filter_table(gt, lds.coef, tid, 256);
+  } else if (FUSE) {
+    build_filter_table(gt, coef + slice * kCoefStride, tid, 256);
   }
+  if (steps > 0) stash(0);
   __syncthreads();
   // FUSE: rows 32 (wave / 2) + l32 of G are this wave's B operands in every step: high part for the four k-steps, low part for
   // the two of the quarter's own half.  Forward: kept in registers, own half first (ks_own, ks_own + 1: high and low part),
@@ -2810,7 +2818,7 @@ template <int DH>
 void launch_contract(const wersa_desc &c, const FastPlan &p, const _Float16 *xf, const bf16_t *xraw,
                      const bf16_t *y, const View &yv, const float *rowdiv, const float *wts, const bf16_t *orows,
                      bool key_side, const FastWs &w, float *S, float *z, bf16_t *Mx, bf16_t *MT,
-                     bf16_t *bb, hipStream_t st) {
+                     bf16_t *bb, const GateFwdArgs &gate, hipStream_t st) {
   const int slices = c.B * c.H;
   dim3 grid(p.chunksC, c.m / p.MB, slices);
   const _Float16 *omT = w.omT + (((c.flags & WERSA_FLAG_SEPARATE_OMEGA) && key_side) ? (int64_t)c.d * c.m : 0);
@@ -2821,7 +2829,7 @@ void launch_contract(const wersa_desc &c, const FastPlan &p, const _Float16 *xf,
                 kern<<<grid, 64 * p.NWC, 0, st>>>(xf, xraw, View{c.stride_b, c.stride_h, c.stride_n, c.H}, w.coef,
                                            key_side ? w.addK : w.addQ, y, yv,
                                            rowdiv, wts, orows, w.dD, w.dDpart, omT, c.n, c.m, p.rowsC, w.Spart,
-                                           w.zpart, bwd ? w.bitsQ : nullptr));
+                                           w.zpart, bwd ? w.bitsQ : nullptr, gate));
   };
   const bool ragged = c.n % 64 != 0, deep = DH == 64 && c.L > kTileL;
   constexpr bool D64 = DH == 64;
@@ -2876,29 +2884,43 @@ wersa_status fast_forward_t(const wersa_desc &c, const bf16_t *q, const bf16_t *
   SetupArgs su{sigma, c.bw_floor, omega, c.d, c.m, nmat, w.scalars, w.omT, setup_blocks(c.d, c.m, nmat)};
   const SetupArgs none{};
   const bool deep = c.L > kTileL;
+  const bool pooled_gate = (c.flags & WERSA_FLAG_POOLED_GATE) != 0;
+  GateFwdArgs gate{};
+  gate.n = c.n, gate.d = c.d, gate.L = c.L, gate.H = c.H;
+  gate.gate_w = gate_w, gate.gate_b = gate_b, gate.scale_w = scale_w, gate.scalars = w.scalars;
+  gate.qbar = qbar, gate.s_out = s, gate.F_out = F, gate.coef_out = w.coef;
   if (pooled && c.n % 128 == 0 && !deep) {
     WERSA_STAGE("wersa_setup", st, setup_kernel<<<su.blocks, 256, 0, st>>>(su));
     // the caller's column sums per 128 token rows: batch b owns row blocks [b n/128, (b+1) n/128)
-    const int chunks = c.n / 128;
-    WERSA_STAGE("gate_fwd_kernel", st,
-                gate_fwd_kernel<<<slices, kGateFwdThreads, 0, st>>>(pooled->sums, chunks, c.n, c.d, c.L, c.H, gate_w, gate_b, scale_w,
-                                                       qbar, s, F, w.coef, (c.flags & WERSA_FLAG_POOLED_GATE) ? 1 : 0,
-                                                       PooledLayout{chunks * pooled->hidden, c.d, pooled->hidden},
-                                                       pooled->amax, chunks * (c.d / kPooledMaxCols), w.scalars,
-                                                       AmaxLayout{chunks * (pooled->hidden / kPooledMaxCols), c.d / kPooledMaxCols,
-                                                                  pooled->hidden / kPooledMaxCols, c.d / kPooledMaxCols}));
+    const int groups = c.d / kPooledMaxCols;
+    const int64_t all = pooled->hidden / kPooledMaxCols;
+    gate.qpart = pooled->sums;
+    gate.chunks = c.n / 128;
+    gate.ql = PooledLayout{gate.chunks * pooled->hidden, c.d, pooled->hidden};
+    gate.amax_part = pooled->amax;
+    gate.amax_chunks = gate.chunks * groups;
+    gate.al = AmaxLayout{gate.chunks * all, groups, all, groups};
   } else {
     // deep: one partial per 64-row tile, kept (with those of K) as the tile sums of the levels above 6
     float *qpart = deep ? w.tileQ : w.qpart;
     WERSA_STAGE("wersa_qbar", st,
                 qbar_partial_kernel<DH><<<dim3(p.chunksQ + su.blocks, slices), 256, 0, st>>>(q, tv, c.n, p.rowsQ, qpart,
                                                                                              p.chunksQ, su, w.qamax));
+    gate.qpart = qpart;
+    gate.chunks = gate.amax_chunks = p.chunksQ;
+    gate.ql = PooledLayout{(int64_t)c.H * p.chunksQ * c.d, (int64_t)p.chunksQ * c.d, c.d};
+    gate.amax_part = w.qamax;
+    gate.al = AmaxLayout{(int64_t)c.H * p.chunksQ, p.chunksQ, 0, p.chunksQ};
+  }
+  // Head dimension 64: the contraction's workgroups, two per compute unit and one round of them, form the gate themselves (us per call, forward: 64 slices of
+  // 4096 rows, m 128 60.6 -> 58.5, 4 of 2000, m 256 34.9 -> 32.5, 128 of 1000 67.0 -> 64.8, attention block with 8 heads of 2048 rows
+  // 51.8 -> 49.0).  Not the thousands of workgroups of head dimension 128's filter, nor a gate that pools heads or has many partial sums.
+  if (DH != 64 || deep || pooled_gate || gate.chunks > kGatePrologueChunks) {
     WERSA_STAGE("gate_fwd_kernel", st,
-                gate_fwd_kernel<<<slices, kGateFwdThreads, 0, st>>>(qpart, p.chunksQ, c.n, c.d, c.L, c.H, gate_w, gate_b, scale_w,
-                                                       qbar, s, F, w.coef, (c.flags & WERSA_FLAG_POOLED_GATE) ? 1 : 0,
-                                                       PooledLayout{(int64_t)c.H * p.chunksQ * c.d, (int64_t)p.chunksQ * c.d, c.d},
-                                                       w.qamax, p.chunksQ, w.scalars,
-                                                       AmaxLayout{(int64_t)c.H * p.chunksQ, p.chunksQ, 0, p.chunksQ}));
+                gate_fwd_kernel<<<slices, kGateFwdThreads, 0, st>>>(gate.qpart, gate.chunks, c.n, c.d, c.L, c.H, gate_w, gate_b, scale_w,
+                                                       qbar, s, F, w.coef, pooled_gate ? 1 : 0, gate.ql,
+                                                       gate.amax_part, gate.amax_chunks, w.scalars, gate.al));
+    gate.qpart = nullptr;
   }
   if (deep) {
     WERSA_STAGE("wersa_qbar", st,
@@ -2913,7 +2935,7 @@ wersa_status fast_forward_t(const wersa_desc &c, const bf16_t *q, const bf16_t *
                 haar_stage_kernel<DH><<<dim3((c.n + 63) / 64, slices, 2), 256, 0, st>>>(q, k, tv, c.n, w.coef, deep ? w.addQ : nullptr,
                                                                                        deep ? w.addK : nullptr, QF, KF));
   }
-  launch_contract<DH>(c, p, KF, k, v, tv, nullptr, nullptr, nullptr, true, w, S, z, w.Sx, w.ST, w.zb, st);
+  launch_contract<DH>(c, p, KF, k, v, tv, nullptr, nullptr, nullptr, true, w, S, z, w.Sx, w.ST, w.zb, gate, st);
   if (launch_rows<DH, 0>(c, p, QF, q, nullptr, nullptr, nullptr, w, omega, nullptr, w.ST, w.zb, out, D,
                          nullptr, st) != hipSuccess)
     return WERSA_ERR_LAUNCH;
@@ -2945,9 +2967,9 @@ wersa_status fast_backward_t(const wersa_desc &c, const bf16_t *q, const bf16_t 
     WERSA_STAGE("wersa_ln_prep", st,
                 ln_prep_kernel<DH><<<dim3(p.chunksL, slices), 256, 0, st>>>(dout, out, tv, D, c.n, p.rowsL, w.dN,
                                                                            w.ones, w.dD, w.dDpart));
-    launch_contract<DH>(c, p, QF, q, w.dN, nv, nullptr, w.dD, nullptr, false, w, w.dS, w.dz, w.dSx, w.dST, w.dzb, st);
+    launch_contract<DH>(c, p, QF, q, w.dN, nv, nullptr, w.dD, nullptr, false, w, w.dS, w.dz, w.dSx, w.dST, w.dzb, GateFwdArgs{}, st);
   } else {
-    launch_contract<DH>(c, p, QF, q, dout, tv, D, nullptr, out, false, w, w.dS, w.dz, w.dSx, w.dST, w.dzb, st);
+    launch_contract<DH>(c, p, QF, q, dout, tv, D, nullptr, out, false, w, w.dS, w.dz, w.dSx, w.dST, w.dzb, GateFwdArgs{}, st);
   }
   auto key_side = [&]() {
     const hipError_t e = launch_rows<DH, 3>(c, p, KF, k, nullptr, nullptr, nullptr, w, omega, nullptr, w.dST, nullptr, dv, nullptr, nullptr, st);

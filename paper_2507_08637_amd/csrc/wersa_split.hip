@@ -469,6 +469,7 @@ struct PrepLds {
   float part[256];
   float small[8];
 };
+template <int DH> using PrepGate = GateLds<16, DH>;   // in the place of the tile
 // TR x CW elements of a strided tensor from row t0, column c0 into LDS; zeros past n and d.
 template <typename T, int DH>
 __device__ __forceinline__ void load_tile(const T *xs, const View &v, const Dims &s, int vec, int t0, int c0, float *tile) {
@@ -502,7 +503,7 @@ __device__ __forceinline__ void filter_pack(PrepLds<DH> &lds, const T *x, const 
   const int tid = threadIdx.x, slice = blockIdx.y;
   const int rg = blockIdx.x / G::PIECES, piece = blockIdx.x % G::PIECES;
   const int t0 = rg * TR, c0 = piece * CW;
-  if (tid < 8) lds.small[tid] = coef[slice * kCoefStride + tid];
+  if (coef && tid < 8) lds.small[tid] = coef[slice * kCoefStride + tid];   // (nullptr: they are there)
   load_tile<T, DH>(x + v.slice_base(slice), v, s, vec, t0, c0, lds.tile);
   __syncthreads();
   const int c = tid % CW, seg = tid / CW;
@@ -547,16 +548,24 @@ __device__ __forceinline__ void filter_pack(PrepLds<DH> &lds, const T *x, const 
 
 // Forward operands: Q_F and K_F packed with k = columns, V packed with k = tokens.
 // Grid (row groups * column pieces, slices, 3: Q, K, V).
-template <typename T, int DH, int PT>
+// GATE: by workgroups that form the gate first.
+template <typename T, int DH, int PT, bool GATE>
 __global__ __launch_bounds__(256) void prep_fwd_kernel(const T *q, const T *k, const T *vv, View v, Dims s, int vec, int L,
                                                       const float *coef, const float *addQ, const float *addK,
-                                                      bf16_t *XQ, bf16_t *XK, bf16_t *VC) {
+                                                      bf16_t *XQ, bf16_t *XK, bf16_t *VC, GateFwdArgs gate) {
   using G = Geo<DH>;
   constexpr int CW = G::CW, TR = G::TR, LS = G::LS;
   __shared__ __attribute__((aligned(16))) PrepLds<DH> lds;
   const int side = blockIdx.z;
   if (side < 2) {
-    filter_pack<T, DH>(lds, side ? k : q, v, s, vec, L, coef, side ? addK : addQ, nullptr, side ? XK : XQ, nullptr);
+    if constexpr (GATE) {
+      static_assert(sizeof(PrepGate<DH>) <= sizeof(lds.tile), "the gate's scratch");
+      PrepGate<DH> &gl = *reinterpret_cast<PrepGate<DH> *>(lds.tile);
+      gate_prologue<16, DH>(gate, blockIdx.y, blockIdx.x == 0 && side == 0, gl);
+      if (threadIdx.x < 8) lds.small[threadIdx.x] = gl.coef[threadIdx.x];
+      __syncthreads();
+    }
+    filter_pack<T, DH>(lds, side ? k : q, v, s, vec, L, GATE ? nullptr : coef, side ? addK : addQ, nullptr, side ? XK : XQ, nullptr);
     return;
   }
   const int tid = threadIdx.x, slice = blockIdx.y;
@@ -1799,16 +1808,24 @@ wersa_status forward_t(const wersa_desc &c, const T *q, const T *k, const T *v, 
   const OmegaPack<T> om{omega, sigma, c.bw_floor, scalars, OA, OB, p.matrices, p.KS, p.CT, PT, (pieces + 255) / 256};
   WERSA_STAGE("split_pool", st, pool_kernel<T><<<dim3(p.chunks + om.blocks, slices, deep ? 2 : 1), 256, 0, st>>>(
       q, k, tv, p.s, vec, p.rows_per_chunk, p.chunks, qpart, kpart, om));
-  WERSA_STAGE("gate_fwd_kernel", st, gate_fwd_kernel<<<slices, kGateFwdThreads, 0, st>>>(
-      qpart, p.chunks, c.n, c.d, c.L, c.H, gate_w, gate_b, scale_w, saved + sv.qbar, saved + sv.s, saved + sv.F, coef,
-      (c.flags & WERSA_FLAG_POOLED_GATE) ? 1 : 0,
-      PooledLayout{(int64_t)c.H * p.chunks * c.d, (int64_t)p.chunks * c.d, c.d}, nullptr, 0, scalars,
-      AmaxLayout{0, 0, 0, 1}, 1));
+  const bool pooled_gate = (c.flags & WERSA_FLAG_POOLED_GATE) != 0;
+  GateFwdArgs gate{qpart, p.chunks, c.n, c.d, c.L, c.H, gate_w, gate_b, scale_w, saved + sv.qbar, saved + sv.s, saved + sv.F, coef,
+                   PooledLayout{(int64_t)c.H * p.chunks * c.d, (int64_t)p.chunks * c.d, c.d}, nullptr, 0, AmaxLayout{0, 0, 0, 1}, scalars};
+  // One round of packing workgroups: they form the gate themselves (one slice of 1024 tokens, d 64, m 64: 34.0 -> 31.4 us per call, 8 of 1500,
+  // d 32, m 512: 54.3 -> 52.9); with more rounds each would wait for it again.
+  const bool fused = !deep && !pooled_gate && p.chunks <= kGatePrologueChunks && (int64_t)p.groups * slices * 3 <= 2048;
+  if (!fused)
+    WERSA_STAGE("gate_fwd_kernel", st, gate_fwd_kernel<<<slices, kGateFwdThreads, 0, st>>>(
+        qpart, p.chunks, c.n, c.d, c.L, c.H, gate_w, gate_b, scale_w, gate.qbar, gate.s_out, gate.F_out, coef, pooled_gate ? 1 : 0, gate.ql, nullptr, 0,
+        scalars, gate.al, 1));
   if (deep)
     WERSA_STAGE("split_deep", st, deep_addend_kernel<<<dim3(slices, 2, c.d / kCoarseCols), 1024, 0, st>>>(
         qpart, kpart, coef, p.ntl, c.d, c.L, w.pyr, addQ, addK));
-  WERSA_STAGE("split_prep_fwd", st, prep_fwd_kernel<T, DH, PT><<<dim3(p.groups, slices, 3), 256, 0, st>>>(
-      q, k, v, tv, p.s, vec, c.L, coef, addQ, addK, XQ, XK, w.VC));
+  auto pack = [&](auto kern) {
+    WERSA_STAGE("split_prep_fwd", st, kern<<<dim3(p.groups, slices, 3), 256, 0, st>>>(q, k, v, tv, p.s, vec, c.L, coef, addQ, addK, XQ, XK, w.VC, gate));
+  };
+  if (fused) pack(&prep_fwd_kernel<T, DH, PT, true>);
+  else pack(&prep_fwd_kernel<T, DH, PT, false>);
   WERSA_STAGE("split_contract", st, contract_kernel<DH, PT, false><<<dim3(p.splits, p.s.mt / p.FW, slices), 512, 0, st>>>(
       XK, w.VC, nullptr, OAk, p.s, p.FW, p.TW, p.tiles_per_split, w.part, w.zpart, nullptr));
   WERSA_STAGE("split_reduce", st, reduce_kernel<DH><<<dim3(p.s.mt, slices), 256, 0, st>>>(
