@@ -929,10 +929,9 @@ __global__ __launch_bounds__(64 * NW, 2) void phiT_contract_kernel(
 // One workgroup = 64 VEC consecutive outputs x 4 waves; wave g sums the chunks g, g+4, ... with up
 // to 16 loads in flight, the four partial sums meet in LDS in a fixed order.  Workgroups
 // [0, m*DH/(64 VEC)) handle M, the ones after those b.
-// Two widths: VEC = 4 columns per lane (16-byte loads, S^T leaves as one piece per column through LDS instead of
-// 2-byte stores m apart) where that still gives every compute unit a workgroup; 1 where it does not (one slice of 131072 rows:
-// 64 workgroups would read 32 MB).  8 slices, m 256, d 64, 59 partials: 11.2 -> 7.8 us; 16 slices,
-// m 512, d 128, 8 partials: 13.8 -> 13.6 us.  Both add in the same order: the results are the same bits.
+// Where there are few outputs (reduce_short_kernel takes the others).  Two widths: VEC = 4 columns per lane (16-byte loads, S^T leaves as one
+// piece per column through LDS instead of 2-byte stores m apart) where that still gives every compute unit a workgroup; 1 where it does not
+// (one slice of 131072 rows: 64 workgroups would read 32 MB).  Both add in the same order: the results are the same bits.
 template <int DH, int VEC>
 __global__ __launch_bounds__(256) void reduce_contract_kernel(const float *Spart, const float *zpart,
                                                              int chunks, int m, const float *scale_ptr,
@@ -1002,6 +1001,76 @@ __global__ __launch_bounds__(256) void reduce_contract_kernel(const float *Spart
       for (int q = 0; q < RW; ++q) o[q] = tile[q * DH + tid];
       *reinterpret_cast<bv *>(MT + (int64_t)slice * W + (int64_t)tid * m + e0 / DH) = o;
     }
+  }
+}
+
+// The same sums, by threads that add all chunks of their four columns themselves: the four interleaved sums of above in four accumulators, the
+// same bits.  1024 elements per workgroup (RW features), 16-byte stores of S.
+// What bounds it: the latency of one round of loads, and the loads and stores in flight; four waves that share the chunks have two each where
+// a problem has many slices, a barrier, and four times the workgroups.  us, four waves and one thread: 64 workgroups of this kernel 8.0, 9.7 (4 slices,
+// d 64, m 256: 128 partials) and 5.4, 6.4; 128 8.1, 7.9 (8 slices) and 5.8, 5.6; 64 slices, d 64, m 128 7.9, 5.6; 16, d 128, m 512 13.3, 9.6;
+// 64, m 512, d 64 16.3, 11.2, d 128 28.5, 16.8.
+template <int DH>
+__global__ __launch_bounds__(256) void reduce_short_kernel(const float *Spart, const float *zpart, int chunks, int m, const float *scale_ptr,
+                                                          float *S, float *z, bf16_t *Mx, bf16_t *MT, bf16_t *bb) {
+  constexpr int DX = DH + 16, COLS = 1024, RW = COLS / DH;
+  const int slice = blockIdx.y, tid = threadIdx.x;
+  const int64_t W = (int64_t)m * DH;
+  const int wblocks = (int)(W / COLS);
+  const bool is_z = (int)blockIdx.x >= wblocks;
+  const int64_t count = is_z ? m : W, e = (int64_t)(is_z ? blockIdx.x - wblocks : blockIdx.x) * COLS + tid * 4;
+  f32x4 acc[4] = {};
+  const bool mine = e < count;   // (m may end inside the workgroup of z)
+  if (mine) {
+    const float *p = (is_z ? zpart : Spart) + (int64_t)slice * chunks * count + e;
+    int c = 0;
+    for (; c + 8 <= chunks; c += 8) {
+      f32x4 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const f32x4 *>(p + (int64_t)(c + u) * count);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc[u & 3] += v[u];
+    }
+    f32x4 v[7];
+#pragma unroll
+    for (int u = 0; u < 7; ++u) v[u] = c + u < chunks ? *reinterpret_cast<const f32x4 *>(p + (int64_t)(c + u) * count) : (f32x4)(0.f);
+#pragma unroll
+    for (int u = 0; u < 7; ++u) acc[u & 3] += v[u];
+  }
+  const f32x4 sum = ((acc[0] + acc[1]) + (acc[2] + acc[3])) * scale_ptr[slice * kCoefStride];
+  typedef bf16_t b16x4 __attribute__((ext_vector_type(4)));
+  b16x4 b;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) b[q] = f32_to_bf16(sum[q]);
+  if (is_z) {
+    if (!mine) return;
+    *reinterpret_cast<f32x4 *>(z + (int64_t)slice * m + e) = sum;
+    *reinterpret_cast<b16x4 *>(bb + (int64_t)slice * m + e) = b;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      u16x8 lo = {}, hi = {};
+      lo[0] = b[q];
+      u16x8 *ext = reinterpret_cast<u16x8 *>(Mx + ((int64_t)slice * m + e + q) * DX + DH);
+      ext[0] = lo;
+      ext[1] = hi;
+    }
+    return;
+  }
+  *reinterpret_cast<f32x4 *>(S + (int64_t)slice * W + e) = sum;
+  const int r = (int)(e / DH), cidx = (int)(e % DH);
+  *reinterpret_cast<b16x4 *>(Mx + ((int64_t)slice * m + r) * DX + cidx) = b;
+  // M transposed: column c of the RW features as pieces of eight; LDS rows of RW + 4 values
+  __shared__ __align__(16) bf16_t tile[DH * (RW + 4)];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) tile[(cidx + q) * (RW + 4) + tid * 4 / DH] = b[q];
+  __syncthreads();
+  constexpr int PIECES = RW / 8;
+  if (tid < DH * PIECES) {
+    const int c = tid / PIECES, k = tid % PIECES * 8;
+    u16x8 o;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) o[q] = tile[c * (RW + 4) + k + q];
+    *reinterpret_cast<u16x8 *>(MT + (int64_t)slice * W + (int64_t)c * m + (int64_t)blockIdx.x * RW + k) = o;
   }
 }
 
@@ -2861,7 +2930,11 @@ void launch_contract(const wersa_desc &c, const FastPlan &p, const _Float16 *xf,
                 (reduce_contract_kernel<DH, VEC.value><<<dim3((unsigned)(W / cols + (c.m + cols - 1) / cols), slices), 256, 0, st>>>(
                     w.Spart, w.zpart, p.chunksC, c.m, w.coef + kCoefCscale, S, z, Mx, MT, bb)));
   };
-  if (slices * (W / 256) >= 256) reduce(std::integral_constant<int, 4>());
+  if (slices * (W / 1024) >= 128)   // (see reduce_short_kernel)
+    WERSA_STAGE("wersa_reduce_contract", st,
+                (reduce_short_kernel<DH><<<dim3((unsigned)(W / 1024 + (c.m + 1023) / 1024), slices), 256, 0, st>>>(
+                    w.Spart, w.zpart, p.chunksC, c.m, w.coef + kCoefCscale, S, z, Mx, MT, bb)));
+  else if (slices * (W / 256) >= 256) reduce(std::integral_constant<int, 4>());
   else reduce(std::integral_constant<int, 1>());
 }
 
