@@ -8,34 +8,36 @@ q, k, v: (B, H, n, d) with a shared layout (any strides, last dimension contiguo
 flow to q, k, v, sigma, gate_w, gate_b, scale_w (omega_rf is a fixed random matrix) and, for the
 block, to x and the four weight matrices (float32 gradients cast to the weights' dtype).
 """
+import ctypes
+
 import torch
 
 from . import binding
 
 
-class _WersaAttention(torch.autograd.Function):
-    @staticmethod
-    def forward(ctx, q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps, bw_floor):
-        out, saved = binding.wersa_forward(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps=eps,
-                                           bw_floor=bw_floor)
-        ctx.save_for_backward(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, out, saved)
-        ctx.cfg = (L, eps, bw_floor)
-        return out
+_node = None
 
-    @staticmethod
-    def backward(ctx, dout):
-        q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, out, saved = ctx.saved_tensors
-        L, eps, bw_floor = ctx.cfg
-        if dout.stride() != q.stride():
-            dout = torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device).copy_(dout)
-        g = binding.wersa_backward(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, out, dout, saved, L,
-                                   eps=eps, bw_floor=bw_floor)
-        return (g["dq"], g["dk"], g["dv"], None, g["dsigma"], g["dgate_w"], g["dgate_b"], g["dscale_w"],
-                None, None, None)
+
+def _load_node():
+    """The extension that holds the attention core's node of the autograd graph (csrc/wersa_torch.cpp), on the library that the
+    binding has loaded."""
+    global _node
+    if _node is None:
+        lib = binding.load_library()
+        try:
+            from . import _wersa_torch as node
+        except ImportError as e:
+            raise RuntimeError("the autograd extension _wersa_torch.so is missing or does not load: build it with "
+                               "`python -m paper_2507_08637_amd.build` (there is no fallback path)") from e
+        node.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.wersa_forward, lib.wersa_backward)))
+        _node = node
+    return _node
 
 
 def wersa_attention(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps=1e-6, bw_floor=1e-6):
-    return _WersaAttention.apply(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps, bw_floor)
+    desc, saved_bytes, workspace = binding.checked_desc(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps, bw_floor, 0)
+    return (_node or _load_node()).attention(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, bytes(desc), saved_bytes, workspace,
+                                             binding.wersa_workspace_bytes(desc, 1))
 
 
 class _WersaBlock(torch.autograd.Function):

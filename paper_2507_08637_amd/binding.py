@@ -138,8 +138,10 @@ def _ptr(t):
 
 
 def _stream(stream):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return ctypes.c_void_p(stream.cuda_stream)
+    # (the handle alone: building a torch.cuda.Stream for it takes 3 us)
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def _nbytes(t):
@@ -158,8 +160,9 @@ def _scratch(nbytes, like, stream):
 
 
 def _same_layout(ref, *others):
+    shape, stride, dtype = ref.shape, ref.stride(), ref.dtype
     for t in others:
-        assert t.shape == ref.shape and t.stride() == ref.stride() and t.dtype == ref.dtype, \
+        assert t.shape == shape and t.stride() == stride and t.dtype == dtype, \
             "q, k, v, out and gradients must share shape, strides and dtype"
 
 
@@ -215,27 +218,33 @@ def alloc_like(desc, ref, for_backward):
     return saved, ws
 
 
-def wersa_forward(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps=1e-6, bw_floor=1e-6,
-                  out=None, saved=None, workspace=None, stream=None, flags=0):
-    """Returns (out, saved).  All tensor arguments live on one CUDA device."""
+def checked_desc(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps, bw_floor, flags):
+    """(descriptor, bytes of saved, bytes of the forward's workspace) of a forward call's arguments, which are checked."""
     lib = load_library()
     _same_layout(q, k, v)
     desc = make_desc(q, L, omega_rf.shape[-1], eps, bw_floor, flags)
     _check_omega(omega_rf, q, flags)
     for p in (sigma, gate_w, gate_b, scale_w):
         assert p.dtype == torch.float32 and p.is_contiguous()
+    sb = lib.wersa_saved_bytes(ctypes.byref(desc))
+    if sb == 0:
+        _check(_probe(desc))
+    return desc, sb, lib.wersa_workspace_bytes(ctypes.byref(desc), 0)
+
+
+def wersa_forward(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps=1e-6, bw_floor=1e-6,
+                  out=None, saved=None, workspace=None, stream=None, flags=0):
+    """Returns (out, saved).  All tensor arguments live on one CUDA device."""
+    lib = load_library()
+    desc, sb, wb = checked_desc(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps, bw_floor, flags)
     if out is None:
         out = torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device)
     else:
         _same_layout(q, out)
-    sb = lib.wersa_saved_bytes(ctypes.byref(desc))
-    if sb == 0:
-        _check(_probe(desc))
     if saved is None:
         saved = torch.empty(sb // 4, dtype=torch.float32, device=q.device)
     else:   # the C ABI takes no size for `saved`: checked here
         assert _nbytes(saved) >= sb, f"saved buffer holds {_nbytes(saved)} bytes, wersa_saved_bytes asks for {sb}"
-    wb = lib.wersa_workspace_bytes(ctypes.byref(desc), 0)
     if workspace is None:
         workspace = _scratch(wb, q, stream)
     _check(lib.wersa_forward(ctypes.byref(desc), _ptr(q), _ptr(k), _ptr(v), _ptr(omega_rf), _ptr(sigma),
