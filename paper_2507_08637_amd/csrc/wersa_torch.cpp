@@ -1,7 +1,7 @@
 // The attention core as a node of torch's autograd graph, in C++: what a training step pays for on the host beyond the launches.  The engine runs
 // a backward on a thread of its own, and interpreter state, reference counts and runtime structures that both threads touch move between their
 // caches at every change.  2 x 4 slices of 1000 tokens, d 64, m 256, bf16, forward and backward: 235 to 246 us where the engine's thread runs far from
-the caller's and 128 to 136 where near with a node written in Python, 128 to 138 and 98 with this one; its kernels take 97.
+// the caller's and 128 to 136 where near with a node written in Python, 128 to 138 and 98 with this one; its kernels take 97.
 //
 // The library is reached through the addresses of its entry points (bind): this module has no link to it, and loads whichever the
 // binding loaded.  Arguments are checked by the caller; the library checks the rest, and its status is raised as the binding's error.
