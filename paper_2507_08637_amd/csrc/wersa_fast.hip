@@ -1126,9 +1126,9 @@ __device__ __forceinline__ void buf_store4(RowBuf r, uint32_t off, float v) {
 // not a multiple of 64; rows are read and written through buffers that end at row n (see row_buffer).  The plain instance has
 // none of that code.  DEEP: L > 6: X_F starts from the per-tile addend of the levels above 6 (tile_add
 // [slices][ceil(n / 64)][DH]).
-constexpr int kWavesApply = 8;   // two per SIMD: one's epilogue runs under the other's matrix instructions
-template <int MODE, int MC, bool LN, bool RAGGED, bool DEEP>
-__global__ __launch_bounds__(kWavesApply * 64, 2) void rows_kernel(
+constexpr int kWavesApply = 8;   // two per SIMD: one's epilogue runs under the other's matrix instructions (four with few rows, see fast_plan)
+template <int MODE, int MC, bool LN, bool RAGGED, bool DEEP, int NW = kWavesApply>
+__global__ __launch_bounds__(NW * 64, 2) void rows_kernel(
     const bf16_t *x, View vx,  // X (Q or K)
     const _Float16 *omT,       // Omega^T fp16 [m][DH]
     const bf16_t *MT,          // S^T (MODE 0) / dS^T (MODE 3), bf16 [slices][DH][m]
@@ -1141,7 +1141,7 @@ __global__ __launch_bounds__(kWavesApply * 64, 2) void rows_kernel(
     uint32_t *bits)            // MODE 3: the ReLU's decisions (see positive_bits)
 {
   static_assert(MODE == 0 || MODE == 3, "the gradient modes have masked_rows_kernel");
-  constexpr int DH = 64, NW = kWavesApply;
+  constexpr int DH = 64;
   constexpr int KS = DH / 16, CT = DH / 32;
   constexpr int AS = DH + 8;            // stride of the [feature][DH] fp16 array (16-byte reads)
   constexpr int NT = NW * 64;
@@ -1480,12 +1480,12 @@ __device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t voff, const voi
 // X comes straight from memory into the wave's panels, one of 4 KiB per 32 columns ([64 rows][32], requested a row group ahead), and
 // dX goes out through the same panel ([32 columns][64 rows]: 16-byte piece q of column c at slot q ^ (c % 8)).
 // ------------------------------------------------------------------------------------
-template <int MODE, int MC, bool RAGGED, bool DEEP>
-__global__ __launch_bounds__(kWavesApply * 64, 2) void masked_rows_kernel(
+template <int MODE, int MC, bool RAGGED, bool DEEP, int NW = kWavesApply>
+__global__ __launch_bounds__(NW * 64, 2) void masked_rows_kernel(
     const bf16_t *x, View vx, const bf16_t *y, View vy, const float *Dsaved, const float *arow, const uint32_t *bits,
     const bf16_t *omega, const bf16_t *Mx, const float *coef, int n, int m, int row_groups, bf16_t *out, View vo,
     float *partF, int L, float *tile_gsum) {
-  constexpr int DH = 64, KS = 4, KSX = 5, CT = 2, NW = kWavesApply, NT = NW * 64;
+  constexpr int DH = 64, KS = 4, KSX = 5, CT = 2, NT = NW * 64;
   constexpr int AM = DH + 16 + 8, BS = MC + 8, WORDS = MC / 64;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   bf16_t *s_Mx = reinterpret_cast<bf16_t *>(smem_raw);                      // [MC][AM]: (S | z) or (dS | dz)
@@ -1895,8 +1895,8 @@ __global__ __launch_bounds__(kWavesApply * 64, 2) void masked_rows_kernel(
     partF[((int64_t)slice * rows + blockIdx.x) * (L + 1) + tid] = tid < L ? ul - ul1 : ul;
   }
 }
-constexpr size_t masked_smem_bytes(int mc) {
-  return (size_t)mc * 88 * 2 + (size_t)64 * (mc + 8) * 2 + kWavesApply * 64 * 4 + (size_t)kWavesApply * 8192;
+constexpr size_t masked_smem_bytes(int mc, int waves) {
+  return (size_t)mc * 88 * 2 + (size_t)64 * (mc + 8) * 2 + (size_t)waves * (64 * 4 + 8192);
 }
 
 // ------------------------------------------------------------------------------------
@@ -2634,7 +2634,7 @@ struct FastPlan {
   int DH, FW, NWC, MB, mc;   // NWC: waves of a phiT_contract workgroup; mc: features staged in LDS per pass by the rows kernels of head dimension 64
   int chunksQ, rowsQ;   // pooled-query partial sums
   int chunksC, rowsC;   // split of n in phiT_contract
-  int rowGroups, rowsWgs;   // rows kernels: groups of 512 rows (head dimension 64) or 256 (128), workgroups per slice
+  int rowWaves, rowGroups, rowsWgs;   // rows kernels: groups of 64 rowWaves rows (head dimension 64) or 256 (128), workgroups per slice
   int chunksL, rowsL;   // split of n in ln_prep
 };
 
@@ -2669,7 +2669,14 @@ FastPlan fast_plan(const wersa_desc &c) {
   const int wantL = kLnWgs / slices < 1 ? 1 : kLnWgs / slices, bpl = (blocks + wantL - 1) / wantL;
   p.rowsL = bpl * 64;
   p.chunksL = (blocks + bpl - 1) / bpl;
-  p.rowGroups = c.d == 64 ? (blocks + kWavesApply - 1) / kWavesApply : (c.n + kWideRows - 1) / kWideRows;
+  // Few rows (head dimension 64): workgroups of four waves, one per SIMD, where that leaves compute units without one; the time is that of one
+  // wave's block then, and two on a SIMD share it.  us of the query side's and the key side's gradient, forward and dV, eight waves and four:
+  // 16 workgroups of four (4 slices of 1000 rows, m 256) 16.0 15.2 11.0 11.1, 13.9 12.7 10.1 9.9; 128 (8 of 4096) 17.4 16.6 11.8 12.1, 15.8 14.7 11.1 11.3, with
+  // m 512 23.9 22.6 18.1 17.9, 20.3 18.7 16.4 15.7; 240 (20 of 3000) 18.8 18.0 13.0 13.0, 18.2 16.6 13.0 12.8; 256 (32 of 2000) 19.0 18.3 13.1 13.1, 19.2 17.5
+  // 13.7 13.2.  (Instances with the LayerNorm output stage or levels above 6 have eight.)
+  p.rowWaves = kWavesApply;
+  if (c.d == 64 && c.L <= kTileL && !(c.flags & WERSA_FLAG_LAYERNORM) && (int64_t)slices * ((blocks + 3) / 4) <= 192) p.rowWaves = 4;
+  p.rowGroups = c.d == 64 ? (blocks + p.rowWaves - 1) / p.rowWaves : (c.n + kWideRows - 1) / kWideRows;
   // One resident workgroup per compute unit (the operand arrays fill most of the LDS): at most
   // 256 workgroups in total, so that no second, mostly empty round follows the first.
   const int wgs = 256 / slices < 1 ? 1 : 256 / slices;
@@ -2761,8 +2768,8 @@ FastWs fast_ws(const wersa_desc &c, const FastPlan &p, int bwd, float *base, flo
 }
 
 template <int MODE>
-size_t rows_smem_bytes(int mc) {   // of rows_kernel
-  constexpr int DH = 64, NW = kWavesApply;
+size_t rows_smem_bytes(int mc, int NW) {   // of rows_kernel
+  constexpr int DH = 64;
   size_t s = (size_t)mc * (DH + 8) * 2 + (size_t)DH * (mc + 8) * 2;
   if (MODE == 0) s += (size_t)mc * 2;
   s += (size_t)NW * (DH / 32) * 64 * 36 * 2 + 2 * 512 * 2;   // X panels per wave and the filter table
@@ -2817,13 +2824,13 @@ hipError_t launch_rows64(const wersa_desc &c, const FastPlan &p, const bf16_t *x
   // key-side modes take the second random matrix when the descriptor has two
   const _Float16 *omT = w.omT + (((c.flags & WERSA_FLAG_SEPARATE_OMEGA) && MODE >= 2) ? (int64_t)c.d * c.m : 0);
   const View tv{c.stride_b, c.stride_h, c.stride_n, c.H};
-  const size_t smem = rows_smem_bytes<MODE>(p.mc);
+  const size_t smem = rows_smem_bytes<MODE>(p.mc, p.rowWaves);
   auto go = [&](auto kern) -> hipError_t {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
     WERSA_STAGE(MODE == 0 ? "wersa_rows_fwd" : "wersa_rows_bwd_v", st,
-                kern<<<dim3(p.rowsWgs, c.B * c.H), kWavesApply * 64, smem, st>>>(
+                kern<<<dim3(p.rowsWgs, c.B * c.H), p.rowWaves * 64, smem, st>>>(
                     x, tv, omT, MT, bb, w.coef, c.eps, c.n, c.m, p.rowGroups, out, tv, Dout, MODE == 3 ? w.addK : w.addQ, w.bitsK));
     return hipSuccess;
   };
@@ -2833,6 +2840,8 @@ hipError_t launch_rows64(const wersa_desc &c, const FastPlan &p, const bf16_t *x
     constexpr int MC = decltype(mcv)::value;
     constexpr bool LNV = decltype(lnv)::value;
     if (deep) return ragged ? go(&rows_kernel<MODE, MC, LNV, true, true>) : go(&rows_kernel<MODE, MC, LNV, false, true>);
+    if constexpr (!LNV)
+      if (p.rowWaves == 4) return ragged ? go(&rows_kernel<MODE, MC, false, true, false, 4>) : go(&rows_kernel<MODE, MC, false, false, false, 4>);
     return ragged ? go(&rows_kernel<MODE, MC, LNV, true, false>) : go(&rows_kernel<MODE, MC, LNV, false, false>);
   };
   using M128 = std::integral_constant<int, 128>;
@@ -2850,11 +2859,11 @@ hipError_t launch_masked64(const wersa_desc &c, const FastPlan &p, const bf16_t 
   if ((c.flags & WERSA_FLAG_SEPARATE_OMEGA) && MODE == 2) omega += (int64_t)c.d * c.m;
   const View tv{c.stride_b, c.stride_h, c.stride_n, c.H};
   auto go = [&](auto kern) -> hipError_t {
-    const size_t smem = masked_smem_bytes(p.mc);
+    const size_t smem = masked_smem_bytes(p.mc, p.rowWaves);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
     WERSA_STAGE(MODE == 1 ? "wersa_grad_q" : "wersa_grad_k", st,
-                kern<<<dim3(p.rowsWgs, c.B * c.H), kWavesApply * 64, smem, st>>>(
+                kern<<<dim3(p.rowsWgs, c.B * c.H), p.rowWaves * 64, smem, st>>>(
                     x, tv, y, yview ? *yview : tv, Dsaved, arow, MODE == 1 ? w.bitsQ : w.bitsK, omega, Mx, w.coef, c.n, c.m,
                     p.rowGroups, out, tv, partF, c.L, MODE == 1 ? w.gsumQ : w.gsumK));
     return hipSuccess;
@@ -2863,6 +2872,7 @@ hipError_t launch_masked64(const wersa_desc &c, const FastPlan &p, const bf16_t 
   auto pick = [&](auto MC) -> hipError_t {
     constexpr int M = MC.value;
     if (deep) return ragged ? go(&masked_rows_kernel<MODE, M, true, true>) : go(&masked_rows_kernel<MODE, M, false, true>);
+    if (p.rowWaves == 4) return ragged ? go(&masked_rows_kernel<MODE, M, true, false, 4>) : go(&masked_rows_kernel<MODE, M, false, false, 4>);
     return ragged ? go(&masked_rows_kernel<MODE, M, true, false>) : go(&masked_rows_kernel<MODE, M, false, false>);
   };
   return p.mc == 256 ? pick(std::integral_constant<int, 256>{}) : pick(std::integral_constant<int, 128>{});
