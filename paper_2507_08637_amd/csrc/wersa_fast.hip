@@ -716,16 +716,16 @@ __global__ __launch_bounds__(64 * NW, 2) void phiT_contract_kernel(
     }
   };
 
+  // The filter's table is visible after the barrier below.  (Loads return in order: the coefficients, where they are there, before the rows.)
+  const bool form_gate = GATE && gate.qpart;
+  if (FUSE && !form_gate) build_filter_table(gt, coef + slice * kCoefStride, tid, 256);
   if (steps > 0) fetch(t_begin);
-  // (the table is visible after the barrier below)
-  if (GATE && gate.qpart) {
+  if (form_gate) {
     typedef GateLds<4, 64> Lds;
     static_assert(sizeof(Lds) <= sizeof(xq) || !GATE, "the gate's scratch lies where X_F goes later");
     Lds &lds = *reinterpret_cast<Lds *>(&xq[0]);
     gate_prologue<4, 64>(gate, slice, chunk == 0 && blockIdx.y == 0, lds);
     build_filter_table(gt, lds.coef, tid, 256);
-  } else if (FUSE) {
-    build_filter_table(gt, coef + slice * kCoefStride, tid, 256);
   }
   if (steps > 0) stash(0);
   __syncthreads();
