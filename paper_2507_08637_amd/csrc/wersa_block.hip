@@ -5,7 +5,8 @@
 //   NN  C[M][N] = A[M][K] B[K][N]              (forward: activations times weights as they are stored; the three
 //       projections in one launch)
 //   NT  C[M][N] = sum_s A_s[M][K] B_s[N][K]^T   (both operands contiguous along K; up to three
-//       (A, B) pairs summed, which gives dX = dQ' W^Q^T + dK' W^K^T + dV' W^V^T in one pass)
+//       (A, B) pairs summed, which gives dX = dQ' W^Q^T + dK' W^K^T + dV' W^V^T in one pass; many tokens: NN
+//       on transposed copies of the weights)
 //   TN  C[M][N] = A[K][M]^T B[K][N]            (both operands contiguous across K: the weight
 //       gradients X^T dQ' ...; split over K into float32 partials, reduced in fixed order)
 // Heads are never transposed: the core reads and writes (B, n, H*d) through its strides.
@@ -436,6 +437,37 @@ __global__ void splitk_reduce_kernel(const float *part, int splits, int64_t coun
   *reinterpret_cast<float4 *>(out + e) = acc;
 }
 
+// out[i] = w[i]^T for up to four hidden x hidden matrices (blockIdx.z), one 64 x 64 tile per workgroup; w's base may be any.
+struct TransposeJob {
+  const bf16_t *w[4];
+  bf16_t *out[4];
+};
+__global__ __launch_bounds__(256) void transpose_kernel(TransposeJob job, int hidden) {
+  constexpr int LS = 64 + 2;   // (rows 33 words apart: a column's values are in different banks)
+  __shared__ bf16_t tile[64 * LS];
+  typedef u16x8 u16x8_any __attribute__((aligned(2)));
+  typedef uint32_t u32_any __attribute__((aligned(4)));
+  const bf16_t *w = job.w[blockIdx.z];
+  bf16_t *out = job.out[blockIdx.z];
+  const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int e = threadIdx.x + 256 * u, r = e >> 3, c = (e & 7) * 8;
+    const u16x8 v = *reinterpret_cast<const u16x8_any *>(w + (int64_t)(r0 + r) * hidden + c0 + c);
+#pragma unroll
+    for (int q = 0; q < 8; q += 2) *reinterpret_cast<u32_any *>(&tile[r * LS + c + q]) = (uint32_t)v[q] | (uint32_t)v[q + 1] << 16;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int e = threadIdx.x + 256 * u, c = e >> 3, r = (e & 7) * 8;
+    u16x8 v;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = tile[(r + q) * LS + c];
+    *reinterpret_cast<u16x8 *>(out + (int64_t)(c0 + c) * hidden + r0 + r) = v;
+  }
+}
+
 // A grid of large tiles is one workgroup per compute unit, each takes several tiles.  Large tiles from one per compute unit on; fewer leave units idle.  Block inference, all products in large tiles against
 // this rule: 2048 tokens, hidden 512 (48 and 16 large tiles) 68.7 -> 53.2 us; 4096 tokens, hidden 1024 (192 and 64)
 // 115.9 -> 106.8; 8192 tokens (384, large either way, and 128) 161.8 -> 156.2; 16384 tokens (all large) 251.9, 251.8.
@@ -477,6 +509,7 @@ struct BlockPlan {
   int64_t tokens, hidden, act;   // act = tokens * hidden elements
   int splits, k_chunk;           // split of the token axis for the weight gradients
   int wgrads;                    // weight gradients of Q, K, V per launch: 3 or 1
+  bool transpose;                // the backward's products with a weight's transpose take a transposed copy
   wersa_desc core;
 };
 
@@ -499,6 +532,11 @@ BlockPlan block_plan(const wersa_desc &c) {
   // Three in one launch while their partials stay below 512 MiB (hidden 1024: 402 MB).  At hidden 2048 one product fills the chip
   // four times over and three launches with a third of the partials (805 -> 268 MB) take the same time (856 us each, 131072 tokens).
   p.wgrads = (int64_t)kMaxSrc * p.splits * p.hidden * p.hidden * 4 <= (int64_t)512 << 20 ? 3 : 1;
+  // With a transposed copy of the weight the second operand's requests are whole lines (see gemm_bf16_kernel): dA 964 -> 828 us, dX 859 -> 831 per
+  // product at 131072 tokens, hidden 2048; the copies take 12 us.  us per training step without and with them: hidden 512, 16384 tokens 369, 371,
+  // 32768 523, 521, 131072 1588, 1571; 1024, 16384 799, 810, 32768 1285, 1271, 131072 4064, 4002; 2048, 8192 1320, 1322, 16384 2115, 2098, 32768
+  // 3721, 3672, 131072 13196, 12952.
+  p.transpose = p.tokens >= 32768;
   p.core = c;
   p.core.stride_n = p.hidden;
   p.core.stride_h = c.d;
@@ -508,7 +546,7 @@ BlockPlan block_plan(const wersa_desc &c) {
 
 // Byte layouts. saved: Q' | K' | V' | A (bf16, (B, n, hidden)) | the core's saved buffer.
 struct BlockSaved { size_t qp, kp, vp, a, core, total; };
-struct BlockWs { size_t qsums, qmax, dA, dQp, dKp, dVp, part, core, total; };
+struct BlockWs { size_t qsums, qmax, wt, dA, dQp, dKp, dVp, part, core, total; };
 size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 
 BlockSaved block_saved(const BlockPlan &p) {
@@ -532,6 +570,7 @@ BlockWs block_ws(const BlockPlan &p, int bwd) {
     w.qmax = off;  off += up256((size_t)(p.tokens / 128) * (p.hidden / kPooledMaxCols) * 4);   // and the largest |Q'| per 64 columns
   } else {
     const size_t act = up256((size_t)p.act * 2);
+    w.wt = off;  off += p.transpose ? 4 * up256((size_t)p.hidden * p.hidden * 2) : 0;
     w.dA = off;  off += act;
     w.dQp = off; off += act;
     w.dKp = off; off += act;
@@ -696,14 +735,28 @@ wersa_status wersa_block_backward(const wersa_desc *desc, const void *x, const v
     return true;
   };
 
-  {  // dA = dY W_out^T: B operand [N = in][K = out] is W_out as stored
+  // Products with a weight's transpose.
+  const bf16_t *wt[4] = {(const bf16_t *)wq, (const bf16_t *)wk, (const bf16_t *)wv, (const bf16_t *)wo};
+  if (p.transpose) {
+    TransposeJob job{};
+    for (int i = 0; i < 4; ++i) {
+      job.w[i] = wt[i];
+      job.out[i] = (bf16_t *)(ws + w.wt + i * up256((size_t)wcount * 2));
+      wt[i] = job.out[i];
+    }
+    WERSA_STAGE("wersa_transpose", st, transpose_kernel<<<dim3(hid / 64, hid / 64, 4), 256, 0, st>>>(job, hid));
+  }
+  auto times_transpose = [&](GemmJob &job) {
+    return (p.transpose ? launch_gemm<false, true, false>("wersa_gemm_nn", job, hid, M, hid, hid, hid, 1, st)
+                        : launch_gemm<false, false, false>("wersa_gemm_nt", job, hid, M, hid, hid, hid, 1, st)) == hipSuccess;
+  };
+  {  // dA = dY W_out^T
     GemmJob job{};
     job.a[0] = (const bf16_t *)dy;
-    job.b[0] = (const bf16_t *)wo;
+    job.b[0] = wt[3];
     job.c[0] = dA;
     job.count = job.batch = 1;
-    if (launch_gemm<false, false, false>("wersa_gemm_nt", job, hid, M, hid, hid, hid, 1, st) != hipSuccess)
-      return WERSA_ERR_LAUNCH;
+    if (!times_transpose(job)) return WERSA_ERR_LAUNCH;
   }
   {
     const bf16_t *const right[1] = {(const bf16_t *)dy};
@@ -717,14 +770,13 @@ wersa_status wersa_block_backward(const wersa_desc *desc, const void *x, const v
   if (cs != WERSA_OK) return cs;
   {  // dX = dQ' W^Q^T + dK' W^K^T + dV' W^V^T
     GemmJob job{};
-    job.a[0] = dQp; job.b[0] = (const bf16_t *)wq;
-    job.a[1] = dKp; job.b[1] = (const bf16_t *)wk;
-    job.a[2] = dVp; job.b[2] = (const bf16_t *)wv;
+    job.a[0] = dQp; job.b[0] = wt[0];
+    job.a[1] = dKp; job.b[1] = wt[1];
+    job.a[2] = dVp; job.b[2] = wt[2];
     job.c[0] = dx;
     job.count = 3;
     job.batch = 1;
-    if (launch_gemm<false, false, false>("wersa_gemm_nt", job, hid, M, hid, hid, hid, 1, st) != hipSuccess)
-      return WERSA_ERR_LAUNCH;
+    if (!times_transpose(job)) return WERSA_ERR_LAUNCH;
   }
   const bf16_t *const right[3] = {dQp, dKp, dVp};
   float *const outs[3] = {dwq, dwk, dwv};

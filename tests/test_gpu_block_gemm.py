@@ -18,6 +18,8 @@ SHAPES = [
     (1, 8, 24576, 64),
     # 256-wide tiles of eight steps, 97 per XCD on 32 workgroups: four of them in one workgroup and three in the others
     (1, 4, 65792, 64),
+    # products with a weight's transpose on transposed copies (from 32768 tokens on): hidden no power of two
+    (1, 12, 32768, 64),
     # weight gradients: 31 splits of nine steps and one of a single step, two tiles per workgroup
     (1, 16, 8960, 64),
 ]
