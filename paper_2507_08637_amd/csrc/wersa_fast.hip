@@ -2488,14 +2488,18 @@ __global__ __launch_bounds__(256) void add_pooled_kernel(bf16_t *dq, View v, con
 
 // Forward: blockIdx.y = 0 for Q, 1 for K; blockIdx.z = group of 16 columns.  T*: tile sums
 // [S][ntiles][d]; A*: addends, same shape; pyr: 2 * S pyramids of pyramid_floats(ntiles, d).
+// IN_LDS: the pyramid is (pyramid_in_lds bytes of dynamic LDS).
+template <bool IN_LDS>
 __global__ __launch_bounds__(1024) void coarse_addend_kernel(const float *Tq, const float *Tk, const float *coef,
                                                             int ntiles, int d, int L, float *pyr, float *Aq, float *Ak) {
-  const int slice = blockIdx.x, side = blockIdx.y;
-  const int c = kCoarseCols * blockIdx.z + (threadIdx.x & (kCoarseCols - 1)), g = threadIdx.x / kCoarseCols;
+  extern __shared__ float lds_pyr[];
+  const int slice = blockIdx.x, side = blockIdx.y, cl = threadIdx.x & (kCoarseCols - 1);
+  const int c = kCoarseCols * blockIdx.z + cl, g = threadIdx.x / kCoarseCols;
   const int64_t base = (int64_t)slice * ntiles * d;
-  float *P = pyr + ((int64_t)slice * 2 + side) * pyramid_floats(ntiles, d);
-  build_tile_pyramid((side ? Tk : Tq) + base, ntiles, d, L - 6, P, c, g);
-  tile_addend(P, coef + slice * kCoefStride, ntiles, d, L - 6, (side ? Ak : Aq) + base, c, g);
+  const float *T = (side ? Tk : Tq) + base, *cf = coef + slice * kCoefStride;
+  float *A = (side ? Ak : Aq) + base, *P = pyr + ((int64_t)slice * 2 + side) * pyramid_floats(ntiles, d);
+  if constexpr (IN_LDS) coarse_addends(T, cf, ntiles, d, L - 6, first_level((lds_float *)lds_pyr, ntiles, kCoarseCols, cl), A, c, g);
+  else coarse_addends(T, cf, ntiles, d, L - 6, first_level(P, ntiles, d, c), A, c, g);
 }
 
 // Backward, after both gradient kernels: Tg* = tile sums of dX_F (written by their epilogues),
@@ -2503,61 +2507,35 @@ __global__ __launch_bounds__(1024) void coarse_addend_kernel(const float *Tq, co
 // rows row .. row + d / 16 - 1 (one per workgroup) of the band partials part*[S][row + d / 16][L + 1], the
 // contribution of the levels above 6: with u_l = 2^-l * sum over 2^l-row blocks and columns of
 // blocksum(dX_F) * blocksum(X), band 6 gets -u_7, band l (7 .. L-1) gets u_l - u_{l+1}, band L
-// gets u_L (the gradient kernels leave u_6 alone in band 6 and zeros above).  Bound by latency: a chain of barriers,
-// one per level and signal and two per inner product before, one per level now (8 slices of 469 tiles, 4 levels:
-// 30.7 -> 14.1 us).
+// gets u_L (the gradient kernels leave u_6 alone in band 6 and zeros above).
+template <bool IN_LDS>
 __global__ __launch_bounds__(1024) void coarse_bwd_kernel(const float *TgQ, const float *TgK, const float *TxQ,
                                                          const float *TxK, const float *coef, int ntiles, int d, int L,
                                                          float *pyr, float *AQ, float *AK, float *partQ,
                                                          float *partK, int row) {
-  const int slice = blockIdx.x, side = blockIdx.y, J = L - 6;
-  const int c = kCoarseCols * blockIdx.z + (threadIdx.x & (kCoarseCols - 1)), g = threadIdx.x / kCoarseCols;
+  extern __shared__ float lds_pyr[];
+  const int slice = blockIdx.x, side = blockIdx.y, J = L - 6, cl = threadIdx.x & (kCoarseCols - 1);
+  const int c = kCoarseCols * blockIdx.z + cl, g = threadIdx.x / kCoarseCols;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t base = (int64_t)slice * ntiles * d;
   float *Pg = pyr + (((int64_t)slice * 2 + side) * 2) * pyramid_floats(ntiles, d);
   float *Px = Pg + pyramid_floats(ntiles, d);
-  // both pyramids level by level, the inner product of a level from the registers that hold its sums
   __shared__ float red[kMaxBands][16];
   __shared__ float u[kMaxBands + 1];
-  const float *pg = (side ? TgK : TgQ) + base, *px = (side ? TxK : TxQ) + base;
-  float *lg = Pg, *lx = Px;
-  int nprev = ntiles;
-  for (int j = 1; j <= J; ++j) {
-    const int nb = (nprev + 1) / 2;
-    float acc = 0.f;
-    for (int b0 = g; b0 < nb; b0 += kCoarseBatch * kCoarseGroups) {
-      float sg[kCoarseBatch], sx[kCoarseBatch];
-#pragma unroll
-      for (int i = 0; i < kCoarseBatch; ++i) {
-        sg[i] = tile_pair(pg, b0 + i * kCoarseGroups, nb, nprev, d, c);
-        sx[i] = tile_pair(px, b0 + i * kCoarseGroups, nb, nprev, d, c);
-      }
-#pragma unroll
-      for (int i = 0; i < kCoarseBatch; ++i) {
-        acc = fmaf(sg[i], sx[i], acc);
-        const int b = b0 + i * kCoarseGroups;
-        if (b < nb) {
-          lg[b * d + c] = sg[i];
-          lx[b * d + c] = sx[i];
-        }
-      }
-    }
-    acc = wave_sum64(acc);
-    if (lane == 0) red[j][wave] = acc;
-    __threadfence_block();
-    __syncthreads();
-    pg = lg;
-    px = lx;
-    lg += nb * d;
-    lx += nb * d;
-    nprev = nb;
+  const float *tg = (side ? TgK : TgQ) + base, *tx = (side ? TxK : TxQ) + base, *cf = coef + slice * kCoefStride;
+  float *A = (side ? AK : AQ) + base;
+  if constexpr (IN_LDS) {
+    lds_float *p = (lds_float *)lds_pyr;
+    coarse_bwd<false>(tg, tx, cf, ntiles, d, J, first_level(p, ntiles, kCoarseCols, cl), first_level(p + (ntiles + 32) * kCoarseCols, ntiles, kCoarseCols, cl), A,
+               c, g, nullptr, red);
+  } else {
+    coarse_bwd<false>(tg, tx, cf, ntiles, d, J, first_level(Pg, ntiles, d, c), first_level(Px, ntiles, d, c), A, c, g, nullptr, red);
   }
   if (wave == 0 && lane >= 1 && lane <= J) {
     float tot = 0.f;
     for (int i = 0; i < 16; ++i) tot += red[lane][i];
     u[6 + lane] = tot / (float)(1 << (6 + lane));
   }
-  tile_addend(Pg, coef + slice * kCoefStride, ntiles, d, J, (side ? AK : AQ) + base, c, g);
   __syncthreads();
   if ((int)threadIdx.x <= L) {
     const int i = threadIdx.x;
@@ -3009,9 +2987,12 @@ wersa_status fast_forward_t(const wersa_desc &c, const bf16_t *q, const bf16_t *
     WERSA_STAGE("wersa_qbar", st,
                 qbar_partial_kernel<DH><<<dim3(p.chunksQ, slices), 256, 0, st>>>(k, tv, c.n, p.rowsQ, w.tileK,
                                                                                  p.chunksQ, none, nullptr));
-    WERSA_STAGE("wersa_coarse_addend", st,
-                coarse_addend_kernel<<<dim3(slices, 2, DH / kCoarseCols), 1024, 0, st>>>(w.tileQ, w.tileK, w.coef, p.chunksQ, DH, c.L, w.pyr,
-                                                                      w.addQ, w.addK));
+    auto go = [&](auto kern, size_t lds) {
+      WERSA_STAGE("wersa_coarse_addend", st, kern<<<dim3(slices, 2, DH / kCoarseCols), 1024, lds, st>>>(w.tileQ, w.tileK, w.coef, p.chunksQ, DH, c.L,
+                                                                                                       w.pyr, w.addQ, w.addK));
+    };
+    if (const size_t lds = pyramid_in_lds(&coarse_addend_kernel<true>, p.chunksQ, 1)) go(&coarse_addend_kernel<true>, lds);
+    else go(&coarse_addend_kernel<false>, 0);
   }
   if (DH != 64) {   // head dimension 64 runs stage A inside the kernels that consume X_F
     WERSA_STAGE("wersa_haar_stage", st,
@@ -3068,11 +3049,14 @@ wersa_status fast_backward_t(const wersa_desc &c, const bf16_t *q, const bf16_t 
   const bool q_first = one_bits_buffer(c);
   if ((q_first && query_side() != hipSuccess) || key_side() != hipSuccess || (!q_first && query_side() != hipSuccess)) return WERSA_ERR_LAUNCH;
   const bool deep = c.L > kTileL;
-  if (deep)   // levels above 6: addends of dQ and dK and the bands' extra row, from the tile sums
-    WERSA_STAGE("wersa_coarse_bwd", st,
-                coarse_bwd_kernel<<<dim3(slices, 2, DH / kCoarseCols), 1024, 0, st>>>(w.gsumQ, w.gsumK, w.tileQ, w.tileK, w.coef,
-                                                                   (c.n + 63) / 64, DH, c.L, w.pyr, w.gaddQ, w.gaddK,
-                                                                   w.partQ, w.partK, p.rowsWgs));
+  if (deep) {   // levels above 6: addends of dQ and dK and the bands' extra row, from the tile sums
+    auto go = [&](auto kern, size_t lds) {
+      WERSA_STAGE("wersa_coarse_bwd", st, kern<<<dim3(slices, 2, DH / kCoarseCols), 1024, lds, st>>>(
+          w.gsumQ, w.gsumK, w.tileQ, w.tileK, w.coef, (c.n + 63) / 64, DH, c.L, w.pyr, w.gaddQ, w.gaddK, w.partQ, w.partK, p.rowsWgs));
+    };
+    if (const size_t lds = pyramid_in_lds(&coarse_bwd_kernel<true>, (c.n + 63) / 64, 2)) go(&coarse_bwd_kernel<true>, lds);
+    else go(&coarse_bwd_kernel<false>, 0);
+  }
   WERSA_STAGE("gate_bwd_slice_kernel", st,
               gate_bwd_slice_kernel<<<slices, kGateBwdThreads, 0, st>>>(w.partQ, w.partK, deep ? p.rowsWgs + DH / kCoarseCols : p.rowsWgs, c.L,
                                                            c.d, c.H, s, gate_w, scale_w, w.dF, w.dlogit, w.dqbar,

@@ -1501,62 +1501,46 @@ __global__ __launch_bounds__(256) void filter_bwd_kernel(const float *gq, const 
 // the addends of dQ, dK from the tile sums of dQ_F, dK_F, and the band inner products of the levels
 // above 6 into d / 16 extra rows of the partials.  Grid (slices, 2, d / 16) of 1024 threads.
 // ------------------------------------------------------------------------------------
+// IN_LDS: the pyramids are (pyramid_in_lds bytes of dynamic LDS).
+template <bool IN_LDS>
 __global__ __launch_bounds__(1024) void deep_addend_kernel(const float *Tq, const float *Tk, const float *coef, int ntiles, int d, int L,
                                                           float *pyr, float *Aq, float *Ak) {
-  const int slice = blockIdx.x, side = blockIdx.y;
-  const int c = kCoarseCols * blockIdx.z + (threadIdx.x & (kCoarseCols - 1)), g = threadIdx.x / kCoarseCols;
+  extern __shared__ float lds_pyr[];
+  const int slice = blockIdx.x, side = blockIdx.y, cl = threadIdx.x & (kCoarseCols - 1);
+  const int c = kCoarseCols * blockIdx.z + cl, g = threadIdx.x / kCoarseCols;
   const int64_t base = (int64_t)slice * ntiles * d;
-  float *P = pyr + ((int64_t)slice * 2 + side) * pyramid_floats(ntiles, d);
-  build_tile_pyramid((side ? Tk : Tq) + base, ntiles, d, L - 6, P, c, g);
-  tile_addend(P, coef + slice * kCoefStride, ntiles, d, L - 6, (side ? Ak : Aq) + base, c, g);
+  const float *T = (side ? Tk : Tq) + base, *cf = coef + slice * kCoefStride;
+  float *A = (side ? Ak : Aq) + base, *P = pyr + ((int64_t)slice * 2 + side) * pyramid_floats(ntiles, d);
+  if constexpr (IN_LDS) coarse_addends(T, cf, ntiles, d, L - 6, first_level((lds_float *)lds_pyr, ntiles, kCoarseCols, cl), A, c, g);
+  else coarse_addends(T, cf, ntiles, d, L - 6, first_level(P, ntiles, d, c), A, c, g);
 }
+template <bool IN_LDS>
 __global__ __launch_bounds__(1024) void deep_bwd_kernel(const float *TgQ, const float *TgK, const float *TxQ, const float *TxK,
                                                        const float *coef, int ntiles, int d, int L, float *pyr, float *AQ,
                                                        float *AK, float *partQ, float *partK, int row) {
-  const int slice = blockIdx.x, side = blockIdx.y, J = L - 6;
-  const int c = kCoarseCols * blockIdx.z + (threadIdx.x & (kCoarseCols - 1)), g = threadIdx.x / kCoarseCols;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  extern __shared__ float lds_pyr[];
+  const int slice = blockIdx.x, side = blockIdx.y, J = L - 6, cl = threadIdx.x & (kCoarseCols - 1);
+  const int c = kCoarseCols * blockIdx.z + cl, g = threadIdx.x / kCoarseCols;
   const int64_t base = (int64_t)slice * ntiles * d;
   float *Pg = pyr + (((int64_t)slice * 2 + side) * 2) * pyramid_floats(ntiles, d);
   float *Px = Pg + pyramid_floats(ntiles, d);
-  const float *Tg = (side ? TgK : TgQ) + base, *Tx = (side ? TxK : TxQ) + base;
-  build_tile_pyramid(Tg, ntiles, d, J, Pg, c, g);
-  build_tile_pyramid(Tx, ntiles, d, J, Px, c, g);
-  tile_addend(Pg, coef + slice * kCoefStride, ntiles, d, J, (side ? AK : AQ) + base, c, g);
-  __shared__ float red[2][16];
+  const float *tg = (side ? TgK : TgQ) + base, *tx = (side ? TxK : TxQ) + base, *cf = coef + slice * kCoefStride;
+  float *A = (side ? AK : AQ) + base;
+  __shared__ float detail[kMaxBands][16], sum[kMaxBands][16];
+  if constexpr (IN_LDS) {
+    lds_float *p = (lds_float *)lds_pyr;
+    coarse_bwd<true>(tg, tx, cf, ntiles, d, J, first_level(p, ntiles, kCoarseCols, cl), first_level(p + (ntiles + 32) * kCoarseCols, ntiles, kCoarseCols, cl), A,
+               c, g, detail, sum);
+  } else {
+    coarse_bwd<true>(tg, tx, cf, ntiles, d, J, first_level(Pg, ntiles, d, c), first_level(Px, ntiles, d, c), A, c, g, detail, sum);
+  }
   float *part = (side ? partK : partQ) + ((int64_t)slice * (row + gridDim.z) + row + blockIdx.z) * (L + 1);
   if ((int)threadIdx.x < 6) part[threadIdx.x] = 0.f;
-  const float *pg = Tg, *px = Tx, *lg = Pg, *lx = Px;
-  int nprev = ntiles;
-  for (int j = 1; j <= J; ++j) {
-    const int nb = (nprev + 1) / 2;
-    float acc = 0.f, top = 0.f;
-#pragma unroll 4
-    for (int b = g; b < nb; b += kCoarseGroups) {
-      const bool two = 2 * b + 1 < nprev;
-      const float dg = pg[2 * b * d + c] - (two ? pg[(2 * b + 1) * d + c] : 0.f);
-      const float dx = px[2 * b * d + c] - (two ? px[(2 * b + 1) * d + c] : 0.f);
-      acc = fmaf(dg, dx, acc);
-      top = fmaf(lg[b * d + c], lx[b * d + c], top);
-    }
-    acc = wave_sum(acc);
-    top = wave_sum(top);
-    if (lane == 0) {
-      red[0][wave] = acc;
-      red[1][wave] = top;
-    }
-    __syncthreads();
-    if (threadIdx.x < 2 && (threadIdx.x == 0 || j == J)) {
-      float tot = 0.f;
-      for (int i = 0; i < 16; ++i) tot += red[threadIdx.x][i];
-      part[threadIdx.x == 0 ? 5 + j : L] = tot / (float)(1 << (6 + j));
-    }
-    __syncthreads();
-    pg = lg;
-    px = lx;
-    lg += nb * d;
-    lx += nb * d;
-    nprev = nb;
+  if ((int)threadIdx.x >= 6 && (int)threadIdx.x <= L) {   // band 5 + j: the details of level 6 + j; band L: the approximation
+    const int j = min((int)threadIdx.x - 5, J);
+    float tot = 0.f;
+    for (int i = 0; i < 16; ++i) tot += (int)threadIdx.x == L ? sum[J][i] : detail[j][i];
+    part[threadIdx.x] = tot / (float)(1 << (6 + j));
   }
 }
 
@@ -1818,9 +1802,13 @@ wersa_status forward_t(const wersa_desc &c, const T *q, const T *k, const T *v, 
     WERSA_STAGE("gate_fwd_kernel", st, gate_fwd_kernel<<<slices, kGateFwdThreads, 0, st>>>(
         qpart, p.chunks, c.n, c.d, c.L, c.H, gate_w, gate_b, scale_w, gate.qbar, gate.s_out, gate.F_out, coef, pooled_gate ? 1 : 0, gate.ql, nullptr, 0,
         scalars, gate.al, 1));
-  if (deep)
-    WERSA_STAGE("split_deep", st, deep_addend_kernel<<<dim3(slices, 2, c.d / kCoarseCols), 1024, 0, st>>>(
-        qpart, kpart, coef, p.ntl, c.d, c.L, w.pyr, addQ, addK));
+  if (deep) {
+    auto go = [&](auto kern, size_t lds) {
+      WERSA_STAGE("split_deep", st, kern<<<dim3(slices, 2, c.d / kCoarseCols), 1024, lds, st>>>(qpart, kpart, coef, p.ntl, c.d, c.L, w.pyr, addQ, addK));
+    };
+    if (const size_t lds = pyramid_in_lds(&deep_addend_kernel<true>, p.ntl, 1)) go(&deep_addend_kernel<true>, lds);
+    else go(&deep_addend_kernel<false>, 0);
+  }
   auto pack = [&](auto kern) {
     WERSA_STAGE("split_prep_fwd", st, kern<<<dim3(p.groups, slices, 3), 256, 0, st>>>(q, k, v, tv, p.s, vec, c.L, coef, addQ, addK, XQ, XK, w.VC, gate));
   };
@@ -1878,9 +1866,14 @@ wersa_status backward_t(const wersa_desc &c, const T *q, const T *k, const T *v,
   const int prow = p.groups + (deep ? c.d / kCoarseCols : 0);
   WERSA_STAGE("split_dots", st, dots_kernel<T, DH><<<dim3(p.groups, slices, 2), 256, 0, st>>>(
       q, k, tv, w.gq, w.gk, p.s, c.L, prow, w.partQ, w.partK, w.tgq, w.tgk));
-  if (deep)
-    WERSA_STAGE("split_deep", st, deep_bwd_kernel<<<dim3(slices, 2, c.d / kCoarseCols), 1024, 0, st>>>(
-        w.tgq, w.tgk, saved + sv.tileQ, saved + sv.tileK, coef, p.ntl, c.d, c.L, w.pyr, w.aq, w.ak, w.partQ, w.partK, p.groups));
+  if (deep) {
+    auto go = [&](auto kern, size_t lds) {
+      WERSA_STAGE("split_deep", st, kern<<<dim3(slices, 2, c.d / kCoarseCols), 1024, lds, st>>>(
+          w.tgq, w.tgk, saved + sv.tileQ, saved + sv.tileK, coef, p.ntl, c.d, c.L, w.pyr, w.aq, w.ak, w.partQ, w.partK, p.groups));
+    };
+    if (const size_t lds = pyramid_in_lds(&deep_bwd_kernel<true>, p.ntl, 2)) go(&deep_bwd_kernel<true>, lds);
+    else go(&deep_bwd_kernel<false>, 0);
+  }
   WERSA_STAGE("gate_bwd_slice_kernel", st, gate_bwd_slice_kernel<<<slices, kGateBwdThreads, 0, st>>>(
       w.partQ, w.partK, prow, c.L, c.d, c.H, saved + sv.s, gate_w, scale_w, w.dF, w.dlogit, w.dqbar,
       (c.flags & WERSA_FLAG_POOLED_GATE) ? 1 : 0));
