@@ -437,10 +437,10 @@ __global__ void splitk_reduce_kernel(const float *part, int splits, int64_t coun
   *reinterpret_cast<float4 *>(out + e) = acc;
 }
 
-// out[i] = w[i]^T for up to four hidden x hidden matrices (blockIdx.z), one 64 x 64 tile per workgroup; w's base may be any.
+// out[i] = w[i]^T for up to three hidden x hidden matrices (blockIdx.z), one 64 x 64 tile per workgroup; w's base may be any.
 struct TransposeJob {
-  const bf16_t *w[4];
-  bf16_t *out[4];
+  const bf16_t *w[kMaxSrc];
+  bf16_t *out[kMaxSrc];
 };
 __global__ __launch_bounds__(256) void transpose_kernel(TransposeJob job, int hidden) {
   constexpr int LS = 64 + 2;   // (rows 33 words apart: a column's values are in different banks)
@@ -505,6 +505,7 @@ hipError_t launch_gemm(const char *name, const GemmJob &job, int ld, int M, int 
 
 constexpr int kMinChunk = 256;   // tokens
 
+size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 struct BlockPlan {
   int64_t tokens, hidden, act;   // act = tokens * hidden elements
   int splits, k_chunk;           // split of the token axis for the weight gradients
@@ -532,22 +533,22 @@ BlockPlan block_plan(const wersa_desc &c) {
   // Three in one launch while their partials stay below 512 MiB (hidden 1024: 402 MB).  At hidden 2048 one product fills the chip
   // four times over and three launches with a third of the partials (805 -> 268 MB) take the same time (856 us each, 131072 tokens).
   p.wgrads = (int64_t)kMaxSrc * p.splits * p.hidden * p.hidden * 4 <= (int64_t)512 << 20 ? 3 : 1;
-  // With a transposed copy of the weight the second operand's requests are whole lines (see gemm_bf16_kernel): dA 964 -> 828 us, dX 859 -> 831 per
-  // product at 131072 tokens, hidden 2048; the copies take 12 us.  us per training step without and with them: hidden 512, 16384 tokens 369, 371,
-  // 32768 523, 521, 131072 1588, 1571; 1024, 16384 799, 810, 32768 1285, 1271, 131072 4064, 4002; 2048, 8192 1320, 1322, 16384 2115, 2098, 32768
-  // 3721, 3672, 131072 13196, 12952.
-  p.transpose = p.tokens >= 32768;
   p.core = c;
   p.core.stride_n = p.hidden;
   p.core.stride_h = c.d;
   p.core.stride_b = (int64_t)c.n * p.hidden;
+  // With a transposed copy of the weight the second operand's requests are whole lines (see gemm_bf16_kernel): dA 964 -> 828 us, dX 859 -> 831 per
+  // product at 131072 tokens, hidden 2048; the copies take 4 us each.  us per training step without and with them: hidden 512, 16384 tokens 369, 371,
+  // 32768 523, 521, 131072 1588, 1571; 1024, 16384 799, 810, 32768 1285, 1271, 131072 4064, 4002; 2048, 8192 1320, 1322, 16384 2115, 2098, 32768
+  // 3721, 3672, 131072 13196, 12952.
+  // The copies lie in the core's workspace, before and after its own use of it.
+  p.transpose = p.tokens >= 32768 && wersa_workspace_bytes(&p.core, 1) >= 3 * up256((size_t)p.hidden * p.hidden * 2);
   return p;
 }
 
 // Byte layouts. saved: Q' | K' | V' | A (bf16, (B, n, hidden)) | the core's saved buffer.
 struct BlockSaved { size_t qp, kp, vp, a, core, total; };
-struct BlockWs { size_t qsums, qmax, wt, dA, dQp, dKp, dVp, part, core, total; };
-size_t up256(size_t x) { return (x + 255) / 256 * 256; }
+struct BlockWs { size_t qsums, qmax, dA, dQp, dKp, dVp, part, core, total; };
 
 BlockSaved block_saved(const BlockPlan &p) {
   BlockSaved s{};
@@ -570,7 +571,6 @@ BlockWs block_ws(const BlockPlan &p, int bwd) {
     w.qmax = off;  off += up256((size_t)(p.tokens / 128) * (p.hidden / kPooledMaxCols) * 4);   // and the largest |Q'| per 64 columns
   } else {
     const size_t act = up256((size_t)p.act * 2);
-    w.wt = off;  off += p.transpose ? 4 * up256((size_t)p.hidden * p.hidden * 2) : 0;
     w.dA = off;  off += act;
     w.dQp = off; off += act;
     w.dKp = off; off += act;
@@ -735,17 +735,16 @@ wersa_status wersa_block_backward(const wersa_desc *desc, const void *x, const v
     return true;
   };
 
-  // Products with a weight's transpose.
-  const bf16_t *wt[4] = {(const bf16_t *)wq, (const bf16_t *)wk, (const bf16_t *)wv, (const bf16_t *)wo};
-  if (p.transpose) {
+  // Products with a weight's transpose: `count` weights, as they are or transposed into the core's workspace.
+  auto transposed = [&](int count, const void *const *w_as_stored, const bf16_t **out) {
     TransposeJob job{};
-    for (int i = 0; i < 4; ++i) {
-      job.w[i] = wt[i];
-      job.out[i] = (bf16_t *)(ws + w.wt + i * up256((size_t)wcount * 2));
-      wt[i] = job.out[i];
+    for (int i = 0; i < count; ++i) {
+      job.w[i] = (const bf16_t *)w_as_stored[i];
+      job.out[i] = (bf16_t *)(ws + w.core + i * up256((size_t)wcount * 2));
+      out[i] = p.transpose ? job.out[i] : job.w[i];
     }
-    WERSA_STAGE("wersa_transpose", st, transpose_kernel<<<dim3(hid / 64, hid / 64, 4), 256, 0, st>>>(job, hid));
-  }
+    if (p.transpose) WERSA_STAGE("wersa_transpose", st, transpose_kernel<<<dim3(hid / 64, hid / 64, count), 256, 0, st>>>(job, hid));
+  };
   auto times_transpose = [&](GemmJob &job) {
     return (p.transpose ? launch_gemm<false, true, false>("wersa_gemm_nn", job, hid, M, hid, hid, hid, 1, st)
                         : launch_gemm<false, false, false>("wersa_gemm_nt", job, hid, M, hid, hid, hid, 1, st)) == hipSuccess;
@@ -753,7 +752,8 @@ wersa_status wersa_block_backward(const wersa_desc *desc, const void *x, const v
   {  // dA = dY W_out^T
     GemmJob job{};
     job.a[0] = (const bf16_t *)dy;
-    job.b[0] = wt[3];
+    const void *const stored[1] = {wo};
+    transposed(1, stored, job.b);
     job.c[0] = dA;
     job.count = job.batch = 1;
     if (!times_transpose(job)) return WERSA_ERR_LAUNCH;
@@ -770,9 +770,11 @@ wersa_status wersa_block_backward(const wersa_desc *desc, const void *x, const v
   if (cs != WERSA_OK) return cs;
   {  // dX = dQ' W^Q^T + dK' W^K^T + dV' W^V^T
     GemmJob job{};
-    job.a[0] = dQp; job.b[0] = wt[0];
-    job.a[1] = dKp; job.b[1] = wt[1];
-    job.a[2] = dVp; job.b[2] = wt[2];
+    job.a[0] = dQp;
+    job.a[1] = dKp;
+    job.a[2] = dVp;
+    const void *const stored[3] = {wq, wk, wv};
+    transposed(3, stored, job.b);
     job.c[0] = dx;
     job.count = 3;
     job.batch = 1;
