@@ -835,10 +835,33 @@ __global__ __launch_bounds__(512, 2) void contract_kernel(const bf16_t *X, const
 // ------------------------------------------------------------------------------------
 // Sum of the values at p, p + step, ...: eight at a time (in flight together) as a tree, eight of these in a chain, and a
 // chain of those.  In one chain, the hundreds of shares of a long sequence would lose more than the products do.
-template <typename V>
+// SHORT: up to 32 shares in few workgroups, sixteen in flight together.
+template <bool SHORT, typename V>
 __device__ __forceinline__ V sum_shares(const float *p, int64_t step, int shares) {
   V acc = (V)(0.f), part = (V)(0.f);
   int sh = 0;
+  if constexpr (SHORT) {
+#pragma unroll 1
+    for (; sh < shares; sh += 16) {
+      V x[16];
+#pragma unroll
+      for (int k = 0; k < 16; k += 8)
+        if (sh + k < shares)
+#pragma unroll
+          for (int i = k; i < k + 8; ++i) x[i] = *reinterpret_cast<const V *>(p + min(sh + i, shares - 1) * step);
+#pragma unroll
+      for (int k = 0; k < 16; k += 8) {
+        if (sh + k + 8 <= shares) {
+          part += ((x[k] + x[k + 1]) + (x[k + 2] + x[k + 3])) + ((x[k + 4] + x[k + 5]) + (x[k + 6] + x[k + 7]));
+        } else {
+#pragma unroll
+          for (int i = k; i < k + 7; ++i)
+            if (sh + i < shares) part += x[i];
+        }
+      }
+    }
+    return part;
+  }
   for (; sh + 8 <= shares; sh += 8) {
     V x[8];
 #pragma unroll
@@ -852,7 +875,7 @@ __device__ __forceinline__ V sum_shares(const float *p, int64_t step, int shares
   for (; sh < shares; ++sh) part += *reinterpret_cast<const V *>(p + sh * step);
   return acc + part;
 }
-template <int DH>
+template <int DH, bool SHORT>
 __global__ __launch_bounds__(256) void reduce_kernel(const float *part, const float *zpart, int shares, int zcols,
                                                     const float *scalars, Dims s, float *S, float *z, float *zpad,
                                                     bf16_t *SA, bf16_t *SB, bf16_t *SAin) {
@@ -876,12 +899,12 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float *part, const fl
 #pragma unroll
     for (int u = 0; u < 32 * PW / 1024; ++u) {
       const int e = (tid + 256 * u) * 4;
-      const f32x4 acc = sum_shares<f32x4>(p0 + e, step, shares);
+      const f32x4 acc = sum_shares<SHORT, f32x4>(p0 + e, step, shares);
 #pragma unroll
       for (int i = 0; i < 4; ++i) tile[(e / PW) * LS + e % PW + i] = acc[i] * c;
     }
     if (DH > 16 && tid < 32)
-      zt[tid] = sum_shares<float>(zpart + ((int64_t)slice * shares * s.mt + ft) * 32 + tid, (int64_t)s.mt * 32, shares) * c;
+      zt[tid] = sum_shares<SHORT, float>(zpart + ((int64_t)slice * shares * s.mt + ft) * 32 + tid, (int64_t)s.mt * 32, shares) * c;
     __syncthreads();
     if (DH == 16 && tid < 32) {
       float acc = 0.f;
@@ -1591,7 +1614,7 @@ struct Plan {
   int groups;                         // 4096-element workgroups per slice
   int ntl;                            // 64-row tiles per slice
 };
-Plan plan_of(const wersa_desc &c) {
+Plan plan_least(const wersa_desc &c, int least) {   // least: token tiles of a workgroup of the contraction at least
   Plan p{};
   const int slices = c.B * c.H;
   p.DH = dh_of(c.d);
@@ -1619,7 +1642,7 @@ Plan plan_of(const wersa_desc &c) {
   p.TW = p.TW < sg ? p.TW : sg;
   const int base = slices * (p.s.mt / p.FW);
   int splits = (kFillBlocks + base - 1) / base;
-  const int most = (p.s.nt + 7) / 8;               // at least eight token tiles each
+  const int most = (p.s.nt + least - 1) / least;
   splits = splits > most ? most : splits;
   p.tiles_per_split = (p.s.nt + splits - 1) / splits;
   p.splits = (p.s.nt + p.tiles_per_split - 1) / p.tiles_per_split;
@@ -1693,6 +1716,24 @@ Ws ws_of(const wersa_desc &c, const Plan &p, int bwd, bool keep, float *base) {
   return w;
 }
 
+// Eight token tiles for a workgroup of the contraction at least, four or two where compute units are left without one: the chain of tiles is
+// the kernel's time then, and up to 24 shares the kernel that adds them does not lose it again (SHORT in sum_shares).
+// us of the contraction and the sum, at eight, four and two tiles: float32, one slice of 1024 tokens, d 64, m 64 8.3 5.1, 6.0 5.5, 4.5 8.2 (32 shares);
+// 4 of 1000, d 128, m 256 34.9 8.8, 20.9 8.3, 14.1 9.0; 16 of 1000, d 64, m 256 19.3 6.6, 13.2 6.9, 11.5 7.6; 2 of 1500, d 32, m 512 12.0 4.5, 8.0 4.8,
+// 6.0 6.2; 8 of 1500, d 64, m 128 12.3 5.7, 9.3 7.9, 9.5 7.8.  What fits wersa_forward_static's scratch, with Q_F and K_F or without, still does.
+Plan plan_of(const wersa_desc &c) {
+  Plan p = plan_least(c, 8);
+  auto fits = [&](const Plan &q, bool keep) { return (size_t)ws_of(c, q, 0, keep, nullptr).total * sizeof(float) <= kStaticScratchBytes; };
+  for (int least = 4; least >= 2; least /= 2) {
+    if ((int64_t)c.B * c.H * (p.s.mt / p.FW) * p.splits >= 256) break;
+    const Plan q = plan_least(c, least);
+    if (q.shares > 24) break;
+    if (!fits(q, false) && (fits(p, false) || (fits(p, true) && !fits(q, true)))) break;
+    p = q;
+  }
+  return p;
+}
+
 // Where Q_F and K_F, packed (6 bytes per element each), live between the forward and the backward.  In `saved` where the rest
 // of the forward's workspace fits wersa_forward_static's scratch: the backward has less to do where latency counts (64 slices
 // of 1000 tokens, d 64, m 64, float32: 110 us, 122 us where it packs them again), and what the static call takes does not
@@ -1749,6 +1790,13 @@ void row_launch(const Plan &p, int slices, F go) {
   if constexpr (DH < 128)
     if (nw == 2) return go(integral_constant<int, 1>(), integral_constant<int, 2>(), grid);
   go(integral_constant<int, 1>(), Full(), grid);
+}
+
+// Calls go(kernel): with more workgroups the registers of sixteen loads cost more than the chain (128 slices of 32 workgroups, 2 shares: 21.8 -> 25.2 us).
+template <int DH, typename F>
+void reduce_launch(const Plan &p, int slices, F go) {
+  if (p.shares > 8 && p.shares <= 32 && slices * p.s.mt <= 256) go(&reduce_kernel<DH, true>);
+  else go(&reduce_kernel<DH, false>);
 }
 
 template <typename T, int DH, int PT, int MODE>
@@ -1816,8 +1864,10 @@ wersa_status forward_t(const wersa_desc &c, const T *q, const T *k, const T *v, 
   else pack(&prep_fwd_kernel<T, DH, PT, false>);
   WERSA_STAGE("split_contract", st, contract_kernel<DH, PT, false><<<dim3(p.splits, p.s.mt / p.FW, slices), 512, 0, st>>>(
       XK, w.VC, nullptr, OAk, p.s, p.FW, p.TW, p.tiles_per_split, w.part, w.zpart, nullptr));
-  WERSA_STAGE("split_reduce", st, reduce_kernel<DH><<<dim3(p.s.mt, slices), 256, 0, st>>>(
-      w.part, w.zpart, p.shares, 1, scalars, p.s, saved + sv.S, saved + sv.z, w.zpad, nullptr, w.SB, nullptr));
+  reduce_launch<DH>(p, slices, [&](auto kern) {
+    WERSA_STAGE("split_reduce", st, kern<<<dim3(p.s.mt, slices), 256, 0, st>>>(
+        w.part, w.zpart, p.shares, 1, scalars, p.s, saved + sv.S, saved + sv.z, w.zpad, nullptr, w.SB, nullptr));
+  });
   if (ln) {
     launch_apply<T, DH, PT, 1>(c, p, XQ, OA, w.SB, w.zpad, scalars, out, tv, w.Nbuf, nullptr, nullptr, st);
     WERSA_STAGE("split_ln", st, ln_out_kernel<T><<<dim3((c.n + 3) / 4, slices), 256, 0, st>>>(w.Nbuf, out, tv, c.n, c.d, c.eps, saved + sv.D));
@@ -1851,9 +1901,11 @@ wersa_status backward_t(const wersa_desc &c, const T *q, const T *k, const T *v,
       w.XQ, w.XS, w.XK, w.ddw, w.rowscale, w.dpart));
   WERSA_STAGE("split_contract", st, contract_kernel<DH, PT, true><<<dim3(p.splits, p.s.mt / p.FW, slices), 512, 0, st>>>(
       XQ, w.NC, w.ddw, OA, p.s, p.FW, p.TW, p.tiles_per_split, w.part, w.zpart, w.bitsQ));
-  WERSA_STAGE("split_reduce", st, reduce_kernel<DH><<<dim3(p.s.mt, slices, 2), 256, 0, st>>>(
-      w.part, w.zpart, p.shares, PT == 1 ? 3 : 1, scalars, p.s, const_cast<float *>(saved + sv.S), const_cast<float *>(saved + sv.z),
-      nullptr, w.dSA, w.dSB, w.SA));
+  reduce_launch<DH>(p, slices, [&](auto kern) {
+    WERSA_STAGE("split_reduce", st, kern<<<dim3(p.s.mt, slices, 2), 256, 0, st>>>(
+        w.part, w.zpart, p.shares, PT == 1 ? 3 : 1, scalars, p.s, const_cast<float *>(saved + sv.S), const_cast<float *>(saved + sv.z),
+        nullptr, w.dSA, w.dSB, w.SA));
+  });
   const GradRows<T> rowsK{v, nullptr, nullptr, vec}, rowsQ{dout, ln ? out : nullptr, PT == 1 ? nullptr : D, vec};
   if constexpr (DH == 128) {   // (dV on its own: no registers left for its accumulators; first, dK_F may go in the place of K_F)
     launch_apply<T, DH, PT, 2>(c, p, XK, OAk, w.dSB, nullptr, scalars, dv, tv, nullptr, nullptr, w.bitsK, st);
