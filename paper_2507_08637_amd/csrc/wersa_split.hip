@@ -15,7 +15,7 @@
 //
 // Measured against the generic kernels, which write every n x m feature matrix to memory: float32 training step, 128
 // slices of 4000 tokens, d 32, m 1024: 13990 -> 2350 us; bf16 training step, 8 slices of 131072 tokens, d 16, m 1024:
-// 26290 -> 2100 us; float32 inference, one slice of 1024 tokens, d 64, m 64: 118 -> 34 us.
+// 26290 -> 2100 us; float32 inference, one slice of 1024 tokens, d 64, m 64: 118 -> 30 us.
 //
 // Layout: every operand is kept in the order in which a wave loads it ("operand tile": 32 vectors x 16
 // k-values of bf16; lane (l32, h) holds vector l32, k = 8 h .. 8 h + 7, 16 bytes; 1 KiB).  Where k runs
@@ -322,6 +322,38 @@ struct Dims {
 // Column sums of Q (and, for L > 6, of K) per chunk of rows; workgroups past `chunks` of slice 0 carry the
 // per-call constants and pack Omega.  Grid (chunks + extra, slices, tensors).
 // ------------------------------------------------------------------------------------
+// What no kernel writes of `saved` (the ends of sections that are rounded up, the feature tile past the last one) is cleared by one more
+// workgroup of the first launch, so that two calls on the same inputs leave the same bytes, whatever was in the memory before.
+struct Gaps {
+  float *at[14];
+  int len[14];
+};
+Gaps gaps_of(const wersa_desc &c, const SavedLayout &sv, float *saved, int64_t tileA, int64_t tileB, const SplitSizes &z) {
+  Gaps g{};
+  int i = 0;
+  const int64_t sl = (int64_t)c.B * c.H;
+  auto end = [&](int64_t off, int64_t used) {   // from the last value to the next multiple of 64
+    g.at[i] = saved + off + used;
+    g.len[i++] = (int)((64 - used % 64) % 64);
+  };
+  end(sv.S, sl * c.m * c.d);
+  end(sv.z, sl * c.m);
+  end(sv.qbar, sl * c.d);
+  end(sv.s, sl * (c.L + 1));
+  end(sv.F, sl * (c.L + 1));
+  end(sv.D, sl * c.n);
+  end(sv.scalars, 4);
+  if (c.L > kTileL)
+    for (const int64_t off : {sv.tileQ, sv.tileK, sv.addQ, sv.addK}) end(off, sl * ((c.n + 63) / 64) * c.d);
+  g.at[i] = saved + sv.coef;   // (all of it: the gate, which comes later, writes as many levels as there are)
+  g.len[i++] = (int)((sl * kCoefStride + 63) / 64 * 64);
+  g.at[i] = saved + sv.OA + z.OA - tileA;
+  g.len[i++] = (int)((64 - z.OA % 64) % 64 + tileA);
+  g.at[i] = saved + sv.OB + z.OB - tileB;
+  g.len[i++] = (int)((64 - z.OB % 64) % 64 + tileB);
+  return g;
+}
+
 template <typename T>
 struct OmegaPack {
   const T *omega;      // [matrices][d][m]
@@ -329,10 +361,17 @@ struct OmegaPack {
   float bw_floor;
   float *scalars;
   bf16_t *OA, *OB;     // features as vectors (k = columns), columns as vectors (k = features)
-  int matrices, KS, CT, PT, blocks;
+  int matrices, KS, CT, PT, blocks;   // (the last one clears)
+  Gaps gaps;
 };
 template <typename T>
 __device__ void omega_pack_body(const OmegaPack<T> &o, const Dims &s, int block) {
+  if (block == o.blocks - 1) {
+#pragma unroll
+    for (int g = 0; g < 14; ++g)
+      for (int e = threadIdx.x; e < o.gaps.len[g]; e += 256) o.gaps.at[g][e] = 0.f;
+    return;
+  }
   if (block == 0 && threadIdx.x == 0) {
     const float sg = *o.sigma, se = fmaxf(sg, o.bw_floor);
     o.scalars[0] = 1.0f / (se * sqrtf((float)s.m));
@@ -1837,7 +1876,8 @@ wersa_status forward_t(const wersa_desc &c, const T *q, const T *k, const T *v, 
   float *qpart = deep ? saved + sv.tileQ : w.qpart, *kpart = deep ? saved + sv.tileK : nullptr;
   const int vec = rows_aligned(c, {q, k, v});
   const int pieces = p.matrices * p.s.mt * 64 * (p.KS + 2 * p.CT);
-  const OmegaPack<T> om{omega, sigma, c.bw_floor, scalars, OA, OB, p.matrices, p.KS, p.CT, PT, (pieces + 255) / 256};
+  const OmegaPack<T> om{omega, sigma, c.bw_floor, scalars, OA, OB, p.matrices, p.KS, p.CT, PT, (pieces + 255) / 256 + 1,
+                        gaps_of(c, sv, saved, tile_floats(p.KS * PT), tile_floats(2 * p.CT * PT), split_sizes(c))};
   WERSA_STAGE("split_pool", st, pool_kernel<T><<<dim3(p.chunks + om.blocks, slices, deep ? 2 : 1), 256, 0, st>>>(
       q, k, tv, p.s, vec, p.rows_per_chunk, p.chunks, qpart, kpart, om));
   const bool pooled_gate = (c.flags & WERSA_FLAG_POOLED_GATE) != 0;
