@@ -81,8 +81,8 @@ def kernel_models(cfg):
     models["split_grad"] = ("mfma", "mfma_bf16", 3 * unit)       # projection, dPhi, dX_F
     models["split_grad_k"] = ("mfma", "mfma_bf16", 4 * unit)     # the same and dV
     # attention block (configuration 5): hidden x hidden projections over all tokens.  Average launch: each form
-    # has launches worth four products (NN: Q', K', V' in one, Y; NT: dA, dX as a sum of three; TN: dW^out and the weight
-    # gradients of Q, K, V, each a launch of its own at hidden 2048).
+    # has launches worth four products (NN: Q', K', V' in one, Y, and on transposed copies of the weights the next two; NT: dA, dX
+    # as a sum of three; TN: dW^out and the weight gradients of Q, K, V, each a launch of its own at hidden 2048).
     hidden, tokens = cfg["H"] * d, cfg["B"] * n
     gemm = 2.0 * tokens * hidden * hidden
     for form, products in (("nn", 2), ("nt", 2), ("tn", 1)):
