@@ -29,15 +29,15 @@ def _load_node():
         except ImportError as e:
             raise RuntimeError("the autograd extension _wersa_torch.so is missing or does not load: build it with "
                                "`python -m paper_2507_08637_amd.build` (there is no fallback path)") from e
-        node.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.wersa_forward, lib.wersa_backward)))
+        node.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.wersa_forward, lib.wersa_backward, lib.wersa_workspace_bytes,
+                                                                    lib.wersa_saved_bytes, lib.wersa_selected_path)))
         _node = node
     return _node
 
 
 def wersa_attention(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps=1e-6, bw_floor=1e-6):
     desc, saved_bytes, workspace = binding.checked_desc(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps, bw_floor, 0)
-    return (_node or _load_node()).attention(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, bytes(desc), saved_bytes, workspace,
-                                             binding.wersa_workspace_bytes(desc, 1))
+    return (_node or _load_node()).attention(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, bytes(desc), saved_bytes, workspace)
 
 
 class _WersaBlock(torch.autograd.Function):

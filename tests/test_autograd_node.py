@@ -1,0 +1,127 @@
+"""The attention core's node of the autograd graph on the CPU, its library calls replaced by entry points that note what they are given:
+what a backward is told about tensors that come back from saved-tensor hooks in another layout."""
+import ctypes
+from contextlib import contextmanager
+
+import pytest
+import torch
+
+from paper_2507_08637_amd import autograd, binding
+
+B, H, N, D, L, M = 2, 4, 100, 64, 3, 128
+
+
+@contextmanager
+def recorded(forward_status=0, backward_status=0):
+    """Calls of wersa_forward and wersa_backward: (descriptor, addresses and sizes)."""
+    lib, calls = binding.load_library(), []
+
+    def entry(like, status):
+        proto = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.POINTER(binding.WersaDesc), *like.argtypes[1:])
+
+        def call(desc, *args):
+            calls.append((binding.WersaDesc.from_buffer_copy(desc.contents), args))
+            return status
+        return proto(call)
+
+    node = autograd._load_node()
+    fakes = entry(lib.wersa_forward, forward_status), entry(lib.wersa_backward, backward_status)
+    address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+    rest = [address(f) for f in (lib.wersa_workspace_bytes, lib.wersa_saved_bytes, lib.wersa_selected_path)]
+    node.bind(*(address(f) for f in fakes), *rest)
+    try:
+        yield calls
+    finally:
+        node.bind(address(lib.wersa_forward), address(lib.wersa_backward), *rest)
+
+
+def tensors(layout, dtype=torch.bfloat16):
+    if layout == "fused":      # slices of one projection's output
+        q, k, v = torch.randn(B, N, 3 * H * D).to(dtype).view(B, N, 3, H, D).permute(2, 0, 3, 1, 4)
+    elif layout == "odd":      # rows that are no multiple of eight elements apart: not for the MFMA path
+        q, k, v = (torch.randn(B, H, N, D + 1).to(dtype)[..., :D] for _ in range(3))
+    else:
+        q, k, v = (torch.randn(B, N, H, D).to(dtype).permute(0, 2, 1, 3) for _ in range(3))
+        if layout == "bhnd":
+            q, k, v = (x.contiguous() for x in (q, k, v))
+    params = [torch.randn(D, M).to(dtype), torch.ones(1), torch.randn(H, L + 1, D), torch.randn(H, L + 1), torch.ones(L + 1)]
+    return [x.detach().requires_grad_(True) for x in (q, k, v)], params
+
+
+def contiguous(x):
+    return x.detach().clone(memory_format=torch.contiguous_format)
+
+
+HOOKS = {"none": None, "contiguous": contiguous, "dense": lambda x: x.detach().clone(memory_format=torch.preserve_format)}
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("hook", HOOKS)
+@pytest.mark.parametrize("layout", ["bhnd", "bnhd", "fused", "odd"])
+def test_backward_describes_the_tensors_that_are_there(layout, hook, dtype):
+    qkv, params = tensors(layout, dtype)
+    unpacked = {}
+
+    def unpack(x):
+        unpacked[x.data_ptr()] = x
+        return x
+
+    with recorded() as calls:
+        if hook == "none":
+            out = autograd.wersa_attention(*qkv, *params, L)
+            for x in (*qkv, out):
+                unpacked[x.data_ptr()] = x
+        else:
+            with torch.autograd.graph.saved_tensors_hooks(HOOKS[hook], unpack):
+                out = autograd.wersa_attention(*qkv, *params, L)
+        assert out.stride() == qkv[0].stride()
+        for dout in (torch.ones_like(out), torch.ones(B, H, N, 1, dtype=dtype).expand(out.shape)):
+            grads = torch.autograd.grad(out, qkv, dout, retain_graph=True)
+            desc, args = calls[-1]
+            strides = (desc.stride_b, desc.stride_h, desc.stride_n)
+            lib = binding.load_library()
+            assert binding.wersa_path_name(desc) == binding.wersa_path_name(calls[0][0])   # the path that laid `saved` out
+            assert args[-2] >= lib.wersa_workspace_bytes(ctypes.byref(desc), 1)
+            assert [g.stride()[:3] for g in grads] == [strides] * 3 and [g.data_ptr() for g in grads] == list(args[11:14])
+            others = [desc.B, desc.H, desc.n, desc.d, desc.m, desc.L, desc.dtype, desc.flags]
+            assert others == [B, H, N, D, M, L, int(dtype == torch.bfloat16), 0]
+            if layout == "odd" and hook != "none" and dtype == torch.bfloat16:   # copied back to where the forward's path had them
+                assert strides == qkv[0].stride()[:3] and not set(args[:3]) & set(unpacked)
+            else:
+                assert [unpacked[a].stride()[:3] for a in (*args[:3], args[8])] == [strides] * 4
+
+
+@pytest.mark.parametrize("index,change", [
+    (1, lambda x: x.transpose(1, 2).contiguous().transpose(1, 2)), (2, lambda x: x.float()), (8, lambda x: x[:, :, 1:]),
+    (0, lambda x: x[..., ::2].repeat_interleave(2, -1).transpose(2, 3).contiguous().transpose(2, 3)), (3, lambda x: x.float()), (3, lambda x: x[:, 1:]),
+    (4, lambda x: x.double()), (5, lambda x: x.transpose(1, 2).contiguous().transpose(1, 2)), (6, lambda x: x[:1]), (7, lambda x: x.half()),
+    (9, lambda x: x[:-1])])
+def test_tensors_that_came_back_otherwise_are_refused(index, change):
+    """q, k, v, omega, sigma, gate_w, gate_b, scale_w, out, saved: one of them in another layout, size or type than the call can take."""
+    qkv, params = tensors("bhnd")
+    seen = []
+
+    def pack(x):
+        seen.append(x)
+        return len(seen) - 1, x.detach()
+
+    with recorded() as calls:
+        with torch.autograd.graph.saved_tensors_hooks(pack, lambda p: change(p[1]) if p[0] == index else p[1]):
+            out = autograd.wersa_attention(*qkv, *params, L)
+        assert len(seen) == 10
+        with pytest.raises(AssertionError):
+            torch.autograd.grad(out, qkv, torch.ones_like(out))
+    assert len(calls) == 1
+
+
+def test_status_of_either_call_is_raised():
+    qkv, params = tensors("bhnd")
+    with recorded(forward_status=3):
+        with pytest.raises(binding.WersaError) as e:
+            autograd.wersa_attention(*qkv, *params, L)
+        assert e.value.status == 3
+    with recorded(backward_status=1):
+        out = autograd.wersa_attention(*qkv, *params, L)
+        with pytest.raises(binding.WersaError) as e:
+            torch.autograd.grad(out, qkv, torch.ones_like(out))
+        assert e.value.status == 1

@@ -114,6 +114,33 @@ def test_saved_tensor_hooks_and_versions():
         torch.autograd.grad(out, [t["q"]], g)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("hook", ["on_cpu", "pinned", "contiguous"])
+@pytest.mark.parametrize("layout", ["bnhd", "fused", "odd"])
+def test_saved_tensors_that_come_back_in_another_layout(layout, hook, dtype):
+    """fused: slices of one projection's output; odd: rows d + 1 elements apart, which in bf16 is another path than dense rows take."""
+    import torch
+    t, g, L = problem("bnhd", dtype=dtype)
+    B, H, n, d = g.shape
+    if layout != "bnhd":
+        wide = torch.empty(B, n, 3 * H * d if layout == "fused" else 3 * H * (d + 1), dtype=g.dtype, device="cuda").view(B, n, 3, H, -1)
+        for i, x in enumerate("qkv"):
+            wide[:, :, i, :, :d] = t[x].permute(0, 2, 1, 3)
+            t[x] = wide[:, :, i, :, :d].permute(0, 2, 1, 3)
+    for x in NAMES:
+        t[x] = t[x].detach().requires_grad_(True)
+    ref, grads = direct(t, g, L)
+    if hook == "contiguous":
+        hooks = torch.autograd.graph.saved_tensors_hooks(lambda x: x.detach().clone(memory_format=torch.contiguous_format), lambda x: x)
+    else:
+        hooks = torch.autograd.graph.save_on_cpu(pin_memory=hook == "pinned")
+    with hooks:
+        out = node(t, L)
+    assert torch.equal(out, ref)
+    for _ in range(2):
+        same(torch.autograd.grad(out, [t[x] for x in NAMES], g, retain_graph=True), grads)
+
+
 def test_what_is_refused():
     import torch
     from paper_2507_08637_amd import binding
