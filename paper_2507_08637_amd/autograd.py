@@ -35,7 +35,32 @@ def _load_node():
     return _node
 
 
+class _WersaAttention(torch.autograd.Function):
+    """The same node in Python, for torch.jit.trace: the tracer records its call, and of the one in C++ only the allocation of the output."""
+
+    @staticmethod
+    def forward(ctx, q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps, bw_floor):
+        out, saved = binding.wersa_forward(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps=eps,
+                                           bw_floor=bw_floor)
+        ctx.save_for_backward(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, out, saved)
+        ctx.cfg = (L, eps, bw_floor)
+        return out
+
+    @staticmethod
+    def backward(ctx, dout):
+        q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, out, saved = ctx.saved_tensors
+        L, eps, bw_floor = ctx.cfg
+        if dout.stride() != q.stride():
+            dout = torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device).copy_(dout)
+        g = binding.wersa_backward(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, out, dout, saved, L,
+                                   eps=eps, bw_floor=bw_floor)
+        return (g["dq"], g["dk"], g["dv"], None, g["dsigma"], g["dgate_w"], g["dgate_b"], g["dscale_w"],
+                None, None, None)
+
+
 def wersa_attention(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps=1e-6, bw_floor=1e-6):
+    if torch.jit.is_tracing():
+        return _WersaAttention.apply(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps, bw_floor)
     desc, saved_bytes, workspace = binding.checked_desc(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps, bw_floor, 0)
     return (_node or _load_node()).attention(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, bytes(desc), saved_bytes, workspace)
 

@@ -125,3 +125,26 @@ def test_status_of_either_call_is_raised():
         with pytest.raises(binding.WersaError) as e:
             torch.autograd.grad(out, qkv, torch.ones_like(out))
         assert e.value.status == 1
+
+
+def test_traced_module_makes_the_call(monkeypatch):
+    """A traced module runs the attention on its own inputs; the library's calls are replaced by ones that compute something on the CPU."""
+    def forward(q, k, v, omega, sigma, gate_w, gate_b, scale_w, L, **kw):
+        return (q + 2 * k + 3 * v) * scale_w[L], torch.zeros(1)
+
+    def backward(q, k, v, omega, sigma, gate_w, gate_b, scale_w, out, dout, saved, L, **kw):
+        s = scale_w[L]
+        return dict(dq=dout * s, dk=2 * dout * s, dv=3 * dout * s, dsigma=torch.zeros(1), dgate_w=torch.zeros_like(gate_w),
+                    dgate_b=torch.zeros_like(gate_b), dscale_w=torch.zeros_like(scale_w))
+
+    monkeypatch.setattr(binding, "wersa_forward", forward)
+    monkeypatch.setattr(binding, "wersa_backward", backward)
+    qkv, params = tensors("bnhd", torch.float32)
+    with recorded():
+        traced = torch.jit.trace(lambda q, k, v, *p: autograd.wersa_attention(q, k, v, *p, L), (*qkv, *params), check_trace=False)
+    qkv, params = tensors("bnhd", torch.float32)
+    params[4] = torch.full((L + 1,), 0.5)
+    out = traced(*qkv, *params)
+    assert torch.equal(out, forward(*qkv, *params, L)[0])
+    grads = torch.autograd.grad(out, qkv, torch.ones_like(out))
+    assert [float(g.mean()) for g in grads] == [0.5, 1.0, 1.5]

@@ -141,6 +141,19 @@ def test_saved_tensors_that_come_back_in_another_layout(layout, hook, dtype):
         same(torch.autograd.grad(out, [t[x] for x in NAMES], g, retain_graph=True), grads)
 
 
+def test_traced_module():
+    import torch
+    t, g, L = problem("bnhd")
+    names = ("q", "k", "v", "omega", "sigma", "gate_w", "gate_b", "scale_w")
+    traced = torch.jit.trace(lambda *a: node(dict(zip(names, a)), L), [t[x] for x in names])
+    u = {x: (t[x] * 0.75).requires_grad_(x in NAMES) for x in names}
+    ref, grads = direct(u, g, L)
+    for _ in range(3):
+        out = traced(*(u[x] for x in names))
+        assert torch.equal(out, ref)
+        same(torch.autograd.grad(out, [u[x] for x in NAMES], g), grads)
+
+
 def test_what_is_refused():
     import torch
     from paper_2507_08637_amd import binding
