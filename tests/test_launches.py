@@ -1,0 +1,26 @@
+"""Which kernels a call launches, on a stand-in for the HIP runtime: the rules of the dispatch, and what becomes of a runtime call that fails."""
+import pytest
+
+from tests.launches import launches
+
+
+def desc(slices, n, d, m, L=4, bf16=True, **kw):
+    from paper_2507_08637_amd.binding import WersaDesc
+    return WersaDesc(1, slices, n, d, L, m, int(bf16), 1e-6, 1e-6, slices * n * d, n * d, d, kw.get("flags", 0))
+
+
+def kernels(what, *a, **kw):
+    (status, error, found), = launches([(what, desc(*a, **kw))])
+    assert (status, error) == (0, 0)
+    return found
+
+
+@pytest.mark.parametrize("what,lds,memory", [("forward", "deep_addend_kernel<1>", "deep_addend_kernel<0>"), ("backward", "deep_bwd_kernel<1>", "deep_bwd_kernel<0>")])
+def test_pyramids_go_to_memory_where_the_runtime_refuses_the_lds(what, lds, memory):
+    """The refused attribute is not an error of the call."""
+    call = [(what, desc(2, 60000, 32, 64, L=10, bf16=False))]
+    (good,), (bad,) = launches(call), launches(call, fail_attributes=True)
+    assert good[:2] == bad[:2] == (0, 0)
+    names = [k[0] for k in good[2]]
+    assert lds in names and memory not in names
+    assert [k[0] for k in bad[2]] == [memory if x == lds else x for x in names]
