@@ -2973,10 +2973,16 @@ wersa_status fast_forward_t(const wersa_desc &c, const bf16_t *q, const bf16_t *
     gate.amax_part = w.qamax;
     gate.al = AmaxLayout{(int64_t)c.H * p.chunksQ, p.chunksQ, 0, p.chunksQ};
   }
-  // Head dimension 64: the contraction's workgroups, two per compute unit and one round of them, form the gate themselves (us per call, forward: 64 slices of
-  // 4096 rows, m 128 60.6 -> 58.5, 4 of 2000, m 256 34.9 -> 32.5, 128 of 1000 67.0 -> 64.8, attention block with 8 heads of 2048 rows
-  // 51.8 -> 49.0).  Not the thousands of workgroups of head dimension 128's filter, nor a gate that pools heads or has many partial sums.
-  if (DH != 64 || deep || pooled_gate || gate.chunks > kGatePrologueChunks) {
+  // Head dimension 64: the contraction's workgroups form the gate themselves where they are one round, two per compute unit (us per call, forward: 64 slices
+  // of 4096 rows, m 128 60.6 -> 58.5, 4 of 2000, m 256 34.9 -> 32.5, 128 of 1000 67.0 -> 64.8, attention block with 8 heads of 2048 rows 51.8 -> 49.0).
+  // In further rounds each waits for it again: there where a slice's features are on one or two workgroups, and with them the launch of its own has many
+  // slices (gate apart and inside: 1000 slices of 256 rows, m 128 105.9, 93.6, m 256 154.2, 142.0; 512 of 1000, m 512 261.0, 254.9; 750 of 256, m 512
+  // 208.9, 205.0), up to where the two meet (1000 of 256, m 512 298.2, 299.4); not with more (128 of 64, m 2048 127.3, 128.8; 160 of 1000, m 2048
+  // 317.8, 323.4; 1000 of 256, m 1024 567.5, 585.2; 1000 of 64, m 4096 2104, 2186).
+  // Not the thousands of workgroups of head dimension 128's filter, nor a gate that pools heads or has many partial sums.
+  const int64_t contracting = (int64_t)p.chunksC * (c.m / p.MB) * slices;
+  const bool inside = contracting <= 512 || (c.m <= 2 * p.MB && contracting <= 1536);
+  if (DH != 64 || deep || pooled_gate || gate.chunks > kGatePrologueChunks || !inside) {
     WERSA_STAGE("gate_fwd_kernel", st,
                 gate_fwd_kernel<<<slices, kGateFwdThreads, 0, st>>>(gate.qpart, gate.chunks, c.n, c.d, c.L, c.H, gate_w, gate_b, scale_w,
                                                        qbar, s, F, w.coef, pooled_gate ? 1 : 0, gate.ql,

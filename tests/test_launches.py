@@ -24,3 +24,11 @@ def test_pyramids_go_to_memory_where_the_runtime_refuses_the_lds(what, lds, memo
     names = [k[0] for k in good[2]]
     assert lds in names and memory not in names
     assert [k[0] for k in bad[2]] == [memory if x == lds else x for x in names]
+
+
+@pytest.mark.parametrize("slices,n,m,apart", [
+    (8, 4096, 256, False), (512, 64, 256, False), (1023, 64, 128, False), (1023, 64, 256, False), (128, 64, 1024, False), (129, 64, 1024, True),
+    (768, 256, 512, False), (769, 256, 512, True), (128, 64, 2048, True), (64, 64, 4096, True), (32, 64, 4096, False), (170, 64, 384, False), (171, 64, 384, True)])
+def test_gate_has_a_launch_of_its_own_where_many_workgroups_would_form_it_again(slices, n, m, apart):
+    names = [k[0] for k in kernels("forward", slices, n, 64, m)]
+    assert ("gate_fwd_kernel" in names) == apart
