@@ -113,7 +113,7 @@ struct Attention : torch::autograd::Function<Attention> {
                 holds_floats(scale_w, d.L + 1),
             "expect omega and the parameters as they were saved");
     require(holds_floats(saved, (int64_t)saved_bytes_fn(&d) / 4), "the saved buffer holds less than wersa_saved_bytes asks for");
-    require(q.device() == dout.device() && out.device() == dout.device() && saved.device() == dout.device(), "saved tensors on another device");
+    for (const Tensor &x : t) require(x.device() == dout.device(), "saved tensors on another device");
     const Tensor dq = like_q(), dk = like_q(), dv = like_q(), dgw = at::empty_like(gate_w), dgb = at::empty_like(gate_b),
                  dsw = at::empty_like(scale_w), dsg = at::empty({1}, sigma.options());
     const Tensor ws = scratch((int64_t)workspace_bytes_fn(&d, 1), q);

@@ -114,6 +114,23 @@ def test_tensors_that_came_back_otherwise_are_refused(index, change):
     assert len(calls) == 1
 
 
+@pytest.mark.parametrize("index", range(10))
+def test_a_tensor_that_came_back_on_another_device_is_refused(index):
+    qkv, params = tensors("bhnd")
+    seen = []
+
+    def pack(x):
+        seen.append(x)
+        return len(seen) - 1, x.detach()
+
+    with recorded() as calls:
+        with torch.autograd.graph.saved_tensors_hooks(pack, lambda p: p[1].to("meta") if p[0] == index else p[1]):
+            out = autograd.wersa_attention(*qkv, *params, L)
+        with pytest.raises(AssertionError, match="device"):
+            torch.autograd.grad(out, qkv, torch.ones_like(out))
+    assert len(calls) == 1
+
+
 def test_status_of_either_call_is_raised():
     qkv, params = tensors("bhnd")
     with recorded(forward_status=3):
