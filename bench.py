@@ -78,8 +78,8 @@ def kernel_models(cfg):
     models["split_contract"] = ("mfma", "mfma_bf16", 2 * unit)   # projection + Phi^T Y
     models["split_apply"] = ("mfma", "mfma_bf16", 2 * unit)      # projection + Phi S
     models["split_apply_dv"] = ("mfma", "mfma_bf16", 2 * unit)   # projection + Phi dS
-    models["split_grad"] = ("mfma", "mfma_bf16", 3 * unit)       # projection, dPhi, dX_F
-    models["split_grad_k"] = ("mfma", "mfma_bf16", 4 * unit)     # the same and dV
+    models["split_grad"] = ("mfma", "mfma_bf16", 2 * unit)       # dPhi, dX_F (the ReLU's decisions come as bits)
+    models["split_grad_k"] = ("mfma", "mfma_bf16", 4 * unit)     # projection, dPhi, dX_F, dV
     # attention block (configuration 5): hidden x hidden projections over all tokens.  Average launch: each form
     # has launches worth four products (NN: Q', K', V' in one, Y, and on transposed copies of the weights the next two; NT: dA, dX
     # as a sum of three; TN: dW^out and the weight gradients of Q, K, V, each a launch of its own at hidden 2048).

@@ -29,3 +29,14 @@ def test_kernel_models_count_the_contractions():
     cfg3 = dict(cfg, n=cfg["n"] + 1)                                                       # partial last block:
     m3, unit3 = bench.kernel_models(cfg3), 2.0 * cfg3["n"] * cfg["d"] * cfg["m"] * 8
     assert m3["wersa_grad_q"][2] == m3["wersa_grad_k"][2] == m3["wersa_rows_bwd_v"][2] == 2 * unit3
+
+
+def test_split_path_models_count_the_contractions():
+    """float32 on the matrix cores: dX_F on the ReLU's decisions as bits performs two contractions, with the projection and dV four."""
+    sys.path.insert(0, ROOT)
+    import bench
+    from paper_2507_08637_amd import workloads
+    cfg = dict(workloads.CONFIGS[4], dtype="f32")
+    unit = 2.0 * cfg["n"] * cfg["d"] * cfg["m"] * cfg["B"] * cfg["H"]
+    m = bench.kernel_models(cfg)
+    assert [m["split_" + x][2] for x in ("contract", "apply", "apply_dv", "grad", "grad_k")] == [2 * unit, 2 * unit, 2 * unit, 2 * unit, 4 * unit]
