@@ -32,3 +32,17 @@ def test_pyramids_go_to_memory_where_the_runtime_refuses_the_lds(what, lds, memo
 def test_gate_has_a_launch_of_its_own_where_many_workgroups_would_form_it_again(slices, n, m, apart):
     names = [k[0] for k in kernels("forward", slices, n, 64, m)]
     assert ("gate_fwd_kernel" in names) == apart
+
+
+@pytest.mark.parametrize("slices,n,waves", [
+    (1, 1, 8), (1, 256, 8), (1, 257, 4), (8, 200, 8), (96, 256, 8), (96, 257, 4), (96, 512, 4), (192, 256, 8), (500, 64, 8), (500, 320, 8), (8, 65536, 8)])
+def test_rows_kernels_have_four_waves_where_that_gives_more_workgroups(slices, n, waves):
+    for what, names in (("forward", ["rows_kernel"]), ("backward", ["masked_rows_kernel"] * 2 + ["rows_kernel"])):
+        found = [(name.split("<")[0], threads) for name, _, threads, _ in kernels(what, slices, n, 64, 256) if "rows_kernel<" in name]
+        assert sorted(found) == [(name, 64 * waves) for name in names]
+
+
+@pytest.mark.parametrize("kw", [dict(L=7), dict(flags=8)])
+def test_rows_kernels_with_deep_levels_or_layernorm_have_eight_waves(kw):
+    for what in ("forward", "backward"):
+        assert {threads for name, _, threads, _ in kernels(what, 4, 1000, 64, 256, **kw) if "rows_kernel<" in name} == {512}
