@@ -2647,16 +2647,18 @@ FastPlan fast_plan(const wersa_desc &c) {
   const int wantL = kLnWgs / slices < 1 ? 1 : kLnWgs / slices, bpl = (blocks + wantL - 1) / wantL;
   p.rowsL = bpl * 64;
   p.chunksL = (blocks + bpl - 1) / bpl;
-  // Few rows (head dimension 64): workgroups of four waves, one per SIMD, where that leaves compute units without one; the time is that of one
-  // wave's block then, and two on a SIMD share it.  us of the query side's and the key side's gradient, forward and dV, eight waves and four:
-  // 16 workgroups of four (4 slices of 1000 rows, m 256) 16.0 15.2 11.0 11.1, 13.9 12.7 10.1 9.9; 128 (8 of 4096) 17.4 16.6 11.8 12.1, 15.8 14.7 11.1 11.3, with
-  // m 512 23.9 22.6 18.1 17.9, 20.3 18.7 16.4 15.7; 240 (20 of 3000) 18.8 18.0 13.0 13.0, 18.2 16.6 13.0 12.8; 256 (32 of 2000) 19.0 18.3 13.1 13.1, 19.2 17.5
-  // 13.7 13.2.  (Instances with the LayerNorm output stage or levels above 6 have eight.)
+  // Few rows (head dimension 64): workgroups of four waves, one per SIMD, where eight waves leave compute units without one and four give each one at
+  // most; the time is that of one wave's block then, and two on a SIMD share it.  us of the query side's and the key side's gradient, forward and dV,
+  // eight waves and four: 16 workgroups of four (4 slices of 1000 rows, m 256) 16.0 15.2 11.0 11.1, 13.9 12.7 10.1 9.9; 128 (8 of 4096) 17.4 16.6 11.8 12.1,
+  // 15.8 14.7 11.1 11.3, with m 512 23.9 22.6 18.1 17.9, 20.3 18.7 16.4 15.7.  Of forward and backward: 200 workgroups (8 of 6400, m 128, 256, 512) 97.1
+  // 114.8 147.1, 92.3 110.0 136.8; 240 (20 of 3000) 102.4 121.6 156.0, 98.7 118.7 148.6; 250 (125 of 500, m 256, 512) 128.1 171.4, 127.7 168.3; 256 (8 of 8192)
+  // 123.0 152.5, 119.4 143.5, (64 of 1000, m 256) 127.4, 126.8, (128 of 320, m 256, 512) 115.3 158.0, 116.8 155.2.  (Instances with the LayerNorm output stage
+  // or levels above 6 have eight.)
   // Not where eight waves hold all rows of a slice and four would too: as many workgroups, and half the threads to stage the operands.  us of forward and
   // backward, eight waves and four: 1 slice of 200 rows, m 256 66.3, 69.5; 8 of 256, m 1024 131.5, 141.8; 32 of 128, m 256 74.6, 77.8, of 256, m 128 67.6, 69.0;
   // 192 of 200, m 256 117.0, 119.1, m 512 156.3, 161.3; but 8 of 320, m 256 82.0, 75.9; 96 of 320 111.6, 109.3.
   p.rowWaves = kWavesApply;
-  if (c.d == 64 && c.L <= kTileL && !(c.flags & WERSA_FLAG_LAYERNORM) && blocks > 4 && (int64_t)slices * ((blocks + 3) / 4) <= 192) p.rowWaves = 4;
+  if (c.d == 64 && c.L <= kTileL && !(c.flags & WERSA_FLAG_LAYERNORM) && blocks > 4 && (int64_t)slices * ((blocks + 3) / 4) <= 256) p.rowWaves = 4;
   p.rowGroups = c.d == 64 ? (blocks + p.rowWaves - 1) / p.rowWaves : (c.n + kWideRows - 1) / kWideRows;
   // One resident workgroup per compute unit (the operand arrays fill most of the LDS): at most
   // 256 workgroups in total, so that no second, mostly empty round follows the first.

@@ -35,7 +35,7 @@ def test_gate_has_a_launch_of_its_own_where_many_workgroups_would_form_it_again(
 
 
 @pytest.mark.parametrize("slices,n,waves", [
-    (1, 1, 8), (1, 256, 8), (1, 257, 4), (8, 200, 8), (96, 256, 8), (96, 257, 4), (96, 512, 4), (192, 256, 8), (500, 64, 8), (500, 320, 8), (8, 65536, 8)])
+    (1, 1, 8), (1, 256, 8), (1, 257, 4), (8, 200, 8), (96, 256, 8), (96, 257, 4), (96, 512, 4), (192, 256, 8), (20, 3000, 4), (128, 320, 4), (1, 65536, 4), (85, 769, 8), (129, 320, 8), (8, 8193, 8), (500, 64, 8), (500, 320, 8), (8, 65536, 8)])
 def test_rows_kernels_have_four_waves_where_that_gives_more_workgroups(slices, n, waves):
     for what, names in (("forward", ["rows_kernel"]), ("backward", ["masked_rows_kernel"] * 2 + ["rows_kernel"])):
         found = [(name.split("<")[0], threads) for name, _, threads, _ in kernels(what, slices, n, 64, 256) if "rows_kernel<" in name]
