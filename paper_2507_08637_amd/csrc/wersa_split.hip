@@ -319,21 +319,28 @@ struct Dims {
 };
 
 // ------------------------------------------------------------------------------------
-// Column sums of Q (and, for L > 6, of K) per chunk of rows; workgroups past `chunks` of slice 0 carry the
-// per-call constants and pack Omega.  Grid (chunks + extra, slices, tensors).
+// Column sums of Q (and, for L > 6, of K) per chunk of rows; the first workgroups (om.blocks) carry the per-call constants and pack Omega.
+// Grid (om.blocks + chunks * slices, 1, tensors): every workgroup has something to do.  (With the packing ones beside the chunks of every slice, idle but
+// for slice 0, a multiple of eight to a slice put all chunks on the same few of the eight dies: 800 slices of 4720 tokens, d 64, m 48, float32, three
+// chunks and five others, 269 us, 202 now; 893 of 1163, d 48, m 176 104, 58.)  Far fewer than 2^24 workgroups in what fits the card.
 // ------------------------------------------------------------------------------------
-// What no kernel writes of `saved` (the ends of sections that are rounded up, the feature tile past the last one) is cleared by one more
-// workgroup of the first launch, so that two calls on the same inputs leave the same bytes, whatever was in the memory before.
+// What no kernel writes of `saved` (the ends of sections that are rounded up, the feature tile past the last one, the coefficients of
+// levels that are not there) is cleared by the first launch, so that two calls on the same inputs leave the same bytes, whatever was in the
+// memory before: by one more of its packing workgroups, and a slice's coefficients by the workgroup of its first chunk.
+// (A loop for every section would wait for the stores of the one before: 25 slices of 275 tokens, d 48, m 144, bf16 9.4 us, 7.1.)
 struct Gaps {
-  float *at[14];
-  int len[14];
+  float *end[12];   // less than 64 values each
+  int len[12];
+  float *tile[2];
+  int tile_len[2];
+  float *coef;
 };
 Gaps gaps_of(const wersa_desc &c, const SavedLayout &sv, float *saved, int64_t tileA, int64_t tileB, const SplitSizes &z) {
   Gaps g{};
   int i = 0;
   const int64_t sl = (int64_t)c.B * c.H;
   auto end = [&](int64_t off, int64_t used) {   // from the last value to the next multiple of 64
-    g.at[i] = saved + off + used;
+    g.end[i] = saved + off + used;
     g.len[i++] = (int)((64 - used % 64) % 64);
   };
   end(sv.S, sl * c.m * c.d);
@@ -343,14 +350,14 @@ Gaps gaps_of(const wersa_desc &c, const SavedLayout &sv, float *saved, int64_t t
   end(sv.F, sl * (c.L + 1));
   end(sv.D, sl * c.n);
   end(sv.scalars, 4);
+  end(sv.coef, sl * kCoefStride);
   if (c.L > kTileL)
     for (const int64_t off : {sv.tileQ, sv.tileK, sv.addQ, sv.addK}) end(off, sl * ((c.n + 63) / 64) * c.d);
-  g.at[i] = saved + sv.coef;   // (all of it: the gate, which comes later, writes as many levels as there are)
-  g.len[i++] = (int)((sl * kCoefStride + 63) / 64 * 64);
-  g.at[i] = saved + sv.OA + z.OA - tileA;
-  g.len[i++] = (int)((64 - z.OA % 64) % 64 + tileA);
-  g.at[i] = saved + sv.OB + z.OB - tileB;
-  g.len[i++] = (int)((64 - z.OB % 64) % 64 + tileB);
+  g.coef = saved + sv.coef;   // (the gate, which comes later, writes as many levels as there are)
+  g.tile[0] = saved + sv.OA + z.OA - tileA;
+  g.tile_len[0] = (int)((64 - z.OA % 64) % 64 + tileA);
+  g.tile[1] = saved + sv.OB + z.OB - tileB;
+  g.tile_len[1] = (int)((64 - z.OB % 64) % 64 + tileB);
   return g;
 }
 
@@ -367,9 +374,13 @@ struct OmegaPack {
 template <typename T>
 __device__ void omega_pack_body(const OmegaPack<T> &o, const Dims &s, int block) {
   if (block == o.blocks - 1) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll
-    for (int g = 0; g < 14; ++g)
-      for (int e = threadIdx.x; e < o.gaps.len[g]; e += 256) o.gaps.at[g][e] = 0.f;
+    for (int g = 0; g < 12; ++g)
+      if (g % 4 == wave && lane < o.gaps.len[g]) o.gaps.end[g][lane] = 0.f;
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+      for (int e = threadIdx.x; e < o.gaps.tile_len[g]; e += 256) o.gaps.tile[g][e] = 0.f;
     return;
   }
   if (block == 0 && threadIdx.x == 0) {
@@ -411,11 +422,12 @@ __device__ void omega_pack_body(const OmegaPack<T> &o, const Dims &s, int block)
 template <typename T>
 __global__ __launch_bounds__(256) void pool_kernel(const T *q, const T *k, View v, Dims s, int vec, int rows_per_chunk,
                                                   int chunks, float *partq, float *partk, OmegaPack<T> om) {
-  if ((int)blockIdx.x >= chunks) {
-    if (blockIdx.y == 0 && blockIdx.z == 0) omega_pack_body(om, s, blockIdx.x - chunks);
+  if ((int)blockIdx.x < om.blocks) {
+    if (blockIdx.z == 0) omega_pack_body(om, s, blockIdx.x);
     return;
   }
-  const int slice = blockIdx.y, chunk = blockIdx.x;
+  const int slice = (blockIdx.x - om.blocks) / chunks, chunk = (blockIdx.x - om.blocks) % chunks;
+  if (chunk == 0 && blockIdx.z == 0 && threadIdx.x < kCoefStride) om.gaps.coef[slice * kCoefStride + threadIdx.x] = 0.f;
   const int cpr = s.d / 8, rpi = 256 / cpr;   // 8 columns per thread, rpi rows at a time
   const int t0 = chunk * rows_per_chunk, t1 = min(s.n, t0 + rows_per_chunk);
   const int cc = threadIdx.x % cpr, rr = threadIdx.x / cpr;
@@ -1878,7 +1890,7 @@ wersa_status forward_t(const wersa_desc &c, const T *q, const T *k, const T *v, 
   const int pieces = p.matrices * p.s.mt * 64 * (p.KS + 2 * p.CT);
   const OmegaPack<T> om{omega, sigma, c.bw_floor, scalars, OA, OB, p.matrices, p.KS, p.CT, PT, (pieces + 255) / 256 + 1,
                         gaps_of(c, sv, saved, tile_floats(p.KS * PT), tile_floats(2 * p.CT * PT), split_sizes(c))};
-  WERSA_STAGE("split_pool", st, pool_kernel<T><<<dim3(p.chunks + om.blocks, slices, deep ? 2 : 1), 256, 0, st>>>(
+  WERSA_STAGE("split_pool", st, pool_kernel<T><<<dim3(om.blocks + p.chunks * slices, 1, deep ? 2 : 1), 256, 0, st>>>(
       q, k, tv, p.s, vec, p.rows_per_chunk, p.chunks, qpart, kpart, om));
   const bool pooled_gate = (c.flags & WERSA_FLAG_POOLED_GATE) != 0;
   GateFwdArgs gate{qpart, p.chunks, c.n, c.d, c.L, c.H, gate_w, gate_b, scale_w, saved + sv.qbar, saved + sv.s, saved + sv.F, coef,

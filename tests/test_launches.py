@@ -46,3 +46,13 @@ def test_rows_kernels_have_four_waves_where_that_gives_more_workgroups(slices, n
 def test_rows_kernels_with_deep_levels_or_layernorm_have_eight_waves(kw):
     for what in ("forward", "backward"):
         assert {threads for name, _, threads, _ in kernels(what, 4, 1000, 64, 256, **kw) if "rows_kernel<" in name} == {512}
+
+
+@pytest.mark.parametrize("slices,n,d,m,L,chunks", [
+    (800, 4720, 64, 48, 2, 3), (893, 1163, 48, 176, 5, 3), (1, 1024, 64, 64, 3, 16), (1, 40, 16, 16, 1, 1), (3, 1000, 32, 64, 8, 16)])
+def test_every_workgroup_of_the_pooling_launch_has_something_to_do(slices, n, d, m, L, chunks):
+    """The chunks of all slices, the packing of Omega once (64 pieces per 32 features and operand tile, 256 to a workgroup) and one that clears."""
+    dh = next(x for x in (16, 32, 64, 128) if d <= x)
+    pieces = (m + 31) // 32 * 64 * (dh // 16 + 2 * max(1, dh // 32))
+    grid, = (grid for name, grid, _, _ in kernels("forward", slices, n, d, m, L, bf16=False) if name.startswith("pool_kernel"))
+    assert grid == ((pieces + 255) // 256 + 1 + chunks * slices, 1, 2 if L > 6 else 1)
