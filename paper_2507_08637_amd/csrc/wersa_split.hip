@@ -1768,21 +1768,31 @@ Ws ws_of(const wersa_desc &c, const Plan &p, int bwd, bool keep, float *base) {
 }
 
 // Eight token tiles for a workgroup of the contraction at least, four or two where compute units are left without one: the chain of tiles is
-// the kernel's time then, and up to 24 shares the kernel that adds them does not lose it again (SHORT in sum_shares).
-// us of the contraction and the sum, at eight, four and two tiles: float32, one slice of 1024 tokens, d 64, m 64 8.3 5.1, 6.0 5.5, 4.5 8.2 (32 shares);
-// 4 of 1000, d 128, m 256 34.9 8.8, 20.9 8.3, 14.1 9.0; 16 of 1000, d 64, m 256 19.3 6.6, 13.2 6.9, 11.5 7.6; 2 of 1500, d 32, m 512 12.0 4.5, 8.0 4.8,
-// 6.0 6.2; 8 of 1500, d 64, m 128 12.3 5.7, 9.3 7.9, 9.5 7.8.  What fits wersa_forward_static's scratch, with Q_F and K_F or without, still does.
+// the kernel's time then, and up to 24 or 16 shares the kernel that adds them does not lose it again (SHORT in sum_shares).  No more workgroups than
+// compute units: at head dimensions 64 and 128 one is all that a compute unit holds, and a second round costs what the shorter chain gave.  us of
+// forward and backward with the coarser split and the finer, workgroups of each in brackets: 160 slices of 185 tokens, d 64, m 64, float32 (160, 320) 122.2,
+// 134.1; 54 of 961, d 64, m 128 (216, 432) 223.9, 244.3; 120 of 382, d 96, m 128, bf16 (240, 360) 313.8, 330.9; but 13 of 490, d 64, m 128, float32
+// (26, 52) 108.9, 99.1; 2 of 217, d 96, m 64, bf16 (2, 4) 128.7, 111.7; 26 of 715, d 32, m 32, float32 (78, 156) 79.7, 73.7.  Two tiles with 16 shares and with
+// more: 5 of 986, d 96, m 96, bf16 (16 shares) 142.9, 139.0; 8 of 460, d 48, m 128, float32 (16) 93.1, 91.6; 3 of 893, d 48, m 64 (28) 76.8, 79.1; 10 of 2950,
+// d 96, m 128 (47) 204.6, 244.7.
+// Below head dimension 128 not to fewer than eight shares from more than one, which are added one after the other (16 of 182 tokens, d 48, m 32, bf16, two
+// shares, four and six 69.9, 73.1, 73.1), and not with head dimension 16 or one-term operands, whose tiles are short: 8 to 4 there 9 slices of 3940, d 16, m 64
+// 78.9, 91.9; 2 of 2882, d 32, m 64, bf16 70.4, 81.0; at best 5 us less (1 of 589, d 32, m 128).
+// us of the contraction and the sum, at eight, four and two tiles: one slice of 1024 tokens, d 64, m 64, float32 8.3 5.1, 6.0 5.5, 4.5 8.2 (32 shares);
+// 4 of 1000, d 128, m 256 34.9 8.8, 20.9 8.3, 14.1 9.0; 16 of 1000, d 64, m 256 19.3 6.6, 13.2 6.9, 11.5 7.6.
+// What fits wersa_forward_static's scratch, with Q_F and K_F or without, still does.
 Plan plan_of(const wersa_desc &c) {
-  Plan p = plan_least(c, 8);
+  const Plan whole = plan_least(c, 8);
+  if (whole.PT == 1 || whole.DH == 16) return whole;
   auto fits = [&](const Plan &q, bool keep) { return (size_t)ws_of(c, q, 0, keep, nullptr).total * sizeof(float) <= kStaticScratchBytes; };
-  for (int least = 4; least >= 2; least /= 2) {
-    if ((int64_t)c.B * c.H * (p.s.mt / p.FW) * p.splits >= 256) break;
+  Plan p = whole;
+  for (int least = 4; least >= (p.DH >= 64 ? 2 : 4); least /= 2) {
     const Plan q = plan_least(c, least);
-    if (q.shares > 24) break;
+    if ((int64_t)c.B * c.H * (q.s.mt / q.FW) * q.splits > 256 || q.shares > (least == 4 ? 24 : 16)) break;
     if (!fits(q, false) && (fits(p, false) || (fits(p, true) && !fits(q, true)))) break;
     p = q;
   }
-  return p;
+  return p.DH < 128 && p.shares < 8 && whole.shares > 1 ? whole : p;
 }
 
 // Where Q_F and K_F, packed (6 bytes per element each), live between the forward and the backward.  In `saved` where the rest

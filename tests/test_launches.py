@@ -56,3 +56,22 @@ def test_every_workgroup_of_the_pooling_launch_has_something_to_do(slices, n, d,
     pieces = (m + 31) // 32 * 64 * (dh // 16 + 2 * max(1, dh // 32))
     grid, = (grid for name, grid, _, _ in kernels("forward", slices, n, d, m, L, bf16=False) if name.startswith("pool_kernel"))
     assert grid == ((pieces + 255) // 256 + 1 + chunks * slices, 1, 2 if L > 6 else 1)
+
+
+@pytest.mark.parametrize("slices,n,d,m,bf16,splits", [
+    (1, 1024, 64, 64, False, 8),      # four token tiles: sixteen shares (two: 32)
+    (4, 1000, 128, 256, False, 16),   # two tiles
+    (13, 490, 64, 128, False, 8),     # two tiles: sixteen shares
+    (160, 185, 64, 64, False, 1),     # four tiles would be 320 workgroups
+    (120, 382, 96, 128, True, 2),     # 360
+    (54, 961, 64, 128, False, 4),     # 432
+    (26, 715, 32, 32, False, 6),      # head dimension 32: four at least
+    (16, 182, 48, 32, True, 1),       # six shares from two
+    (6, 89, 48, 384, False, 1),       # four shares from two
+    (38, 87, 64, 256, False, 2),      # two shares from one tile's worth
+    (9, 3940, 16, 64, True, 16),      # one-term operands: eight at least
+    (2, 2882, 32, 64, True, 12)])
+def test_contraction_is_split_finer_within_one_round(slices, n, d, m, bf16, splits):
+    for what in ("forward", "backward"):
+        (name, grid, _, _), = (k for k in kernels(what, slices, n, d, m, bf16=bf16) if k[0].startswith("contract_kernel"))
+        assert grid[0] == splits and grid[2] == slices
