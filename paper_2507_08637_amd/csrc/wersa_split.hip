@@ -1906,8 +1906,10 @@ wersa_status forward_t(const wersa_desc &c, const T *q, const T *k, const T *v, 
   GateFwdArgs gate{qpart, p.chunks, c.n, c.d, c.L, c.H, gate_w, gate_b, scale_w, saved + sv.qbar, saved + sv.s, saved + sv.F, coef,
                    PooledLayout{(int64_t)c.H * p.chunks * c.d, (int64_t)p.chunks * c.d, c.d}, nullptr, 0, AmaxLayout{0, 0, 0, 1}, scalars};
   // One round of packing workgroups: they form the gate themselves (one slice of 1024 tokens, d 64, m 64: 34.0 -> 31.4 us per call, 8 of 1500,
-  // d 32, m 512: 54.3 -> 52.9); with more rounds each would wait for it again.
-  const bool fused = !deep && !pooled_gate && p.chunks <= kGatePrologueChunks && (int64_t)p.groups * slices * 3 <= 2048;
+  // d 32, m 512: 54.3 -> 52.9); with more rounds each would wait for it again (2460 workgroups, d 64 268.3, 271.7).  Above head dimension 64 a workgroup waits
+  // for a round of loads per four chunks and 64 columns, and the launch of its own is the shorter one from nine chunks on (4 slices of 276
+  // tokens, d 128, m 224, five chunks 62.3, 60.2; 4 of 786, m 160, thirteen 70.4, 70.9; 6 of 2190, m 160, 35 chunks 92.5, 95.9).
+  const bool fused = !deep && !pooled_gate && p.chunks <= (DH == 128 ? 8 : kGatePrologueChunks) && (int64_t)p.groups * slices * 3 <= 2048;
   if (!fused)
     WERSA_STAGE("gate_fwd_kernel", st, gate_fwd_kernel<<<slices, kGateFwdThreads, 0, st>>>(
         qpart, p.chunks, c.n, c.d, c.L, c.H, gate_w, gate_b, scale_w, gate.qbar, gate.s_out, gate.F_out, coef, pooled_gate ? 1 : 0, gate.ql, nullptr, 0,

@@ -75,3 +75,12 @@ def test_contraction_is_split_finer_within_one_round(slices, n, d, m, bf16, spli
     for what in ("forward", "backward"):
         (name, grid, _, _), = (k for k in kernels(what, slices, n, d, m, bf16=bf16) if k[0].startswith("contract_kernel"))
         assert grid[0] == splits and grid[2] == slices
+
+
+@pytest.mark.parametrize("slices,n,d,apart", [
+    (1, 1024, 64, False), (1, 131072, 64, True), (10, 4000, 32, False), (22, 1984, 64, False), (22, 1985, 64, True), (22, 192, 128, False), (4, 512, 128, False),
+    (4, 513, 128, True), (6, 2190, 96, True), (85, 256, 128, False), (86, 256, 128, True)])
+def test_gate_of_the_split_path_has_a_launch_of_its_own(slices, n, d, apart):
+    """More than 2048 packing workgroups of 4096 elements, or above head dimension 64 more than eight chunks of partial sums."""
+    names = [k[0] for k in kernels("forward", slices, n, d, 96, L=3, bf16=False)]
+    assert ("gate_fwd_kernel" in names) == apart
