@@ -43,15 +43,16 @@ class _WersaAttention(torch.autograd.Function):
         out, saved = binding.wersa_forward(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps=eps,
                                            bw_floor=bw_floor)
         ctx.save_for_backward(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, out, saved)
-        ctx.cfg = (L, eps, bw_floor)
+        ctx.cfg = (L, eps, bw_floor, q.stride())
         return out
 
     @staticmethod
     def backward(ctx, dout):
         q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, out, saved = ctx.saved_tensors
-        L, eps, bw_floor = ctx.cfg
-        if dout.stride() != q.stride():
-            dout = torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device).copy_(dout)
+        L, eps, bw_floor, strides = ctx.cfg
+        # (saved-tensor hooks may have made them dense; `saved` is laid out for the path that the forward's strides select)
+        q, k, v, out, dout = (x if x.stride() == strides else torch.empty_strided(x.shape, strides, dtype=x.dtype, device=x.device).copy_(x)
+                              for x in (q, k, v, out, dout))
         g = binding.wersa_backward(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, out, dout, saved, L,
                                    eps=eps, bw_floor=bw_floor)
         return (g["dq"], g["dk"], g["dv"], None, g["dsigma"], g["dgate_w"], g["dgate_b"], g["dscale_w"],

@@ -165,3 +165,25 @@ def test_traced_module_makes_the_call(monkeypatch):
     assert torch.equal(out, forward(*qkv, *params, L)[0])
     grads = torch.autograd.grad(out, qkv, torch.ones_like(out))
     assert [float(g.mean()) for g in grads] == [0.5, 1.0, 1.5]
+
+
+@pytest.mark.parametrize("hook", ["contiguous", "dense"])
+@pytest.mark.parametrize("layout", ["bnhd", "fused", "odd"])
+def test_node_in_python_goes_back_to_the_strides_of_the_forward(monkeypatch, layout, hook):
+    """The node that a trace records: tensors that come back in another layout may select another path than the one that laid saved out."""
+    seen = []
+
+    def forward(q, *a, **kw):
+        return torch.empty_strided(q.shape, q.stride(), dtype=q.dtype).zero_(), torch.zeros(1)
+
+    def backward(q, k, v, omega, sigma, gate_w, gate_b, scale_w, out, dout, saved, L, **kw):
+        seen.extend((q, k, v, out, dout))
+        return dict(dq=q, dk=k, dv=v, dsigma=sigma, dgate_w=gate_w, dgate_b=gate_b, dscale_w=scale_w)
+
+    monkeypatch.setattr(binding, "wersa_forward", forward)
+    monkeypatch.setattr(binding, "wersa_backward", backward)
+    qkv, params = tensors(layout)
+    with torch.autograd.graph.saved_tensors_hooks(HOOKS[hook], lambda x: x):
+        out = autograd._WersaAttention.apply(*qkv, *params, L, 1e-6, 1e-6)
+    grads = torch.autograd.grad(out, qkv, torch.ones(B, H, N, 1, dtype=out.dtype).expand(out.shape))
+    assert [x.stride() for x in seen] == [qkv[0].stride()] * 5 and all(torch.equal(g, x) for g, x in zip(grads, qkv))
