@@ -9,26 +9,30 @@ flow to q, k, v, sigma, gate_w, gate_b, scale_w (omega_rf is a fixed random matr
 block, to x and the four weight matrices (float32 gradients cast to the weights' dtype).
 """
 import ctypes
+import warnings
 
 import torch
 
 from . import binding
 
 
-_node = None
+_node = None   # (False: it does not load)
 
 
 def _load_node():
     """The extension that holds the attention core's node of the autograd graph (csrc/wersa_torch.cpp), on the library that the
-    binding has loaded."""
+    binding has loaded.  It is bound to one version of torch where the library is not: without it the node in Python makes the same
+    calls, and a warning says that its host path is the slower one."""
     global _node
     if _node is None:
         lib = binding.load_library()
         try:
             from . import _wersa_torch as node
         except ImportError as e:
-            raise RuntimeError("the autograd extension _wersa_torch.so is missing or does not load: build it with "
-                               "`python -m paper_2507_08637_amd.build` (there is no fallback path)") from e
+            warnings.warn("the autograd extension _wersa_torch.so is missing or does not load, training steps take up to 100 us longer on "
+                          f"the host: build it with `python -m paper_2507_08637_amd.build` ({e})", RuntimeWarning, stacklevel=3)
+            _node = False
+            return _node
         node.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.wersa_forward, lib.wersa_backward, lib.wersa_workspace_bytes,
                                                                     lib.wersa_saved_bytes, lib.wersa_selected_path)))
         _node = node
@@ -36,7 +40,8 @@ def _load_node():
 
 
 class _WersaAttention(torch.autograd.Function):
-    """The same node in Python, for torch.jit.trace: the tracer records its call, and of the one in C++ only the allocation of the output."""
+    """The same node in Python, for torch.jit.trace (the tracer records its call, and of the one in C++ only the allocation of the output) and where
+    the extension does not load."""
 
     @staticmethod
     def forward(ctx, q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps, bw_floor):
@@ -60,10 +65,11 @@ class _WersaAttention(torch.autograd.Function):
 
 
 def wersa_attention(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps=1e-6, bw_floor=1e-6):
-    if torch.jit.is_tracing():
+    node = _load_node() if _node is None else _node
+    if not node or torch.jit.is_tracing():
         return _WersaAttention.apply(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps, bw_floor)
     desc, saved_bytes, workspace = binding.checked_desc(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, L, eps, bw_floor, 0)
-    return (_node or _load_node()).attention(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, bytes(desc), saved_bytes, workspace)
+    return node.attention(q, k, v, omega_rf, sigma, gate_w, gate_b, scale_w, bytes(desc), saved_bytes, workspace)
 
 
 class _WersaBlock(torch.autograd.Function):

@@ -1,6 +1,7 @@
 """The attention core's node of the autograd graph on the CPU, its library calls replaced by entry points that note what they are given:
 what a backward is told about tensors that come back from saved-tensor hooks in another layout."""
 import ctypes
+import warnings
 from contextlib import contextmanager
 
 import pytest
@@ -187,3 +188,33 @@ def test_node_in_python_goes_back_to_the_strides_of_the_forward(monkeypatch, lay
         out = autograd._WersaAttention.apply(*qkv, *params, L, 1e-6, 1e-6)
     grads = torch.autograd.grad(out, qkv, torch.ones(B, H, N, 1, dtype=out.dtype).expand(out.shape))
     assert [x.stride() for x in seen] == [qkv[0].stride()] * 5 and all(torch.equal(g, x) for g, x in zip(grads, qkv))
+
+
+def test_without_the_extension_the_node_in_python_makes_the_calls(monkeypatch):
+    """libwersa.so alone suffices; one warning."""
+    import sys
+    import paper_2507_08637_amd as package
+    made = []
+
+    def forward(q, k, v, *a, **kw):
+        made.append("forward")
+        return q + k + v, torch.zeros(1)
+
+    def backward(q, k, v, omega, sigma, gate_w, gate_b, scale_w, out, dout, saved, L, **kw):
+        made.append("backward")
+        return dict(dq=dout, dk=2 * dout, dv=3 * dout, dsigma=sigma, dgate_w=gate_w, dgate_b=gate_b, dscale_w=scale_w)
+
+    monkeypatch.delattr(package, "_wersa_torch", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2507_08637_amd._wersa_torch", None)
+    monkeypatch.setattr(autograd, "_node", None)
+    monkeypatch.setattr(binding, "wersa_forward", forward)
+    monkeypatch.setattr(binding, "wersa_backward", backward)
+    qkv, params = tensors("bhnd")
+    with pytest.warns(RuntimeWarning, match="_wersa_torch.so"):
+        out = autograd.wersa_attention(*qkv, *params, L)
+    grads = torch.autograd.grad(out, qkv, torch.ones_like(out))
+    assert [float(g.float().mean()) for g in grads] == [1, 2, 3]
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        autograd.wersa_attention(*qkv, *params, L)
+    assert made == ["forward", "backward", "forward"]
